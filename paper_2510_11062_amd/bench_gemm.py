@@ -1,17 +1,17 @@
-"""The tile loops of the head kernels as plain GEMMs beside the vendor GEMM (hipBLASLt through torch.mm)
-on the shapes the library launches, plus the two-workgroups-per-CU layout that was tried and rejected.
+"""The tile loop of the bf16 head kernels as plain GEMMs beside the vendor GEMM (hipBLASLt through torch.mm) on the
+shapes the library launches.
 
     python -m paper_2510_11062_amd.bench_gemm
 
 One JSON line per case: variant, shape, TFLOP/s, shader clock.  Shapes (bf16, fp32 accumulate):
-  forward / dZ   vocabulary x tokens of one launch x H          151808 x 16384 x 2048   (short k)
-  dHidden        tokens x H x vocabulary                         16384 x 2048 x 151936   (long k)
-  dW             vocabulary x H x tokens of a super-chunk, both operands k-major  151808 x 2048 x 32768
+  logits         vocabulary x tokens of one launch x H          151808 x 16384 x 2048   (short k)
+  dHidden        H x tokens x vocabulary                         2048 x 16384 x 151936   (long k)
+  dW             H x vocabulary x tokens of a super-chunk, both operands k-major  2048 x 151808 x 32768
   a square case  8192^3
-nt4 / km4 are the same loops with 4 wavefronts of 128 x 128 per workgroup instead of 8 of 64 x 128: the
-library uses them where k is long (dHidden, dW) and the 8-wavefront form where k = H (forward).
-The probe (csrc/gemm_probe.hip, built by build.py) runs the library's own loop without any epilogue;
-torch.mm is timed with the output written.  A measurement aid: nothing in the library calls this.
+The suffix of a variant is the wavefront grid: 8 = 4 x 2, t = 2 x 4, 4 = 2 x 2; the library uses ntt for the logits, nt4
+for dHidden and km8 for dW; mx4 is dHidden on untransposed weights.  The probe (csrc/gemm_probe.hip, built by
+build.py) runs the library's own loop without any epilogue; torch.mm is timed with the output written.  A measurement
+aid: nothing in the library calls this.
 """
 from __future__ import annotations
 
@@ -27,15 +27,16 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 PROBE = os.path.join(PKG, "gemm_probe")
 
 SHAPES = [
-    ("forward / dZ (short k)", "nt", 151808, 16384, 2048),
-    ("forward / dZ (short k), 4 wavefronts", "nt4", 151808, 16384, 2048),
-    ("dHidden (long k)", "nt", 16384, 2048, 151936),
-    ("dHidden (long k), 4 wavefronts", "nt4", 16384, 2048, 151936),
-    ("dW (k-major operands)", "km", 151808, 2048, 32768),
-    ("dW (k-major operands), 4 wavefronts", "km4", 151808, 2048, 32768),
-    ("square", "nt", 8192, 8192, 8192),
-    ("microbenchmark shape", "nt", 37888, 32768, 1984),
-    ("microbenchmark shape, two workgroups per CU (rejected layout)", "wg2", 37888, 32768, 1952),
+    ("logits (short k)", "ntt", 151808, 16384, 2048),
+    ("logits (short k)", "nt8", 151808, 16384, 2048),
+    ("logits (short k), 4 wavefronts", "nt4", 151808, 16384, 2048),
+    ("dHidden (long k), 4 wavefronts", "nt4", 2048, 16384, 151936),
+    ("dHidden (long k)", "nt8", 2048, 16384, 151936),
+    ("dHidden (long k), untransposed weights", "mx4", 2048, 16384, 151936),
+    ("dW (k-major operands)", "km8", 2048, 151808, 32768),
+    ("dW (k-major operands)", "kmt", 2048, 151808, 32768),
+    ("dW (k-major operands), 4 wavefronts", "km4", 2048, 151808, 32768),
+    ("square", "nt8", 8192, 8192, 8192),
 ]
 
 
@@ -80,7 +81,7 @@ def main():
         sys.exit(2)
     for label, variant, M, N, K in SHAPES:
         print(json.dumps(probe(label, variant, M, N, K)), flush=True)
-        if variant in ("nt", "km"):     # one vendor line per shape
+        if variant in ("nt8", "km8"):     # one vendor line per shape
             print(json.dumps(vendor(label, variant, M, N, K)), flush=True)
 
 

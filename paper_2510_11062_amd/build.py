@@ -12,7 +12,8 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libat_grpo.so")
 CLIENT = os.path.join(PKG, "abi_client")
 PROBE = os.path.join(PKG, "gemm_probe")
-SOURCES = ["api.hip", "group_advantage.hip", "token_kernels.hip", "head_kernels.hip", "optimizer.hip"]
+SOURCES = ["api.hip", "group_advantage.hip", "token_kernels.hip", "head_kernels.hip", "head_bf16.hip",
+           "optimizer.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -1,0 +1,411 @@
+// Workgroup-tile contraction of bf16 operands on the gfx950 matrix cores.
+//
+// One workgroup produces a 256 x 256 fp32 tile
+//   C[a, b] = sum_k A[a, k] * B[b, k]
+// where each operand may be stored with its rows contiguous along k or k-major (rows of k, contiguous along
+// a or b).  Its wavefronts share the tile as a Grid16 (below).  k is consumed in steps of 64.
+//
+// MFMA shape.  v_mfma_f32_16x16x32_bf16, not 32x32x16: both deliver the same peak, but these kernels are bound by
+// power, and per multiply-add the 16x16x32 form moves half as many accumulator words through the register file.
+// The same loop with 32x32x16 sustains 1330-1370 TFLOP/s at 1.53 GHz (power-limited), with 16x16x32
+// 1520-1560 at 1.75-1.85 GHz (256 x 256 tiles, k = 2048 .. 151936).
+//
+// Data path: global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4, 16 bytes per lane) into a ring of five
+// 32 KiB slots (one operand panel each: all 160 KiB of a compute unit); LDS -> registers with ds_read_b128 (operands
+// contiguous along k) or the transposing ds_read_b64_tr_b16 (k-major operands), fragments fetched one 32-wide sub-step
+// ahead of the MFMAs that consume them.  The direct loads go through inline asm: the compiler would otherwise make
+// every later LDS read wait for all outstanding direct loads.  Their completion is enforced by hand with s_waitcnt vmcnt
+// in front of the one workgroup barrier per k-step.  No value that the k loop uses may come from a load the compiler
+// has to wait for inside the loop (a spilled register, say): such a wait would drain the direct loads too.
+//
+// Instruction order: a wavefront that issues a burst of LDS reads or direct loads keeps its SIMD's matrix pipe idle for
+// the length of the burst.  The loop body is therefore written out as a fixed sequence, pinned with scheduling barriers,
+// in which an MFMA is followed by at most one fragment read and one direct load.  Addresses cost no vector instructions
+// in the loop: global addresses are a scalar base plus a lane offset that does not change, LDS addresses a lane offset
+// per slot plus an immediate.
+//
+// Accumulator layout (per lane, block (i, j), register r = 0..3):
+//   A row of the tile = wm * kRowsA + i * 16 + 4 * (lane / 16) + r
+//   B row of the tile = wn * kRowsB + j * 16 + lane % 16
+// i.e. four consecutive A rows per lane: A is the operand whose index is contiguous in the output.
+#pragma once
+
+#include "common.hpp"
+
+namespace atg {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16v4 __attribute__((__vector_size__(4 * sizeof(__bf16))));
+
+constexpr int kTile16 = 256;                      // rows of each operand per tile
+constexpr int kStepK = 64;                        // k per step
+constexpr int kRingSlots = 5;
+constexpr int kRingSlot = kTile16 * kStepK * 2;   // 32 KiB: one operand panel of one step
+constexpr int kRingBytes = kRingSlots * kRingSlot;
+
+// How the wavefronts of a workgroup share the 256 x 256 tile: WA x WB of them, each owning (256 / WA) x (256 / WB).
+//   Grid16<4, 2> / <2, 4>  8 wavefronts, two per SIMD (128 accumulator registers): one covers part of the other's
+//                          per-tile prologue and epilogue; used where the k loop is short (k = H)
+//   Grid16<2, 2>           4 wavefronts, one per SIMD (256 accumulator registers): a third fewer LDS reads per MFMA and
+//                          half as many wavefronts at each barrier; 4 % faster on long k loops
+template <int WA, int WB>
+struct Grid16 {
+  static constexpr int kWavesA = WA, kWavesB = WB, kThreads = WA * WB * 64;
+  static constexpr int kRowsA = kTile16 / WA, kRowsB = kTile16 / WB;   // rows of a wavefront's sub-tile
+  static constexpr int kIB = kRowsA / 16, kJB = kRowsB / 16;           // accumulator blocks of a wavefront
+  static constexpr int kLoads = 32 / (WA * WB);                        // direct loads per operand, step and wavefront
+  static constexpr int kMm = kIB * kJB, kRd = kIB + kJB;               // MFMAs and fragment reads per sub-step
+  // a fragment read follows every kRdEvery-th MFMA: the last one must be early enough to land before the sub-step ends
+  // (4 wavefronts: every 3rd 1520-1560 TFLOP/s, every 4th 1475-1530)
+  static constexpr int kRdEvery = (kMm / kRd >= 4) ? kMm / kRd - 1 : kMm / kRd;
+};
+
+__device__ __forceinline__ uint32_t lds_addr32(const char* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char*)p));
+}
+
+// the same pointer, known to the compiler to be uniform
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32));
+  return reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// 16 bytes per lane, global -> LDS at (wave-uniform) lds + lane * 16; global address = scalar base + lane offset
+__device__ __forceinline__ void direct_load_s(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
+}
+// the same with a 64-bit address per lane
+__device__ __forceinline__ void direct_load_v(const char* p, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(p), "s"(lds) : "memory");
+}
+
+#define ATG_PIN16() __builtin_amdgcn_sched_barrier(0)
+
+// LDS-only workgroup barrier: waits for this wavefront's LDS operations, not for its outstanding global stores
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // vmcnt and expcnt at their maxima, lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+}
+
+// s_waitcnt vmcnt(N) lgkmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_loads_but() {
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 0xF) | ((N >> 4) << 14));
+}
+
+// ---- operands --------------------------------------------------------------------------------------
+// A panel in LDS is 32 KiB.  Operand contiguous along k: 256 rows of 128 bytes, the 16-byte chunk c of row r stored at
+// chunk c ^ ((r >> 1) & 7).  k-major operand: 64 k-rows of 512 bytes, chunk c (of 32) of k-row k stored at
+// (c & 16) | ((c ^ 2 s) & 15), s = (k & 3) | ((k >> 3) & 1) << 2.  Both make the fragment reads free of bank
+// conflicts.  The swizzle is applied on the global side of the direct loads, whose LDS side is lane * 16.
+
+// rows contiguous along k, all within 4 GiB of `base`
+template <typename G>
+struct RowPanel {
+  static constexpr bool kKMajor = false;
+  const char* base;
+  uint32_t off[G::kLoads];
+  // row_off(row): byte offset of tile row `row` (0..255) from b
+  template <typename F>
+  __device__ __forceinline__ void init(const char* b, int wave, int lane, F row_off) {
+    base = uniform_ptr(b);
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) {
+      const int row = (wave * G::kLoads + q) * 8 + (lane >> 3);
+      off[q] = row_off(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+  }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_s(base, off[q], lds); }
+  __device__ __forceinline__ void advance() { base += kStepK * 2; }
+};
+
+// rows contiguous along k at arbitrary addresses (gathered rows)
+template <typename G>
+struct GatherPanel {
+  static constexpr bool kKMajor = false;
+  const char* p[G::kLoads];
+  // row_ptr(row): address of tile row `row`
+  template <typename F>
+  __device__ __forceinline__ void init(int wave, int lane, F row_ptr) {
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) {
+      const int row = (wave * G::kLoads + q) * 8 + (lane >> 3);
+      p[q] = row_ptr(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+  }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_v(p[q], lds); }
+  __device__ __forceinline__ void advance() {
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) p[q] += kStepK * 2;
+  }
+};
+
+// k-major: k-row k at base + k * ld, 512 bytes of columns per row
+template <typename G>
+struct KMajorPanel {
+  static constexpr bool kKMajor = true;
+  const char* base;
+  uint32_t off[G::kLoads];
+  size_t step;
+  // cmax: last 16-byte chunk (0..31) that may be read (chunks past it are fetched from it; the caller masks them);
+  // 64 * ld < 4 GiB
+  __device__ __forceinline__ void init(const char* b, int wave, int lane, size_t ld, int cmax) {
+    base = uniform_ptr(b);
+    step = ld * kStepK;
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) {
+      const int k = (wave * G::kLoads + q) * 2 + (lane >> 5);
+      const int P = lane & 31, s = (k & 3) | (((k >> 3) & 1) << 2);
+      const int C = (P & 16) | ((P ^ (2 * s)) & 15);
+      off[q] = static_cast<uint32_t>(k * ld) + min(C, cmax) * 16;
+    }
+  }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_s(base, off[q], lds); }
+  __device__ __forceinline__ void advance() { base += step; }
+};
+
+// Fragment reads of one operand: NB blocks of 16 rows starting at tile row `row0`.
+template <int NB, bool KM>
+struct FragReader;
+
+template <int NB>
+struct FragReader<NB, false> {
+  int at[2], cur[2];
+  __device__ __forceinline__ void init(int row0, int lane) {
+    const int r = lane & 15;
+    at[0] = (row0 + r) * (kStepK * 2) + ((((lane >> 4)) ^ ((r >> 1) & 7)) << 4);
+    at[1] = at[0] ^ 64;                           // k + 32: chunk index ^ 4
+  }
+  __device__ __forceinline__ void slot(int byte) {
+    cur[0] = at[0] + byte;
+    cur[1] = at[1] + byte;
+  }
+  __device__ __forceinline__ uint4 read(const char* smem, int ks, int blk) const {
+    return *reinterpret_cast<const uint4*>(smem + cur[ks] + blk * 16 * (kStepK * 2));
+  }
+};
+
+template <int NB>
+struct FragReader<NB, true> {
+  int at[NB], cur[NB];
+  __device__ __forceinline__ void init(int col0, int lane) {
+    // 16 lanes read 4 k-rows x 16 columns: lane 4 r + q the 4 columns q of k-row r; lane i receives column i
+    const int g = lane >> 4, r = (lane & 15) >> 2, q = lane & 3;
+    const int k = 8 * g + r, s = (k & 3) | (((k >> 3) & 1) << 2);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int c = (col0 + b * 16) / 8 + (q >> 1);
+      at[b] = k * (kTile16 * 2) + ((c & 16) | ((c ^ (2 * s)) & 15)) * 16 + (q & 1) * 8;
+    }
+  }
+  __device__ __forceinline__ void slot(int byte) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) cur[b] = at[b] + byte;
+  }
+  __device__ __forceinline__ uint2 tr(const char* p) const {
+    const bf16v4 v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+        (__attribute__((address_space(3))) bf16v4*)(__attribute__((address_space(3))) const char*)p);
+    return __builtin_bit_cast(uint2, v);
+  }
+  __device__ __forceinline__ uint4 read(const char* smem, int ks, int blk) const {
+    const char* p = smem + cur[blk] + ks * 32 * (kTile16 * 2);
+    const uint2 lo = tr(p), hi = tr(p + 4 * (kTile16 * 2));
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+  }
+};
+
+// index of the MFMA after which load k of `cnt` is issued within one sub-step: evenly spread
+__device__ __forceinline__ constexpr int load_after(int k, int cnt, int mm) { return ((2 * k + 1) * mm) / (2 * cnt); }
+
+__device__ __forceinline__ int ring_byte(int first, int i) {
+  int s = first + i;
+  if (s >= kRingSlots) s -= kRingSlots;
+  return s * kRingSlot;
+}
+
+// acc += a b, with the accumulator tied to its registers: the builtin leaves the compiler free to give the result other
+// registers than the addend, and with 256 accumulator registers per lane it then moves hundreds of them per k-step.  The
+// compiler does not see the instruction's latency, so mfma_settle() has to stand between the last one and the first
+// other use of an accumulator; consecutive MFMAs on one accumulator are at least 32 instructions apart.
+template <typename G>
+__device__ __forceinline__ void mfma_in_place(floatx4& acc, bf16v8 a, bf16v8 b) {
+  if constexpr (G::kMm * 4 > 128)
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+template <typename G>
+__device__ __forceinline__ void mfma_settle(floatx4 (&acc)[G::kIB][G::kJB]) {
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+  for (int i = 0; i < G::kIB; ++i)
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) {
+      if constexpr (G::kMm * 4 > 128) asm volatile("" : "+a"(acc[i][j]));
+      else asm volatile("" : "+v"(acc[i][j]));
+    }
+}
+
+// LDS ring: the A and B panels of k-step kt sit in slots (2 kt) % 5 and (2 kt + 1) % 5.  While step kt is consumed, the
+// three other slots receive B of step kt+1 and both panels of step kt+2: up to 96 KiB of loads in flight per compute
+// unit, and every load has at least one and a half steps to land.  Per k-step:
+//   sub-step 0   MFMAs on the first 32 of k; fragments of the second 32; requests A of step kt+2, into the slot that B of
+//                step kt-1 left
+//   wait until all but those A loads have landed; workgroup barrier (one per k-step)
+//   sub-step 1   MFMAs on the second 32; first fragments of step kt+1; requests B of step kt+2, into the slot that A of
+//                step kt has just left
+// A slot is only overwritten after the barrier that follows its last read.
+template <typename G, typename PA, typename PB>
+struct Gemm16 {
+  floatx4 (&acc)[G::kIB][G::kJB];
+  PA& pa;
+  PB& pb;
+  const char* smem;
+  uint32_t wave_lds;
+  FragReader<G::kIB, PA::kKMajor> ra;
+  FragReader<G::kJB, PB::kKMajor> rb;
+  uint4 fa[2][G::kIB], fb[2][G::kJB];
+
+  __device__ __forceinline__ void mm(int f, int n) {
+    const int i = n / G::kJB, j = n % G::kJB;
+    mfma_in_place<G>(acc[i][j], __builtin_bit_cast(bf16v8, fa[f][i]), __builtin_bit_cast(bf16v8, fb[f][j]));
+  }
+  // fragment n of sub-step ks, in the order the MFMAs first need it: A block 0, the B blocks, the other A blocks
+  __device__ __forceinline__ void rd(int ks, int f, int n) {
+    if (n == 0) fa[f][0] = ra.read(smem, ks, 0);
+    else if (n <= G::kJB) fb[f][n - 1] = rb.read(smem, ks, n - 1);
+    else fa[f][n - G::kJB] = ra.read(smem, ks, n - G::kJB);
+  }
+  __device__ __forceinline__ void ld_a(int slot, int q) { pa.load(q, wave_lds + slot + q * 1024); }
+  __device__ __forceinline__ void ld_b(int slot, int q) { pb.load(q, wave_lds + slot + q * 1024); }
+
+  // REQUEST: step kt+2 exists.  (The fragments of step kt+1 are fetched whether it exists or not.)
+  template <bool REQUEST>
+  __device__ __forceinline__ void step(int first) {
+    constexpr int kMm = G::kMm, kRd = G::kRd, kEv = G::kRdEvery, kLd = G::kLoads;
+    const int la = ring_byte(first, 4), lb = ring_byte(first, 0);
+#pragma unroll
+    for (int n = 0; n < kMm; ++n) {
+      mm(0, n);
+      ATG_PIN16();
+      if (n % kEv == 0 && n / kEv < kRd) {
+        rd(1, 1, n / kEv);
+        ATG_PIN16();
+      }
+      if (REQUEST) {
+#pragma unroll
+        for (int k = 0; k < kLd; ++k)
+          if (load_after(k, kLd, kMm) == n) {
+            ld_a(la, k);
+            ATG_PIN16();
+          }
+      }
+    }
+    if (REQUEST) {
+      pa.advance();
+      wait_loads_but<kLd>();
+    } else {
+      wait_loads_but<0>();
+    }
+    __builtin_amdgcn_s_barrier();
+    ATG_PIN16();
+    ra.slot(ring_byte(first, 2));
+    rb.slot(ring_byte(first, 3));
+#pragma unroll
+    for (int n = 0; n < kMm; ++n) {
+      mm(1, n);
+      ATG_PIN16();
+      if (n % kEv == 0 && n / kEv < kRd) {
+        rd(0, 0, n / kEv);
+        ATG_PIN16();
+      }
+      if (REQUEST) {
+#pragma unroll
+        for (int k = 0; k < kLd; ++k)
+          if (load_after(k, kLd, kMm) == n) {
+            ld_b(lb, k);
+            ATG_PIN16();
+          }
+      }
+    }
+    if (REQUEST) pb.advance();
+  }
+
+  __device__ __forceinline__ void request_step(int slot) {
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) ld_a(slot, q);
+    pa.advance();
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) ld_b(slot + kRingSlot, q);
+    pb.advance();
+  }
+
+  // the whole k loop over nk >= 0 steps
+  __device__ __forceinline__ void run(int nk) {
+    if (nk > 0) request_step(0);
+    if (nk > 1) {
+      request_step(2 * kRingSlot);
+      wait_loads_but<2 * G::kLoads>();
+    } else {
+      wait_loads_but<0>();
+    }
+    __builtin_amdgcn_s_barrier();
+    ra.slot(0);
+    rb.slot(kRingSlot);
+#pragma unroll
+    for (int n = 0; n < G::kRd; ++n) rd(0, 0, n);
+    int kt = 0, first = 0;
+    for (; kt + 2 < nk; ++kt) {
+      step<true>(first);
+      first += 2;
+      if (first >= kRingSlots) first -= kRingSlots;
+    }
+    for (; kt < nk; ++kt) {
+      step<false>(first);
+      first += 2;
+      if (first >= kRingSlots) first -= kRingSlots;
+    }
+  }
+};
+
+// The thread's coordinates, recomputed where they are needed: what the compiler derives from an opaque thread index cannot
+// be hoisted out of the loop over tiles, where it would occupy registers through the k loop and be spilled.
+template <typename G>
+struct Coord16 {
+  int lane, wave, wm, wn;
+  __device__ __forceinline__ Coord16() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    wm = wave / G::kWavesB;
+    wn = wave % G::kWavesB;
+  }
+  __device__ __forceinline__ int a_row(int i) const { return wm * G::kRowsA + i * 16 + 4 * (lane >> 4); }   // + r
+  __device__ __forceinline__ int b_row(int j) const { return wn * G::kRowsB + j * 16 + (lane & 15); }
+};
+
+// acc = A B^T over nk steps of 64 (nk may be 0).  Every thread of the workgroup calls it.  The last
+// LDS reads that matter lie in front of the final step's own barrier, so the whole ring may be reused at once.
+template <typename G, typename PA, typename PB>
+__device__ __forceinline__ void gemm16(floatx4 (&acc)[G::kIB][G::kJB], PA& pa, PB& pb, int nk, char* smem,
+                                       const Coord16<G>& co) {
+#pragma unroll
+  for (int i = 0; i < G::kIB; ++i)
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+  Gemm16<G, PA, PB> g{acc, pa, pb, smem,
+                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds_addr32(smem) + co.wave * G::kLoads * 1024)),
+                      {}, {}, {}, {}};
+  g.ra.init(co.wm * G::kRowsA, co.lane);
+  g.rb.init(co.wn * G::kRowsB, co.lane);
+  g.run(nk);
+  mfma_settle<G>(acc);
+}
+
+}  // namespace atg

@@ -369,149 +369,4 @@ __device__ __forceinline__ void gemm_tile(floatx16 (&acc)[Grid::kIB][Grid::kJB],
   pinned_k_loop(ops, nk);
 }
 
-// ------------------------------------------------------------------------------------------------
-// Same tile contraction for operands stored k-major (bf16 only):
-//   C[a, b] = sum_k A[k, a] * B[k, b],   A rows and B rows contiguous along a / b.
-// A k-step is 64 rows of 512 bytes (256 columns) per operand.  Direct loads bring two rows per
-// instruction; fragments are fetched with the transposing LDS read ds_read_b64_tr_b16: inside each
-// group of 16 lanes, lane 4r + q supplies the address of 4 consecutive columns of row r (r = 0..3)
-// and lane i receives column i of those four rows, i.e. 4 consecutive k for one column; two reads
-// give the 8 k-values an MFMA lane needs.  The 16-byte chunk index C of row k is stored at
-// (C & 16) | ((C + 4 * (k & 3)) & 15), which makes every transposing read conflict-free.
-// ------------------------------------------------------------------------------------------------
-typedef __bf16 bf16x4_t __attribute__((__vector_size__(4 * sizeof(__bf16))));
-constexpr int kKmRows = 64;                        // k rows per step
-constexpr int kKmRowBytes = kTile * 2;             // 512 bytes of columns per row
-
-__device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
-  const bf16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-      (__attribute__((address_space(3))) bf16x4_t*)(__attribute__((address_space(3))) const char*)p);
-  return __builtin_bit_cast(uint2, v);
-}
-
-// a0 / b0: address of element [k = 0][first column of the tile]; a_ld / b_ld: row strides in bytes;
-// a_cmax / b_cmax: last 16-byte column chunk (0..31) that may be read (columns past it are fetched from
-// that chunk instead and must be masked by the caller); nk: number of 64-row k-steps.
-template <typename Grid = G8>
-__device__ __forceinline__ void gemm_tile_kmajor(floatx16 (&acc)[Grid::kIB][Grid::kJB], const char* a0, size_t a_ld,
-                                                 int a_cmax, const char* b0, size_t b_ld, int b_cmax, int nk,
-                                                 char* smem) {
-  constexpr int kIB = Grid::kIB, kJB = Grid::kJB, kLoadsPerWave = Grid::kLoadsPerWave;
-  constexpr int kWavesA = Grid::kWavesA, kWavesB = Grid::kWavesB;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave / kWavesB, wn = wave % kWavesB;
-
-#pragma unroll
-  for (int i = 0; i < kIB; ++i)
-#pragma unroll
-    for (int j = 0; j < kJB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  if (nk <= 0) return;
-
-  // direct loads: instruction q of this wavefront fills rows 2*(wave*4+q), +1; lane -> (row parity, chunk)
-  const char* ap[kLoadsPerWave];
-  const char* bp[kLoadsPerWave];
-#pragma unroll
-  for (int q = 0; q < kLoadsPerWave; ++q) {
-    const int k = (wave * kLoadsPerWave + q) * 2 + (lane >> 5);
-    const int P = lane & 31;
-    const int C = (P & 16) | ((P - 4 * (k & 3)) & 15);
-    ap[q] = a0 + static_cast<size_t>(k) * a_ld + min(C, a_cmax) * 16;
-    bp[q] = b0 + static_cast<size_t>(k) * b_ld + min(C, b_cmax) * 16;
-  }
-  const size_t a_step = a_ld * kKmRows, b_step = b_ld * kKmRows;
-  const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kLoadsPerWave * 1024);
-
-  // fragment addresses: group g = lane/16 -> (column half g&1, k half g>>1); L = lane%16 -> (r, q)
-  const int g = lane >> 4, L = lane & 15, r = L >> 2, qq = L & 3;
-  int rd_a[kIB], rd_b[kJB];
-#pragma unroll
-  for (int i = 0; i < kIB; ++i) {
-    const int m = wm * (kTile / kWavesA) + i * 32 + 16 * (g & 1) + 4 * qq;
-    const int C = m >> 3;
-    const int P = (C & 16) | ((C + 4 * r) & 15);
-    rd_a[i] = (8 * (g >> 1) + r) * kKmRowBytes + P * 16 + (m & 7) * 2;
-  }
-#pragma unroll
-  for (int j = 0; j < kJB; ++j) {
-    const int m = wn * (kTile / kWavesB) + j * 32 + 16 * (g & 1) + 4 * qq;
-    const int C = m >> 3;
-    const int P = (C & 16) | ((C + 4 * r) & 15);
-    rd_b[j] = (8 * (g >> 1) + r) * kKmRowBytes + P * 16 + (m & 7) * 2;
-  }
-
-  struct Ops {
-    using G = Grid;
-    floatx16 (&acc)[kIB][kJB];
-    const char* (&ap)[kLoadsPerWave];
-    const char* (&bp)[kLoadsPerWave];
-    const int (&rd_a)[kIB];
-    const int (&rd_b)[kJB];
-    const char* smem;
-    uint32_t wave_lds;
-    size_t a_step, b_step;
-    uint4 fa[2][kIB], fb[2][kJB];
-    __device__ __forceinline__ void mm(int f, int n) {
-      Mma<bf16_t>::run(fa[f][n / kJB], fb[f][n % kJB], acc[n / kJB][n % kJB]);
-    }
-    __device__ __forceinline__ void rd(int sa, int sb, int ks, int f, int n) {
-      // fragment order as in gemm_tile
-      bool is_a;
-      int k;
-      if (kIB == 2) {
-        is_a = n < kIB;
-        k = is_a ? n : n - kIB;
-      } else {
-        is_a = n == 0 || n > kJB;
-        k = n == 0 ? 0 : (n <= kJB ? n - 1 : n - kJB);
-      }
-      const char* p = smem + ks * 16 * kKmRowBytes + (is_a ? sa + rd_a[k % kIB] : sb + rd_b[k % kJB]);
-      const uint2 lo = lds_read_tr16(p);
-      const uint2 hi = lds_read_tr16(p + 4 * kKmRowBytes);
-      const uint4 v = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      if (is_a) fa[f][k % kIB] = v;
-      else fb[f][k % kJB] = v;
-    }
-    __device__ __forceinline__ void ld_a(int slot, int q) {
-      direct_load16(ap[q], wave_lds + slot + q * 1024);
-      ap[q] += a_step;
-    }
-    __device__ __forceinline__ void ld_b(int slot, int q) {
-      direct_load16(bp[q], wave_lds + slot + q * 1024);
-      bp[q] += b_step;
-    }
-  };
-  Ops ops{acc, ap, bp, rd_a, rd_b, smem, wave_lds, a_step, b_step, {}, {}};
-  pinned_k_loop(ops, nk);
-}
-
-// Persistent-grid tile order.  Workgroups are dealt to the 8 XCDs round-robin by the hardware, so
-// workgroup w is given the logical slot (w % 8) * (grid / 8) + w / 8: the 32 workgroups that share
-// one XCD's L2 then walk neighbouring tiles.  Tiles are enumerated in bands of `band` A-tiles:
-// inside a band the order runs down the band's A-tiles first, then to the next B-tile, so the
-// tiles in flight form a compact patch of the output and the operand panels they stream are
-// shared through L2 / Infinity Cache.
-struct TileOrder {
-  int n_a, n_b, band;
-  __device__ __forceinline__ int total() const { return n_a * n_b; }
-  __device__ __forceinline__ void decode(int t, int* ta, int* tb) const {
-    const int per_band = band * n_b;
-    const int bi = t / per_band;
-    const int first = bi * band;
-    const int rows = min(band, n_a - first);
-    const int in_band = t - bi * per_band;
-    *ta = first + in_band % rows;
-    *tb = in_band / rows;
-  }
-};
-
-__device__ __forceinline__ int logical_workgroup() {
-  const int g = gridDim.x, w = blockIdx.x;
-  if ((g & 7) != 0) return w;
-  return (w & 7) * (g >> 3) + (w >> 3);
-}
-
 }  // namespace atg

@@ -1,0 +1,503 @@
+// bf16 contractions of the LM head (gfx950): log-probabilities, exponentials, logit gradient, dHidden, dW.
+//
+// All of them are persistent grids of one workgroup per compute unit over 256 x 256 output tiles (gemm_bf16.hpp).  The
+// operand whose index is contiguous in the output is operand A: a lane then holds four consecutive outputs per
+// accumulator block, and results leave the registers as 16-byte stores without passing through LDS.
+#include <type_traits>
+
+#include "gemm_bf16.hpp"
+#include "head_bf16.hpp"
+#include "head_common.hpp"
+#include "tile_order.hpp"
+
+namespace atg {
+
+namespace {
+
+// Short k loops (k = H) with a heavy epilogue: two wavefronts per SIMD, 128 vocabulary rows x 64 tokens each.  A token's
+// 128 logits of a wavefront are one 256-byte run of the stored exponentials.
+using GLogit = Grid16<2, 4>;
+using GDh = Grid16<2, 2>;   // long k loop (k = V): one wavefront per SIMD
+using GDw = Grid16<4, 2>;
+
+// Row permutation of operand A inside groups of 32: with tile row `row` holding output index a_index(row), the eight
+// values of a lane's accumulator blocks 2 p and 2 p + 1 are eight consecutive outputs, and the four lane groups of a
+// wavefront cover 32 consecutive ones (64 bytes of bf16 per store instruction and row).
+__device__ __forceinline__ int a_index(int row) {
+  return (row & ~31) | (((row >> 2) & 3) << 3) | (((row >> 4) & 1) << 2) | (row & 3);
+}
+// first of the eight outputs of the block pair p (relative to the wavefront's first row)
+__device__ __forceinline__ int pair_first(int p, int lane) { return p * 32 + (lane >> 4) * 8; }
+
+template <int IB>
+__device__ __forceinline__ float pick(const floatx4 (&col)[IB], int i_sel, int r_sel) {
+  float v = 0.f;
+#pragma unroll
+  for (int i = 0; i < IB; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v = (i_sel == i && r_sel == r) ? col[i][r] : v;
+  return v;
+}
+
+__device__ __forceinline__ float across_groups_sum(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
+__device__ __forceinline__ float across_groups_max(float x) {
+  x = fmaxf(x, __shfl_xor(x, 16, 64));
+  return fmaxf(x, __shfl_xor(x, 32, 64));
+}
+
+// logits tile: A = W rows (v0 ..), B = gathered hidden rows (list positions t0 ..)
+template <bool PERMUTED>
+__device__ __forceinline__ void logit_tile(floatx4 (&acc)[GLogit::kIB][GLogit::kJB], const bf16_t* hidden, const bf16_t* W,
+                                           const int32_t* idx, int c0, int n, int v0, int t0, int H, int V, char* smem) {
+  const Coord16<GLogit> co;
+  const uint32_t row_bytes = static_cast<uint32_t>(H) * 2;
+  GatherPanel<GLogit> pb;
+  pb.init(co.wave, co.lane, [&](int row) {
+    const int tk = min(t0 + row, n - 1);
+    return reinterpret_cast<const char*>(hidden) + static_cast<size_t>(idx[c0 + tk]) * row_bytes;
+  });
+  RowPanel<GLogit> pa;
+  pa.init(reinterpret_cast<const char*>(W) + static_cast<size_t>(v0) * row_bytes, co.wave, co.lane, [&](int row) {
+    return static_cast<uint32_t>(min(PERMUTED ? a_index(row) : row, V - 1 - v0)) * row_bytes;
+  });
+  gemm16<GLogit>(acc, pa, pb, H / kStepK, smem, co);
+}
+
+// ------------------------------------------------------------------------------------------------
+// forward: per (vocabulary tile, token) maximum and sum of exponentials, and the target logit
+// ------------------------------------------------------------------------------------------------
+// ENT: also part_u, the partial sums of 2^(z log2e - m) * z that the entropy monitor needs (H = lse - E_p[z])
+template <bool ENT>
+__global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
+    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, float* __restrict__ part_m,
+    float* __restrict__ part_s, float* __restrict__ part_u, float* __restrict__ zy, int H, int V, int TC, int n_vtiles,
+    const int32_t* __restrict__ gate) {
+  using G = GLogit;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (gate && *gate == 0) return;
+  const int n = chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  const TileOrder ord{n_vtiles, (n + kTile16 - 1) / kTile16, 8};
+  float* red_m = reinterpret_cast<float*>(smem);          // [kWavesA][256]
+  float* red_s = red_m + G::kWavesA * kTile16;
+  float* red_u = red_s + G::kWavesA * kTile16;
+
+  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+    int vt, tt;
+    ord.decode(t, &vt, &tt);
+    const int v0 = vt * kTile16, t0 = tt * kTile16;
+    int ycol[G::kJB];          // fetched in front of the k loop, used behind it
+    {
+      const Coord16<G> co;
+#pragma unroll
+      for (int j = 0; j < G::kJB; ++j) {
+        const int tcol = t0 + co.b_row(j);
+        ycol[j] = tcol < n ? token_id[idx[c0 + tcol]] : -1;
+      }
+    }
+    floatx4 acc[G::kIB][G::kJB];
+    logit_tile<false>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+
+    const Coord16<G> co;
+    const int vbase = v0 + co.wm * G::kRowsA;
+    const int vrem = V - vbase;                       // vocabulary rows of this wavefront that exist (may be <= 0)
+    const int vlane = 4 * (co.lane >> 4);             // first row of this lane inside a block
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) {
+      const int tcol = t0 + co.b_row(j);
+      const int rel = ycol[j] - vbase;
+      floatx4 col[G::kIB];
+#pragma unroll
+      for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
+      if (vrem < G::kRowsA) {
+#pragma unroll
+        for (int i = 0; i < G::kIB; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) col[i][r] = (i * 16 + vlane + r < vrem) ? col[i][r] : -INFINITY;
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < G::kIB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, col[i][r]);
+      mx = across_groups_max(mx);
+      const float m2 = (mx == -INFINITY) ? 0.f : mx * kLog2e;
+      float sum = 0.f, usum = 0.f;
+#pragma unroll
+      for (int i = 0; i < G::kIB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float e = fast_exp2(fmaf(col[i][r], kLog2e, -m2));
+          sum += e;
+          if (ENT) usum += e > 0.f ? e * col[i][r] : 0.f;
+        }
+      sum = across_groups_sum(sum);
+      if (ENT) usum = across_groups_sum(usum);
+      if (co.lane < 16) {
+        red_m[co.wm * kTile16 + co.b_row(j)] = (mx == -INFINITY) ? -INFINITY : m2;
+        red_s[co.wm * kTile16 + co.b_row(j)] = sum;
+        if (ENT) red_u[co.wm * kTile16 + co.b_row(j)] = usum;
+      }
+      // target logit: held by exactly one lane of one wavefront of one tile
+      const bool hit = tcol < n && rel >= 0 && rel < G::kRowsA && ((rel >> 2) & 3) == (co.lane >> 4);
+      if (__builtin_amdgcn_ballot_w64(hit) != 0ull) {
+        const float zt = pick<G::kIB>(col, rel >> 4, rel & 3);
+        if (hit) zy[tcol] = zt;
+      }
+    }
+    // fold the wavefronts' shares of the tile: one (max, sum) per token and vocabulary tile
+    lds_barrier();
+    const int tl = threadIdx.x;
+    if (tl < kTile16 && t0 + tl < n) {
+      float M = -INFINITY;
+#pragma unroll
+      for (int q = 0; q < G::kWavesA; ++q) M = fmaxf(M, red_m[q * kTile16 + tl]);
+      float S = 0.f, U = 0.f;
+#pragma unroll
+      for (int q = 0; q < G::kWavesA; ++q) {
+        const float mq = red_m[q * kTile16 + tl];
+        if (mq != -INFINITY) {
+          const float sc = fast_exp2(mq - M);
+          S += red_s[q * kTile16 + tl] * sc;
+          if (ENT) U += red_u[q * kTile16 + tl] * sc;
+        }
+      }
+      part_m[static_cast<size_t>(vt) * TC + t0 + tl] = M;
+      part_s[static_cast<size_t>(vt) * TC + t0 + tl] = S;
+      if (ENT) part_u[static_cast<size_t>(vt) * TC + t0 + tl] = U;
+    }
+    lds_barrier();   // the fold buffers are free again; the stores above need not have landed
+  }
+}
+
+// Stores eight consecutive bf16 outputs of a lane.
+__device__ __forceinline__ void store8(bf16_t* p, const float (&d)[8]) {
+  *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]), pack_bf16x2(d[4], d[5]),
+                                            pack_bf16x2(d[6], d[7]));
+}
+
+// ------------------------------------------------------------------------------------------------
+// exponentials (one-pass forward + backward): E[j][v] = exp(z - c_j) for the tokens j of the launch (zero for the padding
+// columns V .. Vp and for the rows that pad the last tile); part_s[vt][j] = sum over the 256 vocabulary rows of tile vt;
+// zy[j] = target logit
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
+    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ c2,
+    bf16_t* __restrict__ E, float* __restrict__ part_s, float* __restrict__ zy, int H, int V, int Vp, int TC, int n_vtiles) {
+  using G = GLogit;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int n = chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  const TileOrder ord{n_vtiles, (n + kTile16 - 1) / kTile16, 8};
+  float* red_s = reinterpret_cast<float*>(smem);   // [kWavesA][256]
+
+  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+    int vt, tt;
+    ord.decode(t, &vt, &tt);
+    const int v0 = vt * kTile16, t0 = tt * kTile16;
+    int ycol[G::kJB];          // fetched in front of the k loop, used behind it
+    float nc2col[G::kJB];
+    {
+      const Coord16<G> co;
+#pragma unroll
+      for (int j = 0; j < G::kJB; ++j) {
+        const int tcol = t0 + co.b_row(j);
+        ycol[j] = tcol < n ? token_id[idx[c0 + tcol]] : -1;
+        nc2col[j] = tcol < n ? -c2[tcol] : 0.f;
+      }
+    }
+    floatx4 acc[G::kIB][G::kJB];
+    logit_tile<true>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+
+    const Coord16<G> co;
+    const int vbase = v0 + co.wm * G::kRowsA;
+    // tiles that lie fully inside the vocabulary and the token list need no per-element range checks
+    const bool interior = (v0 + kTile16 <= V) && (t0 + kTile16 <= n);
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) {
+      const int tcol = t0 + co.b_row(j);
+      const bool live = tcol < n;
+      const int rel = ycol[j] - vbase;
+      const float nc2 = nc2col[j];
+      const bool hit = live && rel >= 0 && rel < G::kRowsA && ((rel >> 3) & 3) == (co.lane >> 4);
+      if (__builtin_amdgcn_ballot_w64(hit) != 0ull) {
+        floatx4 col[G::kIB];
+#pragma unroll
+        for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
+        const float zt = pick<G::kIB>(col, ((rel >> 5) << 1) | ((rel >> 2) & 1), rel & 3);
+        if (hit) zy[tcol] = zt;
+      }
+      bf16_t* row = E + static_cast<size_t>(tcol) * Vp + vbase;
+      float sum = 0.f;
+#pragma unroll
+      for (int p = 0; p < G::kIB / 2; ++p) {
+        const int vf = pair_first(p, co.lane);
+        float d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) d[e] = fast_exp2(fmaf(acc[2 * p + (e >> 2)][j][e & 3], kLog2e, nc2));
+        if (!interior) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) d[e] = (vbase + vf + e < V && live) ? d[e] : 0.f;
+        }
+        sum += ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]));
+        if (interior || vbase + vf < Vp) store8(row + vf, d);
+      }
+      sum = across_groups_sum(sum);
+      if (co.lane < 16) red_s[co.wm * kTile16 + co.b_row(j)] = sum;
+    }
+    lds_barrier();
+    const int tl = threadIdx.x;
+    if (tl < kTile16 && t0 + tl < n) {
+      float S = 0.f;
+#pragma unroll
+      for (int q = 0; q < G::kWavesA; ++q) S += red_s[q * kTile16 + tl];
+      part_s[static_cast<size_t>(vt) * TC + t0 + tl] = S;
+    }
+    lds_barrier();   // the sums are free again; the stores may still fly
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// logit gradient with the logits recomputed (two-call path, and the fallback of the one-pass step):
+// dZ[t][v] = g_t ([v = y_t] - exp(z - lse_t)); without coefficients g = -1 (softmax - onehot)
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
+    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ lse,
+    const float* __restrict__ coef, bf16_t* __restrict__ dZ, int H, int V, int Vp, int TC, int n_vtiles,
+    const int32_t* __restrict__ gate) {
+  using G = GLogit;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (gate && *gate == 0) return;
+  const int n = chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  const TileOrder ord{n_vtiles, (n + kTile16 - 1) / kTile16, 8};
+
+  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+    int vt, tt;
+    ord.decode(t, &vt, &tt);
+    const int v0 = vt * kTile16, t0 = tt * kTile16;
+    int ycol[G::kJB];          // fetched in front of the k loop, used behind it
+    float gcol[G::kJB], lcol[G::kJB];
+    {
+      const Coord16<G> co;
+#pragma unroll
+      for (int j = 0; j < G::kJB; ++j) {
+        const int tcol = t0 + co.b_row(j);
+        ycol[j] = -1;
+        gcol[j] = lcol[j] = 0.f;
+        if (tcol < n) {
+          const int row = idx[c0 + tcol];
+          ycol[j] = token_id[row];
+          gcol[j] = coef ? coef[row] : -1.f;
+          lcol[j] = lse[row];
+        }
+      }
+    }
+    floatx4 acc[G::kIB][G::kJB];
+    logit_tile<true>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+
+    const Coord16<G> co;
+    const int vbase = v0 + co.wm * G::kRowsA;
+    const bool interior = (v0 + kTile16 <= V) && (t0 + kTile16 <= n);
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) {
+      const int tcol = t0 + co.b_row(j);
+      const bool live = tcol < n;
+      const int rel = ycol[j] - vbase;
+      const float g = gcol[j], nl2 = -lcol[j] * kLog2e;
+      bf16_t* row = dZ + static_cast<size_t>(tcol) * Vp + vbase;
+#pragma unroll
+      for (int p = 0; p < G::kIB / 2; ++p) {
+        const int vf = pair_first(p, co.lane);
+        float d[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) d[e] = -g * fast_exp2(fmaf(acc[2 * p + (e >> 2)][j][e & 3], kLog2e, nl2));
+        if (static_cast<unsigned>(rel - vf) < 8u) {      // the onehot term: one element in V per token
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (rel - vf == e) d[e] += g;
+        }
+        if (!interior) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) d[e] = (vbase + vf + e < V && live) ? d[e] : 0.f;
+        }
+        if (interior || vbase + vf < Vp) store8(row + vf, d);
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// dHidden: A = Wt rows (h), B = dZ / E rows (tokens), k = vocabulary
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(GDh::kThreads) void k_head_dh(const bf16_t* __restrict__ dZ, const bf16_t* __restrict__ Wt,
+                                                           const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
+                                                           int c0, bf16_t* __restrict__ d_hidden, int H, int Vp, int TC,
+                                                           const float* __restrict__ scale, const int32_t* __restrict__ perm,
+                                                           const int32_t* __restrict__ live_cnt) {
+  using G = GDh;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // after the rows were compacted: the first *live_cnt rows of dZ, row j belonging to list position perm[j]
+  const int n = perm ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  const TileOrder ord{(n + kTile16 - 1) / kTile16, (H + kTile16 - 1) / kTile16, 8};
+  const uint32_t row_bytes = static_cast<uint32_t>(Vp) * 2;
+
+  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+    int tt, ht;
+    ord.decode(t, &tt, &ht);
+    const int t0 = tt * kTile16, h0 = ht * kTile16;
+    floatx4 acc[G::kIB][G::kJB];
+    {
+      const Coord16<G> co;
+      RowPanel<G> pa, pb;
+      pa.init(reinterpret_cast<const char*>(Wt) + static_cast<size_t>(h0) * row_bytes, co.wave, co.lane,
+              [&](int row) { return static_cast<uint32_t>(min(a_index(row), H - 1 - h0)) * row_bytes; });
+      pb.init(reinterpret_cast<const char*>(dZ) + static_cast<size_t>(t0) * row_bytes, co.wave, co.lane,
+              [&](int row) { return static_cast<uint32_t>(row) * row_bytes; });
+      gemm16<G>(acc, pa, pb, Vp / kStepK, smem, co);
+    }
+    const Coord16<G> co;
+    const int hbase = h0 + co.wm * G::kRowsA;
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) {
+      const int jt = t0 + co.b_row(j);
+      if (jt < n) {
+        const int jl = perm ? perm[jt] : jt;
+        const float sc = scale ? scale[jl] : 1.f;     // row factor of the one-pass path
+        bf16_t* out = d_hidden + static_cast<size_t>(idx[c0 + jl]) * H + hbase;
+#pragma unroll
+        for (int p = 0; p < G::kIB / 2; ++p) {
+          const int hf = pair_first(p, co.lane);
+          float d[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) d[e] = acc[2 * p + (e >> 2)][j][e & 3] * sc;
+          if (hbase + hf < H) store8(out + hf, d);
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// dW[v][h] (+)= sum_t dZ[t][v] * hG[t][h]: A = hG columns (h), B = dZ columns (v), both k-major, k = tokens
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(GDw::kThreads) void k_head_dw(const bf16_t* __restrict__ dZ, const bf16_t* __restrict__ hG,
+                                                           const int32_t* __restrict__ cnt, int c0, float* __restrict__ dW,
+                                                           int H, int V, int Vp, int TC, int n_vtiles, int accumulate,
+                                                           int first_chunk, const int32_t* __restrict__ live_cnt) {
+  using G = GDw;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // live_cnt: the rows were compacted, only the first *live_cnt of the chunk take part
+  const int n = live_cnt ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
+  if (n <= 0 && !(first_chunk && !accumulate)) return;
+  // bands of 32 / (tiles along H) vocabulary tiles: the 32 workgroups that share an XCD's L2 then cover every
+  // H-tile of the same few vocabulary tiles, and each panel of the large operand (the 10 GB of dZ rows)
+  // is fetched by one XCD only (measured 2.4 % faster than bands of 8)
+  const int n_htiles = (H + kTile16 - 1) / kTile16;
+  const TileOrder ord{n_vtiles, n_htiles, max(1, 32 / n_htiles)};
+  const int nk = (n + kTile16 - 1) / kTile16 * (kTile16 / kStepK);
+
+  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+    int vt, ht;
+    ord.decode(t, &vt, &ht);
+    const int v0 = vt * kTile16, h0 = ht * kTile16;
+    floatx4 acc[G::kIB][G::kJB];
+    {
+      const Coord16<G> co;
+      KMajorPanel<G> pa, pb;
+      pa.init(reinterpret_cast<const char*>(hG + h0), co.wave, co.lane, static_cast<size_t>(H) * 2, min(31, (H - h0) / 8 - 1));
+      pb.init(reinterpret_cast<const char*>(dZ + v0), co.wave, co.lane, static_cast<size_t>(Vp) * 2, min(31, (Vp - v0) / 8 - 1));
+      gemm16<G>(acc, pa, pb, nk, smem, co);
+    }
+    const Coord16<G> co;
+    const int hb = h0 + co.wm * G::kRowsA;     // a whole block of 16 columns exists or does not (H % 64 == 0)
+    const bool interior = hb + G::kRowsA <= H;
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) {
+      const int v = v0 + co.b_row(j);
+      if (v < V) {
+        floatx4* out = reinterpret_cast<floatx4*>(dW + static_cast<size_t>(v) * H + hb + 4 * (co.lane >> 4));
+        if (interior) {
+          floatx4 x[G::kIB];
+#pragma unroll
+          for (int i = 0; i < G::kIB; ++i) x[i] = acc[i][j];
+          if (accumulate) {
+#pragma unroll
+            for (int i = 0; i < G::kIB; ++i) x[i] += out[i * 4];
+          }
+#pragma unroll
+          for (int i = 0; i < G::kIB; ++i) out[i * 4] = x[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < G::kIB; ++i)
+            if (hb + i * 16 < H) out[i * 4] = accumulate ? out[i * 4] + acc[i][j] : acc[i][j];
+        }
+      }
+    }
+  }
+}
+
+}  // namespace
+
+// ================================================================================================
+// launchers
+// ================================================================================================
+int launch_fwd_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
+                    float* part_m, float* part_s, float* part_u, float* zy, hipStream_t s, const int32_t* gate) {
+  auto k = part_u ? k_head_fwd<true> : k_head_fwd<false>;
+  ATG_TRY(allow_big_lds(k, kRingBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
+                     static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, part_m, part_s, part_u, zy, g.H, g.V,
+                     g.TC, g.n_vtiles, gate);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_fe_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
+                   const float* c2, void* E, float* part_s, float* zy, hipStream_t s) {
+  ATG_TRY(allow_big_lds(k_head_fe, kRingBytes));
+  hipLaunchKernelGGL(k_head_fe, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
+                     static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, c2, static_cast<bf16_t*>(E), part_s,
+                     zy, g.H, g.V, g.Vp, g.TC, g.n_vtiles);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
+                   const float* lse, const float* coef, void* dZ, hipStream_t s, const int32_t* gate) {
+  ATG_TRY(allow_big_lds(k_head_dz, kRingBytes));
+  hipLaunchKernelGGL(k_head_dz, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
+                     static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, lse, coef, static_cast<bf16_t*>(dZ),
+                     g.H, g.V, g.Vp, g.TC, g.n_vtiles, gate);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, hipStream_t s,
+                   const float* scale, const int32_t* perm, const int32_t* live_cnt) {
+  ATG_TRY(allow_big_lds(k_head_dh, kRingBytes));
+  hipLaunchKernelGGL(k_head_dh, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, static_cast<const bf16_t*>(dZ),
+                     static_cast<const bf16_t*>(Wt), ch.idx, ch.cnt, ch.c0, static_cast<bf16_t*>(d_hidden), g.H, g.Vp, g.TC,
+                     scale, perm, live_cnt);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, int accumulate,
+                   int first_chunk, hipStream_t s, const int32_t* live_cnt) {
+  ATG_TRY(allow_big_lds(k_head_dw, kRingBytes));
+  hipLaunchKernelGGL(k_head_dw, dim3(gemm_grid()), dim3(GDw::kThreads), kRingBytes, s, static_cast<const bf16_t*>(dZ),
+                     static_cast<const bf16_t*>(hG), ch.cnt, ch.c0, dW, g.H, g.V, g.Vp, g.TC, g.n_vtiles, accumulate,
+                     first_chunk, live_cnt);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+}  // namespace atg

@@ -1,0 +1,19 @@
+// Launchers of the bf16 head contractions (see head_kernels.hpp for the meaning of the arguments).
+#pragma once
+
+#include "head_kernels.hpp"
+
+namespace atg {
+
+int launch_fwd_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
+                    float* part_m, float* part_s, float* part_u, float* zy, hipStream_t s, const int32_t* gate);
+int launch_fe_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
+                   const float* c2, void* E, float* part_s, float* zy, hipStream_t s);
+int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
+                   const float* lse, const float* coef, void* dZ, hipStream_t s, const int32_t* gate);
+int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, hipStream_t s,
+                   const float* scale, const int32_t* perm, const int32_t* live_cnt);
+int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, int accumulate,
+                   int first_chunk, hipStream_t s, const int32_t* live_cnt);
+
+}  // namespace atg

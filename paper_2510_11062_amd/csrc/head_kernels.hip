@@ -13,22 +13,14 @@
 #include <type_traits>
 
 #include "gemm_core.hpp"
-#include "head_kernels.hpp"
+#include "head_bf16.hpp"
+#include "head_common.hpp"
+#include "tile_order.hpp"
 #include "token_kernels.hpp"
 
 namespace atg {
 
 namespace {
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-__device__ __forceinline__ int chunk_count(const int32_t* cnt, int c0, int TC) {
-  const int n = *cnt - c0;
-  return n < 0 ? 0 : (n > TC ? TC : n);
-}
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // ------------------------------------------------------------------------------------------------
 // forward: A = W rows (vocab -> accumulator registers), B = hidden rows (tokens -> lanes)
@@ -267,27 +259,6 @@ __global__ __launch_bounds__(256) void k_transpose(const T* __restrict__ src, in
 // dZ: recompute logits, emit dZ[t][v] and dZt[v][t]
 // ------------------------------------------------------------------------------------------------
 template <typename T>
-struct Pack4;
-template <>
-struct Pack4<float> {
-  static __device__ __forceinline__ void store(float* p, float a, float b, float c, float d) {
-    *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
-  }
-};
-template <>
-struct Pack4<bf16_t> {
-  static __device__ __forceinline__ void store(bf16_t* p, float a, float b, float c, float d) {
-    uint2 u;
-    u.x = pack_bf16x2(a, b);
-    u.y = pack_bf16x2(c, d);
-    *reinterpret_cast<uint2*>(p) = u;
-  }
-};
-
-constexpr int kDzRowStride = kTile * 2 + 8;              // bytes; +8 keeps the 8-byte stores conflict-free
-constexpr int kDzLdsBytes = kTile * kDzRowStride;        // bf16 dZ tile staged for coalesced stores
-
-template <typename T>
 __global__ __launch_bounds__(kGemmThreads) void k_head_dz(
     const T* __restrict__ hidden, const T* __restrict__ W, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id,
@@ -302,7 +273,6 @@ __global__ __launch_bounds__(kGemmThreads) void k_head_dz(
   const TileCoord tc;
   const size_t row_bytes = static_cast<size_t>(H) * sizeof(T);
   const int nk = static_cast<int>(row_bytes / kStepBytes);
-  constexpr bool kStage = sizeof(T) == 2;      // bf16: dZ[t][v] goes through LDS for 16-byte stores
 
   for (int t = logical_workgroup(); t < total; t += gridDim.x) {
     int vt, tt;
@@ -370,17 +340,11 @@ __global__ __launch_bounds__(kGemmThreads) void k_head_dz(
 #pragma unroll
               for (int e = 0; e < 4; ++e) d[e] = (v + e < V && live) ? d[e] : 0.f;   // k padding, rows past the count
             }
-            if (kStage) {
-              uint2 u;
-              u.x = pack_bf16x2(d[0], d[1]);
-              u.y = pack_bf16x2(d[2], d[3]);
-              *reinterpret_cast<uint2*>(smem + tc.b_row(j) * kDzRowStride + vl * 2) = u;
-            } else {
-              if (v < Vp) Pack4<T>::store(dZ + static_cast<size_t>(tcol[j]) * Vp + v, d[0], d[1], d[2], d[3]);
+            if (v < Vp)
+              *reinterpret_cast<float4*>(dZ + static_cast<size_t>(tcol[j]) * Vp + v) = make_float4(d[0], d[1], d[2], d[3]);
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (v + e < V) dZt[static_cast<size_t>(v + e) * TC + tcol[j]] = from_f32<T>(d[e]);
-            }
+            for (int e = 0; e < 4; ++e)
+              if (v + e < V) dZt[static_cast<size_t>(v + e) * TC + tcol[j]] = d[e];
           }
         }
       }
@@ -389,30 +353,6 @@ __global__ __launch_bounds__(kGemmThreads) void k_head_dz(
       emit(std::false_type{});
     else
       emit(std::true_type{});
-    if (kStage) {
-      __syncthreads();
-      // dZ[t][v]: 32 threads x 16 bytes cover the 512 bytes of one token row of the staged tile
-      const int col16 = threadIdx.x & 31;
-      if (v0 + col16 * 8 < Vp) {
-#pragma unroll 4
-        for (int it = 0; it < kTile / 16; ++it) {
-          const int row = it * 16 + (threadIdx.x >> 5);
-          // two 8-byte reads per lane (rows are only 8-byte aligned); lanes 16 apart would hit the same
-          // banks, so the upper half of each row takes its two halves in the opposite order
-          const char* src = smem + row * kDzRowStride + col16 * 16;
-          const int flip = (col16 >> 4) << 3;
-          const uint2 first = *reinterpret_cast<const uint2*>(src + flip);
-          const uint2 second = *reinterpret_cast<const uint2*>(src + (flip ^ 8));
-          const uint2 lo = flip ? second : first;
-          const uint2 hi = flip ? first : second;
-          uint4 u;
-          u.x = lo.x; u.y = lo.y; u.z = hi.x; u.w = hi.y;
-          *reinterpret_cast<uint4*>(reinterpret_cast<char*>(dZ) +
-                                    (static_cast<size_t>(t0 + row) * Vp + v0 + col16 * 8) * 2) = u;
-        }
-      }
-      barrier_lds_only();   // every wavefront has read its part of the staged tile; its stores may still fly
-    }
   }
 }
 
@@ -456,152 +396,6 @@ __global__ __launch_bounds__(256) void k_ref_logit(const bf16_t* __restrict__ hi
   }
   acc = wave_sum(acc);
   if (lane == 0) c2[j] = acc * kLog2e;
-}
-
-constexpr int kFeRedOffset = kDzLdsBytes;                        // staged tile, then the sums of the four vocabulary quarters
-constexpr int kFeLdsBytes = kLdsBytes;
-static_assert(kFeRedOffset + kWavesA * kTile * 4 <= kFeLdsBytes, "the epilogue buffers must fit the k loop's LDS");
-
-// A = W rows (vocab -> accumulator registers), B = hidden rows (tokens -> lanes), as in the forward.
-// E[j][v] = exp(z - c_j) for the tokens j of the launch; part_s[vt][j] = sum over the 256 vocabulary rows
-// of tile vt; zy[j] = target logit.
-__global__ __launch_bounds__(kGemmThreads) void k_head_fe(
-    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id,
-    const float* __restrict__ c2, bf16_t* __restrict__ E, float* __restrict__ part_s, float* __restrict__ zy,
-    int H, int V, int Vp, int TC, int n_vtiles) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{n_vtiles, (n + kTile - 1) / kTile, 8};
-  const int total = ord.total();
-  const TileCoord tc;
-  const size_t row_bytes = static_cast<size_t>(H) * 2;
-  const int nk = static_cast<int>(row_bytes / kStepBytes);
-  float* red_s = reinterpret_cast<float*>(smem + kFeRedOffset);   // [kWavesA][256]
-
-  for (int t = logical_workgroup(); t < total; t += gridDim.x) {
-    int vt, tt;
-    ord.decode(t, &vt, &tt);
-    const int v0 = vt * kTile, t0 = tt * kTile;
-
-    int tcol[kJB], ycol[kJB];
-    float nc2col[kJB];
-#pragma unroll
-    for (int j = 0; j < kJB; ++j) {
-      tcol[j] = t0 + tc.b_row(j);
-      if (tcol[j] < n) {
-        ycol[j] = token_id[idx[c0 + tcol[j]]];
-        nc2col[j] = -c2[tcol[j]];
-      } else {
-        ycol[j] = -1;
-        nc2col[j] = 0.f;
-      }
-    }
-
-    floatx16 acc[kIB][kJB];
-    gemm_tile<bf16_t>(
-        acc,
-        [&](int row) {
-          const int v = min(v0 + row, V - 1);
-          return reinterpret_cast<const char*>(W) + static_cast<size_t>(v) * row_bytes;
-        },
-        [&](int row) {
-          const int tk = min(t0 + row, n - 1);
-          return reinterpret_cast<const char*>(hidden) + static_cast<size_t>(idx[c0 + tk]) * row_bytes;
-        },
-        nk, smem);
-
-    constexpr int kWaveRows = kTile / kWavesA;
-    const int vwave = tc.wm * kWaveRows;             // first vocab row (inside the tile) of this wavefront
-    const int vbase = v0 + vwave;
-
-    // target logit: held by exactly one lane of one wavefront of one tile
-#pragma unroll
-    for (int j = 0; j < kJB; ++j) {
-      const int rel = ycol[j] - vbase;
-      const bool hit = (tcol[j] < n) && rel >= 0 && rel < kWaveRows && (((rel >> 2) & 1) == tc.half);
-      if (__builtin_amdgcn_ballot_w64(hit) != 0ull) {
-        float zt = 0.f;
-#pragma unroll
-        for (int i = 0; i < kIB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vl = i * 32 + 8 * (r >> 2) + (r & 3);   // half bit compared separately
-            if ((rel & ~4) == vl) zt = acc[i][j][r];
-          }
-        if (hit) zy[tcol[j]] = zt;
-      }
-    }
-
-    const bool interior = (v0 + kTile <= V) && (t0 + kTile <= n);
-    float csum[kJB];
-    auto emit = [&](auto guard_c) {
-      constexpr bool kGuard = decltype(guard_c)::value;
-#pragma unroll
-      for (int j = 0; j < kJB; ++j) {
-        const float nc2 = nc2col[j];
-        const bool live = tcol[j] < n;
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < kIB; ++i) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int vl = vwave + i * 32 + 8 * q + 4 * tc.half;   // first of 4 consecutive vocab rows
-            const int v = v0 + vl;
-            float d[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) d[e] = fast_exp2(fmaf(acc[i][j][q * 4 + e], kLog2e, nc2));
-            if (kGuard) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) d[e] = (v + e < V && live) ? d[e] : 0.f;   // k padding, rows past the count
-            }
-            sum += (d[0] + d[1]) + (d[2] + d[3]);
-            uint2 u;
-            u.x = pack_bf16x2(d[0], d[1]);
-            u.y = pack_bf16x2(d[2], d[3]);
-            *reinterpret_cast<uint2*>(smem + tc.b_row(j) * kDzRowStride + vl * 2) = u;
-          }
-        }
-        csum[j] = sum;
-      }
-    };
-    if (interior)
-      emit(std::false_type{});
-    else
-      emit(std::true_type{});
-#pragma unroll
-    for (int j = 0; j < kJB; ++j) {
-      const float sum = csum[j] + __shfl_xor(csum[j], 32, 64);
-      if (tc.half == 0) red_s[tc.wm * kTile + tc.b_row(j)] = sum;
-    }
-    __syncthreads();
-    if (threadIdx.x < kTile && t0 + threadIdx.x < n) {
-      float S = 0.f;
-#pragma unroll
-      for (int q = 0; q < kWavesA; ++q) S += red_s[q * kTile + threadIdx.x];
-      part_s[static_cast<size_t>(vt) * TC + t0 + threadIdx.x] = S;
-    }
-    // E[t][v]: 32 threads x 16 bytes cover the 512 bytes of one token row of the staged tile
-    const int col16 = threadIdx.x & 31;
-    if (v0 + col16 * 8 < Vp) {
-#pragma unroll 4
-      for (int it = 0; it < kTile / 16; ++it) {
-        const int row = it * 16 + (threadIdx.x >> 5);
-        const char* src = smem + row * kDzRowStride + col16 * 16;
-        const int flip = (col16 >> 4) << 3;        // see k_head_dz: keeps the two 8-byte reads off the same banks
-        const uint2 first = *reinterpret_cast<const uint2*>(src + flip);
-        const uint2 second = *reinterpret_cast<const uint2*>(src + (flip ^ 8));
-        const uint2 lo = flip ? second : first;
-        const uint2 hi = flip ? first : second;
-        uint4 u;
-        u.x = lo.x; u.y = lo.y; u.z = hi.x; u.w = hi.y;
-        *reinterpret_cast<uint4*>(reinterpret_cast<char*>(E) +
-                                  (static_cast<size_t>(t0 + row) * Vp + v0 + col16 * 8) * 2) = u;
-      }
-    }
-    barrier_lds_only();   // staged tile and quarter sums are free again; the stores may still fly
-  }
 }
 
 // 256 threads = 64 tokens x 4 slices of the partial sums.  Per token of the launch: S, lse, logp; the
@@ -888,95 +682,22 @@ __global__ __launch_bounds__(256) void k_gather_rows(const bf16_t* __restrict__ 
   }
 }
 
-// ------------------------------------------------------------------------------------------------
-// dW (bf16): dW[v][h] (+)= sum_t dZ[t][v] * hG[t][h], both operands read k-major (no transposed
-// copies): A = dZ columns (vocab -> registers), B = hG columns (h -> lanes), k = tokens
-// ------------------------------------------------------------------------------------------------
-template <typename G>
-__global__ __launch_bounds__(G::kThreads) void k_head_dw_km(const bf16_t* __restrict__ dZ,
-                                                             const bf16_t* __restrict__ hG,
-                                                             const int32_t* __restrict__ cnt, int c0,
-                                                             float* __restrict__ dW, int H, int V, int Vp,
-                                                             int TC, int n_vtiles, int accumulate,
-                                                             int first_chunk, const int32_t* __restrict__ live_cnt) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  // live_cnt: the rows were compacted, only the first *live_cnt of the chunk take part
-  const int n = live_cnt ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
-  if (n <= 0 && !(first_chunk && !accumulate)) return;
-  // bands of 32 / (tiles along H) vocabulary tiles: the 32 workgroups that share an XCD's L2 then cover every
-  // H-tile of the same few vocabulary tiles, and each panel of the large operand (the 10 GB of dZ rows)
-  // is fetched by one XCD only (measured 2.4 % faster than bands of 8)
-  const int n_htiles = (H + kTile - 1) / kTile;
-  const TileOrder ord{n_vtiles, n_htiles, max(1, 32 / n_htiles)};
-  const int total = ord.total();
-  const TileCoordT<G> tc;
-  const int nk = (n + kTile - 1) / kTile * kTile / kKmRows;
-
-  for (int t = logical_workgroup(); t < total; t += gridDim.x) {
-    int vt, ht;
-    ord.decode(t, &vt, &ht);
-    const int v0 = vt * kTile, h0 = ht * kTile;
-    floatx16 acc[G::kIB][G::kJB];
-    gemm_tile_kmajor<G>(acc, reinterpret_cast<const char*>(dZ + v0), static_cast<size_t>(Vp) * 2,
-                     min(31, (Vp - v0) / 8 - 1), reinterpret_cast<const char*>(hG + h0),
-                     static_cast<size_t>(H) * 2, min(31, (H - h0) / 8 - 1), nk, smem);
-#pragma unroll
-    for (int i = 0; i < G::kIB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int v = v0 + tc.a_row(i, r);
-        if (v >= V) continue;
-        float* out = dW + static_cast<size_t>(v) * H;
-#pragma unroll
-        for (int jj = 0; jj < G::kJB; ++jj) {
-          const int h = h0 + tc.b_row(jj);
-          if (h < H) out[h] = accumulate ? out[h] + acc[i][jj][r] : acc[i][jj][r];
-        }
-      }
-  }
-}
-
-template <typename K>
-int allow_big_lds(K kernel, int bytes = kLdsBytes) {
-  ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-  return AT_GRPO_OK;
-}
-
-int gemm_grid() {
-  int cus = device_cu_count();
-  if (cus <= 0) cus = 256;
-  return cus;
-}
-
 }  // namespace
 
 // ================================================================================================
 // launchers
 // ================================================================================================
-template <typename T, bool ENT>
-int launch_head_fwd_t(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
-                      const int32_t* token_id, float* part_m, float* part_s, float* part_u, float* zy,
-                      hipStream_t s, const int32_t* gate) {
-  auto k = k_head_fwd<T, ENT>;
-  ATG_TRY(allow_big_lds(k));
-  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s, static_cast<const T*>(hidden),
-                     static_cast<const T*>(W), ch.idx, ch.cnt, ch.c0, token_id, part_m, part_s, part_u, zy, g.H,
-                     g.V, g.TC, g.n_vtiles, gate);
-  return AT_GRPO_OK;
-}
-
 int launch_head_fwd(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                     const int32_t* token_id, float* part_m, float* part_s, float* part_u, float* zy,
                     hipStream_t s, const int32_t* gate) {
   ProfScope ps(PROF_HEAD_FWD, s);
-  if (g.dtype == AT_GRPO_BF16) {
-    if (part_u) ATG_TRY((launch_head_fwd_t<bf16_t, true>(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s, gate)));
-    else ATG_TRY((launch_head_fwd_t<bf16_t, false>(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s, gate)));
-  } else {
-    if (part_u) ATG_TRY((launch_head_fwd_t<float, true>(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s, gate)));
-    else ATG_TRY((launch_head_fwd_t<float, false>(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s, gate)));
-  }
+  if (g.dtype == AT_GRPO_BF16)
+    return launch_fwd_bf16(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s, gate);
+  auto k = part_u ? k_head_fwd<float, true> : k_head_fwd<float, false>;
+  ATG_TRY(allow_big_lds(k, kLdsBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s, static_cast<const float*>(hidden),
+                     static_cast<const float*>(W), ch.idx, ch.cnt, ch.c0, token_id, part_m, part_s, part_u, zy, g.H,
+                     g.V, g.TC, g.n_vtiles, gate);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
@@ -1027,22 +748,13 @@ int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
                    const int32_t* token_id, const float* lse, const float* coef, void* dZ, void* dZt,
                    hipStream_t s, const int32_t* gate) {
   ProfScope ps(PROF_HEAD_DZ, s);
-  if (g.dtype == AT_GRPO_BF16) {
-    auto k = k_head_dz<bf16_t>;
-    constexpr int lds = kDzLdsBytes > kLdsBytes ? kDzLdsBytes : kLdsBytes;
-    ATG_TRY(allow_big_lds(k, lds));
-    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), lds, s,
-                       static_cast<const bf16_t*>(hidden), static_cast<const bf16_t*>(W), ch.idx, ch.cnt,
-                       ch.c0, token_id, lse, coef, static_cast<bf16_t*>(dZ), static_cast<bf16_t*>(dZt),
-                       g.H, g.V, g.Vp, g.TC, g.n_vtiles, gate);
-  } else {
-    auto k = k_head_dz<float>;
-    ATG_TRY(allow_big_lds(k));
-    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
-                       static_cast<const float*>(hidden), static_cast<const float*>(W), ch.idx, ch.cnt,
-                       ch.c0, token_id, lse, coef, static_cast<float*>(dZ), static_cast<float*>(dZt), g.H,
-                       g.V, g.Vp, g.TC, g.n_vtiles, gate);
-  }
+  if (g.dtype == AT_GRPO_BF16) return launch_dz_bf16(g, ch, hidden, W, token_id, lse, coef, dZ, s, gate);
+  auto k = k_head_dz<float>;
+  ATG_TRY(allow_big_lds(k, kLdsBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
+                     static_cast<const float*>(hidden), static_cast<const float*>(W), ch.idx, ch.cnt,
+                     ch.c0, token_id, lse, coef, static_cast<float*>(dZ), static_cast<float*>(dZt), g.H,
+                     g.V, g.Vp, g.TC, g.n_vtiles, gate);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
@@ -1061,13 +773,7 @@ int launch_head_fe(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
                    const int32_t* token_id, const float* c2, void* E, float* part_s, float* zy, hipStream_t s) {
   ProfScope ps(PROF_HEAD_FE, s);
   if (g.dtype != AT_GRPO_BF16) return AT_GRPO_EUNSUPPORTED;
-  auto k = k_head_fe;
-  ATG_TRY(allow_big_lds(k, kFeLdsBytes));
-  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kFeLdsBytes, s, static_cast<const bf16_t*>(hidden),
-                     static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, c2, static_cast<bf16_t*>(E),
-                     part_s, zy, g.H, g.V, g.Vp, g.TC, g.n_vtiles);
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
+  return launch_fe_bf16(g, ch, hidden, W, token_id, c2, E, part_s, zy, s);
 }
 
 int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const float* part_s, const float* c2,
@@ -1104,19 +810,12 @@ int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* sca
 int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden,
                    hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DH, s);
-  if (g.dtype == AT_GRPO_BF16) {
-    auto k = k_head_dh<bf16_t, G4>;   // k = vocabulary: long loop, 4 wavefronts of 128 x 128
-    ATG_TRY(allow_big_lds(k));
-    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(G4::kThreads), kLdsBytes, s,
-                       static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(Wt), ch.idx, ch.cnt, ch.c0,
-                       static_cast<bf16_t*>(d_hidden), g.H, g.Vp, g.TC, scale, perm, live_cnt);
-  } else {
-    auto k = k_head_dh<float, G8>;
-    ATG_TRY(allow_big_lds(k));
-    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
-                       static_cast<const float*>(dZ), static_cast<const float*>(Wt), ch.idx, ch.cnt, ch.c0,
-                       static_cast<float*>(d_hidden), g.H, g.Vp, g.TC, scale, perm, live_cnt);
-  }
+  if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, Wt, d_hidden, s, scale, perm, live_cnt);
+  auto k = k_head_dh<float, G8>;
+  ATG_TRY(allow_big_lds(k, kLdsBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
+                     static_cast<const float*>(dZ), static_cast<const float*>(Wt), ch.idx, ch.cnt, ch.c0,
+                     static_cast<float*>(d_hidden), g.H, g.Vp, g.TC, scale, perm, live_cnt);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
@@ -1124,19 +823,12 @@ int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
 int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* dZt, const void* hT,
                    float* dW, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DW, s);
-  if (g.dtype == AT_GRPO_BF16) {
-    auto k = k_head_dw_km<G8>;        // 8 wavefronts: measured 4 % faster here than the 4-wavefront layout
-    ATG_TRY(allow_big_lds(k));
-    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(G8::kThreads), kLdsBytes, s, static_cast<const bf16_t*>(dZ),
-                       static_cast<const bf16_t*>(hT), ch.cnt, ch.c0, dW, g.H, g.V, g.Vp, g.TC, g.n_vtiles,
-                       accumulate, first_chunk, live_cnt);
-  } else {
-    auto k = k_head_dw<float>;
-    ATG_TRY(allow_big_lds(k));
-    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
-                       static_cast<const float*>(dZt), static_cast<const float*>(hT), ch.cnt, ch.c0, dW, g.H,
-                       g.V, g.TC, g.n_vtiles, accumulate, first_chunk);
-  }
+  if (g.dtype == AT_GRPO_BF16) return launch_dw_bf16(g, ch, dZ, hT, dW, accumulate, first_chunk, s, live_cnt);
+  auto k = k_head_dw<float>;
+  ATG_TRY(allow_big_lds(k, kLdsBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
+                     static_cast<const float*>(dZt), static_cast<const float*>(hT), ch.cnt, ch.c0, dW, g.H,
+                     g.V, g.TC, g.n_vtiles, accumulate, first_chunk);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
