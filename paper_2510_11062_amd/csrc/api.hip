@@ -76,6 +76,7 @@ struct Plan {
   void* hT;
   void* dZ;
   void* dZt;
+  void* part;        // partial tiles of split contractions (bf16)
   // one-pass forward + backward only
   TokenScratch SB, SF;   // the rows that can carry gradient / the rows with a zero advantage (own flag, cnt, idx)
   HeadGeom gF;           // geometry of the log-probability-only launches
@@ -212,6 +213,7 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
     p->coef = step ? nullptr : ws.take<float>(static_cast<size_t>(n_tok));
     p->Wt = ws.take<char>(static_cast<size_t>(g.H) * g.Vp * g.esize);
     p->hT = ws.take<char>(static_cast<size_t>(g.H) * g.TC * g.esize);
+    p->part = ws.take<char>(head_partial_bytes(g));
     p->dZ = ws.take<char>(static_cast<size_t>(g.TC) * g.Vp * g.esize);
     p->dZt = (g.dtype == AT_GRPO_F32) ? ws.take<char>(static_cast<size_t>(g.V) * g.TC * g.esize) : nullptr;
   }
@@ -393,9 +395,9 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
         char* dZ_sub = static_cast<char*>(p.dZ) + static_cast<size_t>(c1) * p.g.Vp * p.g.esize;
         ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub,
                                p.dZt, s));
-        ATG_TRY(launch_head_dh(gs, sub, dZ_sub, p.Wt, d_hidden, s));
+        ATG_TRY(launch_head_dh(gs, sub, dZ_sub, p.Wt, d_hidden, p.part, s));
       }
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.dZt, p.hT, dW[m], (accumulate_dW != 0 || c > 0) ? 1 : 0,
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.dZt, p.hT, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s));
     }
   }
@@ -470,9 +472,9 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
       // (d_hidden is zero there already); one dHidden launch over the whole super-chunk, so that the rows left
       // fill the grid evenly
       ATG_TRY(launch_compact_rows(p.g, ch, p.scale, p.dZ, p.perm, p.holes, p.movers, p.live_cnt, p.live_cnt + 1, s));
-      ATG_TRY(launch_head_dh(p.g, ch, p.dZ, p.Wt, d_hidden, s, p.scale, p.perm, p.live_cnt));
+      ATG_TRY(launch_head_dh(p.g, ch, p.dZ, p.Wt, d_hidden, p.part, s, p.scale, p.perm, p.live_cnt));
       ATG_TRY(launch_gather_transpose_hidden(p.g, ch, batch->hidden, p.hT, s, p.scale, p.perm, p.live_cnt));
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, nullptr, p.hT, dW[m], (accumulate_dW != 0 || c > 0) ? 1 : 0,
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, nullptr, p.hT, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s, p.live_cnt));
     }
   }

@@ -8,6 +8,7 @@
 #include "gemm_bf16.hpp"
 #include "head_bf16.hpp"
 #include "head_common.hpp"
+#include "split_k.hpp"
 #include "tile_order.hpp"
 
 namespace atg {
@@ -333,114 +334,245 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
   }
 }
 
+// ---- partial tiles of a split contraction (split_k.hpp), in the accumulator layout of grid G -----------------------
+template <typename G>
+__device__ __forceinline__ size_t partial_at(int slot, int wave, int i, int j, int lane) {
+  return static_cast<size_t>(slot) * (kTile16 * kTile16 / 4) + ((wave * G::kIB + i) * G::kJB + j) * 64 + lane;
+}
+
+template <typename G>
+__device__ __forceinline__ void store_partial(floatx4* part, int slot, const floatx4 (&acc)[G::kIB][G::kJB], const Coord16<G>& co) {
+#pragma unroll
+  for (int j = 0; j < G::kJB; ++j)
+#pragma unroll
+    for (int i = 0; i < G::kIB; ++i) part[partial_at<G>(slot, co.wave, i, j, co.lane)] = acc[i][j];
+}
+
+// One wavefront's column block j of split tile q: the sum of its S parts.  unit = (q * wavefronts + wave) * kJB + j.
+template <typename G>
+__device__ __forceinline__ void load_partials(floatx4 (&col)[G::kIB], const floatx4* part, const SplitK& sp, int q, int wave,
+                                              int j, int lane) {
+#pragma unroll
+  for (int i = 0; i < G::kIB; ++i) col[i] = part[partial_at<G>(q, wave, i, j, lane)];
+  for (int s = 1; s < sp.S; ++s)
+#pragma unroll
+    for (int i = 0; i < G::kIB; ++i) col[i] += part[partial_at<G>(s * sp.rest + q, wave, i, j, lane)];
+}
+
+constexpr int kReduceBlocks = 2048, kReduceThreads = 256;
+
 // ------------------------------------------------------------------------------------------------
 // dHidden: A = Wt rows (h), B = dZ / E rows (tokens), k = vocabulary
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(GDh::kThreads) void k_head_dh(const bf16_t* __restrict__ dZ, const bf16_t* __restrict__ Wt,
-                                                           const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                           int c0, bf16_t* __restrict__ d_hidden, int H, int Vp, int TC,
-                                                           const float* __restrict__ scale, const int32_t* __restrict__ perm,
-                                                           const int32_t* __restrict__ live_cnt) {
+struct DhArgs {
+  const bf16_t* dZ;
+  const bf16_t* Wt;
+  const int32_t* idx;
+  const int32_t* cnt;
+  int c0;
+  bf16_t* d_hidden;
+  int H, Vp, TC;
+  const float* scale;         // row factors of the one-pass path, or null
+  const int32_t* perm;        // after the rows were compacted: row j of dZ belongs to list position perm[j] ...
+  const int32_t* live_cnt;    // ... and only the first *live_cnt rows take part
+  floatx4* part;              // partial tiles
+};
+
+__device__ __forceinline__ int rows_of(const int32_t* live_cnt, const int32_t* cnt, int c0, int TC) {
+  const int n = chunk_count(cnt, c0, TC);
+  return live_cnt ? min(*live_cnt, n) : n;
+}
+
+__device__ __forceinline__ void dh_store(const DhArgs& a, const floatx4 (&col)[GDh::kIB], int jt, int n, int hbase, int lane) {
+  if (jt >= n) return;
+  const int jl = a.perm ? a.perm[jt] : jt;
+  const float sc = a.scale ? a.scale[jl] : 1.f;
+  bf16_t* out = a.d_hidden + static_cast<size_t>(a.idx[a.c0 + jl]) * a.H + hbase;
+#pragma unroll
+  for (int p = 0; p < GDh::kIB / 2; ++p) {
+    const int hf = pair_first(p, lane);
+    float d[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d[e] = col[2 * p + (e >> 2)][e & 3] * sc;
+    if (hbase + hf < a.H) store8(out + hf, d);
+  }
+}
+
+__device__ __forceinline__ TileOrder dh_order(int n, int H) {
+  return TileOrder{(n + kTile16 - 1) / kTile16, (H + kTile16 - 1) / kTile16, 8};
+}
+
+__global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
   using G = GDh;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  // after the rows were compacted: the first *live_cnt rows of dZ, row j belonging to list position perm[j]
-  const int n = perm ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
+  const int n = rows_of(a.perm ? a.live_cnt : nullptr, a.cnt, a.c0, a.TC);
   if (n <= 0) return;
-  const TileOrder ord{(n + kTile16 - 1) / kTile16, (H + kTile16 - 1) / kTile16, 8};
-  const uint32_t row_bytes = static_cast<uint32_t>(Vp) * 2;
+  const TileOrder ord = dh_order(n, a.H);
+  const SplitK sp = plan_split(ord.total(), a.Vp / kStepK, gridDim.x);
+  const uint32_t row_bytes = static_cast<uint32_t>(a.Vp) * 2;
+  const int items = sp.full + sp.rest * sp.S;
 
-  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+  for (int it = logical_workgroup(); it < items; it += gridDim.x) {
+    const int part = it < sp.full ? 0 : (it - sp.full) / sp.rest;
+    const int tile = it < sp.full ? it : it - part * sp.rest;
     int tt, ht;
-    ord.decode(t, &tt, &ht);
+    ord.decode(tile, &tt, &ht);
     const int t0 = tt * kTile16, h0 = ht * kTile16;
+    const bool split = it >= sp.full && sp.S > 1;
+    const int k0 = split ? part * sp.chunk : 0;
+    const int nk = split ? min(sp.chunk, a.Vp / kStepK - k0) : a.Vp / kStepK;
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
       RowPanel<G> pa, pb;
-      pa.init(reinterpret_cast<const char*>(Wt) + static_cast<size_t>(h0) * row_bytes, co.wave, co.lane,
-              [&](int row) { return static_cast<uint32_t>(min(a_index(row), H - 1 - h0)) * row_bytes; });
-      pb.init(reinterpret_cast<const char*>(dZ) + static_cast<size_t>(t0) * row_bytes, co.wave, co.lane,
+      const size_t kb = static_cast<size_t>(k0) * kStepK * 2;
+      pa.init(reinterpret_cast<const char*>(a.Wt) + static_cast<size_t>(h0) * row_bytes + kb, co.wave, co.lane,
+              [&](int row) { return static_cast<uint32_t>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
+      pb.init(reinterpret_cast<const char*>(a.dZ) + static_cast<size_t>(t0) * row_bytes + kb, co.wave, co.lane,
               [&](int row) { return static_cast<uint32_t>(row) * row_bytes; });
-      gemm16<G>(acc, pa, pb, Vp / kStepK, smem, co);
+      gemm16<G>(acc, pa, pb, nk, smem, co);
     }
     const Coord16<G> co;
-    const int hbase = h0 + co.wm * G::kRowsA;
+    if (split) {
+      store_partial<G>(a.part, it - sp.full, acc, co);
+    } else {
 #pragma unroll
-    for (int j = 0; j < G::kJB; ++j) {
-      const int jt = t0 + co.b_row(j);
-      if (jt < n) {
-        const int jl = perm ? perm[jt] : jt;
-        const float sc = scale ? scale[jl] : 1.f;     // row factor of the one-pass path
-        bf16_t* out = d_hidden + static_cast<size_t>(idx[c0 + jl]) * H + hbase;
+      for (int j = 0; j < G::kJB; ++j) {
+        floatx4 col[G::kIB];
 #pragma unroll
-        for (int p = 0; p < G::kIB / 2; ++p) {
-          const int hf = pair_first(p, co.lane);
-          float d[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) d[e] = acc[2 * p + (e >> 2)][j][e & 3] * sc;
-          if (hbase + hf < H) store8(out + hf, d);
-        }
+        for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
+        dh_store(a, col, t0 + co.b_row(j), n, h0 + co.wm * G::kRowsA, co.lane);
       }
     }
+  }
+}
+
+// adds the parts of the split tiles and finishes them; `grid` = workgroups of the contraction
+__global__ __launch_bounds__(kReduceThreads) void k_head_dh_reduce(DhArgs a, int grid) {
+  using G = GDh;
+  const int n = rows_of(a.perm ? a.live_cnt : nullptr, a.cnt, a.c0, a.TC);
+  if (n <= 0) return;
+  const TileOrder ord = dh_order(n, a.H);
+  const SplitK sp = plan_split(ord.total(), a.Vp / kStepK, grid);
+  if (sp.S <= 1) return;
+  constexpr int kWaves = G::kThreads / 64;
+  const int lane = threadIdx.x & 63;
+  const int units = sp.rest * kWaves * G::kJB;
+  for (int u = (blockIdx.x * kReduceThreads + threadIdx.x) >> 6; u < units; u += (gridDim.x * kReduceThreads) >> 6) {
+    const int j = u % G::kJB, wave = u / G::kJB % kWaves, q = u / (G::kJB * kWaves);
+    int tt, ht;
+    ord.decode(sp.full + q, &tt, &ht);
+    floatx4 col[G::kIB];
+    load_partials<G>(col, a.part, sp, q, wave, j, lane);
+    dh_store(a, col, tt * kTile16 + (wave % G::kWavesB) * G::kRowsB + j * 16 + (lane & 15), n,
+             ht * kTile16 + (wave / G::kWavesB) * G::kRowsA, lane);
   }
 }
 
 // ------------------------------------------------------------------------------------------------
 // dW[v][h] (+)= sum_t dZ[t][v] * hG[t][h]: A = hG columns (h), B = dZ columns (v), both k-major, k = tokens
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(GDw::kThreads) void k_head_dw(const bf16_t* __restrict__ dZ, const bf16_t* __restrict__ hG,
-                                                           const int32_t* __restrict__ cnt, int c0, float* __restrict__ dW,
-                                                           int H, int V, int Vp, int TC, int n_vtiles, int accumulate,
-                                                           int first_chunk, const int32_t* __restrict__ live_cnt) {
+struct DwArgs {
+  const bf16_t* dZ;
+  const bf16_t* hG;
+  const int32_t* cnt;
+  int c0;
+  float* dW;
+  int H, V, Vp, TC, n_vtiles, accumulate, first_chunk;
+  const int32_t* live_cnt;    // or null: the rows were compacted, only the first *live_cnt take part
+  floatx4* part;              // partial tiles
+};
+
+__device__ __forceinline__ void dw_store(const DwArgs& a, const floatx4 (&col)[GDw::kIB], int v, int hb, int lane) {
+  if (v >= a.V) return;
+  floatx4* out = reinterpret_cast<floatx4*>(a.dW + static_cast<size_t>(v) * a.H + hb + 4 * (lane >> 4));
+  if (hb + GDw::kRowsA <= a.H) {     // a whole block of 16 columns exists or does not (H % 64 == 0)
+    floatx4 x[GDw::kIB];
+#pragma unroll
+    for (int i = 0; i < GDw::kIB; ++i) x[i] = col[i];
+    if (a.accumulate) {
+#pragma unroll
+      for (int i = 0; i < GDw::kIB; ++i) x[i] += out[i * 4];
+    }
+#pragma unroll
+    for (int i = 0; i < GDw::kIB; ++i) out[i * 4] = x[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < GDw::kIB; ++i)
+      if (hb + i * 16 < a.H) out[i * 4] = a.accumulate ? out[i * 4] + col[i] : col[i];
+  }
+}
+
+// bands of 32 / (tiles along H) vocabulary tiles: the 32 workgroups that share an XCD's L2 then cover every
+// H-tile of the same few vocabulary tiles, and each panel of the large operand (the 10 GB of dZ rows)
+// is fetched by one XCD only (measured 2.4 % faster than bands of 8)
+__device__ __forceinline__ TileOrder dw_order(int n_vtiles, int H) {
+  const int n_htiles = (H + kTile16 - 1) / kTile16;
+  return TileOrder{n_vtiles, n_htiles, max(1, 32 / n_htiles)};
+}
+
+__global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
   using G = GDw;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  // live_cnt: the rows were compacted, only the first *live_cnt of the chunk take part
-  const int n = live_cnt ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
-  if (n <= 0 && !(first_chunk && !accumulate)) return;
-  // bands of 32 / (tiles along H) vocabulary tiles: the 32 workgroups that share an XCD's L2 then cover every
-  // H-tile of the same few vocabulary tiles, and each panel of the large operand (the 10 GB of dZ rows)
-  // is fetched by one XCD only (measured 2.4 % faster than bands of 8)
-  const int n_htiles = (H + kTile16 - 1) / kTile16;
-  const TileOrder ord{n_vtiles, n_htiles, max(1, 32 / n_htiles)};
-  const int nk = (n + kTile16 - 1) / kTile16 * (kTile16 / kStepK);
+  const int n = rows_of(a.live_cnt, a.cnt, a.c0, a.TC);
+  if (n <= 0 && !(a.first_chunk && !a.accumulate)) return;
+  const TileOrder ord = dw_order(a.n_vtiles, a.H);
+  const int nk_all = (n + kTile16 - 1) / kTile16 * (kTile16 / kStepK);
+  const SplitK sp = plan_split(ord.total(), nk_all, gridDim.x);
+  const int items = sp.full + sp.rest * sp.S;
 
-  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
+  for (int it = logical_workgroup(); it < items; it += gridDim.x) {
+    const int part = it < sp.full ? 0 : (it - sp.full) / sp.rest;
+    const int tile = it < sp.full ? it : it - part * sp.rest;
     int vt, ht;
-    ord.decode(t, &vt, &ht);
+    ord.decode(tile, &vt, &ht);
     const int v0 = vt * kTile16, h0 = ht * kTile16;
+    const bool split = it >= sp.full && sp.S > 1;
+    const int k0 = split ? part * sp.chunk : 0;
+    const int nk = split ? min(sp.chunk, nk_all - k0) : nk_all;
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
       KMajorPanel<G> pa, pb;
-      pa.init(reinterpret_cast<const char*>(hG + h0), co.wave, co.lane, static_cast<size_t>(H) * 2, min(31, (H - h0) / 8 - 1));
-      pb.init(reinterpret_cast<const char*>(dZ + v0), co.wave, co.lane, static_cast<size_t>(Vp) * 2, min(31, (Vp - v0) / 8 - 1));
+      pa.init(reinterpret_cast<const char*>(a.hG + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
+              static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1));
+      pb.init(reinterpret_cast<const char*>(a.dZ + static_cast<size_t>(k0) * kStepK * a.Vp + v0), co.wave, co.lane,
+              static_cast<size_t>(a.Vp) * 2, min(31, (a.Vp - v0) / 8 - 1));
       gemm16<G>(acc, pa, pb, nk, smem, co);
     }
     const Coord16<G> co;
-    const int hb = h0 + co.wm * G::kRowsA;     // a whole block of 16 columns exists or does not (H % 64 == 0)
-    const bool interior = hb + G::kRowsA <= H;
+    if (split) {
+      store_partial<G>(a.part, it - sp.full, acc, co);
+    } else {
 #pragma unroll
-    for (int j = 0; j < G::kJB; ++j) {
-      const int v = v0 + co.b_row(j);
-      if (v < V) {
-        floatx4* out = reinterpret_cast<floatx4*>(dW + static_cast<size_t>(v) * H + hb + 4 * (co.lane >> 4));
-        if (interior) {
-          floatx4 x[G::kIB];
+      for (int j = 0; j < G::kJB; ++j) {
+        floatx4 col[G::kIB];
 #pragma unroll
-          for (int i = 0; i < G::kIB; ++i) x[i] = acc[i][j];
-          if (accumulate) {
-#pragma unroll
-            for (int i = 0; i < G::kIB; ++i) x[i] += out[i * 4];
-          }
-#pragma unroll
-          for (int i = 0; i < G::kIB; ++i) out[i * 4] = x[i];
-        } else {
-#pragma unroll
-          for (int i = 0; i < G::kIB; ++i)
-            if (hb + i * 16 < H) out[i * 4] = accumulate ? out[i * 4] + acc[i][j] : acc[i][j];
-        }
+        for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
+        dw_store(a, col, v0 + co.b_row(j), h0 + co.wm * G::kRowsA, co.lane);
       }
     }
+  }
+}
+
+__global__ __launch_bounds__(kReduceThreads) void k_head_dw_reduce(DwArgs a, int grid) {
+  using G = GDw;
+  const int n = rows_of(a.live_cnt, a.cnt, a.c0, a.TC);
+  if (n <= 0) return;
+  const TileOrder ord = dw_order(a.n_vtiles, a.H);
+  const SplitK sp = plan_split(ord.total(), (n + kTile16 - 1) / kTile16 * (kTile16 / kStepK), grid);
+  if (sp.S <= 1) return;
+  constexpr int kWaves = G::kThreads / 64;
+  const int lane = threadIdx.x & 63;
+  const int units = sp.rest * kWaves * G::kJB;
+  for (int u = (blockIdx.x * kReduceThreads + threadIdx.x) >> 6; u < units; u += (gridDim.x * kReduceThreads) >> 6) {
+    const int j = u % G::kJB, wave = u / G::kJB % kWaves, q = u / (G::kJB * kWaves);
+    int vt, ht;
+    ord.decode(sp.full + q, &vt, &ht);
+    floatx4 col[G::kIB];
+    load_partials<G>(col, a.part, sp, q, wave, j, lane);
+    dw_store(a, col, vt * kTile16 + (wave % G::kWavesB) * G::kRowsB + j * 16 + (lane & 15),
+             ht * kTile16 + (wave / G::kWavesB) * G::kRowsA, lane);
   }
 }
 
@@ -480,22 +612,26 @@ int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
   return AT_GRPO_OK;
 }
 
-int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, hipStream_t s,
-                   const float* scale, const int32_t* perm, const int32_t* live_cnt) {
+int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, void* part,
+                   hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ATG_TRY(allow_big_lds(k_head_dh, kRingBytes));
-  hipLaunchKernelGGL(k_head_dh, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, static_cast<const bf16_t*>(dZ),
-                     static_cast<const bf16_t*>(Wt), ch.idx, ch.cnt, ch.c0, static_cast<bf16_t*>(d_hidden), g.H, g.Vp, g.TC,
-                     scale, perm, live_cnt);
+  const DhArgs a{static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(Wt), ch.idx, ch.cnt, ch.c0,
+                 static_cast<bf16_t*>(d_hidden), g.H, g.Vp, g.TC, scale, perm, live_cnt, static_cast<floatx4*>(part)};
+  hipLaunchKernelGGL(k_head_dh, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
+  ATG_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_head_dh_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, a, gemm_grid());
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
 
-int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, int accumulate,
-                   int first_chunk, hipStream_t s, const int32_t* live_cnt) {
+int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, void* part,
+                   int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
   ATG_TRY(allow_big_lds(k_head_dw, kRingBytes));
-  hipLaunchKernelGGL(k_head_dw, dim3(gemm_grid()), dim3(GDw::kThreads), kRingBytes, s, static_cast<const bf16_t*>(dZ),
-                     static_cast<const bf16_t*>(hG), ch.cnt, ch.c0, dW, g.H, g.V, g.Vp, g.TC, g.n_vtiles, accumulate,
-                     first_chunk, live_cnt);
+  const DwArgs a{static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(hG), ch.cnt, ch.c0, dW, g.H, g.V, g.Vp, g.TC,
+                 g.n_vtiles, accumulate, first_chunk, live_cnt, static_cast<floatx4*>(part)};
+  hipLaunchKernelGGL(k_head_dw, dim3(gemm_grid()), dim3(GDw::kThreads), kRingBytes, s, a);
+  ATG_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_head_dw_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, a, gemm_grid());
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

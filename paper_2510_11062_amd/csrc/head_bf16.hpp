@@ -1,4 +1,5 @@
-// Launchers of the bf16 head contractions (see head_kernels.hpp for the meaning of the arguments).
+// Launchers of the bf16 head contractions (see head_kernels.hpp for the meaning of the arguments).  `part`: room for
+// the partial tiles of a split contraction, head_partial_bytes() of it.
 #pragma once
 
 #include "head_kernels.hpp"
@@ -11,9 +12,9 @@ int launch_fe_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
                    const float* c2, void* E, float* part_s, float* zy, hipStream_t s);
 int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
                    const float* lse, const float* coef, void* dZ, hipStream_t s, const int32_t* gate);
-int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, hipStream_t s,
-                   const float* scale, const int32_t* perm, const int32_t* live_cnt);
-int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, int accumulate,
-                   int first_chunk, hipStream_t s, const int32_t* live_cnt);
+int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, void* part,
+                   hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt);
+int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, void* part,
+                   int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt);
 
 }  // namespace atg

@@ -15,6 +15,7 @@
 #include "gemm_core.hpp"
 #include "head_bf16.hpp"
 #include "head_common.hpp"
+#include "split_k.hpp"
 #include "tile_order.hpp"
 #include "token_kernels.hpp"
 
@@ -848,10 +849,16 @@ int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* sca
   return AT_GRPO_OK;
 }
 
+size_t head_partial_bytes(const HeadGeom& g) {
+  if (g.dtype != AT_GRPO_BF16) return 0;
+  const int64_t ht = ceil_div(g.H, 256), dh = g.TC / 256 * ht, dw = g.n_vtiles * ht;
+  return split_k_bytes(dh > dw ? dh : dw);
+}
+
 int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden,
-                   hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
+                   void* part, hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DH, s);
-  if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, Wt, d_hidden, s, scale, perm, live_cnt);
+  if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, Wt, d_hidden, part, s, scale, perm, live_cnt);
   auto k = k_head_dh<float, G8>;
   ATG_TRY(allow_big_lds(k, kLdsBytes));
   hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
@@ -862,9 +869,9 @@ int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
 }
 
 int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* dZt, const void* hT,
-                   float* dW, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
+                   float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DW, s);
-  if (g.dtype == AT_GRPO_BF16) return launch_dw_bf16(g, ch, dZ, hT, dW, accumulate, first_chunk, s, live_cnt);
+  if (g.dtype == AT_GRPO_BF16) return launch_dw_bf16(g, ch, dZ, hT, dW, part, accumulate, first_chunk, s, live_cnt);
   auto k = k_head_dw<float>;
   ATG_TRY(allow_big_lds(k, kLdsBytes));
   hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,

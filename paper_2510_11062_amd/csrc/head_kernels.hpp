@@ -52,6 +52,9 @@ int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
                    const int32_t* token_id, const float* lse, const float* coef, void* dZ, void* dZt,
                    hipStream_t s, const int32_t* gate = nullptr);
 
+// Scratch for the partial tiles of launch_head_dh / launch_head_dw over g.TC rows.
+size_t head_partial_bytes(const HeadGeom& g);
+
 // ---- forward and backward from one pass over the logits (bf16) ---------------------------------------
 // A `gate` argument of the launchers above and below is a device word: with a non-null gate the kernel
 // returns at once while the word is 0 (coef == null in launch_head_dz: dZ = softmax - onehot).
@@ -78,8 +81,9 @@ int launch_fallback_scale(const HeadGeom& g, const HeadChunk& ch, int head, cons
 // d_hidden[row] = dZ[j] . Wt^T for the rows of this super-chunk.
 // With `scale`, row j of the result is multiplied by scale[j] (j counted from ch.c0).  With `perm` (after
 // launch_compact_rows), the first *live_cnt rows of dZ are contracted and row j goes to list position perm[j].
+// `part`: head_partial_bytes() of scratch for bf16 (partial tiles of the contraction), unused for fp32.
 int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt,
-                   void* d_hidden, hipStream_t s, const float* scale = nullptr, const int32_t* perm = nullptr,
+                   void* d_hidden, void* part, hipStream_t s, const float* scale = nullptr, const int32_t* perm = nullptr,
                    const int32_t* live_cnt = nullptr);
 
 // Takes the rows with scale[j] == 0 out of a super-chunk of E (bf16, TC <= 32768): rows from the tail are
@@ -92,6 +96,6 @@ int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* sca
 // dW[V][H] (+)= dZ^T . hidden rows.  first_chunk: runs even for an empty list so that dW is defined.
 // bf16 with `live_cnt`: only the first *live_cnt rows of the chunk are contracted.
 int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* dZt, const void* hT,
-                   float* dW, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt = nullptr);
+                   float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt = nullptr);
 
 }  // namespace atg
