@@ -211,7 +211,7 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
   }
   if (bwd) {
     p->coef = step ? nullptr : ws.take<float>(static_cast<size_t>(n_tok));
-    p->Wt = ws.take<char>(static_cast<size_t>(g.H) * g.Vp * g.esize);
+    p->Wt = needs_transposed_w(g, n_tok) ? ws.take<char>(static_cast<size_t>(g.H) * g.Vp * g.esize) : nullptr;
     p->hT = ws.take<char>(static_cast<size_t>(g.H) * g.TC * g.esize);
     p->part = ws.take<char>(head_partial_bytes(g));
     p->dZ = ws.take<char>(static_cast<size_t>(g.TC) * g.Vp * g.esize);
@@ -384,7 +384,7 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
   ATG_TRY(launch_fill_bytes16(d_hidden, p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize, s));
 
   for (int m = 0; m < batch->n_heads; ++m) {
-    ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, s));
+    ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, p.S.cnt + m, s));
     for (int c = 0; c < p.n_chunks; ++c) {
       const HeadChunk ch{p.S.idx + static_cast<size_t>(m) * p.L.n_tok, p.S.cnt + m, c * p.g.TC};
       ATG_TRY(launch_gather_transpose_hidden(p.g, ch, batch->hidden, p.hT, s));
@@ -395,7 +395,7 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
         char* dZ_sub = static_cast<char*>(p.dZ) + static_cast<size_t>(c1) * p.g.Vp * p.g.esize;
         ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub,
                                p.dZt, s));
-        ATG_TRY(launch_head_dh(gs, sub, dZ_sub, p.Wt, d_hidden, p.part, s));
+        ATG_TRY(launch_head_dh(gs, sub, dZ_sub, batch->W[m], p.Wt, d_hidden, p.part, s));
       }
       ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.dZt, p.hT, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s));
@@ -445,7 +445,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
 
   int gate_no = 0;
   for (int m = 0; m < batch->n_heads; ++m) {
-    ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, s));
+    ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, p.SB.cnt + m, s));
     for (int c = 0; c < p.n_chunks; ++c) {
       const HeadChunk ch{p.SB.idx + static_cast<size_t>(m) * p.L.n_tok, p.SB.cnt + m, c * p.g.TC};
       HeadGeom gs = p.g;
@@ -472,7 +472,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
       // (d_hidden is zero there already); one dHidden launch over the whole super-chunk, so that the rows left
       // fill the grid evenly
       ATG_TRY(launch_compact_rows(p.g, ch, p.scale, p.dZ, p.perm, p.holes, p.movers, p.live_cnt, p.live_cnt + 1, s));
-      ATG_TRY(launch_head_dh(p.g, ch, p.dZ, p.Wt, d_hidden, p.part, s, p.scale, p.perm, p.live_cnt));
+      ATG_TRY(launch_head_dh(p.g, ch, p.dZ, batch->W[m], p.Wt, d_hidden, p.part, s, p.scale, p.perm, p.live_cnt));
       ATG_TRY(launch_gather_transpose_hidden(p.g, ch, batch->hidden, p.hT, s, p.scale, p.perm, p.live_cnt));
       ATG_TRY(launch_head_dw(p.g, ch, p.dZ, nullptr, p.hT, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s, p.live_cnt));

@@ -167,6 +167,49 @@ struct KMajorPanel {
   __device__ __forceinline__ void advance() { base += step; }
 };
 
+// k-major with a number of k-rows that need not be a multiple of 64: rows past the last are fetched from the last one (the
+// other operand is zero there)
+template <typename G>
+struct KMajorTailPanel {
+  static constexpr bool kKMajor = true;
+  const char* base;
+  uint32_t off[G::kLoads];
+  size_t ld;
+  int rows, wave, lane, cmax;     // k-rows left from `base` on
+  __device__ __forceinline__ void init(const char* b, int wave_, int lane_, size_t ld_, int cmax_, int rows_) {
+    base = uniform_ptr(b);
+    ld = ld_;
+    rows = rows_;
+    wave = wave_;
+    lane = lane_;
+    cmax = cmax_;
+    offsets();
+  }
+  __device__ __forceinline__ void offsets() {
+#pragma unroll
+    for (int q = 0; q < G::kLoads; ++q) {
+      const int k = (wave * G::kLoads + q) * 2 + (lane >> 5);
+      const int P = lane & 31, s = (k & 3) | (((k >> 3) & 1) << 2);
+      const int C = (P & 16) | ((P ^ (2 * s)) & 15);
+      off[q] = static_cast<uint32_t>(max(min(k, rows - 1), 0) * ld) + min(C, cmax) * 16;
+    }
+  }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_s(base, off[q], lds); }
+  __device__ __forceinline__ void advance() {
+    base += ld * kStepK;
+    rows -= kStepK;
+    if (rows < kStepK) offsets();
+  }
+};
+
+// Transposing read: inside each group of 16 lanes, lane 4 r + q names 4 consecutive columns of row r, and lane i receives
+// column i of the four rows.
+__device__ __forceinline__ uint2 lds_read_tr(const char* p) {
+  const bf16v4 v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+      (__attribute__((address_space(3))) bf16v4*)(__attribute__((address_space(3))) const char*)p);
+  return __builtin_bit_cast(uint2, v);
+}
+
 // Fragment reads of one operand: NB blocks of 16 rows starting at tile row `row0`.
 template <int NB, bool KM>
 struct FragReader;
@@ -205,14 +248,9 @@ struct FragReader<NB, true> {
 #pragma unroll
     for (int b = 0; b < NB; ++b) cur[b] = at[b] + byte;
   }
-  __device__ __forceinline__ uint2 tr(const char* p) const {
-    const bf16v4 v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-        (__attribute__((address_space(3))) bf16v4*)(__attribute__((address_space(3))) const char*)p);
-    return __builtin_bit_cast(uint2, v);
-  }
   __device__ __forceinline__ uint4 read(const char* smem, int ks, int blk) const {
     const char* p = smem + cur[blk] + ks * 32 * (kTile16 * 2);
-    const uint2 lo = tr(p), hi = tr(p + 4 * (kTile16 * 2));
+    const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * (kTile16 * 2));
     return make_uint4(lo.x, lo.y, hi.x, hi.y);
   }
 };

@@ -362,16 +362,62 @@ __device__ __forceinline__ void load_partials(floatx4 (&col)[G::kIB], const floa
 constexpr int kReduceBlocks = 2048, kReduceThreads = 256;
 
 // ------------------------------------------------------------------------------------------------
-// dHidden: A = Wt rows (h), B = dZ / E rows (tokens), k = vocabulary
+// Wt[h][v] = W[v][h], zero for V <= v < Vp: tiles of 64 v x 128 h through LDS, turned by the transposing LDS read (four
+// v of one h per lane and read).  Loads are 256-byte runs of W, stores 128-byte runs of Wt.  Bound by memory: 2.49 GB
+// in 487 us at V = 151936, H = 4096 (963 us with 64 x 64 tiles and 2-byte accesses).
 // ------------------------------------------------------------------------------------------------
+constexpr int kTpThreads = 256, kTpV = 64, kTpH = 128;
+
+__global__ __launch_bounds__(kTpThreads) void k_transpose_w(const bf16_t* __restrict__ W, int V, int Vp, int H,
+                                                            bf16_t* __restrict__ Wt, const int32_t* __restrict__ cnt,
+                                                            int min_rows) {
+  __shared__ __attribute__((aligned(16))) char tile[kTpV * kTpH * 2];
+  if (*cnt <= min_rows) return;       // dHidden reads W itself
+  const int v0 = blockIdx.x * kTpV, h0 = blockIdx.y * kTpH;
+  const int c = threadIdx.x & 15;     // 16-byte chunk of a row
+#pragma unroll
+  for (int p = 0; p < kTpV / 16; ++p) {
+    const int k = p * 16 + (threadIdx.x >> 4), s = (k & 3) | (((k >> 3) & 1) << 2);
+    uint4 x = make_uint4(0, 0, 0, 0);
+    if (v0 + k < V && h0 + c * 8 < H) x = *reinterpret_cast<const uint4*>(W + static_cast<size_t>(v0 + k) * H + h0 + c * 8);
+    *reinterpret_cast<uint4*>(tile + k * (kTpH * 2) + ((c ^ (2 * s)) & 15) * 16) = x;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, r = (lane & 15) >> 2, q = lane & 3;
+  const int k = 8 * g + r, s = (k & 3) | (((k >> 3) & 1) << 2);
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int hb = (wave + 4 * b) * 16, h = h0 + hb + (lane & 15);
+    const int cc = hb / 8 + (q >> 1);
+    const char* at = tile + k * (kTpH * 2) + ((cc ^ (2 * s)) & 15) * 16 + (q & 1) * 8;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const uint2 lo = lds_read_tr(at + half * 32 * (kTpH * 2)), hi = lds_read_tr(at + (half * 32 + 4) * (kTpH * 2));
+      if (h < H)
+        *reinterpret_cast<uint4*>(Wt + static_cast<size_t>(h) * Vp + v0 + half * 32 + g * 8) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// dHidden: A = columns of W (h), B = dZ / E rows (tokens), k = vocabulary.
+// For many rows W is transposed first and both operands are contiguous along k (1500 TFLOP/s); for few rows the
+// contraction reads W as it stands, k-major (1430 TFLOP/s), and the transposition is saved.  Per weight the
+// transposition moves 4 bytes (0.9 ps of the chip's memory time), the slower loop costs 0.07 fs per row: the
+// two meet at 12 600 rows of a head.
+// ------------------------------------------------------------------------------------------------
+constexpr int kUntransposedRows = 12288;
+
 struct DhArgs {
   const bf16_t* dZ;
-  const bf16_t* Wt;
+  const bf16_t* W;            // [V][H]
+  const bf16_t* Wt;           // [H][Vp], read when the head has more than kUntransposedRows rows
   const int32_t* idx;
   const int32_t* cnt;
   int c0;
   bf16_t* d_hidden;
-  int H, Vp, TC;
+  int H, V, Vp, TC;
   const float* scale;         // row factors of the one-pass path, or null
   const int32_t* perm;        // after the rows were compacted: row j of dZ belongs to list position perm[j] ...
   const int32_t* live_cnt;    // ... and only the first *live_cnt rows take part
@@ -383,18 +429,30 @@ __device__ __forceinline__ int rows_of(const int32_t* live_cnt, const int32_t* c
   return live_cnt ? min(*live_cnt, n) : n;
 }
 
+// T: the launch works on transposed weights.  Lane outputs of a block column: with a_index() on the rows of Wt pairs of
+// blocks are eight consecutive h; columns of W are taken as they are, four consecutive h per block.
+template <bool T>
 __device__ __forceinline__ void dh_store(const DhArgs& a, const floatx4 (&col)[GDh::kIB], int jt, int n, int hbase, int lane) {
   if (jt >= n) return;
   const int jl = a.perm ? a.perm[jt] : jt;
   const float sc = a.scale ? a.scale[jl] : 1.f;
   bf16_t* out = a.d_hidden + static_cast<size_t>(a.idx[a.c0 + jl]) * a.H + hbase;
+  if (T) {
 #pragma unroll
-  for (int p = 0; p < GDh::kIB / 2; ++p) {
-    const int hf = pair_first(p, lane);
-    float d[8];
+    for (int p = 0; p < GDh::kIB / 2; ++p) {
+      const int hf = pair_first(p, lane);
+      float d[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) d[e] = col[2 * p + (e >> 2)][e & 3] * sc;
-    if (hbase + hf < a.H) store8(out + hf, d);
+      for (int e = 0; e < 8; ++e) d[e] = col[2 * p + (e >> 2)][e & 3] * sc;
+      if (hbase + hf < a.H) store8(out + hf, d);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < GDh::kIB; ++i) {
+      const int hf = i * 16 + 4 * (lane >> 4);
+      const floatx4 d = col[i] * sc;
+      if (hbase + hf < a.H) *reinterpret_cast<uint2*>(out + hf) = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
+    }
   }
 }
 
@@ -402,13 +460,16 @@ __device__ __forceinline__ TileOrder dh_order(int n, int H) {
   return TileOrder{(n + kTile16 - 1) / kTile16, (H + kTile16 - 1) / kTile16, 8};
 }
 
+template <bool T>
 __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
   using G = GDh;
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  if ((*a.cnt > kUntransposedRows) != T) return;
   const int n = rows_of(a.perm ? a.live_cnt : nullptr, a.cnt, a.c0, a.TC);
   if (n <= 0) return;
   const TileOrder ord = dh_order(n, a.H);
-  const SplitK sp = plan_split(ord.total(), a.Vp / kStepK, gridDim.x);
+  const int nk_all = a.Vp / kStepK;
+  const SplitK sp = plan_split(ord.total(), nk_all, gridDim.x);
   const uint32_t row_bytes = static_cast<uint32_t>(a.Vp) * 2;
   const int items = sp.full + sp.rest * sp.S;
 
@@ -420,17 +481,25 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
     const int t0 = tt * kTile16, h0 = ht * kTile16;
     const bool split = it >= sp.full && sp.S > 1;
     const int k0 = split ? part * sp.chunk : 0;
-    const int nk = split ? min(sp.chunk, a.Vp / kStepK - k0) : a.Vp / kStepK;
+    const int nk = split ? min(sp.chunk, nk_all - k0) : nk_all;
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
-      RowPanel<G> pa, pb;
+      RowPanel<G> pb;
       const size_t kb = static_cast<size_t>(k0) * kStepK * 2;
-      pa.init(reinterpret_cast<const char*>(a.Wt) + static_cast<size_t>(h0) * row_bytes + kb, co.wave, co.lane,
-              [&](int row) { return static_cast<uint32_t>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
       pb.init(reinterpret_cast<const char*>(a.dZ) + static_cast<size_t>(t0) * row_bytes + kb, co.wave, co.lane,
               [&](int row) { return static_cast<uint32_t>(row) * row_bytes; });
-      gemm16<G>(acc, pa, pb, nk, smem, co);
+      if constexpr (T) {
+        RowPanel<G> pa;
+        pa.init(reinterpret_cast<const char*>(a.Wt) + static_cast<size_t>(h0) * row_bytes + kb, co.wave, co.lane,
+                [&](int row) { return static_cast<uint32_t>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
+        gemm16<G>(acc, pa, pb, nk, smem, co);
+      } else {
+        KMajorTailPanel<G> pa;
+        pa.init(reinterpret_cast<const char*>(a.W + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
+                static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1), a.V - k0 * kStepK);
+        gemm16<G>(acc, pa, pb, nk, smem, co);
+      }
     }
     const Coord16<G> co;
     if (split) {
@@ -441,7 +510,7 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
         floatx4 col[G::kIB];
 #pragma unroll
         for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
-        dh_store(a, col, t0 + co.b_row(j), n, h0 + co.wm * G::kRowsA, co.lane);
+        dh_store<T>(a, col, t0 + co.b_row(j), n, h0 + co.wm * G::kRowsA, co.lane);
       }
     }
   }
@@ -455,6 +524,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_head_dh_reduce(DhArgs a, int
   const TileOrder ord = dh_order(n, a.H);
   const SplitK sp = plan_split(ord.total(), a.Vp / kStepK, grid);
   if (sp.S <= 1) return;
+  const bool transposed = *a.cnt > kUntransposedRows;
   constexpr int kWaves = G::kThreads / 64;
   const int lane = threadIdx.x & 63;
   const int units = sp.rest * kWaves * G::kJB;
@@ -464,8 +534,10 @@ __global__ __launch_bounds__(kReduceThreads) void k_head_dh_reduce(DhArgs a, int
     ord.decode(sp.full + q, &tt, &ht);
     floatx4 col[G::kIB];
     load_partials<G>(col, a.part, sp, q, wave, j, lane);
-    dh_store(a, col, tt * kTile16 + (wave % G::kWavesB) * G::kRowsB + j * 16 + (lane & 15), n,
-             ht * kTile16 + (wave / G::kWavesB) * G::kRowsA, lane);
+    const int jt = tt * kTile16 + (wave % G::kWavesB) * G::kRowsB + j * 16 + (lane & 15);
+    const int hbase = ht * kTile16 + (wave / G::kWavesB) * G::kRowsA;
+    if (transposed) dh_store<true>(a, col, jt, n, hbase, lane);
+    else dh_store<false>(a, col, jt, n, hbase, lane);
   }
 }
 
@@ -612,13 +684,32 @@ int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
   return AT_GRPO_OK;
 }
 
-int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden, void* part,
-                   hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
-  ATG_TRY(allow_big_lds(k_head_dh, kRingBytes));
-  const DhArgs a{static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(Wt), ch.idx, ch.cnt, ch.c0,
-                 static_cast<bf16_t*>(d_hidden), g.H, g.Vp, g.TC, scale, perm, live_cnt, static_cast<floatx4*>(part)};
-  hipLaunchKernelGGL(k_head_dh, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
+bool transposes_w_bf16(int64_t n_tok) { return n_tok > kUntransposedRows; }
+
+int launch_transpose_w_bf16(const HeadGeom& g, const void* W, void* Wt, const int32_t* cnt, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(ceil_div(g.Vp, kTpV)), static_cast<unsigned>(ceil_div(g.H, kTpH)));
+  hipLaunchKernelGGL(k_transpose_w, grid, dim3(kTpThreads), 0, s, static_cast<const bf16_t*>(W), g.V, g.Vp, g.H,
+                     static_cast<bf16_t*>(Wt), cnt, kUntransposedRows);
   ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* Wt, void* d_hidden,
+                   void* part, hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
+  const DhArgs a{static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(W), static_cast<const bf16_t*>(Wt), ch.idx,
+                 ch.cnt, ch.c0, static_cast<bf16_t*>(d_hidden), g.H, g.V, g.Vp, g.TC, scale, perm, live_cnt,
+                 static_cast<floatx4*>(part)};
+  // which of the two has work is only known on the device, unless the list is too short or the chunk too far behind
+  if (Wt) {
+    ATG_TRY(allow_big_lds(k_head_dh<true>, kRingBytes));
+    hipLaunchKernelGGL(k_head_dh<true>, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
+    ATG_LAUNCH_CHECK();
+  }
+  if (ch.c0 < kUntransposedRows) {
+    ATG_TRY(allow_big_lds(k_head_dh<false>, kRingBytes));
+    hipLaunchKernelGGL(k_head_dh<false>, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
+    ATG_LAUNCH_CHECK();
+  }
   hipLaunchKernelGGL(k_head_dh_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, a, gemm_grid());
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;

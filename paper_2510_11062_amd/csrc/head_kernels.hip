@@ -754,17 +754,17 @@ int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part
   return AT_GRPO_OK;
 }
 
-int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, hipStream_t s) {
+bool needs_transposed_w(const HeadGeom& g, int64_t n_tok) {
+  return g.dtype != AT_GRPO_BF16 || transposes_w_bf16(n_tok);
+}
+
+int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, const int32_t* cnt, hipStream_t s) {
   ProfScope ps(PROF_TRANSPOSE, s);
+  if (g.dtype == AT_GRPO_BF16) return Wt ? launch_transpose_w_bf16(g, W, Wt, cnt, s) : AT_GRPO_OK;
   dim3 grid(static_cast<unsigned>(ceil_div(g.Vp, 64)), static_cast<unsigned>(ceil_div(g.H, 64)));
-  if (g.dtype == AT_GRPO_BF16)
-    hipLaunchKernelGGL(k_transpose<bf16_t>, grid, dim3(256), 0, s, static_cast<const bf16_t*>(W),
-                       static_cast<int64_t>(g.H), nullptr, nullptr, 0, 0, g.V, g.Vp, g.H,
-                       static_cast<bf16_t*>(Wt), static_cast<int64_t>(g.Vp));
-  else
-    hipLaunchKernelGGL(k_transpose<float>, grid, dim3(256), 0, s, static_cast<const float*>(W),
-                       static_cast<int64_t>(g.H), nullptr, nullptr, 0, 0, g.V, g.Vp, g.H,
-                       static_cast<float*>(Wt), static_cast<int64_t>(g.Vp));
+  hipLaunchKernelGGL(k_transpose<float>, grid, dim3(256), 0, s, static_cast<const float*>(W),
+                     static_cast<int64_t>(g.H), nullptr, nullptr, 0, 0, g.V, g.Vp, g.H,
+                     static_cast<float*>(Wt), static_cast<int64_t>(g.Vp));
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
@@ -855,10 +855,10 @@ size_t head_partial_bytes(const HeadGeom& g) {
   return split_k_bytes(dh > dw ? dh : dw);
 }
 
-int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt, void* d_hidden,
+int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* Wt, void* d_hidden,
                    void* part, hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DH, s);
-  if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, Wt, d_hidden, part, s, scale, perm, live_cnt);
+  if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, W, Wt, d_hidden, part, s, scale, perm, live_cnt);
   auto k = k_head_dh<float, G8>;
   ATG_TRY(allow_big_lds(k, kLdsBytes));
   hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,

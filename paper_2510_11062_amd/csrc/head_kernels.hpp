@@ -36,8 +36,10 @@ int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part
                        const float* part_s, const float* part_u, const float* zy, float* logp,
                        float* lse, float* entropy, hipStream_t s, const int32_t* gate = nullptr);
 
-// Wt[H][Vp] = W[V][H]^T, zero in the k padding.
-int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, hipStream_t s);
+// Wt[H][Vp] = W[V][H]^T, zero in the k padding.  bf16: a head with few rows (*cnt of its list) is left untransposed, and
+// needs_transposed_w() == false for a batch of n_tok rows says that every head is (Wt may then be null).
+bool needs_transposed_w(const HeadGeom& g, int64_t n_tok);
+int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, const int32_t* cnt, hipStream_t s);
 
 // fp32: hT[H][TC] = (gathered hidden rows of this super-chunk)^T, zero for columns past the count.
 // bf16: hT[TC][H] = the gathered rows themselves, zero rows up to the next multiple of 256.
@@ -78,11 +80,11 @@ int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const fl
 int launch_fallback_scale(const HeadGeom& g, const HeadChunk& ch, int head, const CoefArgs& ca, const float* logp,
                           float* scale, const int32_t* gate, hipStream_t s);
 
-// d_hidden[row] = dZ[j] . Wt^T for the rows of this super-chunk.
+// d_hidden[row] = dZ[j] . W for the rows of this super-chunk.
 // With `scale`, row j of the result is multiplied by scale[j] (j counted from ch.c0).  With `perm` (after
 // launch_compact_rows), the first *live_cnt rows of dZ are contracted and row j goes to list position perm[j].
 // `part`: head_partial_bytes() of scratch for bf16 (partial tiles of the contraction), unused for fp32.
-int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* Wt,
+int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* Wt,
                    void* d_hidden, void* part, hipStream_t s, const float* scale = nullptr, const int32_t* perm = nullptr,
                    const int32_t* live_cnt = nullptr);
 

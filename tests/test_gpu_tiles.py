@@ -1,0 +1,41 @@
+"""Head contractions at the sizes where the launch plan changes: last tiles of every dimension, tiles split along k,
+weights read transposed or as they stand.  One-pass step and two-call sequence against the CPU oracle with the bf16
+tolerances of tests/test_gpu_parity.py (the logit gradient and d_hidden are rounded to bf16, 2^-9 per element,
+against 2e-2)."""
+from dataclasses import replace
+
+import pytest
+import torch
+
+from paper_2510_11062_amd import api, synth
+from tests import helpers
+from tests.gpu_case import DeviceCase
+from tests.test_gpu_onepass import check_step_against_oracle
+from tests.test_gpu_parity import say, tolerances
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,V,E,K,length", [
+    (64, 64, 5, 4, 2),          # one k-step of the logits and of dHidden, one tile everywhere
+    (128, 321, 2048, 6, 1),     # 12288 rows: the most that dHidden reads W untransposed for; V no multiple of 64
+    (128, 321, 2050, 6, 1),     # 12300 rows: W is transposed
+    (320, 8192, 65, 8, 1),      # 520 rows: 6 tiles of 128 k-steps in dHidden, split; ragged tiles along H and rows
+    (256, 300, 128, 8, 4),      # 4096 rows: 2 tiles of 64 k-steps in dW, split; ragged last vocabulary tile
+    (192, 4100, 9, 5, 17),      # 765 rows: parts of unequal length, 60 columns in the last k-step
+])
+def test_tiles_and_split_contractions(gpu_device, H, V, E, K, length):
+    cfg = replace(synth.CONFIGS["C3"], name=f"tiles-{H}-{V}-{E * K * length}", dtype="bf16", H=H, V=V, n_heads=1, E=E, N=1,
+                  T=1, K=K, len_lo=length, len_hi=length, reward_kind="uniform", old_sigma=0.02)
+    say(f"[tiles] building {cfg.name}")
+    c = helpers.build_case(cfg, device=gpu_device)
+    ref = helpers.oracle_bwd(c)
+    dc = DeviceCase(c, gpu_device)
+    tol = tolerances(cfg)
+    out = api.at_grpo_policy_loss_fwd_bwd(dc.batch(), dc.old_logp, dc.adv, cfg.eps_clip, cfg.eps_clip)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 0
+    check_step_against_oracle(out, ref, c, cfg, tol, "tiles, one pass")
+    fwd = api.at_grpo_policy_loss_fwd(dc.batch(), dc.old_logp, dc.adv, cfg.eps_clip, cfg.eps_clip)
+    bwd = api.at_grpo_policy_loss_bwd(dc.batch(), dc.old_logp, dc.adv, fwd["logp"], fwd["lse"], cfg.eps_clip, cfg.eps_clip)
+    torch.cuda.synchronize()
+    check_step_against_oracle(dict(fwd, **{k: bwd[k] for k in ("d_hidden", "dW")}), ref, c, cfg, tol, "tiles, two calls")
