@@ -13,7 +13,7 @@ LIB = os.path.join(PKG, "libat_grpo.so")
 CLIENT = os.path.join(PKG, "abi_client")
 PROBE = os.path.join(PKG, "gemm_probe")
 SOURCES = ["api.hip", "group_advantage.hip", "token_kernels.hip", "head_kernels.hip", "head_bf16.hip",
-           "optimizer.hip"]
+           "head_f32.hip", "optimizer.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

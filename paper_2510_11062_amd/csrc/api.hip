@@ -73,10 +73,9 @@ struct Plan {
   float* zy;
   float* coef;
   void* Wt;
-  void* hT;
+  void* hG;          // gathered hidden rows of the super-chunk (bf16)
   void* dZ;
-  void* dZt;
-  void* part;        // partial tiles of split contractions (bf16)
+  void* part;        // partial results of split contractions
   // one-pass forward + backward only
   TokenScratch SB, SF;   // the rows that can carry gradient / the rows with a zero advantage (own flag, cnt, idx)
   HeadGeom gF;           // geometry of the log-probability-only launches
@@ -154,7 +153,6 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
   g.V = b->V;
   g.esize = b->dtype == AT_GRPO_BF16 ? 2 : 4;
   g.Vp = static_cast<int>(round_up(static_cast<size_t>(b->V), 64));
-  g.n_vtiles = static_cast<int>(ceil_div(b->V, 256));
   int64_t tc = static_cast<int64_t>(round_up(static_cast<size_t>(n_tok), 256));
   const bool step = call == AT_GRPO_CALL_POLICY_LOSS_FWD_BWD;
   const bool bwd = call == AT_GRPO_CALL_POLICY_LOSS_BWD || step;
@@ -166,9 +164,10 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
     if (tc > cap) tc = cap;
   }
   g.TC = static_cast<int>(tc);
+  g.vtile = head_vocab_tile(g.dtype);
+  g.n_vtiles = static_cast<int>(ceil_div(g.V, g.vtile));
   p->n_chunks = static_cast<int>(ceil_div(n_tok, tc));
-  // bf16 backward: two launches of dZ / dHidden per full super-chunk (the fp32 path keeps a transposed
-  // copy of dZ whose row stride is the chunk length, and is launched once per chunk)
+  // bf16 backward: two launches of dZ / dHidden per full super-chunk (the fp32 path is launched once per chunk)
   int64_t sub_rows = static_cast<int64_t>(kSubChunkBytes / (static_cast<size_t>(g.H) * g.esize)) / 256 * 256;
   if (sub_rows > kSubChunkTokens) sub_rows = kSubChunkTokens;
   while (sub_rows > 256 && kMaxChunkTokens % sub_rows != 0) sub_rows -= 256;
@@ -212,10 +211,9 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
   if (bwd) {
     p->coef = step ? nullptr : ws.take<float>(static_cast<size_t>(n_tok));
     p->Wt = needs_transposed_w(g, n_tok) ? ws.take<char>(static_cast<size_t>(g.H) * g.Vp * g.esize) : nullptr;
-    p->hT = ws.take<char>(static_cast<size_t>(g.H) * g.TC * g.esize);
+    p->hG = g.dtype == AT_GRPO_BF16 ? ws.take<char>(static_cast<size_t>(g.H) * g.TC * g.esize) : nullptr;
     p->part = ws.take<char>(head_partial_bytes(g));
     p->dZ = ws.take<char>(static_cast<size_t>(g.TC) * g.Vp * g.esize);
-    p->dZt = (g.dtype == AT_GRPO_F32) ? ws.take<char>(static_cast<size_t>(g.V) * g.TC * g.esize) : nullptr;
   }
 }
 
@@ -387,17 +385,16 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
     ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, p.S.cnt + m, s));
     for (int c = 0; c < p.n_chunks; ++c) {
       const HeadChunk ch{p.S.idx + static_cast<size_t>(m) * p.L.n_tok, p.S.cnt + m, c * p.g.TC};
-      ATG_TRY(launch_gather_transpose_hidden(p.g, ch, batch->hidden, p.hT, s));
+      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s));
       HeadGeom gs = p.g;
       gs.TC = p.sub;
       for (int c1 = 0; c1 < p.g.TC; c1 += p.sub) {
         const HeadChunk sub{ch.idx, ch.cnt, ch.c0 + c1};
         char* dZ_sub = static_cast<char*>(p.dZ) + static_cast<size_t>(c1) * p.g.Vp * p.g.esize;
-        ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub,
-                               p.dZt, s));
+        ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub, s));
         ATG_TRY(launch_head_dh(gs, sub, dZ_sub, batch->W[m], p.Wt, d_hidden, p.part, s));
       }
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.dZt, p.hT, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, batch->hidden, p.hG, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s));
     }
   }
@@ -465,7 +462,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
                                 p.zy, s, gate));
         ATG_TRY(launch_lse_combine(gs, sub, p.part_m, p.part_s, nullptr, p.zy, logp, lse, nullptr, s, gate));
         ATG_TRY(launch_fallback_scale(gs, sub, m, ca, logp, scale_sub, gate, s));
-        ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, nullptr, E_sub, nullptr, s,
+        ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, nullptr, E_sub, s,
                                gate));
       }
       // rows on the clipped branch (factor 0) are taken out of the chunk before the two contractions
@@ -473,8 +470,8 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
       // fill the grid evenly
       ATG_TRY(launch_compact_rows(p.g, ch, p.scale, p.dZ, p.perm, p.holes, p.movers, p.live_cnt, p.live_cnt + 1, s));
       ATG_TRY(launch_head_dh(p.g, ch, p.dZ, batch->W[m], p.Wt, d_hidden, p.part, s, p.scale, p.perm, p.live_cnt));
-      ATG_TRY(launch_gather_transpose_hidden(p.g, ch, batch->hidden, p.hT, s, p.scale, p.perm, p.live_cnt));
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, nullptr, p.hT, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
+      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, p.scale, p.perm, p.live_cnt));
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, batch->hidden, p.hG, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s, p.live_cnt));
     }
   }

@@ -557,7 +557,7 @@ struct DwArgs {
 
 __device__ __forceinline__ void dw_store(const DwArgs& a, const floatx4 (&col)[GDw::kIB], int v, int hb, int lane) {
   if (v >= a.V) return;
-  floatx4* out = reinterpret_cast<floatx4*>(a.dW + static_cast<size_t>(v) * a.H + hb + 4 * (lane >> 4));
+  f32x4_any* out = reinterpret_cast<f32x4_any*>(a.dW + static_cast<size_t>(v) * a.H + hb + 4 * (lane >> 4));
   if (hb + GDw::kRowsA <= a.H) {     // a whole block of 16 columns exists or does not (H % 64 == 0)
     floatx4 x[GDw::kIB];
 #pragma unroll

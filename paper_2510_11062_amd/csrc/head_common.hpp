@@ -9,6 +9,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 #ifdef __HIPCC__
+// four fp32 values at an address that need only be aligned for one of them (the caller's dW): still one 16-byte access
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // list positions of the launch: at most TC of the list's *cnt entries from c0 on
 __device__ __forceinline__ int chunk_count(const int32_t* cnt, int c0, int TC) {
   const int n = *cnt - c0;

@@ -1,169 +1,25 @@
-// LM-head kernels of the AT-GRPO policy loss (gfx950).
+// Kernels around the head contractions of the AT-GRPO policy loss (gfx950), and the launchers that choose between the bf16
+// (head_bf16.hip) and fp32 (head_f32.hip) contractions.
 //
-// Forward (log pi_theta(y_t) inside the ratio of Eq. 2): logits tiles z[v, t] = <W[v], hidden[t]>
-// are produced in MFMA accumulators, reduced to per-(vocabulary tile, token) (max, sum-exp)
-// partials and the target logit, and discarded.  A small combine kernel turns the partials into
-// lse and logp.
+// Forward (log pi_theta(y_t) inside the ratio of Eq. 2): logits tiles z[v, t] = <W[v], hidden[t]> are produced in MFMA
+// accumulators, reduced to per-(vocabulary tile, token) (max, sum-exp) partials and the target logit, and discarded.  A
+// small combine kernel turns the partials into lse and logp.
 //
-// Backward: logits tiles are recomputed, turned into dZ = g (onehot - softmax) in registers and
-// written once, as dZ[token][vocab] in the element type of the inputs; two further contractions
-// give dHidden = dZ W (k = vocab, both operands contiguous along k) and dW = dZ^T hidden
-// (k = tokens, both operands read k-major through transposing LDS reads).  The fp32 path keeps a
-// second, transposed copy of dZ instead.
-#include <type_traits>
-
-#include "gemm_core.hpp"
+// Backward: logits tiles are recomputed, turned into dZ = g (onehot - softmax) in registers and written once, as
+// dZ[token][vocab] in the element type of the inputs; two further contractions give dHidden = dZ W (k = vocab) and
+// dW = dZ^T hidden (k = tokens).
 #include "head_bf16.hpp"
 #include "head_common.hpp"
+#include "head_f32.hpp"
+#include "head_kernels.hpp"
 #include "split_k.hpp"
-#include "tile_order.hpp"
 #include "token_kernels.hpp"
 
 namespace atg {
 
 namespace {
 
-// ------------------------------------------------------------------------------------------------
-// forward: A = W rows (vocab -> accumulator registers), B = hidden rows (tokens -> lanes)
-// ------------------------------------------------------------------------------------------------
-// ENT: also emit part_u, the partial sums of 2^(z log2e - m) * z that the entropy monitor needs
-// (H = lse - E_p[z]); the default instantiation carries none of it.
-template <typename T, bool ENT>
-__global__ __launch_bounds__(kGemmThreads) void k_head_fwd(
-    const T* __restrict__ hidden, const T* __restrict__ W, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id,
-    float* __restrict__ part_m, float* __restrict__ part_s, float* __restrict__ part_u,
-    float* __restrict__ zy, int H, int V, int TC, int n_vtiles, const int32_t* __restrict__ gate) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  if (gate && *gate == 0) return;
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{n_vtiles, (n + kTile - 1) / kTile, 8};
-  const int total = ord.total();
-  const TileCoord tc;
-  const size_t row_bytes = static_cast<size_t>(H) * sizeof(T);
-  const int nk = static_cast<int>(row_bytes / kStepBytes);
-  float* red_m = reinterpret_cast<float*>(smem);          // [kWavesA][256]
-  float* red_s = red_m + kWavesA * kTile;                 // [kWavesA][256]
-  float* red_u = red_s + kWavesA * kTile;                 // [kWavesA][256], entropy variant only
-
-  for (int t = logical_workgroup(); t < total; t += gridDim.x) {
-    int vt, tt;
-    ord.decode(t, &vt, &tt);
-    const int v0 = vt * kTile, t0 = tt * kTile;
-
-    int tcol[kJB], ycol[kJB];
-#pragma unroll
-    for (int j = 0; j < kJB; ++j) {
-      tcol[j] = t0 + tc.b_row(j);
-      ycol[j] = (tcol[j] < n) ? token_id[idx[c0 + tcol[j]]] : -1;
-    }
-
-    floatx16 acc[kIB][kJB];
-    gemm_tile<T>(
-        acc,
-        [&](int row) {
-          const int v = min(v0 + row, V - 1);
-          return reinterpret_cast<const char*>(W) + static_cast<size_t>(v) * row_bytes;
-        },
-        [&](int row) {
-          const int tk = min(t0 + row, n - 1);
-          return reinterpret_cast<const char*>(hidden) + static_cast<size_t>(idx[c0 + tk]) * row_bytes;
-        },
-        nk, smem);
-
-    constexpr int kWaveRows = kTile / kWavesA;   // vocab rows one wavefront holds
-    const int vbase = v0 + tc.wm * kWaveRows;
-    const int vrem = V - vbase;                  // rows of it that exist (may be <= 0)
-    const bool ragged = vrem < kWaveRows;
-
-#pragma unroll
-    for (int j = 0; j < kJB; ++j) {
-      float mx = -INFINITY;
-      if (!ragged) {
-#pragma unroll
-        for (int i = 0; i < kIB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < kIB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vl = i * 32 + 8 * (r >> 2) + 4 * tc.half + (r & 3);
-            if (vl < vrem) mx = fmaxf(mx, acc[i][j][r]);
-          }
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m2 = (mx == -INFINITY) ? 0.f : mx * kLog2e;
-      float sum = 0.f, usum = 0.f;
-      if (!ragged) {
-#pragma unroll
-        for (int i = 0; i < kIB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float e = fast_exp2(fmaf(acc[i][j][r], kLog2e, -m2));
-            sum += e;
-            if (ENT) usum = fmaf(e, acc[i][j][r], usum);
-          }
-      } else {
-#pragma unroll
-        for (int i = 0; i < kIB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vl = i * 32 + 8 * (r >> 2) + 4 * tc.half + (r & 3);
-            if (vl < vrem) {
-              const float e = fast_exp2(fmaf(acc[i][j][r], kLog2e, -m2));
-              sum += e;
-              if (ENT) usum = fmaf(e, acc[i][j][r], usum);
-            }
-          }
-      }
-      sum += __shfl_xor(sum, 32, 64);
-      if (ENT) usum += __shfl_xor(usum, 32, 64);
-      if (tc.half == 0) {
-        red_m[tc.wm * kTile + tc.b_row(j)] = (mx == -INFINITY) ? -INFINITY : m2;
-        red_s[tc.wm * kTile + tc.b_row(j)] = sum;
-        if (ENT) red_u[tc.wm * kTile + tc.b_row(j)] = usum;
-      }
-      // target logit: held by exactly one lane of one wavefront of one tile
-      const int rel = ycol[j] - vbase;
-      const bool hit = (tcol[j] < n) && rel >= 0 && rel < kWaveRows && (((rel >> 2) & 1) == tc.half);
-      if (__builtin_amdgcn_ballot_w64(hit) != 0ull) {
-        float zt = 0.f;
-#pragma unroll
-        for (int i = 0; i < kIB; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vl = i * 32 + 8 * (r >> 2) + (r & 3);   // half bit compared separately
-            if ((rel & ~4) == vl) zt = acc[i][j][r];
-          }
-        if (hit) zy[tcol[j]] = zt;
-      }
-    }
-    // fold the four vocabulary quarters of the tile: one (max, sum) per token and vocabulary tile
-    barrier_lds_only();
-    if (threadIdx.x < kTile && t0 + threadIdx.x < n) {
-      float M = -INFINITY;
-#pragma unroll
-      for (int q = 0; q < kWavesA; ++q) M = fmaxf(M, red_m[q * kTile + threadIdx.x]);
-      float S = 0.f, U = 0.f;
-#pragma unroll
-      for (int q = 0; q < kWavesA; ++q) {
-        const float mq = red_m[q * kTile + threadIdx.x];
-        if (mq != -INFINITY) {
-          const float sc = fast_exp2(mq - M);
-          S += red_s[q * kTile + threadIdx.x] * sc;
-          if (ENT) U += red_u[q * kTile + threadIdx.x] * sc;
-        }
-      }
-      part_m[static_cast<size_t>(vt) * TC + t0 + threadIdx.x] = M;
-      part_s[static_cast<size_t>(vt) * TC + t0 + threadIdx.x] = S;
-      if (ENT) part_u[static_cast<size_t>(vt) * TC + t0 + threadIdx.x] = U;
-    }
-    barrier_lds_only();   // the fold buffers are free again; the stores above need not have landed
-  }
-}
+constexpr int kRowPad = 256;      // rows of a super-chunk are padded to the next multiple of this
 
 // ------------------------------------------------------------------------------------------------
 // combine: 1024 threads = 32 tokens x 32 slices of the vocabulary tiles.  Bound by latency where tokens are few (the
@@ -244,145 +100,6 @@ __global__ __launch_bounds__(kCmbThreads) void k_lse_combine(const int32_t* __re
     logp[row] = zy[j] - l;
     if (lse) lse[row] = l;
     if (entropy) entropy[row] = l - Ut / St;     // H = lse - E_p[z]
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// transposes (64 x 64 tiles through LDS)
-// ------------------------------------------------------------------------------------------------
-// dst[c][r] = src_row(r)[c] for r < rows_valid, 0 for rows_valid <= r < rows_pad; c < cols.
-// src_row(r) = src + idx[c0 + r] * src_ld when idx != null, else src + r * src_ld.
-// When cnt != null, rows_valid = chunk count and rows_pad = that rounded up to 256.
-template <typename T>
-__global__ __launch_bounds__(256) void k_transpose(const T* __restrict__ src, int64_t src_ld,
-                                                   const int32_t* __restrict__ idx,
-                                                   const int32_t* __restrict__ cnt, int c0, int TC,
-                                                   int rows_valid, int rows_pad, int cols,
-                                                   T* __restrict__ dst, int64_t dst_ld) {
-  __shared__ T tile[64][65];
-  if (cnt) {
-    rows_valid = chunk_count(cnt, c0, TC);
-    rows_pad = (rows_valid + kTile - 1) / kTile * kTile;
-  }
-  const int r0 = blockIdx.x * 64, col0 = blockIdx.y * 64;
-  if (r0 >= rows_pad) return;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int r = r0 + ty + 4 * k, c = col0 + tx;
-    T v{};
-    if (r < rows_valid && c < cols) {
-      const int64_t sr = idx ? static_cast<int64_t>(idx[c0 + r]) : static_cast<int64_t>(r);
-      v = src[sr * src_ld + c];
-    }
-    tile[ty + 4 * k][tx] = v;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int c = col0 + ty + 4 * k, r = r0 + tx;
-    if (c < cols && r < rows_pad) dst[static_cast<int64_t>(c) * dst_ld + r] = tile[tx][ty + 4 * k];
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// dZ: recompute logits, emit dZ[t][v] and dZt[v][t]
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kGemmThreads) void k_head_dz(
-    const T* __restrict__ hidden, const T* __restrict__ W, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id,
-    const float* __restrict__ lse, const float* __restrict__ coef, T* __restrict__ dZ,
-    T* __restrict__ dZt, int H, int V, int Vp, int TC, int n_vtiles, const int32_t* __restrict__ gate) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  if (gate && *gate == 0) return;
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{n_vtiles, (n + kTile - 1) / kTile, 8};
-  const int total = ord.total();
-  const TileCoord tc;
-  const size_t row_bytes = static_cast<size_t>(H) * sizeof(T);
-  const int nk = static_cast<int>(row_bytes / kStepBytes);
-
-  for (int t = logical_workgroup(); t < total; t += gridDim.x) {
-    int vt, tt;
-    ord.decode(t, &vt, &tt);
-    const int v0 = vt * kTile, t0 = tt * kTile;
-
-    int tcol[kJB], ycol[kJB];
-    float gcol[kJB], l2col[kJB];
-#pragma unroll
-    for (int j = 0; j < kJB; ++j) {
-      tcol[j] = t0 + tc.b_row(j);
-      if (tcol[j] < n) {
-        const int row = idx[c0 + tcol[j]];
-        ycol[j] = token_id[row];
-        gcol[j] = coef ? coef[row] : -1.f;   // without coefficients: softmax - onehot
-        l2col[j] = lse[row] * kLog2e;
-      } else {
-        ycol[j] = -1;
-        gcol[j] = 0.f;
-        l2col[j] = 0.f;
-      }
-    }
-
-    floatx16 acc[kIB][kJB];
-    gemm_tile<T>(
-        acc,
-        [&](int row) {
-          const int v = min(v0 + row, V - 1);
-          return reinterpret_cast<const char*>(W) + static_cast<size_t>(v) * row_bytes;
-        },
-        [&](int row) {
-          const int tk = min(t0 + row, n - 1);
-          return reinterpret_cast<const char*>(hidden) + static_cast<size_t>(idx[c0 + tk]) * row_bytes;
-        },
-        nk, smem);
-
-    const int vwave = tc.wm * (kTile / kWavesA);     // first vocab row (inside the tile) of this wavefront
-    // Tiles that lie fully inside the vocabulary and the token list (all but the last row / column of
-    // tiles) need no per-element range checks; the target's one-hot term is rare (one element in V per
-    // token) and is patched in behind a branch that is almost never taken.
-    const bool interior = (v0 + kTile <= V) && (t0 + kTile <= n);
-    auto emit = [&](auto guard_c) {
-      constexpr bool kGuard = decltype(guard_c)::value;
-#pragma unroll
-      for (int j = 0; j < kJB; ++j) {
-        const float g = gcol[j];
-        const float nl2 = -l2col[j];
-        const bool live = tcol[j] < n;
-#pragma unroll
-        for (int i = 0; i < kIB; ++i) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int vl = vwave + i * 32 + 8 * q + 4 * tc.half;   // first of 4 consecutive vocab rows
-            const int v = v0 + vl;
-            float d[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) d[e] = -g * fast_exp2(fmaf(acc[i][j][q * 4 + e], kLog2e, nl2));
-            const int rel = ycol[j] - v;
-            if (static_cast<unsigned>(rel) < 4u) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (rel == e) d[e] += g;
-            }
-            if (kGuard) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) d[e] = (v + e < V && live) ? d[e] : 0.f;   // k padding, rows past the count
-            }
-            if (v < Vp)
-              *reinterpret_cast<float4*>(dZ + static_cast<size_t>(tcol[j]) * Vp + v) = make_float4(d[0], d[1], d[2], d[3]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (v + e < V) dZt[static_cast<size_t>(v + e) * TC + tcol[j]] = d[e];
-          }
-        }
-      }
-    };
-    if (interior)
-      emit(std::false_type{});
-    else
-      emit(std::true_type{});
   }
 }
 
@@ -585,110 +302,6 @@ __global__ __launch_bounds__(256) void k_move_rows(bf16_t* __restrict__ E, int V
 }
 
 // ------------------------------------------------------------------------------------------------
-// dHidden: A = dZ rows (tokens -> registers), B = Wt rows (h -> lanes), k = vocab
-// ------------------------------------------------------------------------------------------------
-template <typename T, typename G>
-__global__ __launch_bounds__(G::kThreads) void k_head_dh(const T* __restrict__ dZ,
-                                                          const T* __restrict__ Wt,
-                                                          const int32_t* __restrict__ idx,
-                                                          const int32_t* __restrict__ cnt, int c0,
-                                                          T* __restrict__ d_hidden, int H, int Vp,
-                                                          int TC, const float* __restrict__ scale,
-                                                          const int32_t* __restrict__ perm,
-                                                          const int32_t* __restrict__ live_cnt) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  // after the rows were compacted: the first *live_cnt rows of dZ, row j belonging to list position perm[j]
-  const int n = perm ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{(n + kTile - 1) / kTile, (H + kTile - 1) / kTile, 8};
-  const int total = ord.total();
-  const TileCoordT<G> tc;
-  const size_t row_bytes = static_cast<size_t>(Vp) * sizeof(T);
-  const int nk = static_cast<int>(row_bytes / kStepBytes);
-
-  for (int t = logical_workgroup(); t < total; t += gridDim.x) {
-    int tt, ht;
-    ord.decode(t, &tt, &ht);
-    const int t0 = tt * kTile, h0 = ht * kTile;
-    floatx16 acc[G::kIB][G::kJB];
-    gemm_tile<T, G>(
-        acc,
-        [&](int row) { return reinterpret_cast<const char*>(dZ) + static_cast<size_t>(t0 + row) * row_bytes; },
-        [&](int row) {
-          const int h = min(h0 + row, H - 1);
-          return reinterpret_cast<const char*>(Wt) + static_cast<size_t>(h) * row_bytes;
-        },
-        nk, smem);
-#pragma unroll
-    for (int i = 0; i < G::kIB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int jt = t0 + tc.a_row(i, r);
-        if (jt >= n) continue;
-        const int j = perm ? perm[jt] : jt;
-        T* out = d_hidden + static_cast<size_t>(idx[c0 + j]) * H;
-        const float sc = scale ? scale[j] : 1.f;     // row factor of the one-pass path
-#pragma unroll
-        for (int jj = 0; jj < G::kJB; ++jj) {
-          const int h = h0 + tc.b_row(jj);
-          if (h < H) out[h] = from_f32<T>(acc[i][jj][r] * sc);
-        }
-      }
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// dW: A = dZt rows (vocab -> registers), B = hT rows (h -> lanes), k = tokens of the super-chunk
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kGemmThreads) void k_head_dw(const T* __restrict__ dZt,
-                                                          const T* __restrict__ hT,
-                                                          const int32_t* __restrict__ cnt, int c0,
-                                                          float* __restrict__ dW, int H, int V, int TC,
-                                                          int n_vtiles, int accumulate, int first_chunk) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0 && !(first_chunk && !accumulate)) return;
-  const TileOrder ord{n_vtiles, (H + kTile - 1) / kTile, 8};
-  const int total = ord.total();
-  const TileCoord tc;
-  const size_t row_bytes = static_cast<size_t>(TC) * sizeof(T);
-  const int k_tokens = (n + kTile - 1) / kTile * kTile;
-  const int nk = static_cast<int>(static_cast<size_t>(k_tokens) * sizeof(T) / kStepBytes);
-
-  for (int t = logical_workgroup(); t < total; t += gridDim.x) {
-    int vt, ht;
-    ord.decode(t, &vt, &ht);
-    const int v0 = vt * kTile, h0 = ht * kTile;
-    floatx16 acc[kIB][kJB];
-    gemm_tile<T>(
-        acc,
-        [&](int row) {
-          const int v = min(v0 + row, V - 1);
-          return reinterpret_cast<const char*>(dZt) + static_cast<size_t>(v) * row_bytes;
-        },
-        [&](int row) {
-          const int h = min(h0 + row, H - 1);
-          return reinterpret_cast<const char*>(hT) + static_cast<size_t>(h) * row_bytes;
-        },
-        nk, smem);
-#pragma unroll
-    for (int i = 0; i < kIB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int v = v0 + tc.a_row(i, r);
-        if (v >= V) continue;
-        float* out = dW + static_cast<size_t>(v) * H;
-#pragma unroll
-        for (int jj = 0; jj < kJB; ++jj) {
-          const int h = h0 + tc.b_row(jj);
-          if (h < H) out[h] = accumulate ? out[h] + acc[i][jj][r] : acc[i][jj][r];
-        }
-      }
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
 // hG[j][:] = hidden[idx[c0 + j]][:] for j < n, zero rows up to the next multiple of 256 (bf16 rows
 // of the super-chunk made contiguous so that the token contraction can stream them k-major)
 // ------------------------------------------------------------------------------------------------
@@ -700,7 +313,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(const bf16_t* __restrict__ 
                                                      const int32_t* __restrict__ live_cnt, bf16_t* __restrict__ hG) {
   // with perm: row j of hG is list position perm[j], for j < *live_cnt
   const int n = perm ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
-  const int n_pad = (n + kTile - 1) / kTile * kTile;
+  const int n_pad = (n + kRowPad - 1) / kRowPad * kRowPad;
   const int chunks = H / 8;                       // 16-byte pieces per row
   const int rows_per_block = 256 / 32;
   for (int j = blockIdx.x * rows_per_block + (threadIdx.x >> 5); j < n_pad; j += gridDim.x * rows_per_block) {
@@ -729,25 +342,22 @@ __global__ __launch_bounds__(256) void k_gather_rows(const bf16_t* __restrict__ 
 // ================================================================================================
 // launchers
 // ================================================================================================
+int head_vocab_tile(int dtype) { return dtype == AT_GRPO_BF16 ? 256 : kVocabTileF32; }
+
 int launch_head_fwd(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                     const int32_t* token_id, float* part_m, float* part_s, float* part_u, float* zy,
                     hipStream_t s, const int32_t* gate) {
   ProfScope ps(PROF_HEAD_FWD, s);
   if (g.dtype == AT_GRPO_BF16)
     return launch_fwd_bf16(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s, gate);
-  auto k = part_u ? k_head_fwd<float, true> : k_head_fwd<float, false>;
-  ATG_TRY(allow_big_lds(k, kLdsBytes));
-  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s, static_cast<const float*>(hidden),
-                     static_cast<const float*>(W), ch.idx, ch.cnt, ch.c0, token_id, part_m, part_s, part_u, zy, g.H,
-                     g.V, g.TC, g.n_vtiles, gate);
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
+  return launch_fwd_f32(g, ch, hidden, W, token_id, part_m, part_s, part_u, zy, s);
 }
 
 int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part_m, const float* part_s,
                        const float* part_u, const float* zy, float* logp, float* lse, float* entropy,
                        hipStream_t s, const int32_t* gate) {
   ProfScope ps(PROF_LSE_COMBINE, s);
+  if (g.dtype != AT_GRPO_BF16) return launch_lse_combine_f32(g, ch, part_m, part_s, part_u, zy, logp, lse, entropy, s);
   hipLaunchKernelGGL(k_lse_combine, dim3(g.TC / kCmbTokens), dim3(kCmbThreads), 0, s, ch.idx, ch.cnt, ch.c0, g.TC,
                      g.n_vtiles, part_m, part_s, part_u, zy, logp, lse, part_u ? entropy : nullptr, gate);
   ATG_LAUNCH_CHECK();
@@ -755,50 +365,30 @@ int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part
 }
 
 bool needs_transposed_w(const HeadGeom& g, int64_t n_tok) {
-  return g.dtype != AT_GRPO_BF16 || transposes_w_bf16(n_tok);
+  return g.dtype == AT_GRPO_BF16 && transposes_w_bf16(n_tok);
 }
 
 int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, const int32_t* cnt, hipStream_t s) {
   ProfScope ps(PROF_TRANSPOSE, s);
-  if (g.dtype == AT_GRPO_BF16) return Wt ? launch_transpose_w_bf16(g, W, Wt, cnt, s) : AT_GRPO_OK;
-  dim3 grid(static_cast<unsigned>(ceil_div(g.Vp, 64)), static_cast<unsigned>(ceil_div(g.H, 64)));
-  hipLaunchKernelGGL(k_transpose<float>, grid, dim3(256), 0, s, static_cast<const float*>(W),
-                     static_cast<int64_t>(g.H), nullptr, nullptr, 0, 0, g.V, g.Vp, g.H,
-                     static_cast<float*>(Wt), static_cast<int64_t>(g.Vp));
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
+  return Wt ? launch_transpose_w_bf16(g, W, Wt, cnt, s) : AT_GRPO_OK;
 }
 
-int launch_gather_transpose_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hidden, void* hT,
-                                   hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
+int launch_gather_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hidden, void* hG,
+                         hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ProfScope ps(PROF_TRANSPOSE, s);
-  if (g.dtype == AT_GRPO_BF16) {
-    // bf16: plain row gather (the token contraction reads it k-major)
-    hipLaunchKernelGGL(k_gather_rows, dim3(2048), dim3(256), 0, s, static_cast<const bf16_t*>(hidden), ch.idx,
-                       ch.cnt, ch.c0, g.TC, g.H, scale, perm, live_cnt, static_cast<bf16_t*>(hT));
-  } else {
-    dim3 grid(static_cast<unsigned>(g.TC / 64), static_cast<unsigned>(ceil_div(g.H, 64)));
-    hipLaunchKernelGGL(k_transpose<float>, grid, dim3(256), 0, s, static_cast<const float*>(hidden),
-                       static_cast<int64_t>(g.H), ch.idx, ch.cnt, ch.c0, g.TC, 0, 0, g.H,
-                       static_cast<float*>(hT), static_cast<int64_t>(g.TC));
-  }
+  if (!hG) return AT_GRPO_OK;
+  hipLaunchKernelGGL(k_gather_rows, dim3(2048), dim3(256), 0, s, static_cast<const bf16_t*>(hidden), ch.idx,
+                     ch.cnt, ch.c0, g.TC, g.H, scale, perm, live_cnt, static_cast<bf16_t*>(hG));
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
 
 int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
-                   const int32_t* token_id, const float* lse, const float* coef, void* dZ, void* dZt,
+                   const int32_t* token_id, const float* lse, const float* coef, void* dZ,
                    hipStream_t s, const int32_t* gate) {
   ProfScope ps(PROF_HEAD_DZ, s);
   if (g.dtype == AT_GRPO_BF16) return launch_dz_bf16(g, ch, hidden, W, token_id, lse, coef, dZ, s, gate);
-  auto k = k_head_dz<float>;
-  ATG_TRY(allow_big_lds(k, kLdsBytes));
-  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
-                     static_cast<const float*>(hidden), static_cast<const float*>(W), ch.idx, ch.cnt,
-                     ch.c0, token_id, lse, coef, static_cast<float*>(dZ), static_cast<float*>(dZt), g.H,
-                     g.V, g.Vp, g.TC, g.n_vtiles, gate);
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
+  return launch_dz_f32(g, ch, hidden, W, token_id, lse, coef, dZ, s);
 }
 
 int launch_ref_logit(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
@@ -850,7 +440,7 @@ int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* sca
 }
 
 size_t head_partial_bytes(const HeadGeom& g) {
-  if (g.dtype != AT_GRPO_BF16) return 0;
+  if (g.dtype != AT_GRPO_BF16) return partial_bytes_f32(g);
   const int64_t ht = ceil_div(g.H, 256), dh = g.TC / 256 * ht, dw = g.n_vtiles * ht;
   return split_k_bytes(dh > dw ? dh : dw);
 }
@@ -859,26 +449,14 @@ int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
                    void* part, hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DH, s);
   if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, W, Wt, d_hidden, part, s, scale, perm, live_cnt);
-  auto k = k_head_dh<float, G8>;
-  ATG_TRY(allow_big_lds(k, kLdsBytes));
-  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
-                     static_cast<const float*>(dZ), static_cast<const float*>(Wt), ch.idx, ch.cnt, ch.c0,
-                     static_cast<float*>(d_hidden), g.H, g.Vp, g.TC, scale, perm, live_cnt);
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
+  return launch_dh_f32(g, ch, dZ, W, d_hidden, part, s);
 }
 
-int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* dZt, const void* hT,
+int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hidden, const void* hG,
                    float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DW, s);
-  if (g.dtype == AT_GRPO_BF16) return launch_dw_bf16(g, ch, dZ, hT, dW, part, accumulate, first_chunk, s, live_cnt);
-  auto k = k_head_dw<float>;
-  ATG_TRY(allow_big_lds(k, kLdsBytes));
-  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(kGemmThreads), kLdsBytes, s,
-                     static_cast<const float*>(dZt), static_cast<const float*>(hT), ch.cnt, ch.c0, dW, g.H,
-                     g.V, g.TC, g.n_vtiles, accumulate, first_chunk);
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
+  if (g.dtype == AT_GRPO_BF16) return launch_dw_bf16(g, ch, dZ, hG, dW, part, accumulate, first_chunk, s, live_cnt);
+  return launch_dw_f32(g, ch, dZ, hidden, dW, part, accumulate, first_chunk, s);
 }
 
 }  // namespace atg

@@ -13,7 +13,8 @@ struct HeadGeom {
   int H, V;
   int Vp;           // V rounded up to 64 (k padding of the dZ / W^T buffers)
   int TC;           // tokens per super-chunk (multiple of 256)
-  int n_vtiles;     // ceil(V / 256)
+  int vtile;        // vocabulary rows per partial of the log-probability kernels
+  int n_vtiles;     // ceil(V / vtile)
   int esize;        // bytes per element of hidden / W / dZ
 };
 
@@ -36,22 +37,25 @@ int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part
                        const float* part_s, const float* part_u, const float* zy, float* logp,
                        float* lse, float* entropy, hipStream_t s, const int32_t* gate = nullptr);
 
-// Wt[H][Vp] = W[V][H]^T, zero in the k padding.  bf16: a head with few rows (*cnt of its list) is left untransposed, and
-// needs_transposed_w() == false for a batch of n_tok rows says that every head is (Wt may then be null).
+// bf16: Wt[H][Vp] = W[V][H]^T, zero in the k padding.  A head with few rows (*cnt of its list) is left untransposed, and
+// needs_transposed_w() == false for a batch of n_tok rows says that no copy is ever read (Wt may then be null).
 bool needs_transposed_w(const HeadGeom& g, int64_t n_tok);
 int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, const int32_t* cnt, hipStream_t s);
 
-// fp32: hT[H][TC] = (gathered hidden rows of this super-chunk)^T, zero for columns past the count.
-// bf16: hT[TC][H] = the gathered rows themselves, zero rows up to the next multiple of 256.
-// bf16 with `scale`: row j is multiplied by scale[j] (j counted from the start of the super-chunk).
-// bf16 with `perm`: row j is list position perm[j] (and its factor), for j < *live_cnt; zero rows behind.
-int launch_gather_transpose_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hidden,
-                                   void* hT, hipStream_t s, const float* scale = nullptr,
-                                   const int32_t* perm = nullptr, const int32_t* live_cnt = nullptr);
+// vocabulary rows per partial (HeadGeom::vtile)
+int head_vocab_tile(int dtype);
 
-// dZ[TC][Vp] for this super-chunk (element type of hidden); fp32 also fills dZt[V][TC].
+// bf16 (fp32 reads the rows where they lie; hG is null and nothing happens): hG[TC][H] = the gathered hidden rows of this
+// super-chunk, zero rows up to the next multiple of 256.  With `scale`, row j is multiplied by scale[j] (j counted from the
+// start of the super-chunk).  With `perm`, row j is list position perm[j] (and its factor), for j < *live_cnt; zero rows
+// behind.
+int launch_gather_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hidden,
+                         void* hG, hipStream_t s, const float* scale = nullptr,
+                         const int32_t* perm = nullptr, const int32_t* live_cnt = nullptr);
+
+// dZ[TC][Vp] for this super-chunk (element type of hidden).
 int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
-                   const int32_t* token_id, const float* lse, const float* coef, void* dZ, void* dZt,
+                   const int32_t* token_id, const float* lse, const float* coef, void* dZ,
                    hipStream_t s, const int32_t* gate = nullptr);
 
 // Scratch for the partial tiles of launch_head_dh / launch_head_dw over g.TC rows.
@@ -83,7 +87,7 @@ int launch_fallback_scale(const HeadGeom& g, const HeadChunk& ch, int head, cons
 // d_hidden[row] = dZ[j] . W for the rows of this super-chunk.
 // With `scale`, row j of the result is multiplied by scale[j] (j counted from ch.c0).  With `perm` (after
 // launch_compact_rows), the first *live_cnt rows of dZ are contracted and row j goes to list position perm[j].
-// `part`: head_partial_bytes() of scratch for bf16 (partial tiles of the contraction), unused for fp32.
+// `part`: head_partial_bytes() of scratch (partial results of contractions split along k).
 int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* Wt,
                    void* d_hidden, void* part, hipStream_t s, const float* scale = nullptr, const int32_t* perm = nullptr,
                    const int32_t* live_cnt = nullptr);
@@ -97,7 +101,7 @@ int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* sca
 
 // dW[V][H] (+)= dZ^T . hidden rows.  first_chunk: runs even for an empty list so that dW is defined.
 // bf16 with `live_cnt`: only the first *live_cnt rows of the chunk are contracted.
-int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* dZt, const void* hT,
+int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hidden, const void* hG,
                    float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt = nullptr);
 
 }  // namespace atg

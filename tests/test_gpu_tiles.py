@@ -39,3 +39,28 @@ def test_tiles_and_split_contractions(gpu_device, H, V, E, K, length):
     bwd = api.at_grpo_policy_loss_bwd(dc.batch(), dc.old_logp, dc.adv, fwd["logp"], fwd["lse"], cfg.eps_clip, cfg.eps_clip)
     torch.cuda.synchronize()
     check_step_against_oracle(dict(fwd, **{k: bwd[k] for k in ("d_hidden", "dW")}), ref, c, cfg, tol, "tiles, two calls")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,V,E,K,length", [
+    (32, 3, 3, 2, 1),           # one k-step everywhere, fewer vocabulary rows than a lane pair sums
+    (32, 66, 31, 3, 7),         # 651 rows: one column past a tile, rows and k ragged
+    (96, 333, 700, 4, 6),       # 16800 rows: dW split into the most parts, dHidden whole
+    (64, 5000, 20, 4, 2),       # 160 rows: dHidden split along the vocabulary
+    (64, 4200, 128, 8, 2),      # 2048 rows: 128 x 128 tiles in dZ
+    (512, 200, 512, 8, 4),      # 16384 rows: 128 x 128 tiles in dHidden
+    (1024, 8190, 5, 4, 2),      # 128 x 128 tiles in dW
+])
+def test_fp32_tiles(gpu_device, H, V, E, K, length):
+    """The fp32 contractions at the edges of their tiles and of the rules that choose tile and split, against the oracle
+    at the fp32 tolerances (sums of up to 16800 fp32 products against 1e-4)."""
+    cfg = replace(synth.CONFIGS["C1"], name=f"f32-tiles-{H}-{V}-{E * K * length}", H=H, V=V, E=E, N=1, T=1, K=K,
+                  len_lo=length, len_hi=length, reward_kind="uniform", forced_equal_groups=0, old_sigma=0.02)
+    say(f"[tiles] building {cfg.name}")
+    c = helpers.build_case(cfg, device=gpu_device)
+    ref = helpers.oracle_bwd(c)
+    dc = DeviceCase(c, gpu_device)
+    out = api.at_grpo_policy_loss_fwd_bwd(dc.batch(), dc.old_logp, dc.adv, cfg.eps_clip, cfg.eps_clip)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 0
+    check_step_against_oracle(out, ref, c, cfg, tolerances(cfg), "fp32 tiles")
