@@ -51,6 +51,12 @@ typedef enum { AT_GRPO_AGG_TOKEN_MEAN = 0, AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN = 1 }
 /* F_norm of Eq. (1): the group's standard deviation (plus eps_std), or 1. */
 typedef enum { AT_GRPO_NORM_STD = 0, AT_GRPO_NORM_NONE = 1 } at_grpo_norm;
 
+/* May be or'ed into a `norm` argument by a caller whose group buffers all hold
+ * min(R, number of keys) entries (seg_offsets one more): the call then also writes the entries
+ * behind the last group and behind the last listed response (0; -1 for best), so that the buffers
+ * need not be cleared first.  Without it nothing is written there. */
+enum { AT_GRPO_NORM_FILL = 256 };
+
 /* Which responses form a group in Eq. (1): the paper's agent- and turn-wise key, or one of the two
  * groupings it argues against (Sec. 4.1, Fig. 3; Sec. 5.3), kept for comparison runs. */
 typedef enum {
@@ -190,9 +196,8 @@ int at_grpo_group_advantage_mixed(int32_t n_resp, int32_t n_env, int32_t n_agent
  * memory, which every GPU the library runs on holds until the process ends.  The call allocates and
  * frees nothing.  Same inputs, outputs, arithmetic and results as at_grpo_group_advantage, plus
  *   data_error[1]  optional device output (NULL to skip): the error word of this call (AT_GRPO_DATA_*)
- * Limit: at_grpo_workspace_bytes(AT_GRPO_CALL_GROUP_ADVANTAGE, ...) of the same extents must not
- * exceed at_grpo_static_scratch_bytes(), i.e. about 12 * n_resp + 8 * n_env * n_agent * n_turn bytes
- * <= 2 MiB (65 536 responses over 65 536 keys fit, as does every workload of the paper's shape); beyond it the call
+ * Limit: about 12 * n_resp + 8 * n_env * n_agent * n_turn bytes must not exceed
+ * at_grpo_static_scratch_bytes() = 2 MiB (65 536 responses over 65 536 keys fit, as does every workload of the paper's shape); beyond it the call
  * returns AT_GRPO_ESCRATCH and launches nothing.
  * All calls on one GPU share that GPU's array: calls that may overlap on one GPU (different streams
  * or threads) race and must be serialised by the caller.  Everything the kernels need cleared is

@@ -8,17 +8,20 @@ no fallback: if the HIP library is missing or a call fails, an exception is rais
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
 import torch
+from torch._C import _cuda_getCurrentRawStream as _raw_stream     # current stream of a device, as an integer
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libat_grpo.so")
 _lib = None
 
 AGG = {"token_mean": 0, "seq_mean_token_mean": 1}
 NORM = {"std": 0, "none": 1}
+NORM_FILL = 256      # or'ed into norm: the group buffers are filled behind the last group, so they need not be cleared
 GROUP_BY = {"agent_turn": 0, "trajectory": 1, "parallel": 2}
 CALL_GROUP_ADVANTAGE, CALL_TOKEN_LOGPROB, CALL_POLICY_LOSS_FWD, CALL_POLICY_LOSS_BWD, CALL_SURROGATE, \
     CALL_HEAD_UPDATE, CALL_DIAGNOSTICS, CALL_TOKEN_ENTROPY, CALL_POLICY_LOSS_FWD_BWD = range(9)
@@ -127,16 +130,16 @@ def _check(status: int, what: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev_check(*tensors):
     for t in tensors:
-        if t is not None and (not t.is_cuda or not t.is_contiguous()):
+        if t is not None and not (t.is_cuda and t.is_contiguous()):
             raise AtGrpoError("tensors must be contiguous CUDA/HIP tensors")
 
 
@@ -150,7 +153,7 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     Calls on different streams never share scratch (nothing orders them).  A workspace that is outgrown
     is kept alive until release_workspace(): a HIP graph captured earlier holds its raw pointer, and a
     replay must not find that memory handed to somebody else."""
-    key = (str(device), int(torch.cuda.current_stream(device).cuda_stream))
+    key = (device.index, _raw_stream(device.index))
     ws = _workspace_cache.get(key)
     if ws is None or ws.numel() < nbytes:
         if ws is not None:
@@ -248,29 +251,34 @@ def at_grpo_group_advantage(env_id, agent_id, turn_id, reward, n_env: int, n_age
     _i32_check(env_id=env_id, agent_id=agent_id, turn_id=turn_id)
     dev = reward.device
     R = reward.numel()
-    n_keys = n_env * n_agent * n_turn
-    gmax = min(R, n_keys)
-    out = dict(
-        group_id=torch.empty(R, dtype=torch.int32, device=dev),
-        n_groups=torch.zeros(1, dtype=torch.int32, device=dev),
-        seg_offsets=torch.zeros(gmax + 1, dtype=torch.int32, device=dev),
-        perm=torch.zeros(R, dtype=torch.int32, device=dev),
-        adv=torch.empty(R, dtype=torch.float32, device=dev),
-        group_mean=torch.zeros(gmax, dtype=torch.float32, device=dev) if want_stats else None,
-        group_std=torch.zeros(gmax, dtype=torch.float32, device=dev) if want_stats else None,
-    )
-    nbytes = lib.at_grpo_workspace_bytes(CALL_GROUP_ADVANTAGE, None, R, n_env, n_agent, n_turn)
-    if nbytes == 0:
-        raise AtGrpoError("at_grpo_workspace_bytes rejected the id extents")
-    ws = _workspace(nbytes, dev)
-    st = lib.at_grpo_group_advantage(R, n_env, n_agent, n_turn, _ptr(env_id), _ptr(agent_id), _ptr(turn_id),
-                                     _ptr(reward), eps_std, ddof, NORM[norm], _ptr(out["group_id"]),
-                                     _ptr(out["n_groups"]), _ptr(out["seg_offsets"]), _ptr(out["perm"]),
-                                     _ptr(out["adv"]), _ptr(out["group_mean"]), _ptr(out["group_std"]),
-                                     _ptr(ws), ws.numel(), _stream())
+    out = _group_buffers(R, min(R, n_env * n_agent * n_turn), dev, want_stats)
+    ws = _workspace(_group_workspace_bytes(0, R, n_env, n_agent, n_turn, 1), dev)
+    st = lib.at_grpo_group_advantage(R, n_env, n_agent, n_turn, env_id.data_ptr(), agent_id.data_ptr(), turn_id.data_ptr(),
+                                     reward.data_ptr(), eps_std, ddof, NORM[norm] | NORM_FILL, out["group_id"].data_ptr(),
+                                     out["n_groups"].data_ptr(), out["seg_offsets"].data_ptr(), out["perm"].data_ptr(),
+                                     out["adv"].data_ptr(), _ptr(out["group_mean"]), _ptr(out["group_std"]),
+                                     ws.data_ptr(), ws.numel(), _stream())
     _check(st, "at_grpo_group_advantage")
     out["workspace"] = ws
     return out
+
+
+@functools.lru_cache(maxsize=256)
+def _group_workspace_bytes(mode: int, R: int, n_env: int, n_agent: int, n_turn: int, n_sample: int) -> int:
+    nbytes = load_library().at_grpo_group_advantage_keyed_workspace_bytes(mode, R, n_env, n_agent, n_turn, n_sample)
+    if nbytes == 0:
+        raise AtGrpoError("at_grpo_workspace_bytes rejected the id extents")
+    return int(nbytes)
+
+
+def _group_buffers(R: int, gmax: int, dev, want_stats: bool):
+    """Uncleared outputs of a grouping call made with NORM_FILL (every entry is written)."""
+    e = torch.empty
+    i32, f32 = torch.int32, torch.float32
+    return dict(group_id=e(R, dtype=i32, device=dev), n_groups=e(1, dtype=i32, device=dev),
+                seg_offsets=e(gmax + 1, dtype=i32, device=dev), perm=e(R, dtype=i32, device=dev),
+                adv=e(R, dtype=f32, device=dev), group_mean=e(gmax, dtype=f32, device=dev) if want_stats else None,
+                group_std=e(gmax, dtype=f32, device=dev) if want_stats else None)
 
 
 def group_advantage_outputs(R: int, n_keys: int, dev, want_stats: bool = True):
@@ -299,13 +307,11 @@ def at_grpo_group_advantage_keyed(group_by: str, env_id, agent_id, turn_id, rewa
     R = reward.numel()
     mode = GROUP_BY[group_by]
     n_keys = n_env if mode == 1 else n_env * n_agent * n_turn * (n_sample if mode == 2 else 1)
-    out = group_advantage_outputs(R, n_keys, reward.device)
-    nbytes = lib.at_grpo_group_advantage_keyed_workspace_bytes(mode, R, n_env, n_agent, n_turn, n_sample)
-    if nbytes == 0:
-        raise AtGrpoError("at_grpo_group_advantage_keyed_workspace_bytes rejected the extents")
-    ws = _workspace(nbytes, reward.device)
+    out = _group_buffers(R, min(R, n_keys), reward.device, True)
+    out["data_error"] = torch.zeros(1, dtype=torch.int32, device=reward.device)
+    ws = _workspace(_group_workspace_bytes(mode, R, n_env, n_agent, n_turn, n_sample), reward.device)
     st = lib.at_grpo_group_advantage_keyed(mode, R, n_env, n_agent, n_turn, n_sample, _ptr(env_id), _ptr(agent_id),
-                                           _ptr(turn_id), _ptr(sample_id), _ptr(reward), eps_std, ddof, NORM[norm],
+                                           _ptr(turn_id), _ptr(sample_id), _ptr(reward), eps_std, ddof, NORM[norm] | NORM_FILL,
                                            _ptr(out["group_id"]), _ptr(out["n_groups"]), _ptr(out["seg_offsets"]),
                                            _ptr(out["perm"]), _ptr(out["adv"]), _ptr(out["group_mean"]),
                                            _ptr(out["group_std"]), _ptr(ws), ws.numel(), _stream())
@@ -352,26 +358,14 @@ def at_grpo_group_advantage_mixed(env_id, agent_id, turn_id, r_team, r_loc, alph
     _i32_check(env_id=env_id, agent_id=agent_id, turn_id=turn_id)
     dev = r_team.device
     R = r_team.numel()
-    n_keys = n_env * n_agent * n_turn
-    gmax = min(R, n_keys)
-    out = dict(
-        reward=torch.empty(R, dtype=torch.float32, device=dev),
-        group_id=torch.empty(R, dtype=torch.int32, device=dev),
-        n_groups=torch.zeros(1, dtype=torch.int32, device=dev),
-        seg_offsets=torch.zeros(gmax + 1, dtype=torch.int32, device=dev),
-        perm=torch.zeros(R, dtype=torch.int32, device=dev),
-        adv=torch.empty(R, dtype=torch.float32, device=dev),
-        group_mean=torch.zeros(gmax, dtype=torch.float32, device=dev) if want_stats else None,
-        group_std=torch.zeros(gmax, dtype=torch.float32, device=dev) if want_stats else None,
-        best=torch.full((gmax,), -1, dtype=torch.int32, device=dev) if want_best else None,
-    )
-    nbytes = lib.at_grpo_workspace_bytes(CALL_GROUP_ADVANTAGE, None, R, n_env, n_agent, n_turn)
-    if nbytes == 0:
-        raise AtGrpoError("at_grpo_workspace_bytes rejected the id extents")
-    ws = _workspace(nbytes, dev)
+    gmax = min(R, n_env * n_agent * n_turn)
+    out = dict(reward=torch.empty(R, dtype=torch.float32, device=dev))
+    out.update(_group_buffers(R, gmax, dev, want_stats))
+    out["best"] = torch.empty(gmax, dtype=torch.int32, device=dev) if want_best else None
+    ws = _workspace(_group_workspace_bytes(0, R, n_env, n_agent, n_turn, 1), dev)
     st = lib.at_grpo_group_advantage_mixed(R, n_env, n_agent, n_turn, _ptr(env_id), _ptr(agent_id),
                                            _ptr(turn_id), _ptr(r_team), _ptr(r_loc), alpha, eps_std, ddof,
-                                           NORM[norm], _ptr(out["reward"]), _ptr(out["group_id"]),
+                                           NORM[norm] | NORM_FILL, _ptr(out["reward"]), _ptr(out["group_id"]),
                                            _ptr(out["n_groups"]), _ptr(out["seg_offsets"]), _ptr(out["perm"]),
                                            _ptr(out["adv"]), _ptr(out["group_mean"]), _ptr(out["group_std"]),
                                            _ptr(out["best"]), _ptr(ws), ws.numel(), _stream())

@@ -4,13 +4,15 @@
 // rewards inside each group.  Here the key is the injective packing
 //   key = (e * n_agent + i) * n_turn + t,
 // groups are numbered densely in ascending key order, and the responses of a group are listed in
-// ascending original index (a stable sort by key).  Pipeline: histogram over the key space ->
-// exclusive scans (present keys -> dense ids, member counts -> CSR offsets) -> scatter by the
-// arrival rank the histogram's atomic returned (arbitrary order) -> per-group ordering of the
-// segment and the fp32 statistics.  The final ordering makes every output deterministic.
-// Three launch shapes, same device functions: everything in one workgroup (small batches: one
-// launch), five launches with a one-workgroup scan (key boxes up to 65536), seven launches with a
-// three-kernel scan (anything larger).
+// ascending original index (a stable sort by key).  Members are first listed per key in arbitrary order (the
+// return value of a histogram atomic), then ordered by counting inside their group, which makes every output
+// deterministic.  Three paths by size, with the same arithmetic per group:
+//   k_ga_range   up to 65536 responses over as many keys: one launch, two beyond 4096 responses.  Every workgroup owns a
+//                range of keys and scans all keys (they are in L2); nothing passes between workgroups.
+//   k_gp_*       pools of up to 16 million responses: partition by key range, each range finished in LDS, results gathered
+//                back in response order.
+//   k_ga_hist .. anything else (very many keys per response, or few keys with very many members): histogram over the key
+//                box, scans, scatter, finish.
 #include <mutex>
 
 #include "common.hpp"
@@ -198,166 +200,168 @@ struct GaStat {
   int ddof, norm;
 };
 
-// Eq. (1) for one group, sequential in perm order (fp32, two passes).
-__device__ __forceinline__ void group_stats_seq(const int32_t* perm_seg, int n,
-                                                const float* __restrict__ reward, const GaStat& st,
-                                                float* __restrict__ adv, float* mean_out, float* std_out) {
-  const float x0 = reward[perm_seg[0]];
+// One group of at most N <= 16 members, handled by one thread, in registers: ranks by counting, sums in ascending-index
+// order (fp32, two passes).  id(j), x(j): index and reward of member j in arrival order; put_perm(rank, id) and
+// put_adv(j, id, a) store; *best gets the first of the members with the largest reward.
+template <int N, typename Id, typename X, typename PutPerm, typename PutAdv>
+__device__ __forceinline__ void finish_small(int n, Id id_of, X x_of, PutPerm put_perm, PutAdv put_adv, const GaStat& st,
+                                             float* mean_out, float* std_out, int* best) {
+  int id[N];
+  float x[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) id[j] = (j < n) ? id_of(j) : 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < N; ++j) x[j] = (j < n) ? x_of(j) : 0.f;
+  float xs[N];      // rewards in perm order
+  int rank[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) c += (id[i] < id[j]);
+    rank[j] = c;
+  }
+#pragma unroll
+  for (int pos = 0; pos < N; ++pos) {
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < N; ++j) v = (rank[j] == pos && j < n) ? x[j] : v;
+    xs[pos] = v;
+  }
   float sum = 0.f;
   bool same = true;
-  for (int j = 0; j < n; ++j) {
-    const float x = reward[perm_seg[j]];
-    sum += x;
-    same = same && (x == x0);
-  }
-  if (same) {
-    for (int j = 0; j < n; ++j) adv[perm_seg[j]] = 0.f;
-    *mean_out = x0;
-    *std_out = 0.f;
-    return;
-  }
-  const float mean = sum / static_cast<float>(n);
-  float ss = 0.f;
-  for (int j = 0; j < n; ++j) {
-    const float d = reward[perm_seg[j]] - mean;
-    ss += d * d;
-  }
+#pragma unroll
+  for (int pos = 0; pos < N; ++pos)
+    if (pos < n) {
+      sum += xs[pos];
+      same = same && (xs[pos] == xs[0]);
+    }
+  const float mean = same ? xs[0] : sum / static_cast<float>(n);
+  float sd = 0.f, ss = 0.f;
+#pragma unroll
+  for (int pos = 0; pos < N; ++pos)
+    if (pos < n) {
+      const float d = xs[pos] - mean;
+      ss += d * d;
+    }
   const int denom = n - st.ddof;
-  const float sd = denom > 0 ? sqrtf(ss / static_cast<float>(denom)) : 0.f;
-  for (int j = 0; j < n; ++j) {
-    const int r = perm_seg[j];
-    adv[r] = (st.norm == AT_GRPO_NORM_STD) ? (reward[r] - mean) / (sd + st.eps_std) : (reward[r] - mean);
-  }
+  if (!same) sd = denom > 0 ? sqrtf(ss / static_cast<float>(denom)) : 0.f;
+  int top = id[0];
+  float xt = x[0];
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if (j < n) {
+      put_perm(rank[j], id[j]);
+      float a = 0.f;
+      if (!same) a = (st.norm == AT_GRPO_NORM_STD) ? (x[j] - mean) / (sd + st.eps_std) : (x[j] - mean);
+      put_adv(j, id[j], a);
+      if (x[j] > xt || (x[j] == xt && id[j] < top)) {
+        xt = x[j];
+        top = id[j];
+      }
+    }
   *mean_out = mean;
   *std_out = sd;
+  *best = top;
 }
 
-// One group of at most kSmallGroup members, handled by one thread: order the segment, Eq. (1).
-__device__ __forceinline__ void finish_group_by_thread(int g, const int32_t* __restrict__ seg_offsets,
-                                                       const int32_t* __restrict__ arrival,
-                                                       const float* __restrict__ reward, const GaStat& st,
-                                                       int32_t* perm, float* __restrict__ adv,
-                                                       float* __restrict__ group_mean,
-                                                       float* __restrict__ group_std) {
-  const int off = seg_offsets[g], n = seg_offsets[g + 1] - off;
-  if (n > kSmallGroup) return;
-  if (n <= 8) {
-    // whole group in registers: ranks by counting, sums taken in ascending-index order
-    int id[8];
-    float x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) id[j] = (j < n) ? arrival[off + j] : 0x7fffffff;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = (j < n) ? reward[id[j]] : 0.f;
-    int rank[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      int c = 0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) c += (id[i] < id[j]);
-      rank[j] = c;
-    }
-    float xs[8];      // rewards in perm order
-#pragma unroll
-    for (int pos = 0; pos < 8; ++pos) {
-      float v = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v = (rank[j] == pos && j < n) ? x[j] : v;
-      xs[pos] = v;
-    }
-    float sum = 0.f;
-    bool same = true;
-#pragma unroll
-    for (int pos = 0; pos < 8; ++pos)
-      if (pos < n) {
-        sum += xs[pos];
-        same = same && (xs[pos] == xs[0]);
-      }
-    float mean = same ? xs[0] : sum / static_cast<float>(n), sd = 0.f, ss = 0.f;
-#pragma unroll
-    for (int pos = 0; pos < 8; ++pos)
-      if (pos < n) {
-        const float d = xs[pos] - mean;
-        ss += d * d;
-      }
-    const int denom = n - st.ddof;
-    if (!same) sd = denom > 0 ? sqrtf(ss / static_cast<float>(denom)) : 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (j < n) {
-        perm[off + rank[j]] = id[j];
-        float a = 0.f;
-        if (!same) a = (st.norm == AT_GRPO_NORM_STD) ? (x[j] - mean) / (sd + st.eps_std) : (x[j] - mean);
-        adv[id[j]] = a;
-      }
-    if (group_mean) group_mean[g] = mean;
-    if (group_std) group_std[g] = sd;
-    return;
-  }
-  for (int j = 0; j < n; ++j) {
-    const int rj = arrival[off + j];
-    int rank = 0;
-    for (int i = 0; i < n; ++i) rank += (arrival[off + i] < rj);
-    perm[off + rank] = rj;
-  }
-  // perm[off .. off+n) was written by this thread only
-  float mu, sd;
-  group_stats_seq(perm + off, n, reward, st, adv, &mu, &sd);
-  if (group_mean) group_mean[g] = mu;
-  if (group_std) group_std[g] = sd;
+template <typename Id, typename X, typename PutPerm, typename PutAdv>
+__device__ __forceinline__ void finish_by_thread(int n, Id id_of, X x_of, PutPerm put_perm, PutAdv put_adv, const GaStat& st,
+                                                 float* mean, float* sd, int* best) {
+  if (n <= 8) finish_small<8>(n, id_of, x_of, put_perm, put_adv, st, mean, sd, best);
+  else finish_small<kSmallGroup>(n, id_of, x_of, put_perm, put_adv, st, mean, sd, best);
 }
 
-// One larger group, handled by one wavefront: ranks by counting, statistics combined in a fixed order.
-__device__ __forceinline__ void finish_group_by_wave(int g, int lane, const int32_t* __restrict__ seg_offsets,
-                                                     const int32_t* __restrict__ arrival,
-                                                     const float* __restrict__ reward, const GaStat& st,
-                                                     int32_t* perm, float* __restrict__ adv,
-                                                     float* __restrict__ group_mean,
-                                                     float* __restrict__ group_std) {
-  const int off = seg_offsets[g], n = seg_offsets[g + 1] - off;
-  if (n <= kSmallGroup) return;
+// One larger group, handled by one wavefront: ranks by counting, statistics as 64 lane-strided partial sums over the
+// ordered members, combined in a fixed order.  perm: the group's part of the output (global memory); reward(r): reward of
+// response r.
+template <typename Id, typename X, typename Reward, typename PutAdv>
+__device__ __forceinline__ void finish_by_wave(int n, int lane, Id id_of, X x_of, Reward reward, int32_t* perm, PutAdv put_adv, const GaStat& st, float* mean_out, float* std_out, int* best) {
   for (int j = lane; j < n; j += 64) {
-    const int rj = arrival[off + j];
+    const int rj = id_of(j);
     int rank = 0;
-    for (int i = 0; i < n; ++i) rank += (arrival[off + i] < rj);
-    perm[off + rank] = rj;
+    for (int i = 0; i < n; ++i) rank += (id_of(i) < rj);
+    perm[rank] = rj;
   }
   __threadfence();   // the ranks below are read back by other lanes of this wavefront
-  // statistics: lane-strided partial sums combined in a fixed order
-  const float x0 = reward[perm[off]];
-  float sum = 0.f;
-  int same = 1;
+  const float x0 = reward(perm[0]);
+  float sum = 0.f, xt = -INFINITY;
+  int same = 1, top = 0x7fffffff;
   for (int j = lane; j < n; j += 64) {
-    const float x = reward[perm[off + j]];
+    const int r = perm[j];
+    const float x = reward(r);
     sum += x;
     same &= (x == x0);
+    if (x > xt) {        // ascending indices: the first of equal rewards stays
+      xt = x;
+      top = r;
+    }
   }
   sum = wave_sum(sum);
   sum = __shfl(sum, 0, 64);
   same = __builtin_amdgcn_ballot_w64(same == 0) == 0ull;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float xo = __shfl_xor(xt, o, 64);
+    const int to = __shfl_xor(top, o, 64);
+    if (xo > xt || (xo == xt && to < top)) {
+      xt = xo;
+      top = to;
+    }
+  }
   float mean = sum / static_cast<float>(n), sd = 0.f;
   if (same) {
-    for (int j = lane; j < n; j += 64) adv[perm[off + j]] = 0.f;
     mean = x0;
   } else {
     float ss = 0.f;
     for (int j = lane; j < n; j += 64) {
-      const float d = reward[perm[off + j]] - mean;
+      const float d = reward(perm[j]) - mean;
       ss += d * d;
     }
     ss = wave_sum(ss);
     ss = __shfl(ss, 0, 64);
     const int denom = n - st.ddof;
     sd = denom > 0 ? sqrtf(ss / static_cast<float>(denom)) : 0.f;
-    for (int j = lane; j < n; j += 64) {
-      const int r = perm[off + j];
-      adv[r] = (st.norm == AT_GRPO_NORM_STD) ? (reward[r] - mean) / (sd + st.eps_std) : (reward[r] - mean);
-    }
   }
-  if (lane == 0) {
-    if (group_mean) group_mean[g] = mean;
-    if (group_std) group_std[g] = sd;
+  for (int j = lane; j < n; j += 64) {
+    const float x = x_of(j);
+    const float a = same ? 0.f : (st.norm == AT_GRPO_NORM_STD) ? (x - mean) / (sd + st.eps_std) : (x - mean);
+    put_adv(j, id_of(j), a);
   }
+  *mean_out = mean;
+  *std_out = sd;
+  *best = top;
+}
+
+// The group outputs, and how many groups the buffers hold; with `fill` the entries behind the last group and behind the
+// last listed response are set to zero (best: -1).
+struct GaOut {
+  int32_t* group_id;
+  int32_t* n_groups;
+  int32_t* seg_offsets;
+  int32_t* perm;
+  float* adv;
+  float* mean;     // may be null
+  float* std;      // may be null
+  int32_t* best;   // may be null
+  int32_t g_max;
+  int32_t fill;
+};
+
+__device__ __forceinline__ void put_stats(const GaOut& o, int g, float mean, float sd, int best) {
+  if (o.mean) o.mean[g] = mean;
+  if (o.std) o.std[g] = sd;
+  if (o.best) o.best[g] = best;
+}
+
+// fills the outputs behind group G - 1 and listed response n_listed - 1, with `threads` threads of which this is `tid`
+__device__ __forceinline__ void fill_tails(const GaOut& o, int G, int n_listed, int n_resp, int64_t tid, int64_t threads) {
+  if (!o.fill) return;
+  for (int64_t g = G + tid; g < o.g_max; g += threads) {
+    o.seg_offsets[g + 1] = 0;
+    put_stats(o, static_cast<int>(g), 0.f, 0.f, -1);
+  }
+  for (int64_t r = n_listed + tid; r < n_resp; r += threads) o.perm[r] = 0;
 }
 
 // Eq. (3): r = alpha * r_team + r_loc.  One fp32 multiplication, then one fp32 addition (never
@@ -374,41 +378,6 @@ __global__ __launch_bounds__(256) void k_ga_mix(int n, const float* __restrict__
   }
 }
 
-// Tree-structured sampling (Alg. 1): c* = arg max_c r^(c) per group, the first of equal rewards.
-// perm lists a group's members in ascending response index, so a strict comparison keeps the first.
-__global__ __launch_bounds__(256) void k_ga_select(const int32_t* __restrict__ n_groups,
-                                                   const int32_t* __restrict__ seg_offsets,
-                                                   const int32_t* __restrict__ perm,
-                                                   const float* __restrict__ reward,
-                                                   int32_t* __restrict__ best) {
-  const int G = *n_groups;
-  const int stride = gridDim.x * 256;
-  for (int g = blockIdx.x * 256 + threadIdx.x; g < G; g += stride) {
-    const int off = seg_offsets[g], n = seg_offsets[g + 1] - off;
-    int top = perm[off];
-    float xt = reward[top];
-    for (int j = 1; j < n; ++j) {
-      const int r = perm[off + j];
-      const float x = reward[r];
-      if (x > xt) {
-        xt = x;
-        top = r;
-      }
-    }
-    best[g] = top;
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// The whole call in one workgroup, for the sizes a training step actually has (a few thousand
-// groups, a few ten thousand responses): histogram, scans and the key tables live in LDS and the
-// phases are separated by workgroup barriers instead of kernel boundaries, so the call costs one
-// launch instead of five or seven.  Same arithmetic and the same device functions as the multi-launch path.
-// ------------------------------------------------------------------------------------------------
-constexpr int kSingleThreads = 1024;
-constexpr int kSingleMaxKeys = 8192;     // 3 tables of this many ints in LDS (96 KiB)
-constexpr int kSingleMaxResp = 4096;     // beyond this the multi-launch path is faster
-
 struct GaMix {
   const float* r_team;
   const float* r_loc;
@@ -416,8 +385,17 @@ struct GaMix {
   float* reward_out;
 };
 
-// exclusive scan of one int per thread over the 1024-thread workgroup; *total = sum
-__device__ __forceinline__ int block_exclusive_scan_1024(int v, int* lds16, int* total) {
+// the reward of response r: given, or mixed by Eq. (3)
+__device__ __forceinline__ float reward_of(const GaArgs& a, const GaMix& mix, int r) {
+#pragma clang fp contract(off)
+  if (!mix.r_team) return a.reward[r];
+  const float prod = mix.alpha * mix.r_team[r];
+  return prod + mix.r_loc[r];
+}
+
+// exclusive scan of one int per thread over the NT-thread workgroup; *total = sum
+template <int NT>
+__device__ __forceinline__ int block_exclusive_scan(int v, int* lds16, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int incl = v;
 #pragma unroll
@@ -430,7 +408,7 @@ __device__ __forceinline__ int block_exclusive_scan_1024(int v, int* lds16, int*
   __syncthreads();
   int base = 0, sum = 0;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     const int t = lds16[w];
     if (w < wave) base += t;
     sum += t;
@@ -439,165 +417,502 @@ __device__ __forceinline__ int block_exclusive_scan_1024(int v, int* lds16, int*
   return base + incl - v;
 }
 
-__global__ __launch_bounds__(kSingleThreads) void k_ga_single(
-    GaArgs a, GaMix mix, GaStat st, int n_keys, int32_t* __restrict__ err, int32_t* __restrict__ key_of_resp,
-    int32_t* __restrict__ rank_of_resp, int32_t* __restrict__ arrival, int32_t* __restrict__ group_id,
-    int32_t* __restrict__ n_groups, int32_t* __restrict__ seg_offsets, int32_t* perm,
-    float* __restrict__ adv, float* __restrict__ group_mean, float* __restrict__ group_std,
-    int32_t* __restrict__ best) {
-  __shared__ int hist[kSingleMaxKeys];
-  __shared__ int gid_of_key[kSingleMaxKeys];
-  __shared__ int off_of_key[kSingleMaxKeys];
+// ------------------------------------------------------------------------------------------------
+// The sizes a training step has, in one launch (two beyond 4096 responses, so that the keys are only computed once).
+// Workgroup b owns the keys [b * n_own, (b + 1) * n_own).  It scans the keys of all responses, counts those that are
+// smaller and marks which smaller ones occur (one bit each): that is all it needs to know of the others to place its own
+// groups.  Its own members go through an LDS list.  Bound by latency: launches, the scan (from L2), a dozen workgroup
+// barriers.  Whole calls: 128 responses 43 -> 16 us (the outputs were cleared by fills of their own), 20480 mixed rewards
+// 71 -> 23 us (seven launches and the fills before).
+// ------------------------------------------------------------------------------------------------
+constexpr int kRangeMaxResp = 65536, kRangeMaxKeys = 65528;
+constexpr int kRangeList = 4096;         // members listed in LDS; more go to global scratch
+constexpr int kRangeDirect = 4096;       // responses up to which every workgroup computes the keys itself
+constexpr int kRangeRounds = 4;          // responses per thread whose ids are in flight together
+
+// key of a response in 16 bits, or why it has none
+enum : int { kKeyNone = 0xfffd, kKeyBadReward = 0xfffe, kKeyBadId = 0xffff };
+
+__device__ __forceinline__ int key16(const GaArgs& a, const GaMix& mix, int r, float* x) {
+  bool ok;
+  const int64_t key = key_of(a, r, &ok);
+  *x = reward_of(a, mix, r);
+  return !ok ? kKeyBadId : (!finite_reward(*x) ? kKeyBadReward : static_cast<int>(key));
+}
+
+// the keys of all responses, padded to a multiple of 8; the mixed rewards
+__global__ __launch_bounds__(256) void k_ga_keys(GaArgs a, GaMix mix, uint16_t* __restrict__ keys) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= (a.n_resp + 7) / 8 * 8) return;
+  float x = 0.f;
+  const int key = r < a.n_resp ? key16(a, mix, r, &x) : kKeyNone;
+  keys[r] = static_cast<uint16_t>(key);
+  if (mix.reward_out && r < a.n_resp) mix.reward_out[r] = x;
+}
+
+// NT threads, each with at most one own key.  keys16: the keys (then a.reward holds the rewards), or null.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st, int n_keys, int n_own,
+                                                 const uint16_t* __restrict__ keys16, int32_t* __restrict__ err,
+                                                 int32_t* __restrict__ arrival, GaOut o) {
+  __shared__ int present[(kRangeMaxKeys + 31) / 32];
+  __shared__ int count[NT], cursor[NT], first[NT], gid[NT];
+  __shared__ int list_id[kRangeList];
+  __shared__ float list_x[kRangeList];
   __shared__ int lds16[16];
-  __shared__ int s_groups;
-  const int tid = threadIdx.x;
-  if (tid == 0) *err = 0;
-  for (int k = tid; k < n_keys; k += kSingleThreads) hist[k] = 0;
-  if (mix.r_team) {
-#pragma clang fp contract(off)
-    for (int r = tid; r < a.n_resp; r += kSingleThreads) {
-      const float prod = mix.alpha * mix.r_team[r];
-      mix.reward_out[r] = prod + mix.r_loc[r];      // read back below by the thread that wrote it
-    }
-  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.x, lo = b * n_own, own = min(n_own, n_keys - lo);
+  for (int k = tid; k < (lo + 31) / 32; k += NT) present[k] = 0;
+  count[tid] = 0;
   __syncthreads();
 
-  // histogram: the atomic's return value is the arrival rank inside the group
-  for (int r = tid; r < a.n_resp; r += kSingleThreads) {
-    bool ok;
-    const int64_t k64 = key_of(a, r, &ok);
-    int key = -1;
-    if (!ok) {
-      atomicOr(err, AT_GRPO_DATA_ID_RANGE);
-    } else if (!finite_reward(a.reward[r])) {
-      atomicOr(err, AT_GRPO_DATA_REWARD);     // takes no part: no group, advantage 0
-    } else {
-      key = static_cast<int>(k64);
-      rank_of_resp[r] = atomicAdd(&hist[key], 1);
+  int keys[kRangeRounds];          // without keys16: of the last batch, all of them when there is one batch only
+  int below = 0, bad = 0;
+  // (keys that stand for "none" are above every range); workgroup 0 has no smaller keys and looks for bad ones instead
+  auto look = [&](int key, bool new_run) {
+    below += key < lo;
+    const unsigned d = static_cast<unsigned>(key - lo);
+    if (d < static_cast<unsigned>(own)) atomicAdd(&count[d], 1);
+    if (b == 0) {
+      bad |= key == kKeyBadId ? AT_GRPO_DATA_ID_RANGE : (key == kKeyBadReward ? AT_GRPO_DATA_REWARD : 0);
+    } else if (key < lo && new_run) {
+      atomicOr(&present[key >> 5], 1 << (key & 31));   // once per run of equal keys
     }
-    key_of_resp[r] = key;
-  }
-  __syncthreads();
-
-  // scans over the key box: present keys -> dense ids, member counts -> CSR offsets
-  const int per = (n_keys + kSingleThreads - 1) / kSingleThreads;     // <= 8
-  const int k0 = tid * per;
-  int p = 0, c = 0;
-  for (int e = 0; e < per; ++e) {
-    const int h = (k0 + e < n_keys) ? hist[k0 + e] : 0;
-    p += (h > 0);
-    c += h;
-  }
-  int tot_p, tot_c;
-  int gp = block_exclusive_scan_1024(p, lds16, &tot_p);
-  int gc = block_exclusive_scan_1024(c, lds16, &tot_c);
-  for (int e = 0; e < per; ++e) {
-    const int h = (k0 + e < n_keys) ? hist[k0 + e] : 0;
-    if (h > 0) {
-      gid_of_key[k0 + e] = gp;
-      off_of_key[k0 + e] = gc;
-      seg_offsets[gp] = gc;
-      ++gp;
-      gc += h;
-    }
-  }
-  if (tid == 0) {
-    *n_groups = tot_p;
-    seg_offsets[tot_p] = tot_c;
-    s_groups = tot_p;
-  }
-  __syncthreads();
-
-  // scatter by arrival rank
-  for (int r = tid; r < a.n_resp; r += kSingleThreads) {
-    const int key = key_of_resp[r];
-    if (key < 0) {
-      group_id[r] = -1;
-      adv[r] = 0.f;
-      continue;
-    }
-    group_id[r] = gid_of_key[key];
-    arrival[off_of_key[key] + rank_of_resp[r]] = r;
-  }
-  __syncthreads();   // arrival and seg_offsets (global) are read by other threads below
-
-  const int G = s_groups;
-  for (int g = tid; g < G; g += kSingleThreads)
-    finish_group_by_thread(g, seg_offsets, arrival, a.reward, st, perm, adv, group_mean, group_std);
-  const int lane = tid & 63, wave = tid >> 6;
-  for (int g = wave; g < G; g += kSingleThreads / 64)
-    finish_group_by_wave(g, lane, seg_offsets, arrival, a.reward, st, perm, adv, group_mean, group_std);
-  if (best) {
-    __syncthreads();   // perm is complete
-    for (int g = tid; g < G; g += kSingleThreads) {
-      const int off = seg_offsets[g], n = seg_offsets[g + 1] - off;
-      int top = perm[off];
-      float xt = a.reward[top];
-      for (int j = 1; j < n; ++j) {
-        const int r = perm[off + j];
-        const float x = a.reward[r];
-        if (x > xt) {
-          xt = x;
-          top = r;
-        }
+  };
+  if (keys16) {
+    for (int c = tid; c * 8 < a.n_resp; c += NT) {
+      const uint4 v = reinterpret_cast<const uint4*>(keys16)[c];
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      int prev = -1;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int key = (w[e >> 1] >> (16 * (e & 1))) & 0xffff;
+        look(key, key != prev);
+        prev = key;
       }
-      best[g] = top;
     }
-  }
-}
-
-// both finishing roles in one launch: the first n_small blocks take the small groups (a thread each),
-// the remaining blocks the larger ones (a wavefront each)
-__global__ __launch_bounds__(256) void k_ga_finish(int n_small, const int32_t* __restrict__ n_groups,
-                                                   const int32_t* __restrict__ seg_offsets,
-                                                   const int32_t* __restrict__ arrival,
-                                                   const float* __restrict__ reward, GaStat st, int32_t* perm,
-                                                   float* __restrict__ adv, float* __restrict__ group_mean,
-                                                   float* __restrict__ group_std) {
-  const int G = *n_groups;
-  if (static_cast<int>(blockIdx.x) < n_small) {
-    const int stride = n_small * 256;
-    for (int g = blockIdx.x * 256 + threadIdx.x; g < G; g += stride)
-      finish_group_by_thread(g, seg_offsets, arrival, reward, st, perm, adv, group_mean, group_std);
   } else {
-    const int lane = threadIdx.x & 63;
-    const int wave = ((blockIdx.x - n_small) * 256 + threadIdx.x) >> 6;
-    const int n_waves = ((gridDim.x - n_small) * 256) >> 6;
-    for (int g = wave; g < G; g += n_waves)
-      finish_group_by_wave(g, lane, seg_offsets, arrival, reward, st, perm, adv, group_mean, group_std);
+    for (int base = 0; base < a.n_resp; base += kRangeRounds * NT) {
+      float x[kRangeRounds];
+#pragma unroll
+      for (int u = 0; u < kRangeRounds; ++u) {
+        const int r = base + u * NT + tid;
+        x[u] = 0.f;
+        keys[u] = r < a.n_resp ? key16(a, mix, r, &x[u]) : kKeyNone;
+      }
+#pragma unroll
+      for (int u = 0; u < kRangeRounds; ++u) {
+        const int r = base + u * NT + tid;
+        if (mix.reward_out && r < a.n_resp && b == 0) mix.reward_out[r] = x[u];
+        const int prev = __shfl_up(keys[u], 1, 64);
+        look(keys[u], lane == 0 || prev != keys[u]);
+      }
+    }
+  }
+  __syncthreads();                 // every bit is set
+  int bits = 0;
+  for (int k = tid; k < (lo + 31) / 32; k += NT) bits += __popc(present[k]);
+  int all_below, g_below, own_groups, own_members;
+  block_exclusive_scan<NT>(below, lds16, &all_below);
+  block_exclusive_scan<NT>(bits, lds16, &g_below);
+  below = all_below;
+
+  // own keys: dense ids and offsets
+  const int c = tid < own ? count[tid] : 0;
+  const int g_own = block_exclusive_scan<NT>(c > 0 ? 1 : 0, lds16, &own_groups);
+  const int f_own = block_exclusive_scan<NT>(c, lds16, &own_members);
+  first[tid] = f_own;
+  cursor[tid] = f_own;
+  gid[tid] = g_below + g_own;
+  if (c > 0) o.seg_offsets[g_below + g_own] = below + f_own;
+  const bool in_lds = own_members <= kRangeList;
+  __syncthreads();
+
+  // list the own members
+  auto enlist = [&](int r, int key) {
+    const unsigned d = static_cast<unsigned>(key - lo);
+    if (d < static_cast<unsigned>(own)) {
+      const int at = atomicAdd(&cursor[d], 1);
+      if (in_lds) list_id[at] = r;
+      else arrival[below + at] = r;
+      o.group_id[r] = gid[d];
+    }
+    if (b == 0 && key > kKeyNone) {
+      o.group_id[r] = -1;
+      o.adv[r] = 0.f;
+    }
+  };
+  if (keys16) {
+    for (int cc = tid; cc * 8 < a.n_resp; cc += NT) {
+      const uint4 v = reinterpret_cast<const uint4*>(keys16)[cc];
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) enlist(cc * 8 + e, (w[e >> 1] >> (16 * (e & 1))) & 0xffff);
+    }
+  } else {
+    for (int base = 0; base < a.n_resp; base += kRangeRounds * NT) {
+#pragma unroll
+      for (int u = 0; u < kRangeRounds; ++u) {
+        const int r = base + u * NT + tid;
+        float x;
+        if (a.n_resp > kRangeRounds * NT) keys[u] = r < a.n_resp ? key16(a, mix, r, &x) : kKeyNone;   // else still in registers
+        enlist(r, keys[u]);
+      }
+    }
+  }
+  __syncthreads();
+  if (in_lds) {      // all rewards at once: one load latency instead of one per member met above
+    for (int i = tid; i < own_members; i += NT) list_x[i] = reward_of(a, mix, list_id[i]);
+    __syncthreads();
+  }
+
+  auto reward = [&](int r) { return reward_of(a, mix, r); };
+  auto finish = [&](auto id_of, auto x_of) {
+    if (c > 0 && c <= kSmallGroup) {
+      float mean, sd;
+      int best;
+      int32_t* perm = o.perm + below + f_own;
+      finish_by_thread(
+          c, [&](int j) { return id_of(f_own + j); }, [&](int j) { return x_of(f_own + j); },
+          [&](int rank, int r) { perm[rank] = r; }, [&](int, int r, float v) { o.adv[r] = v; }, st, &mean, &sd, &best);
+      put_stats(o, g_below + g_own, mean, sd, best);
+    }
+    for (int k = wave; k < own; k += NT / 64) {
+      const int n = count[k], f = first[k];
+      if (n <= kSmallGroup) continue;
+      float mean, sd;
+      int best;
+      finish_by_wave(
+          n, lane, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); }, reward, o.perm + below + f,
+          [&](int, int r, float v) { o.adv[r] = v; }, st, &mean, &sd, &best);
+      if (lane == 0) put_stats(o, gid[k], mean, sd, best);
+    }
+  };
+  if (in_lds) finish([&](int j) { return list_id[j]; }, [&](int j) { return list_x[j]; });
+  else finish([&](int j) { return arrival[below + j]; }, [&](int j) { return reward(arrival[below + j]); });
+
+  if (b == 0) {
+    const int id_bad = __syncthreads_or(bad & AT_GRPO_DATA_ID_RANGE), x_bad = __syncthreads_or(bad & AT_GRPO_DATA_REWARD);
+    if (tid == 0) *err = (id_bad ? AT_GRPO_DATA_ID_RANGE : 0) | (x_bad ? AT_GRPO_DATA_REWARD : 0);
+  }
+  if (b == static_cast<int>(gridDim.x) - 1) {
+    const int G = g_below + own_groups, listed = below + own_members;
+    if (tid == 0) {
+      *o.n_groups = G;
+      o.seg_offsets[G] = listed;
+    }
+    fill_tails(o, G, listed, a.n_resp, tid, NT);
   }
 }
 
-// both scans over a key box of at most kScanSingleKeys keys in one workgroup
-constexpr int kScanSingleKeys = 65536;
-__global__ __launch_bounds__(kSingleThreads) void k_ga_scan_single(const int32_t* __restrict__ hist, int n_keys,
-                                                                   int32_t* __restrict__ gid_of_key,
-                                                                   int32_t* __restrict__ n_groups,
-                                                                   int32_t* __restrict__ seg_offsets) {
-  __shared__ int lds16[16];
-  const int per = (n_keys + kSingleThreads - 1) / kSingleThreads;
-  const int k0 = threadIdx.x * per;
-  int p = 0, c = 0;
-  for (int e = 0; e < per; ++e) {
-    const int h = (k0 + e < n_keys) ? hist[k0 + e] : 0;
-    p += (h > 0);
-    c += h;
-  }
-  int tot_p, tot_c;
-  int gp = block_exclusive_scan_1024(p, lds16, &tot_p);
-  int gc = block_exclusive_scan_1024(c, lds16, &tot_c);
-  for (int e = 0; e < per; ++e) {
-    const int h = (k0 + e < n_keys) ? hist[k0 + e] : 0;
-    if (h > 0) {
-      gid_of_key[k0 + e] = gp;
-      seg_offsets[gp] = gc;
-      ++gp;
-      gc += h;
+// ------------------------------------------------------------------------------------------------
+// Pools.  A response needs four accesses at unrelated addresses if histogram, ranks, lists and results live in global memory
+// (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of about 3072
+// responses) with LDS counters, so that every run written is a few entries long; each bin is finished by one workgroup in
+// LDS; and one last pass in response order gathers the results, again in runs.  About 84 bytes per response, all streamed.
+// 2^22 shuffled responses over 2^19 keys: 270 us on the stream (partition 101, results 73, bins 56, counts 22).
+// ------------------------------------------------------------------------------------------------
+constexpr int kPoolThreads = 1024, kPoolPer = 16, kPoolBlock = kPoolThreads * kPoolPer;   // responses per partitioning block
+constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolPerBin = 3072;
+constexpr int kPoolMaxKeys = 2048;       // keys of a bin
+constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; more are listed in global scratch
+constexpr int kBinThreads = 512;
+
+struct PoolPlan {
+  int width, bins;           // bin of a key = key / width
+  int32_t* key;              // [R]
+  int32_t* slot;             // [R] place of the response in the partitioned order
+  int32_t* list;             // [R] members of oversized bins
+  int2* kr;                  // [R] (key, response), partitioned
+  float* x;                  // [R] rewards, partitioned
+  float2* result;            // [R] (advantage, group inside the bin), partitioned; bit 31: the advantage is stored already
+  float4* stats;             // [R] (mean, std, best, offset) of group i of the bin at bin_base + i
+  int32_t* blk;              // [blocks][bins]
+  int32_t* bin_cnt;          // [bins]
+  int32_t* bin_base;         // [bins + 1]
+  int32_t* cursor;           // [bins]
+  int32_t* bin_groups;       // [bins]
+  int32_t* gid_base;         // [bins + 1]
+};
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_init(int32_t* __restrict__ bin_cnt, int bins, int32_t* __restrict__ err) {
+  for (int i = threadIdx.x; i < bins; i += kPoolThreads) bin_cnt[i] = 0;
+  if (threadIdx.x == 0) *err = 0;
+}
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_count(GaArgs a, GaMix mix, PoolPlan p, int32_t* __restrict__ err) {
+  __shared__ int hist[kPoolMaxBins];
+  for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) hist[i] = 0;
+  __syncthreads();
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolBlock + threadIdx.x;
+  int bad = 0;
+#pragma unroll 4
+  for (int u = 0; u < kPoolPer; ++u) {
+    const int64_t r = r0 + u * kPoolThreads;
+    if (r < a.n_resp) {
+      bool ok;
+      const int64_t k64 = key_of(a, static_cast<int>(r), &ok);
+      const float x = reward_of(a, mix, static_cast<int>(r));
+      if (mix.reward_out) mix.reward_out[r] = x;
+      int key = -1;
+      if (!ok) bad |= AT_GRPO_DATA_ID_RANGE;
+      else if (!finite_reward(x)) bad |= AT_GRPO_DATA_REWARD;
+      else key = static_cast<int>(k64);
+      p.key[r] = key;
+      if (key >= 0) atomicAdd(&hist[static_cast<unsigned>(key) / static_cast<unsigned>(p.width)], 1);
     }
   }
+  if (bad) atomicOr(err, bad);
+  __syncthreads();
+  for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) {
+    const int c = hist[i];
+    p.blk[static_cast<size_t>(blockIdx.x) * p.bins + i] = c;
+    if (c) atomicAdd(&p.bin_cnt[i], c);
+  }
+}
+
+// exclusive scan of n <= 4096 counts by one workgroup; out[n] = total
+__device__ __forceinline__ void scan_small(const int32_t* in, int n, int32_t* out, int32_t* out2, int* lds16) {
+  int v[kPoolMaxBins / kPoolThreads], sum = 0;
+#pragma unroll
+  for (int e = 0; e < kPoolMaxBins / kPoolThreads; ++e) {
+    const int i = threadIdx.x * (kPoolMaxBins / kPoolThreads) + e;
+    v[e] = i < n ? in[i] : 0;
+    sum += v[e];
+  }
+  int total;
+  int at = block_exclusive_scan<kPoolThreads>(sum, lds16, &total);
+#pragma unroll
+  for (int e = 0; e < kPoolMaxBins / kPoolThreads; ++e) {
+    const int i = threadIdx.x * (kPoolMaxBins / kPoolThreads) + e;
+    if (i < n) {
+      out[i] = at;
+      if (out2) out2[i] = at;
+    }
+    at += v[e];
+  }
+  if (threadIdx.x == 0) out[n] = total;
+}
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_bases(PoolPlan p) {
+  __shared__ int lds16[16];
+  scan_small(p.bin_cnt, p.bins, p.bin_base, p.cursor, lds16);
+}
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const float* __restrict__ reward, PoolPlan p) {
+  __shared__ int next[kPoolMaxBins];
+  for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) {
+    const int c = p.blk[static_cast<size_t>(blockIdx.x) * p.bins + i];
+    next[i] = c ? atomicAdd(&p.cursor[i], c) : 0;
+  }
+  __syncthreads();
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolBlock + threadIdx.x;
+#pragma unroll 4
+  for (int u = 0; u < kPoolPer; ++u) {
+    const int64_t r = r0 + u * kPoolThreads;
+    if (r < n_resp) {
+      const int key = p.key[r];
+      if (key >= 0) {
+        const int at = atomicAdd(&next[static_cast<unsigned>(key) / static_cast<unsigned>(p.width)], 1);
+        p.kr[at] = make_int2(key, static_cast<int>(r));
+        p.x[at] = reward[r];
+        p.slot[r] = at;
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float* __restrict__ reward, GaStat st, int64_t n_keys,
+                                                        GaOut o) {
+  __shared__ int list_id[kPoolCap];
+  __shared__ float list_x[kPoolCap];
+  __shared__ uint16_t place[kPoolCap];
+  __shared__ int count[kPoolMaxKeys], next[kPoolMaxKeys];
+  __shared__ uint16_t gid[kPoolMaxKeys];
+  __shared__ int wsum[2][kBinThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int bin = blockIdx.x, base = p.bin_base[bin], m = p.bin_base[bin + 1] - base;
+  const int lo = bin * p.width;
+  const int own = static_cast<int>(min(static_cast<int64_t>(p.width), n_keys - lo));
+  const bool in_lds = m <= kPoolCap;
+  for (int k = tid; k < own; k += kBinThreads) count[k] = 0;
+  __syncthreads();
+  for (int e = tid; e < m; e += kBinThreads) atomicAdd(&count[p.kr[base + e].x - lo], 1);
+  __syncthreads();
+  // offsets and ids of the keys that occur: each thread owns a run of keys
+  constexpr int kPer = kPoolMaxKeys / kBinThreads;
+  int c[kPer], members = 0, groups = 0;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int k = tid * kPer + e;
+    c[e] = k < own ? count[k] : 0;
+    members += c[e];
+    groups += c[e] > 0;
+  }
+  int im = members, ig = groups;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int um = __shfl_up(im, d, 64), ug = __shfl_up(ig, d, 64);
+    if (lane >= d) {
+      im += um;
+      ig += ug;
+    }
+  }
+  if (lane == 63) {
+    wsum[0][wave] = im;
+    wsum[1][wave] = ig;
+  }
+  __syncthreads();
+  int at = im - members, g = ig - groups, n_groups = 0;
+#pragma unroll
+  for (int w = 0; w < kBinThreads / 64; ++w) {
+    if (w < wave) {
+      at += wsum[0][w];
+      g += wsum[1][w];
+    }
+    n_groups += wsum[1][w];
+  }
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int k = tid * kPer + e;
+    if (k < own) {
+      next[k] = at;
+      gid[k] = static_cast<uint16_t>(g);
+      at += c[e];
+      g += c[e] > 0;
+    }
+  }
+  if (tid == 0) p.bin_groups[bin] = n_groups;
+  __syncthreads();
+  for (int e = tid; e < m; e += kBinThreads) {
+    const int2 kr = p.kr[base + e];
+    const int k = kr.x - lo, f = atomicAdd(&next[k], 1);
+    if (in_lds) {
+      list_id[f] = kr.y;
+      list_x[f] = p.x[base + e];
+      place[e] = static_cast<uint16_t>(f);
+    } else {
+      p.list[base + f] = kr.y;
+      p.result[base + e] = make_float2(0.f, __int_as_float(static_cast<int>(gid[k] | 0x80000000u)));
+    }
+  }
+  __syncthreads();
+  // next[k] is now one past the members of key k
+  auto reward_at = [&](int r) { return reward[r]; };
+  auto finish = [&](auto id_of, auto x_of, auto put_adv) {
+    for (int k = tid; k < own; k += kBinThreads) {
+      const int n = count[k], f = next[k] - n;
+      if (n == 0 || n > kSmallGroup) continue;
+      float mean, sd;
+      int best;
+      int32_t* perm = o.perm + base + f;
+      finish_by_thread(
+          n, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); },
+          [&](int rank, int r) { perm[rank] = r; }, [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
+      p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
+    }
+    for (int k = wave; k < own; k += kBinThreads / 64) {
+      const int n = count[k], f = next[k] - n;
+      if (n <= kSmallGroup) continue;
+      float mean, sd;
+      int best;
+      finish_by_wave(
+          n, lane, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); }, reward_at, o.perm + base + f,
+          [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
+      if (lane == 0) p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
+    }
+  };
+  if (in_lds) {
+    // a member's advantage takes the place of its reward, which only its own group reads
+    finish([&](int j) { return list_id[j]; }, [&](int j) { return list_x[j]; }, [&](int j, int, float v) { list_x[j] = v; });
+    __syncthreads();
+    for (int e = tid; e < m; e += kBinThreads)
+      p.result[base + e] = make_float2(list_x[place[e]], __int_as_float(static_cast<int>(gid[p.kr[base + e].x - lo])));
+  } else {
+    finish([&](int j) { return p.list[base + j]; }, [&](int j) { return reward[p.list[base + j]]; },
+           [&](int, int r, float v) { o.adv[r] = v; });
+  }
+}
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_groups(PoolPlan p, GaOut o) {
+  __shared__ int lds16[16];
+  scan_small(p.bin_groups, p.bins, p.gid_base, nullptr, lds16);
+  __threadfence();
+  __syncthreads();
   if (threadIdx.x == 0) {
-    *n_groups = tot_p;
-    seg_offsets[tot_p] = tot_c;
+    const int G = p.gid_base[p.bins];
+    *o.n_groups = G;
+    o.seg_offsets[G] = p.bin_base[p.bins];
+  }
+}
+
+// results in response order; the blocks behind `resp_blocks` write the groups of a bin each, the last ones fill the tails
+__global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp_blocks, GaOut o) {
+  if (static_cast<int>(blockIdx.x) < resp_blocks) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = (static_cast<int64_t>(blockIdx.x) * 4 + u) * 256 + threadIdx.x;
+      if (r >= n_resp) break;
+      const int key = p.key[r];
+      if (key < 0) {
+        o.group_id[r] = -1;
+        o.adv[r] = 0.f;
+      } else {
+        const float2 res = p.result[p.slot[r]];
+        const int lg = __float_as_int(res.y);
+        o.group_id[r] = p.gid_base[static_cast<unsigned>(key) / static_cast<unsigned>(p.width)] + (lg & 0x7fffffff);
+        if (lg >= 0) o.adv[r] = res.x;
+      }
+    }
+    return;
+  }
+  const int bin = blockIdx.x - resp_blocks;
+  if (bin < p.bins) {
+    const int g0 = p.gid_base[bin], n = p.gid_base[bin + 1] - g0, base = p.bin_base[bin];
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const float4 s = p.stats[base + i];
+      o.seg_offsets[g0 + i] = __float_as_int(s.w);
+      put_stats(o, g0 + i, s.x, s.y, __float_as_int(s.z));
+    }
+    return;
+  }
+  const int64_t tid = static_cast<int64_t>(bin - p.bins) * 256 + threadIdx.x;
+  fill_tails(o, p.gid_base[p.bins], p.bin_base[p.bins], n_resp, tid,
+             static_cast<int64_t>(gridDim.x - resp_blocks - p.bins) * 256);
+}
+
+// both finishing roles in one launch: the first n_small blocks take the small groups (a thread each), the next n_large the
+// larger ones (a wavefront each), the rest the tails
+__global__ __launch_bounds__(256) void k_ga_finish(int n_small, int n_large, int n_resp, const int32_t* __restrict__ arrival,
+                                                   const float* __restrict__ reward, GaStat st, GaOut o) {
+  const int G = *o.n_groups, b = blockIdx.x;
+  auto put_adv = [&](int, int r, float v) { o.adv[r] = v; };
+  if (b < n_small) {
+    for (int g = b * 256 + threadIdx.x; g < G; g += n_small * 256) {
+      const int off = o.seg_offsets[g], n = o.seg_offsets[g + 1] - off;
+      if (n > kSmallGroup) continue;
+      float mean, sd;
+      int best;
+      finish_by_thread(
+          n, [&](int j) { return arrival[off + j]; }, [&](int j) { return reward[arrival[off + j]]; },
+          [&](int rank, int r) { o.perm[off + rank] = r; }, put_adv, st, &mean, &sd, &best);
+      put_stats(o, g, mean, sd, best);
+    }
+  } else if (b < n_small + n_large) {
+    const int lane = threadIdx.x & 63;
+    for (int g = ((b - n_small) * 256 + threadIdx.x) >> 6; g < G; g += (n_large * 256) >> 6) {
+      const int off = o.seg_offsets[g], n = o.seg_offsets[g + 1] - off;
+      if (n <= kSmallGroup) continue;
+      float mean, sd;
+      int best;
+      finish_by_wave(
+          n, lane, [&](int j) { return arrival[off + j]; }, [&](int j) { return reward[arrival[off + j]]; },
+          [&](int r) { return reward[r]; }, o.perm + off, put_adv, st, &mean, &sd, &best);
+      if (lane == 0) put_stats(o, g, mean, sd, best);
+    }
+  } else {
+    fill_tails(o, G, o.seg_offsets[G], n_resp, static_cast<int64_t>(b - n_small - n_large) * 256 + threadIdx.x,
+               static_cast<int64_t>(gridDim.x - n_small - n_large) * 256);
   }
 }
 
@@ -610,6 +925,8 @@ __global__ void k_ga_clear2(int32_t* __restrict__ p, int64_t n, int32_t* __restr
 
 struct GaPlan {
   int64_t n_keys, n_blocks;
+  bool pooled;
+  PoolPlan pool;
   int32_t *err, *hist, *gid_of_key, *key_of_resp, *rank_of_resp, *arrival, *bsum_p, *bsum_c;
 };
 
@@ -638,6 +955,36 @@ bool plan(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t n_turn, int32_
   return true;
 }
 
+// The pool path's scratch, behind the common part; false if the path does not apply: too few responses to fill the chip
+// with bins, bins of too many keys, or so few keys that the bins overflow.
+bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
+  if (n_resp <= kRangeMaxResp && p->n_keys <= kRangeMaxKeys) return false;
+  int64_t want = ceil_div(n_resp, kPoolPerBin);
+  if (want < kPoolMinBins) want = kPoolMinBins;
+  if (want > kPoolMaxBins) want = kPoolMaxBins;
+  const int64_t width = ceil_div(p->n_keys, want);
+  PoolPlan& q = p->pool;
+  q.width = static_cast<int>(width);
+  q.bins = static_cast<int>(ceil_div(p->n_keys, width));
+  if (width > kPoolMaxKeys || n_resp < kRangeMaxResp / 2) return false;
+  if (static_cast<int64_t>(n_resp) > static_cast<int64_t>(q.bins) * kPoolCap * 3 / 4) return false;
+  const size_t R = static_cast<size_t>(n_resp), blocks = static_cast<size_t>(ceil_div(n_resp, kPoolBlock));
+  q.key = p->key_of_resp;
+  q.slot = p->rank_of_resp;
+  q.list = p->arrival;
+  q.kr = ws.take<int2>(R);
+  q.x = ws.take<float>(R);
+  q.result = ws.take<float2>(R);
+  q.stats = ws.take<float4>(R);
+  q.blk = ws.take<int32_t>(blocks * static_cast<size_t>(q.bins));
+  q.bin_cnt = ws.take<int32_t>(static_cast<size_t>(q.bins));
+  q.bin_base = ws.take<int32_t>(static_cast<size_t>(q.bins) + 1);
+  q.cursor = ws.take<int32_t>(static_cast<size_t>(q.bins));
+  q.bin_groups = ws.take<int32_t>(static_cast<size_t>(q.bins));
+  q.gid_base = ws.take<int32_t>(static_cast<size_t>(q.bins) + 1);
+  return true;
+}
+
 }  // namespace
 
 size_t group_advantage_workspace(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t n_turn, int32_t group_by,
@@ -645,11 +992,20 @@ size_t group_advantage_workspace(int32_t n_resp, int32_t n_env, int32_t n_agent,
   WsAlloc ws(nullptr);
   GaPlan p;
   if (!plan(n_resp, n_env, n_agent, n_turn, group_by, n_sample, ws, &p)) return 0;
+  plan_pool(n_resp, ws, &p);
   return ws.bytes();
 }
 
 size_t group_advantage_workspace(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t n_turn) {
   return group_advantage_workspace(n_resp, n_env, n_agent, n_turn, AT_GRPO_GROUP_BY_AGENT_TURN, 1);
+}
+
+// what the call can do with at the least (the pool path needs more and is left out then)
+size_t group_advantage_least_workspace(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t n_turn) {
+  WsAlloc ws(nullptr);
+  GaPlan p;
+  if (!plan(n_resp, n_env, n_agent, n_turn, AT_GRPO_GROUP_BY_AGENT_TURN, 1, ws, &p)) return 0;
+  return ws.bytes();
 }
 
 }  // namespace atg
@@ -675,6 +1031,8 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     return AT_GRPO_EINVAL;
   if (group_by == AT_GRPO_GROUP_BY_PARALLEL && (!sample_id || n_sample <= 0)) return AT_GRPO_EINVAL;
   if (ddof != 0 && ddof != 1) return AT_GRPO_EINVAL;
+  const int32_t fill = (norm & AT_GRPO_NORM_FILL) != 0;
+  norm &= ~AT_GRPO_NORM_FILL;
   if (norm != AT_GRPO_NORM_STD && norm != AT_GRPO_NORM_NONE) return AT_GRPO_EINVAL;
   if (!(eps_std >= 0.f)) return AT_GRPO_EINVAL;
   WsAlloc ws(workspace);
@@ -685,14 +1043,57 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   ProfScope ps(PROF_GROUP, s);
 
-  if (p.n_keys <= kSingleMaxKeys && n_resp <= kSingleMaxResp) {
-    const GaMix mix{r_team, r_loc, alpha, reward_out};
-    const GaArgs a1{n_resp, n_env, n_agent, n_turn, env_id, agent_id, turn_id, r_team ? reward_out : reward,
-                    group_by, n_sample, sample_id};
-    const GaStat st1{eps_std, ddof, norm};
-    hipLaunchKernelGGL(k_ga_single, dim3(1), dim3(kSingleThreads), 0, s, a1, mix, st1, static_cast<int>(p.n_keys),
-                       p.err, p.key_of_resp, p.rank_of_resp, p.arrival, group_id, n_groups, seg_offsets, perm, adv,
-                       group_mean, group_std, best);
+  const GaMix mix{r_team, r_loc, alpha, r_team ? reward_out : nullptr};
+  GaArgs a{n_resp, n_env, n_agent, n_turn, env_id, agent_id, turn_id, reward, group_by, n_sample, sample_id};
+  const GaStat st{eps_std, ddof, norm};
+  const int64_t g_max = n_resp < p.n_keys ? n_resp : p.n_keys;      // most groups there can be
+  const GaOut o{group_id, n_groups, seg_offsets, perm, adv, group_mean, group_std, best, static_cast<int32_t>(g_max), fill};
+
+  if (n_resp <= kRangeMaxResp && p.n_keys <= kRangeMaxKeys) {
+    // A workgroup per 256 responses, and enough that each has at most one key per thread.  Every workgroup scans all keys, so
+    // large calls take more threads.  Measured on the stream, launch gaps included, 256 / 1024 threads: 64 responses 11 / 12 us,
+    // 1024: 12 / 13, 4096: 25 / 14; 65536 responses with a workgroup per 128 / 256 / 512: 49 / 31 / 32 us.
+    const bool direct = n_resp <= kRangeDirect;
+    const int threads = n_resp <= 1024 ? 256 : 1024;
+    const int64_t by_resp = ceil_div(n_resp, 256), by_keys = ceil_div(p.n_keys, threads);
+    const int64_t blocks = by_resp > by_keys ? by_resp : by_keys;
+    const int own = static_cast<int>(ceil_div(p.n_keys, blocks));
+    const dim3 grid(static_cast<unsigned>(ceil_div(p.n_keys, own)));
+    uint16_t* keys16 = direct ? nullptr : reinterpret_cast<uint16_t*>(p.key_of_resp);
+    GaMix given = mix;
+    if (!direct) {
+      hipLaunchKernelGGL(k_ga_keys, dim3(static_cast<unsigned>(ceil_div(n_resp, 256) + 1)), dim3(256), 0, s, a, mix, keys16);
+      ATG_LAUNCH_CHECK();
+      if (r_team) a.reward = reward_out;
+      given = GaMix{nullptr, nullptr, 0.f, nullptr};
+    }
+    if (threads == 256)
+      hipLaunchKernelGGL(k_ga_range<256>, grid, dim3(256), 0, s, a, given, st, static_cast<int>(p.n_keys), own, keys16, p.err,
+                         p.arrival, o);
+    else
+      hipLaunchKernelGGL(k_ga_range<1024>, grid, dim3(1024), 0, s, a, given, st, static_cast<int>(p.n_keys), own, keys16, p.err,
+                         p.arrival, o);
+    ATG_LAUNCH_CHECK();
+    return AT_GRPO_OK;
+  }
+  if (plan_pool(n_resp, ws, &p) && workspace_bytes >= ws.bytes()) {
+    const unsigned blocks = static_cast<unsigned>(ceil_div(n_resp, kPoolBlock));
+    const float* rw = r_team ? reward_out : reward;
+    hipLaunchKernelGGL(k_gp_init, dim3(1), dim3(kPoolThreads), 0, s, p.pool.bin_cnt, p.pool.bins, p.err);
+    ATG_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_gp_count, dim3(blocks), dim3(kPoolThreads), 0, s, a, mix, p.pool, p.err);
+    ATG_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_gp_bases, dim3(1), dim3(kPoolThreads), 0, s, p.pool);
+    ATG_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_gp_partition, dim3(blocks), dim3(kPoolThreads), 0, s, n_resp, rw, p.pool);
+    ATG_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_gp_bin, dim3(p.pool.bins), dim3(kBinThreads), 0, s, p.pool, rw, st, p.n_keys, o);
+    ATG_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_gp_groups, dim3(1), dim3(kPoolThreads), 0, s, p.pool, o);
+    ATG_LAUNCH_CHECK();
+    const int resp_blocks = static_cast<int>(ceil_div(n_resp, 1024));
+    hipLaunchKernelGGL(k_gp_out, dim3(static_cast<unsigned>(resp_blocks + p.pool.bins + (fill ? 64 : 0))), dim3(256), 0, s,
+                       p.pool, n_resp, resp_blocks, o);
     ATG_LAUNCH_CHECK();
     return AT_GRPO_OK;
   }
@@ -701,10 +1102,8 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     hipLaunchKernelGGL(k_ga_mix, dim3(static_cast<unsigned>(ceil_div(n_resp, 256))), dim3(256), 0, s, n_resp,
                        r_team, r_loc, alpha, reward_out);
     ATG_LAUNCH_CHECK();
-    reward = reward_out;
+    a.reward = reward = reward_out;
   }
-  const GaArgs a{n_resp, n_env, n_agent, n_turn, env_id, agent_id, turn_id, reward, group_by, n_sample, sample_id};
-  const GaStat st{eps_std, ddof, norm};
   const unsigned rb = static_cast<unsigned>(ceil_div(n_resp, 256));
   const unsigned kb = static_cast<unsigned>(p.n_blocks);
 
@@ -713,34 +1112,22 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
   ATG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_ga_hist, dim3(rb), dim3(256), 0, s, a, p.err, p.hist, p.key_of_resp, p.rank_of_resp);
   ATG_LAUNCH_CHECK();
-  if (p.n_keys <= kScanSingleKeys) {
-    hipLaunchKernelGGL(k_ga_scan_single, dim3(1), dim3(kSingleThreads), 0, s, p.hist, static_cast<int>(p.n_keys),
-                       p.gid_of_key, n_groups, seg_offsets);
-    ATG_LAUNCH_CHECK();
-  } else {
-    hipLaunchKernelGGL(k_ga_scan_partial, dim3(kb), dim3(256), 0, s, p.hist, p.n_keys, p.bsum_p, p.bsum_c);
-    ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_ga_scan_top, dim3(1), dim3(256), 0, s, p.n_blocks, p.bsum_p, p.bsum_c, n_groups,
-                       seg_offsets);
-    ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_ga_scan_apply, dim3(kb), dim3(256), 0, s, p.hist, p.n_keys, p.bsum_p, p.bsum_c,
-                       p.gid_of_key, seg_offsets);
-    ATG_LAUNCH_CHECK();
-  }
+  hipLaunchKernelGGL(k_ga_scan_partial, dim3(kb), dim3(256), 0, s, p.hist, p.n_keys, p.bsum_p, p.bsum_c);
+  ATG_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_ga_scan_top, dim3(1), dim3(256), 0, s, p.n_blocks, p.bsum_p, p.bsum_c, n_groups, seg_offsets);
+  ATG_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_ga_scan_apply, dim3(kb), dim3(256), 0, s, p.hist, p.n_keys, p.bsum_p, p.bsum_c,
+                     p.gid_of_key, seg_offsets);
+  ATG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_ga_scatter, dim3(rb), dim3(256), 0, s, n_resp, p.key_of_resp, p.rank_of_resp,
                      p.gid_of_key, seg_offsets, group_id, p.arrival, adv);
   ATG_LAUNCH_CHECK();
   // at most min(R, keys) groups exist; both finishing roles stride over them
-  const int64_t g_max = n_resp < p.n_keys ? n_resp : p.n_keys;
-  const unsigned fs = static_cast<unsigned>(ceil_div(g_max, 256) > 4096 ? 4096 : ceil_div(g_max, 256));
-  const unsigned fl = static_cast<unsigned>(ceil_div(g_max, 4) > 4096 ? 4096 : ceil_div(g_max, 4));
-  hipLaunchKernelGGL(k_ga_finish, dim3(fs + fl), dim3(256), 0, s, static_cast<int>(fs), n_groups, seg_offsets,
-                     p.arrival, reward, st, perm, adv, group_mean, group_std);
+  const int fs = static_cast<int>(ceil_div(g_max, 256) > 4096 ? 4096 : ceil_div(g_max, 256));
+  const int fl = static_cast<int>(ceil_div(g_max, 4) > 4096 ? 4096 : ceil_div(g_max, 4));
+  hipLaunchKernelGGL(k_ga_finish, dim3(static_cast<unsigned>(fs + fl + (fill ? 64 : 0))), dim3(256), 0, s, fs, fl, n_resp,
+                     p.arrival, reward, st, o);
   ATG_LAUNCH_CHECK();
-  if (best) {
-    hipLaunchKernelGGL(k_ga_select, dim3(fs), dim3(256), 0, s, n_groups, seg_offsets, perm, reward, best);
-    ATG_LAUNCH_CHECK();
-  }
   return AT_GRPO_OK;
 }
 
@@ -845,7 +1232,7 @@ extern "C" int at_grpo_group_advantage_static(int32_t n_resp, int32_t n_env, int
                                               int32_t* data_error, void* hip_stream) {
   if (!reward) return AT_GRPO_EINVAL;
   if (n_resp <= 0 || n_env <= 0 || n_agent <= 0 || n_turn <= 0) return AT_GRPO_EINVAL;
-  const size_t need = group_advantage_workspace(n_resp, n_env, n_agent, n_turn);
+  const size_t need = group_advantage_least_workspace(n_resp, n_env, n_agent, n_turn);
   if (need == 0 || need > kStaticScratchBytes) return AT_GRPO_ESCRATCH;
   void* ws = nullptr;
   ATG_TRY(static_scratch(&ws));

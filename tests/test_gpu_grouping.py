@@ -1,0 +1,87 @@
+"""Grouping at the sizes where the launch plan changes: one launch (key ranges), pools (partition by key range), and the
+histogram pipeline for what neither takes.  Integers against the oracle in full; advantages and statistics on groups
+the oracle handles one by one, within 1e-4 (fp32 sums of a few members)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import at_grpo_oracle as orc
+from paper_2510_11062_amd import api
+from tests.gpu_case import host
+from tests.test_gpu_parity import say
+
+
+def draw(E, N, T, sizes, seed):
+    """sizes: members of every key, in key order."""
+    rng = np.random.default_rng(seed)
+    key = np.repeat(np.arange(E * N * T), sizes)[rng.permutation(int(np.sum(sizes)))]
+    reward = (rng.integers(0, 9, size=key.size) / np.float32(8)).astype(np.float32)
+    return (key // (N * T)).astype(np.int32), (key // T % N).astype(np.int32), (key % T).astype(np.int32), reward
+
+
+CASES = {
+    "range: most responses": (2048, 2, 4, lambda rng, n: np.full(n, 4)),
+    "range: most keys": (8191, 2, 4, lambda rng, n: np.ones(n, int)),
+    "range: more members than a list holds": (2, 1, 2, lambda rng, n: np.array([6000, 3, 4097, 700])),
+    "range: 4097 responses": (241, 1, 1, lambda rng, n: np.full(n, 17)),
+    "pool: fewest responses": (8193, 2, 2, lambda rng, n: np.full(n, 2)),
+    "pool: keys missing, sizes up to 24": (3000, 2, 12, lambda rng, n: rng.integers(0, 25, n) * (rng.random(n) < 0.4)),
+    "pool: one oversized bin": (5000, 2, 3, lambda rng, n: np.where(np.arange(n) == 777, 9000, 3)),
+    "histogram: few keys": (4, 1, 2, lambda rng, n: np.full(n, 8800)),
+    "histogram: few responses, many keys": (40000, 1, 2, lambda rng, n: (rng.random(n) < 0.2).astype(int)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mixed", [False, True], ids=["given", "mixed"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_grouping_paths(gpu_device, name, mixed):
+    E, N, T, sizes_of = CASES[name]
+    rng = np.random.default_rng(len(name))
+    env, agent, turn, reward = draw(E, N, T, sizes_of(rng, E * N * T), 11)
+    R = env.size
+    # some responses take no part: an id out of range, a reward that is not finite
+    env = env.copy()
+    env[R // 3] = E
+    bad = np.array([0, R // 2])
+    reward = reward.copy()
+    reward[bad] = [np.inf, np.nan]
+    kept = np.ones(R, bool)
+    kept[[R // 3, *bad]] = False
+    say(f"[grouping] {name} R={R} keys={E * N * T} mixed={mixed}")
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    ids = (dev(env), dev(agent), dev(turn))
+    if mixed:
+        loc = (np.arange(R) % 5 / np.float32(7)).astype(np.float32)
+        out = api.at_grpo_group_advantage_mixed(*ids, dev(reward), dev(loc), 0.3, E, N, T)
+        reward = orc.mix_rewards(reward, loc, 0.3)
+        assert np.array_equal(host(out["reward"])[kept].view(np.uint32), reward[kept].view(np.uint32))
+    else:
+        out = api.at_grpo_group_advantage(*ids, dev(reward), E, N, T)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 3          # AT_GRPO_DATA_ID_RANGE | AT_GRPO_DATA_REWARD
+    rows = np.nonzero(kept)[0]
+    gid, G, offs, perm = orc.group_segments(orc.group_key(env[kept], agent[kept], turn[kept], N, T))
+    gmax = min(R, E * N * T)
+    assert int(out["n_groups"].item()) == G
+    got = host(out["group_id"])
+    assert np.array_equal(got[kept], gid) and np.all(got[~kept] == -1)
+    seg = host(out["seg_offsets"])
+    assert seg.size == gmax + 1 and np.array_equal(seg[:G + 1], offs) and np.all(seg[G + 1:] == 0)
+    assert np.array_equal(host(out["perm"])[:rows.size], rows[perm]) and np.all(host(out["perm"])[rows.size:] == 0)
+    pick = np.sort(np.random.default_rng(1).choice(G, size=min(G, 300), replace=False))
+    members = np.concatenate([rows[perm[offs[g]:offs[g + 1]]] for g in pick])
+    sub = np.repeat(np.arange(pick.size), [offs[g + 1] - offs[g] for g in pick])
+    adv, mean, std = orc.group_advantage(reward[members], sub, pick.size)
+    a = host(out["adv"]).astype(np.float64)
+    assert np.all(a[~kept] == 0) and np.all(a[members][std[sub] == 0] == 0)
+    assert np.allclose(a[members], adv, rtol=1e-4, atol=1e-6)
+    assert np.allclose(host(out["group_mean"])[pick], mean, rtol=1e-4, atol=1e-7)
+    assert np.allclose(host(out["group_std"])[pick], std, rtol=1e-4, atol=1e-7)
+    assert np.all(host(out["group_mean"])[G:] == 0) and np.all(host(out["group_std"])[G:] == 0)
+    if mixed:
+        best = host(out["best"])
+        assert np.all(best[G:] == -1)
+        # ascending members: the first of the largest rewards
+        want = [rows[perm[offs[g]:offs[g + 1]]][np.argmax(reward[rows[perm[offs[g]:offs[g + 1]]]])] for g in pick]
+        assert np.array_equal(best[pick], want)
