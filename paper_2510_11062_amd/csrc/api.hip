@@ -239,10 +239,14 @@ int enqueue_logprob_lists(const at_grpo_batch* b, const Plan& p, const HeadGeom&
 
 int enqueue_logprob(const at_grpo_batch* b, const Plan& p, float* logp, float* lse, float* entropy,
                     hipStream_t s) {
-  ATG_TRY(launch_route(p.L, p.S, s));
-  ATG_TRY(launch_compact(p.L, p.S, true, s));
-  ATG_TRY(launch_zero_nonparticipating(p.L, p.S, logp, lse, s));
-  if (entropy) ATG_TRY(launch_zero_nonparticipating(p.L, p.S, entropy, nullptr, s));
+  if (prep_is_small(p.L)) {
+    ATG_TRY(launch_prep_logprob(p.L, p.S, logp, lse, entropy, s));
+  } else {
+    ATG_TRY(launch_route(p.L, p.S, s));
+    ATG_TRY(launch_compact(p.L, p.S, true, s));
+    ATG_TRY(launch_zero_nonparticipating(p.L, p.S, logp, lse, s));
+    if (entropy) ATG_TRY(launch_zero_nonparticipating(p.L, p.S, entropy, nullptr, s));
+  }
   return enqueue_logprob_lists(b, p, p.g, p.S, logp, lse, entropy, s);
 }
 
@@ -374,11 +378,16 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
   // participation and weights, then the coefficient; rows with g_t = 0 drop out of the lists
-  ATG_TRY(launch_route(p.L, p.S, s));
-  ATG_TRY(launch_compact(p.L, p.S, false, s));
-  if (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN) ATG_TRY(launch_resp_len(p.L, p.S, s));
-  ATG_TRY(launch_coef(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, grad_loss, p.coef, s));
-  ATG_TRY(launch_compact(p.L, p.S, true, s));
+  if (prep_is_small(p.L)) {
+    ATG_TRY(launch_prep_backward(p.L, p.S, logp, make_coef_args(p.S, old_logp, adv, eps_low, eps_high, agg, grad_loss),
+                                 p.coef, s));
+  } else {
+    ATG_TRY(launch_route(p.L, p.S, s));
+    ATG_TRY(launch_compact(p.L, p.S, false, s));
+    if (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN) ATG_TRY(launch_resp_len(p.L, p.S, s));
+    ATG_TRY(launch_coef(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, grad_loss, p.coef, s));
+    ATG_TRY(launch_compact(p.L, p.S, true, s));
+  }
   ATG_TRY(launch_fill_bytes16(d_hidden, p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize, s));
 
   for (int m = 0; m < batch->n_heads; ++m) {
@@ -426,18 +435,22 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
   ATG_TRY(check_workspace(workspace, workspace_bytes, ws.bytes()));
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
-  // participation; the weights of Eq. (2) count every participating row, whatever its advantage
-  ATG_TRY(launch_route(p.L, p.S, s));
-  ATG_TRY(launch_compact(p.L, p.S, false, s));
-  if (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN) ATG_TRY(launch_resp_len(p.L, p.S, s));
-  ATG_TRY(launch_zero_nonparticipating(p.L, p.S, logp, lse, s));
-  // rows of responses with a zero advantage carry no gradient: they only need their log-probability
-  ATG_TRY(launch_split_by_advantage(p.L, p.S, adv, p.SB.flag, p.SF.flag, s));
-  ATG_TRY(launch_compact(p.L, p.SF, true, s));
-  ATG_TRY(launch_compact(p.L, p.SB, true, s));
+  // participation; the weights of Eq. (2) count every participating row, whatever its advantage.
+  // Rows of responses with a zero advantage carry no gradient: they only need their log-probability.
+  if (prep_is_small(p.L)) {
+    ATG_TRY(launch_prep_step(p.L, p.S, p.SB, p.SF, adv, logp, lse, p.gates, p.n_gates, s));
+  } else {
+    ATG_TRY(launch_route(p.L, p.S, s));
+    ATG_TRY(launch_compact(p.L, p.S, false, s));
+    if (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN) ATG_TRY(launch_resp_len(p.L, p.S, s));
+    ATG_TRY(launch_zero_nonparticipating(p.L, p.S, logp, lse, s));
+    ATG_TRY(launch_split_by_advantage(p.L, p.S, adv, p.SB.flag, p.SF.flag, s));
+    ATG_TRY(launch_compact(p.L, p.SF, true, s));
+    ATG_TRY(launch_compact(p.L, p.SB, true, s));
+    ATG_TRY(launch_fill_i32(p.gates, p.n_gates, 0, s));
+  }
   ATG_TRY(enqueue_logprob_lists(batch, p, p.gF, p.SF, logp, lse, nullptr, s));
   ATG_TRY(launch_fill_bytes16(d_hidden, p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize, s));
-  ATG_TRY(launch_fill_i32(p.gates, p.n_gates, 0, s));
   const CoefArgs ca = make_coef_args(p.S, old_logp, adv, eps_low, eps_high, agg, grad_loss);
 
   int gate_no = 0;

@@ -486,11 +486,199 @@ __global__ __launch_bounds__(256) void k_zero_nonparticipating(int64_t n_tok,
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Small batches: everything between the layout and the head contractions in one launch of one workgroup.  The general path
+// takes 8 to 16 launches of 2 to 5 us for it (fills, routing, counts, scan, scatter, ...), which is most of a small call;
+// here the rows' heads stay in LDS from one phase to the next.  Bound by latency: 5 to 9 us for up to 2300 rows.  Step of C1
+// (fp32) 126 -> 72 us, log-probabilities of one response 388 -> 372, micro-batch of 2300 rows 3670 -> 3528.
+// ------------------------------------------------------------------------------------------------
+enum PrepMode {
+  PREP_LOGPROB,    // lists of the participating rows; logp / lse / entropy = 0 elsewhere
+  PREP_BACKWARD,   // weights and coefficients; lists of the rows whose coefficient is not zero
+  PREP_STEP        // weights; lists of the rows with and without an advantage; logp / lse = 0 elsewhere; gates cleared
+};
+
+constexpr int kPsThreads = 1024, kPsRows = 32768, kPsPer = 8, kPsTile = kPsThreads * kPsPer;
+constexpr int kPsBatch = 4;            // rows of a response that a lane requests before it uses the first
+constexpr int kPsNoAdv = 0x40;         // mark of a participating row: its head, with this bit where the advantage is zero
+static_assert(kMaxHeads <= kPsNoAdv, "head and flag share a byte");
+
+struct PrepArgs {
+  TokenLayout L;
+  TokenScratch S;
+  int lanes;                           // per response
+  float *logp, *lse, *entropy;         // zeroed where a row takes no part (LOGPROB, STEP); logp is read by BACKWARD
+  CoefArgs ca;                         // BACKWARD
+  float* coef;
+  const float* adv;                    // STEP
+  int32_t *cnt_b, *idx_b, *cnt_f, *idx_f;
+  int32_t* gates;
+  int n_gates;
+};
+
+template <int MODE>
+__global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
+  __shared__ __attribute__((aligned(16))) int8_t mark[kPsRows];
+  __shared__ int part[2][kPsThreads / 64];
+  __shared__ int rows_of_head[kMaxHeads], resps_of_head[kMaxHeads];
+  const TokenLayout& L = a.L;
+  const int tid = threadIdx.x, n = static_cast<int>(L.n_tok);
+
+  if (tid == 0) *a.S.err = 0;
+  if (tid < kMaxHeads) rows_of_head[tid] = resps_of_head[tid] = 0;
+  for (int i = tid * 16; i < n; i += kPsThreads * 16) *reinterpret_cast<int4*>(mark + i) = make_int4(-1, -1, -1, -1);
+  if (MODE != PREP_LOGPROB)
+    for (int t = tid; t < n; t += kPsThreads) a.S.resp_of_tok[t] = -1;
+  if (MODE == PREP_STEP)
+    for (int i = tid; i < a.n_gates; i += kPsThreads) a.gates[i] = 0;
+  __syncthreads();
+
+  // rows of every response: a.lanes lanes each
+  const int lanes = a.lanes, lane = tid & (lanes - 1);
+  for (int r = tid / lanes; r < L.n_resp; r += kPsThreads / lanes) {
+    const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
+    if (lo < 0 || hi < lo || hi > L.n_tok) {
+      if (lane == 0) {
+        atomicOr(a.S.err, AT_GRPO_DATA_SEQLENS);
+        a.S.resp_len[r] = 0;
+      }
+      continue;
+    }
+    const int head = head_of_response(r, L.n_heads, L.n_agent, L.resp_agent, L.head_of_agent, a.S.err);
+    int mine = head;
+    if (MODE == PREP_STEP && head >= 0 && a.adv[r] == 0.f) mine |= kPsNoAdv;   // NaN counts as non-zero and propagates
+    int c = 0;
+    const int end = static_cast<int>(hi);
+    for (int t0 = static_cast<int>(lo) + lane; t0 < end; t0 += lanes * kPsBatch) {
+      int y[kPsBatch], m[kPsBatch];
+#pragma unroll
+      for (int b = 0; b < kPsBatch; ++b) {
+        const int t = t0 + b * lanes;
+        y[b] = 0;
+        m[b] = 1;
+        if (t < end) {
+          if (L.token_id) y[b] = L.token_id[t];
+          if (L.mask) m[b] = L.mask[t];
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < kPsBatch; ++b) {
+        const int t = t0 + b * lanes;
+        if (t >= end) break;
+        bool on = head >= 0 && m[b] != 0;
+        if (on && (y[b] < 0 || y[b] >= L.V)) {
+          atomicOr(a.S.err, AT_GRPO_DATA_TOKEN_RANGE);
+          on = false;
+        }
+        if (MODE != PREP_LOGPROB) a.S.resp_of_tok[t] = r;
+        mark[t] = static_cast<int8_t>(on ? mine : -1);
+        c += on;
+      }
+    }
+    for (int o = lanes >> 1; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    if (MODE != PREP_LOGPROB && lane == 0) {
+      a.S.resp_len[r] = c;
+      if (c > 0) {
+        atomicAdd(&rows_of_head[head], c);
+        atomicAdd(&resps_of_head[head], 1);
+      }
+    }
+  }
+  __syncthreads();
+
+  if (MODE != PREP_LOGPROB && tid < kMaxHeads) {
+    a.S.cnt[tid] = rows_of_head[tid];
+    a.S.resp_cnt[tid] = resps_of_head[tid];
+  }
+  if (MODE == PREP_BACKWARD) {
+    __syncthreads();
+#pragma unroll 4
+    for (int t = tid; t < n; t += kPsThreads) {
+      const int f = mark[t];
+      float g = 0.f;
+      if (f >= 0) {
+        g = coef_value(a.ca, f, t, a.logp[t]);
+        if (g == 0.f) {
+          g = 0.f;          // also folds -0
+          mark[t] = -1;
+        }
+      }
+      a.coef[t] = g;
+    }
+    __syncthreads();
+  } else {
+    for (int t = tid; t < n; t += kPsThreads) {
+      if (mark[t] < 0) {
+        a.logp[t] = 0.f;
+        if (a.lse) a.lse[t] = 0.f;
+        if (a.entropy) a.entropy[t] = 0.f;
+      }
+    }
+  }
+
+  // lists, ascending: eight consecutive rows per thread; the counts of both lists travel in one word (at most 8192 each)
+  const int wlane = tid & 63, wave = tid >> 6;
+  int buf = 0;
+  for (int m = 0; m < kMaxHeads; ++m) {
+    int run_b = 0, run_f = 0;
+    if (m < L.n_heads) {
+      int32_t* out_b = a.idx_b + static_cast<size_t>(m) * n;
+      int32_t* out_f = MODE == PREP_STEP ? a.idx_f + static_cast<size_t>(m) * n : nullptr;
+      for (int base = 0; base < n; base += kPsTile) {
+        const int t0 = base + tid * kPsPer;
+        uint2 w = make_uint2(0xffffffffu, 0xffffffffu);
+        if (t0 < n) w = *reinterpret_cast<const uint2*>(mark + t0);
+        int8_t f[kPsPer];
+        int v = 0;
+#pragma unroll
+        for (int e = 0; e < kPsPer; ++e) {
+          f[e] = t0 + e < n ? static_cast<int8_t>((e < 4 ? w.x : w.y) >> (8 * (e & 3))) : int8_t{-1};
+          v += f[e] == m ? 1 : (f[e] == (m | kPsNoAdv) ? 0x10000 : 0);
+        }
+        int incl = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int up = __shfl_up(incl, o, 64);
+          if (wlane >= o) incl += up;
+        }
+        if (wlane == 63) part[buf][wave] = incl;
+        __syncthreads();          // the other buffer's readers passed the barrier in front of this one's
+        int before = incl - v, total = 0;
+#pragma unroll
+        for (int k = 0; k < kPsThreads / 64; ++k) {
+          const int x = part[buf][k];
+          before += k < wave ? x : 0;
+          total += x;
+        }
+        buf ^= 1;
+        int pos_b = run_b + (before & 0xffff), pos_f = run_f + (before >> 16);
+#pragma unroll
+        for (int e = 0; e < kPsPer; ++e) {
+          if (f[e] == m) out_b[pos_b++] = t0 + e;
+          else if (MODE == PREP_STEP && f[e] == (m | kPsNoAdv)) out_f[pos_f++] = t0 + e;
+        }
+        run_b += total & 0xffff;
+        run_f += total >> 16;
+      }
+    }
+    if (tid == 0) {
+      a.cnt_b[m] = run_b;
+      if (MODE == PREP_STEP) a.cnt_f[m] = run_f;
+    }
+  }
+}
+
 unsigned grid_for(int64_t n, int per_block, int64_t cap = 1 << 20) {
   int64_t g = ceil_div(n, per_block);
   if (g < 1) g = 1;
   if (g > cap) g = cap;
   return static_cast<unsigned>(g);
+}
+
+// lanes of the one-workgroup preparation that share a response: a batch of four rows per lane covers the mean
+int team_lanes_small(const TokenLayout& L) {
+  const int64_t mean_rows = L.n_tok / (L.n_resp > 0 ? L.n_resp : 1);
+  return mean_rows > 128 ? 64 : mean_rows > 64 ? 32 : 16;
 }
 
 // lanes that share a response in the row kernels: by the mean number of rows
@@ -642,6 +830,63 @@ int launch_zero_nonparticipating(const TokenLayout& L, const TokenScratch& S, fl
   ProfScope ps(PROF_PREP, s);
   hipLaunchKernelGGL(k_zero_nonparticipating, dim3(static_cast<unsigned>(S.n_blk256)), dim3(256), 0, s,
                      L.n_tok, S.flag, logp, lse);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+// One workgroup walks the responses kPsThreads / lanes at a time, about 1 us each time, where the general path takes that
+// many launches; beyond 16 times the two meet.
+bool prep_is_small(const TokenLayout& L) {
+  return L.n_tok <= kPsRows && static_cast<int64_t>(L.n_resp) * team_lanes_small(L) <= 16 * kPsThreads;
+}
+
+static PrepArgs prep_args(const TokenLayout& L, const TokenScratch& S) {
+  PrepArgs a{};
+  a.L = L;
+  a.S = S;
+  a.lanes = team_lanes_small(L);
+  a.cnt_b = S.cnt;
+  a.idx_b = S.idx;
+  return a;
+}
+
+int launch_prep_logprob(const TokenLayout& L, const TokenScratch& S, float* logp, float* lse, float* entropy, hipStream_t s) {
+  ProfScope ps(PROF_PREP, s);
+  PrepArgs a = prep_args(L, S);
+  a.logp = logp;
+  a.lse = lse;
+  a.entropy = entropy;
+  hipLaunchKernelGGL(k_prep_small<PREP_LOGPROB>, dim3(1), dim3(kPsThreads), 0, s, a);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_prep_backward(const TokenLayout& L, const TokenScratch& S, const float* logp, const CoefArgs& ca, float* coef,
+                         hipStream_t s) {
+  ProfScope ps(PROF_PREP, s);
+  PrepArgs a = prep_args(L, S);
+  a.logp = const_cast<float*>(logp);   // only read in this mode
+  a.ca = ca;
+  a.coef = coef;
+  hipLaunchKernelGGL(k_prep_small<PREP_BACKWARD>, dim3(1), dim3(kPsThreads), 0, s, a);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_prep_step(const TokenLayout& L, const TokenScratch& S, const TokenScratch& SB, const TokenScratch& SF,
+                     const float* adv, float* logp, float* lse, int32_t* gates, int n_gates, hipStream_t s) {
+  ProfScope ps(PROF_PREP, s);
+  PrepArgs a = prep_args(L, S);
+  a.logp = logp;
+  a.lse = lse;
+  a.adv = adv;
+  a.cnt_b = SB.cnt;
+  a.idx_b = SB.idx;
+  a.cnt_f = SF.cnt;
+  a.idx_f = SF.idx;
+  a.gates = gates;
+  a.n_gates = n_gates;
+  hipLaunchKernelGGL(k_prep_small<PREP_STEP>, dim3(1), dim3(kPsThreads), 0, s, a);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

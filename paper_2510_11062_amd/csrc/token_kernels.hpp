@@ -138,4 +138,17 @@ int launch_split_by_advantage(const TokenLayout& L, const TokenScratch& S, const
 int launch_zero_nonparticipating(const TokenLayout& L, const TokenScratch& S, float* logp, float* lse,
                                  hipStream_t s);
 
+// The same preparation in one launch, for batches small enough (prep_is_small): replaces launch_route, launch_compact and
+// what stands between and behind them.
+bool prep_is_small(const TokenLayout& L);
+// cnt and idx of S; logp, lse, entropy (the last two may be null) = 0 on rows that take no part
+int launch_prep_logprob(const TokenLayout& L, const TokenScratch& S, float* logp, float* lse, float* entropy, hipStream_t s);
+// resp_of_tok, resp_len, resp_cnt of S; coef; cnt and idx of the rows whose coefficient is not zero
+int launch_prep_backward(const TokenLayout& L, const TokenScratch& S, const float* logp, const CoefArgs& ca, float* coef,
+                         hipStream_t s);
+// resp_of_tok, resp_len, cnt, resp_cnt of S; cnt and idx of SB (advantage not zero) and SF (zero); logp = lse = 0 on rows
+// that take no part; gates = 0
+int launch_prep_step(const TokenLayout& L, const TokenScratch& S, const TokenScratch& SB, const TokenScratch& SF,
+                     const float* adv, float* logp, float* lse, int32_t* gates, int n_gates, hipStream_t s);
+
 }  // namespace atg
