@@ -161,9 +161,10 @@ __global__ __launch_bounds__(256) void k_resp_cnt(TokenLayout L, const int32_t* 
 // 4-row vectors.  each(logp, old_logp) is called for every participating row, in ascending order within a lane, and returns
 // the row's clip flags, which are stored when clip_mask is given.
 //
-// kRowBatch vectors per lane are requested before the first is used (C5's 6144 responses of up to 4096 rows: 21.5 -> 19.9 us;
-// diagnostics, one row per lane and load before, 21.5 -> 20.5).
-constexpr int kRowBatch = 4;
+// kRowBatch vectors per lane are requested before the first is used.  Two: four take 95 to 106 registers, so that fewer
+// wavefronts are resident than C5 has responses (both calls together 41.9 us with four, 39.2 with two; 65536 responses of 8
+// to 32 rows 63.8 and 59.8).
+constexpr int kRowBatch = 2;
 
 // vectors of rows of tensors that need not start on a vector's boundary
 typedef float f32x4_rows __attribute__((ext_vector_type(4), aligned(4)));
@@ -681,10 +682,12 @@ int team_lanes_small(const TokenLayout& L) {
   return mean_rows > 128 ? 64 : mean_rows > 64 ? 32 : 16;
 }
 
-// lanes that share a response in the row kernels: by the mean number of rows
+// Lanes that share a response in the row kernels, by the mean number of rows.  The call ends with its longest response, which
+// may be many times the mean: C5 (mean 289 rows, up to 4096) takes 53.2 us for both calls with 32 lanes, 41.9 with 64.  With
+// uniform lengths (64 .. 512, 100 .. 200, 400 .. 900) neither choice shows beside the launches.
 int team_lanes(const TokenLayout& L) {
   const int64_t mean_rows = L.n_tok / (L.n_resp > 0 ? L.n_resp : 1);
-  return mean_rows >= 512 ? 64 : mean_rows >= 160 ? 32 : 16;
+  return mean_rows >= 160 ? 64 : mean_rows >= 60 ? 32 : 16;
 }
 
 }  // namespace
