@@ -283,7 +283,9 @@ __device__ __forceinline__ void finish_by_wave(int n, int lane, Id id_of, X x_of
     for (int i = 0; i < n; ++i) rank += (id_of(i) < rj);
     perm[rank] = rj;
   }
-  __threadfence();   // the ranks below are read back by other lanes of this wavefront
+  // the ranks are read back by other lanes of this wavefront: a fence of the workgroup is enough, and a device-wide one writes
+  // back the L2 for every group (2^20 responses in groups of 24: 797 us in rollout order and 914 shuffled, now 123 and 153)
+  __threadfence_block();
   const float x0 = reward(perm[0]);
   float sum = 0.f, xt = -INFINITY;
   int same = 1, top = 0x7fffffff;
@@ -635,6 +637,19 @@ struct PoolPlan {
   int32_t* gid_base;         // [bins + 1]
 };
 
+// atomicAdd(&counter[bin], 1) of every active lane.  In rollout order all lanes of a wavefront name the same bin, and 64 atomics
+// on one LDS word take turns: the lanes that agree with the first one share a single addition
+// (300000 responses over 37500 keys in rollout order 65 -> 55 us, shuffled 74 -> 72).
+__device__ __forceinline__ int count_in_bin(int* counter, int bin) {
+  const int first = __builtin_amdgcn_readfirstlane(bin);
+  const uint64_t same = __builtin_amdgcn_ballot_w64(bin == first);
+  if (bin != first) return atomicAdd(&counter[bin], 1);
+  const int lane = threadIdx.x & 63;
+  int at = 0;
+  if ((same & ((uint64_t{1} << lane) - 1)) == 0) at = atomicAdd(&counter[first], static_cast<int>(__popcll(same)));
+  return __builtin_amdgcn_readfirstlane(at) + static_cast<int>(__popcll(same & ((uint64_t{1} << lane) - 1)));
+}
+
 __global__ __launch_bounds__(kPoolThreads) void k_gp_init(int32_t* __restrict__ bin_cnt, int bins, int32_t* __restrict__ err) {
   for (int i = threadIdx.x; i < bins; i += kPoolThreads) bin_cnt[i] = 0;
   if (threadIdx.x == 0) *err = 0;
@@ -659,7 +674,7 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_count(GaArgs a, GaMix mix, 
       else if (!finite_reward(x)) bad |= AT_GRPO_DATA_REWARD;
       else key = static_cast<int>(k64);
       p.key[r] = key;
-      if (key >= 0) atomicAdd(&hist[static_cast<unsigned>(key) / static_cast<unsigned>(p.width)], 1);
+      if (key >= 0) count_in_bin(hist, static_cast<int>(static_cast<unsigned>(key) / static_cast<unsigned>(p.width)));
     }
   }
   if (bad) atomicOr(err, bad);
@@ -713,7 +728,7 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const
     if (r < n_resp) {
       const int key = p.key[r];
       if (key >= 0) {
-        const int at = atomicAdd(&next[static_cast<unsigned>(key) / static_cast<unsigned>(p.width)], 1);
+        const int at = count_in_bin(next, static_cast<int>(static_cast<unsigned>(key) / static_cast<unsigned>(p.width)));
         p.kr[at] = make_int2(key, static_cast<int>(r));
         p.x[at] = reward[r];
         p.slot[r] = at;
@@ -899,16 +914,28 @@ __global__ __launch_bounds__(256) void k_ga_finish(int n_small, int n_large, int
       put_stats(o, g, mean, sd, best);
     }
   } else if (b < n_small + n_large) {
-    const int lane = threadIdx.x & 63;
-    for (int g = ((b - n_small) * 256 + threadIdx.x) >> 6; g < G; g += (n_large * 256) >> 6) {
-      const int off = o.seg_offsets[g], n = o.seg_offsets[g + 1] - off;
-      if (n <= kSmallGroup) continue;
-      float mean, sd;
-      int best;
-      finish_by_wave(
-          n, lane, [&](int j) { return arrival[off + j]; }, [&](int j) { return reward[arrival[off + j]]; },
-          [&](int r) { return reward[r]; }, o.perm + off, put_adv, st, &mean, &sd, &best);
-      if (lane == 0) put_stats(o, g, mean, sd, best);
+    // a wavefront looks at the sizes of up to 64 consecutive groups at once: one group at a time, a million groups of one
+    // member took 16384 wavefronts 64 dependent pairs of loads each
+    // (129 us in rollout order and 206 shuffled, now 52 and 130)
+    const int lane = threadIdx.x & 63, wave = ((b - n_small) * 256 + static_cast<int>(threadIdx.x)) >> 6;
+    const int n_waves = (n_large * 256) >> 6;
+    const int per = min(64, (G + n_waves - 1) / n_waves);
+    for (int64_t g0 = static_cast<int64_t>(wave) * per; g0 < G; g0 += static_cast<int64_t>(n_waves) * per) {
+      int from = 0, members = 0;
+      if (lane < per && g0 + lane < G) {
+        from = o.seg_offsets[g0 + lane];
+        members = o.seg_offsets[g0 + lane + 1] - from;
+      }
+      for (uint64_t large = __builtin_amdgcn_ballot_w64(members > kSmallGroup); large != 0; large &= large - 1) {
+        const int j = __builtin_ctzll(large);
+        const int off = __shfl(from, j, 64), n = __shfl(members, j, 64);
+        float mean, sd;
+        int best;
+        finish_by_wave(
+            n, lane, [&](int m) { return arrival[off + m]; }, [&](int m) { return reward[arrival[off + m]]; },
+            [&](int r) { return reward[r]; }, o.perm + off, put_adv, st, &mean, &sd, &best);
+        if (lane == 0) put_stats(o, static_cast<int>(g0) + j, mean, sd, best);
+      }
     }
   } else {
     fill_tails(o, G, o.seg_offsets[G], n_resp, static_cast<int64_t>(b - n_small - n_large) * 256 + threadIdx.x,
