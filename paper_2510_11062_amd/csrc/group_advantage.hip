@@ -612,7 +612,8 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
 // (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of about 3072
 // responses) with LDS counters, so that every run written is a few entries long; each bin is finished by one workgroup in
 // LDS; and one last pass in response order gathers the results, again in runs.  About 84 bytes per response, all streamed.
-// 2^22 shuffled responses over 2^19 keys: 270 us on the stream (partition 101, results 73, bins 56, counts 22).
+// 2^22 shuffled responses over 2^19 keys: 257 us for the whole call (272 with one response at a time in the partition and in the
+// gathering of the results).
 // ------------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 1024, kPoolPer = 16, kPoolBlock = kPoolThreads * kPoolPer;   // responses per partitioning block
 constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolPerBin = 3072;
@@ -722,17 +723,23 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const
   }
   __syncthreads();
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolBlock + threadIdx.x;
-#pragma unroll 4
-  for (int u = 0; u < kPoolPer; ++u) {
-    const int64_t r = r0 + u * kPoolThreads;
-    if (r < n_resp) {
-      const int key = p.key[r];
-      if (key >= 0) {
-        const int at = count_in_bin(next, static_cast<int>(static_cast<unsigned>(key) / static_cast<unsigned>(p.width)));
-        p.kr[at] = make_int2(key, static_cast<int>(r));
-        p.x[at] = reward[r];
-        p.slot[r] = at;
-      }
+  for (int u0 = 0; u0 < kPoolPer; u0 += 4) {
+    int key[4];
+    float x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = r0 + (u0 + u) * kPoolThreads;
+      key[u] = r < n_resp ? p.key[r] : -1;
+      x[u] = r < n_resp ? reward[r] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (key[u] < 0) continue;
+      const int r = static_cast<int>(r0 + (u0 + u) * kPoolThreads);
+      const int at = count_in_bin(next, static_cast<int>(static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)));
+      p.kr[at] = make_int2(key[u], r);
+      p.x[at] = x[u];
+      p.slot[r] = at;
     }
   }
 }
@@ -864,19 +871,29 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_groups(PoolPlan p, GaOut o)
 // results in response order; the blocks behind `resp_blocks` write the groups of a bin each, the last ones fill the tails
 __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp_blocks, GaOut o) {
   if (static_cast<int>(blockIdx.x) < resp_blocks) {
+    // the loads of a thread's four responses go out together
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x;
+    int key[4], at[4];
+    float2 res[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int64_t r = (static_cast<int64_t>(blockIdx.x) * 4 + u) * 256 + threadIdx.x;
+      const int64_t r = r0 + u * 256;
+      key[u] = r < n_resp ? p.key[r] : -1;
+      at[u] = r < n_resp ? p.slot[r] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) res[u] = key[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f);   // no slot without a key
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = r0 + u * 256;
       if (r >= n_resp) break;
-      const int key = p.key[r];
-      if (key < 0) {
+      if (key[u] < 0) {
         o.group_id[r] = -1;
         o.adv[r] = 0.f;
       } else {
-        const float2 res = p.result[p.slot[r]];
-        const int lg = __float_as_int(res.y);
-        o.group_id[r] = p.gid_base[static_cast<unsigned>(key) / static_cast<unsigned>(p.width)] + (lg & 0x7fffffff);
-        if (lg >= 0) o.adv[r] = res.x;
+        const int lg = __float_as_int(res[u].y);
+        o.group_id[r] = p.gid_base[static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)] + (lg & 0x7fffffff);
+        if (lg >= 0) o.adv[r] = res[u].x;
       }
     }
     return;
