@@ -177,7 +177,8 @@ size_t at_grpo_group_advantage_keyed_workspace_bytes(int32_t group_by, int32_t n
  *   best[G]     optional (NULL to skip): response index of the candidate with the largest reward of
  *               each group, the lowest response index among equal rewards; the buffer must hold
  *               min(R, n_env*n_agent*n_turn) entries
- * r_team[R], r_loc[R] are inputs; alpha must be finite.  Every other argument, the workspace size
+ * r_team[R], r_loc[R] are inputs; reward may be one of them itself (mixed in place), in whole; alpha must be
+ * finite.  Every other argument, the workspace size
  * (AT_GRPO_CALL_GROUP_ADVANTAGE) and the error behaviour are those of at_grpo_group_advantage; a
  * non-finite mixed reward raises AT_GRPO_DATA_REWARD.
  */

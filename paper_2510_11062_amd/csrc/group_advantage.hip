@@ -369,9 +369,8 @@ __device__ __forceinline__ void fill_tails(const GaOut& o, int G, int n_listed, 
 // Eq. (3): r = alpha * r_team + r_loc.  One fp32 multiplication, then one fp32 addition (never
 // contracted to an fma): the result decides which groups count as all-equal and which candidate
 // is the arg max, so its rounding is part of the definition.
-__global__ __launch_bounds__(256) void k_ga_mix(int n, const float* __restrict__ r_team,
-                                                const float* __restrict__ r_loc, float alpha,
-                                                float* __restrict__ reward) {
+// reward may be r_team or r_loc itself.
+__global__ __launch_bounds__(256) void k_ga_mix(int n, const float* r_team, const float* r_loc, float alpha, float* reward) {
 #pragma clang fp contract(off)
   const int r = blockIdx.x * 256 + threadIdx.x;
   if (r < n) {
@@ -442,7 +441,8 @@ __device__ __forceinline__ int key16(const GaArgs& a, const GaMix& mix, int r, f
   return !ok ? kKeyBadId : (!finite_reward(*x) ? kKeyBadReward : static_cast<int>(key));
 }
 
-// the keys of all responses, padded to a multiple of 8; the mixed rewards
+// the keys of all responses, padded to a multiple of 8 (the array holds 256 bytes at the least); the mixed rewards, which may
+// take the place of what they are mixed from
 __global__ __launch_bounds__(256) void k_ga_keys(GaArgs a, GaMix mix, uint16_t* __restrict__ keys) {
   const int r = blockIdx.x * 256 + threadIdx.x;
   if (r >= (a.n_resp + 7) / 8 * 8) return;
@@ -1058,6 +1058,12 @@ using namespace atg;
 
 namespace {
 
+// do n elements at a and m elements at b (4 bytes each) have memory in common?
+bool overlap(const void* a, int64_t n, const void* b, int64_t m) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + static_cast<uintptr_t>(m) * 4 && y < x + static_cast<uintptr_t>(n) * 4;
+}
+
 int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t n_turn,
                         const int32_t* env_id, const int32_t* agent_id, const int32_t* turn_id,
                         const float* reward, float eps_std, int32_t ddof, int32_t norm, int32_t* group_id,
@@ -1097,7 +1103,21 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     // A workgroup per 256 responses, and enough that each has at most one key per thread.  Every workgroup scans all keys, so
     // large calls take more threads.  Measured on the stream, launch gaps included, 256 / 1024 threads: 64 responses 11 / 12 us,
     // 1024: 12 / 13, 4096: 25 / 14; 65536 responses with a workgroup per 128 / 256 / 512: 49 / 31 / 32 us.
-    const bool direct = n_resp <= kRangeDirect;
+    // Where an output lies on an input (rewards mixed in place), one workgroup's results could reach another that still has
+    // inputs to read: the keys then go through a launch of their own, behind which a reward is only read for its own group.
+    bool in_place = false;
+    for (const void* in : {static_cast<const void*>(env_id), static_cast<const void*>(agent_id), static_cast<const void*>(turn_id),
+                           static_cast<const void*>(sample_id), static_cast<const void*>(reward),
+                           static_cast<const void*>(r_team), static_cast<const void*>(r_loc)}) {
+      for (const void* out : {static_cast<const void*>(mix.reward_out), static_cast<const void*>(group_id),
+                              static_cast<const void*>(perm), static_cast<const void*>(adv)})
+        in_place = in_place || overlap(in, n_resp, out, n_resp);
+      for (const void* out : {static_cast<const void*>(group_mean), static_cast<const void*>(group_std),
+                              static_cast<const void*>(best), static_cast<const void*>(seg_offsets)})
+        in_place = in_place || overlap(in, n_resp, out, g_max + 1);
+      in_place = in_place || overlap(in, n_resp, n_groups, 1);
+    }
+    const bool direct = n_resp <= kRangeDirect && !in_place;
     const int threads = n_resp <= 1024 ? 256 : 1024;
     const int64_t by_resp = ceil_div(n_resp, 256), by_keys = ceil_div(p.n_keys, threads);
     const int64_t blocks = by_resp > by_keys ? by_resp : by_keys;

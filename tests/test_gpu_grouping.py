@@ -85,3 +85,43 @@ def test_grouping_paths(gpu_device, name, mixed):
         # ascending members: the first of the largest rewards
         want = [rows[perm[offs[g]:offs[g + 1]]][np.argmax(reward[rows[perm[offs[g]:offs[g + 1]]]])] for g in pick]
         assert np.array_equal(best[pick], want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("over", ["team", "loc", "given"])
+@pytest.mark.parametrize("shape", [(4, 2, 2, 4), (16, 2, 4, 8), (20, 3, 5, 10), (512, 2, 1, 4), (257, 2, 1, 8), (4096, 2, 2, 4),
+                                   (1, 1, 2, 40000)], ids=str)
+def test_results_in_place(gpu_device, shape, over):
+    """Mixed rewards over one of their parts, and advantages over the rewards they come from: bit for bit what separate
+    arrays give, on every launch plan."""
+    E, N, T, K = shape
+    env, agent, turn, team = draw(E, N, T, np.full(E * N * T, K), 7)
+    R, G = env.size, E * N * T
+    say(f"[grouping] in place over {over} {shape}")
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    ids = (dev(env), dev(agent), dev(turn))
+    loc = (np.arange(R) % 5 / np.float32(7)).astype(np.float32)
+    lib = api.load_library()
+    if over == "given":
+        ref = api.at_grpo_group_advantage(*ids, dev(team), E, N, T)
+    else:
+        ref = api.at_grpo_group_advantage_mixed(*ids, dev(team), dev(loc), 0.3, E, N, T)
+    ws = ref["workspace"]
+    got = api.group_advantage_outputs(R, G, gpu_device)
+    best = torch.full((G,), -1, dtype=torch.int32, device=gpu_device)
+    r_team, r_loc = dev(team), dev(loc)
+    tail = lambda adv: [got["group_id"].data_ptr(), got["n_groups"].data_ptr(), got["seg_offsets"].data_ptr(),
+                        got["perm"].data_ptr(), adv.data_ptr(), got["group_mean"].data_ptr(), got["group_std"].data_ptr()]
+    head = [R, E, N, T, *(t.data_ptr() for t in ids)]
+    scratch = [ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream]
+    if over == "given":
+        assert lib.at_grpo_group_advantage(*head, r_team.data_ptr(), 1e-6, 0, 0, *tail(r_team), *scratch) == 0
+        got["adv"] = r_team
+    else:
+        reward = r_team if over == "team" else r_loc
+        assert lib.at_grpo_group_advantage_mixed(*head, r_team.data_ptr(), r_loc.data_ptr(), 0.3, 1e-6, 0, 0, reward.data_ptr(),
+                                                 *tail(got["adv"]), best.data_ptr(), *scratch) == 0
+        got["reward"], got["best"] = reward, best
+    torch.cuda.synchronize()
+    for k in set(got) & set(ref) - {"workspace", "data_error"}:
+        assert np.array_equal(host(got[k]).view(np.uint32), host(ref[k]).view(np.uint32)), k
