@@ -14,7 +14,9 @@ from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
 import torch
-from torch._C import _cuda_getCurrentRawStream as _raw_stream     # current stream of a device, as an integer
+
+# current stream of a device, as an integer (a torch without a GPU backend lacks it; there every call is refused before this)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libat_grpo.so")
 _lib = None

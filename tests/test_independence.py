@@ -1,6 +1,8 @@
 """Structure checks: the oracle and the product path share no code, the binding has no fallback."""
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -50,3 +52,18 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
     monkeypatch.setattr(api, "_lib", None, raising=False)
     with pytest.raises(api.AtGrpoError):
         api.load_library()
+
+
+def test_package_imports_on_a_torch_without_a_gpu_backend():
+    """Such a torch lacks the stream query; the package imports all the same, and calls fail with the binding's own error."""
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2510_11062_amd import api\n"
+            "ids = torch.zeros(4, dtype=torch.int32)\n"
+            "try:\n"
+            "    api.at_grpo_group_advantage(ids, ids, ids, torch.zeros(4), 1, 1, 1)\n"
+            "except api.AtGrpoError as e:\n"
+            "    assert 'CUDA/HIP' in str(e), e\n"
+            "    print('refused')\n")
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0 and out.stdout.strip() == "refused", out.stderr
