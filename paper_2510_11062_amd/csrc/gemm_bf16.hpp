@@ -82,6 +82,10 @@ __device__ __forceinline__ void direct_load_v(const char* p, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(p), "s"(lds) : "memory");
 }
 
+// from base + off: with 32-bit offsets the base stays scalar; operands whose panel spans 4 GiB or more take 64-bit ones
+__device__ __forceinline__ void direct_load(const char* base, uint32_t off, uint32_t lds) { direct_load_s(base, off, lds); }
+__device__ __forceinline__ void direct_load(const char* base, uint64_t off, uint32_t lds) { direct_load_v(base + off, lds); }
+
 #define ATG_PIN16() __builtin_amdgcn_sched_barrier(0)
 
 // LDS-only workgroup barrier: waits for this wavefront's LDS operations, not for its outstanding global stores
@@ -102,12 +106,14 @@ __device__ __forceinline__ void wait_loads_but() {
 // (c & 16) | ((c ^ 2 s) & 15), s = (k & 3) | ((k >> 3) & 1) << 2.  Both make the fragment reads free of bank
 // conflicts.  The swizzle is applied on the global side of the direct loads, whose LDS side is lane * 16.
 
-// rows contiguous along k, all within 4 GiB of `base`
-template <typename G>
+// Off: uint32_t where 256 rows of the operand (64 k-rows of a k-major one) lie within 4 GiB, else uint64_t (see wide_rows)
+
+// rows contiguous along k
+template <typename G, typename Off = uint32_t>
 struct RowPanel {
   static constexpr bool kKMajor = false;
   const char* base;
-  uint32_t off[G::kLoads];
+  Off off[G::kLoads];
   // row_off(row): byte offset of tile row `row` (0..255) from b
   template <typename F>
   __device__ __forceinline__ void init(const char* b, int wave, int lane, F row_off) {
@@ -118,7 +124,7 @@ struct RowPanel {
       off[q] = row_off(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
   }
-  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_s(base, off[q], lds); }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load(base, off[q], lds); }
   __device__ __forceinline__ void advance() { base += kStepK * 2; }
 };
 
@@ -144,14 +150,13 @@ struct GatherPanel {
 };
 
 // k-major: k-row k at base + k * ld, 512 bytes of columns per row
-template <typename G>
+template <typename G, typename Off = uint32_t>
 struct KMajorPanel {
   static constexpr bool kKMajor = true;
   const char* base;
-  uint32_t off[G::kLoads];
+  Off off[G::kLoads];
   size_t step;
-  // cmax: last 16-byte chunk (0..31) that may be read (chunks past it are fetched from it; the caller masks them);
-  // 64 * ld < 4 GiB
+  // cmax: last 16-byte chunk (0..31) that may be read (chunks past it are fetched from it; the caller masks them)
   __device__ __forceinline__ void init(const char* b, int wave, int lane, size_t ld, int cmax) {
     base = uniform_ptr(b);
     step = ld * kStepK;
@@ -160,20 +165,20 @@ struct KMajorPanel {
       const int k = (wave * G::kLoads + q) * 2 + (lane >> 5);
       const int P = lane & 31, s = (k & 3) | (((k >> 3) & 1) << 2);
       const int C = (P & 16) | ((P ^ (2 * s)) & 15);
-      off[q] = static_cast<uint32_t>(k * ld) + min(C, cmax) * 16;
+      off[q] = static_cast<Off>(k * ld) + min(C, cmax) * 16;
     }
   }
-  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_s(base, off[q], lds); }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load(base, off[q], lds); }
   __device__ __forceinline__ void advance() { base += step; }
 };
 
 // k-major with a number of k-rows that need not be a multiple of 64: rows past the last are fetched from the last one (the
 // other operand is zero there)
-template <typename G>
+template <typename G, typename Off = uint32_t>
 struct KMajorTailPanel {
   static constexpr bool kKMajor = true;
   const char* base;
-  uint32_t off[G::kLoads];
+  Off off[G::kLoads];
   size_t ld;
   int rows, wave, lane, cmax;     // k-rows left from `base` on
   __device__ __forceinline__ void init(const char* b, int wave_, int lane_, size_t ld_, int cmax_, int rows_) {
@@ -191,10 +196,10 @@ struct KMajorTailPanel {
       const int k = (wave * G::kLoads + q) * 2 + (lane >> 5);
       const int P = lane & 31, s = (k & 3) | (((k >> 3) & 1) << 2);
       const int C = (P & 16) | ((P ^ (2 * s)) & 15);
-      off[q] = static_cast<uint32_t>(max(min(k, rows - 1), 0) * ld) + min(C, cmax) * 16;
+      off[q] = static_cast<Off>(max(min(k, rows - 1), 0) * ld) + min(C, cmax) * 16;
     }
   }
-  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_s(base, off[q], lds); }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load(base, off[q], lds); }
   __device__ __forceinline__ void advance() {
     base += ld * kStepK;
     rows -= kStepK;

@@ -49,20 +49,20 @@ __device__ __forceinline__ float across_groups_max(float x) {
   return fmaxf(x, __shfl_xor(x, 32, 64));
 }
 
-// logits tile: A = W rows (v0 ..), B = gathered hidden rows (list positions t0 ..)
-template <bool PERMUTED>
+// logits tile: A = W rows (v0 ..), B = gathered hidden rows (list positions t0 ..).  Off: offsets inside an operand panel
+template <bool PERMUTED, typename Off>
 __device__ __forceinline__ void logit_tile(floatx4 (&acc)[GLogit::kIB][GLogit::kJB], const bf16_t* hidden, const bf16_t* W,
                                            const int32_t* idx, int c0, int n, int v0, int t0, int H, int V, char* smem) {
   const Coord16<GLogit> co;
-  const uint32_t row_bytes = static_cast<uint32_t>(H) * 2;
+  const Off row_bytes = static_cast<Off>(H) * 2;
   GatherPanel<GLogit> pb;
   pb.init(co.wave, co.lane, [&](int row) {
     const int tk = min(t0 + row, n - 1);
     return reinterpret_cast<const char*>(hidden) + static_cast<size_t>(idx[c0 + tk]) * row_bytes;
   });
-  RowPanel<GLogit> pa;
+  RowPanel<GLogit, Off> pa;
   pa.init(reinterpret_cast<const char*>(W) + static_cast<size_t>(v0) * row_bytes, co.wave, co.lane, [&](int row) {
-    return static_cast<uint32_t>(min(PERMUTED ? a_index(row) : row, V - 1 - v0)) * row_bytes;
+    return static_cast<Off>(min(PERMUTED ? a_index(row) : row, V - 1 - v0)) * row_bytes;
   });
   gemm16<GLogit>(acc, pa, pb, H / kStepK, smem, co);
 }
@@ -71,7 +71,7 @@ __device__ __forceinline__ void logit_tile(floatx4 (&acc)[GLogit::kIB][GLogit::k
 // forward: per (vocabulary tile, token) maximum and sum of exponentials, and the target logit
 // ------------------------------------------------------------------------------------------------
 // ENT: also part_u, the partial sums of 2^(z log2e - m) * z that the entropy monitor needs (H = lse - E_p[z])
-template <bool ENT>
+template <bool ENT, typename Off>
 __global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
     const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, float* __restrict__ part_m,
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
       }
     }
     floatx4 acc[G::kIB][G::kJB];
-    logit_tile<false>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+    logit_tile<false, Off>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
 
     const Coord16<G> co;
     const int vbase = v0 + co.wm * G::kRowsA;
@@ -186,6 +186,7 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&d)[8]) {
 // columns V .. Vp and for the rows that pad the last tile); part_s[vt][j] = sum over the 256 vocabulary rows of tile vt;
 // zy[j] = target logit
 // ------------------------------------------------------------------------------------------------
+template <typename Off>
 __global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
     const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ c2,
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
       }
     }
     floatx4 acc[G::kIB][G::kJB];
-    logit_tile<true>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+    logit_tile<true, Off>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
 
     const Coord16<G> co;
     const int vbase = v0 + co.wm * G::kRowsA;
@@ -267,6 +268,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
 // logit gradient with the logits recomputed (two-call path, and the fallback of the one-pass step):
 // dZ[t][v] = g_t ([v = y_t] - exp(z - lse_t)); without coefficients g = -1 (softmax - onehot)
 // ------------------------------------------------------------------------------------------------
+template <typename Off>
 __global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
     const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ lse,
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
       }
     }
     floatx4 acc[G::kIB][G::kJB];
-    logit_tile<true>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+    logit_tile<true, Off>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
 
     const Coord16<G> co;
     const int vbase = v0 + co.wm * G::kRowsA;
@@ -460,7 +462,7 @@ __device__ __forceinline__ TileOrder dh_order(int n, int H) {
   return TileOrder{(n + kTile16 - 1) / kTile16, (H + kTile16 - 1) / kTile16, 8};
 }
 
-template <bool T>
+template <bool T, typename Off>
 __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
   using G = GDh;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -470,7 +472,7 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
   const TileOrder ord = dh_order(n, a.H);
   const int nk_all = a.Vp / kStepK;
   const SplitK sp = plan_split(ord.total(), nk_all, gridDim.x);
-  const uint32_t row_bytes = static_cast<uint32_t>(a.Vp) * 2;
+  const Off row_bytes = static_cast<Off>(a.Vp) * 2;
   const int items = sp.full + sp.rest * sp.S;
 
   for (int it = logical_workgroup(); it < items; it += gridDim.x) {
@@ -485,17 +487,17 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
-      RowPanel<G> pb;
+      RowPanel<G, Off> pb;
       const size_t kb = static_cast<size_t>(k0) * kStepK * 2;
       pb.init(reinterpret_cast<const char*>(a.dZ) + static_cast<size_t>(t0) * row_bytes + kb, co.wave, co.lane,
-              [&](int row) { return static_cast<uint32_t>(row) * row_bytes; });
+              [&](int row) { return static_cast<Off>(row) * row_bytes; });
       if constexpr (T) {
-        RowPanel<G> pa;
+        RowPanel<G, Off> pa;
         pa.init(reinterpret_cast<const char*>(a.Wt) + static_cast<size_t>(h0) * row_bytes + kb, co.wave, co.lane,
-                [&](int row) { return static_cast<uint32_t>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
+                [&](int row) { return static_cast<Off>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
         gemm16<G>(acc, pa, pb, nk, smem, co);
       } else {
-        KMajorTailPanel<G> pa;
+        KMajorTailPanel<G, Off> pa;
         pa.init(reinterpret_cast<const char*>(a.W + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
                 static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1), a.V - k0 * kStepK);
         gemm16<G>(acc, pa, pb, nk, smem, co);
@@ -583,6 +585,7 @@ __device__ __forceinline__ TileOrder dw_order(int n_vtiles, int H) {
   return TileOrder{n_vtiles, n_htiles, max(1, 32 / n_htiles)};
 }
 
+template <typename Off>
 __global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
   using G = GDw;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -605,7 +608,7 @@ __global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
-      KMajorPanel<G> pa, pb;
+      KMajorPanel<G, Off> pa, pb;
       pa.init(reinterpret_cast<const char*>(a.hG + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
               static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1));
       pb.init(reinterpret_cast<const char*>(a.dZ + static_cast<size_t>(k0) * kStepK * a.Vp + v0), co.wave, co.lane,
@@ -653,9 +656,17 @@ __global__ __launch_bounds__(kReduceThreads) void k_head_dw_reduce(DwArgs a, int
 // ================================================================================================
 // launchers
 // ================================================================================================
+namespace {
+
+// 256 rows of W, Wt or dZ span 4 GiB or more (a vocabulary or a hidden size beyond 8.3 million): 64-bit offsets in the panels
+bool wide_rows(const HeadGeom& g) { return static_cast<int64_t>(g.H > g.Vp ? g.H : g.Vp) * 2 * kTile16 >= int64_t{1} << 32; }
+
+}  // namespace
+
 int launch_fwd_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
                     float* part_m, float* part_s, float* part_u, float* zy, hipStream_t s, const int32_t* gate) {
-  auto k = part_u ? k_head_fwd<true> : k_head_fwd<false>;
+  auto k = wide_rows(g) ? (part_u ? k_head_fwd<true, uint64_t> : k_head_fwd<false, uint64_t>)
+                        : (part_u ? k_head_fwd<true, uint32_t> : k_head_fwd<false, uint32_t>);
   ATG_TRY(allow_big_lds(k, kRingBytes));
   hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
                      static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, part_m, part_s, part_u, zy, g.H, g.V,
@@ -666,8 +677,9 @@ int launch_fwd_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, 
 
 int launch_fe_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
                    const float* c2, void* E, float* part_s, float* zy, hipStream_t s) {
-  ATG_TRY(allow_big_lds(k_head_fe, kRingBytes));
-  hipLaunchKernelGGL(k_head_fe, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
+  auto k = wide_rows(g) ? k_head_fe<uint64_t> : k_head_fe<uint32_t>;
+  ATG_TRY(allow_big_lds(k, kRingBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
                      static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, c2, static_cast<bf16_t*>(E), part_s,
                      zy, g.H, g.V, g.Vp, g.TC, g.n_vtiles);
   ATG_LAUNCH_CHECK();
@@ -676,8 +688,9 @@ int launch_fe_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
 
 int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
                    const float* lse, const float* coef, void* dZ, hipStream_t s, const int32_t* gate) {
-  ATG_TRY(allow_big_lds(k_head_dz, kRingBytes));
-  hipLaunchKernelGGL(k_head_dz, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
+  auto k = wide_rows(g) ? k_head_dz<uint64_t> : k_head_dz<uint32_t>;
+  ATG_TRY(allow_big_lds(k, kRingBytes));
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GLogit::kThreads), kRingBytes, s, static_cast<const bf16_t*>(hidden),
                      static_cast<const bf16_t*>(W), ch.idx, ch.cnt, ch.c0, token_id, lse, coef, static_cast<bf16_t*>(dZ),
                      g.H, g.V, g.Vp, g.TC, g.n_vtiles, gate);
   ATG_LAUNCH_CHECK();
@@ -701,13 +714,15 @@ int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
                  static_cast<floatx4*>(part)};
   // which of the two has work is only known on the device, unless the list is too short or the chunk too far behind
   if (Wt) {
-    ATG_TRY(allow_big_lds(k_head_dh<true>, kRingBytes));
-    hipLaunchKernelGGL(k_head_dh<true>, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
+    auto k = wide_rows(g) ? k_head_dh<true, uint64_t> : k_head_dh<true, uint32_t>;
+    ATG_TRY(allow_big_lds(k, kRingBytes));
+    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
     ATG_LAUNCH_CHECK();
   }
   if (ch.c0 < kUntransposedRows) {
-    ATG_TRY(allow_big_lds(k_head_dh<false>, kRingBytes));
-    hipLaunchKernelGGL(k_head_dh<false>, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
+    auto k = wide_rows(g) ? k_head_dh<false, uint64_t> : k_head_dh<false, uint32_t>;
+    ATG_TRY(allow_big_lds(k, kRingBytes));
+    hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GDh::kThreads), kRingBytes, s, a);
     ATG_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(k_head_dh_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, a, gemm_grid());
@@ -717,10 +732,11 @@ int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
 
 int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, void* part,
                    int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
-  ATG_TRY(allow_big_lds(k_head_dw, kRingBytes));
+  auto k = wide_rows(g) ? k_head_dw<uint64_t> : k_head_dw<uint32_t>;
+  ATG_TRY(allow_big_lds(k, kRingBytes));
   const DwArgs a{static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(hG), ch.cnt, ch.c0, dW, g.H, g.V, g.Vp, g.TC,
                  g.n_vtiles, accumulate, first_chunk, live_cnt, static_cast<floatx4*>(part)};
-  hipLaunchKernelGGL(k_head_dw, dim3(gemm_grid()), dim3(GDw::kThreads), kRingBytes, s, a);
+  hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GDw::kThreads), kRingBytes, s, a);
   ATG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_head_dw_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, a, gemm_grid());
   ATG_LAUNCH_CHECK();

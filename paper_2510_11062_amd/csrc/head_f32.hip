@@ -460,7 +460,8 @@ __global__ __launch_bounds__(kF32Threads) void k_head_dh_sum(const float* __rest
 }
 
 // dW[v][h] (+)= sum_t dZ[t][v] hidden[t][h]: A = hidden columns (gathered rows), B = dZ columns, k = tokens of the chunk.
-// With one part the result goes to dW, else part p goes to rows p V .. of `part`.
+// With one part the result goes to dW, else part p goes to rows p V .. of `part`.  The tiles run along the grid's first
+// dimension, those of one vocabulary range side by side (the other dimensions end at 65535).
 template <int T>
 __global__ __launch_bounds__(kF32Threads) void k_head_dw(const float* __restrict__ dZ, const float* __restrict__ hidden,
                                                          const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
@@ -470,7 +471,8 @@ __global__ __launch_bounds__(kF32Threads) void k_head_dw(const float* __restrict
   __shared__ __attribute__((aligned(16))) float lds[F32Tile<T>::kLdsFloats];
   const int n = chunk_count(cnt, c0, TC);
   if (n <= 0 && gridDim.z == 1 && !(first_chunk && !accumulate)) return;
-  const int h0 = blockIdx.x * T, v0 = blockIdx.y * T;
+  const int h_tiles = (H + T - 1) / T;
+  const int h0 = static_cast<int>(blockIdx.x) % h_tiles * T, v0 = static_cast<int>(blockIdx.x) / h_tiles * T;
   int s0, s1;
   part_range((n + kF32StepK - 1) / kF32StepK, blockIdx.z, gridDim.z, &s0, &s1);
   auto h_row = [&](int k) { return hidden + static_cast<size_t>(idx[c0 + k]) * H + h0; };
@@ -606,7 +608,7 @@ int launch_dh_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const 
 template <int T>
 static void dw_t(const HeadGeom& g, const HeadChunk& ch, const float* dZ, const float* hidden, float* dW, float* part, int parts,
                  int accumulate, int first_chunk, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(ceil_div(g.H, T)), static_cast<unsigned>(ceil_div(g.V, T)), parts);
+  const dim3 grid(static_cast<unsigned>(ceil_div(g.H, T) * ceil_div(g.V, T)), 1, parts);
   hipLaunchKernelGGL(k_head_dw<T>, grid, dim3(kF32Threads), 0, s, dZ, hidden, ch.idx, ch.cnt, ch.c0, dW, part, g.H, g.V, g.Vp,
                      g.TC, accumulate, first_chunk);
 }

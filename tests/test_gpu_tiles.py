@@ -64,3 +64,53 @@ def test_fp32_tiles(gpu_device, H, V, E, K, length):
     torch.cuda.synchronize()
     assert api.error_word(out["workspace"]) == 0
     check_step_against_oracle(out, ref, c, cfg, tolerances(cfg), "fp32 tiles")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("one_pass", [True, False], ids=["one_pass", "two_calls"])
+@pytest.mark.parametrize("dtype,V,H,n", [(torch.bfloat16, 34_200_003, 64, 300), (torch.bfloat16, 8_600_001, 64, 12_400),
+                                         (torch.float32, 8_500_003, 32, 300)],
+                         ids=["64 k-rows of 4 GiB", "256 transposed rows of 4 GiB", "fp32"])
+def test_vocabulary_of_millions(gpu_device, dtype, V, H, n, one_pass):
+    """Rows of dZ so long that a tile of them spans 4 GiB and more.  With p about 1 / V, row y_t of dW is g_t h_t up to
+    n / V, and d_hidden of a row is g (W[y] - E_p[W]), which fp32 torch gives for sampled rows."""
+    say(f"[tiles] V={V} H={H} n={n} {dtype} one_pass={one_pass}")
+    gen = torch.Generator(device=gpu_device).manual_seed(3)
+    W = torch.randn(V, H, generator=gen, device=gpu_device, dtype=dtype).mul_(0.02)
+    hidden = torch.randn(n, H, generator=gen, device=gpu_device, dtype=dtype)
+    y = torch.randint(0, V, (n,), generator=gen, device=gpu_device, dtype=torch.int32)
+    y[-1] = V - 1
+    cu = torch.arange(0, n + 1, 100, device=gpu_device)
+    adv = torch.where(torch.arange(cu.numel() - 1, device=gpu_device) % 2 == 0, 1.0, -0.5).float()
+    batch = api.Batch(hidden, [W], y, cu)
+    old = api.at_grpo_token_logprob(batch)["logp"]
+    if one_pass:
+        out = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, 0.2, 0.2)
+    else:
+        fwd = api.at_grpo_policy_loss_fwd(batch, old, adv, 0.2, 0.2)
+        out = api.at_grpo_policy_loss_bwd(batch, old, adv, fwd["logp"], fwd["lse"], 0.2, 0.2)
+        out["logp"] = fwd["logp"]
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 0
+    g = (-adv / n).repeat_interleave(100)
+    rows = torch.unique(torch.cat([torch.arange(0, n, max(1, n // 60), device=gpu_device),
+                                   torch.arange(250, n, 256, device=gpu_device), torch.arange(n - 3, n, device=gpu_device)]))
+    h, step = hidden[rows].float(), 1 << 20
+    lse = torch.full((rows.numel(),), -float("inf"), device=gpu_device)
+    for v in range(0, V, step):
+        lse = torch.logaddexp(lse, torch.logsumexp(h @ W[v:v + step].float().T, 1))
+    target = W[y.long()].float()
+    mean = torch.zeros(rows.numel(), H, device=gpu_device)
+    for v in range(0, V, step):
+        w = W[v:v + step].float()
+        mean += torch.exp(h @ w.T - lse[:, None]) @ w
+    close = lambda a, r: float((a - r).norm() / r.norm())
+    tol = 2e-2 if dtype == torch.bfloat16 else 1e-3
+    assert (out["logp"][rows] - ((h * target[rows]).sum(1) - lse)).abs().max() <= 1e-3
+    assert close(out["d_hidden"][rows].float(), g[rows, None] * (target[rows] - mean)) <= tol
+    one = torch.bincount(y.long() - y.min(), minlength=1)[y.long() - y.min()] == 1      # tokens drawn once
+    want = g[:, None] * hidden.float()
+    assert close(out["dW"][0][y.long()][one], want[one]) <= tol
+    del W, out, batch
+    api.release_workspace()
+    torch.cuda.empty_cache()
