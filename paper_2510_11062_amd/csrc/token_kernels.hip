@@ -159,12 +159,9 @@ __global__ __launch_bounds__(256) void k_resp_cnt(TokenLayout L, const int32_t* 
 
 // Rows lo .. hi of a response, read by a team of LPR lanes (64, 32 or 16, chosen from the mean response length) in aligned
 // 4-row vectors.  each(logp, old_logp) is called for every participating row, in ascending order within a lane, and returns
-// the row's clip flags, which are stored when clip_mask is given.
-//
-// kRowBatch vectors per lane are requested before the first is used.  Two: four take 95 to 106 registers, so that fewer
-// wavefronts are resident than C5 has responses (both calls together 41.9 us with four, 39.2 with two; 65536 responses of 8
-// to 32 rows 63.8 and 59.8).
-constexpr int kRowBatch = 2;
+// the row's clip flags, which are stored when clip_mask is given.  One vector of each input per lane and round: with two
+// requested ahead, many rows take longer (28 million rows in responses of about 289, 32 lanes: 105 us, 99 with one), and few
+// are bound by launches either way.
 
 // vectors of rows of tensors that need not start on a vector's boundary
 typedef float f32x4_rows __attribute__((ext_vector_type(4), aligned(4)));
@@ -187,54 +184,41 @@ __device__ __forceinline__ void each_row(const TokenLayout& L, const float* __re
     const int bits = on ? each(logp[t], old_logp[t]) : 0;
     if (clip_mask) clip_mask[t] = static_cast<uint8_t>(bits);
   };
-  for (int64_t u = (lo >> 2) + lane; (u << 2) < hi; u += LPR * kRowBatch) {
-    f32x4_rows lp[kRowBatch], ol[kRowBatch];
-    i32x4_rows y4[kRowBatch];
-    uint32_t m4[kRowBatch];
+  for (int64_t u = (lo >> 2) + lane; (u << 2) < hi; u += LPR) {
+    const int64_t t0 = u << 2;
+    if (t0 + 4 <= L.n_tok) {
+      // rows of a neighbouring response inside the vector are read but not used
+      const f32x4_rows lp = *reinterpret_cast<const f32x4_rows*>(logp + t0);
+      const f32x4_rows ol = *reinterpret_cast<const f32x4_rows*>(old_logp + t0);
+      uint32_t m4 = 0x01010101u;
+      if (L.mask) m4 = *reinterpret_cast<const u8x4_rows*>(L.mask + t0);
+      i32x4_rows y4 = 0;
+      if (L.token_id) y4 = *reinterpret_cast<const i32x4_rows*>(L.token_id + t0);
+      const bool interior = (t0 >= lo) && (t0 + 4 <= hi);
+      uint32_t out = 0;
 #pragma unroll
-    for (int b = 0; b < kRowBatch; ++b) {
-      // rows of a neighbouring response inside a vector are read but not used
-      const int64_t t0 = (u + b * LPR) << 2;
-      m4[b] = 0x01010101u;
-      y4[b] = 0;
-      if (t0 < hi && t0 + 4 <= L.n_tok) {
-        lp[b] = *reinterpret_cast<const f32x4_rows*>(logp + t0);
-        ol[b] = *reinterpret_cast<const f32x4_rows*>(old_logp + t0);
-        if (L.mask) m4[b] = *reinterpret_cast<const u8x4_rows*>(L.mask + t0);
-        if (L.token_id) y4[b] = *reinterpret_cast<const i32x4_rows*>(L.token_id + t0);
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < kRowBatch; ++b) {
-      const int64_t t0 = (u + b * LPR) << 2;
-      if (t0 >= hi) break;
-      if (t0 + 4 <= L.n_tok) {
-        const bool interior = (t0 >= lo) && (t0 + 4 <= hi);
-        uint32_t out = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const bool mine = interior || (t0 + e >= lo && t0 + e < hi);
-          bool on = mine && (head >= 0) && (((m4[b] >> (8 * e)) & 0xffu) != 0);
-          if (on && L.token_id != nullptr && (y4[b][e] < 0 || y4[b][e] >= L.V)) {
-            atomicOr(err, AT_GRPO_DATA_TOKEN_RANGE);
-            on = false;
-          }
-          if (on) out |= static_cast<uint32_t>(each(lp[b][e], ol[b][e])) << (8 * e);
+      for (int e = 0; e < 4; ++e) {
+        const bool mine = interior || (t0 + e >= lo && t0 + e < hi);
+        bool on = mine && (head >= 0) && (((m4 >> (8 * e)) & 0xffu) != 0);
+        if (on && L.token_id != nullptr && (y4[e] < 0 || y4[e] >= L.V)) {
+          atomicOr(err, AT_GRPO_DATA_TOKEN_RANGE);
+          on = false;
         }
-        if (clip_mask) {
-          if (interior) {
-            *reinterpret_cast<u8x4_rows*>(clip_mask + t0) = out;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (t0 + e >= lo && t0 + e < hi) clip_mask[t0 + e] = static_cast<uint8_t>(out >> (8 * e));
-          }
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (t0 + e >= lo && t0 + e < hi) one(t0 + e);
+        if (on) out |= static_cast<uint32_t>(each(lp[e], ol[e])) << (8 * e);
       }
+      if (clip_mask) {
+        if (interior) {
+          *reinterpret_cast<u8x4_rows*>(clip_mask + t0) = out;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (t0 + e >= lo && t0 + e < hi) clip_mask[t0 + e] = static_cast<uint8_t>(out >> (8 * e));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (t0 + e >= lo && t0 + e < hi) one(t0 + e);
     }
   }
 }
@@ -682,12 +666,17 @@ int team_lanes_small(const TokenLayout& L) {
   return mean_rows > 128 ? 64 : mean_rows > 64 ? 32 : 16;
 }
 
-// Lanes that share a response in the row kernels, by the mean number of rows.  The call ends with its longest response, which
-// may be many times the mean: C5 (mean 289 rows, up to 4096) takes 53.2 us for both calls with 32 lanes, 41.9 with 64.  With
-// uniform lengths (64 .. 512, 100 .. 200, 400 .. 900) neither choice shows beside the launches.
+// Lanes that share a response in the row kernels, by the mean number of rows and by how many responses there are.  The chip
+// holds 8192 of these wavefronts.  While the responses are few rounds of it, the call ends with its longest response, which may
+// be many times the mean: more lanes (C5, 6228 responses of 289 rows in the mean and up to 4096: surrogate 19 us with 64 lanes,
+// 26 with 32; 24 000 such responses 36 and 42).  Beyond that the rate counts, and lanes without rows cost: 28 million rows in
+// responses of about 170 take 126 us with 64 lanes, 109 with 32; of about 100, 152 with 32 and 135 with 16; of about 600, 88
+// with 64 and 90 with 32.
 int team_lanes(const TokenLayout& L) {
   const int64_t mean_rows = L.n_tok / (L.n_resp > 0 ? L.n_resp : 1);
-  return mean_rows >= 160 ? 64 : mean_rows >= 60 ? 32 : 16;
+  if (mean_rows >= 512) return 64;
+  if (mean_rows >= 160) return L.n_resp <= 32768 ? 64 : 32;
+  return mean_rows >= 60 && L.n_resp <= 8192 ? 32 : 16;
 }
 
 }  // namespace

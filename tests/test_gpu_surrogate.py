@@ -1,0 +1,65 @@
+"""Surrogate and diagnostics on both sides of every switch of the lanes that share a response (16, 32, 64), with tensors
+that start anywhere, against the CPU oracle: flags and counts exact, sums within fp32's 1e-4 as in tests/test_gpu_parity.py
+(here the mean of terms of both signs and size about 1, hence 1e-6 absolute)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import at_grpo_oracle as orc
+from paper_2510_11062_amd import api
+from tests.gpu_case import host
+from tests.test_gpu_parity import say
+
+
+SIZES = [(50, 59), (50, 60), (8192, 60), (8193, 60), (50, 159), (50, 160), (32768, 160), (32769, 160), (33000, 511), (50, 512)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_resp,mean,shift", [(n, m, 0) for n, m in SIZES] + [(n, m, s) for n, m in SIZES if n < 9000 for s in (1, 3)])
+def test_rows_per_team(gpu_device, n_resp, mean, shift):
+    rng = np.random.default_rng(n_resp + mean)
+    lengths = rng.integers(0, 2 * mean + 1, n_resp)
+    lengths[0] += n_resp * mean - lengths.sum() if n_resp * mean > lengths.sum() else 0
+    while lengths.sum() > n_resp * mean:                       # the mean decides, so it is met exactly
+        at = rng.integers(0, n_resp, n_resp)
+        over = lengths.sum() - n_resp * mean
+        pick = np.unique(at[lengths[at] > 0])[:over]
+        lengths[pick] -= 1
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    n, V, heads = int(cu[-1]), 1000, 3
+    assert n == n_resp * mean
+    say(f"[surrogate] {n_resp} responses of {mean} rows, shift {shift}")
+    logp = (-12 * rng.random(n)).astype(np.float32)
+    old = (logp + 0.2 * rng.standard_normal(n)).astype(np.float32)
+    token = rng.integers(0, V, n).astype(np.int32)
+    token[[7, n // 2, n - 1]] = [V, -1, V + 5]
+    mask = (rng.random(n) < 0.9).astype(np.uint8)
+    mask[7] = 1
+    adv = rng.standard_normal(n_resp).astype(np.float32)
+    adv[::5] = 0
+    agent = rng.integers(0, 3, n_resp).astype(np.int32)
+    head_of_agent = np.array([2, 0, 1], np.int32)
+
+    def dev(a):
+        t = torch.from_numpy(np.concatenate([a[:shift], a]) if shift else a).to(gpu_device)
+        return t[shift:]
+
+    batch = api.Batch(None, None, dev(token), torch.from_numpy(cu).to(gpu_device), dev(mask), dev(agent), dev(head_of_agent),
+                      n_tok=n, V=V, n_heads=heads)
+    good = np.where((token >= 0) & (token < V), mask, 0).astype(np.uint8)
+    resp, head = orc.token_heads(n, cu, agent, head_of_agent)
+    for agg in ("token_mean", "seq_mean_token_mean"):
+        out = api.at_grpo_surrogate_from_logp(batch, dev(logp), dev(old), dev(adv), 0.2, 0.28, agg)
+        torch.cuda.synchronize()
+        assert api.error_word(out["workspace"]) == 4           # AT_GRPO_DATA_TOKEN_RANGE
+        ref = orc.policy_loss_from_logp(logp, old, adv, good, head, resp, heads, 0.2, 0.28, agg)
+        assert np.array_equal(host(out["clip_mask"]), ref[1]) and np.array_equal(host(out["n_valid"]), ref[2])
+        loss = host(out["loss"]).astype(np.float64)
+        assert np.all(np.abs(loss - ref[0]) <= 1e-4 * np.abs(ref[0]) + 1e-6), (loss, ref[0])
+    counts, kl, ratio = orc.surrogate_diagnostics(logp, old, adv, good, head, resp, heads, 0.2, 0.28)
+    out = api.at_grpo_surrogate_diagnostics(batch, dev(logp), dev(old), dev(adv), 0.2, 0.28)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 4
+    assert np.array_equal(host(out["counts"]).astype(np.int64), counts)
+    stats = host(out["stats"]).astype(np.float64)
+    assert np.allclose(stats[:, 0], kl, rtol=1e-4, atol=1e-7) and np.allclose(stats[:, 1], ratio, rtol=1e-4, atol=0)
