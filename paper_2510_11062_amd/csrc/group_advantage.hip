@@ -62,14 +62,29 @@ __device__ __forceinline__ int64_t key_of(const GaArgs& a, int r, bool* ok) {
 
 __device__ __forceinline__ bool finite_reward(float x) { return fabsf(x) <= 3.402823466e38f; }
 
-// Histogram over the key box.  The atomic's return value is the response's arrival rank inside its
-// group.  Neighbouring lanes with the same key (candidates of one group emitted together, the
-// order a rollout produces) are folded into one atomic per run.
+// hist[key] += 1 for the wavefront's lanes with key >= 0; returns the lane's arrival rank inside its group.  Neighbouring lanes
+// with the same key (candidates of one group emitted together, the order a rollout produces) are folded into one atomic
+// per run.  Every lane of the wavefront calls it.
+__device__ __forceinline__ int count_runs(int32_t* hist, int key) {
+  const int lane = threadIdx.x & 63;
+  const int prev = __shfl_up(key, 1, 64);
+  const bool head = (lane == 0) || (key != prev);
+  const unsigned long long heads = __builtin_amdgcn_ballot_w64(head);
+  const unsigned long long below = heads & ((2ull << lane) - 1ull);          // heads at or below this lane
+  const int start = 63 - __builtin_clzll(below);
+  const unsigned long long above = (lane == 63) ? 0ull : (heads >> (lane + 1)) << (lane + 1);
+  const int next = above ? __builtin_ctzll(above) : 64;
+  int base = 0;
+  if (head && key >= 0) base = atomicAdd(&hist[key], next - lane);
+  base = __shfl(base, start, 64);
+  return base + (lane - start);
+}
+
+// histogram over the key box
 __global__ __launch_bounds__(256) void k_ga_hist(GaArgs a, int32_t* __restrict__ err,
                                                  int32_t* __restrict__ hist, int32_t* __restrict__ key_of_resp,
                                                  int32_t* __restrict__ rank_of_resp) {
   const int r = blockIdx.x * 256 + threadIdx.x;
-  const int lane = threadIdx.x & 63;
   int key = -1;
   if (r < a.n_resp) {
     bool ok;
@@ -83,18 +98,8 @@ __global__ __launch_bounds__(256) void k_ga_hist(GaArgs a, int32_t* __restrict__
     }
     key_of_resp[r] = key;
   }
-  // runs of equal keys inside the wavefront
-  const int prev = __shfl_up(key, 1, 64);
-  const bool head = (lane == 0) || (key != prev);
-  const unsigned long long heads = __builtin_amdgcn_ballot_w64(head);
-  const unsigned long long below = heads & ((2ull << lane) - 1ull);          // heads at or below this lane
-  const int start = 63 - __builtin_clzll(below);
-  const unsigned long long above = (lane == 63) ? 0ull : (heads >> (lane + 1)) << (lane + 1);
-  const int next = above ? __builtin_ctzll(above) : 64;
-  int base = 0;
-  if (head && key >= 0) base = atomicAdd(&hist[key], next - lane);
-  base = __shfl(base, start, 64);
-  if (r < a.n_resp && key >= 0) rank_of_resp[r] = base + (lane - start);
+  const int rank = count_runs(hist, key);
+  if (r < a.n_resp && key >= 0) rank_of_resp[r] = rank;
 }
 
 // per-block sums of (key present, members) over 2048 keys
@@ -366,6 +371,50 @@ __device__ __forceinline__ void fill_tails(const GaOut& o, int G, int n_listed, 
   for (int64_t r = n_listed + tid; r < n_resp; r += threads) o.perm[r] = 0;
 }
 
+// Groups 0 .. n - 1 of a list of members in arrival order, outputs from group g0 on: off(i) is the first member of group i,
+// off(n) the end of the last.  The groups are shared by `parts` workgroups of 256 threads (a thread per small group) or by
+// `waves` wavefronts (one per larger group).
+template <typename Off>
+__device__ __forceinline__ void finish_small_groups(int n, int g0, int part, int parts, Off off, const int32_t* arrival,
+                                                    const float* reward, const GaStat& st, const GaOut& o) {
+  for (int g = part * 256 + static_cast<int>(threadIdx.x); g < n; g += parts * 256) {
+    const int from = off(g), members = off(g + 1) - from;
+    if (members > kSmallGroup) continue;
+    float mean, sd;
+    int best;
+    finish_by_thread(
+        members, [&](int j) { return arrival[from + j]; }, [&](int j) { return reward[arrival[from + j]]; },
+        [&](int rank, int r) { o.perm[from + rank] = r; }, [&](int, int r, float v) { o.adv[r] = v; }, st, &mean, &sd, &best);
+    put_stats(o, g0 + g, mean, sd, best);
+  }
+}
+
+// A wavefront looks at the sizes of up to 64 consecutive groups at once: one group at a time, a million groups of one member
+// took 16384 wavefronts 64 dependent pairs of loads each (129 us in rollout order and 206 shuffled, now 52 and 130).
+template <typename Off>
+__device__ __forceinline__ void finish_large_groups(int n, int g0, int wave, int waves, Off off, const int32_t* arrival,
+                                                    const float* reward, const GaStat& st, const GaOut& o) {
+  const int lane = threadIdx.x & 63;
+  const int per = min(64, (n + waves - 1) / waves);
+  for (int64_t first = static_cast<int64_t>(wave) * per; first < n; first += static_cast<int64_t>(waves) * per) {
+    int from = 0, members = 0;
+    if (lane < per && first + lane < n) {
+      from = off(static_cast<int>(first) + lane);
+      members = off(static_cast<int>(first) + lane + 1) - from;
+    }
+    for (uint64_t large = __builtin_amdgcn_ballot_w64(members > kSmallGroup); large != 0; large &= large - 1) {
+      const int j = __builtin_ctzll(large);
+      const int f = __shfl(from, j, 64), m = __shfl(members, j, 64);
+      float mean, sd;
+      int best;
+      finish_by_wave(
+          m, lane, [&](int i) { return arrival[f + i]; }, [&](int i) { return reward[arrival[f + i]]; },
+          [&](int r) { return reward[r]; }, o.perm + f, [&](int, int r, float v) { o.adv[r] = v; }, st, &mean, &sd, &best);
+      if (lane == 0) put_stats(o, g0 + static_cast<int>(first) + j, mean, sd, best);
+    }
+  }
+}
+
 // Eq. (3): r = alpha * r_team + r_loc.  One fp32 multiplication, then one fp32 addition (never
 // contracted to an fma): the result decides which groups count as all-equal and which candidate
 // is the arg max, so its rounding is part of the definition.
@@ -430,6 +479,9 @@ constexpr int kRangeMaxResp = 65536, kRangeMaxKeys = 65528;
 constexpr int kRangeList = 4096;         // members listed in LDS; more go to global scratch
 constexpr int kRangeDirect = 4096;       // responses up to which every workgroup computes the keys itself
 constexpr int kRangeRounds = 4;          // responses per thread whose ids are in flight together
+constexpr int kRangeOwn = 128;           // keys of a workgroup beyond which its list may be left to the whole grid
+constexpr int kRangeBlocks = 512;        // workgroups of such calls: 256 responses or 1024 keys each (more than kRangeOwn)
+static_assert(kRangeMaxKeys / kRangeOwn <= kRangeBlocks, "one word pair each");
 
 // key of a response in 16 bits, or why it has none
 enum : int { kKeyNone = 0xfffd, kKeyBadReward = 0xfffe, kKeyBadId = 0xffff };
@@ -452,11 +504,22 @@ __global__ __launch_bounds__(256) void k_ga_keys(GaArgs a, GaMix mix, uint16_t* 
   if (mix.reward_out && r < a.n_resp) mix.reward_out[r] = x;
 }
 
+// eight keys, and how many equal ones from each on (an LDS atomic per run: responses of a group side by side would take turns)
+__device__ __forceinline__ void keys_and_runs(const uint4& v, int (&key)[8], int (&run)[8]) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int e = 0; e < 8; ++e) key[e] = (w[e >> 1] >> (16 * (e & 1))) & 0xffff;
+#pragma unroll
+  for (int e = 7; e >= 0; --e) run[e] = e < 7 && key[e] == key[min(e + 1, 7)] ? run[min(e + 1, 7)] + 1 : 1;
+}
+
 // NT threads, each with at most one own key.  keys16: the keys (then a.reward holds the rewards), or null.
+// Where the responses lie in the key range is only seen here: a workgroup whose members do not fit its list finishes them out of
+// global scratch, or, with `left`, leaves them to k_ga_left and says which groups those are: left[2 b] groups from left[2 b + 1].
 template <int NT>
 __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st, int n_keys, int n_own,
                                                  const uint16_t* __restrict__ keys16, int32_t* __restrict__ err,
-                                                 int32_t* __restrict__ arrival, GaOut o) {
+                                                 int32_t* __restrict__ arrival, int32_t* __restrict__ left, GaOut o) {
   __shared__ int present[(kRangeMaxKeys + 31) / 32];
   __shared__ int count[NT], cursor[NT], first[NT], gid[NT];
   __shared__ int list_id[kRangeList];
@@ -470,11 +533,12 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
 
   int keys[kRangeRounds];          // without keys16: of the last batch, all of them when there is one batch only
   int below = 0, bad = 0;
-  // (keys that stand for "none" are above every range); workgroup 0 has no smaller keys and looks for bad ones instead
-  auto look = [&](int key, bool new_run) {
+  // (keys that stand for "none" are above every range); workgroup 0 has no smaller keys and looks for bad ones instead.
+  // members: 0, or how many equal keys from this one on are counted at once
+  auto look = [&](int key, bool new_run, int members) {
     below += key < lo;
     const unsigned d = static_cast<unsigned>(key - lo);
-    if (d < static_cast<unsigned>(own)) atomicAdd(&count[d], 1);
+    if (members > 0 && d < static_cast<unsigned>(own)) atomicAdd(&count[d], members);
     if (b == 0) {
       bad |= key == kKeyBadId ? AT_GRPO_DATA_ID_RANGE : (key == kKeyBadReward ? AT_GRPO_DATA_REWARD : 0);
     } else if (key < lo && new_run) {
@@ -484,13 +548,12 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   if (keys16) {
     for (int c = tid; c * 8 < a.n_resp; c += NT) {
       const uint4 v = reinterpret_cast<const uint4*>(keys16)[c];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-      int prev = -1;
+      int key[8], run[8];
+      keys_and_runs(v, key, run);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const int key = (w[e >> 1] >> (16 * (e & 1))) & 0xffff;
-        look(key, key != prev);
-        prev = key;
+        const bool first_of_run = e == 0 || key[e] != key[e - 1];
+        look(key[e], first_of_run, first_of_run ? run[e] : 0);
       }
     }
   } else {
@@ -507,7 +570,7 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
         const int r = base + u * NT + tid;
         if (mix.reward_out && r < a.n_resp && b == 0) mix.reward_out[r] = x[u];
         const int prev = __shfl_up(keys[u], 1, 64);
-        look(keys[u], lane == 0 || prev != keys[u]);
+        look(keys[u], lane == 0 || prev != keys[u], 1);
       }
     }
   }
@@ -531,10 +594,11 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   __syncthreads();
 
   // list the own members
-  auto enlist = [&](int r, int key) {
+  int at = 0;
+  auto enlist = [&](int r, int key, int members) {     // members: as in look(); 0 takes the place behind the one before
     const unsigned d = static_cast<unsigned>(key - lo);
     if (d < static_cast<unsigned>(own)) {
-      const int at = atomicAdd(&cursor[d], 1);
+      at = members > 0 ? atomicAdd(&cursor[d], members) : at + 1;
       if (in_lds) list_id[at] = r;
       else arrival[below + at] = r;
       o.group_id[r] = gid[d];
@@ -547,9 +611,10 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   if (keys16) {
     for (int cc = tid; cc * 8 < a.n_resp; cc += NT) {
       const uint4 v = reinterpret_cast<const uint4*>(keys16)[cc];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      int key[8], run[8];
+      keys_and_runs(v, key, run);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) enlist(cc * 8 + e, (w[e >> 1] >> (16 * (e & 1))) & 0xffff);
+      for (int e = 0; e < 8; ++e) enlist(cc * 8 + e, key[e], e == 0 || key[e] != key[e - 1] ? run[e] : 0);
     }
   } else {
     for (int base = 0; base < a.n_resp; base += kRangeRounds * NT) {
@@ -558,7 +623,7 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
         const int r = base + u * NT + tid;
         float x;
         if (a.n_resp > kRangeRounds * NT) keys[u] = r < a.n_resp ? key16(a, mix, r, &x) : kKeyNone;   // else still in registers
-        enlist(r, keys[u]);
+        enlist(r, keys[u], 1);
       }
     }
   }
@@ -590,8 +655,12 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
       if (lane == 0) put_stats(o, gid[k], mean, sd, best);
     }
   };
+  if (left && tid == 0) {
+    left[2 * b] = in_lds ? 0 : own_groups;
+    left[2 * b + 1] = g_below;
+  }
   if (in_lds) finish([&](int j) { return list_id[j]; }, [&](int j) { return list_x[j]; });
-  else finish([&](int j) { return arrival[below + j]; }, [&](int j) { return reward(arrival[below + j]); });
+  else if (!left) finish([&](int j) { return arrival[below + j]; }, [&](int j) { return reward(arrival[below + j]); });
 
   if (b == 0) {
     const int id_bad = __syncthreads_or(bad & AT_GRPO_DATA_ID_RANGE), x_bad = __syncthreads_or(bad & AT_GRPO_DATA_REWARD);
@@ -607,6 +676,24 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   }
 }
 
+// The groups that workgroups of k_ga_range left, shared by the grid.
+__global__ __launch_bounds__(256) void k_ga_left(int n_blocks, const int32_t* __restrict__ left, const int32_t* __restrict__ arrival,
+                                                 const float* __restrict__ reward, GaStat st, GaOut o) {
+  __shared__ int groups[kRangeBlocks];
+  int any = 0;
+  for (int b = threadIdx.x; b < n_blocks; b += 256) any |= groups[b] = left[2 * b];
+  if (!__syncthreads_or(any)) return;
+  for (int b = 0; b < n_blocks; ++b) {
+    const int n = groups[b];
+    if (n == 0) continue;
+    const int g0 = left[2 * b + 1];
+    auto off = [&](int g) { return o.seg_offsets[g0 + g]; };
+    finish_small_groups(n, g0, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), off, arrival, reward, st, o);
+    finish_large_groups(n, g0, static_cast<int>(blockIdx.x * 256 + threadIdx.x) >> 6, static_cast<int>(gridDim.x) * 4, off, arrival,
+                        reward, st, o);
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // Pools.  A response needs four accesses at unrelated addresses if histogram, ranks, lists and results live in global memory
 // (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of about 3072
@@ -614,21 +701,31 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
 // LDS; and one last pass in response order gathers the results, again in runs.  About 84 bytes per response, all streamed.
 // 2^22 shuffled responses over 2^19 keys: 257 us for the whole call (272 with one response at a time in the partition and in the
 // gathering of the results).
+//
+// How many responses a bin has depends on where the ids lie in their extents, which only the device sees.  Bins that do not
+// fit LDS (a pool from a part of the extents, say) are therefore not left to one workgroup: from the partition on their
+// responses go the way of the histogram path (ranks from global counters, member lists by group, groups shared by the whole
+// grid), inside the launches that the other bins need anyway.  262144 responses in groups of 128 that lie in one bin of
+// 2^19 keys: 8275 us by one workgroup, 75 now; 2^20 in groups of 8 from a quarter of their extents, in rollout order and
+// shuffled: 104 and 138 us by a workgroup per bin, 101 and 154 now.
 // ------------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 1024, kPoolPer = 16, kPoolBlock = kPoolThreads * kPoolPer;   // responses per partitioning block
 constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolPerBin = 3072;
 constexpr int kPoolMaxKeys = 2048;       // keys of a bin
-constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; more are listed in global scratch
+constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; a bin with more is "large"
 constexpr int kBinThreads = 512;
+constexpr int kLargeBlocks = 512;        // workgroups that finish the groups of the large bins
 
 struct PoolPlan {
   int width, bins;           // bin of a key = key / width
   int32_t* key;              // [R]
-  int32_t* slot;             // [R] place of the response in the partitioned order
-  int32_t* list;             // [R] members of oversized bins
+  int32_t* slot;             // [R] place of the response in the partitioned order; of a large bin: bit 31 and rank inside its group
+  int32_t* list;             // [R] members of the large bins, by group
+  int32_t* hist;             // [keys] of a large bin: members, then the first one's place in `list`
+  int32_t* gid_of_key;       // [keys] of a large bin: group inside the bin
   int2* kr;                  // [R] (key, response), partitioned
   float* x;                  // [R] rewards, partitioned
-  float2* result;            // [R] (advantage, group inside the bin), partitioned; bit 31: the advantage is stored already
+  float2* result;            // [R] (advantage, group inside the bin), partitioned
   float4* stats;             // [R] (mean, std, best, offset) of group i of the bin at bin_base + i
   int32_t* blk;              // [blocks][bins]
   int32_t* bin_cnt;          // [bins]
@@ -636,6 +733,7 @@ struct PoolPlan {
   int32_t* cursor;           // [bins]
   int32_t* bin_groups;       // [bins]
   int32_t* gid_base;         // [bins + 1]
+  int32_t* large;            // [bins + 1] number of large bins, then which ones they are
 };
 
 // atomicAdd(&counter[bin], 1) of every active lane.  In rollout order all lanes of a wavefront name the same bin, and 64 atomics
@@ -710,16 +808,34 @@ __device__ __forceinline__ void scan_small(const int32_t* in, int n, int32_t* ou
   if (threadIdx.x == 0) out[n] = total;
 }
 
-__global__ __launch_bounds__(kPoolThreads) void k_gp_bases(PoolPlan p) {
+// workgroup 0: bases of the bins, list of the large ones; the others clear the counters of the large bins' keys, a wavefront per
+// bin
+constexpr int kBasesBins = kPoolThreads / 64;
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_bases(PoolPlan p, int64_t n_keys) {
   __shared__ int lds16[16];
-  scan_small(p.bin_cnt, p.bins, p.bin_base, p.cursor, lds16);
+  __shared__ int n_large;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) n_large = 0;
+    scan_small(p.bin_cnt, p.bins, p.bin_base, p.cursor, lds16);
+    __syncthreads();
+    for (int i = threadIdx.x; i < p.bins; i += kPoolThreads)
+      if (p.bin_cnt[i] > kPoolCap) p.large[1 + atomicAdd(&n_large, 1)] = i;
+    __syncthreads();
+    if (threadIdx.x == 0) p.large[0] = n_large;
+    return;
+  }
+  const int bin = (blockIdx.x - 1) * kBasesBins + (threadIdx.x >> 6);
+  if (bin >= p.bins || p.bin_cnt[bin] <= kPoolCap) return;
+  const int64_t lo = static_cast<int64_t>(bin) * p.width, end = min(lo + p.width, n_keys);
+  for (int64_t k = lo + (threadIdx.x & 63); k < end; k += 64) p.hist[k] = 0;
 }
 
 __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const float* __restrict__ reward, PoolPlan p) {
   __shared__ int next[kPoolMaxBins];
   for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) {
     const int c = p.blk[static_cast<size_t>(blockIdx.x) * p.bins + i];
-    next[i] = c ? atomicAdd(&p.cursor[i], c) : 0;
+    next[i] = c == 0 ? 0 : (p.bin_cnt[i] > kPoolCap ? INT32_MIN : atomicAdd(&p.cursor[i], c));   // places in large bins: below zero
   }
   __syncthreads();
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolBlock + threadIdx.x;
@@ -734,12 +850,20 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (key[u] < 0) continue;
       const int r = static_cast<int>(r0 + (u0 + u) * kPoolThreads);
-      const int at = count_in_bin(next, static_cast<int>(static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)));
-      p.kr[at] = make_int2(key[u], r);
-      p.x[at] = x[u];
-      p.slot[r] = at;
+      int at = 0;
+      if (key[u] >= 0) {
+        at = count_in_bin(next, static_cast<int>(static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)));
+        if (at >= 0) {
+          p.kr[at] = make_int2(key[u], r);
+          p.x[at] = x[u];
+          p.slot[r] = at;
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(at < 0) != 0) {
+        const int rank = count_runs(p.hist, at < 0 ? key[u] : -1);
+        if (at < 0) p.slot[r] = INT32_MIN | rank;
+      }
     }
   }
 }
@@ -756,10 +880,15 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
   const int bin = blockIdx.x, base = p.bin_base[bin], m = p.bin_base[bin + 1] - base;
   const int lo = bin * p.width;
   const int own = static_cast<int>(min(static_cast<int64_t>(p.width), n_keys - lo));
-  const bool in_lds = m <= kPoolCap;
-  for (int k = tid; k < own; k += kBinThreads) count[k] = 0;
+  if (m == 0) {
+    if (tid == 0) p.bin_groups[bin] = 0;
+    return;
+  }
+  const bool large = m > kPoolCap;
+  for (int k = tid; k < own; k += kBinThreads) count[k] = large ? p.hist[lo + k] : 0;
   __syncthreads();
-  for (int e = tid; e < m; e += kBinThreads) atomicAdd(&count[p.kr[base + e].x - lo], 1);
+  if (!large)
+    for (int e = tid; e < m; e += kBinThreads) atomicAdd(&count[p.kr[base + e].x - lo], 1);
   __syncthreads();
   // offsets and ids of the keys that occur: each thread owns a run of keys
   constexpr int kPer = kPoolMaxKeys / kBinThreads;
@@ -800,64 +929,75 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
     if (k < own) {
       next[k] = at;
       gid[k] = static_cast<uint16_t>(g);
+      if (large && c[e] > 0) {
+        p.hist[lo + k] = base + at;
+        p.gid_of_key[lo + k] = g;
+        p.stats[base + g].w = __int_as_float(base + at);
+      }
       at += c[e];
       g += c[e] > 0;
     }
   }
   if (tid == 0) p.bin_groups[bin] = n_groups;
+  if (large) return;
   __syncthreads();
   for (int e = tid; e < m; e += kBinThreads) {
     const int2 kr = p.kr[base + e];
     const int k = kr.x - lo, f = atomicAdd(&next[k], 1);
-    if (in_lds) {
-      list_id[f] = kr.y;
-      list_x[f] = p.x[base + e];
-      place[e] = static_cast<uint16_t>(f);
-    } else {
-      p.list[base + f] = kr.y;
-      p.result[base + e] = make_float2(0.f, __int_as_float(static_cast<int>(gid[k] | 0x80000000u)));
-    }
+    list_id[f] = kr.y;
+    list_x[f] = p.x[base + e];
+    place[e] = static_cast<uint16_t>(f);
   }
   __syncthreads();
-  // next[k] is now one past the members of key k
-  auto reward_at = [&](int r) { return reward[r]; };
-  auto finish = [&](auto id_of, auto x_of, auto put_adv) {
-    for (int k = tid; k < own; k += kBinThreads) {
-      const int n = count[k], f = next[k] - n;
-      if (n == 0 || n > kSmallGroup) continue;
-      float mean, sd;
-      int best;
-      int32_t* perm = o.perm + base + f;
-      finish_by_thread(
-          n, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); },
-          [&](int rank, int r) { perm[rank] = r; }, [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
-      p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
-    }
-    for (int k = wave; k < own; k += kBinThreads / 64) {
-      const int n = count[k], f = next[k] - n;
-      if (n <= kSmallGroup) continue;
-      float mean, sd;
-      int best;
-      finish_by_wave(
-          n, lane, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); }, reward_at, o.perm + base + f,
-          [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
-      if (lane == 0) p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
-    }
-  };
-  if (in_lds) {
-    // a member's advantage takes the place of its reward, which only its own group reads
-    finish([&](int j) { return list_id[j]; }, [&](int j) { return list_x[j]; }, [&](int j, int, float v) { list_x[j] = v; });
-    __syncthreads();
-    for (int e = tid; e < m; e += kBinThreads)
-      p.result[base + e] = make_float2(list_x[place[e]], __int_as_float(static_cast<int>(gid[p.kr[base + e].x - lo])));
-  } else {
-    finish([&](int j) { return p.list[base + j]; }, [&](int j) { return reward[p.list[base + j]]; },
-           [&](int, int r, float v) { o.adv[r] = v; });
+  // next[k] is now one past the members of key k; a member's advantage takes the place of its reward, which only its own
+  // group reads
+  auto id_of = [&](int j) { return list_id[j]; };
+  auto x_of = [&](int j) { return list_x[j]; };
+  auto put_adv = [&](int j, int, float v) { list_x[j] = v; };
+  for (int k = tid; k < own; k += kBinThreads) {
+    const int n = count[k], f = next[k] - n;
+    if (n == 0 || n > kSmallGroup) continue;
+    float mean, sd;
+    int best;
+    int32_t* perm = o.perm + base + f;
+    finish_by_thread(
+        n, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); },
+        [&](int rank, int r) { perm[rank] = r; }, [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
+    p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
   }
+  for (int k = wave; k < own; k += kBinThreads / 64) {
+    const int n = count[k], f = next[k] - n;
+    if (n <= kSmallGroup) continue;
+    float mean, sd;
+    int best;
+    finish_by_wave(
+        n, lane, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); }, [&](int r) { return reward[r]; },
+        o.perm + base + f, [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
+    if (lane == 0) p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
+  }
+  __syncthreads();
+  for (int e = tid; e < m; e += kBinThreads)
+    p.result[base + e] = make_float2(list_x[place[e]], __int_as_float(static_cast<int>(gid[p.kr[base + e].x - lo])));
 }
 
-__global__ __launch_bounds__(kPoolThreads) void k_gp_groups(PoolPlan p, GaOut o) {
+// workgroup 0: ids of the bins' first groups; the others list the members of the large bins
+__global__ __launch_bounds__(kPoolThreads) void k_gp_groups(PoolPlan p, int n_resp, GaOut o) {
   __shared__ int lds16[16];
+  if (blockIdx.x > 0) {
+    if (p.large[0] == 0) return;
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x - 1) * kPoolThreads * 4 + threadIdx.x;
+    int key[4], s[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = r0 + u * kPoolThreads;
+      key[u] = r < n_resp ? p.key[r] : -1;
+      s[u] = r < n_resp ? p.slot[r] : 0;         // meaningless without a key
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (key[u] >= 0 && s[u] < 0) p.list[p.hist[key[u]] + (s[u] & 0x7fffffff)] = static_cast<int>(r0 + u * kPoolThreads);
+    return;
+  }
   scan_small(p.bin_groups, p.bins, p.gid_base, nullptr, lds16);
   __threadfence();
   __syncthreads();
@@ -868,7 +1008,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_groups(PoolPlan p, GaOut o)
   }
 }
 
-// results in response order; the blocks behind `resp_blocks` write the groups of a bin each, the last ones fill the tails
+// results in response order; the blocks behind `resp_blocks` write the groups of a bin each, the last ones fill the tails.
+// Advantages and groups of large bins are left to k_gp_large.
 __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp_blocks, GaOut o) {
   if (static_cast<int>(blockIdx.x) < resp_blocks) {
     // the loads of a thread's four responses go out together
@@ -882,7 +1023,7 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
       at[u] = r < n_resp ? p.slot[r] : 0;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) res[u] = key[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f);   // no slot without a key
+    for (int u = 0; u < 4; ++u) res[u] = key[u] >= 0 && at[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f);   // no slot without a key
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t r = r0 + u * 256;
@@ -891,9 +1032,9 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
         o.group_id[r] = -1;
         o.adv[r] = 0.f;
       } else {
-        const int lg = __float_as_int(res[u].y);
-        o.group_id[r] = p.gid_base[static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)] + (lg & 0x7fffffff);
-        if (lg >= 0) o.adv[r] = res[u].x;
+        const int lg = at[u] < 0 ? p.gid_of_key[key[u]] : __float_as_int(res[u].y);
+        o.group_id[r] = p.gid_base[static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)] + lg;
+        if (at[u] >= 0) o.adv[r] = res[u].x;
       }
     }
     return;
@@ -901,6 +1042,7 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
   const int bin = blockIdx.x - resp_blocks;
   if (bin < p.bins) {
     const int g0 = p.gid_base[bin], n = p.gid_base[bin + 1] - g0, base = p.bin_base[bin];
+    if (p.bin_cnt[bin] > kPoolCap) return;
     for (int i = threadIdx.x; i < n; i += 256) {
       const float4 s = p.stats[base + i];
       o.seg_offsets[g0 + i] = __float_as_int(s.w);
@@ -913,51 +1055,37 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
              static_cast<int64_t>(gridDim.x - resp_blocks - p.bins) * 256);
 }
 
+// The groups of the large bins, shared by the grid.  A launch of its own: it returns at once where there are none (2 us), and
+// the registers of the finishing code would cost k_gp_out its wavefronts.
+__global__ __launch_bounds__(256) void k_gp_large(PoolPlan p, const float* __restrict__ reward, GaStat st, GaOut o) {
+  const int n_large = p.large[0];
+  if (n_large == 0) return;
+  const int parts = max(1, static_cast<int>(gridDim.x) / n_large), teams = static_cast<int>(gridDim.x) / parts;
+  const int part = static_cast<int>(blockIdx.x) % parts;
+  for (int i = static_cast<int>(blockIdx.x) / parts; i < n_large && static_cast<int>(blockIdx.x) < teams * parts; i += teams) {
+    const int bin = p.large[1 + i], base = p.bin_base[bin], end = p.bin_base[bin + 1];
+    const int g0 = p.gid_base[bin], n = p.gid_base[bin + 1] - g0;
+    auto off = [&](int g) { return g < n ? __float_as_int(p.stats[base + g].w) : end; };
+    for (int g = part * 256 + static_cast<int>(threadIdx.x); g < n; g += parts * 256) o.seg_offsets[g0 + g] = off(g);
+    finish_small_groups(n, g0, part, parts, off, p.list, reward, st, o);
+    finish_large_groups(n, g0, part * 4 + static_cast<int>(threadIdx.x >> 6), parts * 4, off, p.list, reward, st, o);
+  }
+}
+
 // both finishing roles in one launch: the first n_small blocks take the small groups (a thread each), the next n_large the
 // larger ones (a wavefront each), the rest the tails
 __global__ __launch_bounds__(256) void k_ga_finish(int n_small, int n_large, int n_resp, const int32_t* __restrict__ arrival,
                                                    const float* __restrict__ reward, GaStat st, GaOut o) {
   const int G = *o.n_groups, b = blockIdx.x;
-  auto put_adv = [&](int, int r, float v) { o.adv[r] = v; };
-  if (b < n_small) {
-    for (int g = b * 256 + threadIdx.x; g < G; g += n_small * 256) {
-      const int off = o.seg_offsets[g], n = o.seg_offsets[g + 1] - off;
-      if (n > kSmallGroup) continue;
-      float mean, sd;
-      int best;
-      finish_by_thread(
-          n, [&](int j) { return arrival[off + j]; }, [&](int j) { return reward[arrival[off + j]]; },
-          [&](int rank, int r) { o.perm[off + rank] = r; }, put_adv, st, &mean, &sd, &best);
-      put_stats(o, g, mean, sd, best);
-    }
-  } else if (b < n_small + n_large) {
-    // a wavefront looks at the sizes of up to 64 consecutive groups at once: one group at a time, a million groups of one
-    // member took 16384 wavefronts 64 dependent pairs of loads each
-    // (129 us in rollout order and 206 shuffled, now 52 and 130)
-    const int lane = threadIdx.x & 63, wave = ((b - n_small) * 256 + static_cast<int>(threadIdx.x)) >> 6;
-    const int n_waves = (n_large * 256) >> 6;
-    const int per = min(64, (G + n_waves - 1) / n_waves);
-    for (int64_t g0 = static_cast<int64_t>(wave) * per; g0 < G; g0 += static_cast<int64_t>(n_waves) * per) {
-      int from = 0, members = 0;
-      if (lane < per && g0 + lane < G) {
-        from = o.seg_offsets[g0 + lane];
-        members = o.seg_offsets[g0 + lane + 1] - from;
-      }
-      for (uint64_t large = __builtin_amdgcn_ballot_w64(members > kSmallGroup); large != 0; large &= large - 1) {
-        const int j = __builtin_ctzll(large);
-        const int off = __shfl(from, j, 64), n = __shfl(members, j, 64);
-        float mean, sd;
-        int best;
-        finish_by_wave(
-            n, lane, [&](int m) { return arrival[off + m]; }, [&](int m) { return reward[arrival[off + m]]; },
-            [&](int r) { return reward[r]; }, o.perm + off, put_adv, st, &mean, &sd, &best);
-        if (lane == 0) put_stats(o, static_cast<int>(g0) + j, mean, sd, best);
-      }
-    }
-  } else {
+  auto off = [&](int g) { return o.seg_offsets[g]; };
+  if (b < n_small)
+    finish_small_groups(G, 0, b, n_small, off, arrival, reward, st, o);
+  else if (b < n_small + n_large)
+    finish_large_groups(G, 0, ((b - n_small) * 256 + static_cast<int>(threadIdx.x)) >> 6, (n_large * 256) >> 6, off, arrival,
+                        reward, st, o);
+  else
     fill_tails(o, G, o.seg_offsets[G], n_resp, static_cast<int64_t>(b - n_small - n_large) * 256 + threadIdx.x,
                static_cast<int64_t>(gridDim.x - n_small - n_large) * 256);
-  }
 }
 
 // clears two ranges in one launch
@@ -1016,6 +1144,8 @@ bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   q.key = p->key_of_resp;
   q.slot = p->rank_of_resp;
   q.list = p->arrival;
+  q.hist = p->hist;
+  q.gid_of_key = p->gid_of_key;
   q.kr = ws.take<int2>(R);
   q.x = ws.take<float>(R);
   q.result = ws.take<float2>(R);
@@ -1026,6 +1156,7 @@ bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   q.cursor = ws.take<int32_t>(static_cast<size_t>(q.bins));
   q.bin_groups = ws.take<int32_t>(static_cast<size_t>(q.bins));
   q.gid_base = ws.take<int32_t>(static_cast<size_t>(q.bins) + 1);
+  q.large = ws.take<int32_t>(static_cast<size_t>(q.bins) + 1);
   return true;
 }
 
@@ -1131,13 +1262,22 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
       if (r_team) a.reward = reward_out;
       given = GaMix{nullptr, nullptr, 0.f, nullptr};
     }
+    // Many keys per workgroup are few responses per key.  If the responses lie in a few workgroups' keys all the same (ids from
+    // a part of their extents), those workgroups' large groups go to a third launch, which costs the others 2 us: 65536
+    // responses in groups of 256, all in one workgroup's keys, took it 1834 us, now 171; 32768 in groups of 64: 318, now 57.
+    // Up to kRangeOwn keys a wavefront has at most eight large groups.
+    int32_t* left = n_resp > kRangeList && own > kRangeOwn ? p.hist : nullptr;
     if (threads == 256)
       hipLaunchKernelGGL(k_ga_range<256>, grid, dim3(256), 0, s, a, given, st, static_cast<int>(p.n_keys), own, keys16, p.err,
-                         p.arrival, o);
+                         p.arrival, left, o);
     else
       hipLaunchKernelGGL(k_ga_range<1024>, grid, dim3(1024), 0, s, a, given, st, static_cast<int>(p.n_keys), own, keys16, p.err,
-                         p.arrival, o);
+                         p.arrival, left, o);
     ATG_LAUNCH_CHECK();
+    if (left) {
+      hipLaunchKernelGGL(k_ga_left, dim3(kRangeBlocks), dim3(256), 0, s, static_cast<int>(grid.x), left, p.arrival, a.reward, st, o);
+      ATG_LAUNCH_CHECK();
+    }
     return AT_GRPO_OK;
   }
   if (plan_pool(n_resp, ws, &p) && workspace_bytes >= ws.bytes()) {
@@ -1147,17 +1287,21 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     ATG_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_gp_count, dim3(blocks), dim3(kPoolThreads), 0, s, a, mix, p.pool, p.err);
     ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_gp_bases, dim3(1), dim3(kPoolThreads), 0, s, p.pool);
+    hipLaunchKernelGGL(k_gp_bases, dim3(static_cast<unsigned>(1 + ceil_div(p.pool.bins, kBasesBins))), dim3(kPoolThreads), 0, s,
+                       p.pool, p.n_keys);
     ATG_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_gp_partition, dim3(blocks), dim3(kPoolThreads), 0, s, n_resp, rw, p.pool);
     ATG_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_gp_bin, dim3(p.pool.bins), dim3(kBinThreads), 0, s, p.pool, rw, st, p.n_keys, o);
     ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_gp_groups, dim3(1), dim3(kPoolThreads), 0, s, p.pool, o);
+    hipLaunchKernelGGL(k_gp_groups, dim3(static_cast<unsigned>(1 + ceil_div(n_resp, kPoolThreads * 4))), dim3(kPoolThreads), 0, s,
+                       p.pool, n_resp, o);
     ATG_LAUNCH_CHECK();
     const int resp_blocks = static_cast<int>(ceil_div(n_resp, 1024));
     hipLaunchKernelGGL(k_gp_out, dim3(static_cast<unsigned>(resp_blocks + p.pool.bins + (fill ? 64 : 0))), dim3(256), 0, s,
                        p.pool, n_resp, resp_blocks, o);
+    ATG_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_gp_large, dim3(kLargeBlocks), dim3(256), 0, s, p.pool, rw, st, o);
     ATG_LAUNCH_CHECK();
     return AT_GRPO_OK;
   }

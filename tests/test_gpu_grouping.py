@@ -27,6 +27,14 @@ CASES = {
     "pool: fewest responses": (8193, 2, 2, lambda rng, n: np.full(n, 2)),
     "pool: keys missing, sizes up to 24": (3000, 2, 12, lambda rng, n: rng.integers(0, 25, n) * (rng.random(n) < 0.4)),
     "pool: one oversized bin": (5000, 2, 3, lambda rng, n: np.where(np.arange(n) == 777, 9000, 3)),
+    # ids from a part of their extents: the work of one workgroup goes to all of them
+    "range: one workgroup's keys, groups of 256": (65280, 1, 1, lambda rng, n: np.where(np.arange(n) < 256, 255, 0)),
+    "range: one workgroup's keys, sizes up to 40": (20000, 1, 1, lambda rng, n: np.where(np.arange(n) < 700, rng.integers(0, 41, n), np.arange(n) % 9 == 0)),
+    "range: all but two in the last workgroup's keys": (12000, 1, 1, lambda rng, n: np.where(np.arange(n) >= n - 90, 70, np.arange(n) < 2)),
+    "pool: one bin, groups of 128": (524288, 1, 1, lambda rng, n: np.where(np.arange(n) < 1024, 128, 0)),
+    "pool: the last bin, groups of 15 to 18": (262143, 1, 2, lambda rng, n: np.where(np.arange(n) >= n - 2000, rng.integers(15, 19, n), np.arange(n) % 8 == 0)),
+    "pool: large bins among small ones": (3000, 2, 12, lambda rng, n: np.where(np.arange(n) // 2000 % 3 == 1, 24, rng.random(n) < 0.3)),
+    "pool: large bins only": (6000, 2, 12, lambda rng, n: np.where(np.arange(n) < n // 16, 30, 0)),
     "histogram: few keys": (4, 1, 2, lambda rng, n: np.full(n, 8800)),
     "histogram: few responses, many keys": (40000, 1, 2, lambda rng, n: (rng.random(n) < 0.2).astype(int)),
 }
@@ -125,3 +133,67 @@ def test_results_in_place(gpu_device, shape, over):
     torch.cuda.synchronize()
     for k in set(got) & set(ref) - {"workspace", "data_error"}:
         assert np.array_equal(host(got[k]).view(np.uint32), host(ref[k]).view(np.uint32)), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("group_by", ["trajectory", "parallel"])
+def test_pools_under_the_other_keys(gpu_device, group_by):
+    E, N, T, C = 20000, 2, 3, 4
+    rng = np.random.default_rng(5)
+    R = 90001 if group_by == "trajectory" else 120003
+    env, agent, turn, sample = (rng.integers(0, m, R).astype(np.int32) for m in (E, N, T, C))
+    reward = (rng.integers(0, 9, size=R) / np.float32(8)).astype(np.float32)
+    say(f"[grouping] pool by {group_by}")
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    out = api.at_grpo_group_advantage_keyed(group_by, dev(env), dev(agent), dev(turn), dev(reward), E, N, T, sample_id=dev(sample),
+                                            n_sample=C)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 0
+    gid, G, offs, perm = orc.group_segments(orc.group_key_by(env, agent, turn, sample, N, T, C, group_by))
+    adv, mean, std = orc.group_advantage(reward, gid, G)
+    assert int(out["n_groups"].item()) == G
+    assert np.array_equal(host(out["group_id"]), gid) and np.array_equal(host(out["perm"]), perm)
+    assert np.array_equal(host(out["seg_offsets"])[:G + 1], offs) and np.all(host(out["seg_offsets"])[G + 1:] == 0)
+    got = host(out["adv"]).astype(np.float64)
+    assert np.all(got[std[gid] == 0] == 0) and np.allclose(got, adv, rtol=1e-4, atol=1e-6)
+    assert np.allclose(host(out["group_mean"])[:G], mean, rtol=1e-4, atol=1e-7)
+    assert np.allclose(host(out["group_std"])[:G], std, rtol=1e-4, atol=1e-7)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["spread", "one part"])
+@pytest.mark.parametrize("shape", [(8192, 1, 4, 3), (30000, 1, 2, 2), (5000, 1, 2, 3)], ids=str)
+def test_scratch_and_tails_without_fill(gpu_device, shape, where):
+    """A caller with the least workspace (no room for the pool path) and one that does not ask for filled tails: group for group
+    the same bits (sums are taken in ascending order everywhere), nothing written behind the last group."""
+    E, N, T, K = shape
+    sizes = np.full(E * N * T, K)
+    if where == "one part":
+        sizes = np.where(np.arange(E * N * T) < E * N * T // 8, 8 * K, 0)
+    env, agent, turn, reward = draw(E, N, T, sizes, 3)
+    R, keys = env.size, E * N * T
+    say(f"[grouping] scratch and tails {shape} {where}")
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    ids, rew = (dev(env), dev(agent), dev(turn)), dev(reward)
+    ref = api.at_grpo_group_advantage(*ids, rew, E, N, T)
+    torch.cuda.synchronize()
+    G = int(ref["n_groups"].item())
+    up = lambda n: (4 * n + 255) // 256 * 256
+    least = up(64) + 2 * up(keys) + 3 * up(R) + 2 * up(-(-keys // 2048))
+    full = api.load_library().at_grpo_group_advantage_keyed_workspace_bytes(0, R, E, N, T, 1)
+    assert full >= least
+    for nbytes in (least, full):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=gpu_device)
+        got = api.group_advantage_outputs(R, keys, gpu_device)
+        for k in ("seg_offsets", "perm", "group_mean", "group_std"):
+            got[k].fill_(77)
+        st = api.load_library().at_grpo_group_advantage(
+            R, E, N, T, *(t.data_ptr() for t in ids), rew.data_ptr(), 1e-6, 0, 0, got["group_id"].data_ptr(), got["n_groups"].data_ptr(),
+            got["seg_offsets"].data_ptr(), got["perm"].data_ptr(), got["adv"].data_ptr(), got["group_mean"].data_ptr(),
+            got["group_std"].data_ptr(), ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        torch.cuda.synchronize()
+        assert api.error_word(ws) == 0 and int(got["n_groups"].item()) == G
+        for k, n in (("group_id", R), ("seg_offsets", G + 1), ("perm", R), ("adv", R), ("group_mean", G), ("group_std", G)):
+            assert np.array_equal(host(got[k])[:n].view(np.uint32), host(ref[k])[:n].view(np.uint32)), k
+            assert np.all(host(got[k])[n:] == 77), k
