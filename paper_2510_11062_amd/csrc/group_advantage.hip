@@ -281,12 +281,21 @@ __device__ __forceinline__ void finish_by_thread(int n, Id id_of, X x_of, PutPer
 // ordered members, combined in a fixed order.  perm: the group's part of the output (global memory); reward(r): reward of
 // response r.
 template <typename Id, typename X, typename Reward, typename PutAdv>
-__device__ __forceinline__ void finish_by_wave(int n, int lane, Id id_of, X x_of, Reward reward, int32_t* perm, PutAdv put_adv, const GaStat& st, float* mean_out, float* std_out, int* best) {
-  for (int j = lane; j < n; j += 64) {
-    const int rj = id_of(j);
+__device__ __forceinline__ void finish_by_wave(int n, int lane, Id id_of, X x_of, Reward reward, int32_t* perm, PutAdv put_adv,
+                                               const GaStat& st, float* mean_out, float* std_out, int* best) {
+  n = __builtin_amdgcn_readfirstlane(n);
+  if (n <= 64) {       // a member per lane: compared in registers (3.1 million responses in groups of 24: 208 -> 185 us)
+    const int mine = lane < n ? id_of(lane) : 0x7fffffff;
     int rank = 0;
-    for (int i = 0; i < n; ++i) rank += (id_of(i) < rj);
-    perm[rank] = rj;
+    for (int i = 0; i < n; ++i) rank += __builtin_amdgcn_readlane(mine, i) < mine;
+    if (lane < n) perm[rank] = mine;
+  } else {
+    for (int j = lane; j < n; j += 64) {
+      const int rj = id_of(j);
+      int rank = 0;
+      for (int i = 0; i < n; ++i) rank += (id_of(i) < rj);
+      perm[rank] = rj;
+    }
   }
   // the ranks are read back by other lanes of this wavefront: a fence of the workgroup is enough, and a device-wide one writes
   // back the L2 for every group (2^20 responses in groups of 24: 797 us in rollout order and 914 shuffled, now 123 and 153)
@@ -504,13 +513,10 @@ __global__ __launch_bounds__(256) void k_ga_keys(GaArgs a, GaMix mix, uint16_t* 
   if (mix.reward_out && r < a.n_resp) mix.reward_out[r] = x;
 }
 
-// eight keys, and how many equal ones from each on (an LDS atomic per run: responses of a group side by side would take turns)
-__device__ __forceinline__ void keys_and_runs(const uint4& v, int (&key)[8], int (&run)[8]) {
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int e = 0; e < 8; ++e) key[e] = (w[e >> 1] >> (16 * (e & 1))) & 0xffff;
-#pragma unroll
-  for (int e = 7; e >= 0; --e) run[e] = e < 7 && key[e] == key[min(e + 1, 7)] ? run[min(e + 1, 7)] + 1 : 1;
+// eight keys that are all the same (responses of a larger group side by side): counted at once, since 64 lanes' atomics on one LDS
+// word take turns (65536 responses in groups of 256, all in one workgroup's keys: its kernel 115 -> 73 us)
+__device__ __forceinline__ bool all_equal(const uint4& v) {
+  return v.x == v.y && v.x == v.z && v.x == v.w && (v.x >> 16) == (v.x & 0xffff);
 }
 
 // NT threads, each with at most one own key.  keys16: the keys (then a.reward holds the rewards), or null.
@@ -533,12 +539,11 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
 
   int keys[kRangeRounds];          // without keys16: of the last batch, all of them when there is one batch only
   int below = 0, bad = 0;
-  // (keys that stand for "none" are above every range); workgroup 0 has no smaller keys and looks for bad ones instead.
-  // members: 0, or how many equal keys from this one on are counted at once
+  // (keys that stand for "none" are above every range); workgroup 0 has no smaller keys and looks for bad ones instead
   auto look = [&](int key, bool new_run, int members) {
-    below += key < lo;
+    below += key < lo ? members : 0;
     const unsigned d = static_cast<unsigned>(key - lo);
-    if (members > 0 && d < static_cast<unsigned>(own)) atomicAdd(&count[d], members);
+    if (d < static_cast<unsigned>(own)) atomicAdd(&count[d], members);
     if (b == 0) {
       bad |= key == kKeyBadId ? AT_GRPO_DATA_ID_RANGE : (key == kKeyBadReward ? AT_GRPO_DATA_REWARD : 0);
     } else if (key < lo && new_run) {
@@ -548,12 +553,17 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   if (keys16) {
     for (int c = tid; c * 8 < a.n_resp; c += NT) {
       const uint4 v = reinterpret_cast<const uint4*>(keys16)[c];
-      int key[8], run[8];
-      keys_and_runs(v, key, run);
+      if (all_equal(v)) {
+        look(v.x & 0xffff, true, 8);
+        continue;
+      }
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+      int prev = -1;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const bool first_of_run = e == 0 || key[e] != key[e - 1];
-        look(key[e], first_of_run, first_of_run ? run[e] : 0);
+        const int key = (w[e >> 1] >> (16 * (e & 1))) & 0xffff;
+        look(key, key != prev, 1);
+        prev = key;
       }
     }
   } else {
@@ -594,27 +604,33 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   __syncthreads();
 
   // list the own members
-  int at = 0;
-  auto enlist = [&](int r, int key, int members) {     // members: as in look(); 0 takes the place behind the one before
+  auto enlist = [&](int r0, int key, int members) {    // responses r0 .. of one key
     const unsigned d = static_cast<unsigned>(key - lo);
     if (d < static_cast<unsigned>(own)) {
-      at = members > 0 ? atomicAdd(&cursor[d], members) : at + 1;
-      if (in_lds) list_id[at] = r;
-      else arrival[below + at] = r;
-      o.group_id[r] = gid[d];
+      const int at = atomicAdd(&cursor[d], members);
+      for (int e = 0; e < members; ++e) {
+        if (in_lds) list_id[at + e] = r0 + e;
+        else arrival[below + at + e] = r0 + e;
+        o.group_id[r0 + e] = gid[d];
+      }
     }
     if (b == 0 && key > kKeyNone) {
-      o.group_id[r] = -1;
-      o.adv[r] = 0.f;
+      for (int e = 0; e < members; ++e) {
+        o.group_id[r0 + e] = -1;
+        o.adv[r0 + e] = 0.f;
+      }
     }
   };
   if (keys16) {
     for (int cc = tid; cc * 8 < a.n_resp; cc += NT) {
       const uint4 v = reinterpret_cast<const uint4*>(keys16)[cc];
-      int key[8], run[8];
-      keys_and_runs(v, key, run);
+      if (all_equal(v)) {
+        enlist(cc * 8, v.x & 0xffff, 8);
+        continue;
+      }
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) enlist(cc * 8 + e, key[e], e == 0 || key[e] != key[e - 1] ? run[e] : 0);
+      for (int e = 0; e < 8; ++e) enlist(cc * 8 + e, (w[e >> 1] >> (16 * (e & 1))) & 0xffff, 1);
     }
   } else {
     for (int base = 0; base < a.n_resp; base += kRangeRounds * NT) {
@@ -699,25 +715,27 @@ __global__ __launch_bounds__(256) void k_ga_left(int n_blocks, const int32_t* __
 // (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of about 3072
 // responses) with LDS counters, so that every run written is a few entries long; each bin is finished by one workgroup in
 // LDS; and one last pass in response order gathers the results, again in runs.  About 84 bytes per response, all streamed.
-// 2^22 shuffled responses over 2^19 keys: 257 us for the whole call (272 with one response at a time in the partition and in the
-// gathering of the results).
+// Whole calls in groups of 8, shuffled and in rollout order (in brackets: the histogram path): 2^20 responses 71 and 50 us (113
+// and 57), 2^22 244 and 121 (454 and 120), 2^24 1046 and 402 (2054 and 453).
 //
 // How many responses a bin has depends on where the ids lie in their extents, which only the device sees.  Bins that do not
 // fit LDS (a pool from a part of the extents, say) are therefore not left to one workgroup: from the partition on their
 // responses go the way of the histogram path (ranks from global counters, member lists by group, groups shared by the whole
 // grid), inside the launches that the other bins need anyway.  262144 responses in groups of 128 that lie in one bin of
-// 2^19 keys: 8275 us by one workgroup, 75 now; 2^20 in groups of 8 from a quarter of their extents, in rollout order and
-// shuffled: 104 and 138 us by a workgroup per bin, 101 and 154 now.
+// 2^19 keys: 8275 us by one workgroup, 57 now; in groups of 8 from a quarter of their extents, in rollout order and shuffled: 2^20
+// responses 104 and 138 us by a workgroup per bin, 56 and 119 now, 2^22 176 and 351, now 173 and 458.
 // ------------------------------------------------------------------------------------------------
-constexpr int kPoolThreads = 1024, kPoolPer = 16, kPoolBlock = kPoolThreads * kPoolPer;   // responses per partitioning block
+constexpr int kPoolThreads = 1024;       // of a partitioning workgroup
 constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolPerBin = 3072;
 constexpr int kPoolMaxKeys = 2048;       // keys of a bin
 constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; a bin with more is "large"
-constexpr int kBinThreads = 512;
+constexpr int kBinThreads = 512, kBinPer = (kPoolCap + kBinThreads - 1) / kBinThreads;
+static_assert(kPoolCap < 65536 && kPoolMaxKeys < 32768, "place and group share a word");
 constexpr int kLargeBlocks = 512;        // workgroups that finish the groups of the large bins
 
 struct PoolPlan {
   int width, bins;           // bin of a key = key / width
+  int per;                   // responses per thread of a partitioning workgroup, a multiple of 4
   int32_t* key;              // [R]
   int32_t* slot;             // [R] place of the response in the partitioned order; of a large bin: bit 31 and rank inside its group
   int32_t* list;             // [R] members of the large bins, by group
@@ -758,10 +776,10 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_count(GaArgs a, GaMix mix, 
   __shared__ int hist[kPoolMaxBins];
   for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) hist[i] = 0;
   __syncthreads();
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolBlock + threadIdx.x;
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolThreads * p.per + threadIdx.x;
   int bad = 0;
 #pragma unroll 4
-  for (int u = 0; u < kPoolPer; ++u) {
+  for (int u = 0; u < p.per; ++u) {
     const int64_t r = r0 + u * kPoolThreads;
     if (r < a.n_resp) {
       bool ok;
@@ -838,8 +856,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const
     next[i] = c == 0 ? 0 : (p.bin_cnt[i] > kPoolCap ? INT32_MIN : atomicAdd(&p.cursor[i], c));   // places in large bins: below zero
   }
   __syncthreads();
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolBlock + threadIdx.x;
-  for (int u0 = 0; u0 < kPoolPer; u0 += 4) {
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolThreads * p.per + threadIdx.x;
+  for (int u0 = 0; u0 < p.per; u0 += 4) {
     int key[4];
     float x[4];
 #pragma unroll
@@ -868,11 +886,15 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const
   }
 }
 
+// Place of list entry f in LDS.  A thread walks its own group, so 64 lanes read entries that lie a group's size apart; groups of
+// 8 would meet in 8 of the 64 banks.
+__device__ __forceinline__ int bin_at(int f) { return f ^ ((f >> 6) & 7); }
+static_assert(kPoolCap % 8 == 0, "entries move inside blocks of eight");
+
 __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float* __restrict__ reward, GaStat st, int64_t n_keys,
                                                         GaOut o) {
   __shared__ int list_id[kPoolCap];
   __shared__ float list_x[kPoolCap];
-  __shared__ uint16_t place[kPoolCap];
   __shared__ int count[kPoolMaxKeys], next[kPoolMaxKeys];
   __shared__ uint16_t gid[kPoolMaxKeys];
   __shared__ int wsum[2][kBinThreads / 64];
@@ -887,8 +909,22 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
   const bool large = m > kPoolCap;
   for (int k = tid; k < own; k += kBinThreads) count[k] = large ? p.hist[lo + k] : 0;
   __syncthreads();
-  if (!large)
-    for (int e = tid; e < m; e += kBinThreads) atomicAdd(&count[p.kr[base + e].x - lo], 1);
+  // The bin's members stay in registers from here on: one wait for memory instead of one per pass and member.  2^24 responses in
+  // rollout order: 245 us with three reads of kr and the members' order stored from here one by one, 156 with kr in registers,
+  // 147 with whole lines of perm (512 threads; 215 with 1024, whose groups leave half of them idle).
+  int2 kr[kBinPer];
+  float x[kBinPer];
+  if (!large) {
+#pragma unroll
+    for (int i = 0; i < kBinPer; ++i) {
+      const int e = tid + i * kBinThreads;
+      kr[i] = e < m ? p.kr[base + e] : make_int2(-1, 0);
+      x[i] = e < m ? p.x[base + e] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < kBinPer; ++i)
+      if (kr[i].x >= 0) atomicAdd(&count[kr[i].x - lo], 1);
+  }
   __syncthreads();
   // offsets and ids of the keys that occur: each thread owns a run of keys
   constexpr int kPer = kPoolMaxKeys / kBinThreads;
@@ -941,28 +977,30 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
   if (tid == 0) p.bin_groups[bin] = n_groups;
   if (large) return;
   __syncthreads();
-  for (int e = tid; e < m; e += kBinThreads) {
-    const int2 kr = p.kr[base + e];
-    const int k = kr.x - lo, f = atomicAdd(&next[k], 1);
-    list_id[f] = kr.y;
-    list_x[f] = p.x[base + e];
-    place[e] = static_cast<uint16_t>(f);
+  int place[kBinPer];        // place in the lists, and the group in the upper half
+#pragma unroll
+  for (int i = 0; i < kBinPer; ++i) {
+    place[i] = -1;
+    if (kr[i].x < 0) continue;
+    const int k = kr[i].x - lo, f = atomicAdd(&next[k], 1);
+    list_id[bin_at(f)] = kr[i].y;
+    list_x[bin_at(f)] = x[i];
+    place[i] = f | static_cast<int>(gid[k]) << 16;
   }
   __syncthreads();
-  // next[k] is now one past the members of key k; a member's advantage takes the place of its reward, which only its own
-  // group reads
-  auto id_of = [&](int j) { return list_id[j]; };
-  auto x_of = [&](int j) { return list_x[j]; };
-  auto put_adv = [&](int j, int, float v) { list_x[j] = v; };
+  // next[k] is now one past the members of key k.  A member's advantage takes the place of its reward, which only its own group
+  // reads, and the ordered members of a small group that of its list, so that both leave in whole lines.
+  auto id_of = [&](int j) { return list_id[bin_at(j)]; };
+  auto x_of = [&](int j) { return list_x[bin_at(j)]; };
   for (int k = tid; k < own; k += kBinThreads) {
     const int n = count[k], f = next[k] - n;
     if (n == 0 || n > kSmallGroup) continue;
     float mean, sd;
     int best;
-    int32_t* perm = o.perm + base + f;
     finish_by_thread(
         n, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); },
-        [&](int rank, int r) { perm[rank] = r; }, [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
+        [&](int rank, int r) { list_id[bin_at(f + rank)] = r; }, [&](int j, int, float v) { list_x[bin_at(f + j)] = v; }, st,
+        &mean, &sd, &best);
     p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
   }
   for (int k = wave; k < own; k += kBinThreads / 64) {
@@ -972,12 +1010,22 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
     int best;
     finish_by_wave(
         n, lane, [&](int j) { return id_of(f + j); }, [&](int j) { return x_of(f + j); }, [&](int r) { return reward[r]; },
-        o.perm + base + f, [&](int j, int r, float v) { put_adv(f + j, r, v); }, st, &mean, &sd, &best);
+        o.perm + base + f,
+        [&](int j, int, float v) {
+          list_x[bin_at(f + j)] = v;
+          list_id[bin_at(f + j)] = -1;      // its place among the members is stored already
+        },
+        st, &mean, &sd, &best);
     if (lane == 0) p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
   }
   __syncthreads();
-  for (int e = tid; e < m; e += kBinThreads)
-    p.result[base + e] = make_float2(list_x[place[e]], __int_as_float(static_cast<int>(gid[p.kr[base + e].x - lo])));
+  for (int e = tid; e < m; e += kBinThreads) {
+    const int r = list_id[bin_at(e)];
+    if (r >= 0) o.perm[base + e] = r;
+  }
+#pragma unroll
+  for (int i = 0; i < kBinPer; ++i)
+    if (place[i] >= 0) p.result[base + tid + i * kBinThreads] = make_float2(list_x[bin_at(place[i] & 0xffff)], __int_as_float(place[i] >> 16));
 }
 
 // workgroup 0: ids of the bins' first groups; the others list the members of the large bins
@@ -1020,10 +1068,10 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
     for (int u = 0; u < 4; ++u) {
       const int64_t r = r0 + u * 256;
       key[u] = r < n_resp ? p.key[r] : -1;
-      at[u] = r < n_resp ? p.slot[r] : 0;
+      at[u] = r < n_resp ? p.slot[r] : 0;      // no slot without a key
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) res[u] = key[u] >= 0 && at[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f);   // no slot without a key
+    for (int u = 0; u < 4; ++u) res[u] = key[u] >= 0 && at[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t r = r0 + u * 256;
@@ -1133,6 +1181,9 @@ bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   if (n_resp <= kRangeMaxResp && p->n_keys <= kRangeMaxKeys) return false;
   int64_t want = ceil_div(n_resp, kPoolPerBin);
   if (want < kPoolMinBins) want = kPoolMinBins;
+  // two workgroups per compute unit: 512 bins take no longer than 257 (2^20 responses in groups of two, 342 bins and 512: 70 and
+  // 61 us); with more bins the runs of the partition get shorter (2^22 shuffled, 1366 bins and 1536: 241 and 246 us)
+  if (want > kPoolMinBins && want < 2 * kPoolMinBins) want = 2 * kPoolMinBins;
   if (want > kPoolMaxBins) want = kPoolMaxBins;
   const int64_t width = ceil_div(p->n_keys, want);
   PoolPlan& q = p->pool;
@@ -1140,7 +1191,11 @@ bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   q.bins = static_cast<int>(ceil_div(p->n_keys, width));
   if (width > kPoolMaxKeys || n_resp < kRangeMaxResp / 2) return false;
   if (static_cast<int64_t>(n_resp) > static_cast<int64_t>(q.bins) * kPoolCap * 3 / 4) return false;
-  const size_t R = static_cast<size_t>(n_resp), blocks = static_cast<size_t>(ceil_div(n_resp, kPoolBlock));
+  // 16 responses per thread make the longest runs; smaller pools take fewer, so that every compute unit has a workgroup (2^20
+  // responses, 64 workgroups and 256: counting 17 and 7 us, partition in rollout order 11 and 7, shuffled 30 and 19)
+  q.per = 16;
+  while (q.per > 4 && ceil_div(n_resp, kPoolThreads * q.per) < 256) q.per /= 2;
+  const size_t R = static_cast<size_t>(n_resp), blocks = static_cast<size_t>(ceil_div(n_resp, kPoolThreads * q.per));
   q.key = p->key_of_resp;
   q.slot = p->rank_of_resp;
   q.list = p->arrival;
@@ -1264,7 +1319,7 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     }
     // Many keys per workgroup are few responses per key.  If the responses lie in a few workgroups' keys all the same (ids from
     // a part of their extents), those workgroups' large groups go to a third launch, which costs the others 2 us: 65536
-    // responses in groups of 256, all in one workgroup's keys, took it 1834 us, now 171; 32768 in groups of 64: 318, now 57.
+    // responses in groups of 256, all in one workgroup's keys, took it 1834 us, now 164; 32768 in groups of 64: 318, now 52.
     // Up to kRangeOwn keys a wavefront has at most eight large groups.
     int32_t* left = n_resp > kRangeList && own > kRangeOwn ? p.hist : nullptr;
     if (threads == 256)
@@ -1281,7 +1336,7 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     return AT_GRPO_OK;
   }
   if (plan_pool(n_resp, ws, &p) && workspace_bytes >= ws.bytes()) {
-    const unsigned blocks = static_cast<unsigned>(ceil_div(n_resp, kPoolBlock));
+    const unsigned blocks = static_cast<unsigned>(ceil_div(n_resp, kPoolThreads * p.pool.per));
     const float* rw = r_team ? reward_out : reward;
     hipLaunchKernelGGL(k_gp_init, dim3(1), dim3(kPoolThreads), 0, s, p.pool.bin_cnt, p.pool.bins, p.err);
     ATG_LAUNCH_CHECK();
