@@ -1,0 +1,127 @@
+"""Bad data and empty parts on both sides of the switch between the one-workgroup preparation of small batches and the general
+kernels: every error bit, zeros on the offending rows, everything else as the CPU oracle has it with those rows masked out (at
+the tolerances of tests/test_gpu_parity.py)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import at_grpo_oracle as orc
+from paper_2510_11062_amd import api, synth
+from tests import helpers
+from tests.gpu_case import DeviceCase, host
+from tests.test_gpu_onepass import check_step_against_oracle
+from tests.test_gpu_parity import assert_logp_close, say, tolerances
+
+SEQLENS, AGENTS, TOKENS = 8, 16, 4
+
+
+def build(dtype, E, device):
+    """E environments x 3 agents x 4 candidates (length 0 among them); agent 1 shares head 0, so head 1 is empty."""
+    cfg = replace(synth.CONFIGS["C1"], name=f"errors-{dtype}-{E}", dtype=dtype, H=32 if dtype == "f32" else 64, V=66, n_heads=3, E=E,
+                  N=3, T=1, K=4, len_lo=0, len_hi=14, padded=False, reward_kind="uniform", forced_equal_groups=2, old_sigma=0.02)
+    c = helpers.build_case(cfg, device=device)
+    st = c.st
+    st.head_of_agent[:] = [0, 0, 2]
+    c.resp_of_tok, c.head_of_tok = orc.token_heads(st.n_tok, st.cu_seqlens, st.agent_id, st.head_of_agent)
+    rng = np.random.default_rng(E)
+    mask = (rng.random(st.n_tok) < 0.8).astype(np.uint8)
+    mask[c.resp_of_tok == 5] = 0                       # a response without a participating row
+    st.mask = mask.copy()
+    c.token_id, c.old_logp = helpers.oracle_rollout_standin(c.hidden, c.W, None, c.head_of_tok, c.u, c.noise)
+    return cfg, c
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("agg", ["token_mean", "seq_mean_token_mean"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("E", [4, 92], ids=["small", "general"])       # 48 and 1104 responses (up to 1024 are small)
+@pytest.mark.parametrize("bad", ["nothing", "tokens", "agents", "lengths", "all"])
+def test_bad_data(gpu_device, E, dtype, bad, agg):
+    cfg, c = build(dtype, E, gpu_device)
+    st = c.st
+    say(f"[errors] {cfg.name} {bad} {agg}: {st.n_tok} rows")
+    token, cu, agent, head_of_agent = c.token_id.copy(), st.cu_seqlens.copy(), st.agent_id.astype(np.int32).copy(), st.head_of_agent
+    head_of_agent = np.array([*head_of_agent, 7], np.int32)              # a fourth agent, routed to a head that does not exist
+    out_rows = np.zeros(st.n_tok, bool)
+    want = 0
+    R = cu.size - 1
+    filled = np.nonzero(np.diff(st.cu_seqlens) > 1)[0]
+    if bad in ("tokens", "all"):
+        on = np.nonzero(st.mask)[0]
+        pick = on[[0, on.size // 2, -1]]
+        token[pick] = [cfg.V, -1, 2 ** 31 - 1]
+        token[np.nonzero(st.mask == 0)[0][:2]] = -5                        # masked rows may hold anything
+        out_rows[pick] = True
+        want |= TOKENS
+    if bad in ("agents", "all"):
+        for r, a in zip(filled[[1, 7, filled.size // 2]], (-1, 4, 3)):
+            agent[r] = a
+            out_rows[c.resp_of_tok == r] = True
+        want |= AGENTS
+    if bad in ("lengths", "all"):
+        k = int(filled[filled.size // 3])                                    # responses k - 1 and k lose their common bound
+        cu[k] = -1
+        cu[R] = st.n_tok + 5                                                 # and the last one its end
+        for r in (k - 1, k, R - 1):
+            out_rows[c.resp_of_tok == r] = True
+        want |= SEQLENS
+    st.mask = np.where(out_rows, 0, st.mask).astype(np.uint8)
+    ref = helpers.oracle_bwd(c, agg=agg)
+    assert ref["n_valid"][1] == 0 and ref["n_valid"][0] > 0 and ref["n_valid"][2] > 0
+    dc = DeviceCase(c, gpu_device, token_id=token)
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    dc.cu, dc.resp_agent, dc.head_of_agent = dev(cu), dev(agent), dev(head_of_agent)
+    if bad != "nothing":        # the rows are to drop out by their data, not by the mask
+        dc.mask = dev(np.where(out_rows, 1, st.mask).astype(np.uint8))
+    tol = tolerances(cfg)
+    eps = cfg.eps_clip
+
+    def buffers():              # rows of a response without bounds belong to none: their flags are not written
+        z = lambda n, t: torch.zeros(n, dtype=t, device=gpu_device)
+        out = dict(loss=z(3, torch.float32), logp=z(st.n_tok, torch.float32), lse=z(st.n_tok, torch.float32),
+                   clip_mask=z(st.n_tok, torch.uint8), n_valid=z(3, torch.int32))
+        out["logp"].fill_(7)
+        out["lse"].fill_(7)
+        return out
+
+    lp = api.at_grpo_token_logprob(dc.batch())
+    torch.cuda.synchronize()
+    assert api.error_word(lp["workspace"]) == want
+    assert_logp_close(host(lp["logp"]), ref["logp"], tol, "logp")
+    assert np.all(host(lp["logp"])[ref["w"] == 0] == 0)
+    ent = api.at_grpo_token_entropy(dc.batch())
+    torch.cuda.synchronize()
+    assert api.error_word(ent["workspace"]) == want and np.all(host(ent["entropy"])[ref["w"] == 0] == 0)
+
+    fwd = api.at_grpo_policy_loss_fwd(dc.batch(), dc.old_logp, dc.adv, eps, eps, agg=agg, out=buffers())
+    torch.cuda.synchronize()
+    assert api.error_word(fwd["workspace"]) == want
+    bwd = api.at_grpo_policy_loss_bwd(dc.batch(), dc.old_logp, dc.adv, fwd["logp"], fwd["lse"], eps, eps, agg=agg)
+    torch.cuda.synchronize()
+    assert api.error_word(bwd["workspace"]) == want
+    check_step_against_oracle(dict(fwd, d_hidden=bwd["d_hidden"], dW=bwd["dW"]), ref, c, cfg, tol, f"{bad}, two calls")
+    assert float(fwd["loss"][1]) == 0 and float(bwd["dW"][1].abs().max()) == 0
+
+    step = api.at_grpo_policy_loss_fwd_bwd(dc.batch(), dc.old_logp, dc.adv, eps, eps, agg=agg, out=buffers())
+    torch.cuda.synchronize()
+    assert api.error_word(step["workspace"]) == want
+    check_step_against_oracle(step, ref, c, cfg, tol, f"{bad}, one call")
+    assert float(step["loss"][1]) == 0 and float(step["dW"][1].abs().max()) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("E", [4, 92], ids=["small", "general"])
+def test_nothing_takes_part(gpu_device, E, dtype):
+    cfg, c = build(dtype, E, gpu_device)
+    dc = DeviceCase(c, gpu_device)
+    dc.mask = torch.zeros_like(dc.mask)
+    say(f"[errors] {cfg.name}: all rows masked")
+    out = api.at_grpo_policy_loss_fwd_bwd(dc.batch(), dc.old_logp, dc.adv, cfg.eps_clip, cfg.eps_clip)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 0
+    for k in ("loss", "logp", "lse", "clip_mask", "n_valid", "d_hidden"):
+        assert float(out[k].abs().max()) == 0, k
+    assert all(float(g.abs().max()) == 0 for g in out["dW"])
