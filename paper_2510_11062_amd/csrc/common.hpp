@@ -138,23 +138,27 @@ __device__ __forceinline__ int block_sum_256_int(int v, int* lds4) {
   return lds4[0] + lds4[1] + lds4[2] + lds4[3];
 }
 
-// Exclusive scan of one int per thread over a 256-thread block; *total gets the block sum.
-__device__ __forceinline__ int block_exclusive_scan_256(int v, int* lds4, int* total) {
+// Exclusive scan of one int per thread over a block of NT threads; *total gets the block sum.  lds: NT / 64 words.
+template <int NT>
+__device__ __forceinline__ int block_exclusive_scan(int v, int* lds, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int incl = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    int up = __shfl_up(incl, o, 64);
+    const int up = __shfl_up(incl, o, 64);
     if (lane >= o) incl += up;
   }
   __syncthreads();
-  if (lane == 63) lds4[wave] = incl;
+  if (lane == 63) lds[wave] = incl;
   __syncthreads();
-  int base = 0;
+  int base = 0, sum = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w)
-    if (w < wave) base += lds4[w];
-  *total = lds4[0] + lds4[1] + lds4[2] + lds4[3];
+  for (int w = 0; w < NT / 64; ++w) {
+    const int t = lds[w];
+    if (w < wave) base += t;
+    sum += t;
+  }
+  *total = sum;
   return base + incl - v;
 }
 #endif  // __HIPCC__

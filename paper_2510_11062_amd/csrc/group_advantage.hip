@@ -135,8 +135,8 @@ __global__ __launch_bounds__(256) void k_ga_scan_top(int64_t n_blocks, int32_t* 
     const int vp = (b < n_blocks) ? bsum_p[b] : 0;
     const int vc = (b < n_blocks) ? bsum_c[b] : 0;
     int tp, tcn;
-    const int ep = block_exclusive_scan_256(vp, lds4, &tp);
-    const int ec = block_exclusive_scan_256(vc, lds4, &tcn);
+    const int ep = block_exclusive_scan<256>(vp, lds4, &tp);
+    const int ec = block_exclusive_scan<256>(vc, lds4, &tcn);
     if (b < n_blocks) {
       bsum_p[b] = run_p + ep;
       bsum_c[b] = run_c + ec;
@@ -167,8 +167,8 @@ __global__ __launch_bounds__(256) void k_ga_scan_apply(const int32_t* __restrict
     c += h[e];
   }
   int tp, tcn;
-  int gp = boff_p[blockIdx.x] + block_exclusive_scan_256(p, lds4, &tp);
-  int gc = boff_c[blockIdx.x] + block_exclusive_scan_256(c, lds4, &tcn);
+  int gp = boff_p[blockIdx.x] + block_exclusive_scan<256>(p, lds4, &tp);
+  int gc = boff_c[blockIdx.x] + block_exclusive_scan<256>(c, lds4, &tcn);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     if (h[e] > 0) {
@@ -450,30 +450,6 @@ __device__ __forceinline__ float reward_of(const GaArgs& a, const GaMix& mix, in
   if (!mix.r_team) return a.reward[r];
   const float prod = mix.alpha * mix.r_team[r];
   return prod + mix.r_loc[r];
-}
-
-// exclusive scan of one int per thread over the NT-thread workgroup; *total = sum
-template <int NT>
-__device__ __forceinline__ int block_exclusive_scan(int v, int* lds16, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int up = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += up;
-  }
-  __syncthreads();
-  if (lane == 63) lds16[wave] = incl;
-  __syncthreads();
-  int base = 0, sum = 0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    const int t = lds16[w];
-    if (w < wave) base += t;
-    sum += t;
-  }
-  *total = sum;
-  return base + incl - v;
 }
 
 // ------------------------------------------------------------------------------------------------

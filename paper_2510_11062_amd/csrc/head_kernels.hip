@@ -218,27 +218,6 @@ __global__ __launch_bounds__(256) void k_fallback_scale(const int32_t* __restric
 // run of consecutive rows; sums are taken in a fixed order, so the result does not change from run to run.
 constexpr int kPlanThreads = 1024;
 
-__device__ __forceinline__ int block_exclusive_scan_1024(int v, int* lds16, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int up = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += up;
-  }
-  __syncthreads();
-  if (lane == 63) lds16[wave] = incl;
-  __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kPlanThreads / 64; ++w) {
-    if (w < wave) base += lds16[w];
-    tot += lds16[w];
-  }
-  *total = tot;
-  return base + incl - v;
-}
-
 __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const int32_t* __restrict__ cnt, int c0, int TC,
                                                                const float* __restrict__ scale,
                                                                int32_t* __restrict__ perm, int32_t* __restrict__ holes,
@@ -253,7 +232,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const int32_t* __
   int c = 0;
   for (int j = j0; j < j1; ++j) c += (scale[j] != 0.f);
   int L;
-  const int before = block_exclusive_scan_1024(c, lds16, &L);   // live rows in front of this thread's run
+  const int before = block_exclusive_scan<kPlanThreads>(c, lds16, &L);   // live rows in front of this thread's run
   if (threadIdx.x == 0) live_below_L = L;                        // L == n: every row is live
   __syncthreads();
   if (j0 <= L && L < j1) {                                       // the thread that owns position L

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void k_scan_blocks(const int32_t* __restrict__
       const int64_t b = base + threadIdx.x;
       const int v = (b < n_blk) ? blk_cnt[m * n_blk + b] : 0;
       int tot;
-      const int ex = block_exclusive_scan_256(v, lds4, &tot);
+      const int ex = block_exclusive_scan<256>(v, lds4, &tot);
       if (b < n_blk) blk_off[m * n_blk + b] = running + ex;
       running += tot;
     }
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void k_scatter(const int32_t* __restrict__ fla
 #pragma unroll
     for (int e = 0; e < 8; ++e) c += (f[e] == m);
     int tot;
-    int pos = blk_off[m * n_blk + blockIdx.x] + block_exclusive_scan_256(c, lds4, &tot);
+    int pos = blk_off[m * n_blk + blockIdx.x] + block_exclusive_scan<256>(c, lds4, &tot);
     int32_t* out = idx + static_cast<int64_t>(m) * n_tok;
 #pragma unroll
     for (int e = 0; e < 8; ++e)
