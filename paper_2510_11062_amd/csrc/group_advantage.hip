@@ -463,7 +463,9 @@ __device__ __forceinline__ float reward_of(const GaArgs& a, const GaMix& mix, in
 constexpr int kRangeMaxResp = 65536, kRangeMaxKeys = 65528;
 constexpr int kRangeList = 4096;         // members listed in LDS; more go to global scratch
 constexpr int kRangeDirect = 4096;       // responses up to which every workgroup computes the keys itself
+constexpr int kRangeFew = 1024;          // responses up to which 256 threads do
 constexpr int kRangeRounds = 4;          // responses per thread whose ids are in flight together
+static_assert(kRangeFew <= kRangeRounds * 256 && kRangeDirect <= kRangeRounds * 1024, "the keys of all responses stay in registers");
 constexpr int kRangeOwn = 128;           // keys of a workgroup beyond which its list may be left to the whole grid
 constexpr int kRangeBlocks = 512;        // workgroups of such calls: 256 responses or 1024 keys each (more than kRangeOwn)
 static_assert(kRangeMaxKeys / kRangeOwn <= kRangeBlocks, "one word pair each");
@@ -513,7 +515,7 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   count[tid] = 0;
   __syncthreads();
 
-  int keys[kRangeRounds];          // without keys16: of the last batch, all of them when there is one batch only
+  int keys[kRangeRounds];          // without keys16
   int below = 0, bad = 0;
   // (keys that stand for "none" are above every range); workgroup 0 has no smaller keys and looks for bad ones instead
   auto look = [&](int key, bool new_run, int members) {
@@ -543,21 +545,19 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
       }
     }
   } else {
-    for (int base = 0; base < a.n_resp; base += kRangeRounds * NT) {
-      float x[kRangeRounds];
+    float x[kRangeRounds];
 #pragma unroll
-      for (int u = 0; u < kRangeRounds; ++u) {
-        const int r = base + u * NT + tid;
-        x[u] = 0.f;
-        keys[u] = r < a.n_resp ? key16(a, mix, r, &x[u]) : kKeyNone;
-      }
+    for (int u = 0; u < kRangeRounds; ++u) {
+      const int r = u * NT + tid;
+      x[u] = 0.f;
+      keys[u] = r < a.n_resp ? key16(a, mix, r, &x[u]) : kKeyNone;
+    }
 #pragma unroll
-      for (int u = 0; u < kRangeRounds; ++u) {
-        const int r = base + u * NT + tid;
-        if (mix.reward_out && r < a.n_resp && b == 0) mix.reward_out[r] = x[u];
-        const int prev = __shfl_up(keys[u], 1, 64);
-        look(keys[u], lane == 0 || prev != keys[u], 1);
-      }
+    for (int u = 0; u < kRangeRounds; ++u) {
+      const int r = u * NT + tid;
+      if (mix.reward_out && r < a.n_resp && b == 0) mix.reward_out[r] = x[u];
+      const int prev = __shfl_up(keys[u], 1, 64);
+      look(keys[u], lane == 0 || prev != keys[u], 1);
     }
   }
   __syncthreads();                 // every bit is set
@@ -609,15 +609,8 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
       for (int e = 0; e < 8; ++e) enlist(cc * 8 + e, (w[e >> 1] >> (16 * (e & 1))) & 0xffff, 1);
     }
   } else {
-    for (int base = 0; base < a.n_resp; base += kRangeRounds * NT) {
 #pragma unroll
-      for (int u = 0; u < kRangeRounds; ++u) {
-        const int r = base + u * NT + tid;
-        float x;
-        if (a.n_resp > kRangeRounds * NT) keys[u] = r < a.n_resp ? key16(a, mix, r, &x) : kKeyNone;   // else still in registers
-        enlist(r, keys[u], 1);
-      }
-    }
+    for (int u = 0; u < kRangeRounds; ++u) enlist(u * NT + tid, keys[u], 1);
   }
   __syncthreads();
   if (in_lds) {      // all rewards at once: one load latency instead of one per member met above
@@ -1280,7 +1273,7 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
       in_place = in_place || overlap(in, n_resp, n_groups, 1);
     }
     const bool direct = n_resp <= kRangeDirect && !in_place;
-    const int threads = n_resp <= 1024 ? 256 : 1024;
+    const int threads = n_resp <= kRangeFew ? 256 : 1024;
     const int64_t by_resp = ceil_div(n_resp, 256), by_keys = ceil_div(p.n_keys, threads);
     const int64_t blocks = by_resp > by_keys ? by_resp : by_keys;
     const int own = static_cast<int>(ceil_div(p.n_keys, blocks));
