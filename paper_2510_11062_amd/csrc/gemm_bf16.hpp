@@ -7,8 +7,8 @@
 //
 // MFMA shape.  v_mfma_f32_16x16x32_bf16, not 32x32x16: both deliver the same peak, but these kernels are bound by
 // power, and per multiply-add the 16x16x32 form moves half as many accumulator words through the register file.
-// The same loop with 32x32x16 sustains 1330-1370 TFLOP/s at 1.53 GHz (power-limited), with 16x16x32
-// 1520-1560 at 1.75-1.85 GHz (256 x 256 tiles, k = 2048 .. 151936).
+// On 256 x 256 tiles 32x32x16 gave 1360 TFLOP/s at 1.59 GHz (k = 2048, the logits) and 1310 at 1.44-1.54 (k = 151936,
+// dHidden); 16x16x32 gives 1427-1473 at 1.74-1.82 and 1477-1523 at 1.68-1.74 (five runs on four boxes).
 //
 // Data path: global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4, 16 bytes per lane) into a ring of five
 // 32 KiB slots (one operand panel each: all 160 KiB of a compute unit); LDS -> registers with ds_read_b128 (operands
@@ -57,7 +57,7 @@ struct Grid16 {
   static constexpr int kLoads = 32 / (WA * WB);                        // direct loads per operand, step and wavefront
   static constexpr int kMm = kIB * kJB, kRd = kIB + kJB;               // MFMAs and fragment reads per sub-step
   // a fragment read follows every kRdEvery-th MFMA: the last one must be early enough to land before the sub-step ends
-  // (4 wavefronts: every 3rd 1520-1560 TFLOP/s, every 4th 1475-1530)
+  // (4 wavefronts, same box: every 3rd 1494 TFLOP/s at k = 151936 and 1414 with a k-major operand, every 4th 1472 and 1377)
   static constexpr int kRdEvery = (kMm / kRd >= 4) ? kMm / kRd - 1 : kMm / kRd;
 };
 

@@ -404,10 +404,10 @@ __global__ __launch_bounds__(kTpThreads) void k_transpose_w(const bf16_t* __rest
 
 // ------------------------------------------------------------------------------------------------
 // dHidden: A = columns of W (h), B = dZ / E rows (tokens), k = vocabulary.
-// For many rows W is transposed first and both operands are contiguous along k (1500 TFLOP/s); for few rows the
-// contraction reads W as it stands, k-major (1430 TFLOP/s), and the transposition is saved.  Per weight the
-// transposition moves 4 bytes (0.9 ps of the chip's memory time), the slower loop costs 0.07 fs per row: the
-// two meet at 12 600 rows of a head.
+// For many rows W is transposed first and both operands are contiguous along k (1477-1523 TFLOP/s); for few rows the
+// contraction reads W as it stands, k-major (1404-1431 TFLOP/s on the same boxes), and the transposition is saved.  Per weight
+// the transposition takes 0.8 ps (H = 4096) to 1.1 ps (H = 2048) of the chip, the slower loop 0.07 to 0.085 fs per row:
+// the two meet between 9 000 and 16 000 rows of a head, and the line lies in the middle.
 // ------------------------------------------------------------------------------------------------
 constexpr int kUntransposedRows = 12288;
 
