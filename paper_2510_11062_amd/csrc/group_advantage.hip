@@ -469,6 +469,8 @@ static_assert(kRangeFew <= kRangeRounds * 256 && kRangeDirect <= kRangeRounds * 
 constexpr int kRangeOwn = 128;           // keys of a workgroup beyond which its list may be left to the whole grid
 constexpr int kRangeBlocks = 512;        // workgroups of such calls: 256 responses or 1024 keys each (more than kRangeOwn)
 static_assert(kRangeMaxKeys / kRangeOwn <= kRangeBlocks, "one word pair each");
+constexpr int kLeftBlocks = 128;         // workgroups that finish what others left: 512 wavefronts (with 512 workgroups the launch that
+                                         // finds nothing to do takes 4 us instead of 2)
 
 // key of a response in 16 bits, or why it has none
 enum : int { kKeyNone = 0xfffd, kKeyBadReward = 0xfffe, kKeyBadId = 0xffff };
@@ -692,7 +694,7 @@ __global__ __launch_bounds__(256) void k_ga_left(int n_blocks, const int32_t* __
 // responses go the way of the histogram path (ranks from global counters, member lists by group, groups shared by the whole
 // grid), inside the launches that the other bins need anyway.  262144 responses in groups of 128 that lie in one bin of
 // 2^19 keys: 8275 us by one workgroup, 57 now; in groups of 8 from a quarter of their extents, in rollout order and shuffled: 2^20
-// responses 104 and 138 us by a workgroup per bin, 56 and 119 now, 2^22 176 and 351, now 173 and 458.
+// responses 104 and 138 us by a workgroup per bin, 58 and 119 now, 2^22 176 and 351, now 148 and 449 (130 and 461 by histogram).
 // ------------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 1024;       // of a partitioning workgroup
 constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolPerBin = 3072;
@@ -700,7 +702,7 @@ constexpr int kPoolMaxKeys = 2048;       // keys of a bin
 constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; a bin with more is "large"
 constexpr int kBinThreads = 512, kBinPer = (kPoolCap + kBinThreads - 1) / kBinThreads;
 static_assert(kPoolCap < 65536 && kPoolMaxKeys < 32768, "place and group share a word");
-constexpr int kLargeBlocks = 512;        // workgroups that finish the groups of the large bins
+constexpr int kLargeBlocks = 1024;       // workgroups that finish the groups of the large bins (342 large bins: 148 us, with 512 170)
 
 struct PoolPlan {
   int width, bins;           // bin of a key = key / width
@@ -717,7 +719,7 @@ struct PoolPlan {
   int32_t* blk;              // [blocks][bins]
   int32_t* bin_cnt;          // [bins]
   int32_t* bin_base;         // [bins + 1]
-  int32_t* cursor;           // [bins]
+  int32_t* cursor;           // [bins] of a large bin: has it groups of more than kSmallGroup?
   int32_t* bin_groups;       // [bins]
   int32_t* gid_base;         // [bins + 1]
   int32_t* large;            // [bins + 1] number of large bins, then which ones they are
@@ -944,7 +946,14 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
     }
   }
   if (tid == 0) p.bin_groups[bin] = n_groups;
-  if (large) return;
+  if (large) {
+    bool wave_groups = false;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) wave_groups = wave_groups || c[e] > kSmallGroup;
+    const int any = __syncthreads_or(wave_groups);
+    if (tid == 0) p.cursor[bin] = any;
+    return;
+  }
   __syncthreads();
   int place[kBinPer];        // place in the lists, and the group in the upper half
 #pragma unroll
@@ -1077,15 +1086,19 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
 __global__ __launch_bounds__(256) void k_gp_large(PoolPlan p, const float* __restrict__ reward, GaStat st, GaOut o) {
   const int n_large = p.large[0];
   if (n_large == 0) return;
-  const int parts = max(1, static_cast<int>(gridDim.x) / n_large), teams = static_cast<int>(gridDim.x) / parts;
-  const int part = static_cast<int>(blockIdx.x) % parts;
-  for (int i = static_cast<int>(blockIdx.x) / parts; i < n_large && static_cast<int>(blockIdx.x) < teams * parts; i += teams) {
+  // the bins' first parts come first: consecutive workgroups, which the hardware deals to the XCDs in turn, have equal work
+  const int teams = min(n_large, static_cast<int>(gridDim.x)), parts = static_cast<int>(gridDim.x) / teams;
+  const int part = static_cast<int>(blockIdx.x) / teams;
+  if (part >= parts) return;
+  for (int i = static_cast<int>(blockIdx.x) % teams; i < n_large; i += teams) {
     const int bin = p.large[1 + i], base = p.bin_base[bin], end = p.bin_base[bin + 1];
     const int g0 = p.gid_base[bin], n = p.gid_base[bin + 1] - g0;
+    const bool wave_groups = p.cursor[bin] != 0;
+    if (part * 256 >= n && !wave_groups) continue;
     auto off = [&](int g) { return g < n ? __float_as_int(p.stats[base + g].w) : end; };
     for (int g = part * 256 + static_cast<int>(threadIdx.x); g < n; g += parts * 256) o.seg_offsets[g0 + g] = off(g);
     finish_small_groups(n, g0, part, parts, off, p.list, reward, st, o);
-    finish_large_groups(n, g0, part * 4 + static_cast<int>(threadIdx.x >> 6), parts * 4, off, p.list, reward, st, o);
+    if (wave_groups) finish_large_groups(n, g0, part * 4 + static_cast<int>(threadIdx.x >> 6), parts * 4, off, p.list, reward, st, o);
   }
 }
 
@@ -1299,7 +1312,8 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
                          p.arrival, left, o);
     ATG_LAUNCH_CHECK();
     if (left) {
-      hipLaunchKernelGGL(k_ga_left, dim3(kRangeBlocks), dim3(256), 0, s, static_cast<int>(grid.x), left, p.arrival, a.reward, st, o);
+      hipLaunchKernelGGL(k_ga_left, dim3(kLeftBlocks), dim3(256), 0, s, static_cast<int>(grid.x), left, p.arrival, a.reward, st,
+                         o);
       ATG_LAUNCH_CHECK();
     }
     return AT_GRPO_OK;
