@@ -469,8 +469,8 @@ static_assert(kRangeFew <= kRangeRounds * 256 && kRangeDirect <= kRangeRounds * 
 constexpr int kRangeOwn = 128;           // keys of a workgroup beyond which its list may be left to the whole grid
 constexpr int kRangeBlocks = 512;        // workgroups of such calls: 256 responses or 1024 keys each (more than kRangeOwn)
 static_assert(kRangeMaxKeys / kRangeOwn <= kRangeBlocks, "one word pair each");
-constexpr int kLeftBlocks = 128;         // workgroups that finish what others left: 512 wavefronts (with 512 workgroups the launch that
-                                         // finds nothing to do takes 4 us instead of 2)
+constexpr int kLeftBlocks = 128;         // workgroups that finish what others left (512: the launch that finds nothing to do takes
+                                         // 4 us instead of 2)
 
 // key of a response in 16 bits, or why it has none
 enum : int { kKeyNone = 0xfffd, kKeyBadReward = 0xfffe, kKeyBadId = 0xffff };
@@ -683,26 +683,28 @@ __global__ __launch_bounds__(256) void k_ga_left(int n_blocks, const int32_t* __
 
 // ------------------------------------------------------------------------------------------------
 // Pools.  A response needs four accesses at unrelated addresses if histogram, ranks, lists and results live in global memory
-// (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of about 3072
+// (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of 3072 to 4096
 // responses) with LDS counters, so that every run written is a few entries long; each bin is finished by one workgroup in
 // LDS; and one last pass in response order gathers the results, again in runs.  About 84 bytes per response, all streamed.
 // Whole calls in groups of 8, shuffled and in rollout order (in brackets: the histogram path): 2^20 responses 71 and 50 us (113
-// and 57), 2^22 244 and 121 (454 and 120), 2^24 1046 and 402 (2054 and 453).
+// and 57), 2^22 226 and 113 (454 and 120), 2^24 1043 and 401 (2054 and 453).
 //
 // How many responses a bin has depends on where the ids lie in their extents, which only the device sees.  Bins that do not
 // fit LDS (a pool from a part of the extents, say) are therefore not left to one workgroup: from the partition on their
 // responses go the way of the histogram path (ranks from global counters, member lists by group, groups shared by the whole
 // grid), inside the launches that the other bins need anyway.  262144 responses in groups of 128 that lie in one bin of
 // 2^19 keys: 8275 us by one workgroup, 57 now; in groups of 8 from a quarter of their extents, in rollout order and shuffled: 2^20
-// responses 104 and 138 us by a workgroup per bin, 58 and 119 now, 2^22 176 and 351, now 148 and 449 (130 and 461 by histogram).
+// responses 104 and 138 us by a workgroup per bin, 57 and 119 now, 2^22 176 and 351, now 131 and 437 (130 and 461 by histogram).
 // ------------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 1024;       // of a partitioning workgroup
-constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolPerBin = 3072;
+constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolRound = 512;
+constexpr int kPoolPerBin = 4096, kPoolFewPerBin = 3072;      // responses per bin
 constexpr int kPoolMaxKeys = 2048;       // keys of a bin
 constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; a bin with more is "large"
 constexpr int kBinThreads = 512, kBinPer = (kPoolCap + kBinThreads - 1) / kBinThreads;
 static_assert(kPoolCap < 65536 && kPoolMaxKeys < 32768, "place and group share a word");
-constexpr int kLargeBlocks = 1024;       // workgroups that finish the groups of the large bins (342 large bins: 148 us, with 512 170)
+constexpr int kLargeBlocks = 1024;       // workgroups that finish the groups of the large bins (2^22 responses in 342 large bins:
+                                         // 148 us, with 512 workgroups 170)
 
 struct PoolPlan {
   int width, bins;           // bin of a key = key / width
@@ -1003,7 +1005,8 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
   }
 #pragma unroll
   for (int i = 0; i < kBinPer; ++i)
-    if (place[i] >= 0) p.result[base + tid + i * kBinThreads] = make_float2(list_x[bin_at(place[i] & 0xffff)], __int_as_float(place[i] >> 16));
+    if (place[i] >= 0)
+      p.result[base + tid + i * kBinThreads] = make_float2(list_x[bin_at(place[i] & 0xffff)], __int_as_float(place[i] >> 16));
 }
 
 // workgroup 0: ids of the bins' first groups; the others list the members of the large bins
@@ -1161,22 +1164,28 @@ bool plan(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t n_turn, int32_
 // with bins, bins of too many keys, or so few keys that the bins overflow.
 bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   if (n_resp <= kRangeMaxResp && p->n_keys <= kRangeMaxKeys) return false;
-  int64_t want = ceil_div(n_resp, kPoolPerBin);
-  if (want < kPoolMinBins) want = kPoolMinBins;
-  // two workgroups per compute unit: 512 bins take no longer than 257 (2^20 responses in groups of two, 342 bins and 512: 70 and
-  // 61 us); with more bins the runs of the partition get shorter (2^22 shuffled, 1366 bins and 1536: 241 and 246 us)
-  if (want > kPoolMinBins && want < 2 * kPoolMinBins) want = 2 * kPoolMinBins;
+  // Whole rounds of two workgroups per compute unit: a bin takes as long as its members, a started round as long as a full one
+  // (2^22 responses in groups of 8, 1366 bins and 1024: in rollout order 120 and 113 us, environments shuffled 130 and 120, all
+  // shuffled 243 and 226; 2 million in groups of 24, 652 and 512: 156 and 127).  One workgroup per compute unit does up to
+  // 786432 (10^6 responses in groups of two, 256 bins and 512: 71 and 60).  More bins where so few would span too many keys.
+  int64_t want = ceil_div(n_resp, kPoolPerBin * kPoolRound) * kPoolRound, most = ceil_div(n_resp, kPoolFewPerBin);
+  if (most < kPoolMinBins) most = want = kPoolMinBins;
+  if (most > kPoolMaxBins) most = kPoolMaxBins;
   if (want > kPoolMaxBins) want = kPoolMaxBins;
+  // about a response per key: the histogram is as fast in any order (10^6 responses in groups of one: 51 us, 75 in bins)
+  if (ceil_div(p->n_keys, most) > kPoolMaxKeys) return false;
+  if (ceil_div(p->n_keys, want) > kPoolMaxKeys) want = most;
   const int64_t width = ceil_div(p->n_keys, want);
   PoolPlan& q = p->pool;
   q.width = static_cast<int>(width);
   q.bins = static_cast<int>(ceil_div(p->n_keys, width));
-  if (width > kPoolMaxKeys || n_resp < kRangeMaxResp / 2) return false;
+  if (n_resp < kRangeMaxResp / 2) return false;
   if (static_cast<int64_t>(n_resp) > static_cast<int64_t>(q.bins) * kPoolCap * 3 / 4) return false;
-  // 16 responses per thread make the longest runs; smaller pools take fewer, so that every compute unit has a workgroup (2^20
-  // responses, 64 workgroups and 256: counting 17 and 7 us, partition in rollout order 11 and 7, shuffled 30 and 19)
+  // 16 responses per thread make the longest runs; smaller pools take fewer, so that most compute units have a workgroup (2^20
+  // responses, 64 workgroups and 256: counting 17 and 7 us, partition in rollout order 11 and 7, shuffled 30 and 19).  Two and a
+  // half million, whole call with 153 and 306 workgroups: rollout order 87 and 81 us, shuffled 145 and 160.
   q.per = 16;
-  while (q.per > 4 && ceil_div(n_resp, kPoolThreads * q.per) < 256) q.per /= 2;
+  while (q.per > 4 && ceil_div(n_resp, kPoolThreads * q.per) < 144) q.per /= 2;
   const size_t R = static_cast<size_t>(n_resp), blocks = static_cast<size_t>(ceil_div(n_resp, kPoolThreads * q.per));
   q.key = p->key_of_resp;
   q.slot = p->rank_of_resp;
@@ -1273,19 +1282,22 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     // 1024: 12 / 13, 4096: 25 / 14; 65536 responses with a workgroup per 128 / 256 / 512: 49 / 31 / 32 us.
     // Where an output lies on an input (rewards mixed in place), one workgroup's results could reach another that still has
     // inputs to read: the keys then go through a launch of their own, behind which a reward is only read for its own group.
-    bool in_place = false;
-    for (const void* in : {static_cast<const void*>(env_id), static_cast<const void*>(agent_id), static_cast<const void*>(turn_id),
-                           static_cast<const void*>(sample_id), static_cast<const void*>(reward),
-                           static_cast<const void*>(r_team), static_cast<const void*>(r_loc)}) {
-      for (const void* out : {static_cast<const void*>(mix.reward_out), static_cast<const void*>(group_id),
-                              static_cast<const void*>(perm), static_cast<const void*>(adv)})
-        in_place = in_place || overlap(in, n_resp, out, n_resp);
-      for (const void* out : {static_cast<const void*>(group_mean), static_cast<const void*>(group_std),
-                              static_cast<const void*>(best), static_cast<const void*>(seg_offsets)})
-        in_place = in_place || overlap(in, n_resp, out, g_max + 1);
-      in_place = in_place || overlap(in, n_resp, n_groups, 1);
-    }
-    const bool direct = n_resp <= kRangeDirect && !in_place;
+    const auto in_place = [&] {
+      for (const void* in : {static_cast<const void*>(env_id), static_cast<const void*>(agent_id), static_cast<const void*>(turn_id),
+                             static_cast<const void*>(sample_id), static_cast<const void*>(reward),
+                             static_cast<const void*>(r_team), static_cast<const void*>(r_loc)}) {
+        if (!in) continue;
+        for (const void* out : {static_cast<const void*>(mix.reward_out), static_cast<const void*>(group_id),
+                                static_cast<const void*>(perm), static_cast<const void*>(adv)})
+          if (overlap(in, n_resp, out, n_resp)) return true;
+        for (const void* out : {static_cast<const void*>(group_mean), static_cast<const void*>(group_std),
+                                static_cast<const void*>(best), static_cast<const void*>(seg_offsets)})
+          if (overlap(in, n_resp, out, g_max + 1)) return true;
+        if (overlap(in, n_resp, n_groups, 1)) return true;
+      }
+      return false;
+    };
+    const bool direct = n_resp <= kRangeDirect && !in_place();
     const int threads = n_resp <= kRangeFew ? 256 : 1024;
     const int64_t by_resp = ceil_div(n_resp, 256), by_keys = ceil_div(p.n_keys, threads);
     const int64_t blocks = by_resp > by_keys ? by_resp : by_keys;

@@ -26,6 +26,9 @@ CASES = {
     "range: 4097 responses": (241, 1, 1, lambda rng, n: np.full(n, 17)),
     "pool: fewest responses": (8193, 2, 2, lambda rng, n: np.full(n, 2)),
     "pool: keys missing, sizes up to 24": (3000, 2, 12, lambda rng, n: rng.integers(0, 25, n) * (rng.random(n) < 0.4)),
+    "pool: the first with 512 bins": (49153, 2, 2, lambda rng, n: np.full(n, 4)),
+    "pool: bins of fewer responses for their keys": (525000, 2, 1, lambda rng, n: 1 + (np.arange(n) % 2)),
+    "histogram: as many keys as responses": (500000, 2, 1, lambda rng, n: np.ones(n, int)),
     "pool: one oversized bin": (5000, 2, 3, lambda rng, n: np.where(np.arange(n) == 777, 9000, 3)),
     # ids from a part of their extents: the work of one workgroup goes to all of them
     "range: one workgroup's keys, groups of 256": (65280, 1, 1, lambda rng, n: np.where(np.arange(n) < 256, 255, 0)),
