@@ -44,21 +44,26 @@ constexpr int kRingSlots = 5;
 constexpr int kRingSlot = kTile16 * kStepK * 2;   // 32 KiB: one operand panel of one step
 constexpr int kRingBytes = kRingSlots * kRingSlot;
 
-// How the wavefronts of a workgroup share the 256 x 256 tile: WA x WB of them, each owning (256 / WA) x (256 / WB).
+// How the wavefronts of a workgroup share the TA x TB tile: WA x WB of them, each owning (TA / WA) x (TB / WB).
 //   Grid16<4, 2> / <2, 4>  8 wavefronts, two per SIMD (128 accumulator registers): one covers part of the other's
 //                          per-tile prologue and epilogue; used where the k loop is short (k = H)
 //   Grid16<2, 2>           4 wavefronts, one per SIMD (256 accumulator registers): a third fewer LDS reads per MFMA and
 //                          half as many wavefronts at each barrier; 7 % faster on the long k loop of dHidden
-template <int WA, int WB>
+// Tiles of fewer than 256 rows of an operand still take a whole ring slot per panel.
+template <int WA, int WB, int TA = kTile16, int TB = kTile16>
 struct Grid16 {
   static constexpr int kWavesA = WA, kWavesB = WB, kThreads = WA * WB * 64;
-  static constexpr int kRowsA = kTile16 / WA, kRowsB = kTile16 / WB;   // rows of a wavefront's sub-tile
+  static constexpr int kTileA = TA, kTileB = TB;
+  static constexpr int kRowsA = TA / WA, kRowsB = TB / WB;             // rows of a wavefront's sub-tile
   static constexpr int kIB = kRowsA / 16, kJB = kRowsB / 16;           // accumulator blocks of a wavefront
-  static constexpr int kLoads = 32 / (WA * WB);                        // direct loads per operand, step and wavefront
+  static constexpr int kLoadsA = TA / 8 / (WA * WB);                   // direct loads per step and wavefront
+  static constexpr int kLoadsB = TB / 8 / (WA * WB);
   static constexpr int kMm = kIB * kJB, kRd = kIB + kJB;               // MFMAs and fragment reads per sub-step
   // a fragment read follows every kRdEvery-th MFMA: the last one must be early enough to land before the sub-step ends
   // (4 wavefronts, same box: every 3rd 1494 TFLOP/s at k = 151936 and 1414 with a k-major operand, every 4th 1472 and 1377)
   static constexpr int kRdEvery = (kMm / kRd >= 4) ? kMm / kRd - 1 : kMm / kRd;
+  static_assert(kRowsA % 16 == 0 && kRowsB % 16 == 0 && kLoadsA >= 1 && kLoadsB >= 1, "whole blocks, whole loads");
+  static_assert(kRdEvery >= 1 && (kRd - 1) * kRdEvery < kMm, "every fragment is read inside its sub-step");
 };
 
 __device__ __forceinline__ uint32_t lds_addr32(const char* p) {
@@ -108,19 +113,21 @@ __device__ __forceinline__ void wait_loads_but() {
 
 // Off: uint32_t where 256 rows of the operand (64 k-rows of a k-major one) lie within 4 GiB, else uint64_t (see wide_rows)
 
+// NL: direct loads of a wavefront per step (kLoadsA or kLoadsB of the grid)
+
 // rows contiguous along k
-template <typename G, typename Off = uint32_t>
+template <int NL, typename Off = uint32_t>
 struct RowPanel {
   static constexpr bool kKMajor = false;
   const char* base;
-  Off off[G::kLoads];
-  // row_off(row): byte offset of tile row `row` (0..255) from b
+  Off off[NL];
+  // row_off(row): byte offset of tile row `row` from b
   template <typename F>
   __device__ __forceinline__ void init(const char* b, int wave, int lane, F row_off) {
     base = uniform_ptr(b);
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) {
-      const int row = (wave * G::kLoads + q) * 8 + (lane >> 3);
+    for (int q = 0; q < NL; ++q) {
+      const int row = (wave * NL + q) * 8 + (lane >> 3);
       off[q] = row_off(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
   }
@@ -129,40 +136,39 @@ struct RowPanel {
 };
 
 // rows contiguous along k at arbitrary addresses (gathered rows)
-template <typename G>
+template <int NL>
 struct GatherPanel {
   static constexpr bool kKMajor = false;
-  const char* p[G::kLoads];
-  // row_ptr(row): address of tile row `row`
+  const char* p[NL];
+  // the tile row that load q fetches for this lane
+  static __device__ __forceinline__ int row(int q, int wave, int lane) { return (wave * NL + q) * 8 + (lane >> 3); }
+  // row_ptr(q): address of tile row row(q)
   template <typename F>
   __device__ __forceinline__ void init(int wave, int lane, F row_ptr) {
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) {
-      const int row = (wave * G::kLoads + q) * 8 + (lane >> 3);
-      p[q] = row_ptr(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
-    }
+    for (int q = 0; q < NL; ++q) p[q] = row_ptr(q) + (((lane & 7) ^ ((row(q, wave, lane) >> 1) & 7)) << 4);
   }
   __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load_v(p[q], lds); }
   __device__ __forceinline__ void advance() {
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) p[q] += kStepK * 2;
+    for (int q = 0; q < NL; ++q) p[q] += kStepK * 2;
   }
 };
 
 // k-major: k-row k at base + k * ld, 512 bytes of columns per row
-template <typename G, typename Off = uint32_t>
+template <int NL, typename Off = uint32_t>
 struct KMajorPanel {
   static constexpr bool kKMajor = true;
   const char* base;
-  Off off[G::kLoads];
+  Off off[NL];
   size_t step;
   // cmax: last 16-byte chunk (0..31) that may be read (chunks past it are fetched from it; the caller masks them)
   __device__ __forceinline__ void init(const char* b, int wave, int lane, size_t ld, int cmax) {
     base = uniform_ptr(b);
     step = ld * kStepK;
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) {
-      const int k = (wave * G::kLoads + q) * 2 + (lane >> 5);
+    for (int q = 0; q < NL; ++q) {
+      const int k = (wave * NL + q) * 2 + (lane >> 5);
       const int P = lane & 31, s = (k & 3) | (((k >> 3) & 1) << 2);
       const int C = (P & 16) | ((P ^ (2 * s)) & 15);
       off[q] = static_cast<Off>(k * ld) + min(C, cmax) * 16;
@@ -174,11 +180,11 @@ struct KMajorPanel {
 
 // k-major with a number of k-rows that need not be a multiple of 64: rows past the last are fetched from the last one (the
 // other operand is zero there)
-template <typename G, typename Off = uint32_t>
+template <int NL, typename Off = uint32_t>
 struct KMajorTailPanel {
   static constexpr bool kKMajor = true;
   const char* base;
-  Off off[G::kLoads];
+  Off off[NL];
   size_t ld;
   int rows, wave, lane, cmax;     // k-rows left from `base` on
   __device__ __forceinline__ void init(const char* b, int wave_, int lane_, size_t ld_, int cmax_, int rows_) {
@@ -192,8 +198,8 @@ struct KMajorTailPanel {
   }
   __device__ __forceinline__ void offsets() {
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) {
-      const int k = (wave * G::kLoads + q) * 2 + (lane >> 5);
+    for (int q = 0; q < NL; ++q) {
+      const int k = (wave * NL + q) * 2 + (lane >> 5);
       const int P = lane & 31, s = (k & 3) | (((k >> 3) & 1) << 2);
       const int C = (P & 16) | ((P ^ (2 * s)) & 15);
       off[q] = static_cast<Off>(max(min(k, rows - 1), 0) * ld) + min(C, cmax) * 16;
@@ -307,7 +313,7 @@ struct Gemm16 {
   PA& pa;
   PB& pb;
   const char* smem;
-  uint32_t wave_lds;
+  uint32_t lds_a, lds_b;      // where this wavefront's part of a panel lies in a slot
   FragReader<G::kIB, PA::kKMajor> ra;
   FragReader<G::kJB, PB::kKMajor> rb;
   uint4 fa[2][G::kIB], fb[2][G::kJB];
@@ -322,13 +328,13 @@ struct Gemm16 {
     else if (n <= G::kJB) fb[f][n - 1] = rb.read(smem, ks, n - 1);
     else fa[f][n - G::kJB] = ra.read(smem, ks, n - G::kJB);
   }
-  __device__ __forceinline__ void ld_a(int slot, int q) { pa.load(q, wave_lds + slot + q * 1024); }
-  __device__ __forceinline__ void ld_b(int slot, int q) { pb.load(q, wave_lds + slot + q * 1024); }
+  __device__ __forceinline__ void ld_a(int slot, int q) { pa.load(q, lds_a + slot + q * 1024); }
+  __device__ __forceinline__ void ld_b(int slot, int q) { pb.load(q, lds_b + slot + q * 1024); }
 
-  // REQUEST: step kt+2 exists.  (The fragments of step kt+1 are fetched whether it exists or not.)
-  template <bool REQUEST>
+  // REQUEST: step kt+2 exists; NEXT: step kt+1 does
+  template <bool REQUEST, bool NEXT>
   __device__ __forceinline__ void step(int first) {
-    constexpr int kMm = G::kMm, kRd = G::kRd, kEv = G::kRdEvery, kLd = G::kLoads;
+    constexpr int kMm = G::kMm, kRd = G::kRd, kEv = G::kRdEvery, kLa = G::kLoadsA, kLb = G::kLoadsB;
     const int la = ring_byte(first, 4), lb = ring_byte(first, 0);
 #pragma unroll
     for (int n = 0; n < kMm; ++n) {
@@ -340,8 +346,8 @@ struct Gemm16 {
       }
       if (REQUEST) {
 #pragma unroll
-        for (int k = 0; k < kLd; ++k)
-          if (load_after(k, kLd, kMm) == n) {
+        for (int k = 0; k < kLa; ++k)
+          if (load_after(k, kLa, kMm) == n) {
             ld_a(la, k);
             ATG_PIN16();
           }
@@ -349,26 +355,28 @@ struct Gemm16 {
     }
     if (REQUEST) {
       pa.advance();
-      wait_loads_but<kLd>();
+      wait_loads_but<kLa>();
     } else {
       wait_loads_but<0>();
     }
     __builtin_amdgcn_s_barrier();
     ATG_PIN16();
-    ra.slot(ring_byte(first, 2));
-    rb.slot(ring_byte(first, 3));
+    if (NEXT) {
+      ra.slot(ring_byte(first, 2));
+      rb.slot(ring_byte(first, 3));
+    }
 #pragma unroll
     for (int n = 0; n < kMm; ++n) {
       mm(1, n);
       ATG_PIN16();
-      if (n % kEv == 0 && n / kEv < kRd) {
+      if (NEXT && n % kEv == 0 && n / kEv < kRd) {
         rd(0, 0, n / kEv);
         ATG_PIN16();
       }
       if (REQUEST) {
 #pragma unroll
-        for (int k = 0; k < kLd; ++k)
-          if (load_after(k, kLd, kMm) == n) {
+        for (int k = 0; k < kLb; ++k)
+          if (load_after(k, kLb, kMm) == n) {
             ld_b(lb, k);
             ATG_PIN16();
           }
@@ -379,22 +387,33 @@ struct Gemm16 {
 
   __device__ __forceinline__ void request_step(int slot) {
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) ld_a(slot, q);
+    for (int q = 0; q < G::kLoadsA; ++q) ld_a(slot, q);
     pa.advance();
 #pragma unroll
-    for (int q = 0; q < G::kLoads; ++q) ld_b(slot + kRingSlot, q);
+    for (int q = 0; q < G::kLoadsB; ++q) ld_b(slot + kRingSlot, q);
     pb.advance();
   }
 
-  // the whole k loop over nk >= 0 steps
-  __device__ __forceinline__ void run(int nk) {
+  // Requests the first two of nk steps, into slots 0 to 3.  The last reads of a tile's panels lie in front of its final step's
+  // barrier, so the next tile's may be requested as soon as run() is through: they travel while the results leave.
+  __device__ __forceinline__ void begin(int nk) {
     if (nk > 0) request_step(0);
-    if (nk > 1) {
-      request_step(2 * kRingSlot);
-      wait_loads_but<2 * G::kLoads>();
-    } else {
-      wait_loads_but<0>();
-    }
+    if (nk > 1) request_step(2 * kRingSlot);
+  }
+
+  // acc = A B^T over nk >= 0 steps, of which begin() has requested the first two.  Every thread of the workgroup calls it.
+  // fetch(0) and fetch(1) stand in front of the last step but one and the last: what a caller loads there costs no registers
+  // in the loop and no wait behind it.
+  template <typename F>
+  __device__ __forceinline__ void run(int nk, F fetch) {
+#pragma unroll
+    for (int i = 0; i < G::kIB; ++i)
+#pragma unroll
+      for (int j = 0; j < G::kJB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+    if (nk > 1) wait_loads_but<G::kLoadsA + G::kLoadsB>();
+    else wait_loads_but<0>();
     __builtin_amdgcn_s_barrier();
     ra.slot(0);
     rb.slot(kRingSlot);
@@ -402,15 +421,19 @@ struct Gemm16 {
     for (int n = 0; n < G::kRd; ++n) rd(0, 0, n);
     int kt = 0, first = 0;
     for (; kt + 2 < nk; ++kt) {
-      step<true>(first);
+      step<true, true>(first);
       first += 2;
       if (first >= kRingSlots) first -= kRingSlots;
     }
-    for (; kt < nk; ++kt) {
-      step<false>(first);
+    fetch(0);
+    if (kt + 1 < nk) {
+      step<false, true>(first);
       first += 2;
       if (first >= kRingSlots) first -= kRingSlots;
     }
+    fetch(1);
+    if (nk > 0) step<false, false>(first);
+    mfma_settle<G>(acc);
   }
 };
 
@@ -431,24 +454,24 @@ struct Coord16 {
   __device__ __forceinline__ int b_row(int j) const { return wn * G::kRowsB + j * 16 + (lane & 15); }
 };
 
-// acc = A B^T over nk steps of 64 (nk may be 0).  Every thread of the workgroup calls it.  The last
-// LDS reads that matter lie in front of the final step's own barrier, so the whole ring may be reused at once.
+template <typename G, typename PA, typename PB>
+__device__ __forceinline__ Gemm16<G, PA, PB> make_gemm16(floatx4 (&acc)[G::kIB][G::kJB], PA& pa, PB& pb, char* smem,
+                                                         const Coord16<G>& co) {
+  const uint32_t lds = lds_addr32(smem);
+  Gemm16<G, PA, PB> g{acc, pa, pb, smem, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds + co.wave * G::kLoadsA * 1024)),
+                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds + co.wave * G::kLoadsB * 1024)), {}, {}, {}, {}};
+  g.ra.init(co.wm * G::kRowsA, co.lane);
+  g.rb.init(co.wn * G::kRowsB, co.lane);
+  return g;
+}
+
+// one tile on its own: acc = A B^T over nk steps of 64 (nk may be 0)
 template <typename G, typename PA, typename PB>
 __device__ __forceinline__ void gemm16(floatx4 (&acc)[G::kIB][G::kJB], PA& pa, PB& pb, int nk, char* smem,
                                        const Coord16<G>& co) {
-#pragma unroll
-  for (int i = 0; i < G::kIB; ++i)
-#pragma unroll
-    for (int j = 0; j < G::kJB; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-  Gemm16<G, PA, PB> g{acc, pa, pb, smem,
-                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds_addr32(smem) + co.wave * G::kLoads * 1024)),
-                      {}, {}, {}, {}};
-  g.ra.init(co.wm * G::kRowsA, co.lane);
-  g.rb.init(co.wn * G::kRowsB, co.lane);
-  g.run(nk);
-  mfma_settle<G>(acc);
+  auto g = make_gemm16<G>(acc, pa, pb, smem, co);
+  g.begin(nk);
+  g.run(nk, [](int) {});
 }
 
 }  // namespace atg

@@ -47,8 +47,8 @@ __global__ __launch_bounds__(G::kThreads) void k_probe(const char* __restrict__ 
     ord.decode(t, &ta, &tb);
     const Coord16<G> co;
     floatx4 acc[G::kIB][G::kJB];
-    typename std::conditional<AK, KMajorPanel<G>, RowPanel<G>>::type pa;
-    typename std::conditional<BK, KMajorPanel<G>, RowPanel<G>>::type pb;
+    typename std::conditional<AK, KMajorPanel<G::kLoadsA>, RowPanel<G::kLoadsA>>::type pa;
+    typename std::conditional<BK, KMajorPanel<G::kLoadsB>, RowPanel<G::kLoadsB>>::type pb;
     if constexpr (AK) pa.init(A + static_cast<size_t>(ta) * kTile16 * 2, co.wave, co.lane, lda, 31);
     else pa.init(A + static_cast<size_t>(ta) * kTile16 * lda, co.wave, co.lane, [&](int r) { return static_cast<uint32_t>(r * lda); });
     if constexpr (BK) pb.init(B + static_cast<size_t>(tb) * kTile16 * 2, co.wave, co.lane, ldb, 31);

@@ -49,68 +49,138 @@ __device__ __forceinline__ float across_groups_max(float x) {
   return fmaxf(x, __shfl_xor(x, 32, 64));
 }
 
-// logits tile: A = W rows (v0 ..), B = gathered hidden rows (list positions t0 ..).  Off: offsets inside an operand panel
-template <bool PERMUTED, typename Off>
-__device__ __forceinline__ void logit_tile(floatx4 (&acc)[GLogit::kIB][GLogit::kJB], const bf16_t* hidden, const bf16_t* W,
-                                           const int32_t* idx, int c0, int n, int v0, int t0, int H, int V, char* smem) {
-  const Coord16<GLogit> co;
-  const Off row_bytes = static_cast<Off>(H) * 2;
-  GatherPanel<GLogit> pb;
-  pb.init(co.wave, co.lane, [&](int row) {
-    const int tk = min(t0 + row, n - 1);
-    return reinterpret_cast<const char*>(hidden) + static_cast<size_t>(idx[c0 + tk]) * row_bytes;
-  });
-  RowPanel<GLogit, Off> pa;
-  pa.init(reinterpret_cast<const char*>(W) + static_cast<size_t>(v0) * row_bytes, co.wave, co.lane, [&](int row) {
-    return static_cast<Off>(min(PERMUTED ? a_index(row) : row, V - 1 - v0)) * row_bytes;
-  });
-  gemm16<GLogit>(acc, pa, pb, H / kStepK, smem, co);
+// A launch of logits tiles: A = W rows (v0 ..), B = gathered hidden rows (list positions t0 ..)
+struct LogitIn {
+  const bf16_t* hidden;
+  const bf16_t* W;
+  const int32_t* idx;      // of the launch's first list position
+  const int32_t* token_id;
+  int n, H, V;
+};
+
+// What the epilogue needs to know of a lane's tokens, one per accumulator block column: fetched behind the k loop's last
+// requests (list first, then what it points to), so it costs no registers in the loop and no wait
+// (columns past the end of the list repeat its last row)
+template <typename G>
+struct TokenCols {
+  int row[G::kJB], y[G::kJB];
+  __device__ __forceinline__ void rows(const LogitIn& in, int t0, const Coord16<G>& co) {
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) row[j] = in.idx[min(t0 + co.b_row(j), in.n - 1)];
+  }
+  __device__ __forceinline__ void targets(const LogitIn& in) {
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) y[j] = in.token_id[row[j]];
+  }
+};
+
+// The tiles it = first, first + gridDim.x, ... < end of one shape; place(it, &v0, &t0) says where a tile lies.  The next
+// tile's first two steps are requested in front of a tile's epilogue, whose LDS is the ring's last slot, and what the epilogue
+// has to look up is fetched beside the last two steps.  That takes 2 us of waiting from a tile of 50 to 100 us, and gives less,
+// since the clock falls as the matrix cores are busier: C2's step 393.6 -> 391.2 ms, entropy of 4700 rows at H = 2048
+// 4343 -> 4317 us, log-probabilities of 197 rows at H = 4096 381 -> 378.
+// Off: offsets inside an operand panel
+template <typename G, bool PERMUTED, typename Off, typename Place, typename Epilogue>
+__device__ __forceinline__ void logit_tiles(const LogitIn& in, int first, int end, Place place, char* smem, Epilogue epi) {
+  if (first >= end) return;
+  const int nk = in.H / kStepK;
+  const Off row_bytes = static_cast<Off>(in.H) * 2;
+  RowPanel<G::kLoadsA, Off> pa;
+  GatherPanel<G::kLoadsB> pb;
+  int rows[G::kLoadsB];
+  auto fetch_rows = [&](int t0) {
+    const Coord16<G> co;
+#pragma unroll
+    for (int q = 0; q < G::kLoadsB; ++q) rows[q] = in.idx[min(t0 + pb.row(q, co.wave, co.lane), in.n - 1)];
+  };
+  auto aim = [&](int v0) {
+    const Coord16<G> co;
+    pa.init(reinterpret_cast<const char*>(in.W) + static_cast<size_t>(v0) * row_bytes, co.wave, co.lane, [&](int row) {
+      return static_cast<Off>(min(PERMUTED ? a_index(row) : row, in.V - 1 - v0)) * row_bytes;
+    });
+    pb.init(co.wave, co.lane,
+            [&](int q) { return reinterpret_cast<const char*>(in.hidden) + static_cast<size_t>(rows[q]) * row_bytes; });
+  };
+  floatx4 acc[G::kIB][G::kJB];
+  auto g = make_gemm16<G>(acc, pa, pb, smem, Coord16<G>());
+  int v0, t0;
+  place(first, &v0, &t0);
+  fetch_rows(t0);
+  aim(v0);
+  g.begin(nk);
+  for (int it = first;;) {
+    const int next = it + static_cast<int>(gridDim.x);
+    int vn = 0, tn = 0;
+    if (next < end) place(next, &vn, &tn);
+    TokenCols<G> cols;
+    typename Epilogue::template Fetched<G> more;
+    g.run(nk, [&](int stage) {
+      const Coord16<G> co;
+      if (stage == 0) {
+        if (next < end) fetch_rows(tn);
+        cols.rows(in, t0, co);
+      } else {
+        cols.targets(in);
+        epi.fetch(more, cols, in, t0, co);
+      }
+    });
+    if (next < end) {
+      aim(vn);
+      g.begin(nk);
+    }
+    epi.template finish<G>(acc, cols, more, v0, t0, in, smem + (kRingSlots - 1) * kRingSlot);
+    if (next >= end) break;
+    it = next;
+    v0 = vn;
+    t0 = tn;
+  }
+}
+
+// All tiles of a launch: whole tiles first, then the column of the tokens that do not fill one
+template <bool PERMUTED, typename Off, typename Epilogue>
+__device__ __forceinline__ void logit_launch(const LogitIn& in, int n_vtiles, char* smem, Epilogue epi) {
+  const TileOrder ord{n_vtiles, (in.n + kTile16 - 1) / kTile16, 8};
+  logit_tiles<GLogit, PERMUTED, Off>(
+      in, logical_workgroup(), ord.total(),
+      [&](int it, int* v0, int* t0) {
+        int vt, tt;
+        ord.decode(it, &vt, &tt);
+        *v0 = vt * kTile16;
+        *t0 = tt * kTile16;
+      },
+      smem, epi);
 }
 
 // ------------------------------------------------------------------------------------------------
 // forward: per (vocabulary tile, token) maximum and sum of exponentials, and the target logit
 // ------------------------------------------------------------------------------------------------
 // ENT: also part_u, the partial sums of 2^(z log2e - m) * z that the entropy monitor needs (H = lse - E_p[z])
-template <bool ENT, typename Off>
-__global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
-    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, float* __restrict__ part_m,
-    float* __restrict__ part_s, float* __restrict__ part_u, float* __restrict__ zy, int H, int V, int TC, int n_vtiles,
-    const int32_t* __restrict__ gate) {
-  using G = GLogit;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  if (gate && *gate == 0) return;
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{n_vtiles, (n + kTile16 - 1) / kTile16, 8};
-  float* red_m = reinterpret_cast<float*>(smem);          // [kWavesA][256]
-  float* red_s = red_m + G::kWavesA * kTile16;
-  float* red_u = red_s + G::kWavesA * kTile16;
+template <bool ENT>
+struct FwdEpilogue {
+  float *part_m, *part_s, *part_u, *zy;
+  int TC;
 
-  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
-    int vt, tt;
-    ord.decode(t, &vt, &tt);
-    const int v0 = vt * kTile16, t0 = tt * kTile16;
-    int ycol[G::kJB];          // fetched in front of the k loop, used behind it
-    {
-      const Coord16<G> co;
-#pragma unroll
-      for (int j = 0; j < G::kJB; ++j) {
-        const int tcol = t0 + co.b_row(j);
-        ycol[j] = tcol < n ? token_id[idx[c0 + tcol]] : -1;
-      }
-    }
-    floatx4 acc[G::kIB][G::kJB];
-    logit_tile<false, Off>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+  template <typename G>
+  struct Fetched {};
+  template <typename G>
+  __device__ __forceinline__ void fetch(Fetched<G>&, const TokenCols<G>&, const LogitIn&, int, const Coord16<G>&) const {}
 
+  template <typename G>
+  __device__ __forceinline__ void finish(const floatx4 (&acc)[G::kIB][G::kJB], const TokenCols<G>& cols, const Fetched<G>&,
+                                         int v0, int t0, const LogitIn& in, char* lds) const {
+    constexpr int T = G::kTileB;
+    float* red_m = reinterpret_cast<float*>(lds);          // [kWavesA][T]
+    float* red_s = red_m + G::kWavesA * T;
+    float* red_u = red_s + G::kWavesA * T;
     const Coord16<G> co;
+    const int n = in.n;
     const int vbase = v0 + co.wm * G::kRowsA;
-    const int vrem = V - vbase;                       // vocabulary rows of this wavefront that exist (may be <= 0)
+    const int vrem = in.V - vbase;                    // vocabulary rows of this wavefront that exist (may be <= 0)
     const int vlane = 4 * (co.lane >> 4);             // first row of this lane inside a block
 #pragma unroll
     for (int j = 0; j < G::kJB; ++j) {
       const int tcol = t0 + co.b_row(j);
-      const int rel = ycol[j] - vbase;
+      const int rel = cols.y[j] - vbase;
       floatx4 col[G::kIB];
 #pragma unroll
       for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
@@ -139,9 +209,9 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
       sum = across_groups_sum(sum);
       if (ENT) usum = across_groups_sum(usum);
       if (co.lane < 16) {
-        red_m[co.wm * kTile16 + co.b_row(j)] = (mx == -INFINITY) ? -INFINITY : m2;
-        red_s[co.wm * kTile16 + co.b_row(j)] = sum;
-        if (ENT) red_u[co.wm * kTile16 + co.b_row(j)] = usum;
+        red_m[co.wm * T + co.b_row(j)] = (mx == -INFINITY) ? -INFINITY : m2;
+        red_s[co.wm * T + co.b_row(j)] = sum;
+        if (ENT) red_u[co.wm * T + co.b_row(j)] = usum;
       }
       // target logit: held by exactly one lane of one wavefront of one tile
       const bool hit = tcol < n && rel >= 0 && rel < G::kRowsA && ((rel >> 2) & 3) == (co.lane >> 4);
@@ -150,29 +220,44 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
         if (hit) zy[tcol] = zt;
       }
     }
-    // fold the wavefronts' shares of the tile: one (max, sum) per token and vocabulary tile
+    // fold the wavefronts' shares of the tile: one (max, sum) per token and vocabulary tile.  The buffers are free again
+    // behind the next tile's first barrier.
     lds_barrier();
-    const int tl = threadIdx.x;
-    if (tl < kTile16 && t0 + tl < n) {
+    const int tl = co.wave * 64 + co.lane;
+    if (tl < T && t0 + tl < n) {
       float M = -INFINITY;
 #pragma unroll
-      for (int q = 0; q < G::kWavesA; ++q) M = fmaxf(M, red_m[q * kTile16 + tl]);
+      for (int q = 0; q < G::kWavesA; ++q) M = fmaxf(M, red_m[q * T + tl]);
       float S = 0.f, U = 0.f;
 #pragma unroll
       for (int q = 0; q < G::kWavesA; ++q) {
-        const float mq = red_m[q * kTile16 + tl];
+        const float mq = red_m[q * T + tl];
         if (mq != -INFINITY) {
           const float sc = fast_exp2(mq - M);
-          S += red_s[q * kTile16 + tl] * sc;
-          if (ENT) U += red_u[q * kTile16 + tl] * sc;
+          S += red_s[q * T + tl] * sc;
+          if (ENT) U += red_u[q * T + tl] * sc;
         }
       }
-      part_m[static_cast<size_t>(vt) * TC + t0 + tl] = M;
-      part_s[static_cast<size_t>(vt) * TC + t0 + tl] = S;
-      if (ENT) part_u[static_cast<size_t>(vt) * TC + t0 + tl] = U;
+      const size_t at = static_cast<size_t>(v0 / kTile16) * TC + t0 + tl;
+      part_m[at] = M;
+      part_s[at] = S;
+      if (ENT) part_u[at] = U;
     }
-    lds_barrier();   // the fold buffers are free again; the stores above need not have landed
   }
+};
+
+template <bool ENT, typename Off>
+__global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
+    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, float* __restrict__ part_m,
+    float* __restrict__ part_s, float* __restrict__ part_u, float* __restrict__ zy, int H, int V, int TC, int n_vtiles,
+    const int32_t* __restrict__ gate) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (gate && *gate == 0) return;
+  const int n = chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  logit_launch<false, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V}, n_vtiles, smem,
+                           FwdEpilogue<ENT>{part_m, part_s, part_u, zy, TC});
 }
 
 // Stores eight consecutive bf16 outputs of a lane.
@@ -186,46 +271,38 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&d)[8]) {
 // columns V .. Vp and for the rows that pad the last tile); part_s[vt][j] = sum over the 256 vocabulary rows of tile vt;
 // zy[j] = target logit
 // ------------------------------------------------------------------------------------------------
-template <typename Off>
-__global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
-    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ c2,
-    bf16_t* __restrict__ E, float* __restrict__ part_s, float* __restrict__ zy, int H, int V, int Vp, int TC, int n_vtiles) {
-  using G = GLogit;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{n_vtiles, (n + kTile16 - 1) / kTile16, 8};
-  float* red_s = reinterpret_cast<float*>(smem);   // [kWavesA][256]
+struct FeEpilogue {
+  const float* c2;
+  bf16_t* E;
+  float *part_s, *zy;
+  int Vp, TC;
 
-  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
-    int vt, tt;
-    ord.decode(t, &vt, &tt);
-    const int v0 = vt * kTile16, t0 = tt * kTile16;
-    int ycol[G::kJB];          // fetched in front of the k loop, used behind it
-    float nc2col[G::kJB];
-    {
-      const Coord16<G> co;
+  template <typename G>
+  struct Fetched {
+    float nc2[G::kJB];
+  };
+  template <typename G>
+  __device__ __forceinline__ void fetch(Fetched<G>& f, const TokenCols<G>&, const LogitIn& in, int t0, const Coord16<G>& co) const {
 #pragma unroll
-      for (int j = 0; j < G::kJB; ++j) {
-        const int tcol = t0 + co.b_row(j);
-        ycol[j] = tcol < n ? token_id[idx[c0 + tcol]] : -1;
-        nc2col[j] = tcol < n ? -c2[tcol] : 0.f;
-      }
-    }
-    floatx4 acc[G::kIB][G::kJB];
-    logit_tile<true, Off>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+    for (int j = 0; j < G::kJB; ++j) f.nc2[j] = -c2[min(t0 + co.b_row(j), in.n - 1)];
+  }
 
+  template <typename G>
+  __device__ __forceinline__ void finish(const floatx4 (&acc)[G::kIB][G::kJB], const TokenCols<G>& cols, const Fetched<G>& f,
+                                         int v0, int t0, const LogitIn& in, char* lds) const {
+    constexpr int T = G::kTileB;
+    float* red_s = reinterpret_cast<float*>(lds);   // [kWavesA][T]
     const Coord16<G> co;
+    const int n = in.n, V = in.V;
     const int vbase = v0 + co.wm * G::kRowsA;
     // tiles that lie fully inside the vocabulary and the token list need no per-element range checks
-    const bool interior = (v0 + kTile16 <= V) && (t0 + kTile16 <= n);
+    const bool interior = (v0 + G::kTileA <= V) && (t0 + T <= n);
 #pragma unroll
     for (int j = 0; j < G::kJB; ++j) {
       const int tcol = t0 + co.b_row(j);
       const bool live = tcol < n;
-      const int rel = ycol[j] - vbase;
-      const float nc2 = nc2col[j];
+      const int rel = cols.y[j] - vbase;
+      const float nc2 = f.nc2[j];
       const bool hit = live && rel >= 0 && rel < G::kRowsA && ((rel >> 3) & 3) == (co.lane >> 4);
       if (__builtin_amdgcn_ballot_w64(hit) != 0ull) {
         floatx4 col[G::kIB];
@@ -250,70 +327,66 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
         if (interior || vbase + vf < Vp) store8(row + vf, d);
       }
       sum = across_groups_sum(sum);
-      if (co.lane < 16) red_s[co.wm * kTile16 + co.b_row(j)] = sum;
+      if (co.lane < 16) red_s[co.wm * T + co.b_row(j)] = sum;
     }
-    lds_barrier();
-    const int tl = threadIdx.x;
-    if (tl < kTile16 && t0 + tl < n) {
+    lds_barrier();      // the sums are free again behind the next tile's first barrier
+    const int tl = co.wave * 64 + co.lane;
+    if (tl < T && t0 + tl < n) {
       float S = 0.f;
 #pragma unroll
-      for (int q = 0; q < G::kWavesA; ++q) S += red_s[q * kTile16 + tl];
-      part_s[static_cast<size_t>(vt) * TC + t0 + tl] = S;
+      for (int q = 0; q < G::kWavesA; ++q) S += red_s[q * T + tl];
+      part_s[static_cast<size_t>(v0 / kTile16) * TC + t0 + tl] = S;
     }
-    lds_barrier();   // the sums are free again; the stores may still fly
   }
+};
+
+template <typename Off>
+__global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
+    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ c2,
+    bf16_t* __restrict__ E, float* __restrict__ part_s, float* __restrict__ zy, int H, int V, int Vp, int TC, int n_vtiles) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int n = chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  logit_launch<true, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V}, n_vtiles, smem,
+                          FeEpilogue{c2, E, part_s, zy, Vp, TC});
 }
 
 // ------------------------------------------------------------------------------------------------
 // logit gradient with the logits recomputed (two-call path, and the fallback of the one-pass step):
 // dZ[t][v] = g_t ([v = y_t] - exp(z - lse_t)); without coefficients g = -1 (softmax - onehot)
 // ------------------------------------------------------------------------------------------------
-template <typename Off>
-__global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
-    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
-    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ lse,
-    const float* __restrict__ coef, bf16_t* __restrict__ dZ, int H, int V, int Vp, int TC, int n_vtiles,
-    const int32_t* __restrict__ gate) {
-  using G = GLogit;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  if (gate && *gate == 0) return;
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0) return;
-  const TileOrder ord{n_vtiles, (n + kTile16 - 1) / kTile16, 8};
+struct DzEpilogue {
+  const float *lse, *coef;
+  bf16_t* dZ;
+  int Vp;
 
-  for (int t = logical_workgroup(); t < ord.total(); t += gridDim.x) {
-    int vt, tt;
-    ord.decode(t, &vt, &tt);
-    const int v0 = vt * kTile16, t0 = tt * kTile16;
-    int ycol[G::kJB];          // fetched in front of the k loop, used behind it
-    float gcol[G::kJB], lcol[G::kJB];
-    {
-      const Coord16<G> co;
+  template <typename G>
+  struct Fetched {
+    float g[G::kJB], l[G::kJB];
+  };
+  template <typename G>
+  __device__ __forceinline__ void fetch(Fetched<G>& f, const TokenCols<G>& cols, const LogitIn&, int, const Coord16<G>&) const {
 #pragma unroll
-      for (int j = 0; j < G::kJB; ++j) {
-        const int tcol = t0 + co.b_row(j);
-        ycol[j] = -1;
-        gcol[j] = lcol[j] = 0.f;
-        if (tcol < n) {
-          const int row = idx[c0 + tcol];
-          ycol[j] = token_id[row];
-          gcol[j] = coef ? coef[row] : -1.f;
-          lcol[j] = lse[row];
-        }
-      }
+    for (int j = 0; j < G::kJB; ++j) {
+      f.g[j] = coef ? coef[cols.row[j]] : -1.f;
+      f.l[j] = lse[cols.row[j]];
     }
-    floatx4 acc[G::kIB][G::kJB];
-    logit_tile<true, Off>(acc, hidden, W, idx, c0, n, v0, t0, H, V, smem);
+  }
 
+  template <typename G>
+  __device__ __forceinline__ void finish(const floatx4 (&acc)[G::kIB][G::kJB], const TokenCols<G>& cols, const Fetched<G>& f,
+                                         int v0, int t0, const LogitIn& in, char*) const {
     const Coord16<G> co;
+    const int n = in.n, V = in.V;
     const int vbase = v0 + co.wm * G::kRowsA;
-    const bool interior = (v0 + kTile16 <= V) && (t0 + kTile16 <= n);
+    const bool interior = (v0 + G::kTileA <= V) && (t0 + G::kTileB <= n);
 #pragma unroll
     for (int j = 0; j < G::kJB; ++j) {
       const int tcol = t0 + co.b_row(j);
       const bool live = tcol < n;
-      const int rel = ycol[j] - vbase;
-      const float g = gcol[j], nl2 = -lcol[j] * kLog2e;
+      const int rel = cols.y[j] - vbase;
+      const float g = f.g[j], nl2 = -f.l[j] * kLog2e;
       bf16_t* row = dZ + static_cast<size_t>(tcol) * Vp + vbase;
 #pragma unroll
       for (int p = 0; p < G::kIB / 2; ++p) {
@@ -334,6 +407,19 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
       }
     }
   }
+};
+
+template <typename Off>
+__global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
+    const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ W, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int c0, const int32_t* __restrict__ token_id, const float* __restrict__ lse,
+    const float* __restrict__ coef, bf16_t* __restrict__ dZ, int H, int V, int Vp, int TC, int n_vtiles,
+    const int32_t* __restrict__ gate) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (gate && *gate == 0) return;
+  const int n = chunk_count(cnt, c0, TC);
+  if (n <= 0) return;
+  logit_launch<true, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V}, n_vtiles, smem, DzEpilogue{lse, coef, dZ, Vp});
 }
 
 // ---- partial tiles of a split contraction (split_k.hpp), in the accumulator layout of grid G -----------------------
@@ -487,17 +573,17 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
-      RowPanel<G, Off> pb;
+      RowPanel<G::kLoadsB, Off> pb;
       const size_t kb = static_cast<size_t>(k0) * kStepK * 2;
       pb.init(reinterpret_cast<const char*>(a.dZ) + static_cast<size_t>(t0) * row_bytes + kb, co.wave, co.lane,
               [&](int row) { return static_cast<Off>(row) * row_bytes; });
       if constexpr (T) {
-        RowPanel<G, Off> pa;
+        RowPanel<G::kLoadsA, Off> pa;
         pa.init(reinterpret_cast<const char*>(a.Wt) + static_cast<size_t>(h0) * row_bytes + kb, co.wave, co.lane,
                 [&](int row) { return static_cast<Off>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
         gemm16<G>(acc, pa, pb, nk, smem, co);
       } else {
-        KMajorTailPanel<G, Off> pa;
+        KMajorTailPanel<G::kLoadsA, Off> pa;
         pa.init(reinterpret_cast<const char*>(a.W + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
                 static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1), a.V - k0 * kStepK);
         gemm16<G>(acc, pa, pb, nk, smem, co);
@@ -608,7 +694,8 @@ __global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
     floatx4 acc[G::kIB][G::kJB];
     {
       const Coord16<G> co;
-      KMajorPanel<G, Off> pa, pb;
+      KMajorPanel<G::kLoadsA, Off> pa;
+      KMajorPanel<G::kLoadsB, Off> pb;
       pa.init(reinterpret_cast<const char*>(a.hG + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
               static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1));
       pb.init(reinterpret_cast<const char*>(a.dZ + static_cast<size_t>(k0) * kStepK * a.Vp + v0), co.wave, co.lane,
