@@ -3,6 +3,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "head_common.hpp"
 #include "head_kernels.hpp"
 #include "token_kernels.hpp"
 
@@ -176,7 +177,7 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
 
   if (call == AT_GRPO_CALL_TOKEN_LOGPROB || call == AT_GRPO_CALL_POLICY_LOSS_FWD ||
       call == AT_GRPO_CALL_TOKEN_ENTROPY) {
-    const size_t np = static_cast<size_t>(g.n_vtiles) * static_cast<size_t>(g.TC);
+    const size_t np = logit_part_floats(g.n_vtiles, g.TC);
     p->part_m = ws.take<float>(np);
     p->part_s = ws.take<float>(np);
     p->part_u = call == AT_GRPO_CALL_TOKEN_ENTROPY ? ws.take<float>(np) : nullptr;
@@ -194,7 +195,7 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
     p->gF = g;
     p->gF.TC = static_cast<int>(tc < kSubChunkTokens ? tc : kSubChunkTokens);
     const size_t rows = static_cast<size_t>(p->sub > p->gF.TC ? p->sub : p->gF.TC);   // rows of the largest launch
-    const size_t np = static_cast<size_t>(g.n_vtiles) * rows;
+    const size_t np = logit_part_floats(g.n_vtiles, static_cast<int64_t>(rows));
     p->part_m = ws.take<float>(np);
     p->part_s = ws.take<float>(np);
     p->part_u = nullptr;
@@ -473,8 +474,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
         // otherwise)
         ATG_TRY(launch_head_fwd(gs, sub, batch->hidden, batch->W[m], batch->token_id, p.part_m, p.part_s, nullptr,
                                 p.zy, s, gate));
-        ATG_TRY(launch_lse_combine(gs, sub, p.part_m, p.part_s, nullptr, p.zy, logp, lse, nullptr, s, gate));
-        ATG_TRY(launch_fallback_scale(gs, sub, m, ca, logp, scale_sub, gate, s));
+        ATG_TRY(launch_lse_combine(gs, sub, p.part_m, p.part_s, nullptr, p.zy, logp, lse, nullptr, s, gate, m, &ca, scale_sub));
         ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, nullptr, E_sub, s,
                                gate));
       }

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "gemm_bf16.hpp"
+#include "gemm_stream.hpp"
 #include "head_bf16.hpp"
 #include "head_common.hpp"
 #include "split_k.hpp"
@@ -18,6 +19,15 @@ namespace {
 // Short k loops (k = H) with a heavy epilogue: two wavefronts per SIMD, 128 vocabulary rows x 64 tokens each.  A token's
 // 128 logits of a wavefront are one 256-byte run of the stored exponentials.
 using GLogit = Grid16<2, 4>;
+// A half and a quarter of its tokens, for the last round of the persistent grid
+using GLogit128 = Grid16<4, 2, kTile16, 128>;
+using GLogit64 = Grid16<8, 1, kTile16, 64>;
+// Launches of few tokens (narrow_launch), on tiles of 128 vocabulary rows: twice as many tiles share out better where there
+// are few, and more steps fit the ring
+template <int T>
+using GNarrow = typename std::conditional<(T <= 128), Grid16<4, 2, kNarrowV, T>, Grid16<2, 4, kNarrowV, T>>::type;
+constexpr int narrow_depth(int T) { return T <= 64 ? 6 : T <= 128 ? 4 : 3; }    // steps in the ring
+constexpr int kFoldBytes = 4 * 256 * 3 * 4;     // [wavefronts along the vocabulary][tokens] x 3 behind the ring
 using GDh = Grid16<2, 2>;   // long k loop (k = V): one wavefront per SIMD
 using GDw = Grid16<4, 2>;
 
@@ -72,6 +82,10 @@ struct TokenCols {
 #pragma unroll
     for (int j = 0; j < G::kJB; ++j) y[j] = in.token_id[row[j]];
   }
+  __device__ __forceinline__ void settle() {
+#pragma unroll
+    for (int j = 0; j < G::kJB; ++j) asm volatile("" : "+v"(y[j]));
+  }
 };
 
 // The tiles it = first, first + gridDim.x, ... < end of one shape; place(it, &v0, &t0) says where a tile lies.  The next
@@ -124,6 +138,9 @@ __device__ __forceinline__ void logit_tiles(const LogitIn& in, int first, int en
         epi.fetch(more, cols, in, t0, co);
       }
     });
+    // here since the last step's barrier; a wait for them behind the requests would wait for those as well
+    cols.settle();
+    more.settle();
     if (next < end) {
       aim(vn);
       g.begin(nk);
@@ -136,12 +153,84 @@ __device__ __forceinline__ void logit_tiles(const LogitIn& in, int first, int en
   }
 }
 
-// All tiles of a launch: whole tiles first, then the column of the tokens that do not fill one
+// A launch of at most T tokens, as one stream of k-steps over this workgroup's vocabulary tiles.  Bound by memory: the weights
+// pass once, for little arithmetic.  V = 151936, 256 x 256 tiles before: 8 tokens at H = 4096 396 -> 240 us (5.2 TB/s), 100
+// and 150 tokens at H = 2048 199 -> 143 and 208 -> 164 us.  With 200 tokens the arithmetic is as long as the loads, and the
+// tiles of 256 x 256 are as fast (390 us at H = 4096, 405 as a stream).
+template <int T, bool PERMUTED, typename Epilogue>
+__device__ __forceinline__ void logit_stream(const LogitIn& in, char* smem, Epilogue epi) {
+  using G = GNarrow<T>;
+  using PA = RowPanel<G::kLoadsA>;
+  using PB = GatherPanel<G::kLoadsB>;
+  using S = Stream16<G, PA, PB, narrow_depth(T)>;
+  static_assert(G::kThreads == GLogit::kThreads && S::kBytes + kFoldBytes <= kRingBytes, "fits the launch");
+  const int nk = in.H / kStepK, grid = gridDim.x, first = logical_workgroup();
+  if (first * kNarrowV >= in.V) return;
+  const uint32_t row_bytes = static_cast<uint32_t>(in.H) * 2;
+  PA pa;
+  PB pb;
+  TokenCols<G> cols;
+  typename Epilogue::template Fetched<G> more;
+  {
+    const Coord16<G> co;
+    cols.rows(in, 0, co);
+    cols.targets(in);
+    epi.fetch(more, cols, in, 0, co);
+    // they have to be here before the stream starts: a wait for them behind it would wait for the stream as well
+    cols.settle();
+    more.settle();
+    pb.init(co.wave, co.lane, [&](int q) {
+      const int t = min(pb.row(q, co.wave, co.lane), in.n - 1);
+      return reinterpret_cast<const char*>(in.hidden) + static_cast<size_t>(in.idx[t]) * row_bytes;
+    });
+  }
+  auto aim = [&](int v0) {
+    const Coord16<G> co;
+    pa.init(reinterpret_cast<const char*>(in.W) + static_cast<size_t>(v0) * row_bytes, co.wave, co.lane, [&](int row) {
+      return static_cast<uint32_t>(min(PERMUTED ? a_index(row) : row, in.V - 1 - v0)) * row_bytes;
+    });
+  };
+  int v_req = first * kNarrowV, k_req = 0;      // of the step requested last
+  auto next = [&] {                             // (behind the last tile: that one again)
+    if (++k_req < nk) return;
+    k_req = 0;
+    if (v_req + grid * kNarrowV < in.V) v_req += grid * kNarrowV;
+    aim(v_req);
+#pragma unroll
+    for (int q = 0; q < G::kLoadsB; ++q) pb.p[q] -= row_bytes;
+  };
+  floatx4 acc[G::kIB][G::kJB];
+  S st(acc, pa, pb, smem, Coord16<G>());
+  aim(v_req);
+  st.begin(next);
+  for (int v0 = first * kNarrowV; v0 < in.V; v0 += grid * kNarrowV) {
+    st.clear();
+    for (int k = 0; k < nk; ++k) st.step(next);
+    epi.template finish<G>(acc, cols, more, v0, 0, in, smem + kRingBytes - kFoldBytes);
+  }
+  st.finish();
+}
+
+// All tiles of a launch.  Those that do not fill a round of the grid are cut into halves or quarters of their tokens if there
+// are workgroups for all of them: 594 tiles (the full vocabulary, up to 256 tokens) are two rounds and a half instead of three
+// (197 tokens at H = 4096 372 -> 346 us with the call's other kernels, 400 at H = 2048, 4.6 rounds, 345 -> 328).
 template <bool PERMUTED, typename Off, typename Epilogue>
 __device__ __forceinline__ void logit_launch(const LogitIn& in, int n_vtiles, char* smem, Epilogue epi) {
+  constexpr bool kCut = sizeof(Off) == 4;       // (not for vocabularies beyond 8.3 million)
+  if constexpr (kCut) {
+    if (narrow_launch(in.n)) {
+      if (in.n <= 64) logit_stream<64, PERMUTED>(in, smem, epi);
+      else if (in.n <= 128) logit_stream<128, PERMUTED>(in, smem, epi);
+      else logit_stream<192, PERMUTED>(in, smem, epi);
+      return;
+    }
+  }
   const TileOrder ord{n_vtiles, (in.n + kTile16 - 1) / kTile16, 8};
+  const int me = logical_workgroup(), grid = gridDim.x, rest = ord.total() % grid;
+  const int cuts = !kCut || rest * 2 > grid ? 1 : rest * 4 > grid ? 2 : 4;
+  const int whole = cuts == 1 ? ord.total() : ord.total() - rest;
   logit_tiles<GLogit, PERMUTED, Off>(
-      in, logical_workgroup(), ord.total(),
+      in, me, whole,
       [&](int it, int* v0, int* t0) {
         int vt, tt;
         ord.decode(it, &vt, &tt);
@@ -149,6 +238,26 @@ __device__ __forceinline__ void logit_launch(const LogitIn& in, int n_vtiles, ch
         *t0 = tt * kTile16;
       },
       smem, epi);
+  if constexpr (kCut) {
+    if (cuts == 1 || me >= rest * cuts) return;
+    int vt, tt;
+    ord.decode(whole + me / cuts, &vt, &tt);
+    const int t = tt * kTile16 + me % cuts * (kTile16 / cuts);
+    if (t >= in.n) return;
+    auto place = [&](int, int* v0, int* t0) {
+      *v0 = vt * kTile16;
+      *t0 = t;
+    };
+    lds_barrier();      // the whole tiles' epilogues are done with LDS
+    if (cuts == 2) logit_tiles<GLogit128, PERMUTED, Off>(in, 0, 1, place, smem, epi);
+    else logit_tiles<GLogit64, PERMUTED, Off>(in, 0, 1, place, smem, epi);
+  }
+}
+
+// Where the partial results of vocabulary tile v0 and token t of a launch are kept (see narrow_launch)
+template <typename G>
+__device__ __forceinline__ size_t part_index(int v0, int t, int TC) {
+  return static_cast<size_t>(v0 / G::kTileA) * (G::kTileA == kNarrowV ? kNarrowStride : TC) + t;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -161,7 +270,9 @@ struct FwdEpilogue {
   int TC;
 
   template <typename G>
-  struct Fetched {};
+  struct Fetched {
+    __device__ __forceinline__ void settle() {}
+  };
   template <typename G>
   __device__ __forceinline__ void fetch(Fetched<G>&, const TokenCols<G>&, const LogitIn&, int, const Coord16<G>&) const {}
 
@@ -221,7 +332,7 @@ struct FwdEpilogue {
       }
     }
     // fold the wavefronts' shares of the tile: one (max, sum) per token and vocabulary tile.  The buffers are free again
-    // behind the next tile's first barrier.
+    // behind the next step's barrier.
     lds_barrier();
     const int tl = co.wave * 64 + co.lane;
     if (tl < T && t0 + tl < n) {
@@ -238,7 +349,7 @@ struct FwdEpilogue {
           if (ENT) U += red_u[q * T + tl] * sc;
         }
       }
-      const size_t at = static_cast<size_t>(v0 / kTile16) * TC + t0 + tl;
+      const size_t at = part_index<G>(v0, t0 + tl, TC);
       part_m[at] = M;
       part_s[at] = S;
       if (ENT) part_u[at] = U;
@@ -280,6 +391,10 @@ struct FeEpilogue {
   template <typename G>
   struct Fetched {
     float nc2[G::kJB];
+    __device__ __forceinline__ void settle() {
+#pragma unroll
+      for (int j = 0; j < G::kJB; ++j) asm volatile("" : "+v"(nc2[j]));
+    }
   };
   template <typename G>
   __device__ __forceinline__ void fetch(Fetched<G>& f, const TokenCols<G>&, const LogitIn& in, int t0, const Coord16<G>& co) const {
@@ -329,13 +444,13 @@ struct FeEpilogue {
       sum = across_groups_sum(sum);
       if (co.lane < 16) red_s[co.wm * T + co.b_row(j)] = sum;
     }
-    lds_barrier();      // the sums are free again behind the next tile's first barrier
+    lds_barrier();      // the sums are free again behind the next step's barrier
     const int tl = co.wave * 64 + co.lane;
     if (tl < T && t0 + tl < n) {
       float S = 0.f;
 #pragma unroll
       for (int q = 0; q < G::kWavesA; ++q) S += red_s[q * T + tl];
-      part_s[static_cast<size_t>(v0 / kTile16) * TC + t0 + tl] = S;
+      part_s[part_index<G>(v0, t0 + tl, TC)] = S;
     }
   }
 };
@@ -364,6 +479,10 @@ struct DzEpilogue {
   template <typename G>
   struct Fetched {
     float g[G::kJB], l[G::kJB];
+    __device__ __forceinline__ void settle() {
+#pragma unroll
+      for (int j = 0; j < G::kJB; ++j) asm volatile("" : "+v"(g[j]), "+v"(l[j]));
+    }
   };
   template <typename G>
   __device__ __forceinline__ void fetch(Fetched<G>& f, const TokenCols<G>& cols, const LogitIn&, int, const Coord16<G>&) const {
@@ -643,23 +762,36 @@ struct DwArgs {
   floatx4* part;              // partial tiles
 };
 
-__device__ __forceinline__ void dw_store(const DwArgs& a, const floatx4 (&col)[GDw::kIB], int v, int hb, int lane) {
-  if (v >= a.V) return;
-  f32x4_any* out = reinterpret_cast<f32x4_any*>(a.dW + static_cast<size_t>(v) * a.H + hb + 4 * (lane >> 4));
-  if (hb + GDw::kRowsA <= a.H) {     // a whole block of 16 columns exists or does not (H % 64 == 0)
-    floatx4 x[GDw::kIB];
+// A wavefront's sub-tile, NJ block columns at a time; v0, h0: of the tile.  ADD: the values to add are requested for all NJ
+// columns before the first is stored.  Without ADD nothing is read, and nothing may wait: neither the choice between the two nor
+// the check of the vocabulary's end is made between the stores, since a register that a load may be on its way to makes
+// them wait for everything in flight.
+template <typename G, int NJ, bool ADD>
+__device__ __forceinline__ void dw_store_tile(const DwArgs& a, const floatx4 (&acc)[G::kIB][G::kJB], int v0, int h0,
+                                              const Coord16<G>& co) {
+  const int hb = h0 + co.wm * G::kRowsA;
+  auto at = [&](int j) {
+    return reinterpret_cast<f32x4_any*>(a.dW + static_cast<size_t>(v0 + co.b_row(j)) * a.H + hb + 4 * (co.lane >> 4));
+  };
+  if (hb + G::kRowsA <= a.H && v0 + G::kTileB <= a.V) {
 #pragma unroll
-    for (int i = 0; i < GDw::kIB; ++i) x[i] = col[i];
-    if (a.accumulate) {
+    for (int j0 = 0; j0 < G::kJB; j0 += NJ) {
+      floatx4 x[NJ][G::kIB];
 #pragma unroll
-      for (int i = 0; i < GDw::kIB; ++i) x[i] += out[i * 4];
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < G::kIB; ++i) x[j][i] = ADD ? at(j0 + j)[i * 4] + acc[i][j0 + j] : acc[i][j0 + j];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < G::kIB; ++i) at(j0 + j)[i * 4] = x[j][i];
     }
-#pragma unroll
-    for (int i = 0; i < GDw::kIB; ++i) out[i * 4] = x[i];
   } else {
 #pragma unroll
-    for (int i = 0; i < GDw::kIB; ++i)
-      if (hb + i * 16 < a.H) out[i * 4] = a.accumulate ? out[i * 4] + col[i] : col[i];
+    for (int j = 0; j < G::kJB; ++j)
+#pragma unroll
+      for (int i = 0; i < G::kIB; ++i)      // a whole block of 16 columns exists or does not (H % 64 == 0)
+        if (v0 + co.b_row(j) < a.V && hb + i * 16 < a.H) at(j)[i * 4] = ADD ? at(j)[i * 4] + acc[i][j] : acc[i][j];
   }
 }
 
@@ -671,6 +803,10 @@ __device__ __forceinline__ TileOrder dw_order(int n_vtiles, int H) {
   return TileOrder{n_vtiles, n_htiles, max(1, 32 / n_htiles)};
 }
 
+// k-steps of n rows.  The rows of the last step that do not exist are zero in hG and finite in dZ.  (In whole tiles of 256 rows
+// before: 64 tokens at H = 2048 362 -> 250 us.)
+__device__ __forceinline__ int dw_steps(int n) { return (n + kStepK - 1) / kStepK; }
+
 template <typename Off>
 __global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
   using G = GDw;
@@ -678,7 +814,7 @@ __global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
   const int n = rows_of(a.live_cnt, a.cnt, a.c0, a.TC);
   if (n <= 0 && !(a.first_chunk && !a.accumulate)) return;
   const TileOrder ord = dw_order(a.n_vtiles, a.H);
-  const int nk_all = (n + kTile16 - 1) / kTile16 * (kTile16 / kStepK);
+  const int nk_all = dw_steps(n);
   const SplitK sp = plan_split(ord.total(), nk_all, gridDim.x);
   const int items = sp.full + sp.rest * sp.S;
 
@@ -703,17 +839,10 @@ __global__ __launch_bounds__(GDw::kThreads) void k_head_dw(DwArgs a) {
       gemm16<G>(acc, pa, pb, nk, smem, co);
     }
     const Coord16<G> co;
-    if (split) {
-      store_partial<G>(a.part, it - sp.full, acc, co);
-    } else {
-#pragma unroll
-      for (int j = 0; j < G::kJB; ++j) {
-        floatx4 col[G::kIB];
-#pragma unroll
-        for (int i = 0; i < G::kIB; ++i) col[i] = acc[i][j];
-        dw_store(a, col, v0 + co.b_row(j), h0 + co.wm * G::kRowsA, co.lane);
-      }
-    }
+    constexpr int kCols = sizeof(Off) == 4 ? 4 : 1;      // (64-bit offsets leave no registers for more)
+    if (split) store_partial<G>(a.part, it - sp.full, acc, co);
+    else if (a.accumulate) dw_store_tile<G, kCols, true>(a, acc, v0, h0, co);
+    else dw_store_tile<G, kCols, false>(a, acc, v0, h0, co);
   }
 }
 
@@ -722,7 +851,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_head_dw_reduce(DwArgs a, int
   const int n = rows_of(a.live_cnt, a.cnt, a.c0, a.TC);
   if (n <= 0) return;
   const TileOrder ord = dw_order(a.n_vtiles, a.H);
-  const SplitK sp = plan_split(ord.total(), (n + kTile16 - 1) / kTile16 * (kTile16 / kStepK), grid);
+  const SplitK sp = plan_split(ord.total(), dw_steps(n), grid);
   if (sp.S <= 1) return;
   constexpr int kWaves = G::kThreads / 64;
   const int lane = threadIdx.x & 63;
@@ -733,8 +862,16 @@ __global__ __launch_bounds__(kReduceThreads) void k_head_dw_reduce(DwArgs a, int
     ord.decode(sp.full + q, &vt, &ht);
     floatx4 col[G::kIB];
     load_partials<G>(col, a.part, sp, q, wave, j, lane);
-    dw_store(a, col, vt * kTile16 + (wave % G::kWavesB) * G::kRowsB + j * 16 + (lane & 15),
-             ht * kTile16 + (wave / G::kWavesB) * G::kRowsA, lane);
+    const int v = vt * kTile16 + (wave % G::kWavesB) * G::kRowsB + j * 16 + (lane & 15);
+    const int hb = ht * kTile16 + (wave / G::kWavesB) * G::kRowsA;
+    f32x4_any* out = reinterpret_cast<f32x4_any*>(a.dW + static_cast<size_t>(v) * a.H + hb + 4 * (lane >> 4));
+    if (v >= a.V) continue;
+#pragma unroll
+    for (int i = 0; i < G::kIB; ++i)
+      if (a.accumulate && hb + i * 16 < a.H) col[i] += out[i * 4];
+#pragma unroll
+    for (int i = 0; i < G::kIB; ++i)
+      if (hb + i * 16 < a.H) out[i * 4] = col[i];
   }
 }
 
@@ -749,6 +886,7 @@ namespace {
 bool wide_rows(const HeadGeom& g) { return static_cast<int64_t>(g.H > g.Vp ? g.H : g.Vp) * 2 * kTile16 >= int64_t{1} << 32; }
 
 }  // namespace
+
 
 int launch_fwd_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
                     float* part_m, float* part_s, float* part_u, float* zy, hipStream_t s, const int32_t* gate) {
@@ -783,6 +921,8 @@ int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
+
+bool narrow_launches_bf16(const HeadGeom& g) { return !wide_rows(g); }
 
 bool transposes_w_bf16(int64_t n_tok) { return n_tok > kUntransposedRows; }
 
@@ -819,10 +959,10 @@ int launch_dh_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
 
 int launch_dw_bf16(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, void* part,
                    int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
-  auto k = wide_rows(g) ? k_head_dw<uint64_t> : k_head_dw<uint32_t>;
-  ATG_TRY(allow_big_lds(k, kRingBytes));
   const DwArgs a{static_cast<const bf16_t*>(dZ), static_cast<const bf16_t*>(hG), ch.cnt, ch.c0, dW, g.H, g.V, g.Vp, g.TC,
                  g.n_vtiles, accumulate, first_chunk, live_cnt, static_cast<floatx4*>(part)};
+  auto k = wide_rows(g) ? k_head_dw<uint64_t> : k_head_dw<uint32_t>;
+  ATG_TRY(allow_big_lds(k, kRingBytes));
   hipLaunchKernelGGL(k, dim3(gemm_grid()), dim3(GDw::kThreads), kRingBytes, s, a);
   ATG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_head_dw_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, s, a, gemm_grid());

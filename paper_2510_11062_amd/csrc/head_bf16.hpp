@@ -12,6 +12,8 @@ int launch_fe_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
                    const float* c2, void* E, float* part_s, float* zy, hipStream_t s);
 int launch_dz_bf16(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
                    const float* lse, const float* coef, void* dZ, hipStream_t s, const int32_t* gate);
+// do logits launches of few tokens follow narrow_launch()?
+bool narrow_launches_bf16(const HeadGeom& g);
 // Wt = W transposed, unless the head's list is short enough for dHidden to read W itself (then Wt is not touched; with
 // transposes_w_bf16(rows of the batch) == false no list can be long enough and Wt may be null everywhere).
 bool transposes_w_bf16(int64_t n_tok);

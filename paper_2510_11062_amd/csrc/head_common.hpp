@@ -21,6 +21,18 @@ __device__ __forceinline__ int chunk_count(const int32_t* cnt, int c0, int TC) {
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 #endif
 
+// Does a bf16 logits launch of n tokens run on tiles of kNarrowV vocabulary rows instead of 256?  Its partial results are then
+// one row of kNarrowStride per kNarrowV vocabulary rows, else one of TC per 256.
+constexpr int kNarrowV = 128, kNarrowStride = 256;
+#ifdef __HIPCC__
+__device__ __forceinline__ bool narrow_launch(int n) { return n <= 192; }
+#endif
+// floats of partial results of one kind that a launch of TC rows over n_vtiles 256-row vocabulary tiles leaves
+inline size_t logit_part_floats(int n_vtiles, int64_t TC) {
+  const int64_t stride = 256 / kNarrowV * kNarrowStride;
+  return static_cast<size_t>(n_vtiles) * static_cast<size_t>(TC > stride ? TC : stride);
+}
+
 template <typename K>
 int allow_big_lds(K kernel, int bytes) {
   ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));

@@ -30,6 +30,16 @@ constexpr int kRowPad = 256;      // rows of a super-chunk are padded to the nex
 // ------------------------------------------------------------------------------------------------
 constexpr int kCmbTokens = 32, kCmbSlices = 32, kCmbThreads = kCmbTokens * kCmbSlices, kCmbBatch = 8;
 
+// how many rows of partial results a launch of n tokens left, and how far apart they are
+struct PartialRows {
+  int count, stride;
+  __device__ __forceinline__ PartialRows(int n, int narrow, int V, int n_vtiles, int TC) {
+    const bool nl = narrow && narrow_launch(n);
+    count = nl ? (V + kNarrowV - 1) / kNarrowV : n_vtiles;
+    stride = nl ? kNarrowStride : TC;
+  }
+};
+
 // sum over a group of 32 lanes, in a fixed order
 __device__ __forceinline__ float group32_sum(float x) {
 #pragma unroll
@@ -39,13 +49,14 @@ __device__ __forceinline__ float group32_sum(float x) {
 
 __global__ __launch_bounds__(kCmbThreads) void k_lse_combine(const int32_t* __restrict__ idx,
                                                              const int32_t* __restrict__ cnt, int c0, int TC,
-                                                             int n_part, const float* __restrict__ part_m,
+                                                             int V, int n_vtiles, int narrow, const float* __restrict__ part_m,
                                                              const float* __restrict__ part_s,
                                                              const float* __restrict__ part_u,
                                                              const float* __restrict__ zy,
                                                              float* __restrict__ logp, float* __restrict__ lse,
                                                              float* __restrict__ entropy,
-                                                             const int32_t* __restrict__ gate) {
+                                                             const int32_t* __restrict__ gate, int head, CoefArgs ca,
+                                                             float* __restrict__ scale) {
   __shared__ float sm[kCmbSlices][kCmbTokens + 1], ss[kCmbSlices][kCmbTokens + 1], su[kCmbSlices][kCmbTokens + 1];
   if (gate && *gate == 0) return;
   const int n = chunk_count(cnt, c0, TC);
@@ -53,14 +64,15 @@ __global__ __launch_bounds__(kCmbThreads) void k_lse_combine(const int32_t* __re
   {
     const int tx = threadIdx.x & (kCmbTokens - 1), py = threadIdx.x / kCmbTokens;
     const int j = blockIdx.x * kCmbTokens + tx;
+    const PartialRows parts(n, narrow, V, n_vtiles, TC);
     float M = -INFINITY, S = 0.f, U = 0.f;
-    for (int p = py; p < n_part; p += kCmbSlices * kCmbBatch) {
+    for (int p = py; p < parts.count; p += kCmbSlices * kCmbBatch) {
       float m[kCmbBatch], s[kCmbBatch], u[kCmbBatch];
 #pragma unroll
       for (int e = 0; e < kCmbBatch; ++e) {
         const int q = p + e * kCmbSlices;
-        const bool ok = q < n_part && j < n;
-        const size_t at = static_cast<size_t>(q) * TC + j;
+        const bool ok = q < parts.count && j < n;
+        const size_t at = static_cast<size_t>(q) * parts.stride + j;
         m[e] = ok ? part_m[at] : -INFINITY;
         s[e] = ok ? part_s[at] : 0.f;
         u[e] = (ok && part_u) ? part_u[at] : 0.f;
@@ -97,9 +109,11 @@ __global__ __launch_bounds__(kCmbThreads) void k_lse_combine(const int32_t* __re
   if (py == 0 && j < n) {
     const float l = (Mt + __log2f(St)) * kLn2;
     const int row = idx[c0 + j];
-    logp[row] = zy[j] - l;
+    const float lp = zy[j] - l;
+    logp[row] = lp;
     if (lse) lse[row] = l;
     if (entropy) entropy[row] = l - Ut / St;     // H = lse - E_p[z]
+    if (scale) scale[j] = -coef_value(ca, head, row, lp);   // E is about to become softmax - onehot: a = -g
   }
 }
 
@@ -149,7 +163,7 @@ __global__ __launch_bounds__(256) void k_ref_logit(const bf16_t* __restrict__ hi
 // a = -g / S; the element of E that carries the onehot term is replaced by e_y - S.  A row whose S is not in
 // [.., 2^60) (overflow, NaN) or whose reference is not finite raises the gate and gets a = 0.
 __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                            int c0, int TC, int n_part, int head,
+                                                            int c0, int TC, int V, int n_vtiles, int narrow, int head,
                                                             const float* __restrict__ part_s,
                                                             const float* __restrict__ c2,
                                                             const float* __restrict__ zy,
@@ -163,13 +177,14 @@ __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __res
   {
     const int tx = threadIdx.x & (kCmbTokens - 1), py = threadIdx.x / kCmbTokens;
     const int j = blockIdx.x * kCmbTokens + tx;
+    const PartialRows parts(n, narrow, V, n_vtiles, TC);
     float S = 0.f;
-    for (int p = py; p < n_part; p += kCmbSlices * kCmbBatch) {
+    for (int p = py; p < parts.count; p += kCmbSlices * kCmbBatch) {
       float s[kCmbBatch];
 #pragma unroll
       for (int e = 0; e < kCmbBatch; ++e) {
         const int q = p + e * kCmbSlices;
-        s[e] = (q < n_part && j < n) ? part_s[static_cast<size_t>(q) * TC + j] : 0.f;
+        s[e] = (q < parts.count && j < n) ? part_s[static_cast<size_t>(q) * parts.stride + j] : 0.f;
       }
 #pragma unroll
       for (int e = 0; e < kCmbBatch; ++e) S += s[e];
@@ -194,19 +209,6 @@ __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __res
     E[static_cast<size_t>(j) * Vp + token_id[row]] = f32_to_bf16(ey - St);
     if (!ok) atomicOr(gate, 1);
   }
-}
-
-// After the two-pass kernels have replaced a launch's E by softmax - onehot: a = -g.
-__global__ __launch_bounds__(256) void k_fallback_scale(const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                        int c0, int TC, int head, CoefArgs ca,
-                                                        const float* __restrict__ logp, float* __restrict__ scale,
-                                                        const int32_t* __restrict__ gate) {
-  if (*gate == 0) return;
-  const int n = chunk_count(cnt, c0, TC);
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  const int row = idx[c0 + j];
-  scale[j] = -coef_value(ca, head, row, logp[row]);
 }
 
 // Rows on the clipped branch of Eq. (2) (factor scale[j] == 0) carry no gradient.  They are taken out of the
@@ -334,11 +336,12 @@ int launch_head_fwd(const HeadGeom& g, const HeadChunk& ch, const void* hidden, 
 
 int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part_m, const float* part_s,
                        const float* part_u, const float* zy, float* logp, float* lse, float* entropy,
-                       hipStream_t s, const int32_t* gate) {
+                       hipStream_t s, const int32_t* gate, int head, const CoefArgs* ca, float* scale) {
   ProfScope ps(PROF_LSE_COMBINE, s);
   if (g.dtype != AT_GRPO_BF16) return launch_lse_combine_f32(g, ch, part_m, part_s, part_u, zy, logp, lse, entropy, s);
   hipLaunchKernelGGL(k_lse_combine, dim3(g.TC / kCmbTokens), dim3(kCmbThreads), 0, s, ch.idx, ch.cnt, ch.c0, g.TC,
-                     g.n_vtiles, part_m, part_s, part_u, zy, logp, lse, part_u ? entropy : nullptr, gate);
+                     g.V, g.n_vtiles, narrow_launches_bf16(g), part_m, part_s, part_u, zy, logp, lse, part_u ? entropy : nullptr, gate,
+                     head, ca ? *ca : CoefArgs{}, scale);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
@@ -391,17 +394,8 @@ int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const fl
                       const float* zy, const int32_t* token_id, const CoefArgs& ca, float* logp, float* lse,
                       float* scale, void* E, int32_t* gate, hipStream_t s) {
   ProfScope ps(PROF_LSE_COMBINE, s);
-  hipLaunchKernelGGL(k_fe_combine, dim3(g.TC / kCmbTokens), dim3(kCmbThreads), 0, s, ch.idx, ch.cnt, ch.c0, g.TC, g.n_vtiles,
-                     head, part_s, c2, zy, token_id, ca, logp, lse, scale, static_cast<bf16_t*>(E), g.Vp, gate);
-  ATG_LAUNCH_CHECK();
-  return AT_GRPO_OK;
-}
-
-int launch_fallback_scale(const HeadGeom& g, const HeadChunk& ch, int head, const CoefArgs& ca, const float* logp,
-                          float* scale, const int32_t* gate, hipStream_t s) {
-  ProfScope ps(PROF_COEF, s);
-  hipLaunchKernelGGL(k_fallback_scale, dim3(g.TC / 256), dim3(256), 0, s, ch.idx, ch.cnt, ch.c0, g.TC, head, ca,
-                     logp, scale, gate);
+  hipLaunchKernelGGL(k_fe_combine, dim3(g.TC / kCmbTokens), dim3(kCmbThreads), 0, s, ch.idx, ch.cnt, ch.c0, g.TC, g.V, g.n_vtiles,
+                     narrow_launches_bf16(g), head, part_s, c2, zy, token_id, ca, logp, lse, scale, static_cast<bf16_t*>(E), g.Vp, gate);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

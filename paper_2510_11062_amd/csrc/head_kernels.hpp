@@ -32,10 +32,13 @@ int launch_head_fwd(const HeadGeom& g, const HeadChunk& ch, const void* hidden, 
                     hipStream_t s, const int32_t* gate = nullptr);
 
 // logp[row], lse[row] for the rows of this super-chunk (lse may be null).
-// With part_u, also entropy[row] = lse - E_p[z].
+// With part_u, also entropy[row] = lse - E_p[z].  bf16 with `scale` (and ca): also scale[j] = -g_j, the factor of rows whose E
+// becomes softmax - onehot.
+struct CoefArgs;
 int launch_lse_combine(const HeadGeom& g, const HeadChunk& ch, const float* part_m,
                        const float* part_s, const float* part_u, const float* zy, float* logp,
-                       float* lse, float* entropy, hipStream_t s, const int32_t* gate = nullptr);
+                       float* lse, float* entropy, hipStream_t s, const int32_t* gate = nullptr, int head = 0,
+                       const CoefArgs* ca = nullptr, float* scale = nullptr);
 
 // bf16: Wt[H][Vp] = W[V][H]^T, zero in the k padding.  A head with few rows (*cnt of its list) is left untransposed, and
 // needs_transposed_w() == false for a batch of n_tok rows says that no copy is ever read (Wt may then be null).
@@ -64,7 +67,6 @@ size_t head_partial_bytes(const HeadGeom& g);
 // ---- forward and backward from one pass over the logits (bf16) ---------------------------------------
 // A `gate` argument of the launchers above and below is a device word: with a non-null gate the kernel
 // returns at once while the word is 0 (coef == null in launch_head_dz: dZ = softmax - onehot).
-struct CoefArgs;
 
 // c2[j] = log2(e) * z[j][y_j], the reference of the exponentials, for the tokens of the launch.
 int launch_ref_logit(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
@@ -79,10 +81,6 @@ int launch_head_fe(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
 int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const float* part_s, const float* c2,
                       const float* zy, const int32_t* token_id, const CoefArgs& ca, float* logp, float* lse,
                       float* scale, void* E, int32_t* gate, hipStream_t s);
-
-// Runs only while *gate != 0: scale[j] = -g_j from logp (E then holds softmax - onehot).
-int launch_fallback_scale(const HeadGeom& g, const HeadChunk& ch, int head, const CoefArgs& ca, const float* logp,
-                          float* scale, const int32_t* gate, hipStream_t s);
 
 // d_hidden[row] = dZ[j] . W for the rows of this super-chunk.
 // With `scale`, row j of the result is multiplied by scale[j] (j counted from ch.c0).  With `perm` (after

@@ -7,14 +7,16 @@
 // of an XCD still stream the same operand panels.
 //
 // S minimises  rounds(S) * ceil(nk / S)  + what the partials cost (a step of 64 takes 1.5 us per workgroup; a partial tile
-// of 256 KiB is written and read once: 0.13 us of the whole chip's memory bandwidth, 0.09 steps).
+// of 256 KiB is written and read once: 0.13 us of the whole chip's memory bandwidth, 0.09 steps).  Many parts are for results of
+// a few tiles: dHidden of 64 tokens at H = 2048 is 8 tiles, which 16 parts each leave on half of the compute units
+// (233 us with the sum of the parts, now 172).
 #pragma once
 
 #include "common.hpp"
 
 namespace atg {
 
-constexpr int kSplitMax = 16;              // parts per tile
+constexpr int kSplitMax = 64;              // parts per tile
 constexpr int kSplitTiles = 1024;          // partial tiles a launch may leave
 constexpr size_t kPartialTileBytes = size_t{256} * 256 * 4;
 
@@ -37,8 +39,7 @@ __device__ __forceinline__ SplitK plan_split(int tiles, int nk, int grid) {
   p.chunk = nk;
   if (p.rest == 0) return p;
   int best = nk * 16;                       // in sixteenths of a step
-#pragma unroll
-  for (int S = 2; S <= kSplitMax; ++S) {
+  for (int S = 2; S <= kSplitMax; S += S < 16 ? 1 : 8) {
     if (S * 4 > nk || p.rest * S > kSplitTiles) continue;   // parts of at least four steps
     const int chunk = (nk + S - 1) / S;
     const int cost = (p.rest * S + grid - 1) / grid * chunk * 16 + p.rest * S * 3 / 2 + 80;

@@ -1,0 +1,89 @@
+"""Logits launches of few tokens (streams of k-steps on narrow tiles) and tiles cut in the last round, at the sizes where
+those rules switch, against plain torch in 64 bits.  Log-probabilities and entropies are fp32 sums of up to 2048 exact products (2e-5 of values up to 12); the gradients carry two roundings to bf16
+(2^-8 in the worst case: rows within 1e-2, the whole within 5e-3)."""
+import math
+
+import pytest
+import torch
+
+from paper_2510_11062_amd import api
+from tests.test_gpu_parity import say
+
+EPS = 0.2
+
+
+def make(dev, lengths, adv, H, V, seed=1):
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    n = sum(lengths)
+    hidden = torch.randn(n, H, generator=gen, device=dev).bfloat16()
+    W = (torch.randn(V, H, generator=gen, device=dev) * 0.02).bfloat16()
+    y = torch.randint(0, V, (n,), generator=gen, device=dev, dtype=torch.int32)
+    y[-1] = V - 1
+    cu = torch.tensor([0] + list(lengths), device=dev).cumsum(0)
+    z = hidden.double() @ W.double().T
+    logp = torch.log_softmax(z, 1)
+    drift = 0.05 * torch.randn(n, generator=gen, device=dev, dtype=torch.float64).clamp(-3, 3)
+    old = (logp.gather(1, y.long()[:, None])[:, 0] + drift).float()
+    adv = torch.tensor(adv, device=dev, dtype=torch.float32)
+    return api.Batch(hidden, [W], y, cu), logp, old, adv
+
+
+def reference(batch, logp, old, adv, lengths):
+    """log-probabilities, entropies, and the gradients of Eq. (2) (token mean) of rows with an advantage"""
+    p = logp.exp()
+    lp = logp.gather(1, batch.token_id.long()[:, None])[:, 0]
+    A = adv.double().repeat_interleave(torch.tensor(lengths, device=adv.device))
+    d = lp - old.double()
+    flat = (A == 0) | ((d > math.log1p(EPS)) & (A > 0)) | ((d < math.log1p(-EPS)) & (A < 0))
+    g = torch.where(flat, torch.zeros_like(A), -A * d.clamp(max=50).exp() / len(A))
+    dz = -g[:, None] * p
+    dz[torch.arange(len(A), device=A.device), batch.token_id.long()] += g
+    dz[flat] = 0
+    return lp, -(p * logp).sum(1), dz @ batch.W[0].double(), dz.T @ batch.hidden.double()
+
+
+def close(got, ref, what):
+    got = got.double()
+    assert bool(torch.isfinite(got).all()), what
+    rows = (got - ref).norm(dim=1) / (ref.norm(dim=1) + 1e-2 * ref.norm() / math.sqrt(ref.shape[0]))
+    assert float(rows.max()) <= 1e-2, (what, float(rows.max()))
+    assert float((got - ref).norm() / ref.norm()) <= 5e-3, what
+
+
+def check(batch, logp, old, adv, lengths, two_calls=True):
+    lp, ent, dh, dw = reference(batch, logp, old, adv, lengths)
+    out = api.at_grpo_token_entropy(batch)
+    step = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, EPS, EPS)
+    torch.cuda.synchronize()
+    assert api.error_word(step["workspace"]) == 0
+    for got in (out["logp"], step["logp"]):
+        assert float((got.double() - lp).abs().max()) <= 2e-5
+    assert float((out["entropy"].double() - ent).abs().max()) <= 2e-5
+    close(step["d_hidden"], dh, "d_hidden, one pass")
+    close(step["dW"][0], dw, "dW, one pass")
+    if not two_calls:
+        return
+    back = api.at_grpo_policy_loss_bwd(batch, old, adv, out["logp"], out["lse"], EPS, EPS)
+    close(back["d_hidden"], dh, "d_hidden, two calls")
+    close(back["dW"][0], dw, "dW, two calls")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,H,V", [
+    (1, 64, 128),           # one row, one k-step, one narrow tile
+    (64, 64, 129),          # the widest of the narrowest; a tile of one vocabulary row
+    (65, 192, 300),         # three k-steps in a ring of four; an odd number of narrow tiles
+    (128, 2048, 1000),
+    (129, 128, 70000),      # several tiles per workgroup, two k-steps each: requests run tiles ahead
+    (192, 320, 33000),      # the last stream; 258 tiles on 256 workgroups
+    (193, 320, 33000),      # 129 whole tiles: not cut
+    (250, 64, 20000),       # 79 tiles: halves, the second with 122 tokens
+    (256, 128, 16385),      # 65 tiles, one of a single vocabulary row: halves
+    (300, 192, 8200),       # 66 tiles of two token tiles, the second one's second half empty: halves
+    (450, 64, 5000),        # 40 tiles: quarters, the last one empty
+    (700, 64, 30000),       # 354 tiles: a whole round and 98 in halves
+])
+def test_few_tokens(gpu_device, n, H, V):
+    say(f"[few] n={n} H={H} V={V}")
+    lengths = [n - n // 2] + ([n // 2] if n > 1 else [])
+    check(*make(gpu_device, lengths, [1.0, -0.5][:len(lengths)], H, V), lengths)
