@@ -483,7 +483,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
       // fill the grid evenly
       ATG_TRY(launch_compact_rows(p.g, ch, p.scale, p.dZ, p.perm, p.holes, p.movers, p.live_cnt, p.live_cnt + 1, s));
       ATG_TRY(launch_head_dh(p.g, ch, p.dZ, batch->W[m], p.Wt, d_hidden, p.part, s, p.scale, p.perm, p.live_cnt));
-      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, p.scale, p.perm, p.live_cnt));
+      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, p.scale, p.perm, p.live_cnt, p.dZ));
       ATG_TRY(launch_head_dw(p.g, ch, p.dZ, batch->hidden, p.hG, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s, p.live_cnt));
     }

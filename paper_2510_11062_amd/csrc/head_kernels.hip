@@ -20,6 +20,7 @@ namespace atg {
 namespace {
 
 constexpr int kRowPad = 256;      // rows of a super-chunk are padded to the next multiple of this
+constexpr int kRowStep = 64;      // rows of a k-step of dW
 
 // ------------------------------------------------------------------------------------------------
 // combine: 1024 threads = 32 tokens x 32 slices of the vocabulary tiles.  Bound by latency where tokens are few (the
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(kCmbThreads) void k_lse_combine(const int32_t* __re
     logp[row] = lp;
     if (lse) lse[row] = l;
     if (entropy) entropy[row] = l - Ut / St;     // H = lse - E_p[z]
-    if (scale) scale[j] = -coef_value(ca, head, row, lp);   // E is about to become softmax - onehot: a = -g
+    if (scale) scale[j] = -coef_or_zero(ca, head, row, lp);   // E is about to become softmax - onehot: a = -g
   }
 }
 
@@ -203,8 +204,8 @@ __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __res
     logp[row] = lp;
     lse[row] = l;
     const bool ok = (St < kMaxRefSum) && (fabsf(c2v) < INFINITY);
-    const float g = coef_value(ca, head, row, lp);
-    scale[j] = ok ? -g / St : 0.f;
+    const float g = coef_or_zero(ca, head, row, lp);
+    scale[j] = (ok && g != 0.f) ? -g / St : 0.f;
     const float ey = fast_exp2(fmaf(zy[j], kLog2e, -c2v));
     E[static_cast<size_t>(j) * Vp + token_id[row]] = f32_to_bf16(ey - St);
     if (!ok) atomicOr(gate, 1);
@@ -269,29 +270,36 @@ __global__ __launch_bounds__(kPlanThreads) void k_compact_plan(const int32_t* __
   }
 }
 
-// E[holes[p]][:] = E[movers[p]][:] for p < *pair_cnt; 16 bytes per lane, one row per workgroup at a time
+// E[holes[p]][:] = E[movers[p]][:] for p < *pair_cnt; 16 bytes per lane.  A row is shared by kMoveParts workgroups: a few
+// rows of the full vocabulary (300 KB each) are spread over the chip.
+constexpr int kMoveParts = 8;
+
 __global__ __launch_bounds__(256) void k_move_rows(bf16_t* __restrict__ E, int Vp, const int32_t* __restrict__ holes,
                                                    const int32_t* __restrict__ movers,
                                                    const int32_t* __restrict__ pair_cnt) {
   const int m = *pair_cnt;
   const int chunks = Vp / 8;   // 16-byte pieces per row (Vp is a multiple of 64)
-  for (int p = blockIdx.x; p < m; p += gridDim.x) {
+  const int part = blockIdx.x % kMoveParts;
+  for (int p = blockIdx.x / kMoveParts; p < m; p += gridDim.x / kMoveParts) {
     const uint4* src = reinterpret_cast<const uint4*>(E + static_cast<size_t>(movers[p]) * Vp);
     uint4* dst = reinterpret_cast<uint4*>(E + static_cast<size_t>(holes[p]) * Vp);
-    for (int c = threadIdx.x; c < chunks; c += 256) dst[c] = src[c];
+#pragma unroll 4
+    for (int c = part * 256 + threadIdx.x; c < chunks; c += kMoveParts * 256) dst[c] = src[c];
   }
 }
 
 // ------------------------------------------------------------------------------------------------
 // hG[j][:] = hidden[idx[c0 + j]][:] for j < n, zero rows up to the next multiple of 256 (bf16 rows
-// of the super-chunk made contiguous so that the token contraction can stream them k-major)
+// of the super-chunk made contiguous so that the token contraction can stream them k-major).  With E: its rows from n up to
+// a whole k-step of that contraction are cleared too (what rows that take no part hold need not be finite).
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_gather_rows(const bf16_t* __restrict__ hidden,
                                                      const int32_t* __restrict__ idx,
                                                      const int32_t* __restrict__ cnt, int c0, int TC, int H,
                                                      const float* __restrict__ scale,
                                                      const int32_t* __restrict__ perm,
-                                                     const int32_t* __restrict__ live_cnt, bf16_t* __restrict__ hG) {
+                                                     const int32_t* __restrict__ live_cnt, bf16_t* __restrict__ hG,
+                                                     bf16_t* __restrict__ E, int Vp) {
   // with perm: row j of hG is list position perm[j], for j < *live_cnt
   const int n = perm ? min(*live_cnt, chunk_count(cnt, c0, TC)) : chunk_count(cnt, c0, TC);
   const int n_pad = (n + kRowPad - 1) / kRowPad * kRowPad;
@@ -316,6 +324,10 @@ __global__ __launch_bounds__(256) void k_gather_rows(const bf16_t* __restrict__ 
       for (int c = threadIdx.x & 31; c < chunks; c += 32) dst[c] = src ? src[c] : make_uint4(0, 0, 0, 0);
     }
   }
+  if (!E) return;
+  const int64_t pieces = static_cast<int64_t>((n + kRowStep - 1) / kRowStep * kRowStep - n) * (Vp / 8);
+  uint4* rest = reinterpret_cast<uint4*>(E + static_cast<size_t>(n) * Vp);
+  for (int64_t c = blockIdx.x * int64_t{256} + threadIdx.x; c < pieces; c += gridDim.x * int64_t{256}) rest[c] = make_uint4(0, 0, 0, 0);
 }
 
 }  // namespace
@@ -356,11 +368,11 @@ int launch_transpose_w(const HeadGeom& g, const void* W, void* Wt, const int32_t
 }
 
 int launch_gather_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hidden, void* hG,
-                         hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
+                         hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt, void* E) {
   ProfScope ps(PROF_TRANSPOSE, s);
   if (!hG) return AT_GRPO_OK;
   hipLaunchKernelGGL(k_gather_rows, dim3(2048), dim3(256), 0, s, static_cast<const bf16_t*>(hidden), ch.idx,
-                     ch.cnt, ch.c0, g.TC, g.H, scale, perm, live_cnt, static_cast<bf16_t*>(hG));
+                     ch.cnt, ch.c0, g.TC, g.H, scale, perm, live_cnt, static_cast<bf16_t*>(hG), static_cast<bf16_t*>(E), g.Vp);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

@@ -54,7 +54,8 @@ int head_vocab_tile(int dtype);
 // behind.
 int launch_gather_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hidden,
                          void* hG, hipStream_t s, const float* scale = nullptr,
-                         const int32_t* perm = nullptr, const int32_t* live_cnt = nullptr);
+                         const int32_t* perm = nullptr, const int32_t* live_cnt = nullptr,
+                         void* E = nullptr);
 
 // dZ[TC][Vp] for this super-chunk (element type of hidden).
 int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,

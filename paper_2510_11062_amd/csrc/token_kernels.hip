@@ -486,6 +486,11 @@ enum PrepMode {
 constexpr int kPsThreads = 1024, kPsRows = 32768, kPsPer = 8, kPsTile = kPsThreads * kPsPer;
 constexpr int kPsBatch = 4;            // rows of a response that a lane requests before it uses the first
 constexpr int kPsNoAdv = 0x40;         // mark of a participating row: its head, with this bit where the advantage is zero
+// Up to so many rows without an advantage join the list of a head's other rows, behind them (their factor is zero, so they
+// are taken out again in front of the backward contractions).  A list of their own costs a pass over the head's weights and
+// tiles that do not fill the chip; on the common list they cost the write of their exponentials, 7 % of their contraction.
+// Micro-batch of 2300 rows at the full vocabulary: 3500 -> 3390 us.
+constexpr int kPsMerge = 2048;
 static_assert(kMaxHeads <= kPsNoAdv, "head and flag share a byte");
 
 struct PrepArgs {
@@ -505,12 +510,12 @@ template <int MODE>
 __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
   __shared__ __attribute__((aligned(16))) int8_t mark[kPsRows];
   __shared__ int part[2][kPsThreads / 64];
-  __shared__ int rows_of_head[kMaxHeads], resps_of_head[kMaxHeads];
+  __shared__ int rows_of_head[kMaxHeads], resps_of_head[kMaxHeads], no_adv_of_head[kMaxHeads];
   const TokenLayout& L = a.L;
   const int tid = threadIdx.x, n = static_cast<int>(L.n_tok);
 
   if (tid == 0) *a.S.err = 0;
-  if (tid < kMaxHeads) rows_of_head[tid] = resps_of_head[tid] = 0;
+  if (tid < kMaxHeads) rows_of_head[tid] = resps_of_head[tid] = no_adv_of_head[tid] = 0;
   for (int i = tid * 16; i < n; i += kPsThreads * 16) *reinterpret_cast<int4*>(mark + i) = make_int4(-1, -1, -1, -1);
   if (MODE != PREP_LOGPROB)
     for (int t = tid; t < n; t += kPsThreads) a.S.resp_of_tok[t] = -1;
@@ -566,6 +571,7 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
       if (c > 0) {
         atomicAdd(&rows_of_head[head], c);
         atomicAdd(&resps_of_head[head], 1);
+        if (mine != head) atomicAdd(&no_adv_of_head[head], c);
       }
     }
   }
@@ -606,9 +612,13 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
   int buf = 0;
   for (int m = 0; m < kMaxHeads; ++m) {
     int run_b = 0, run_f = 0;
+    bool merge = false;
     if (m < L.n_heads) {
       int32_t* out_b = a.idx_b + static_cast<size_t>(m) * n;
       int32_t* out_f = MODE == PREP_STEP ? a.idx_f + static_cast<size_t>(m) * n : nullptr;
+      const int rows_f = MODE == PREP_STEP ? no_adv_of_head[m] : 0, rows_b = MODE == PREP_STEP ? rows_of_head[m] - rows_f : 0;
+      merge = rows_b > 0 && rows_f > 0 && rows_f <= kPsMerge;
+      if (merge) out_f = out_b + rows_b;
       for (int base = 0; base < n; base += kPsTile) {
         const int t0 = base + tid * kPsPer;
         uint2 w = make_uint2(0xffffffffu, 0xffffffffu);
@@ -647,8 +657,8 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
       }
     }
     if (tid == 0) {
-      a.cnt_b[m] = run_b;
-      if (MODE == PREP_STEP) a.cnt_f[m] = run_f;
+      a.cnt_b[m] = merge ? run_b + run_f : run_b;
+      if (MODE == PREP_STEP) a.cnt_f[m] = merge ? 0 : run_f;
     }
   }
 }

@@ -96,6 +96,11 @@ __device__ __forceinline__ float coef_value(const CoefArgs& a, int head, int64_t
   if (bits & AT_GRPO_CLIP_ZERO_GRAD) return 0.f;
   return -w * A * ratio * (a.grad_loss ? a.grad_loss[head] : 1.f);
 }
+
+// The same on a list that also holds rows without an advantage, whatever their ratio is.
+__device__ __forceinline__ float coef_or_zero(const CoefArgs& a, int head, int64_t t, float logp) {
+  return a.adv[a.resp_of_tok[t]] == 0.f ? 0.f : coef_value(a, head, t, logp);
+}
 #endif  // __HIPCC__
 
 int launch_fill_i32(int32_t* p, int64_t n, int32_t value, hipStream_t s);
@@ -146,8 +151,8 @@ int launch_prep_logprob(const TokenLayout& L, const TokenScratch& S, float* logp
 // resp_of_tok, resp_len, resp_cnt of S; coef; cnt and idx of the rows whose coefficient is not zero
 int launch_prep_backward(const TokenLayout& L, const TokenScratch& S, const float* logp, const CoefArgs& ca, float* coef,
                          hipStream_t s);
-// resp_of_tok, resp_len, cnt, resp_cnt of S; cnt and idx of SB (advantage not zero) and SF (zero); logp = lse = 0 on rows
-// that take no part; gates = 0
+// resp_of_tok, resp_len, cnt, resp_cnt of S; cnt and idx of SB (advantage not zero) and SF (zero; a few of them stand behind
+// the others on SB's list instead); logp = lse = 0 on rows that take no part; gates = 0
 int launch_prep_step(const TokenLayout& L, const TokenScratch& S, const TokenScratch& SB, const TokenScratch& SF,
                      const float* adv, float* logp, float* lse, int32_t* gates, int n_gates, hipStream_t s);
 

@@ -1,5 +1,6 @@
-"""Logits launches of few tokens (streams of k-steps on narrow tiles) and tiles cut in the last round, at the sizes where
-those rules switch, against plain torch in 64 bits.  Log-probabilities and entropies are fp32 sums of up to 2048 exact products (2e-5 of values up to 12); the gradients carry two roundings to bf16
+"""Logits launches of few tokens (streams of k-steps on narrow tiles), tiles cut in the last round, and rows without an
+advantage on the list of the others, at the sizes where those rules switch, against plain torch in 64 bits.  Log-probabilities
+and entropies are fp32 sums of up to 2048 exact products (2e-5 of values up to 12); the gradients carry two roundings to bf16
 (2^-8 in the worst case: rows within 1e-2, the whole within 5e-3)."""
 import math
 
@@ -87,3 +88,27 @@ def test_few_tokens(gpu_device, n, H, V):
     say(f"[few] n={n} H={H} V={V}")
     lengths = [n - n // 2] + ([n // 2] if n > 1 else [])
     check(*make(gpu_device, lengths, [1.0, -0.5][:len(lengths)], H, V), lengths)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("with_adv,without", [(1, 1), (100, 2048), (100, 2049), (700, 300), (64, 63)])
+def test_rows_without_advantage(gpu_device, with_adv, without):
+    """Up to 2048 of them stand on the list of the others; wherever they stand they get their log-probability and no gradient,
+    also where their ratio overflows."""
+    say(f"[few] {with_adv} rows with and {without} without an advantage")
+    lengths = [without - without // 2, with_adv, without // 2]
+    batch, logp, old, adv = make(gpu_device, lengths, [0.0, 0.7, 0.0], 128, 2000)
+    old[:1] = -300.0
+    check(batch, logp, old, adv, lengths, two_calls=False)
+
+
+@pytest.mark.gpu
+def test_hidden_rows_without_advantage_need_not_be_finite(gpu_device):
+    say("[few] infinite hidden rows without an advantage")
+    lengths = [30, 70, 40]
+    batch, logp, old, adv = make(gpu_device, lengths, [0.0, 0.7, 0.0], 128, 2000)
+    _, _, dh, dw = reference(batch, logp, old, adv, lengths)
+    batch.hidden[100:103] = float("inf")
+    step = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, EPS, EPS)
+    close(step["d_hidden"], dh, "d_hidden")
+    close(step["dW"][0], dw, "dW")
