@@ -323,8 +323,7 @@ extern "C" int at_grpo_surrogate_from_logp(const at_grpo_batch* batch, const flo
   make_plan(batch, AT_GRPO_CALL_SURROGATE, ws, &p);
   ATG_TRY(check_workspace(workspace, workspace_bytes, ws.bytes()));
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  ATG_TRY(launch_fill_i32(p.S.err, 1, 0, s));
-  return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, s);
+  return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, true, s);
 }
 
 extern "C" int at_grpo_surrogate_diagnostics(const at_grpo_batch* batch, const float* logp,
@@ -357,7 +356,7 @@ extern "C" int at_grpo_policy_loss_fwd(const at_grpo_batch* batch, const float* 
   ATG_TRY(check_workspace(workspace, workspace_bytes, ws.bytes()));
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   ATG_TRY(enqueue_logprob(batch, p, logp, lse, nullptr, s));
-  return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, s);
+  return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, false, s);
 }
 
 extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* old_logp, const float* adv,
@@ -488,7 +487,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
                              c == 0 ? 1 : 0, s, p.live_cnt));
     }
   }
-  return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, s);
+  return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, false, s);
 }
 
 extern "C" const char* at_grpo_status_string(int32_t status) {

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void k_resp_cnt(TokenLayout L, const int32_t* 
   }
 }
 
-// Rows lo .. hi of a response, read by a team of LPR lanes (64, 32 or 16, chosen from the mean response length) in aligned
+// Rows lo .. hi of a response, read by a team of LPR lanes (256, 64, 32 or 16, chosen from the mean response length) in aligned
 // 4-row vectors.  each(logp, old_logp) is called for every participating row, in ascending order within a lane, and returns
 // the row's clip flags, which are stored when clip_mask is given.  One vector of each input per lane and round: with two
 // requested ahead, many rows take longer (28 million rows in responses of about 289, 32 lanes: 105 us, 99 with one), and few
@@ -168,16 +168,53 @@ typedef float f32x4_rows __attribute__((ext_vector_type(4), aligned(4)));
 typedef int i32x4_rows __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u8x4_rows __attribute__((aligned(1)));
 
+// Sums and ors over a team's lanes; every lane gets the result.  A team of 256 is a workgroup: lds holds a word per wavefront.
+template <int LPR, typename T, typename Op>
+__device__ __forceinline__ T team_reduce(T v, T* lds, Op op) {
+#pragma unroll
+  for (int o = (LPR < 64 ? LPR : 64) / 2; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
+  if constexpr (LPR > 64) {
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = lds[0];
+#pragma unroll
+    for (int w = 1; w < LPR / 64; ++w) v = op(v, lds[w]);
+  }
+  return v;
+}
+struct Plus {
+  template <typename T>
+  __device__ __forceinline__ T operator()(T a, T b) const { return a + b; }
+};
+struct Or {
+  __device__ __forceinline__ int operator()(int a, int b) const { return a | b; }
+};
+
+// A response's head (0xff: none) and the data errors met in its rows share a word: the kernel that adds the responses up
+// also collects the errors, so no word has to be cleared beforehand (two launches of 1.4 us fewer for surrogate and monitors).
+constexpr int kNoHead = 0xff, kErrShift = 8;
+
+// head of a response, or -1 and an error bit
+__device__ __forceinline__ int head_or_error(const TokenLayout& L, int r, int* bad) {
+  if (L.n_heads == 1 || L.resp_agent == nullptr || L.head_of_agent == nullptr) return 0;
+  const int a = L.resp_agent[r];
+  const int h = (a < 0 || a >= L.n_agent) ? -1 : L.head_of_agent[a];
+  if (h >= 0 && h < L.n_heads) return h;
+  *bad |= AT_GRPO_DATA_AGENT_RANGE;
+  return -1;
+}
+
 template <int LPR, typename F>
 __device__ __forceinline__ void each_row(const TokenLayout& L, const float* __restrict__ logp,
                                          const float* __restrict__ old_logp, int64_t lo, int64_t hi, int head, int lane,
-                                         uint8_t* __restrict__ clip_mask, int32_t* __restrict__ err, F each) {
+                                         uint8_t* __restrict__ clip_mask, int* bad, F each) {
   auto one = [&](int64_t t) {
     bool on = (head >= 0) && (L.mask == nullptr || L.mask[t] != 0);
     if (on && L.token_id != nullptr) {
       const int y = L.token_id[t];
       if (y < 0 || y >= L.V) {
-        atomicOr(err, AT_GRPO_DATA_TOKEN_RANGE);
+        *bad |= AT_GRPO_DATA_TOKEN_RANGE;
         on = false;
       }
     }
@@ -201,7 +238,7 @@ __device__ __forceinline__ void each_row(const TokenLayout& L, const float* __re
         const bool mine = interior || (t0 + e >= lo && t0 + e < hi);
         bool on = mine && (head >= 0) && (((m4 >> (8 * e)) & 0xffu) != 0);
         if (on && L.token_id != nullptr && (y4[e] < 0 || y4[e] >= L.V)) {
-          atomicOr(err, AT_GRPO_DATA_TOKEN_RANGE);
+          *bad |= AT_GRPO_DATA_TOKEN_RANGE;
           on = false;
         }
         if (on) out |= static_cast<uint32_t>(each(lp[e], ol[e])) << (8 * e);
@@ -233,8 +270,9 @@ __global__ __launch_bounds__(256) void k_surrogate_resp(TokenLayout L, const flo
                                                         uint8_t* __restrict__ clip_mask,
                                                         float* __restrict__ resp_sum,
                                                         int32_t* __restrict__ resp_cnt,
-                                                        int32_t* __restrict__ resp_head,
-                                                        int32_t* __restrict__ err) {
+                                                        int32_t* __restrict__ resp_head) {
+  __shared__ float lds_f[4];
+  __shared__ int lds_i[4];
   const int lane = threadIdx.x & (LPR - 1);
   const int team = (blockIdx.x * blockDim.x + threadIdx.x) / LPR;
   const int n_teams = (gridDim.x * blockDim.x) / LPR;
@@ -242,18 +280,18 @@ __global__ __launch_bounds__(256) void k_surrogate_resp(TokenLayout L, const flo
     const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
     if (lo < 0 || hi < lo || hi > L.n_tok) {
       if (lane == 0) {
-        atomicOr(err, AT_GRPO_DATA_SEQLENS);
         resp_sum[r] = 0.f;
         resp_cnt[r] = 0;
-        resp_head[r] = -1;
+        resp_head[r] = kNoHead | AT_GRPO_DATA_SEQLENS << kErrShift;
       }
       continue;
     }
-    const int head = head_of_response(r, L.n_heads, L.n_agent, L.resp_agent, L.head_of_agent, err);
+    int bad = 0;
+    const int head = head_or_error(L, r, &bad);
     const float A = adv[r];
     float sum = 0.f;
     int cnt = 0;
-    each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, clip_mask, err, [&](float lp, float ol) {
+    each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, clip_mask, &bad, [&](float lp, float ol) {
       int bits;
       float ratio;
       sum += surrogate_term(lp, ol, A, cc, &bits, &ratio);
@@ -265,15 +303,13 @@ __global__ __launch_bounds__(256) void k_surrogate_resp(TokenLayout L, const flo
       for (int64_t t = lane; t < lo; t += LPR) clip_mask[t] = 0;
     if (clip_mask && r == L.n_resp - 1)
       for (int64_t t = hi + lane; t < L.n_tok; t += LPR) clip_mask[t] = 0;
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) {
-      sum += __shfl_xor(sum, o, 64);
-      cnt += __shfl_xor(cnt, o, 64);
-    }
+    sum = team_reduce<LPR>(sum, lds_f, Plus());
+    cnt = team_reduce<LPR>(cnt, lds_i, Plus());
+    bad = team_reduce<LPR>(bad, lds_i, Or());
     if (lane == 0) {
       resp_sum[r] = (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN && cnt > 0) ? sum / static_cast<float>(cnt) : sum;
       resp_cnt[r] = cnt;
-      resp_head[r] = head;
+      resp_head[r] = (head & kNoHead) | bad << kErrShift;
     }
   }
 }
@@ -282,15 +318,18 @@ __global__ __launch_bounds__(256) void k_surrogate_resp(TokenLayout L, const flo
 __global__ __launch_bounds__(1024) void k_loss_final(int n_resp, const float* __restrict__ resp_sum,
                                                      const int32_t* __restrict__ resp_cnt,
                                                      const int32_t* __restrict__ resp_head, int agg,
-                                                     float* __restrict__ loss, int32_t* __restrict__ n_valid) {
+                                                     float* __restrict__ loss, int32_t* __restrict__ n_valid,
+                                                     int32_t* __restrict__ err, int first) {
   __shared__ float fs[16];
-  __shared__ int is[16], ir[16];
+  __shared__ int is[16], ir[16], ie[16];
   const int m = blockIdx.x;
   float acc = 0.f;
-  int cnt = 0, nresp = 0;
+  int cnt = 0, nresp = 0, bad = 0;
 #pragma unroll 8
   for (int r = threadIdx.x; r < n_resp; r += 1024) {
-    const bool mine = resp_head[r] == m;
+    const int hw = resp_head[r];
+    const bool mine = (hw & kNoHead) == m;
+    bad |= hw >> kErrShift;
     const float sv = resp_sum[r];
     const int cv = resp_cnt[r];
     acc += mine ? sv : 0.f;
@@ -300,21 +339,25 @@ __global__ __launch_bounds__(1024) void k_loss_final(int n_resp, const float* __
   acc = wave_sum(acc);
   cnt = wave_sum_int(cnt);
   nresp = wave_sum_int(nresp);
+  if (__builtin_amdgcn_ballot_w64(bad != 0) != 0ull) bad = team_reduce<64>(bad, ie, Or());
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) {
     fs[wave] = acc;
     is[wave] = cnt;
     ir[wave] = nresp;
+    ie[wave] = bad;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     float tot = 0.f;
-    int c = 0, nr = 0;
+    int c = 0, nr = 0, e = 0;
     for (int w = 0; w < 16; ++w) {
       tot += fs[w];
       c += is[w];
       nr += ir[w];
+      e |= ie[w];
     }
+    if (m == 0) *err = first ? e : *err | e;      // kernels in front of this one may have raised bits
     const int denom = (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN) ? nr : c;
     loss[m] = denom > 0 ? -tot / static_cast<float>(denom) : 0.f;
     if (n_valid) n_valid[m] = c;
@@ -336,22 +379,23 @@ struct DiagPartials {
 template <int LPR>
 __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* __restrict__ logp,
                                                    const float* __restrict__ old_logp,
-                                                   const float* __restrict__ adv, ClipConst cc, DiagPartials P,
-                                                   int32_t* __restrict__ err) {
+                                                   const float* __restrict__ adv, ClipConst cc, DiagPartials P) {
+  __shared__ float lds_f[4];
+  __shared__ int lds_i[4];
   const int lane = threadIdx.x & (LPR - 1);
   const int team = (blockIdx.x * blockDim.x + threadIdx.x) / LPR;
   const int n_teams = (gridDim.x * blockDim.x) / LPR;
   for (int r = team; r < L.n_resp; r += n_teams) {
     const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
-    int head = -1;
+    int head = -1, bad = 0;
     int n = 0, low = 0, high = 0, zero = 0;
     float kl = 0.f, rs = 0.f;
     if (lo < 0 || hi < lo || hi > L.n_tok) {
-      if (lane == 0) atomicOr(err, AT_GRPO_DATA_SEQLENS);
+      bad = AT_GRPO_DATA_SEQLENS;
     } else {
-      head = head_of_response(r, L.n_heads, L.n_agent, L.resp_agent, L.head_of_agent, err);
+      head = head_or_error(L, r, &bad);
       const float A = adv[r];
-      each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, nullptr, err, [&](float lp, float ol) {
+      each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, nullptr, &bad, [&](float lp, float ol) {
         const float d = lp - ol;
         const bool is_low = d < cc.lo, is_high = d > cc.hi;
         ++n;
@@ -363,17 +407,15 @@ __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* _
         return 0;
       });
     }
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) {
-      n += __shfl_xor(n, o, 64);
-      low += __shfl_xor(low, o, 64);
-      high += __shfl_xor(high, o, 64);
-      zero += __shfl_xor(zero, o, 64);
-      kl += __shfl_xor(kl, o, 64);
-      rs += __shfl_xor(rs, o, 64);
-    }
+    n = team_reduce<LPR>(n, lds_i, Plus());
+    low = team_reduce<LPR>(low, lds_i, Plus());
+    high = team_reduce<LPR>(high, lds_i, Plus());
+    zero = team_reduce<LPR>(zero, lds_i, Plus());
+    bad = team_reduce<LPR>(bad, lds_i, Or());
+    kl = team_reduce<LPR>(kl, lds_f, Plus());
+    rs = team_reduce<LPR>(rs, lds_f, Plus());
     if (lane == 0) {
-      P.head[r] = head;
+      P.head[r] = (head & kNoHead) | bad << kErrShift;
       P.n[r] = n;
       P.low[r] = low;
       P.high[r] = high;
@@ -386,15 +428,18 @@ __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* _
 
 // one 1024-thread block per head: fixed-order sums of the per-response partials
 __global__ __launch_bounds__(1024) void k_diag_final(int n_resp, DiagPartials P, int32_t* __restrict__ counts,
-                                                     float* __restrict__ stats) {
-  __shared__ int is[4][16];
+                                                     float* __restrict__ stats, int32_t* __restrict__ err) {
+  __shared__ int is[4][16], ie[16];
   __shared__ float fs[2][16];
   const int m = blockIdx.x;
   int c[4] = {0, 0, 0, 0};
   float f[2] = {0.f, 0.f};
+  int bad = 0;
 #pragma unroll 4
   for (int r = threadIdx.x; r < n_resp; r += 1024) {   // loads that do not wait for the head: 7.1 us with a branch on it
-    const bool mine = P.head[r] == m;
+    const int hw = P.head[r];
+    const bool mine = (hw & kNoHead) == m;
+    bad |= hw >> kErrShift;
     const int n = P.n[r], low = P.low[r], high = P.high[r], zero = P.zero[r];
     const float kl = P.kl[r], ratio = P.ratio[r];
     c[0] += mine ? n : 0;
@@ -415,8 +460,13 @@ __global__ __launch_bounds__(1024) void k_diag_final(int n_resp, DiagPartials P,
     f[k] = wave_sum(f[k]);
     if (lane == 0) fs[k][wave] = f[k];
   }
+  if (__builtin_amdgcn_ballot_w64(bad != 0) != 0ull) bad = team_reduce<64>(bad, ie, Or());
+  if (lane == 0) ie[wave] = bad;
   __syncthreads();
   if (threadIdx.x == 0) {
+    int e = 0;
+    for (int w = 0; w < 16; ++w) e |= ie[w];
+    if (m == 0) *err = e;
     int tot[4] = {0, 0, 0, 0};
     float ft[2] = {0.f, 0.f};
     for (int w = 0; w < 16; ++w) {
@@ -489,7 +539,8 @@ constexpr int kPsNoAdv = 0x40;         // mark of a participating row: its head,
 // Up to so many rows without an advantage join the list of a head's other rows, behind them (their factor is zero, so they
 // are taken out again in front of the backward contractions).  A list of their own costs a pass over the head's weights and
 // tiles that do not fill the chip; on the common list they cost the write of their exponentials, 7 % of their contraction.
-// Micro-batch of 2300 rows at the full vocabulary: 3500 -> 3390 us.
+// (Micro-batch of 2300 rows at the full vocabulary: 212 us for a few hundred rows of their own beside 1041 for the others'
+// exponentials, 1107 together.)
 constexpr int kPsMerge = 2048;
 static_assert(kMaxHeads <= kPsNoAdv, "head and flag share a byte");
 
@@ -676,6 +727,11 @@ int team_lanes_small(const TokenLayout& L) {
   return mean_rows > 128 ? 64 : mean_rows > 64 ? 32 : 16;
 }
 
+// A workgroup per response where there are at most two per compute unit, so that nothing but the longest response counts: 240
+// responses of 290 rows in the mean 10.1 -> 5.4 us; 1024 of 288 take 6.0 with a wavefront and 5.8 with a workgroup each, 6144 of 289
+// 13.0 and 19.0.
+constexpr int kWideTeams = 512;
+
 // Lanes that share a response in the row kernels, by the mean number of rows and by how many responses there are.  The chip
 // holds 8192 of these wavefronts.  While the responses are few rounds of it, the call ends with its longest response, which may
 // be many times the mean: more lanes (C5, 6228 responses of 289 rows in the mean and up to 4096: surrogate 19 us with 64 lanes,
@@ -684,6 +740,7 @@ int team_lanes_small(const TokenLayout& L) {
 // with 64 and 90 with 32.
 int team_lanes(const TokenLayout& L) {
   const int64_t mean_rows = L.n_tok / (L.n_resp > 0 ? L.n_resp : 1);
+  if (mean_rows >= 160 && L.n_resp <= kWideTeams) return 256;
   if (mean_rows >= 512) return 64;
   if (mean_rows >= 160) return L.n_resp <= 32768 ? 64 : 32;
   return mean_rows >= 60 && L.n_resp <= 8192 ? 32 : 16;
@@ -746,16 +803,16 @@ int launch_resp_len(const TokenLayout& L, const TokenScratch& S, hipStream_t s) 
 
 int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* logp, const float* old_logp,
                      const float* adv, float eps_low, float eps_high, int agg, float* loss,
-                     uint8_t* clip_mask, int32_t* n_valid, hipStream_t s) {
+                     uint8_t* clip_mask, int32_t* n_valid, bool first, hipStream_t s) {
   ProfScope ps(PROF_SURROGATE, s);
   const ClipConst cc = make_clip(eps_low, eps_high);
   const int lanes = team_lanes(L);
-  auto k = lanes == 64 ? k_surrogate_resp<64> : lanes == 32 ? k_surrogate_resp<32> : k_surrogate_resp<16>;
+  auto k = lanes == 256 ? k_surrogate_resp<256> : lanes == 64 ? k_surrogate_resp<64> : lanes == 32 ? k_surrogate_resp<32> : k_surrogate_resp<16>;
   hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, L, logp, old_logp, adv, cc, agg,
-                     clip_mask, S.resp_sum, S.resp_len, S.resp_head, S.err);
+                     clip_mask, S.resp_sum, S.resp_len, S.resp_head);
   ATG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_loss_final, dim3(L.n_heads), dim3(1024), 0, s, L.n_resp, S.resp_sum, S.resp_len,
-                     S.resp_head, agg, loss, n_valid);
+                     S.resp_head, agg, loss, n_valid, S.err, first ? 1 : 0);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
@@ -781,13 +838,12 @@ int launch_diagnostics(const TokenLayout& L, const float* logp, const float* old
   P.zero = ws.take<int32_t>(static_cast<size_t>(L.n_resp));
   P.kl = reinterpret_cast<float*>(ws.take<int32_t>(static_cast<size_t>(L.n_resp)));
   P.ratio = reinterpret_cast<float*>(ws.take<int32_t>(static_cast<size_t>(L.n_resp)));
-  ATG_TRY(launch_fill_i32(err, 1, 0, s));
   const ClipConst cc = make_clip(eps_low, eps_high);
   const int lanes = team_lanes(L);
-  auto k = lanes == 64 ? k_diag_resp<64> : lanes == 32 ? k_diag_resp<32> : k_diag_resp<16>;
-  hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, L, logp, old_logp, adv, cc, P, err);
+  auto k = lanes == 256 ? k_diag_resp<256> : lanes == 64 ? k_diag_resp<64> : lanes == 32 ? k_diag_resp<32> : k_diag_resp<16>;
+  hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, L, logp, old_logp, adv, cc, P);
   ATG_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_diag_final, dim3(L.n_heads), dim3(1024), 0, s, L.n_resp, P, counts, stats);
+  hipLaunchKernelGGL(k_diag_final, dim3(L.n_heads), dim3(1024), 0, s, L.n_resp, P, counts, stats, err);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

@@ -116,10 +116,11 @@ int launch_compact(const TokenLayout& L, const TokenScratch& S, bool with_idx, h
 int launch_resp_len(const TokenLayout& L, const TokenScratch& S, hipStream_t s);
 
 // Per-token surrogate terms + clip mask + per-head loss (Eq. 2).  Self-contained: reads the layout
-// directly (16, 32 or 64 lanes per response); overwrites resp_len with its own per-response counts.
+// directly (16 to 256 lanes per response); overwrites resp_len with its own per-response counts.  first: the call's first
+// kernel, which sets the error word; otherwise it adds to it.
 int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* logp,
                      const float* old_logp, const float* adv, float eps_low, float eps_high, int agg,
-                     float* loss, uint8_t* clip_mask, int32_t* n_valid, hipStream_t s);
+                     float* loss, uint8_t* clip_mask, int32_t* n_valid, bool first, hipStream_t s);
 
 // Diagnostics of the clipped-ratio update: counts[n_heads][4] = (rows, below, above, zero-gradient),
 // stats[n_heads][2] = (mean of ratio - 1 - d, mean ratio).  Self-contained like launch_surrogate; its

@@ -1,4 +1,4 @@
-"""Surrogate and diagnostics on both sides of every switch of the lanes that share a response (16, 32, 64), with tensors
+"""Surrogate and diagnostics on both sides of every switch of the lanes that share a response (16, 32, 64, 256), with tensors
 that start anywhere, against the CPU oracle: flags and counts exact, sums within fp32's 1e-4 as in tests/test_gpu_parity.py
 (here the mean of terms of both signs and size about 1, hence 1e-6 absolute)."""
 import numpy as np
@@ -11,7 +11,8 @@ from tests.gpu_case import host
 from tests.test_gpu_parity import say
 
 
-SIZES = [(50, 59), (50, 60), (8192, 60), (8193, 60), (50, 159), (50, 160), (32768, 160), (32769, 160), (33000, 511), (50, 512)]
+SIZES = [(50, 59), (50, 60), (8192, 60), (8193, 60), (50, 159), (50, 160), (32768, 160), (32769, 160), (33000, 511), (50, 512),
+         (512, 160), (513, 160)]
 
 
 @pytest.mark.gpu
