@@ -388,12 +388,21 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
     ATG_TRY(launch_coef(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, grad_loss, p.coef, s));
     ATG_TRY(launch_compact(p.L, p.S, true, s));
   }
-  ATG_TRY(launch_fill_bytes16(d_hidden, p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize, s));
+  const int64_t hidden_bytes = p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize;
+  const bool f32 = batch->dtype == AT_GRPO_F32;      // its first dZ launch clears d_hidden
+  if (!f32) ATG_TRY(launch_fill_bytes16(d_hidden, hidden_bytes, s));
 
   for (int m = 0; m < batch->n_heads; ++m) {
     ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, p.S.cnt + m, s));
     for (int c = 0; c < p.n_chunks; ++c) {
       const HeadChunk ch{p.S.idx + static_cast<size_t>(m) * p.L.n_tok, p.S.cnt + m, c * p.g.TC};
+      const int add = (accumulate_dW != 0 || c > 0) ? 1 : 0;
+      if (f32) {
+        ATG_TRY(launch_head_dz(p.g, ch, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, p.dZ, s, nullptr,
+                               m == 0 && c == 0 ? d_hidden : nullptr, hidden_bytes));
+        ATG_TRY(launch_head_grads(p.g, ch, p.dZ, batch->W[m], batch->hidden, d_hidden, dW[m], p.part, add, c == 0 ? 1 : 0, s));
+        continue;
+      }
       ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s));
       HeadGeom gs = p.g;
       gs.TC = p.sub;
@@ -403,8 +412,7 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
         ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub, s));
         ATG_TRY(launch_head_dh(gs, sub, dZ_sub, batch->W[m], p.Wt, d_hidden, p.part, s));
       }
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, batch->hidden, p.hG, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
-                             c == 0 ? 1 : 0, s));
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.hG, dW[m], p.part, add, c == 0 ? 1 : 0, s));
     }
   }
   return AT_GRPO_OK;
@@ -483,7 +491,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
       ATG_TRY(launch_compact_rows(p.g, ch, p.scale, p.dZ, p.perm, p.holes, p.movers, p.live_cnt, p.live_cnt + 1, s));
       ATG_TRY(launch_head_dh(p.g, ch, p.dZ, batch->W[m], p.Wt, d_hidden, p.part, s, p.scale, p.perm, p.live_cnt));
       ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, p.scale, p.perm, p.live_cnt, p.dZ));
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, batch->hidden, p.hG, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.hG, dW[m], p.part, (accumulate_dW != 0 || c > 0) ? 1 : 0,
                              c == 0 ? 1 : 0, s, p.live_cnt));
     }
   }

@@ -367,15 +367,22 @@ __global__ __launch_bounds__(256) void k_lse_combine_f32(const int32_t* __restri
   }
 }
 
-// dZ[t][v] = g_t ([v = y_t] - exp(z - lse_t)), zero in the padding columns V .. Vp
+// dZ[t][v] = g_t ([v = y_t] - exp(z - lse_t)), zero in the padding columns V .. Vp.  With `clear`: the call's first launch also
+// clears d_hidden (n16 pieces of 16 bytes), which the next one writes rows of.
 template <int T>
 __global__ __launch_bounds__(kF32Threads) void k_head_dz(const float* __restrict__ hidden, const float* __restrict__ W,
                                                          const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                                                          int c0, const int32_t* __restrict__ token_id,
                                                          const float* __restrict__ lse, const float* __restrict__ coef,
-                                                         float* __restrict__ dZ, int H, int V, int Vp, int TC) {
+                                                         float* __restrict__ dZ, int H, int V, int Vp, int TC,
+                                                         uint4* __restrict__ clear, int64_t n16) {
   constexpr int kB = F32Tile<T>::kB;
   __shared__ __attribute__((aligned(16))) float lds[F32Tile<T>::kLdsFloats];
+  if (clear) {
+    const int64_t block = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * gridDim.y * kF32Threads;
+    for (int64_t e = block * kF32Threads + threadIdx.x; e < n16; e += stride) clear[e] = make_uint4(0, 0, 0, 0);
+  }
   const int n = chunk_count(cnt, c0, TC);
   const int v0 = blockIdx.x * T, t0 = blockIdx.y * T;
   if (t0 >= n) return;
@@ -412,24 +419,39 @@ __device__ __forceinline__ void part_range(int steps, int part, int parts, int* 
   *s1 = min(*s0 + chunk, steps);
 }
 
+// dHidden and dW of a super-chunk, which only have dZ in common: in one launch where all of their workgroups fit the chip
+// together, since a small step is a chain of short launches (C1: 10.2 and 9.8 us one after the other, 11.7 together; 2.6 and 3.2
+// for the sums of their parts, now 4.0; two heads of 54 rows at H = 480, V = 2746, 664 workgroups: 22.7 and 17.5).  With more of
+// them dW's tiles, which are long, would start unevenly as dHidden's end (16000 rows, H = 256, V = 8000: 577 and 725 us one after
+// the other, 1701 together).
+struct F32Grads {
+  const float* dZ;
+  const float* W;
+  const float* hidden;
+  const int32_t* idx;
+  const int32_t* cnt;
+  float* d_hidden;
+  float* dW;
+  float *part_h, *part_w;      // partial results of dHidden and of dW
+  int c0, H, V, Vp, TC, accumulate, first_chunk;
+  int h_tiles, t_tiles, h_parts;      // of dHidden: tiles along H and along the tokens, parts along k
+  int w_tiles, w_parts;               // of dW: all tiles, parts along k
+  int of_h;                           // tiles of dHidden times parts; 0: the launch has none
+};
+
 // dHidden: A = W columns (h), B = dZ rows (tokens), k = vocabulary.  With one part the result goes to d_hidden, else part p
-// goes to rows p TC .. of `part`.
+// goes to rows p TC .. of `part_h`.
 template <int T>
-__global__ __launch_bounds__(kF32Threads) void k_head_dh(const float* __restrict__ dZ, const float* __restrict__ W,
-                                                         const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                         int c0, float* __restrict__ d_hidden, float* __restrict__ part,
-                                                         int H, int V, int Vp, int TC) {
+__device__ __forceinline__ void dh_tile(const F32Grads& a, int block, int n, float* lds) {
   constexpr int kB = F32Tile<T>::kB;
-  __shared__ __attribute__((aligned(16))) float lds[F32Tile<T>::kLdsFloats];
-  const int n = chunk_count(cnt, c0, TC);
-  const int h0 = blockIdx.x * T, t0 = blockIdx.y * T;
+  const int h0 = block % a.h_tiles * T, t0 = block / a.h_tiles % a.t_tiles * T, z = block / (a.h_tiles * a.t_tiles);
   if (t0 >= n) return;
   int s0, s1;
-  part_range(Vp / kF32StepK, blockIdx.z, gridDim.z, &s0, &s1);
-  auto w_row = [&](int k) { return W + static_cast<size_t>(k) * H + h0; };
-  F32Columns<T, decltype(w_row)> la{w_row, V, H - h0, {}};
+  part_range(a.Vp / kF32StepK, z, a.h_parts, &s0, &s1);
+  auto w_row = [&](int k) { return a.W + static_cast<size_t>(k) * a.H + h0; };
+  F32Columns<T, decltype(w_row)> la{w_row, a.V, a.H - h0, {}};
   F32Rows<T> lb;
-  lb.init([&](int row) { return dZ + static_cast<size_t>(min(t0 + row, n - 1)) * Vp; });
+  lb.init([&](int row) { return a.dZ + static_cast<size_t>(min(t0 + row, n - 1)) * a.Vp; });
   f32x4 acc[kB][kB];
   gemm_f32<T>(acc, la, lb, s0, s1, lds);
   const F32Coord co;
@@ -438,47 +460,29 @@ __global__ __launch_bounds__(kF32Threads) void k_head_dh(const float* __restrict
   for (int j = 0; j < kB; ++j) {
     const int t = t0 + co.wn * (T / 2) + j * 16 + (co.lane & 15);
     if (t >= n) continue;
-    float* out = gridDim.z == 1 ? d_hidden + static_cast<size_t>(idx[c0 + t]) * H
-                                : part + (static_cast<size_t>(blockIdx.z) * TC + t) * H;
+    float* out = a.h_parts == 1 ? a.d_hidden + static_cast<size_t>(a.idx[a.c0 + t]) * a.H
+                                : a.part_h + (static_cast<size_t>(z) * a.TC + t) * a.H;
 #pragma unroll
     for (int i = 0; i < kB; ++i)
-      if (hl + i * 16 < H) *reinterpret_cast<f32x4*>(out + hl + i * 16) = acc[i][j];
-  }
-}
-
-__global__ __launch_bounds__(kF32Threads) void k_head_dh_sum(const float* __restrict__ part, int parts,
-                                                             const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                             int c0, float* __restrict__ d_hidden, int H, int TC) {
-  const int n = chunk_count(cnt, c0, TC);
-  const int64_t all = static_cast<int64_t>(n) * (H / 4), stride = static_cast<int64_t>(TC) * (H / 4);
-  const f32x4* src = reinterpret_cast<const f32x4*>(part);
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(kF32Threads) + threadIdx.x; e < all; e += gridDim.x * static_cast<int64_t>(kF32Threads)) {
-    f32x4 x = src[e];
-    for (int p = 1; p < parts; ++p) x += src[p * stride + e];
-    reinterpret_cast<f32x4*>(d_hidden + static_cast<size_t>(idx[c0 + e / (H / 4)]) * H)[e % (H / 4)] = x;
+      if (hl + i * 16 < a.H) *reinterpret_cast<f32x4*>(out + hl + i * 16) = acc[i][j];
   }
 }
 
 // dW[v][h] (+)= sum_t dZ[t][v] hidden[t][h]: A = hidden columns (gathered rows), B = dZ columns, k = tokens of the chunk.
-// With one part the result goes to dW, else part p goes to rows p V .. of `part`.  The tiles run along the grid's first
-// dimension, those of one vocabulary range side by side (the other dimensions end at 65535).
+// With one part the result goes to dW, else part p goes to rows p V .. of `part_w`.  The tiles of one vocabulary range are side
+// by side.
 template <int T>
-__global__ __launch_bounds__(kF32Threads) void k_head_dw(const float* __restrict__ dZ, const float* __restrict__ hidden,
-                                                         const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                         int c0, float* __restrict__ dW, float* __restrict__ part, int H, int V,
-                                                         int Vp, int TC, int accumulate, int first_chunk) {
+__device__ __forceinline__ void dw_tile(const F32Grads& a, int block, int n, float* lds) {
   constexpr int kB = F32Tile<T>::kB;
-  __shared__ __attribute__((aligned(16))) float lds[F32Tile<T>::kLdsFloats];
-  const int n = chunk_count(cnt, c0, TC);
-  if (n <= 0 && gridDim.z == 1 && !(first_chunk && !accumulate)) return;
-  const int h_tiles = (H + T - 1) / T;
-  const int h0 = static_cast<int>(blockIdx.x) % h_tiles * T, v0 = static_cast<int>(blockIdx.x) / h_tiles * T;
+  if (n <= 0 && a.w_parts == 1 && !(a.first_chunk && !a.accumulate)) return;
+  const int h_tiles = (a.H + T - 1) / T, tile = block % a.w_tiles, z = block / a.w_tiles;
+  const int h0 = tile % h_tiles * T, v0 = tile / h_tiles * T;
   int s0, s1;
-  part_range((n + kF32StepK - 1) / kF32StepK, blockIdx.z, gridDim.z, &s0, &s1);
-  auto h_row = [&](int k) { return hidden + static_cast<size_t>(idx[c0 + k]) * H + h0; };
-  auto z_row = [&](int k) { return dZ + static_cast<size_t>(k) * Vp + v0; };
-  F32Columns<T, decltype(h_row)> la{h_row, n, H - h0, {}};
-  F32Columns<T, decltype(z_row)> lb{z_row, n, Vp - v0, {}};
+  part_range((n + kF32StepK - 1) / kF32StepK, z, a.w_parts, &s0, &s1);
+  auto h_row = [&](int k) { return a.hidden + static_cast<size_t>(a.idx[a.c0 + k]) * a.H + h0; };
+  auto z_row = [&](int k) { return a.dZ + static_cast<size_t>(k) * a.Vp + v0; };
+  F32Columns<T, decltype(h_row)> la{h_row, n, a.H - h0, {}};
+  F32Columns<T, decltype(z_row)> lb{z_row, n, a.Vp - v0, {}};
   f32x4 acc[kB][kB];
   gemm_f32<T>(acc, la, lb, s0, s1, lds);
   const F32Coord co;
@@ -486,26 +490,48 @@ __global__ __launch_bounds__(kF32Threads) void k_head_dw(const float* __restrict
 #pragma unroll
   for (int j = 0; j < kB; ++j) {
     const int v = v0 + co.wn * (T / 2) + j * 16 + (co.lane & 15);
-    if (v >= V) continue;
-    float* out = gridDim.z == 1 ? dW + static_cast<size_t>(v) * H : part + (static_cast<size_t>(blockIdx.z) * V + v) * H;
-    const bool add = gridDim.z == 1 && accumulate;
+    if (v >= a.V) continue;
+    float* out = a.w_parts == 1 ? a.dW + static_cast<size_t>(v) * a.H : a.part_w + (static_cast<size_t>(z) * a.V + v) * a.H;
+    const bool add = a.w_parts == 1 && a.accumulate;
 #pragma unroll
     for (int i = 0; i < kB; ++i)
-      if (hl + i * 16 < H) {
+      if (hl + i * 16 < a.H) {
         f32x4_any* o = reinterpret_cast<f32x4_any*>(out + hl + i * 16);
         *o = add ? *o + acc[i][j] : acc[i][j];
       }
   }
 }
 
-__global__ __launch_bounds__(kF32Threads) void k_head_dw_sum(const float* __restrict__ part, int parts, float* __restrict__ dW,
-                                                             int64_t n4, int accumulate) {
-  const f32x4* src = reinterpret_cast<const f32x4*>(part);
-  f32x4_any* dst = reinterpret_cast<f32x4_any*>(dW);
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(kF32Threads) + threadIdx.x; e < n4; e += gridDim.x * static_cast<int64_t>(kF32Threads)) {
+// the first a.of_h workgroups have a tile of dHidden each, the others one of dW
+template <int T>
+__global__ __launch_bounds__(kF32Threads) void k_head_grads(F32Grads a) {
+  __shared__ __attribute__((aligned(16))) float lds[F32Tile<T>::kLdsFloats];
+  const int n = chunk_count(a.cnt, a.c0, a.TC), block = blockIdx.x;
+  if (block < a.of_h) dh_tile<T>(a, block, n, lds);
+  else dw_tile<T>(a, block - a.of_h, n, lds);
+}
+
+// adds the parts up: the first h_blocks workgroups those of dHidden, the others those of dW
+__global__ __launch_bounds__(kF32Threads) void k_head_grads_sum(F32Grads a, int h_blocks) {
+  const f32x4* src;
+  if (static_cast<int>(blockIdx.x) < h_blocks) {
+    const int64_t row = a.H / 4, all = chunk_count(a.cnt, a.c0, a.TC) * row, stride = a.TC * row;
+    src = reinterpret_cast<const f32x4*>(a.part_h);
+    for (int64_t e = blockIdx.x * static_cast<int64_t>(kF32Threads) + threadIdx.x; e < all; e += h_blocks * static_cast<int64_t>(kF32Threads)) {
+      f32x4 x = src[e];
+      for (int p = 1; p < a.h_parts; ++p) x += src[p * stride + e];
+      reinterpret_cast<f32x4*>(a.d_hidden + static_cast<size_t>(a.idx[a.c0 + e / row]) * a.H)[e % row] = x;
+    }
+    return;
+  }
+  const int64_t n4 = static_cast<int64_t>(a.V) * a.H / 4;
+  const int64_t threads = (gridDim.x - h_blocks) * static_cast<int64_t>(kF32Threads);
+  src = reinterpret_cast<const f32x4*>(a.part_w);
+  f32x4_any* dst = reinterpret_cast<f32x4_any*>(a.dW);
+  for (int64_t e = (blockIdx.x - h_blocks) * static_cast<int64_t>(kF32Threads) + threadIdx.x; e < n4; e += threads) {
     f32x4 x = src[e];
-    for (int p = 1; p < parts; ++p) x += src[p * n4 + e];
-    dst[e] = accumulate ? dst[e] + x : x;
+    for (int p = 1; p < a.w_parts; ++p) x += src[p * n4 + e];
+    dst[e] = a.accumulate ? dst[e] + x : x;
   }
 }
 
@@ -536,10 +562,13 @@ unsigned sum_blocks(int64_t n4) {
 
 }  // namespace
 
+static size_t part_h_bytes(const HeadGeom& g) {
+  const int parts = dh_parts(g);
+  return parts > 1 ? round_up(static_cast<size_t>(parts) * g.TC * g.H * 4, 256) : 0;
+}
 size_t partial_bytes_f32(const HeadGeom& g) {
-  const int a = dh_parts(g), b = dw_parts(g);
-  const size_t dh = a > 1 ? static_cast<size_t>(a) * g.TC * g.H * 4 : 0, dw = b > 1 ? static_cast<size_t>(b) * g.V * g.H * 4 : 0;
-  return dh > dw ? dh : dw;
+  const int parts = dw_parts(g);
+  return part_h_bytes(g) + (parts > 1 ? static_cast<size_t>(parts) * g.V * g.H * 4 : 0);
 }
 
 int launch_fwd_f32(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
@@ -563,68 +592,69 @@ int launch_lse_combine_f32(const HeadGeom& g, const HeadChunk& ch, const float* 
 
 template <int T>
 static void dz_t(const HeadGeom& g, const HeadChunk& ch, const float* hidden, const float* W, const int32_t* token_id,
-                 const float* lse, const float* coef, float* dZ, hipStream_t s) {
+                 const float* lse, const float* coef, float* dZ, uint4* clear, int64_t n16, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(ceil_div(g.V, T)), static_cast<unsigned>(ceil_div(g.TC, T)));
   hipLaunchKernelGGL(k_head_dz<T>, grid, dim3(kF32Threads), 0, s, hidden, W, ch.idx, ch.cnt, ch.c0, token_id, lse, coef, dZ,
-                     g.H, g.V, g.Vp, g.TC);
+                     g.H, g.V, g.Vp, g.TC, clear, n16);
 }
 
 int launch_dz_f32(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
-                  const float* lse, const float* coef, void* dZ, hipStream_t s) {
+                  const float* lse, const float* coef, void* dZ, void* clear, int64_t n_bytes, hipStream_t s) {
   const float* h = static_cast<const float*>(hidden);
   const float* w = static_cast<const float*>(W);
-  if (pick_tile(g.V, g.TC) == 128) dz_t<128>(g, ch, h, w, token_id, lse, coef, static_cast<float*>(dZ), s);
-  else dz_t<64>(g, ch, h, w, token_id, lse, coef, static_cast<float*>(dZ), s);
+  float* z = static_cast<float*>(dZ);
+  uint4* c = static_cast<uint4*>(clear);
+  if (pick_tile(g.V, g.TC) == 128) dz_t<128>(g, ch, h, w, token_id, lse, coef, z, c, n_bytes / 16, s);
+  else dz_t<64>(g, ch, h, w, token_id, lse, coef, z, c, n_bytes / 16, s);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
 
-template <int T>
-static void dh_t(const HeadGeom& g, const HeadChunk& ch, const float* dZ, const float* W, float* d_hidden, float* part, int parts,
-                 hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(ceil_div(g.H, T)), static_cast<unsigned>(ceil_div(g.TC, T)), parts);
-  hipLaunchKernelGGL(k_head_dh<T>, grid, dim3(kF32Threads), 0, s, dZ, W, ch.idx, ch.cnt, ch.c0, d_hidden, part, g.H, g.V,
-                     g.Vp, g.TC);
-}
-
-int launch_dh_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, void* d_hidden, void* part,
-                  hipStream_t s) {
-  const int parts = dh_parts(g);
-  const float* z = static_cast<const float*>(dZ);
-  const float* w = static_cast<const float*>(W);
-  float* out = static_cast<float*>(d_hidden);
-  float* pt = static_cast<float*>(part);
-  if (pick_tile(g.H, g.TC) == 128) dh_t<128>(g, ch, z, w, out, pt, parts, s);
-  else dh_t<64>(g, ch, z, w, out, pt, parts, s);
-  ATG_LAUNCH_CHECK();
-  if (parts > 1) {
-    hipLaunchKernelGGL(k_head_dh_sum, dim3(sum_blocks(static_cast<int64_t>(g.TC) * g.H / 4)), dim3(kF32Threads), 0, s, pt,
-                       parts, ch.idx, ch.cnt, ch.c0, out, g.H, g.TC);
+int launch_grads_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* hidden, void* d_hidden,
+                     float* dW, void* part, int accumulate, int first_chunk, hipStream_t s) {
+  const int th = pick_tile(g.H, g.TC), tw = pick_tile(g.H, g.V);
+  F32Grads a{};
+  a.dZ = static_cast<const float*>(dZ);
+  a.W = static_cast<const float*>(W);
+  a.hidden = static_cast<const float*>(hidden);
+  a.idx = ch.idx;
+  a.cnt = ch.cnt;
+  a.d_hidden = static_cast<float*>(d_hidden);
+  a.dW = dW;
+  a.part_h = static_cast<float*>(part);
+  a.part_w = reinterpret_cast<float*>(static_cast<char*>(part) + part_h_bytes(g));
+  a.c0 = ch.c0;
+  a.H = g.H;
+  a.V = g.V;
+  a.Vp = g.Vp;
+  a.TC = g.TC;
+  a.accumulate = accumulate;
+  a.first_chunk = first_chunk;
+  a.h_tiles = static_cast<int>(ceil_div(g.H, th));
+  a.t_tiles = static_cast<int>(ceil_div(g.TC, th));
+  a.h_parts = dh_parts(g);
+  const int64_t w_tiles = ceil_div(g.H, tw) * ceil_div(g.V, tw);
+  a.w_tiles = static_cast<int>(w_tiles);
+  a.w_parts = dw_parts(g);
+  const int64_t of_h = static_cast<int64_t>(a.h_tiles) * a.t_tiles * a.h_parts, of_w = w_tiles * a.w_parts;
+  a.of_h = static_cast<int>(of_h);
+  const auto launch = [&](int T, int64_t blocks) {
+    auto k = T == 128 ? k_head_grads<128> : k_head_grads<64>;
+    hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(blocks)), dim3(kF32Threads), 0, s, a);
+  };
+  if (th == 64 && tw == 64 && of_h + of_w <= 3 * device_cu_count()) {      // three workgroups of 64 x 64 tiles fit a compute unit
+    launch(64, of_h + of_w);
+  } else {
+    launch(th, of_h);
     ATG_LAUNCH_CHECK();
+    a.of_h = 0;
+    launch(tw, of_w);
   }
-  return AT_GRPO_OK;
-}
-
-template <int T>
-static void dw_t(const HeadGeom& g, const HeadChunk& ch, const float* dZ, const float* hidden, float* dW, float* part, int parts,
-                 int accumulate, int first_chunk, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(ceil_div(g.H, T) * ceil_div(g.V, T)), 1, parts);
-  hipLaunchKernelGGL(k_head_dw<T>, grid, dim3(kF32Threads), 0, s, dZ, hidden, ch.idx, ch.cnt, ch.c0, dW, part, g.H, g.V, g.Vp,
-                     g.TC, accumulate, first_chunk);
-}
-
-int launch_dw_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hidden, float* dW, void* part,
-                  int accumulate, int first_chunk, hipStream_t s) {
-  const int parts = dw_parts(g);
-  const float* z = static_cast<const float*>(dZ);
-  const float* h = static_cast<const float*>(hidden);
-  float* pt = static_cast<float*>(part);
-  if (pick_tile(g.H, g.V) == 128) dw_t<128>(g, ch, z, h, dW, pt, parts, accumulate, first_chunk, s);
-  else dw_t<64>(g, ch, z, h, dW, pt, parts, accumulate, first_chunk, s);
   ATG_LAUNCH_CHECK();
-  if (parts > 1) {
-    const int64_t n4 = static_cast<int64_t>(g.V) * g.H / 4;
-    hipLaunchKernelGGL(k_head_dw_sum, dim3(sum_blocks(n4)), dim3(kF32Threads), 0, s, pt, parts, dW, n4, accumulate);
+  const unsigned hb = a.h_parts > 1 ? sum_blocks(static_cast<int64_t>(g.TC) * g.H / 4) : 0;
+  const unsigned wb = a.w_parts > 1 ? sum_blocks(static_cast<int64_t>(g.V) * g.H / 4) : 0;
+  if (hb + wb > 0) {
+    hipLaunchKernelGGL(k_head_grads_sum, dim3(hb + wb), dim3(kF32Threads), 0, s, a, static_cast<int>(hb));
     ATG_LAUNCH_CHECK();
   }
   return AT_GRPO_OK;

@@ -14,10 +14,9 @@ int launch_fwd_f32(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
 int launch_lse_combine_f32(const HeadGeom& g, const HeadChunk& ch, const float* part_m, const float* part_s, const float* part_u,
                            const float* zy, float* logp, float* lse, float* entropy, hipStream_t s);
 int launch_dz_f32(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W, const int32_t* token_id,
-                  const float* lse, const float* coef, void* dZ, hipStream_t s);
-int launch_dh_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, void* d_hidden, void* part,
-                  hipStream_t s);
-int launch_dw_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hidden, float* dW, void* part,
-                  int accumulate, int first_chunk, hipStream_t s);
+                  const float* lse, const float* coef, void* dZ, void* clear, int64_t clear_bytes, hipStream_t s);
+// dHidden and dW
+int launch_grads_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* hidden, void* d_hidden,
+                     float* dW, void* part, int accumulate, int first_chunk, hipStream_t s);
 
 }  // namespace atg

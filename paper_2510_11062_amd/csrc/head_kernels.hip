@@ -379,10 +379,10 @@ int launch_gather_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hid
 
 int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                    const int32_t* token_id, const float* lse, const float* coef, void* dZ,
-                   hipStream_t s, const int32_t* gate) {
+                   hipStream_t s, const int32_t* gate, void* clear, int64_t clear_bytes) {
   ProfScope ps(PROF_HEAD_DZ, s);
   if (g.dtype == AT_GRPO_BF16) return launch_dz_bf16(g, ch, hidden, W, token_id, lse, coef, dZ, s, gate);
-  return launch_dz_f32(g, ch, hidden, W, token_id, lse, coef, dZ, s);
+  return launch_dz_f32(g, ch, hidden, W, token_id, lse, coef, dZ, clear, clear_bytes, s);
 }
 
 int launch_ref_logit(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
@@ -433,15 +433,21 @@ size_t head_partial_bytes(const HeadGeom& g) {
 int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* Wt, void* d_hidden,
                    void* part, hipStream_t s, const float* scale, const int32_t* perm, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DH, s);
-  if (g.dtype == AT_GRPO_BF16) return launch_dh_bf16(g, ch, dZ, W, Wt, d_hidden, part, s, scale, perm, live_cnt);
-  return launch_dh_f32(g, ch, dZ, W, d_hidden, part, s);
+  if (g.dtype != AT_GRPO_BF16) return AT_GRPO_EUNSUPPORTED;
+  return launch_dh_bf16(g, ch, dZ, W, Wt, d_hidden, part, s, scale, perm, live_cnt);
 }
 
-int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hidden, const void* hG,
-                   float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
+int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt) {
   ProfScope ps(PROF_HEAD_DW, s);
-  if (g.dtype == AT_GRPO_BF16) return launch_dw_bf16(g, ch, dZ, hG, dW, part, accumulate, first_chunk, s, live_cnt);
-  return launch_dw_f32(g, ch, dZ, hidden, dW, part, accumulate, first_chunk, s);
+  if (g.dtype != AT_GRPO_BF16) return AT_GRPO_EUNSUPPORTED;
+  return launch_dw_bf16(g, ch, dZ, hG, dW, part, accumulate, first_chunk, s, live_cnt);
+}
+
+int launch_head_grads(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* hidden, void* d_hidden,
+                      float* dW, void* part, int accumulate, int first_chunk, hipStream_t s) {
+  ProfScope ps(PROF_HEAD_DH, s);
+  if (g.dtype == AT_GRPO_BF16) return AT_GRPO_EUNSUPPORTED;
+  return launch_grads_f32(g, ch, dZ, W, hidden, d_hidden, dW, part, accumulate, first_chunk, s);
 }
 
 }  // namespace atg

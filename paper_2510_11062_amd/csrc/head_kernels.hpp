@@ -57,10 +57,11 @@ int launch_gather_hidden(const HeadGeom& g, const HeadChunk& ch, const void* hid
                          const int32_t* perm = nullptr, const int32_t* live_cnt = nullptr,
                          void* E = nullptr);
 
-// dZ[TC][Vp] for this super-chunk (element type of hidden).
+// dZ[TC][Vp] for this super-chunk (element type of hidden).  fp32: the launch also sets clear_bytes (a multiple of 16) of
+// `clear` to zero, whatever the list holds.
 int launch_head_dz(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                    const int32_t* token_id, const float* lse, const float* coef, void* dZ,
-                   hipStream_t s, const int32_t* gate = nullptr);
+                   hipStream_t s, const int32_t* gate = nullptr, void* clear = nullptr, int64_t clear_bytes = 0);
 
 // Scratch for the partial tiles of launch_head_dh / launch_head_dw over g.TC rows.
 size_t head_partial_bytes(const HeadGeom& g);
@@ -83,7 +84,7 @@ int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const fl
                       const float* zy, const int32_t* token_id, const CoefArgs& ca, float* logp, float* lse,
                       float* scale, void* E, int32_t* gate, hipStream_t s);
 
-// d_hidden[row] = dZ[j] . W for the rows of this super-chunk.
+// bf16: d_hidden[row] = dZ[j] . W for the rows of this super-chunk.
 // With `scale`, row j of the result is multiplied by scale[j] (j counted from ch.c0).  With `perm` (after
 // launch_compact_rows), the first *live_cnt rows of dZ are contracted and row j goes to list position perm[j].
 // `part`: head_partial_bytes() of scratch (partial results of contractions split along k).
@@ -98,9 +99,12 @@ int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
 int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* scale, void* E, int32_t* perm,
                         int32_t* holes, int32_t* movers, int32_t* live_cnt, int32_t* pair_cnt, hipStream_t s);
 
-// dW[V][H] (+)= dZ^T . hidden rows.  first_chunk: runs even for an empty list so that dW is defined.
-// bf16 with `live_cnt`: only the first *live_cnt rows of the chunk are contracted.
-int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hidden, const void* hG,
-                   float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt = nullptr);
+// bf16: dW[V][H] (+)= dZ^T . hidden rows.  first_chunk: runs even for an empty list so that dW is defined.
+// With `live_cnt`: only the first *live_cnt rows of the chunk are contracted.
+int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* hG, float* dW, void* part, int accumulate, int first_chunk, hipStream_t s, const int32_t* live_cnt = nullptr);
+
+// fp32: both of them, in one launch.
+int launch_head_grads(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* hidden, void* d_hidden,
+                      float* dW, void* part, int accumulate, int first_chunk, hipStream_t s);
 
 }  // namespace atg
