@@ -13,6 +13,7 @@
 //                back in response order.
 //   k_ga_hist .. anything else (very many keys per response, or few keys with very many members): histogram over the key
 //                box, scans, scatter, finish.
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
@@ -384,9 +385,9 @@ __device__ __forceinline__ void fill_tails(const GaOut& o, int G, int n_listed, 
 // off(n) the end of the last.  The groups are shared by `parts` workgroups of 256 threads (a thread per small group) or by
 // `waves` wavefronts (one per larger group).
 template <typename Off>
-__device__ __forceinline__ void finish_small_groups(int n, int g0, int part, int parts, Off off, const int32_t* arrival,
+__device__ __forceinline__ void finish_small_groups(int n, int g0, int part, int parts, int t, Off off, const int32_t* arrival,
                                                     const float* reward, const GaStat& st, const GaOut& o) {
-  for (int g = part * 256 + static_cast<int>(threadIdx.x); g < n; g += parts * 256) {
+  for (int g = part * 256 + t; g < n; g += parts * 256) {
     const int from = off(g), members = off(g + 1) - from;
     if (members > kSmallGroup) continue;
     float mean, sd;
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(256) void k_ga_left(int n_blocks, const int32_t* __
     if (n == 0) continue;
     const int g0 = left[2 * b + 1];
     auto off = [&](int g) { return o.seg_offsets[g0 + g]; };
-    finish_small_groups(n, g0, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), off, arrival, reward, st, o);
+    finish_small_groups(n, g0, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), threadIdx.x, off, arrival, reward, st, o);
     finish_large_groups(n, g0, static_cast<int>(blockIdx.x * 256 + threadIdx.x) >> 6, static_cast<int>(gridDim.x) * 4, off, arrival,
                         reward, st, o);
   }
@@ -686,15 +687,15 @@ __global__ __launch_bounds__(256) void k_ga_left(int n_blocks, const int32_t* __
 // (2^22 shuffled responses: 440 us on the stream).  Instead the responses are partitioned by key range ("bins" of 3072 to 4096
 // responses) with LDS counters, so that every run written is a few entries long; each bin is finished by one workgroup in
 // LDS; and one last pass in response order gathers the results, again in runs.  About 84 bytes per response, all streamed.
-// Whole calls in groups of 8, shuffled and in rollout order (in brackets: the histogram path): 2^20 responses 71 and 50 us (113
-// and 57), 2^22 226 and 113 (454 and 120), 2^24 1043 and 401 (2054 and 453).
+// Whole calls in groups of 8, shuffled and in rollout order (in brackets: the histogram path): 2^20 responses 69 and 47 us (113
+// and 57), 2^22 159 and 118 (454 and 120), 2^24 614 and 400 (2054 and 453).
 //
 // How many responses a bin has depends on where the ids lie in their extents, which only the device sees.  Bins that do not
 // fit LDS (a pool from a part of the extents, say) are therefore not left to one workgroup: from the partition on their
 // responses go the way of the histogram path (ranks from global counters, member lists by group, groups shared by the whole
 // grid), inside the launches that the other bins need anyway.  262144 responses in groups of 128 that lie in one bin of
 // 2^19 keys: 8275 us by one workgroup, 57 now; in groups of 8 from a quarter of their extents, in rollout order and shuffled: 2^20
-// responses 104 and 138 us by a workgroup per bin, 57 and 119 now, 2^22 176 and 351, now 131 and 437 (130 and 461 by histogram).
+// responses 104 and 138 us by a workgroup per bin, 54 and 115 now, 2^22 176 and 351, now 126 and 441 (130 and 461 by histogram).
 // ------------------------------------------------------------------------------------------------
 constexpr int kPoolThreads = 1024;       // of a partitioning workgroup
 constexpr int kPoolMaxBins = 4096, kPoolMinBins = 256, kPoolRound = 512;
@@ -702,19 +703,28 @@ constexpr int kPoolPerBin = 4096, kPoolFewPerBin = 3072;      // responses per b
 constexpr int kPoolMaxKeys = 2048;       // keys of a bin
 constexpr int kPoolCap = 6016;           // responses of a bin that fit its lists; a bin with more is "large"
 constexpr int kBinThreads = 512, kBinPer = (kPoolCap + kBinThreads - 1) / kBinThreads;
+static_assert(kPoolMaxKeys <= kPoolCap, "a large bin has more responses than keys");
 static_assert(kPoolCap < 65536 && kPoolMaxKeys < 32768, "place and group share a word");
 constexpr int kLargeBlocks = 1024;       // workgroups that finish the groups of the large bins (2^22 responses in 342 large bins:
                                          // 148 us, with 512 workgroups 170)
+
+constexpr int kTicketBins = 32;    // bins that draw tickets from one counter (one for all: 446 us instead of 441 where all bins are large)
+constexpr int kSortPer = 16;       // responses per thread of the pools whose blocks are sorted
+constexpr int kSortUsed = kPoolThreads * kSortPer / 64;      // bins that a sorted block uses at the least (runs of 64)
 
 struct PoolPlan {
   int width, bins;           // bin of a key = key / width
   int per;                   // responses per thread of a partitioning workgroup, a multiple of 4
   int32_t* key;              // [R]
-  int32_t* slot;             // [R] place of the response in the partitioned order; of a large bin: bit 31 and rank inside its group
+  int32_t* slot;             // [R] place of the response in the partitioned order; of a large bin: bit 31 and rank inside its group.
+                             // Of a sorted block (see k_gp_partition): places of its responses in ascending order
+  uint16_t* member;          // [R] of a sorted block: which response of the block has that place
+  int32_t* sorted;           // [blocks] of a sorted block (one that may be one, before it is partitioned): its responses with a key (0),
+                             // else -1
   int32_t* list;             // [R] members of the large bins, by group
-  int32_t* hist;             // [keys] of a large bin: members, then the first one's place in `list`
-  int32_t* gid_of_key;       // [keys] of a large bin: group inside the bin
-  int2* kr;                  // [R] (key, response), partitioned
+  int32_t* hist;             // [keys] of a large bin: members
+  int2* kr;                  // [R] (key, response), partitioned.  Of a large bin: (first member's place in `list`, group inside the bin)
+                             // of its keys in turn, which are fewer than its responses
   float* x;                  // [R] rewards, partitioned
   float2* result;            // [R] (advantage, group inside the bin), partitioned
   float4* stats;             // [R] (mean, std, best, offset) of group i of the bin at bin_base + i
@@ -724,6 +734,7 @@ struct PoolPlan {
   int32_t* cursor;           // [bins] of a large bin: has it groups of more than kSmallGroup?
   int32_t* bin_groups;       // [bins]
   int32_t* gid_base;         // [bins + 1]
+  int32_t* bins_done;        // workgroups of k_gp_bin that have counted their groups: [1 + i] of the bins of i in turn, [0] full ones
   int32_t* large;            // [bins + 1] number of large bins, then which ones they are
 };
 
@@ -747,6 +758,7 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_init(int32_t* __restrict__ 
 
 __global__ __launch_bounds__(kPoolThreads) void k_gp_count(GaArgs a, GaMix mix, PoolPlan p, int32_t* __restrict__ err) {
   __shared__ int hist[kPoolMaxBins];
+  __shared__ int used;
   for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) hist[i] = 0;
   __syncthreads();
   const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kPoolThreads * p.per + threadIdx.x;
@@ -768,28 +780,38 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_count(GaArgs a, GaMix mix, 
     }
   }
   if (bad) atomicOr(err, bad);
+  if (threadIdx.x == 0) used = 0;
   __syncthreads();
+  int mine = 0;
   for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) {
     const int c = hist[i];
     p.blk[static_cast<size_t>(blockIdx.x) * p.bins + i] = c;
     if (c) atomicAdd(&p.bin_cnt[i], c);
+    mine += c ? 1 : 0;
+  }
+  if (p.per == kSortPer) {
+    if (mine) atomicAdd(&used, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) p.sorted[blockIdx.x] = used >= kSortUsed ? 0 : -1;
   }
 }
 
-// exclusive scan of n <= 4096 counts by one workgroup; out[n] = total
-__device__ __forceinline__ void scan_small(const int32_t* in, int n, int32_t* out, int32_t* out2, int* lds16) {
-  int v[kPoolMaxBins / kPoolThreads], sum = 0;
+// exclusive scan of n <= kPoolMaxBins counts `in(i)` by one workgroup of NT threads; out[n] = total, which is returned
+template <int NT, typename In>
+__device__ __forceinline__ int scan_small(In in, int n, int32_t* out, int32_t* out2, int* lds) {
+  constexpr int kPer = kPoolMaxBins / NT;
+  int v[kPer], sum = 0;
 #pragma unroll
-  for (int e = 0; e < kPoolMaxBins / kPoolThreads; ++e) {
-    const int i = threadIdx.x * (kPoolMaxBins / kPoolThreads) + e;
-    v[e] = i < n ? in[i] : 0;
+  for (int e = 0; e < kPer; ++e) {
+    const int i = threadIdx.x * kPer + e;
+    v[e] = i < n ? in(i) : 0;
     sum += v[e];
   }
   int total;
-  int at = block_exclusive_scan<kPoolThreads>(sum, lds16, &total);
+  int at = block_exclusive_scan<NT>(sum, lds, &total);
 #pragma unroll
-  for (int e = 0; e < kPoolMaxBins / kPoolThreads; ++e) {
-    const int i = threadIdx.x * (kPoolMaxBins / kPoolThreads) + e;
+  for (int e = 0; e < kPer; ++e) {
+    const int i = threadIdx.x * kPer + e;
     if (i < n) {
       out[i] = at;
       if (out2) out2[i] = at;
@@ -797,6 +819,7 @@ __device__ __forceinline__ void scan_small(const int32_t* in, int n, int32_t* ou
     at += v[e];
   }
   if (threadIdx.x == 0) out[n] = total;
+  return total;
 }
 
 // workgroup 0: bases of the bins, list of the large ones; the others clear the counters of the large bins' keys, a wavefront per
@@ -808,7 +831,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_bases(PoolPlan p, int64_t n
   __shared__ int n_large;
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) n_large = 0;
-    scan_small(p.bin_cnt, p.bins, p.bin_base, p.cursor, lds16);
+    if (threadIdx.x <= kPoolMaxBins / kTicketBins) p.bins_done[threadIdx.x] = 0;
+    scan_small<kPoolThreads>([&](int i) { return p.bin_cnt[i]; }, p.bins, p.bin_base, p.cursor, lds16);
     __syncthreads();
     for (int i = threadIdx.x; i < p.bins; i += kPoolThreads)
       if (p.bin_cnt[i] > kPoolCap) p.large[1 + atomicAdd(&n_large, 1)] = i;
@@ -822,8 +846,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_bases(PoolPlan p, int64_t n
   for (int64_t k = lo + (threadIdx.x & 63); k < end; k += 64) p.hist[k] = 0;
 }
 
-__global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const float* __restrict__ reward, PoolPlan p) {
-  __shared__ int next[kPoolMaxBins];
+// every response of the block stored where it belongs; next: [bins] in LDS
+__device__ __forceinline__ void partition_block(int n_resp, const float* __restrict__ reward, const PoolPlan& p, int* next) {
   for (int i = threadIdx.x; i < p.bins; i += kPoolThreads) {
     const int c = p.blk[static_cast<size_t>(blockIdx.x) * p.bins + i];
     next[i] = c == 0 ? 0 : (p.bin_cnt[i] > kPoolCap ? INT32_MIN : atomicAdd(&p.cursor[i], c));   // places in large bins: below zero
@@ -859,24 +883,159 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const
   }
 }
 
+// A block of the largest pools whose responses lie in many bins (shuffled, it has 16 responses per bin): stored one by one where
+// they belong, the lanes' stores would reach 1024 places a run apart, each a little at a time, and the L2 of an XCD does not hold
+// the lines that its 32 workgroups have begun.  Such a block is sorted by bin in LDS first, and leaves field by field in whole
+// runs; its results come back the same way (k_gp_turn).  Shuffled pools in groups of 8, partition and results in response order:
+// 2^22 93 + 55 us one by one, 48 + 30 sorted; 2^24 524 + 279 and 222 + 149.  Bound by the latency of its passes through LDS, one
+// workgroup on each compute unit.  Other blocks gain nothing: in rollout order consecutive lanes have consecutive places, and
+// blocks with members of large bins rank them one by one in any case.  Pools of less than 2.4 million have fewer responses per
+// block, and runs that stay in L2 (2^20 shuffled: 20 us, 31 sorted).
+// ALL: blocks that are not sorted are done here too; otherwise they are left to k_gp_partition, which takes two workgroups per
+// compute unit where this one's LDS leaves room for one (2^24 in rollout order: 69 us, here 100).
+template <bool ALL>
+__global__ __launch_bounds__(kPoolThreads) void k_gp_partition_sorted(int n_resp, const float* __restrict__ reward, PoolPlan p) {
+  constexpr int PER = kSortPer, B = kPoolThreads * PER;
+  extern __shared__ __attribute__((aligned(16))) int lds[];
+  __shared__ int lds16[16];
+  int* place = lds;                // [B]
+  int* field = lds + B;            // [B]; until the places are known: distance of a bin's places from its local ones
+  int* next = lds + 2 * B;         // [bins]
+  const int tid = threadIdx.x;
+  if (p.sorted[blockIdx.x] < 0) {
+    if (ALL) partition_block(n_resp, reward, p, next);
+    return;
+  }
+  const int32_t* blk = p.blk + static_cast<size_t>(blockIdx.x) * p.bins;
+  const int64_t block0 = static_cast<int64_t>(blockIdx.x) * B, r0 = block0 + tid;
+  // each thread owns a run of bins
+  constexpr int kPer = kPoolMaxBins / kPoolThreads;
+  int c[kPer], members = 0;
+  bool large = false;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid * kPer + e;
+    c[e] = i < p.bins ? blk[i] : 0;
+    members += c[e];
+    large = large || (c[e] > 0 && p.bin_cnt[i] > kPoolCap);
+  }
+  if (__syncthreads_or(large)) {
+    if (tid == 0) p.sorted[blockIdx.x] = -1;
+    if (ALL) partition_block(n_resp, reward, p, next);
+    return;
+  }
+  int key[PER];
+  float x[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t r = r0 + u * kPoolThreads;
+    key[u] = r < n_resp ? p.key[r] : -1;
+    x[u] = r < n_resp ? reward[r] : 0.f;
+  }
+  int total;
+  int at = block_exclusive_scan<kPoolThreads>(members, lds16, &total);
+  if (tid == 0) p.sorted[blockIdx.x] = total;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid * kPer + e;
+    if (i >= p.bins) continue;
+    next[i] = at;
+    if (c[e] > 0) field[i] = atomicAdd(&p.cursor[i], c[e]) - at;
+    at += c[e];
+  }
+  __syncthreads();
+  int local[PER];                  // place inside the block, in the order of the bins
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    local[u] = -1;
+    if (key[u] < 0) continue;
+    const int bin = static_cast<int>(static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width));
+    local[u] = atomicAdd(&next[bin], 1);
+    place[local[u]] = local[u] + field[bin];
+  }
+  __syncthreads();
+  int to[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = tid + i * kPoolThreads;
+    to[i] = j < total ? place[j] : -1;
+    if (j >= total && block0 + j < n_resp) p.slot[block0 + j] = 0;      // not a place in a large bin
+  }
+  // one field after the other goes through LDS into that order and out
+  auto leave = [&](auto value, auto put) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (local[u] >= 0) field[local[u]] = value(u);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (to[i] >= 0) put(i, to[i], field[tid + i * kPoolThreads]);
+    __syncthreads();
+  };
+  leave([&](int u) { return __float_as_int(x[u]); }, [&](int, int t, int v) { p.x[t] = __int_as_float(v); });
+  int k_out[PER];
+  leave([&](int u) { return key[u]; }, [&](int i, int, int v) { k_out[i] = v; });
+  leave([&](int u) { return tid + u * kPoolThreads; },
+        [&](int i, int t, int v) {
+          const int64_t j = block0 + tid + i * kPoolThreads;
+          p.kr[t] = make_int2(k_out[i], static_cast<int>(block0) + v);
+          p.slot[j] = t;
+          p.member[j] = static_cast<uint16_t>(v);
+        });
+}
+
+// sorted: blocks that k_gp_partition_sorted has done are skipped
+__global__ __launch_bounds__(kPoolThreads) void k_gp_partition(int n_resp, const float* __restrict__ reward, PoolPlan p, int sorted) {
+  __shared__ int next[kPoolMaxBins];
+  if (sorted && p.sorted[blockIdx.x] >= 0) return;
+  partition_block(n_resp, reward, p, next);
+}
+
 // Place of list entry f in LDS.  A thread walks its own group, so 64 lanes read entries that lie a group's size apart; groups of
 // 8 would meet in 8 of the 64 banks.
 __device__ __forceinline__ int bin_at(int f) { return f ^ ((f >> 6) & 7); }
 static_assert(kPoolCap % 8 == 0, "entries move inside blocks of eight");
 
-__global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float* __restrict__ reward, GaStat st, int64_t n_keys,
+__global__ __launch_bounds__(kBinThreads, 4) void k_gp_bin(PoolPlan p, const float* __restrict__ reward, GaStat st, int64_t n_keys,
                                                         GaOut o) {
   __shared__ int list_id[kPoolCap];
   __shared__ float list_x[kPoolCap];
   __shared__ int count[kPoolMaxKeys], next[kPoolMaxKeys];
   __shared__ uint16_t gid[kPoolMaxKeys];
   __shared__ int wsum[2][kBinThreads / 64];
+  __shared__ int last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int bin = blockIdx.x, base = p.bin_base[bin], m = p.bin_base[bin + 1] - base;
   const int lo = bin * p.width;
   const int own = static_cast<int>(min(static_cast<int64_t>(p.width), n_keys - lo));
+  // The workgroup that is the last to have counted its bin's groups turns the counts into ids of first groups: 3 to 5 us in this
+  // launch, where one of its own took 6.5 and its gap.  The counts pass between the XCDs' caches as atomics; the exchange has returned before the ticket is drawn.
+  int before = 0, ticket = 0;
+  auto publish = [&](int n_groups) { if (tid == 0) before = atomicExch(&p.bin_groups[bin], n_groups); };
+  auto draw = [&] {
+    if (tid != 0) return;
+    asm volatile("" : "+v"(before));
+    ticket = atomicAdd(&p.bins_done[1 + bin / kTicketBins], 1);
+  };
+  auto scan_if_last = [&] {
+    if (tid == 0) {
+      const int first = bin / kTicketBins * kTicketBins;
+      last = ticket == min(kTicketBins, p.bins - first) - 1 &&
+             atomicAdd(p.bins_done, 1) == (p.bins + kTicketBins - 1) / kTicketBins - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    const int G = scan_small<kBinThreads>(
+        [&](int i) { return __hip_atomic_load(&p.bin_groups[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, p.bins, p.gid_base,
+        nullptr, wsum[0]);
+    if (tid != 0) return;
+    *o.n_groups = G;
+    o.seg_offsets[G] = p.bin_base[p.bins];
+  };
   if (m == 0) {
-    if (tid == 0) p.bin_groups[bin] = 0;
+    publish(0);
+    draw();
+    scan_if_last();
     return;
   }
   const bool large = m > kPoolCap;
@@ -939,21 +1098,22 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
       next[k] = at;
       gid[k] = static_cast<uint16_t>(g);
       if (large && c[e] > 0) {
-        p.hist[lo + k] = base + at;
-        p.gid_of_key[lo + k] = g;
+        p.kr[base + k] = make_int2(base + at, g);
         p.stats[base + g].w = __int_as_float(base + at);
       }
       at += c[e];
       g += c[e] > 0;
     }
   }
-  if (tid == 0) p.bin_groups[bin] = n_groups;
+  publish(n_groups);
   if (large) {
     bool wave_groups = false;
 #pragma unroll
     for (int e = 0; e < kPer; ++e) wave_groups = wave_groups || c[e] > kSmallGroup;
     const int any = __syncthreads_or(wave_groups);
     if (tid == 0) p.cursor[bin] = any;
+    draw();
+    scan_if_last();
     return;
   }
   __syncthreads();
@@ -998,6 +1158,7 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
         st, &mean, &sd, &best);
     if (lane == 0) p.stats[base + gid[k]] = make_float4(mean, sd, __int_as_float(best), __int_as_float(base + f));
   }
+  draw();
   __syncthreads();
   for (int e = tid; e < m; e += kBinThreads) {
     const int r = list_id[bin_at(e)];
@@ -1007,43 +1168,17 @@ __global__ __launch_bounds__(kBinThreads) void k_gp_bin(PoolPlan p, const float*
   for (int i = 0; i < kBinPer; ++i)
     if (place[i] >= 0)
       p.result[base + tid + i * kBinThreads] = make_float2(list_x[bin_at(place[i] & 0xffff)], __int_as_float(place[i] >> 16));
-}
-
-// workgroup 0: ids of the bins' first groups; the others list the members of the large bins
-__global__ __launch_bounds__(kPoolThreads) void k_gp_groups(PoolPlan p, int n_resp, GaOut o) {
-  __shared__ int lds16[16];
-  if (blockIdx.x > 0) {
-    if (p.large[0] == 0) return;
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x - 1) * kPoolThreads * 4 + threadIdx.x;
-    int key[4], s[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t r = r0 + u * kPoolThreads;
-      key[u] = r < n_resp ? p.key[r] : -1;
-      s[u] = r < n_resp ? p.slot[r] : 0;         // meaningless without a key
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (key[u] >= 0 && s[u] < 0) p.list[p.hist[key[u]] + (s[u] & 0x7fffffff)] = static_cast<int>(r0 + u * kPoolThreads);
-    return;
-  }
-  scan_small(p.bin_groups, p.bins, p.gid_base, nullptr, lds16);
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int G = p.gid_base[p.bins];
-    *o.n_groups = G;
-    o.seg_offsets[G] = p.bin_base[p.bins];
-  }
+  scan_if_last();
 }
 
 // results in response order; the blocks behind `resp_blocks` write the groups of a bin each, the last ones fill the tails.
-// Advantages and groups of large bins are left to k_gp_large.
+// Members of the large bins are listed; their advantages and groups are left to k_gp_large.
 __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp_blocks, GaOut o) {
   if (static_cast<int>(blockIdx.x) < resp_blocks) {
     // the loads of a thread's four responses go out together
+    if (p.per == kSortPer && p.sorted[blockIdx.x / kSortPer] >= 0) return;      // left to k_gp_turn
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x;
-    int key[4], at[4];
+    int key[4], at[4], gid0[4], first[4];
     float2 res[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -1052,7 +1187,14 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
       at[u] = r < n_resp ? p.slot[r] : 0;      // no slot without a key
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) res[u] = key[u] >= 0 && at[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f);
+    for (int u = 0; u < 4; ++u) {
+      const bool in_large = key[u] >= 0 && at[u] < 0;
+      const int bin = key[u] < 0 ? 0 : static_cast<int>(static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width));
+      gid0[u] = p.gid_base[bin];
+      const int2 g = in_large ? p.kr[p.bin_base[bin] + (key[u] - bin * p.width)] : make_int2(0, 0);
+      first[u] = g.x;
+      res[u] = in_large ? make_float2(0.f, __int_as_float(g.y)) : (key[u] >= 0 ? p.result[at[u]] : make_float2(0.f, 0.f));
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t r = r0 + u * 256;
@@ -1061,9 +1203,9 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
         o.group_id[r] = -1;
         o.adv[r] = 0.f;
       } else {
-        const int lg = at[u] < 0 ? p.gid_of_key[key[u]] : __float_as_int(res[u].y);
-        o.group_id[r] = p.gid_base[static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)] + lg;
+        o.group_id[r] = gid0[u] + __float_as_int(res[u].y);
         if (at[u] >= 0) o.adv[r] = res[u].x;
+        else p.list[first[u] + (at[u] & 0x7fffffff)] = static_cast<int>(r);
       }
     }
     return;
@@ -1084,25 +1226,80 @@ __global__ __launch_bounds__(256) void k_gp_out(PoolPlan p, int n_resp, int resp
              static_cast<int64_t>(gridDim.x - resp_blocks - p.bins) * 256);
 }
 
-// The groups of the large bins, shared by the grid.  A launch of its own: it returns at once where there are none (2 us), and
-// the registers of the finishing code would cost k_gp_out its wavefronts.
-__global__ __launch_bounds__(256) void k_gp_large(PoolPlan p, const float* __restrict__ reward, GaStat st, GaOut o) {
+// The groups of the large bins, shared by `units` units of 256 threads of which this is number `unit`, with thread `t` of them.
+__device__ __forceinline__ void finish_large_bins(const PoolPlan& p, const float* __restrict__ reward, const GaStat& st, const GaOut& o,
+                                                  int unit, int units, int t) {
   const int n_large = p.large[0];
   if (n_large == 0) return;
   // the bins' first parts come first: consecutive workgroups, which the hardware deals to the XCDs in turn, have equal work
-  const int teams = min(n_large, static_cast<int>(gridDim.x)), parts = static_cast<int>(gridDim.x) / teams;
-  const int part = static_cast<int>(blockIdx.x) / teams;
+  const int teams = min(n_large, units), parts = units / teams;
+  const int part = unit / teams;
   if (part >= parts) return;
-  for (int i = static_cast<int>(blockIdx.x) % teams; i < n_large; i += teams) {
+  for (int i = unit % teams; i < n_large; i += teams) {
     const int bin = p.large[1 + i], base = p.bin_base[bin], end = p.bin_base[bin + 1];
     const int g0 = p.gid_base[bin], n = p.gid_base[bin + 1] - g0;
     const bool wave_groups = p.cursor[bin] != 0;
     if (part * 256 >= n && !wave_groups) continue;
     auto off = [&](int g) { return g < n ? __float_as_int(p.stats[base + g].w) : end; };
-    for (int g = part * 256 + static_cast<int>(threadIdx.x); g < n; g += parts * 256) o.seg_offsets[g0 + g] = off(g);
-    finish_small_groups(n, g0, part, parts, off, p.list, reward, st, o);
-    if (wave_groups) finish_large_groups(n, g0, part * 4 + static_cast<int>(threadIdx.x >> 6), parts * 4, off, p.list, reward, st, o);
+    for (int g = part * 256 + t; g < n; g += parts * 256) o.seg_offsets[g0 + g] = off(g);
+    finish_small_groups(n, g0, part, parts, t, off, p.list, reward, st, o);
+    if (wave_groups) finish_large_groups(n, g0, part * 4 + (t >> 6), parts * 4, off, p.list, reward, st, o);
   }
+}
+
+// A launch of its own: it returns at once where there are no large bins (2 to 5 us), and the registers of the finishing code would cost
+// k_gp_out its wavefronts.  Pools whose blocks may be sorted have k_gp_turn do it.
+__global__ __launch_bounds__(256) void k_gp_large(PoolPlan p, const float* __restrict__ reward, GaStat st, GaOut o) {
+  finish_large_bins(p, reward, st, o, blockIdx.x, gridDim.x, threadIdx.x);
+}
+
+// Results of the sorted blocks in response order: read in the order of their places, run by run, and turned in LDS.  Then the
+// groups of the large bins: a launch that finds nothing to do takes 4.6 us at 2^22 responses, and one of those is enough.
+__device__ __forceinline__ void turn_block(const PoolPlan& p, int n_resp, const GaOut& o, float2* turned) {
+  constexpr int PER = kSortPer;
+  const int64_t block0 = static_cast<int64_t>(blockIdx.x) * kPoolThreads * PER, r0 = block0 + threadIdx.x;
+  const int sorted = p.sorted[blockIdx.x];
+  if (sorted < 0) return;
+  int at[PER], who[PER];
+  float2 res[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = threadIdx.x + i * kPoolThreads;
+    at[i] = j < sorted ? p.slot[block0 + j] : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = threadIdx.x + i * kPoolThreads;
+    who[i] = j < sorted ? p.member[block0 + j] : -1;
+    res[i] = at[i] >= 0 ? p.result[at[i]] : make_float2(0.f, 0.f);
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+    if (who[i] >= 0) turned[who[i]] = res[i];
+  int key[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t r = r0 + u * kPoolThreads;
+    key[u] = r < n_resp ? p.key[r] : -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t r = r0 + u * kPoolThreads;
+    if (r >= n_resp) break;
+    const float2 v = key[u] < 0 ? make_float2(0.f, 0.f) : turned[threadIdx.x + u * kPoolThreads];
+    o.group_id[r] = key[u] < 0 ? -1 : p.gid_base[static_cast<unsigned>(key[u]) / static_cast<unsigned>(p.width)] + __float_as_int(v.y);
+    o.adv[r] = v.x;
+  }
+}
+
+__global__ __launch_bounds__(kPoolThreads) void k_gp_turn(PoolPlan p, int n_resp, int blocks, const float* __restrict__ reward, GaStat st, GaOut o) {
+  extern __shared__ __attribute__((aligned(16))) float2 turned[];      // [kPoolThreads * kSortPer]
+  if (static_cast<int>(blockIdx.x) < blocks) turn_block(p, n_resp, o, turned);
+  constexpr int kUnits = kPoolThreads / 256;
+  const int sub = static_cast<int>(threadIdx.x) >> 8;
+  finish_large_bins(p, reward, st, o, sub * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x),
+                    kUnits * static_cast<int>(gridDim.x), threadIdx.x & 255);
 }
 
 // both finishing roles in one launch: the first n_small blocks take the small groups (a thread each), the next n_large the
@@ -1112,7 +1309,7 @@ __global__ __launch_bounds__(256) void k_ga_finish(int n_small, int n_large, int
   const int G = *o.n_groups, b = blockIdx.x;
   auto off = [&](int g) { return o.seg_offsets[g]; };
   if (b < n_small)
-    finish_small_groups(G, 0, b, n_small, off, arrival, reward, st, o);
+    finish_small_groups(G, 0, b, n_small, threadIdx.x, off, arrival, reward, st, o);
   else if (b < n_small + n_large)
     finish_large_groups(G, 0, ((b - n_small) * 256 + static_cast<int>(threadIdx.x)) >> 6, (n_large * 256) >> 6, off, arrival,
                         reward, st, o);
@@ -1191,9 +1388,10 @@ bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   q.slot = p->rank_of_resp;
   q.list = p->arrival;
   q.hist = p->hist;
-  q.gid_of_key = p->gid_of_key;
   q.kr = ws.take<int2>(R);
   q.x = ws.take<float>(R);
+  q.member = ws.take<uint16_t>(blocks * kPoolThreads * q.per);
+  q.sorted = ws.take<int32_t>(blocks);
   q.result = ws.take<float2>(R);
   q.stats = ws.take<float4>(R);
   q.blk = ws.take<int32_t>(blocks * static_cast<size_t>(q.bins));
@@ -1202,6 +1400,7 @@ bool plan_pool(int32_t n_resp, WsAlloc& ws, GaPlan* p) {
   q.cursor = ws.take<int32_t>(static_cast<size_t>(q.bins));
   q.bin_groups = ws.take<int32_t>(static_cast<size_t>(q.bins));
   q.gid_base = ws.take<int32_t>(static_cast<size_t>(q.bins) + 1);
+  q.bins_done = ws.take<int32_t>(1 + kPoolMaxBins / kTicketBins);
   q.large = ws.take<int32_t>(static_cast<size_t>(q.bins) + 1);
   return true;
 }
@@ -1340,19 +1539,37 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     hipLaunchKernelGGL(k_gp_bases, dim3(static_cast<unsigned>(1 + ceil_div(p.pool.bins, kBasesBins))), dim3(kPoolThreads), 0, s,
                        p.pool, p.n_keys);
     ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_gp_partition, dim3(blocks), dim3(kPoolThreads), 0, s, n_resp, rw, p.pool);
-    ATG_LAUNCH_CHECK();
+    // Blocks that are one round of workgroups are partitioned by one launch, whose LDS leaves room for one per compute unit (2^22 in
+    // rollout order 19 us; k_gp_partition 18 and the launch in front of it 5); more of them take a second one for those not sorted.
+    const bool may_sort = p.pool.per == kSortPer, one_round = blocks <= static_cast<unsigned>(device_cu_count());
+    if (may_sort) {
+      const int bytes = (2 * kPoolThreads * kSortPer + p.pool.bins) * 4;
+      auto k = one_round ? k_gp_partition_sorted<true> : k_gp_partition_sorted<false>;
+      ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+      hipLaunchKernelGGL(k, dim3(blocks), dim3(kPoolThreads), bytes, s, n_resp, rw, p.pool);
+      ATG_LAUNCH_CHECK();
+    }
+    if (!may_sort || !one_round) {
+      hipLaunchKernelGGL(k_gp_partition, dim3(blocks), dim3(kPoolThreads), 0, s, n_resp, rw, p.pool, may_sort ? 1 : 0);
+      ATG_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL(k_gp_bin, dim3(p.pool.bins), dim3(kBinThreads), 0, s, p.pool, rw, st, p.n_keys, o);
-    ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_gp_groups, dim3(static_cast<unsigned>(1 + ceil_div(n_resp, kPoolThreads * 4))), dim3(kPoolThreads), 0, s,
-                       p.pool, n_resp, o);
     ATG_LAUNCH_CHECK();
     const int resp_blocks = static_cast<int>(ceil_div(n_resp, 1024));
     hipLaunchKernelGGL(k_gp_out, dim3(static_cast<unsigned>(resp_blocks + p.pool.bins + (fill ? 64 : 0))), dim3(256), 0, s,
                        p.pool, n_resp, resp_blocks, o);
     ATG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_gp_large, dim3(kLargeBlocks), dim3(256), 0, s, p.pool, rw, st, o);
-    ATG_LAUNCH_CHECK();
+    // both behind k_gp_out, which lists the members of the large bins
+    if (may_sort) {
+      const int bytes = kPoolThreads * kSortPer * 8;
+      ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gp_turn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+      hipLaunchKernelGGL(k_gp_turn, dim3(std::max(blocks, static_cast<unsigned>(kLargeBlocks * 256 / kPoolThreads))), dim3(kPoolThreads),
+                         bytes, s, p.pool, n_resp, static_cast<int>(blocks), rw, st, o);
+      ATG_LAUNCH_CHECK();
+    } else {
+      hipLaunchKernelGGL(k_gp_large, dim3(kLargeBlocks), dim3(256), 0, s, p.pool, rw, st, o);
+      ATG_LAUNCH_CHECK();
+    }
     return AT_GRPO_OK;
   }
   if (r_team) {

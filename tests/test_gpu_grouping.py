@@ -236,3 +236,54 @@ def test_replays_on_other_inputs(gpu_device, shape):
         torch.cuda.synchronize()
         for k in ref:
             assert torch.equal(out[k], ref[k]), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,order,crowded", [(2342913, "shuffled", 0), (4194304, "shuffled", 0), (4194305, "half in rollout order", 0),
+                                             (2400001, "half in rollout order", 2048), (4300001, "shuffled", 2048)], ids=str)
+def test_blocks_sorted_by_bin(gpu_device, n, order, crowded):
+    """The largest pools: blocks of 16384 responses that lie in many bins are sorted by bin first.  One round of workgroups and more,
+    a ragged last block, blocks in rollout order among them, every tenth response without a key, and keys so crowded that their bins
+    exceed the LDS lists (blocks with members of those are not sorted)."""
+    rng = np.random.default_rng(n + crowded)
+    E, K = n // 8, 8
+    key = np.arange(n) // K % E
+    crowd = np.arange(n) >= n - 40000 if crowded else np.zeros(n, bool)
+    key[crowd] = rng.integers(0, max(crowded, 1), int(crowd.sum()))
+    shuffled = n - 60000 if crowded else n
+    lo = shuffled // 2 if order.startswith("half") else 0
+    key[lo:shuffled] = key[lo:shuffled][rng.permutation(shuffled - lo)]
+    env = key.astype(np.int32)
+    kept = rng.random(n) >= 0.1
+    env[~kept] = np.where(np.arange(n)[~kept] % 2 == 0, E, -1)
+    reward = (rng.integers(0, 9, size=n) / np.float32(8)).astype(np.float32)
+    zero = np.zeros(n, np.int32)
+    say(f"[grouping] sorted blocks n={n} {order} crowded={crowded}")
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    out = api.at_grpo_group_advantage(dev(env), dev(zero), dev(zero), dev(reward), E, 1, 1)
+    torch.cuda.synchronize()
+    rows = np.nonzero(kept)[0]
+    gid, G, offs, perm = orc.group_segments(orc.group_key(env[kept], zero[kept], zero[kept], 1, 1))
+    assert int(out["n_groups"].item()) == G
+    got = host(out["group_id"])
+    assert np.array_equal(got[kept], gid) and np.all(got[~kept] == -1)
+    seg = host(out["seg_offsets"])
+    assert np.array_equal(seg[:G + 1], offs) and np.all(seg[G + 1:] == 0)
+    assert np.array_equal(host(out["perm"])[:rows.size], rows[perm]) and np.all(host(out["perm"])[rows.size:] == 0)
+    # means of all groups in 64 bits, the oracle's results on 300 of them; fp32 sums of a group's members: within 1e-4, as above
+    x = reward[kept].astype(np.float64)
+    count = np.bincount(gid, minlength=G)
+    mean = np.bincount(gid, x, G) / count
+    pick = np.sort(rng.choice(G, size=300, replace=False))
+    members = np.concatenate([perm[offs[g]:offs[g + 1]] for g in pick])
+    sub = np.repeat(np.arange(pick.size), count[pick])
+    adv, m, s = orc.group_advantage(reward[kept][members], sub, pick.size)
+    a = host(out["adv"]).astype(np.float64)
+    assert np.all(a[~kept] == 0)
+    assert np.allclose(a[kept][members], adv, rtol=1e-4, atol=1e-6)
+    assert np.allclose(host(out["group_mean"])[:G], mean, rtol=1e-4, atol=1e-7)
+    assert np.allclose(host(out["group_std"])[pick], s, rtol=1e-4, atol=1e-7)
+    # all responses: what their groups' own statistics give
+    gm, gs = host(out["group_mean"]).astype(np.float64)[gid], host(out["group_std"]).astype(np.float64)[gid]
+    want = np.where(gs > 0, (x - gm) / np.where(gs > 0, gs, 1), 0)
+    assert np.allclose(a[kept], want, rtol=1e-4, atol=1e-5)
