@@ -187,3 +187,28 @@ def test_head_update_full_size_head(gpu_device):
     again = once()
     for a, b in zip((master, low, m, v, gn), again):
         assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bf16", [False, True], ids=["f32", "bf16"])
+def test_head_update_past_the_caches(gpu_device, bf16):
+    """Two heads that together exceed what stays in the caches, against the same heads one call at a time, which do not: without
+    clipping an element's result does not depend on the others, so all arrays are the same bits (a ragged last workgroup included)."""
+    dev, V, H = gpu_device, 9001, 500
+    say(f"[head_update] past the caches V={V} H={H} bf16={bf16}")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    draw = lambda s: torch.randn((V, H), generator=gen, device=dev) * s
+    first = [(draw(0.02), draw(1e-4), draw(1e-5), draw(1e-5) ** 2) for _ in range(2)]
+    results = []
+    for groups in ([[0, 1]], [[0], [1]]):
+        state = [[x.clone() for x in head] for head in first]
+        low = [s[0].to(torch.bfloat16) if bf16 else s[0] for s in state]
+        for hs in groups:
+            api.at_grpo_head_update([low[h] for h in hs], [state[h][1] for h in hs], [state[h][2] for h in hs], [state[h][3] for h in hs], 5,
+                                    W_master=[state[h][0] for h in hs] if bf16 else None, lr=1e-3, max_grad_norm=0.0)
+        torch.cuda.synchronize()
+        results.append([x for s in state for x in s] + low)
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+    assert not torch.equal(results[0][0], first[0][0])
