@@ -87,9 +87,22 @@ __device__ __forceinline__ void direct_load_v(const char* p, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(p), "s"(lds) : "memory");
 }
 
+// direct_load_s for lines that nothing reads again while the caches hold them
+__device__ __forceinline__ void direct_load_once(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(off), "s"(base), "s"(lds) : "memory");
+}
+
 // from base + off: with 32-bit offsets the base stays scalar; operands whose panel spans 4 GiB or more take 64-bit ones
-__device__ __forceinline__ void direct_load(const char* base, uint32_t off, uint32_t lds) { direct_load_s(base, off, lds); }
-__device__ __forceinline__ void direct_load(const char* base, uint64_t off, uint32_t lds) { direct_load_v(base + off, lds); }
+template <bool ONCE = false>
+__device__ __forceinline__ void direct_load(const char* base, uint32_t off, uint32_t lds) {
+  if (ONCE) direct_load_once(base, off, lds);
+  else direct_load_s(base, off, lds);
+}
+template <bool ONCE = false>
+__device__ __forceinline__ void direct_load(const char* base, uint64_t off, uint32_t lds) {
+  static_assert(!ONCE, "few tokens of a vocabulary beyond 8.3 million: in whole tiles, by the usual loads");
+  direct_load_v(base + off, lds);
+}
 
 #define ATG_PIN16() __builtin_amdgcn_sched_barrier(0)
 
@@ -113,10 +126,10 @@ __device__ __forceinline__ void wait_loads_but() {
 
 // Off: uint32_t where 256 rows of the operand (64 k-rows of a k-major one) lie within 4 GiB, else uint64_t (see wide_rows)
 
-// NL: direct loads of a wavefront per step (kLoadsA or kLoadsB of the grid)
+// NL: direct loads of a wavefront per step (kLoadsA or kLoadsB of the grid); ONCE: nothing reads the panel again (direct_load_once)
 
 // rows contiguous along k
-template <int NL, typename Off = uint32_t>
+template <int NL, typename Off = uint32_t, bool ONCE = false>
 struct RowPanel {
   static constexpr bool kKMajor = false;
   const char* base;
@@ -131,7 +144,7 @@ struct RowPanel {
       off[q] = row_off(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
   }
-  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load(base, off[q], lds); }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load<ONCE>(base, off[q], lds); }
   __device__ __forceinline__ void advance() { base += kStepK * 2; }
 };
 
@@ -180,7 +193,7 @@ struct KMajorPanel {
 
 // k-major with a number of k-rows that need not be a multiple of 64: rows past the last are fetched from the last one (the
 // other operand is zero there)
-template <int NL, typename Off = uint32_t>
+template <int NL, typename Off = uint32_t, bool ONCE = false>
 struct KMajorTailPanel {
   static constexpr bool kKMajor = true;
   const char* base;
@@ -205,7 +218,7 @@ struct KMajorTailPanel {
       off[q] = static_cast<Off>(max(min(k, rows - 1), 0) * ld) + min(C, cmax) * 16;
     }
   }
-  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load(base, off[q], lds); }
+  __device__ __forceinline__ void load(int q, uint32_t lds) { direct_load<ONCE>(base, off[q], lds); }
   __device__ __forceinline__ void advance() {
     base += ld * kStepK;
     rows -= kStepK;

@@ -154,13 +154,14 @@ __device__ __forceinline__ void logit_tiles(const LogitIn& in, int first, int en
 }
 
 // A launch of at most T tokens, as one stream of k-steps over this workgroup's vocabulary tiles.  Bound by memory: the weights
-// pass once, for little arithmetic.  V = 151936, 256 x 256 tiles before: 8 tokens at H = 4096 396 -> 240 us (5.2 TB/s), 100
-// and 150 tokens at H = 2048 199 -> 143 and 208 -> 164 us.  With 200 tokens the arithmetic is as long as the loads, and the
+// pass once, for little arithmetic.  V = 151936, 256 x 256 tiles before: 8 tokens at H = 4096 396 -> 217 us (5.7 TB/s), 100
+// tokens at H = 2048 199 -> 135 us (of these 240 -> 217 and 144 -> 135 by loads past the caches).  With 200 tokens the arithmetic is as long as the loads, and the
 // tiles of 256 x 256 are as fast (390 us at H = 4096, 405 as a stream).
-template <int T, bool PERMUTED, typename Epilogue>
+// ONCE: see read_once
+template <int T, bool PERMUTED, bool ONCE, typename Epilogue>
 __device__ __forceinline__ void logit_stream(const LogitIn& in, char* smem, Epilogue epi) {
   using G = GNarrow<T>;
-  using PA = RowPanel<G::kLoadsA>;
+  using PA = RowPanel<G::kLoadsA, uint32_t, ONCE>;
   using PB = GatherPanel<G::kLoadsB>;
   using S = Stream16<G, PA, PB, narrow_depth(T)>;
   static_assert(G::kThreads == GLogit::kThreads && S::kBytes + kFoldBytes <= kRingBytes, "fits the launch");
@@ -211,6 +212,13 @@ __device__ __forceinline__ void logit_stream(const LogitIn& in, char* smem, Epil
   st.finish();
 }
 
+template <bool PERMUTED, bool ONCE, typename Epilogue>
+__device__ __forceinline__ void logit_narrow(const LogitIn& in, char* smem, Epilogue epi) {
+  if (in.n <= 64) logit_stream<64, PERMUTED, ONCE>(in, smem, epi);
+  else if (in.n <= 128) logit_stream<128, PERMUTED, ONCE>(in, smem, epi);
+  else logit_stream<192, PERMUTED, ONCE>(in, smem, epi);
+}
+
 // All tiles of a launch.  Those that do not fill a round of the grid are cut into halves or quarters of their tokens if there
 // are workgroups for all of them: 594 tiles (the full vocabulary, up to 256 tokens) are two rounds and a half instead of three
 // (197 tokens at H = 4096 372 -> 346 us with the call's other kernels, 400 at H = 2048, 4.6 rounds, 345 -> 328).
@@ -219,9 +227,8 @@ __device__ __forceinline__ void logit_launch(const LogitIn& in, int n_vtiles, ch
   constexpr bool kCut = sizeof(Off) == 4;       // (not for vocabularies beyond 8.3 million)
   if constexpr (kCut) {
     if (narrow_launch(in.n)) {
-      if (in.n <= 64) logit_stream<64, PERMUTED>(in, smem, epi);
-      else if (in.n <= 128) logit_stream<128, PERMUTED>(in, smem, epi);
-      else logit_stream<192, PERMUTED>(in, smem, epi);
+      if (read_once(in.n, in.V, in.H)) logit_narrow<PERMUTED, true>(in, smem, epi);
+      else logit_narrow<PERMUTED, false>(in, smem, epi);
       return;
     }
   }
@@ -667,13 +674,10 @@ __device__ __forceinline__ TileOrder dh_order(int n, int H) {
   return TileOrder{(n + kTile16 - 1) / kTile16, (H + kTile16 - 1) / kTile16, 8};
 }
 
-template <bool T, typename Off>
-__global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
+template <bool T, typename Off, bool ONCE>
+__device__ __forceinline__ void dh_tiles(const DhArgs& a, int n) {
   using G = GDh;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  if ((*a.cnt > kUntransposedRows) != T) return;
-  const int n = rows_of(a.perm ? a.live_cnt : nullptr, a.cnt, a.c0, a.TC);
-  if (n <= 0) return;
   const TileOrder ord = dh_order(n, a.H);
   const int nk_all = a.Vp / kStepK;
   const SplitK sp = plan_split(ord.total(), nk_all, gridDim.x);
@@ -702,7 +706,7 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
                 [&](int row) { return static_cast<Off>(min(a_index(row), a.H - 1 - h0)) * row_bytes; });
         gemm16<G>(acc, pa, pb, nk, smem, co);
       } else {
-        KMajorTailPanel<G::kLoadsA, Off> pa;
+        KMajorTailPanel<G::kLoadsA, Off, ONCE> pa;
         pa.init(reinterpret_cast<const char*>(a.W + static_cast<size_t>(k0) * kStepK * a.H + h0), co.wave, co.lane,
                 static_cast<size_t>(a.H) * 2, min(31, (a.H - h0) / 8 - 1), a.V - k0 * kStepK);
         gemm16<G>(acc, pa, pb, nk, smem, co);
@@ -721,6 +725,20 @@ __global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
       }
     }
   }
+}
+
+template <bool T, typename Off>
+__global__ __launch_bounds__(GDh::kThreads) void k_head_dh(DhArgs a) {
+  if ((*a.cnt > kUntransposedRows) != T) return;
+  const int n = rows_of(a.perm ? a.live_cnt : nullptr, a.cnt, a.c0, a.TC);
+  if (n <= 0) return;
+  if constexpr (!T && sizeof(Off) == 4) {
+    if (read_once(n, a.V, a.H)) {
+      dh_tiles<T, Off, true>(a, n);
+      return;
+    }
+  }
+  dh_tiles<T, Off, false>(a, n);
 }
 
 // adds the parts of the split tiles and finishes them; `grid` = workgroups of the contraction

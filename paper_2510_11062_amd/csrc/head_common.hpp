@@ -26,6 +26,11 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 constexpr int kNarrowV = 128, kNarrowStride = 256;
 #ifdef __HIPCC__
 __device__ __forceinline__ bool narrow_launch(int n) { return n <= 192; }
+// bf16 weights that a launch of few tokens passes by once and that the Infinity Cache of 256 MB does not hold until the next launch
+// reads them: loaded past the caches, by logits and dHidden alike.  Both launches of a step at H = 2048, V = 151936: 8 tokens 328 ->
+// 289 us, 64 339 -> 304, 160 349 -> 337 (with the logits' loads alone past the caches dHidden misses what they had left: 138 ->
+// 185 us); log-probabilities of 8 tokens at H = 4096 238 -> 218.  205 MB of weights: 38 us by usual loads, 43 past the caches.
+__device__ __forceinline__ bool read_once(int n, int V, int H) { return narrow_launch(n) && static_cast<int64_t>(V) * H > (128 << 20); }
 #endif
 // floats of partial results of one kind that a launch of TC rows over n_vtiles 256-row vocabulary tiles leaves
 inline size_t logit_part_floats(int n_vtiles, int64_t TC) {

@@ -112,3 +112,12 @@ def test_hidden_rows_without_advantage_need_not_be_finite(gpu_device):
     step = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, EPS, EPS)
     close(step["d_hidden"], dh, "d_hidden")
     close(step["dW"][0], dw, "dW")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,H,V", [(1, 2048, 65537), (65, 2048, 65537), (192, 2048, 65537), (130, 1024, 131200), (192, 2048, 65536)])
+def test_weights_past_the_caches(gpu_device, n, H, V):
+    """The first sizes of weights that the caches do not hold (and the last that they do): ragged vocabulary tiles and k-steps."""
+    say(f"[few] weights past the caches n={n} H={H} V={V}")
+    lengths = [n - n // 2] + ([n // 2] if n > 1 else [])
+    check(*make(gpu_device, lengths, [1.0, -0.5][:len(lengths)], H, V), lengths)
