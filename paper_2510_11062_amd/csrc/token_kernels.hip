@@ -561,12 +561,13 @@ template <int MODE>
 __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
   __shared__ __attribute__((aligned(16))) int8_t mark[kPsRows];
   __shared__ int part[2][kPsThreads / 64];
-  __shared__ int rows_of_head[kMaxHeads], resps_of_head[kMaxHeads], no_adv_of_head[kMaxHeads];
+  __shared__ int rows_of_head[kMaxHeads], resps_of_head[kMaxHeads];
+  __shared__ uint32_t listed[kMaxHeads];      // rows with an advantage, and in the upper half those without
   const TokenLayout& L = a.L;
   const int tid = threadIdx.x, n = static_cast<int>(L.n_tok);
 
   if (tid == 0) *a.S.err = 0;
-  if (tid < kMaxHeads) rows_of_head[tid] = resps_of_head[tid] = no_adv_of_head[tid] = 0;
+  if (tid < kMaxHeads) rows_of_head[tid] = resps_of_head[tid] = listed[tid] = 0;
   for (int i = tid * 16; i < n; i += kPsThreads * 16) *reinterpret_cast<int4*>(mark + i) = make_int4(-1, -1, -1, -1);
   if (MODE != PREP_LOGPROB)
     for (int t = tid; t < n; t += kPsThreads) a.S.resp_of_tok[t] = -1;
@@ -622,7 +623,6 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
       if (c > 0) {
         atomicAdd(&rows_of_head[head], c);
         atomicAdd(&resps_of_head[head], 1);
-        if (mine != head) atomicAdd(&no_adv_of_head[head], c);
       }
     }
   }
@@ -658,8 +658,42 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
     }
   }
 
-  // lists, ascending: eight consecutive rows per thread; the counts of both lists travel in one word (at most 8192 each)
+  // eight consecutive rows per thread; what lies behind the last row is not marked
   const int wlane = tid & 63, wave = tid >> 6;
+  static_assert(kPsRows % 16 == 0 && kPsRows < 65536, "whole pieces of marks; both counts of a head fit a word");
+  auto load_marks = [&](int t0, int8_t(&f)[kPsPer]) {
+    uint2 w = make_uint2(0xffffffffu, 0xffffffffu);
+    if (t0 < n) w = *reinterpret_cast<const uint2*>(mark + t0);
+#pragma unroll
+    for (int e = 0; e < kPsPer; ++e) f[e] = static_cast<int8_t>((e < 4 ? w.x : w.y) >> (8 * (e & 3)));
+  };
+  // with an advantage: in the lower half, without one: in the upper
+  auto count_marks = [&](const int8_t(&f)[kPsPer], int m) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int e = 0; e < kPsPer; ++e) v += f[e] == m ? 1 : (f[e] == (m | kPsNoAdv) ? 0x10000 : 0);
+    return v;
+  };
+
+  // How long a head's two lists become, counted on the marks that they are made from.  (The responses' counts above say something
+  // else where bounds of responses overlap: a row then counts for each of them.  That is a data error, which must not decide where
+  // anything is stored.)
+  if (MODE == PREP_STEP) {
+    for (int m = 0; m < L.n_heads; ++m) {
+      uint32_t v = 0;
+      for (int t0 = tid * kPsPer; t0 < n; t0 += kPsTile) {
+        int8_t f[kPsPer];
+        load_marks(t0, f);
+        v += count_marks(f, m);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      if (wlane == 0 && v != 0) atomicAdd(&listed[m], v);
+    }
+    __syncthreads();
+  }
+
+  // lists, ascending; the counts of a tile's rows on both lists travel in one word (at most 8192 each)
   int buf = 0;
   for (int m = 0; m < kMaxHeads; ++m) {
     int run_b = 0, run_f = 0;
@@ -667,20 +701,14 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
     if (m < L.n_heads) {
       int32_t* out_b = a.idx_b + static_cast<size_t>(m) * n;
       int32_t* out_f = MODE == PREP_STEP ? a.idx_f + static_cast<size_t>(m) * n : nullptr;
-      const int rows_f = MODE == PREP_STEP ? no_adv_of_head[m] : 0, rows_b = MODE == PREP_STEP ? rows_of_head[m] - rows_f : 0;
+      const int rows_f = MODE == PREP_STEP ? listed[m] >> 16 : 0, rows_b = MODE == PREP_STEP ? listed[m] & 0xffff : 0;
       merge = rows_b > 0 && rows_f > 0 && rows_f <= kPsMerge;
       if (merge) out_f = out_b + rows_b;
       for (int base = 0; base < n; base += kPsTile) {
         const int t0 = base + tid * kPsPer;
-        uint2 w = make_uint2(0xffffffffu, 0xffffffffu);
-        if (t0 < n) w = *reinterpret_cast<const uint2*>(mark + t0);
         int8_t f[kPsPer];
-        int v = 0;
-#pragma unroll
-        for (int e = 0; e < kPsPer; ++e) {
-          f[e] = t0 + e < n ? static_cast<int8_t>((e < 4 ? w.x : w.y) >> (8 * (e & 3))) : int8_t{-1};
-          v += f[e] == m ? 1 : (f[e] == (m | kPsNoAdv) ? 0x10000 : 0);
-        }
+        load_marks(t0, f);
+        const int v = count_marks(f, m);
         int incl = v;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {

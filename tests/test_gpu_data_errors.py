@@ -125,3 +125,54 @@ def test_nothing_takes_part(gpu_device, E, dtype):
     for k in ("loss", "logp", "lse", "clip_mask", "n_valid", "d_hidden"):
         assert float(out[k].abs().max()) == 0, k
     assert all(float(g.abs().max()) == 0 for g in out["dW"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [40, 2600, 33000], ids=["40", "2600", "general"])      # up to 32768 rows are small
+@pytest.mark.parametrize("cu,adv", [
+    ((0, 10, 20, 5, 40), (1, 0, -1, 0)),          # response 2 has no bounds; 3 covers rows of 0 and 1 again
+    ((0, 10, 5, 20, 40), (1, 0, 0, -1)),
+    ((0, 10, 5, 20, 40), (0, 0, 1, 0)),
+    ((0, 40, 0, 40, 0, 40), (1, 0, 0, 0, -1)),    # all rows three times, once with an advantage, or twice
+    ((0, 30, 0, 30, 20, 40), (0, 0, -1, 0, 0)),
+], ids=str)
+def test_overlapping_bounds(gpu_device, dtype, n, cu, adv):
+    """A bound that is too small: its response is reported, and the next one has rows that others have too.  Which of them such a row
+    goes with is open, but nothing may leave the lists: the scratch memory is full of the number of a masked row, which must
+    stay untouched (a place on a list that nobody wrote would name it)."""
+    say(f"[errors] overlapping bounds {dtype} n={n} {cu} {adv}")
+    dev, H, V, masked = gpu_device, 64, 130, 3
+    cu = np.array(cu, np.int64) * (n // 40)
+    n = int(cu.max())
+    gen = torch.Generator(device=dev).manual_seed(n)
+    hidden = torch.randn(n, H, generator=gen, device=dev).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    W = (torch.randn(V, H, generator=gen, device=dev) * 0.1).to(hidden.dtype)
+    y = torch.randint(0, V, (n,), generator=gen, device=dev, dtype=torch.int32)
+    logp = torch.log_softmax(hidden.double() @ W.double().T, 1)
+    lp, lse = logp.gather(1, y.long()[:, None])[:, 0], -logp[:, 0] + (hidden.double() @ W[0].double())
+    mask = torch.ones(n, dtype=torch.uint8, device=dev)
+    mask[masked] = 0
+    on, with_adv, n_valid = np.zeros(n, bool), np.zeros(n, bool), 0
+    for r, A in enumerate(adv):
+        if cu[r] <= cu[r + 1]:
+            rows = slice(cu[r], cu[r + 1])
+            on[rows] = True
+            with_adv[rows] |= A != 0
+            n_valid += int(mask[rows].sum())
+    on[masked] = False
+    on, with_adv = torch.from_numpy(on).to(dev), torch.from_numpy(with_adv).to(dev)
+    batch = api.Batch(hidden, [W], y, torch.from_numpy(cu).to(dev), mask)
+    ws = api._workspace(api.at_grpo_workspace_bytes(api.CALL_POLICY_LOSS_FWD_BWD, batch), dev)
+    ws[:ws.numel() // 4 * 4].view(torch.int32).fill_(masked)
+    old = (lp + 0.05 * torch.randn(n, generator=gen, device=dev, dtype=torch.float64).clamp(-3, 3)).float()
+    out = api.at_grpo_policy_loss_fwd_bwd(batch, old, torch.tensor(adv, dtype=torch.float32, device=dev), 0.2, 0.2)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == SEQLENS
+    assert int(out["n_valid"][0]) == n_valid
+    zero = torch.zeros_like(lp)
+    for got, ref in ((out["logp"], lp), (out["lse"], lse)):      # fp32 sums of 64 products and of 130 exponentials
+        assert float((got.double() - torch.where(on, ref, zero)).abs().max()) <= 2e-5
+        assert float(got[~on].abs().max()) == 0
+    assert bool(torch.isfinite(out["loss"]).all() and torch.isfinite(out["d_hidden"].float()).all() and torch.isfinite(out["dW"][0]).all())
+    assert float(out["d_hidden"][~(on & with_adv)].float().abs().max()) == 0
