@@ -80,6 +80,14 @@ struct ProfScope {
 
 int device_cu_count();
 
+// The limit belongs to the kernel, not to a launch: every caller sets the same `bytes` for it, or calls on other host threads
+// could find it lowered between this and their launch.
+template <typename K>
+int allow_big_lds(K kernel, int bytes) {
+  ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  return AT_GRPO_OK;
+}
+
 #ifdef __HIPCC__
 // ---- device helpers ------------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(static_cast<uint32_t>(v.bits) << 16); }

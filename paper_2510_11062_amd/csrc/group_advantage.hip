@@ -711,6 +711,7 @@ constexpr int kLargeBlocks = 1024;       // workgroups that finish the groups of
 constexpr int kTicketBins = 32;    // bins that draw tickets from one counter (one for all: 446 us instead of 441 where all bins are large)
 constexpr int kSortPer = 16;       // responses per thread of the pools whose blocks are sorted
 constexpr int kSortUsed = kPoolThreads * kSortPer / 64;      // bins that a sorted block uses at the least (runs of 64)
+constexpr int kSortLds = (2 * kPoolThreads * kSortPer + kPoolMaxBins) * 4, kTurnLds = kPoolThreads * kSortPer * 8;
 
 struct PoolPlan {
   int width, bins;           // bin of a key = key / width
@@ -900,7 +901,7 @@ __global__ __launch_bounds__(kPoolThreads) void k_gp_partition_sorted(int n_resp
   __shared__ int lds16[16];
   int* place = lds;                // [B]
   int* field = lds + B;            // [B]; until the places are known: distance of a bin's places from its local ones
-  int* next = lds + 2 * B;         // [bins]
+  int* next = lds + 2 * B;         // [bins], at most kPoolMaxBins
   const int tid = threadIdx.x;
   if (p.sorted[blockIdx.x] < 0) {
     if (ALL) partition_block(n_resp, reward, p, next);
@@ -1543,10 +1544,9 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     // rollout order 19 us; k_gp_partition 18 and the launch in front of it 5); more of them take a second one for those not sorted.
     const bool may_sort = p.pool.per == kSortPer, one_round = blocks <= static_cast<unsigned>(device_cu_count());
     if (may_sort) {
-      const int bytes = (2 * kPoolThreads * kSortPer + p.pool.bins) * 4;
       auto k = one_round ? k_gp_partition_sorted<true> : k_gp_partition_sorted<false>;
-      ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-      hipLaunchKernelGGL(k, dim3(blocks), dim3(kPoolThreads), bytes, s, n_resp, rw, p.pool);
+      ATG_TRY(allow_big_lds(k, kSortLds));
+      hipLaunchKernelGGL(k, dim3(blocks), dim3(kPoolThreads), kSortLds, s, n_resp, rw, p.pool);
       ATG_LAUNCH_CHECK();
     }
     if (!may_sort || !one_round) {
@@ -1561,10 +1561,9 @@ int run_group_advantage(int32_t n_resp, int32_t n_env, int32_t n_agent, int32_t 
     ATG_LAUNCH_CHECK();
     // both behind k_gp_out, which lists the members of the large bins
     if (may_sort) {
-      const int bytes = kPoolThreads * kSortPer * 8;
-      ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gp_turn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+      ATG_TRY(allow_big_lds(k_gp_turn, kTurnLds));
       hipLaunchKernelGGL(k_gp_turn, dim3(std::max(blocks, static_cast<unsigned>(kLargeBlocks * 256 / kPoolThreads))), dim3(kPoolThreads),
-                         bytes, s, p.pool, n_resp, static_cast<int>(blocks), rw, st, o);
+                         kTurnLds, s, p.pool, n_resp, static_cast<int>(blocks), rw, st, o);
       ATG_LAUNCH_CHECK();
     } else {
       hipLaunchKernelGGL(k_gp_large, dim3(kLargeBlocks), dim3(256), 0, s, p.pool, rw, st, o);

@@ -38,12 +38,6 @@ inline size_t logit_part_floats(int n_vtiles, int64_t TC) {
   return static_cast<size_t>(n_vtiles) * static_cast<size_t>(TC > stride ? TC : stride);
 }
 
-template <typename K>
-int allow_big_lds(K kernel, int bytes) {
-  ATG_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-  return AT_GRPO_OK;
-}
-
 // persistent grid: one workgroup per compute unit
 inline int gemm_grid() {
   const int cus = device_cu_count();

@@ -1,6 +1,8 @@
 """Grouping at the sizes where the launch plan changes: one launch (key ranges), pools (partition by key range), and the
 histogram pipeline for what neither takes.  Integers against the oracle in full; advantages and statistics on groups
 the oracle handles one by one, within 1e-4 (fp32 sums of a few members)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -287,3 +289,40 @@ def test_blocks_sorted_by_bin(gpu_device, n, order, crowded):
     gm, gs = host(out["group_mean"]).astype(np.float64)[gid], host(out["group_std"]).astype(np.float64)[gid]
     want = np.where(gs > 0, (x - gm) / np.where(gs > 0, gs, 1), 0)
     assert np.allclose(a[kept], want, rtol=1e-4, atol=1e-5)
+
+
+@pytest.mark.gpu
+def test_pools_of_two_host_threads(gpu_device):
+    """Two host threads, each with pools of its own size on its own stream: both kernels that need more LDS than a launch may ask
+    for by itself, with 1536 bins in one thread and 2048 in the other.  Every call has its own results."""
+    dev = gpu_device
+    pools = []
+    for n in (4300000, 8380000):
+        gen = torch.Generator(device=dev).manual_seed(n)
+        env = (torch.arange(n, device=dev, dtype=torch.int32) // 8)[torch.randperm(n, generator=gen, device=dev)].contiguous()
+        zero = torch.zeros(n, dtype=torch.int32, device=dev)
+        pools.append((env, zero, zero, torch.rand(n, generator=gen, device=dev), (n + 7) // 8, 1, 1))
+    ref = [{k: v.clone() for k, v in api.at_grpo_group_advantage(*p).items() if k != "workspace"} for p in pools]
+    torch.cuda.synchronize()
+    say("[grouping] pools of two host threads")
+    start, failed = threading.Barrier(2), []
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                start.wait()
+                for _ in range(30):
+                    out = api.at_grpo_group_advantage(*pools[i])
+                    stream.synchronize()
+                    assert api.error_word(out["workspace"]) == 0
+                    failed.extend((i, k) for k in ref[i] if not torch.equal(out[k], ref[i][k]))
+        except Exception as e:      # an assertion in another thread does not fail the test by itself
+            failed.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
