@@ -1010,12 +1010,16 @@ __global__ __launch_bounds__(kBinThreads, 4) void k_gp_bin(PoolPlan p, const flo
   const int lo = bin * p.width;
   const int own = static_cast<int>(min(static_cast<int64_t>(p.width), n_keys - lo));
   // The workgroup that is the last to have counted its bin's groups turns the counts into ids of first groups: 3 to 5 us in this
-  // launch, where one of its own took 6.5 and its gap.  The counts pass between the XCDs' caches as atomics; the exchange has returned before the ticket is drawn.
+  // launch, where one of its own took 6.5 and its gap.  Only the counts have to be in order with the tickets, and they are atomics,
+  // performed where all XCDs meet.  So it takes no more than that the exchange has returned before the ticket is drawn: the
+  // statement between them needs its result, and no access to memory passes it in either direction.  (With a release on the ticket
+  // and an acquire on the last one instead, every workgroup writes its L2 back: 2^22 shuffled 159 -> 176 us, in rollout order 120 ->
+  // 138, 2^24 620 -> 757 and 403 -> 537.)  The reading side is behind the barrier that hands `last` on.
   int before = 0, ticket = 0;
   auto publish = [&](int n_groups) { if (tid == 0) before = atomicExch(&p.bin_groups[bin], n_groups); };
   auto draw = [&] {
     if (tid != 0) return;
-    asm volatile("" : "+v"(before));
+    asm volatile("" : "+v"(before) : : "memory");
     ticket = atomicAdd(&p.bins_done[1 + bin / kTicketBins], 1);
   };
   auto scan_if_last = [&] {
