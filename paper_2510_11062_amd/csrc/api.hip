@@ -457,7 +457,6 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
     ATG_TRY(launch_compact(p.L, p.SB, true, s));
     ATG_TRY(launch_fill_i32(p.gates, p.n_gates, 0, s));
   }
-  ATG_TRY(enqueue_logprob_lists(batch, p, p.gF, p.SF, logp, lse, nullptr, s));
   ATG_TRY(launch_fill_bytes16(d_hidden, p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize, s));
   const CoefArgs ca = make_coef_args(p.S, old_logp, adv, eps_low, eps_high, agg, grad_loss);
 
@@ -476,7 +475,7 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
         ATG_TRY(launch_ref_logit(gs, sub, batch->hidden, batch->W[m], batch->token_id, p.c2, s));
         ATG_TRY(launch_head_fe(gs, sub, batch->hidden, batch->W[m], batch->token_id, p.c2, E_sub, p.part_s, p.zy, s));
         ATG_TRY(launch_fe_combine(gs, sub, m, p.part_s, p.c2, p.zy, batch->token_id, ca, logp, lse, scale_sub,
-                                  E_sub, gate, s));
+                                  E_sub, gate, p.SF.idx + static_cast<size_t>(m) * p.L.n_tok, p.SF.cnt + m, s));
         // exponent range exceeded somewhere in this launch: the two-pass kernels redo it (they return at once
         // otherwise)
         ATG_TRY(launch_head_fwd(gs, sub, batch->hidden, batch->W[m], batch->token_id, p.part_m, p.part_s, nullptr,
@@ -495,6 +494,8 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
                              c == 0 ? 1 : 0, s, p.live_cnt));
     }
   }
+  // rows without an advantage that have a list of their own, or whose exponentials left their range
+  ATG_TRY(enqueue_logprob_lists(batch, p, p.gF, p.SF, logp, lse, nullptr, s));
   return launch_surrogate(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, loss, clip_mask, n_valid, false, s);
 }
 

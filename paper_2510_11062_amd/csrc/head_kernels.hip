@@ -162,7 +162,8 @@ __global__ __launch_bounds__(256) void k_ref_logit(const bf16_t* __restrict__ hi
 
 // Thread layout of k_lse_combine.  Per token of the launch: S, lse, logp; the backward coefficient g and the row factor
 // a = -g / S; the element of E that carries the onehot term is replaced by e_y - S.  A row whose S is not in
-// [.., 2^60) (overflow, NaN) or whose reference is not finite raises the gate and gets a = 0.
+// [.., 2^60) (overflow, NaN) or whose reference is not finite raises the gate and gets a = 0.  Without an advantage it needs no
+// gradient, and the whole launch is not redone for its log-probability: it joins the list of such rows (`later`, *n_later of them).
 __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                                                             int c0, int TC, int V, int n_vtiles, int narrow, int head,
                                                             const float* __restrict__ part_s,
@@ -171,7 +172,8 @@ __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __res
                                                             const int32_t* __restrict__ token_id, CoefArgs ca,
                                                             float* __restrict__ logp, float* __restrict__ lse,
                                                             float* __restrict__ scale, bf16_t* __restrict__ E, int Vp,
-                                                            int32_t* __restrict__ gate) {
+                                                            int32_t* __restrict__ gate, int32_t* __restrict__ later,
+                                                            int32_t* __restrict__ n_later) {
   __shared__ float ss[kCmbSlices][kCmbTokens + 1];
   const int n = chunk_count(cnt, c0, TC);
   if (static_cast<int>(blockIdx.x) * kCmbTokens >= n) return;
@@ -208,7 +210,9 @@ __global__ __launch_bounds__(kCmbThreads) void k_fe_combine(const int32_t* __res
     scale[j] = (ok && g != 0.f) ? -g / St : 0.f;
     const float ey = fast_exp2(fmaf(zy[j], kLog2e, -c2v));
     E[static_cast<size_t>(j) * Vp + token_id[row]] = f32_to_bf16(ey - St);
-    if (!ok) atomicOr(gate, 1);
+    if (ok) return;
+    if (ca.adv[ca.resp_of_tok[row]] == 0.f) later[atomicAdd(n_later, 1)] = row;
+    else atomicOr(gate, 1);
   }
 }
 
@@ -404,10 +408,11 @@ int launch_head_fe(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
 
 int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const float* part_s, const float* c2,
                       const float* zy, const int32_t* token_id, const CoefArgs& ca, float* logp, float* lse,
-                      float* scale, void* E, int32_t* gate, hipStream_t s) {
+                      float* scale, void* E, int32_t* gate, int32_t* later, int32_t* n_later, hipStream_t s) {
   ProfScope ps(PROF_LSE_COMBINE, s);
   hipLaunchKernelGGL(k_fe_combine, dim3(g.TC / kCmbTokens), dim3(kCmbThreads), 0, s, ch.idx, ch.cnt, ch.c0, g.TC, g.V, g.n_vtiles,
-                     narrow_launches_bf16(g), head, part_s, c2, zy, token_id, ca, logp, lse, scale, static_cast<bf16_t*>(E), g.Vp, gate);
+                     narrow_launches_bf16(g), head, part_s, c2, zy, token_id, ca, logp, lse, scale, static_cast<bf16_t*>(E), g.Vp, gate,
+                     later, n_later);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

@@ -79,10 +79,10 @@ int launch_head_fe(const HeadGeom& g, const HeadChunk& ch, const void* hidden, c
                    const int32_t* token_id, const float* c2, void* E, float* part_s, float* zy, hipStream_t s);
 
 // logp / lse of the rows; scale[j] = -g_j / S_j; E[j][y_j] = e_y - S_j; raises *gate when a row's sum is
-// out of range (that row gets scale 0).
+// out of range (that row gets scale 0), unless the row has no advantage: it then goes to later[(*n_later)++], in any order.
 int launch_fe_combine(const HeadGeom& g, const HeadChunk& ch, int head, const float* part_s, const float* c2,
                       const float* zy, const int32_t* token_id, const CoefArgs& ca, float* logp, float* lse,
-                      float* scale, void* E, int32_t* gate, hipStream_t s);
+                      float* scale, void* E, int32_t* gate, int32_t* later, int32_t* n_later, hipStream_t s);
 
 // bf16: d_hidden[row] = dZ[j] . W for the rows of this super-chunk.
 // With `scale`, row j of the result is multiplied by scale[j] (j counted from ch.c0).  With `perm` (after

@@ -103,13 +103,53 @@ def test_rows_without_advantage(gpu_device, with_adv, without):
 
 
 @pytest.mark.gpu
-def test_hidden_rows_without_advantage_need_not_be_finite(gpu_device):
-    say("[few] infinite hidden rows without an advantage")
-    lengths = [30, 70, 40]
+@pytest.mark.parametrize("without", [70, 2200])       # on the list of the others, and on one of their own
+def test_rows_without_advantage_out_of_range(gpu_device, without):
+    """Rows without an advantage whose exponentials leave their range (targets that are all but impossible) or whose hidden state is
+    infinite: they get their own log-probability, and the others' results stay the same bits, which they do not where the
+    launch is redone by the kernels that round softmax - onehot."""
+    say(f"[few] {without} rows without an advantage, some of them out of range")
+    a, b = without - 40, 40
+    lengths = [a, 70, b]
     batch, logp, old, adv = make(gpu_device, lengths, [0.0, 0.7, 0.0], 128, 2000)
     _, _, dh, dw = reference(batch, logp, old, adv, lengths)
-    batch.hidden[100:103] = float("inf")
+    clean = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, EPS, EPS)
+    clean = {k: clean[k][0].clone() if k == "dW" else clean[k].clone() for k in ("logp", "d_hidden", "dW")}
+    far, inf = [0, 7, a - 1, a + 70], [a + 75, a + 109]
+    batch.hidden[far] *= 512
+    z = batch.hidden[far].double() @ batch.W[0].double().T
+    batch.token_id[far] = z.argmin(1).int()
+    want = z.min(1).values - z.logsumexp(1)
+    assert float(want.max()) < -100               # beyond e^-88 for certain
+    batch.hidden[inf] = float("inf")
     step = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, EPS, EPS)
+    torch.cuda.synchronize()
+    close(step["d_hidden"], dh, "d_hidden")
+    close(step["dW"][0], dw, "dW")
+    assert torch.equal(step["d_hidden"], clean["d_hidden"]) and torch.equal(step["dW"][0], clean["dW"])
+    rest = torch.ones(sum(lengths), dtype=torch.bool, device=gpu_device)
+    rest[far + inf] = False
+    assert torch.equal(step["logp"][rest], clean["logp"][rest])
+    # logits of up to a few hundred: fp32 sums of 128 products
+    assert float((step["logp"][far].double() - want).abs().max()) <= 4e-6 * float(z.abs().max())
+
+
+@pytest.mark.gpu
+def test_rows_of_both_kinds_out_of_range(gpu_device):
+    """The launch is redone for a row with an advantage; the rows without one get their log-probability all the same."""
+    say("[few] rows of both kinds out of range")
+    lengths = [30, 70, 40]
+    batch, logp, old, adv = make(gpu_device, lengths, [0.0, 0.7, 0.0], 128, 2000)
+    far = [0, 29, 100, 110, 139]
+    batch.hidden[far + [50]] *= 512
+    z = batch.hidden.double() @ batch.W[0].double().T
+    batch.token_id[far + [50]] = z[far + [50]].argmin(1).int()
+    logp = torch.log_softmax(z, 1)
+    old[50] = logp[50, batch.token_id[50].long()].float()
+    lp, _, dh, dw = reference(batch, logp, old, adv, lengths)
+    step = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, EPS, EPS)
+    torch.cuda.synchronize()
+    assert float((step["logp"].double() - lp).abs().max()) <= 4e-6 * float(z.abs().max())
     close(step["d_hidden"], dh, "d_hidden")
     close(step["dW"][0], dw, "dW")
 
