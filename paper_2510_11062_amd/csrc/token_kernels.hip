@@ -537,11 +537,15 @@ constexpr int kPsThreads = 1024, kPsRows = 32768, kPsPer = 8, kPsTile = kPsThrea
 constexpr int kPsBatch = 4;            // rows of a response that a lane requests before it uses the first
 constexpr int kPsNoAdv = 0x40;         // mark of a participating row: its head, with this bit where the advantage is zero
 // Up to so many rows without an advantage join the list of a head's other rows, behind them (their factor is zero, so they
-// are taken out again in front of the backward contractions).  A list of their own costs a pass over the head's weights and
-// tiles that do not fill the chip; on the common list they cost the write of their exponentials, 7 % of their contraction.
-// (Micro-batch of 2300 rows at the full vocabulary: 212 us for a few hundred rows of their own beside 1041 for the others'
-// exponentials, 1107 together.)
-constexpr int kPsMerge = 2048;
+// are taken out again in front of the backward contractions); up to kPsMergeMost where as many have one.  A list of their own costs
+// a pass over the head's weights and tiles that do not fill the chip; on the common list they cost the write of their exponentials,
+// 7 % of their contraction, and few rows with an advantage in front of them a whole tile more of it.  Steps on two lists and on one,
+// us, rows with + without an advantage (H = 2048 at V = 32000, H = 2048 and H = 4096 at V = 151936):
+//   64 + 64     246, 759, 1352 and 223, 648, 1143     64 + 512    272, 895, 1623 and 283, 870, 1562
+//   64 + 1024   311, 1109, 2049 and 343, 1129, 2036   200 + 1536  395, 1514, 2859 and 421, 1508, 2788
+//   700 + 768   484, 1823, 3472 and 468, 1801, 3416   700 + 1536  542, 2171, 4128 and 563, 2173, 4113
+//   2000 + 1024 847, 3787, 7225 and 863, 3751, 7132   2000 + 2000 941, 4128, 7918 and 954, 4190, 7987
+constexpr int kPsMerge = 512, kPsMergeMost = 1024;
 static_assert(kMaxHeads <= kPsNoAdv, "head and flag share a byte");
 
 struct PrepArgs {
@@ -702,7 +706,7 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
       int32_t* out_b = a.idx_b + static_cast<size_t>(m) * n;
       int32_t* out_f = MODE == PREP_STEP ? a.idx_f + static_cast<size_t>(m) * n : nullptr;
       const int rows_f = MODE == PREP_STEP ? listed[m] >> 16 : 0, rows_b = MODE == PREP_STEP ? listed[m] & 0xffff : 0;
-      merge = rows_b > 0 && rows_f > 0 && rows_f <= kPsMerge;
+      merge = rows_b > 0 && rows_f > 0 && rows_f <= max(kPsMerge, min(rows_b, kPsMergeMost));
       if (merge) out_f = out_b + rows_b;
       for (int base = 0; base < n; base += kPsTile) {
         const int t0 = base + tid * kPsPer;

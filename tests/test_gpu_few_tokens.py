@@ -91,10 +91,11 @@ def test_few_tokens(gpu_device, n, H, V):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("with_adv,without", [(1, 1), (100, 2048), (100, 2049), (700, 300), (64, 63)])
+@pytest.mark.parametrize("with_adv,without", [(1, 1), (100, 2048), (100, 2049), (700, 300), (64, 63), (64, 512), (64, 513), (700, 700),
+                                              (700, 701), (1100, 1024), (1100, 1025)])
 def test_rows_without_advantage(gpu_device, with_adv, without):
-    """Up to 2048 of them stand on the list of the others; wherever they stand they get their log-probability and no gradient,
-    also where their ratio overflows."""
+    """Up to 512 of them stand on the list of the others, up to 1024 where as many have an advantage; wherever they stand they get
+    their log-probability and no gradient, also where their ratio overflows."""
     say(f"[few] {with_adv} rows with and {without} without an advantage")
     lengths = [without - without // 2, with_adv, without // 2]
     batch, logp, old, adv = make(gpu_device, lengths, [0.0, 0.7, 0.0], 128, 2000)
