@@ -153,7 +153,7 @@ def run_config(cfg, dev, steps, warmup, path="one_pass"):
     grad_rows = valid & (A_tok != 0) & ((fwd["clip_mask"] & 4) == 0)
     n_grad = int(grad_rows.sum().item())
     hv2 = 2.0 * cfg.H * cfg.V
-    if path == "one_pass":
+    if path == "one_pass" and cfg.dtype == "bf16":
         # rows of non-zero advantage get their logits once (head_fe), the others only their log-probability
         # (head_fwd); the two backward contractions run over the first class and are credited with the rows that
         # carry gradient (the clipped ones among them multiply by a zero factor)
@@ -165,6 +165,8 @@ def run_config(cfg, dev, steps, warmup, path="one_pass"):
     else:
         flops = {"head_fwd": hv2 * n_valid, "head_dz": hv2 * n_grad, "head_dh": hv2 * n_grad, "head_dw": hv2 * n_grad}
         rows_of = {"head_fwd": valid, "head_dz": grad_rows, "head_dh": grad_rows, "head_dw": grad_rows}
+        if prof["head_dw"][0] == 0:       # small fp32 batches: both gradients in one launch, timed as head_dh
+            flops["head_dh"] += flops.pop("head_dw")
     kern = max(flops, key=lambda k: prof[k][1])
     kern_ms = prof[kern][1] / steps
     achieved = flops[kern] / (kern_ms * 1e-3) / 1e12

@@ -367,7 +367,8 @@ int32_t at_grpo_version(void);
  *   at_grpo_profile_enable(1) starts recording, (0) stops and drops what was recorded.
  *   at_grpo_profile_read synchronises the recorded events and returns, for kernel class
  *   `which` (0 .. at_grpo_profile_classes()-1), the number of launches and their total
- *   duration in milliseconds since recording started; the name is a static string.
+ *   duration in milliseconds since recording started; the name is a static string.  Small fp32
+ *   batches compute both gradients of the head in one launch, which counts as "head_dh".
  */
 int at_grpo_profile_enable(int32_t on);
 int32_t at_grpo_profile_classes(void);

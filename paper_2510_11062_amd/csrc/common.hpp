@@ -59,7 +59,7 @@ enum ProfClass {
   PROF_COEF,           // backward coefficient g_t
   PROF_TRANSPOSE,      // W^T and gathered hidden^T
   PROF_HEAD_DZ,        // logits recompute + dZ
-  PROF_HEAD_DH,        // dHidden = dZ W
+  PROF_HEAD_DH,        // dHidden = dZ W; fp32 launches that compute dW as well, or add up the parts of both
   PROF_HEAD_DW,        // dW = dZ^T hidden
   PROF_FILL,           // buffer clears
   PROF_GRAD_NORM,      // global gradient norm of the head update

@@ -638,22 +638,26 @@ int launch_grads_f32(const HeadGeom& g, const HeadChunk& ch, const void* dZ, con
   a.w_parts = dw_parts(g);
   const int64_t of_h = static_cast<int64_t>(a.h_tiles) * a.t_tiles * a.h_parts, of_w = w_tiles * a.w_parts;
   a.of_h = static_cast<int>(of_h);
-  const auto launch = [&](int T, int64_t blocks) {
+  const auto launch = [&](int cls, int T, int64_t blocks) {
+    ProfScope ps(cls, s);
     auto k = T == 128 ? k_head_grads<128> : k_head_grads<64>;
     hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(blocks)), dim3(kF32Threads), 0, s, a);
   };
-  if (th == 64 && tw == 64 && of_h + of_w <= 3 * device_cu_count()) {      // three workgroups of 64 x 64 tiles fit a compute unit
-    launch(64, of_h + of_w);
+  // three workgroups of 64 x 64 tiles fit a compute unit
+  const bool together = th == 64 && tw == 64 && of_h + of_w <= 3 * device_cu_count();
+  if (together) {
+    launch(PROF_HEAD_DH, 64, of_h + of_w);
   } else {
-    launch(th, of_h);
+    launch(PROF_HEAD_DH, th, of_h);
     ATG_LAUNCH_CHECK();
     a.of_h = 0;
-    launch(tw, of_w);
+    launch(PROF_HEAD_DW, tw, of_w);
   }
   ATG_LAUNCH_CHECK();
   const unsigned hb = a.h_parts > 1 ? sum_blocks(static_cast<int64_t>(g.TC) * g.H / 4) : 0;
   const unsigned wb = a.w_parts > 1 ? sum_blocks(static_cast<int64_t>(g.V) * g.H / 4) : 0;
   if (hb + wb > 0) {
+    ProfScope ps(together || hb > 0 ? PROF_HEAD_DH : PROF_HEAD_DW, s);
     hipLaunchKernelGGL(k_head_grads_sum, dim3(hb + wb), dim3(kF32Threads), 0, s, a, static_cast<int>(hb));
     ATG_LAUNCH_CHECK();
   }

@@ -450,7 +450,6 @@ int launch_head_dw(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const
 
 int launch_head_grads(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* hidden, void* d_hidden,
                       float* dW, void* part, int accumulate, int first_chunk, hipStream_t s) {
-  ProfScope ps(PROF_HEAD_DH, s);
   if (g.dtype == AT_GRPO_BF16) return AT_GRPO_EUNSUPPORTED;
   return launch_grads_f32(g, ch, dZ, W, hidden, d_hidden, dW, part, accumulate, first_chunk, s);
 }

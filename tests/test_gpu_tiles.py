@@ -67,6 +67,46 @@ def test_fp32_tiles(gpu_device, H, V, E, K, length):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("accumulate", [False, True], ids=["overwrite", "accumulate"])
+@pytest.mark.parametrize("over", [0, 1], ids=["one launch", "two launches"])
+def test_fp32_gradients_of_three_heads_in_one_launch_or_two(gpu_device, over, accumulate):
+    """The last size at which the workgroups of dHidden and dW fit the chip together (three per compute unit), and the first at
+    which they do not: 210 rows are 4 tiles of dHidden in 32 parts each, and dW has a tile per 64 vocabulary rows.  The
+    profile says which of them were launched.  Against torch in 64 bits: fp32 sums of up to V products, 1e-5."""
+    dev, H, heads = gpu_device, 64, 3
+    V = 64 * (3 * torch.cuda.get_device_properties(dev).multi_processor_count - 4 * 32) + over
+    say(f"[tiles] fp32 V={V} accumulate={accumulate}")
+    gen = torch.Generator(device=dev).manual_seed(V)
+    n, R = 210, 6
+    hidden = torch.randn(n, H, generator=gen, device=dev)
+    W = [torch.randn(V, H, generator=gen, device=dev) * 0.05 for _ in range(heads)]
+    y = torch.randint(0, V, (n,), generator=gen, device=dev, dtype=torch.int32)
+    y[-1] = V - 1
+    cu = torch.arange(R + 1, device=dev) * (n // R)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=dev)
+    adv = torch.tensor([1.0, -0.5, 0.8, 0.0, 2.0, -1.0], device=dev)
+    batch = api.Batch(hidden, W, y, cu, None, i32([0, 1, 2, 0, 1, 2]), i32([0, 1, 2]))
+    old = api.at_grpo_token_logprob(batch)["logp"].clone()
+    dW0 = [torch.randn(V, H, generator=gen, device=dev) * 1e-3 for _ in range(heads)]
+    dW = [w.clone() for w in dW0]
+    api.at_grpo_profile_enable(True)
+    out = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, 0.2, 0.2, dW=dW, accumulate_dW=accumulate)
+    torch.cuda.synchronize()
+    prof = api.at_grpo_profile_read()
+    api.at_grpo_profile_enable(False)
+    assert prof["head_dh"][0] >= heads and (prof["head_dw"][0] >= heads) == bool(over)
+    rows = torch.arange(n, device=dev)
+    for m in range(heads):
+        mine = (rows // (n // R)) % heads == m
+        h, t = hidden[mine].double(), y[mine].long()
+        g = -adv[rows[mine] // (n // R)].double() / int(mine.sum())       # ratio 1
+        dz = -g[:, None] * torch.softmax(h @ W[m].double().T, 1)
+        dz[torch.arange(len(t), device=dev), t] += g
+        for got, ref in ((out["d_hidden"][mine], dz @ W[m].double()), (dW[m], dz.T @ h + (dW0[m].double() if accumulate else 0))):
+            assert float((got.double() - ref).norm() / ref.norm()) <= 1e-5
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("one_pass", [True, False], ids=["one_pass", "two_calls"])
 @pytest.mark.parametrize("dtype,V,H,n", [(torch.bfloat16, 34_200_003, 64, 300), (torch.bfloat16, 8_600_001, 64, 12_400),
                                          (torch.float32, 8_500_003, 32, 300)],
