@@ -431,8 +431,9 @@ int launch_compact_rows(const HeadGeom& g, const HeadChunk& ch, const float* sca
 
 size_t head_partial_bytes(const HeadGeom& g) {
   if (g.dtype != AT_GRPO_BF16) return partial_bytes_f32(g);
-  const int64_t ht = ceil_div(g.H, 256), dh = g.TC / 256 * ht, dw = g.n_vtiles * ht;
-  return split_k_bytes(dh > dw ? dh : dw);
+  const int64_t ht = ceil_div(g.H, 256);
+  const size_t dh = split_k_bytes(g.TC / 256 * ht, g.Vp / kRowStep), dw = split_k_bytes(g.n_vtiles * ht, g.TC / kRowStep);
+  return dh > dw ? dh : dw;
 }
 
 int launch_head_dh(const HeadGeom& g, const HeadChunk& ch, const void* dZ, const void* W, const void* Wt, void* d_hidden,

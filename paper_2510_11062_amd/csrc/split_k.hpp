@@ -17,6 +17,7 @@
 namespace atg {
 
 constexpr int kSplitMax = 64;              // parts per tile
+constexpr int kSplitSteps = 4;             // k-steps of a part at the least
 constexpr int kSplitTiles = 1024;          // partial tiles a launch may leave
 constexpr size_t kPartialTileBytes = size_t{256} * 256 * 4;
 
@@ -24,10 +25,11 @@ struct SplitK {
   int full, rest, S, chunk;                // tiles done whole; tiles split; parts per split tile; k-steps per part
 };
 
-// bytes of partials that a launch over at most `tiles` tiles needs
-inline size_t split_k_bytes(int64_t tiles) {
-  const int64_t most = tiles * kSplitMax;
-  return static_cast<size_t>(most < kSplitTiles ? most : kSplitTiles) * kPartialTileBytes;
+// bytes of partials that a launch over at most `tiles` tiles of at most `nk` k-steps needs
+inline size_t split_k_bytes(int64_t tiles, int64_t nk) {
+  const int64_t parts = nk / kSplitSteps < kSplitMax ? nk / kSplitSteps : kSplitMax;
+  if (parts < 2) return 0;
+  return static_cast<size_t>(tiles * parts < kSplitTiles ? tiles * parts : kSplitTiles) * kPartialTileBytes;
 }
 
 #ifdef __HIPCC__
@@ -40,7 +42,7 @@ __device__ __forceinline__ SplitK plan_split(int tiles, int nk, int grid) {
   if (p.rest == 0) return p;
   int best = nk * 16;                       // in sixteenths of a step
   for (int S = 2; S <= kSplitMax; S += S < 16 ? 1 : 8) {
-    if (S * 4 > nk || p.rest * S > kSplitTiles) continue;   // parts of at least four steps
+    if (S * kSplitSteps > nk || p.rest * S > kSplitTiles) continue;
     const int chunk = (nk + S - 1) / S;
     const int cost = (p.rest * S + grid - 1) / grid * chunk * 16 + p.rest * S * 3 / 2 + 80;
     if (cost < best) {

@@ -92,6 +92,18 @@ def test_workspace_query_and_argument_errors_on_host():
     assert lib.at_grpo_surrogate_diagnostics(b, None, None, None, 0.2, 0.2, None, None, None, 0, None) == 1
 
 
+def test_room_for_partial_results():
+    """Of a small head no more than its few k-steps can be cut into (here dHidden's one tile of 16 steps into four parts, 1 MiB), of a
+    large one 1024 partial tiles."""
+    b = api._Batch()
+    b.dtype, b.n_heads, b.n_resp = 1, 1, 8
+    b.H, b.V, b.n_tok = 64, 1000, 256
+    assert api.load_library().at_grpo_workspace_bytes(api.CALL_POLICY_LOSS_BWD, b, 0, 0, 0, 0) < 2 << 20
+    b.H, b.V, b.n_tok = 2048, 151936, 2300
+    rest = api.load_library().at_grpo_workspace_bytes(api.CALL_POLICY_LOSS_BWD, b, 0, 0, 0, 0) - 2304 * (151936 + 2048) * 2
+    assert 0 <= rest - (256 << 20) < 1 << 20
+
+
 # ---------------------------------------------------------------------------- S1 + S2
 def run_group_advantage(dev, st, cfg, **kw):
     i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(dev)
