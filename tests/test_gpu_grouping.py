@@ -40,6 +40,7 @@ CASES = {
     "pool: the last bin, groups of 15 to 18": (262143, 1, 2, lambda rng, n: np.where(np.arange(n) >= n - 2000, rng.integers(15, 19, n), np.arange(n) % 8 == 0)),
     "pool: large bins among small ones": (3000, 2, 12, lambda rng, n: np.where(np.arange(n) // 2000 % 3 == 1, 24, rng.random(n) < 0.3)),
     "pool: large bins only": (6000, 2, 12, lambda rng, n: np.where(np.arange(n) < n // 16, 30, 0)),
+    "pool: blocks sorted by bin": (150001, 1, 2, lambda rng, n: np.full(n, 8)),
     "histogram: few keys": (4, 1, 2, lambda rng, n: np.full(n, 8800)),
     "histogram: few responses, many keys": (40000, 1, 2, lambda rng, n: (rng.random(n) < 0.2).astype(int)),
 }
@@ -103,7 +104,8 @@ def test_grouping_paths(gpu_device, name, mixed):
 @pytest.mark.gpu
 @pytest.mark.parametrize("over", ["team", "loc", "given"])
 @pytest.mark.parametrize("shape", [(4, 2, 2, 4), (16, 2, 4, 8), (20, 3, 5, 10), (512, 2, 1, 4), (257, 2, 1, 8), (4096, 2, 2, 4),
-                                   (1, 1, 2, 40000), (262144, 1, 1, 128, 1024), (65280, 1, 1, 200, 256)], ids=str)
+                                   (1, 1, 2, 40000), (262144, 1, 1, 128, 1024), (65280, 1, 1, 200, 256),
+                                   (300000, 1, 1, 8), (540000, 1, 1, 8)], ids=str)      # blocks sorted by bin: one round, more
 def test_results_in_place(gpu_device, shape, over):
     """Mixed rewards over one of their parts, and advantages over the rewards they come from: bit for bit what separate
     arrays give, on every launch plan."""
@@ -169,7 +171,7 @@ def test_pools_under_the_other_keys(gpu_device, group_by):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("where", ["spread", "one part"])
-@pytest.mark.parametrize("shape", [(8192, 1, 4, 3), (30000, 1, 2, 2), (5000, 1, 2, 3)], ids=str)
+@pytest.mark.parametrize("shape", [(8192, 1, 4, 3), (30000, 1, 2, 2), (5000, 1, 2, 3), (300000, 1, 2, 4)], ids=str)
 def test_scratch_and_tails_without_fill(gpu_device, shape, where):
     """A caller with the least workspace (no room for the pool path) and one that does not ask for filled tails: group for group
     the same bits (sums are taken in ascending order everywhere), nothing written behind the last group."""
@@ -289,6 +291,74 @@ def test_blocks_sorted_by_bin(gpu_device, n, order, crowded):
     gm, gs = host(out["group_mean"]).astype(np.float64)[gid], host(out["group_std"]).astype(np.float64)[gid]
     want = np.where(gs > 0, (x - gm) / np.where(gs > 0, gs, 1), 0)
     assert np.allclose(a[kept], want, rtol=1e-4, atol=1e-5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("group_by,E,R", [("trajectory", 600000, 2400011), ("parallel", 50000, 2400007), ("trajectory", 600000, 4300003)])
+def test_sorted_blocks_under_the_other_keys(gpu_device, group_by, E, R):
+    N, T, C = 2, 3, 4
+    rng = np.random.default_rng(R)
+    env, agent, turn, sample = (rng.integers(0, m, R).astype(np.int32) for m in (E, N, T, C))
+    reward = (rng.integers(0, 9, size=R) / np.float32(8)).astype(np.float32)
+    say(f"[grouping] sorted blocks by {group_by} R={R}")
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    out = api.at_grpo_group_advantage_keyed(group_by, dev(env), dev(agent), dev(turn), dev(reward), E, N, T, sample_id=dev(sample),
+                                            n_sample=C)
+    torch.cuda.synchronize()
+    assert api.error_word(out["workspace"]) == 0
+    gid, G, offs, perm = orc.group_segments(orc.group_key_by(env, agent, turn, sample, N, T, C, group_by))
+    assert int(out["n_groups"].item()) == G
+    assert np.array_equal(host(out["group_id"]), gid) and np.array_equal(host(out["perm"]), perm)
+    assert np.array_equal(host(out["seg_offsets"])[:G + 1], offs) and np.all(host(out["seg_offsets"])[G + 1:] == 0)
+    pick = np.sort(rng.choice(G, size=300, replace=False))
+    members = np.concatenate([perm[offs[g]:offs[g + 1]] for g in pick])
+    sub = np.repeat(np.arange(pick.size), [offs[g + 1] - offs[g] for g in pick])
+    adv, mean, std = orc.group_advantage(reward[members], sub, pick.size)
+    got = host(out["adv"]).astype(np.float64)[members]
+    assert np.all(got[std[sub] == 0] == 0) and np.allclose(got, adv, rtol=1e-4, atol=1e-6)
+    assert np.allclose(host(out["group_mean"])[pick], mean, rtol=1e-4, atol=1e-7)
+    assert np.allclose(host(out["group_std"])[pick], std, rtol=1e-4, atol=1e-7)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [2400001, 4300001])
+def test_replays_from_shuffled_to_rollout_order(gpu_device, n):
+    """A captured call whose blocks are sorted in one replay, are not in the next, and hold members of large bins in a third: what the
+    places of a block mean changes, and nothing of one pass reaches the next."""
+    E, rng = n // 8, np.random.default_rng(n)
+    order = np.arange(n) // 8 % E
+    shuffled = order[rng.permutation(n)]
+    crowded = shuffled.copy()
+    crowded[n // 3:n // 3 + 40000] = rng.integers(0, 2048, 40000)
+    half = np.concatenate([order[:n // 2], shuffled[n // 2:]])
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+    zero = torch.zeros(n, dtype=torch.int32, device=gpu_device)
+    batches = [(dev(k.astype(np.int32)), dev((rng.integers(0, 9, size=n) / np.float32(8)).astype(np.float32)))
+               for k in (shuffled, order, crowded, shuffled, half, order)]
+    env, reward = torch.empty_like(batches[0][0]), torch.empty_like(batches[0][1])
+    call = lambda: api.at_grpo_group_advantage(env, zero, zero, reward, E, 1, 1)
+    env.copy_(batches[0][0])
+    reward.copy_(batches[0][1])
+    call()
+    torch.cuda.synchronize()
+    say(f"[grouping] capture of sorted blocks n={n}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call()
+    for e, r in batches:
+        env.copy_(e)
+        reward.copy_(r)
+        ref = {k: v.clone() for k, v in call().items() if k != "workspace"}
+        torch.cuda.synchronize()
+        key = e.long()
+        assert int(ref["n_groups"].item()) == int(torch.unique(key).numel())
+        assert torch.equal(ref["perm"].long(), torch.sort(key, stable=True).indices)
+        for k in ref:
+            out[k].fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in ref:
+            assert torch.equal(out[k], ref[k]), k
 
 
 @pytest.mark.gpu

@@ -64,3 +64,57 @@ def test_rows_per_team(gpu_device, n_resp, mean, shift):
     assert np.array_equal(host(out["counts"]).astype(np.int64), counts)
     stats = host(out["stats"]).astype(np.float64)
     assert np.allclose(stats[:, 0], kl, rtol=1e-4, atol=1e-7) and np.allclose(stats[:, 1], ratio, rtol=1e-4, atol=0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_resp,mean", [(512, 160), (513, 160), (100, 70), (100, 20)])      # 256, 64, 32 and 16 lanes per response
+def test_data_errors_per_team(gpu_device, n_resp, mean):
+    """Bounds, agents and tokens out of range: the error word, and everything else as if those rows were masked; then clean data on
+    the same scratch memory, whose error word nothing clears beforehand."""
+    rng = np.random.default_rng(n_resp * mean)
+    cu = np.arange(n_resp + 1, dtype=np.int64) * mean
+    n, V, heads = n_resp * mean, 1000, 3
+    say(f"[surrogate] data errors, {n_resp} responses of {mean} rows")
+    logp = (-12 * rng.random(n)).astype(np.float32)
+    old = (logp + 0.2 * rng.standard_normal(n)).astype(np.float32)
+    token = rng.integers(0, V, n).astype(np.int32)
+    mask = (rng.random(n) < 0.9).astype(np.uint8)
+    adv = rng.standard_normal(n_resp).astype(np.float32)
+    agent = rng.integers(0, 3, n_resp).astype(np.int32)
+    head_of_agent = np.array([2, 0, 1, 7], np.int32)           # a fourth agent without a head
+    dev = lambda a: torch.from_numpy(a).to(gpu_device)
+
+    def check(want, token, cu_given, agent_given, out_resp, bad_tok):
+        batch = api.Batch(None, None, dev(token), dev(cu_given), dev(mask), dev(agent_given), dev(head_of_agent), n_tok=n, V=V, n_heads=heads)
+        good = mask.copy()
+        good[bad_tok] = 0
+        resp, head = orc.token_heads(n, cu, agent, head_of_agent)
+        good[np.isin(resp, out_resp)] = 0
+        for agg in ("token_mean", "seq_mean_token_mean"):
+            out = api.at_grpo_surrogate_from_logp(batch, dev(logp), dev(old), dev(adv), 0.2, 0.28, agg)
+            torch.cuda.synchronize()
+            assert api.error_word(out["workspace"]) == want
+            ref = orc.policy_loss_from_logp(logp, old, adv, good, head, resp, heads, 0.2, 0.28, agg)
+            has_bounds = np.repeat((np.diff(cu_given) >= 0) & (cu_given[:-1] >= 0) & (cu_given[1:] <= n), mean)
+            assert np.array_equal(host(out["clip_mask"])[has_bounds], ref[1][has_bounds]) and np.array_equal(host(out["n_valid"]), ref[2])
+            loss = host(out["loss"]).astype(np.float64)
+            assert np.all(np.abs(loss - ref[0]) <= 1e-4 * np.abs(ref[0]) + 1e-6), (loss, ref[0])
+        counts, kl, ratio = orc.surrogate_diagnostics(logp, old, adv, good, head, resp, heads, 0.2, 0.28)
+        out = api.at_grpo_surrogate_diagnostics(batch, dev(logp), dev(old), dev(adv), 0.2, 0.28)
+        torch.cuda.synchronize()
+        assert api.error_word(out["workspace"]) == want
+        assert np.array_equal(host(out["counts"]).astype(np.int64), counts)
+        stats = host(out["stats"]).astype(np.float64)
+        assert np.allclose(stats[:, 0], kl, rtol=1e-4, atol=1e-7) and np.allclose(stats[:, 1], ratio, rtol=1e-4, atol=0)
+
+    k, last = n_resp // 3, n_resp - 1
+    bad_cu, bad_agent, bad_token = cu.copy(), agent.copy(), token.copy()
+    bad_cu[k], bad_cu[-1] = -1, n + 5                          # responses k - 1 and k lose their common bound, the last one its end
+    bad_agent[[2, k + 2, last - 1]] = [-1, 4, 3]
+    at = np.nonzero(mask[5 * mean:6 * mean])[0][:3] + 5 * mean
+    bad_token[at] = [V, -1, 2 ** 31 - 1]
+    check(8, token, bad_cu, agent, [k - 1, k, last], [])
+    check(0, token, cu, agent, [], [])
+    check(16, token, cu, bad_agent, [2, k + 2, last - 1], [])
+    check(28, bad_token, bad_cu, bad_agent, [k - 1, k, last, 2, k + 2, last - 1], at)
+    check(0, token, cu, agent, [], [])
