@@ -41,7 +41,7 @@ KERNEL_SYMBOL = {"head_fwd": "k_head_fwd", "head_fe": "k_head_fe", "head_dz": "k
 
 
 # the kernels and the launch plan (rows per launch) that decides what one launch moves
-HEAD_KERNEL_SOURCES = ("common.hpp", "gemm_bf16.hpp", "split_k.hpp", "tile_order.hpp", "head_common.hpp", "head_kernels.hpp", "head_bf16.hip",
+HEAD_KERNEL_SOURCES = ("common.hpp", "gemm_bf16.hpp", "gemm_stream.hpp", "split_k.hpp", "tile_order.hpp", "head_common.hpp", "head_kernels.hpp", "head_bf16.hip",
                        "head_kernels.hip", "api.hip")
 
 

@@ -1,6 +1,6 @@
 // Workgroup-tile contraction of bf16 operands on the gfx950 matrix cores.
 //
-// One workgroup produces a 256 x 256 fp32 tile
+// One workgroup produces a 256 x 256 fp32 tile (or a part of one, see Grid16)
 //   C[a, b] = sum_k A[a, k] * B[b, k]
 // where each operand may be stored with its rows contiguous along k or k-major (rows of k, contiguous along
 // a or b).  Its wavefronts share the tile as a Grid16 (below).  k is consumed in steps of 64.
@@ -16,7 +16,8 @@
 // ahead of the MFMAs that consume them.  The direct loads go through inline asm: the compiler would otherwise make
 // every later LDS read wait for all outstanding direct loads.  Their completion is enforced by hand with s_waitcnt vmcnt
 // in front of the one workgroup barrier per k-step.  No value that the k loop uses may come from a load the compiler
-// has to wait for inside the loop (a spilled register, say): such a wait would drain the direct loads too.
+// has to wait for inside the loop (a spilled register, say): such a wait would drain the direct loads too.  (In the assembly, what
+// the kernels of head_bf16.hip spill lies outside their k loops, except four words a step of dW with 64-bit offsets.)
 //
 // Instruction order: a wavefront that issues a burst of LDS reads or direct loads keeps its SIMD's matrix pipe idle for
 // the length of the burst.  The loop body is therefore written out as a fixed sequence, pinned with scheduling barriers,
@@ -291,7 +292,8 @@ __device__ __forceinline__ int ring_byte(int first, int i) {
 // acc += a b, with the accumulator tied to its registers: the builtin leaves the compiler free to give the result other
 // registers than the addend, and with 256 accumulator registers per lane it then moves hundreds of them per k-step.  The
 // compiler does not see the instruction's latency, so mfma_settle() has to stand between the last one and the first
-// other use of an accumulator; consecutive MFMAs on one accumulator are at least 32 instructions apart.
+// other use of an accumulator.  Between two MFMAs on one accumulator stand the kMm - 1 others of a sub-step: 31 and more on whole
+// tiles, 15 and 7 on halves and quarters, of 16 cycles each, against the one whose result has to be there.
 template <typename G>
 __device__ __forceinline__ void mfma_in_place(floatx4& acc, bf16v8 a, bf16v8 b) {
   if constexpr (G::kMm * 4 > 128)

@@ -1,8 +1,9 @@
 // bf16 contractions of the LM head (gfx950): log-probabilities, exponentials, logit gradient, dHidden, dW.
 //
-// All of them are persistent grids of one workgroup per compute unit over 256 x 256 output tiles (gemm_bf16.hpp).  The
-// operand whose index is contiguous in the output is operand A: a lane then holds four consecutive outputs per
-// accumulator block, and results leave the registers as 16-byte stores without passing through LDS.
+// All of them are persistent grids of one workgroup per compute unit over 256 x 256 output tiles (gemm_bf16.hpp), which the
+// logits' last round cuts along the tokens; the logits of up to 192 tokens are streams over tiles of 128 vocabulary rows and 64,
+// 128 or 192 tokens (gemm_stream.hpp).  The operand whose index is contiguous in the output is operand A: a lane then holds four
+// consecutive outputs per accumulator block, and results leave the registers as 16-byte stores without passing through LDS.
 #include <type_traits>
 
 #include "gemm_bf16.hpp"
@@ -90,9 +91,10 @@ struct TokenCols {
 
 // The tiles it = first, first + gridDim.x, ... < end of one shape; place(it, &v0, &t0) says where a tile lies.  The next
 // tile's first two steps are requested in front of a tile's epilogue, whose LDS is the ring's last slot, and what the epilogue
-// has to look up is fetched beside the last two steps.  That takes 2 us of waiting from a tile of 50 to 100 us, and gives less,
-// since the clock falls as the matrix cores are busier: C2's step 393.6 -> 391.2 ms, entropy of 4700 rows at H = 2048
-// 4343 -> 4317 us, log-probabilities of 197 rows at H = 4096 381 -> 378.
+// has to look up is fetched beside the last two steps.  That takes 2 us of waiting from a tile, of 14 to 100 us, and gives less,
+// since the clock falls as the matrix cores are busier: log-probabilities of 3000 rows at H = 1024, V = 32000 184 -> 178 us, a step
+// of 8000 rows at H = 1024, V = 50000 2170 -> 2140, entropy of 4700 rows at H = 2048 4343 -> 4317; C2's step by less than its
+// runs differ (393.6 and 391.2 ms).
 // Off: offsets inside an operand panel
 template <typename G, bool PERMUTED, typename Off, typename Place, typename Epilogue>
 __device__ __forceinline__ void logit_tiles(const LogitIn& in, int first, int end, Place place, char* smem, Epilogue epi) {
@@ -386,7 +388,7 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&d)[8]) {
 
 // ------------------------------------------------------------------------------------------------
 // exponentials (one-pass forward + backward): E[j][v] = exp(z - c_j) for the tokens j of the launch (zero for the padding
-// columns V .. Vp and for the rows that pad the last tile); part_s[vt][j] = sum over the 256 vocabulary rows of tile vt;
+// columns V .. Vp and for the rows that pad the last tile); part_s = sums over the vocabulary rows of each tile, at part_index();
 // zy[j] = target logit
 // ------------------------------------------------------------------------------------------------
 struct FeEpilogue {

@@ -24,9 +24,10 @@ struct HeadChunk {
   int32_t c0;           // first list position of this super-chunk
 };
 
-// part_m / part_s: [n_vtiles][TC] per-(vocabulary tile, token) running max (log2 domain) and
-// sum; zy: [TC] target logit.  hidden / W are the caller's tensors.
-// part_u: null, or [n_vtiles][TC] partial sums for the entropy monitor (selects the kernel variant).
+// part_m / part_s: per-(vocabulary tile, token) running max (log2 domain) and sum, [n_vtiles][TC], in bf16 launches of few
+// tokens [ceil(V / kNarrowV)][kNarrowStride] (see narrow_launch; logit_part_floats() is room for both); zy: [TC] target
+// logit.  hidden / W are the caller's tensors.
+// part_u: null, or partial sums for the entropy monitor, laid out the same (selects the kernel variant).
 int launch_head_fwd(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                     const int32_t* token_id, float* part_m, float* part_s, float* part_u, float* zy,
                     hipStream_t s, const int32_t* gate = nullptr);
@@ -74,7 +75,7 @@ size_t head_partial_bytes(const HeadGeom& g);
 int launch_ref_logit(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                      const int32_t* token_id, float* c2, hipStream_t s);
 
-// E[j][v] = exp(z[j][v] - c_j) (bf16, [TC][Vp]); part_s[n_vtiles][TC] partial row sums; zy[TC] target logit.
+// E[j][v] = exp(z[j][v] - c_j) (bf16, [TC][Vp]); part_s partial row sums, laid out as above; zy[TC] target logit.
 int launch_head_fe(const HeadGeom& g, const HeadChunk& ch, const void* hidden, const void* W,
                    const int32_t* token_id, const float* c2, void* E, float* part_s, float* zy, hipStream_t s);
 

@@ -32,7 +32,7 @@ struct TokenScratch {
   int32_t* resp_len;     // [n_resp] participating rows per response
   int32_t* resp_cnt;     // [kMaxHeads] responses with at least one participating row, per head
   float* resp_sum;       // [n_resp] per-response sum (or mean) of surrogate terms
-  int32_t* resp_head;    // [n_resp] head of each response (-1: takes no part)
+  int32_t* resp_head;    // [n_resp] head of each response (kNoHead: takes no part) and, from bit kErrShift on, its data errors
   int64_t n_blk;         // ceil(n_tok / kTokPerBlock)
   int64_t n_blk256;      // ceil(n_tok / 256)
 };
