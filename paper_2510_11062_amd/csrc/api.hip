@@ -403,7 +403,7 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
         ATG_TRY(launch_head_grads(p.g, ch, p.dZ, batch->W[m], batch->hidden, d_hidden, dW[m], p.part, add, c == 0 ? 1 : 0, s));
         continue;
       }
-      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s));
+      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, nullptr, nullptr, nullptr, p.dZ));
       HeadGeom gs = p.g;
       gs.TC = p.sub;
       for (int c1 = 0; c1 < p.g.TC; c1 += p.sub) {

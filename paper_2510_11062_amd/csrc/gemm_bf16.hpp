@@ -58,7 +58,7 @@ struct Grid16 {
   static constexpr int kRowsA = TA / WA, kRowsB = TB / WB;             // rows of a wavefront's sub-tile
   static constexpr int kIB = kRowsA / 16, kJB = kRowsB / 16;           // accumulator blocks of a wavefront
   static constexpr int kLoadsA = TA / 8 / (WA * WB);                   // direct loads per step and wavefront
-  static constexpr int kLoadsB = TB / 8 / (WA * WB);
+  static constexpr int kLoadsB = (TB / 8 + WA * WB - 1) / (WA * WB);   // (TB = 160 or 224 on 8 wavefronts: rows past the tile's, unused)
   static constexpr int kMm = kIB * kJB, kRd = kIB + kJB;               // MFMAs and fragment reads per sub-step
   // a fragment read follows every kRdEvery-th MFMA: the last one must be early enough to land before the sub-step ends
   // (4 wavefronts, same box: every 3rd 1494 TFLOP/s at k = 151936 and 1414 with a k-major operand, every 4th 1472 and 1377)

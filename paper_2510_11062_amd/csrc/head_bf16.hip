@@ -4,6 +4,8 @@
 // logits' last round cuts along the tokens; the logits of up to 192 tokens are streams over tiles of 128 vocabulary rows and 64,
 // 128 or 192 tokens (gemm_stream.hpp).  The operand whose index is contiguous in the output is operand A: a lane then holds four
 // consecutive outputs per accumulator block, and results leave the registers as 16-byte stores without passing through LDS.
+#include <limits.h>
+
 #include <type_traits>
 
 #include "gemm_bf16.hpp"
@@ -20,7 +22,11 @@ namespace {
 // Short k loops (k = H) with a heavy epilogue: two wavefronts per SIMD, 128 vocabulary rows x 64 tokens each.  A token's
 // 128 logits of a wavefront are one 256-byte run of the stored exponentials.
 using GLogit = Grid16<2, 4>;
-// A half and a quarter of its tokens, for the last round of the persistent grid
+// Fewer tokens (balanced_tokens)
+using GLogit224 = Grid16<4, 2, kTile16, 224>;
+using GLogit192 = Grid16<4, 2, kTile16, 192>;
+using GLogit160 = Grid16<4, 2, kTile16, 160>;
+// At most a half and a quarter of a tile's tokens, for the last round of the persistent grid
 using GLogit128 = Grid16<4, 2, kTile16, 128>;
 using GLogit64 = Grid16<8, 1, kTile16, 64>;
 // Launches of few tokens (narrow_launch), on tiles of 128 vocabulary rows: twice as many tiles share out better where there
@@ -66,7 +72,8 @@ struct LogitIn {
   const bf16_t* W;
   const int32_t* idx;      // of the launch's first list position
   const int32_t* token_id;
-  int n, H, V;
+  int n, H, V;             // n: list positions of the launch, or of the part of it that a cut tile covers
+  int pad_end;             // positions from n up to here are the launch's padding (from here on: not this tile's)
 };
 
 // What the epilogue needs to know of a lane's tokens, one per accumulator block column: fetched behind the k loop's last
@@ -221,9 +228,54 @@ __device__ __forceinline__ void logit_narrow(const LogitIn& in, char* smem, Epil
   else logit_stream<192, PERMUTED, ONCE>(in, smem, epi);
 }
 
-// All tiles of a launch.  Those that do not fill a round of the grid are cut into halves or quarters of their tokens if there
+// Tokens of a tile: as many tiles as 256 tokens each take, of equal size, in steps of 32 (from 1569 tokens on that is always 256).
+// A last tile of 256 that is mostly padding costs its whole arithmetic.  Log-probabilities at V = 151936, all tiles of 256 before: 300
+// tokens 272 -> 235 us at H = 2048 and 515 -> 432 at H = 4096, 600 379 -> 362, 1100 606 -> 572, entropy of 300 290 -> 250; 2048
+// tokens and more are as they were.
+__device__ __forceinline__ int balanced_tokens(int n) {
+  const int tiles = (n + kTile16 - 1) / kTile16;
+  return ((n + tiles - 1) / tiles + 31) / 32 * 32;
+}
+
+// All tiles of a launch, of G.  Those that do not fill a round of the grid are cut into halves or quarters of their tokens if there
 // are workgroups for all of them: 594 tiles (the full vocabulary, up to 256 tokens) are two rounds and a half instead of three
 // (197 tokens at H = 4096 372 -> 346 us with the call's other kernels, 400 at H = 2048, 4.6 rounds, 345 -> 328).
+template <typename G, bool PERMUTED, typename Off, typename Epilogue>
+__device__ __forceinline__ void logit_rounds(const LogitIn& in, int n_vtiles, char* smem, Epilogue epi) {
+  constexpr bool kCut = sizeof(Off) == 4;       // (not for vocabularies beyond 8.3 million)
+  constexpr int T = G::kTileB;
+  const TileOrder ord{n_vtiles, (in.n + T - 1) / T, 8};
+  const int me = logical_workgroup(), grid = gridDim.x, rest = ord.total() % grid;
+  const int cuts = !kCut || rest * 2 > grid ? 1 : rest * 4 > grid ? 2 : 4;
+  const int whole = cuts == 1 ? ord.total() : ord.total() - rest;
+  logit_tiles<G, PERMUTED, Off>(
+      in, me, whole,
+      [&](int it, int* v0, int* t0) {
+        int vt, tt;
+        ord.decode(it, &vt, &tt);
+        *v0 = vt * kTile16;
+        *t0 = tt * T;
+      },
+      smem, epi);
+  if constexpr (kCut) {
+    if (cuts == 1 || me >= rest * cuts) return;
+    int vt, tt;
+    ord.decode(whole + me / cuts, &vt, &tt);
+    const int t = tt * T + me % cuts * (T / cuts);
+    if (t >= in.n) return;
+    LogitIn part = in;
+    part.pad_end = t + T / cuts;
+    part.n = min(in.n, part.pad_end);
+    auto place = [&](int, int* v0, int* t0) {
+      *v0 = vt * kTile16;
+      *t0 = t;
+    };
+    lds_barrier();      // the whole tiles' epilogues are done with LDS
+    if (cuts == 2) logit_tiles<GLogit128, PERMUTED, Off>(part, 0, 1, place, smem, epi);
+    else logit_tiles<GLogit64, PERMUTED, Off>(part, 0, 1, place, smem, epi);
+  }
+}
+
 template <bool PERMUTED, typename Off, typename Epilogue>
 __device__ __forceinline__ void logit_launch(const LogitIn& in, int n_vtiles, char* smem, Epilogue epi) {
   constexpr bool kCut = sizeof(Off) == 4;       // (not for vocabularies beyond 8.3 million)
@@ -234,32 +286,15 @@ __device__ __forceinline__ void logit_launch(const LogitIn& in, int n_vtiles, ch
       return;
     }
   }
-  const TileOrder ord{n_vtiles, (in.n + kTile16 - 1) / kTile16, 8};
-  const int me = logical_workgroup(), grid = gridDim.x, rest = ord.total() % grid;
-  const int cuts = !kCut || rest * 2 > grid ? 1 : rest * 4 > grid ? 2 : 4;
-  const int whole = cuts == 1 ? ord.total() : ord.total() - rest;
-  logit_tiles<GLogit, PERMUTED, Off>(
-      in, me, whole,
-      [&](int it, int* v0, int* t0) {
-        int vt, tt;
-        ord.decode(it, &vt, &tt);
-        *v0 = vt * kTile16;
-        *t0 = tt * kTile16;
-      },
-      smem, epi);
   if constexpr (kCut) {
-    if (cuts == 1 || me >= rest * cuts) return;
-    int vt, tt;
-    ord.decode(whole + me / cuts, &vt, &tt);
-    const int t = tt * kTile16 + me % cuts * (kTile16 / cuts);
-    if (t >= in.n) return;
-    auto place = [&](int, int* v0, int* t0) {
-      *v0 = vt * kTile16;
-      *t0 = t;
-    };
-    lds_barrier();      // the whole tiles' epilogues are done with LDS
-    if (cuts == 2) logit_tiles<GLogit128, PERMUTED, Off>(in, 0, 1, place, smem, epi);
-    else logit_tiles<GLogit64, PERMUTED, Off>(in, 0, 1, place, smem, epi);
+    switch (balanced_tokens(in.n)) {
+      case 160: return logit_rounds<GLogit160, PERMUTED, Off>(in, n_vtiles, smem, epi);
+      case 192: return logit_rounds<GLogit192, PERMUTED, Off>(in, n_vtiles, smem, epi);
+      case 224: return logit_rounds<GLogit224, PERMUTED, Off>(in, n_vtiles, smem, epi);
+      default: return logit_rounds<GLogit, PERMUTED, Off>(in, n_vtiles, smem, epi);
+    }
+  } else {
+    logit_rounds<GLogit, PERMUTED, Off>(in, n_vtiles, smem, epi);
   }
 }
 
@@ -376,7 +411,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fwd(
   if (gate && *gate == 0) return;
   const int n = chunk_count(cnt, c0, TC);
   if (n <= 0) return;
-  logit_launch<false, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V}, n_vtiles, smem,
+  logit_launch<false, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V, INT_MAX}, n_vtiles, smem,
                            FwdEpilogue<ENT>{part_m, part_s, part_u, zy, TC});
 }
 
@@ -448,7 +483,7 @@ struct FeEpilogue {
           for (int e = 0; e < 8; ++e) d[e] = (vbase + vf + e < V && live) ? d[e] : 0.f;
         }
         sum += ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]));
-        if (interior || vbase + vf < Vp) store8(row + vf, d);
+        if (interior || (vbase + vf < Vp && tcol < in.pad_end)) store8(row + vf, d);
       }
       sum = across_groups_sum(sum);
       if (co.lane < 16) red_s[co.wm * T + co.b_row(j)] = sum;
@@ -472,7 +507,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_fe(
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int n = chunk_count(cnt, c0, TC);
   if (n <= 0) return;
-  logit_launch<true, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V}, n_vtiles, smem,
+  logit_launch<true, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V, INT_MAX}, n_vtiles, smem,
                           FeEpilogue{c2, E, part_s, zy, Vp, TC});
 }
 
@@ -531,7 +566,7 @@ struct DzEpilogue {
 #pragma unroll
           for (int e = 0; e < 8; ++e) d[e] = (vbase + vf + e < V && live) ? d[e] : 0.f;
         }
-        if (interior || vbase + vf < Vp) store8(row + vf, d);
+        if (interior || (vbase + vf < Vp && tcol < in.pad_end)) store8(row + vf, d);
       }
     }
   }
@@ -547,7 +582,7 @@ __global__ __launch_bounds__(GLogit::kThreads) void k_head_dz(
   if (gate && *gate == 0) return;
   const int n = chunk_count(cnt, c0, TC);
   if (n <= 0) return;
-  logit_launch<true, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V}, n_vtiles, smem, DzEpilogue{lse, coef, dZ, Vp});
+  logit_launch<true, Off>(LogitIn{hidden, W, idx + c0, token_id, n, H, V, INT_MAX}, n_vtiles, smem, DzEpilogue{lse, coef, dZ, Vp});
 }
 
 // ---- partial tiles of a split contraction (split_k.hpp), in the accumulator layout of grid G -----------------------

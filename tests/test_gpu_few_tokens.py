@@ -162,3 +162,29 @@ def test_weights_past_the_caches(gpu_device, n, H, V):
     say(f"[few] weights past the caches n={n} H={H} V={V}")
     lengths = [n - n // 2] + ([n // 2] if n > 1 else [])
     check(*make(gpu_device, lengths, [1.0, -0.5][:len(lengths)], H, V), lengths)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,H,V", [
+    (224, 64, 20000),       # one token tile of 224, 79 vocabulary tiles: halves of 112
+    (225, 64, 1000),        # one of 256
+    (257, 192, 8200),       # two of 160, 66 tiles in all: halves of 80
+    (320, 64, 5000),        # 40 tiles: quarters of 40
+    (321, 128, 3000),       # two of 192
+    (384, 64, 20000),       # 158 tiles: not cut
+    (385, 64, 33000),       # 258 tiles of 224: a whole round and two in quarters of 56
+    (448, 64, 700),
+    (449, 64, 700),         # two of 256
+    (513, 128, 2100),       # three of 192
+    (1120, 64, 1300),       # five of 224, all full
+    (1568, 64, 520),        # the last size that is not in tiles of 256
+    (1569, 64, 520),
+])
+def test_equal_token_tiles(gpu_device, n, H, V):
+    """Also on a workspace full of NaN: rows behind the last tile are read by the contractions over tokens."""
+    say(f"[few] equal token tiles n={n} H={H} V={V}")
+    lengths = [n - n // 2, n // 2]
+    case = make(gpu_device, lengths, [1.0, -0.5], H, V)
+    check(*case, lengths)
+    api.at_grpo_token_entropy(case[0])["workspace"].fill_(255)
+    check(*case, lengths)
