@@ -44,6 +44,8 @@ constexpr int kStepK = 64;                        // k per step
 constexpr int kRingSlots = 5;
 constexpr int kRingSlot = kTile16 * kStepK * 2;   // 32 KiB: one operand panel of one step
 constexpr int kRingBytes = kRingSlots * kRingSlot;
+constexpr int kRingA = 3 * kRingSlot;             // the first three slots are A's, the others B's
+constexpr int kRingFree = 2 * kRingSlot;          // the slot that a tile's first two steps leave to the epilogue in front of it
 
 // How the wavefronts of a workgroup share the TA x TB tile: WA x WB of them, each owning (TA / WA) x (TB / WB).
 //   Grid16<4, 2> / <2, 4>  8 wavefronts, two per SIMD (128 accumulator registers): one covers part of the other's
@@ -63,7 +65,16 @@ struct Grid16 {
   // a fragment read follows every kRdEvery-th MFMA: the last one must be early enough to land before the sub-step ends
   // (4 wavefronts, same box: every 3rd 1494 TFLOP/s at k = 151936 and 1414 with a k-major operand, every 4th 1472 and 1377)
   static constexpr int kRdEvery = (kMm / kRd >= 4) ? kMm / kRd - 1 : kMm / kRd;
+  // When the loads of Gemm16 are issued: a step's B loads behind the first kSpanB MFMAs of its sub-step, the first kFirstA of its A
+  // loads behind the others there, and the rest in the next sub-step.  With two wavefronts per SIMD, B within a quarter, as it has the
+  // least time to land, and A in two halves; with one, evenly.  Us per step at V = 151936 under full load, B over a quarter with half of
+  // A / over a quarter without A / evenly without A: dW of 250000 rows at H = 2048 106.1, 109.2, 109.5 ms, exponentials 110.1, 109.8,
+  // 110.2, dHidden 101.0, 100.1, 99.4; dHidden of 37000 at H = 4096 on three heads 32.9, 33.0, 32.8.  In short bursts, where the clock
+  // is higher, the exponentials of 20000 rows take 8.94, 8.95 and 9.70 ms.
+  static constexpr int kSpanB = WA * WB == 4 ? kMm : kMm / 4;
+  static constexpr int kFirstA = WA * WB == 4 ? 0 : kLoadsA / 2;
   static_assert(kRowsA % 16 == 0 && kRowsB % 16 == 0 && kLoadsA >= 1 && kLoadsB >= 1, "whole blocks, whole loads");
+  static_assert(kLoadsB <= kSpanB && kFirstA <= kMm - kSpanB && kLoadsA - kFirstA <= kMm, "at most one load behind an MFMA");
   static_assert(kRdEvery >= 1 && (kRd - 1) * kRdEvery < kMm, "every fragment is read inside its sub-step");
 };
 
@@ -282,11 +293,10 @@ struct FragReader<NB, true> {
 
 // index of the MFMA after which load k of `cnt` is issued within one sub-step: evenly spread
 __device__ __forceinline__ constexpr int load_after(int k, int cnt, int mm) { return ((2 * k + 1) * mm) / (2 * cnt); }
-
-__device__ __forceinline__ int ring_byte(int first, int i) {
-  int s = first + i;
-  if (s >= kRingSlots) s -= kRingSlots;
-  return s * kRingSlot;
+// the load issued after MFMA n, or -1
+__device__ __forceinline__ constexpr int load_behind(int n, int cnt, int mm) {
+  const int k = (2 * n * cnt + mm - 1) / (2 * mm);
+  return k < cnt && load_after(k, cnt, mm) == n ? k : -1;
 }
 
 // acc += a b, with the accumulator tied to its registers: the builtin leaves the compiler free to give the result other
@@ -313,14 +323,18 @@ __device__ __forceinline__ void mfma_settle(floatx4 (&acc)[G::kIB][G::kJB]) {
     }
 }
 
-// LDS ring: the A and B panels of k-step kt sit in slots (2 kt) % 5 and (2 kt + 1) % 5.  While step kt is consumed, the
-// three other slots receive B of step kt+1 and both panels of step kt+2: up to 96 KiB of loads in flight per compute
-// unit, and every load has at least one and a half steps to land.  Per k-step:
-//   sub-step 0   MFMAs on the first 32 of k; fragments of the second 32; requests A of step kt+2, into the slot that B of
-//                step kt-1 left
+// LDS ring: three slots for the A panels and two for the B panels of consecutive k-steps: A of step kt in slot kt % 3, B in slot
+// 3 + kt % 2.  What step kt leaves free at its barrier is requested again from there on, B of step kt+2 first: it has up to a whole
+// step to land, A of step kt+3 up to two (the A panels are the weights, the B panels what more workgroups share).  With both
+// operands taking turns in the five slots (A of step kt+2 requested in front of that barrier, B behind it) steps of 20000 rows took
+// 27.8 ms at H = 2048 and 54.8 at H = 4096, now 26.1 and 51.8, and log-probabilities of 300 rows 235 -> 228 and 432 -> 411 us, of 8192
+// rows 3670 -> 3560.  Where the launches go on for long, power is the bound and the gain smaller: 250000 rows 329 -> 325 ms,
+// 37000 at H = 4096 on three heads 99.9 -> 98.4.  (Three slots for dW's B, the rows of dZ, instead: dW of 20000 rows 8.6 -> 9.0 ms.)
+// Per k-step:
+//   sub-step 0   MFMAs on the first 32 of k; fragments of the second 32; requests the other A loads of step kt+2
 //   wait until all but those A loads have landed; workgroup barrier (one per k-step)
-//   sub-step 1   MFMAs on the second 32; first fragments of step kt+1; requests B of step kt+2, into the slot that A of
-//                step kt has just left
+//   sub-step 1   MFMAs on the second 32; first fragments of step kt+1; requests B of step kt+2 and the first kFirstA loads of A of
+//                step kt+3, into the slots that step kt has just left
 // A slot is only overwritten after the barrier that follows its last read.
 template <typename G, typename PA, typename PB>
 struct Gemm16 {
@@ -328,11 +342,14 @@ struct Gemm16 {
   PA& pa;
   PB& pb;
   const char* smem;
-  uint32_t lds_a, lds_b;      // where this wavefront's part of a panel lies in a slot
+  uint32_t lds_a, lds_b;      // where this wavefront's part of a panel lies in the first slot of its operand
   FragReader<G::kIB, PA::kKMajor> ra;
   FragReader<G::kJB, PB::kKMajor> rb;
   uint4 fa[2][G::kIB], fb[2][G::kJB];
+  int sa, sb;                 // byte offsets of the slots of the step being consumed
 
+  __device__ __forceinline__ static int behind_a(int s) { return s == 2 * kRingSlot ? 0 : s + kRingSlot; }
+  __device__ __forceinline__ static int behind_b(int s) { return s ^ kRingSlot; }
   __device__ __forceinline__ void mm(int f, int n) {
     const int i = n / G::kJB, j = n % G::kJB;
     mfma_in_place<G>(acc[i][j], __builtin_bit_cast(bf16v8, fa[f][i]), __builtin_bit_cast(bf16v8, fb[f][j]));
@@ -345,12 +362,17 @@ struct Gemm16 {
   }
   __device__ __forceinline__ void ld_a(int slot, int q) { pa.load(q, lds_a + slot + q * 1024); }
   __device__ __forceinline__ void ld_b(int slot, int q) { pb.load(q, lds_b + slot + q * 1024); }
+  __device__ __forceinline__ void aim_reads(int a, int b) {
+    ra.slot(a);
+    rb.slot(kRingA + b);
+  }
 
-  // REQUEST: step kt+2 exists; NEXT: step kt+1 does
-  template <bool REQUEST, bool NEXT>
-  __device__ __forceinline__ void step(int first) {
-    constexpr int kMm = G::kMm, kRd = G::kRd, kEv = G::kRdEvery, kLa = G::kLoadsA, kLb = G::kLoadsB;
-    const int la = ring_byte(first, 4), lb = ring_byte(first, 0);
+  // REQUEST: step kt+2 exists; MORE: step kt+3 does; NEXT: step kt+1 does
+  template <bool REQUEST, bool MORE, bool NEXT>
+  __device__ __forceinline__ void step() {
+    constexpr int kMm = G::kMm, kRd = G::kRd, kEv = G::kRdEvery, kSpan = G::kSpanB;
+    constexpr int kFirst = G::kFirstA, kSecond = G::kLoadsA - G::kFirstA, kRest = kMm > kSpan ? kMm - kSpan : 1;
+    const int na = behind_a(sa), nb = behind_b(sb), nna = behind_a(na);
 #pragma unroll
     for (int n = 0; n < kMm; ++n) {
       mm(0, n);
@@ -359,27 +381,20 @@ struct Gemm16 {
         rd(1, 1, n / kEv);
         ATG_PIN16();
       }
-      if (REQUEST) {
-#pragma unroll
-        for (int k = 0; k < kLa; ++k)
-          if (load_after(k, kLa, kMm) == n) {
-            ld_a(la, k);
-            ATG_PIN16();
-          }
+      if (REQUEST && load_behind(n, kSecond, kMm) >= 0) {
+        ld_a(nna, kFirst + load_behind(n, kSecond, kMm));
+        ATG_PIN16();
       }
     }
     if (REQUEST) {
       pa.advance();
-      wait_loads_but<kLa>();
+      wait_loads_but<G::kLoadsA>();
     } else {
       wait_loads_but<0>();
     }
     __builtin_amdgcn_s_barrier();
     ATG_PIN16();
-    if (NEXT) {
-      ra.slot(ring_byte(first, 2));
-      rb.slot(ring_byte(first, 3));
-    }
+    if (NEXT) aim_reads(na, nb);
 #pragma unroll
     for (int n = 0; n < kMm; ++n) {
       mm(1, n);
@@ -388,32 +403,34 @@ struct Gemm16 {
         rd(0, 0, n / kEv);
         ATG_PIN16();
       }
-      if (REQUEST) {
-#pragma unroll
-        for (int k = 0; k < kLb; ++k)
-          if (load_after(k, kLb, kMm) == n) {
-            ld_b(lb, k);
-            ATG_PIN16();
-          }
+      if (REQUEST && n < kSpan && load_behind(n, G::kLoadsB, kSpan) >= 0) {
+        ld_b(sb, load_behind(n, G::kLoadsB, kSpan));
+        ATG_PIN16();
+      }
+      if (MORE && kFirst > 0 && n >= kSpan && load_behind(n - kSpan, kFirst, kRest) >= 0) {
+        ld_a(sa, load_behind(n - kSpan, kFirst, kRest));
+        ATG_PIN16();
       }
     }
     if (REQUEST) pb.advance();
+    sa = na;
+    sb = nb;
   }
 
-  __device__ __forceinline__ void request_step(int slot) {
+  __device__ __forceinline__ void request_step(int a, int b) {
 #pragma unroll
-    for (int q = 0; q < G::kLoadsA; ++q) ld_a(slot, q);
+    for (int q = 0; q < G::kLoadsA; ++q) ld_a(a, q);
     pa.advance();
 #pragma unroll
-    for (int q = 0; q < G::kLoadsB; ++q) ld_b(slot + kRingSlot, q);
+    for (int q = 0; q < G::kLoadsB; ++q) ld_b(b, q);
     pb.advance();
   }
 
-  // Requests the first two of nk steps, into slots 0 to 3.  The last reads of a tile's panels lie in front of its final step's
-  // barrier, so the next tile's may be requested as soon as run() is through: they travel while the results leave.
+  // Requests the first two of nk steps, into all slots but kRingFree.  The last reads of a tile's panels lie in front of its final
+  // step's barrier, so the next tile's may be requested as soon as run() is through: they travel while the results leave.
   __device__ __forceinline__ void begin(int nk) {
-    if (nk > 0) request_step(0);
-    if (nk > 1) request_step(2 * kRingSlot);
+    if (nk > 0) request_step(0, 0);
+    if (nk > 1) request_step(kRingSlot, kRingSlot);
   }
 
   // acc = A B^T over nk >= 0 steps, of which begin() has requested the first two.  Every thread of the workgroup calls it.
@@ -430,24 +447,24 @@ struct Gemm16 {
     if (nk > 1) wait_loads_but<G::kLoadsA + G::kLoadsB>();
     else wait_loads_but<0>();
     __builtin_amdgcn_s_barrier();
-    ra.slot(0);
-    rb.slot(kRingSlot);
+    sa = sb = 0;
+    aim_reads(0, 0);
 #pragma unroll
     for (int n = 0; n < G::kRd; ++n) rd(0, 0, n);
-    int kt = 0, first = 0;
-    for (; kt + 2 < nk; ++kt) {
-      step<true, true>(first);
-      first += 2;
-      if (first >= kRingSlots) first -= kRingSlots;
+    if (nk > 2) {
+#pragma unroll
+      for (int q = 0; q < G::kFirstA; ++q) ld_a(kRingFree, q);
+    }
+    int kt = 0;
+    for (; kt + 3 < nk; ++kt) step<true, true, true>();
+    if (kt + 2 < nk) {
+      step<true, false, true>();
+      ++kt;
     }
     fetch(0);
-    if (kt + 1 < nk) {
-      step<false, true>(first);
-      first += 2;
-      if (first >= kRingSlots) first -= kRingSlots;
-    }
+    if (kt + 1 < nk) step<false, false, true>();
     fetch(1);
-    if (nk > 0) step<false, false>(first);
+    if (nk > 0) step<false, false, false>();
     mfma_settle<G>(acc);
   }
 };
@@ -474,7 +491,7 @@ __device__ __forceinline__ Gemm16<G, PA, PB> make_gemm16(floatx4 (&acc)[G::kIB][
                                                          const Coord16<G>& co) {
   const uint32_t lds = lds_addr32(smem);
   Gemm16<G, PA, PB> g{acc, pa, pb, smem, static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds + co.wave * G::kLoadsA * 1024)),
-                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds + co.wave * G::kLoadsB * 1024)), {}, {}, {}, {}};
+                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds + kRingA + co.wave * G::kLoadsB * 1024)), {}, {}, {}, {}, 0, 0};
   g.ra.init(co.wm * G::kRowsA, co.lane);
   g.rb.init(co.wn * G::kRowsB, co.lane);
   return g;

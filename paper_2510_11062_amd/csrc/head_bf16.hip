@@ -97,7 +97,7 @@ struct TokenCols {
 };
 
 // The tiles it = first, first + gridDim.x, ... < end of one shape; place(it, &v0, &t0) says where a tile lies.  The next
-// tile's first two steps are requested in front of a tile's epilogue, whose LDS is the ring's last slot, and what the epilogue
+// tile's first two steps are requested in front of a tile's epilogue, whose LDS is the slot that they leave free, and what the epilogue
 // has to look up is fetched beside the last two steps.  That takes 2 us of waiting from a tile, of 14 to 100 us, and gives less,
 // since the clock falls as the matrix cores are busier: log-probabilities of 3000 rows at H = 1024, V = 32000 184 -> 178 us, a step
 // of 8000 rows at H = 1024, V = 50000 2170 -> 2140, entropy of 4700 rows at H = 2048 4343 -> 4317; C2's step by less than its
@@ -154,7 +154,7 @@ __device__ __forceinline__ void logit_tiles(const LogitIn& in, int first, int en
       aim(vn);
       g.begin(nk);
     }
-    epi.template finish<G>(acc, cols, more, v0, t0, in, smem + (kRingSlots - 1) * kRingSlot);
+    epi.template finish<G>(acc, cols, more, v0, t0, in, smem + kRingFree);
     if (next >= end) break;
     it = next;
     v0 = vn;
