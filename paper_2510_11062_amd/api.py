@@ -1,4 +1,4 @@
-"""Thin Python binding of libat_grpo.so: argument marshalling only.
+"""Thin Python binding of libat_grpo.so: argument marshalling only (for the grouping calls, whose kernels are short, in csrc/binding.cpp).
 
 Every function has the name of the C entry point it calls (see include/at_grpo.h) and takes
 torch tensors that already live on the GPU; outputs and the workspace are allocated here with
@@ -20,6 +20,8 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libat_grpo.so")
 _lib = None
+_binding = None             # csrc/binding.cpp, loaded with the library
+_group_fn = _mixed_fn = 0   # addresses of the library's grouping calls
 
 AGG = {"token_mean": 0, "seq_mean_token_mean": 1}
 NORM = {"std": 0, "none": 1}
@@ -66,7 +68,7 @@ def library_path() -> str:
 
 def load_library():
     """Loads libat_grpo.so (built in-tree by paper_2510_11062_amd.build); raises if it is missing."""
-    global _lib
+    global _lib, _binding, _group_fn, _mixed_fn
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -121,6 +123,13 @@ def load_library():
     lib.at_grpo_profile_classes.restype = i32
     lib.at_grpo_profile_read.argtypes = [i32, C.POINTER(C.c_char_p), C.POINTER(C.c_int64),
                                          C.POINTER(C.c_double)]
+    try:
+        from . import _binding as binding
+    except ImportError as e:
+        raise AtGrpoError(f"_binding.so is missing or does not load ({e}): run `python -m paper_2510_11062_amd.build`") from e
+    _group_fn = C.cast(lib.at_grpo_group_advantage, vp).value
+    _mixed_fn = C.cast(lib.at_grpo_group_advantage_mixed, vp).value
+    _binding = binding
     _lib = lib
     return lib
 
@@ -247,22 +256,28 @@ def at_grpo_workspace_bytes(call: int, batch: Optional[Batch] = None, n_resp=0, 
 def at_grpo_group_advantage(env_id, agent_id, turn_id, reward, n_env: int, n_agent: int, n_turn: int,
                             eps_std: float = 1e-6, ddof: int = 0, norm: str = "std", want_stats: bool = True):
     """Returns dict(group_id, n_groups, seg_offsets, perm, adv, group_mean, group_std, workspace)."""
-    lib = load_library()
-    _dev_check(env_id, agent_id, turn_id, reward)
-    _f32_check(reward=reward)
-    _i32_check(env_id=env_id, agent_id=agent_id, turn_id=turn_id)
-    dev = reward.device
-    R = reward.numel()
-    out = _group_buffers(R, min(R, n_env * n_agent * n_turn), dev, want_stats)
-    ws = _workspace(_group_workspace_bytes(0, R, n_env, n_agent, n_turn, 1), dev)
-    st = lib.at_grpo_group_advantage(R, n_env, n_agent, n_turn, env_id.data_ptr(), agent_id.data_ptr(), turn_id.data_ptr(),
-                                     reward.data_ptr(), eps_std, ddof, NORM[norm] | NORM_FILL, out["group_id"].data_ptr(),
-                                     out["n_groups"].data_ptr(), out["seg_offsets"].data_ptr(), out["perm"].data_ptr(),
-                                     out["adv"].data_ptr(), _ptr(out["group_mean"]), _ptr(out["group_std"]),
-                                     ws.data_ptr(), ws.numel(), _stream())
-    _check(st, "at_grpo_group_advantage")
-    out["workspace"] = ws
-    return out
+    if _lib is None:
+        load_library()
+    return _group_call("at_grpo_group_advantage", _group_fn, env_id, agent_id, turn_id, reward, None, 0.0, n_env, n_agent, n_turn,
+                       eps_std, ddof, norm, want_stats, False)
+
+
+def _group_call(what, fn, env_id, agent_id, turn_id, reward, r_loc, alpha, n_env, n_agent, n_turn, eps_std, ddof, norm, want_stats,
+                want_best):
+    out = None
+    if reward.is_cuda:
+        ws = _workspace(_group_workspace_bytes(0, reward.numel(), n_env, n_agent, n_turn, 1), reward.device)
+        out = _binding.group_advantage(fn, env_id, agent_id, turn_id, reward, r_loc, alpha, n_env, n_agent, n_turn, eps_std, ddof,
+                                       NORM[norm] | NORM_FILL, want_stats, want_best, ws.data_ptr(), ws.numel(), _stream())
+    if type(out) is dict:
+        out["workspace"] = ws
+        return out
+    if out is None:     # says which argument it was
+        _dev_check(env_id, agent_id, turn_id, reward, r_loc)
+        _f32_check(**(dict(reward=reward) if r_loc is None else dict(r_team=reward, r_loc=r_loc)))
+        _i32_check(env_id=env_id, agent_id=agent_id, turn_id=turn_id)
+        raise AtGrpoError(f"{what}: every argument must be a tensor")
+    _check(out, what)
 
 
 @functools.lru_cache(maxsize=256)
@@ -354,26 +369,12 @@ def at_grpo_group_advantage_mixed(env_id, agent_id, turn_id, r_team, r_loc, alph
     """Eq. (3) mixing in front of at_grpo_group_advantage, plus the per-group arg max.
 
     Returns the dict of at_grpo_group_advantage extended by reward[R] and best[min(R, keys)]."""
-    lib = load_library()
-    _dev_check(env_id, agent_id, turn_id, r_team, r_loc)
-    _f32_check(r_team=r_team, r_loc=r_loc)
-    _i32_check(env_id=env_id, agent_id=agent_id, turn_id=turn_id)
-    dev = r_team.device
-    R = r_team.numel()
-    gmax = min(R, n_env * n_agent * n_turn)
-    out = dict(reward=torch.empty(R, dtype=torch.float32, device=dev))
-    out.update(_group_buffers(R, gmax, dev, want_stats))
-    out["best"] = torch.empty(gmax, dtype=torch.int32, device=dev) if want_best else None
-    ws = _workspace(_group_workspace_bytes(0, R, n_env, n_agent, n_turn, 1), dev)
-    st = lib.at_grpo_group_advantage_mixed(R, n_env, n_agent, n_turn, _ptr(env_id), _ptr(agent_id),
-                                           _ptr(turn_id), _ptr(r_team), _ptr(r_loc), alpha, eps_std, ddof,
-                                           NORM[norm] | NORM_FILL, _ptr(out["reward"]), _ptr(out["group_id"]),
-                                           _ptr(out["n_groups"]), _ptr(out["seg_offsets"]), _ptr(out["perm"]),
-                                           _ptr(out["adv"]), _ptr(out["group_mean"]), _ptr(out["group_std"]),
-                                           _ptr(out["best"]), _ptr(ws), ws.numel(), _stream())
-    _check(st, "at_grpo_group_advantage_mixed")
-    out["workspace"] = ws
-    return out
+    if _lib is None:
+        load_library()
+    if r_loc is None:
+        raise AtGrpoError("at_grpo_group_advantage_mixed needs r_loc")
+    return _group_call("at_grpo_group_advantage_mixed", _mixed_fn, env_id, agent_id, turn_id, r_team, r_loc, alpha, n_env, n_agent,
+                       n_turn, eps_std, ddof, norm, want_stats, want_best)
 
 
 def at_grpo_head_update(W, dW, m, v, step: int, W_master=None, lr: float = 1e-6, beta1: float = 0.9,

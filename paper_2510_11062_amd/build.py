@@ -12,8 +12,9 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libat_grpo.so")
 CLIENT = os.path.join(PKG, "abi_client")
 PROBE = os.path.join(PKG, "gemm_probe")
-SOURCES = ["api.hip", "group_advantage.hip", "token_kernels.hip", "head_kernels.hip", "head_bf16.hip",
-           "head_f32.hip", "optimizer.hip"]
+BINDING = os.path.join(PKG, "_binding.so")
+SOURCES = ["head_bf16.hip", "head_f32.hip", "group_advantage.hip", "api.hip", "token_kernels.hip", "head_kernels.hip",
+           "optimizer.hip"]      # the longest first
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -45,6 +46,20 @@ def build_client(verbose: bool = True) -> str:
     return CLIENT
 
 
+def build_binding() -> str:
+    """The grouping call's host side as a CPython extension on torch's headers (csrc/binding.cpp).  It is handed the
+    library's functions, so it is not linked with it."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wno-attributes",
+           *[a for d in cpp_extension.include_paths() for a in ("-isystem", d)],
+           "-isystem", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
+           *["-L" + d for d in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    subprocess.run(cmd, check=True)
+    return BINDING
+
+
 def build_probe(verbose: bool = True) -> str:
     """The tile loops as plain GEMMs (measurement aid, see csrc/gemm_probe.hip and bench_gemm.py)."""
     cmd = [HIPCC, *[f for f in FLAGS if f != "-fPIC"], os.path.join(CSRC, "gemm_probe.hip"), "-o", PROBE]
@@ -55,12 +70,15 @@ def build_probe(verbose: bool = True) -> str:
 
 
 def build(verbose: bool = True) -> str:
-    with ThreadPoolExecutor(max_workers=4) as pool:
+    with ThreadPoolExecutor(max_workers=6) as pool:
+        binding = pool.submit(build_binding)
         objs = list(pool.map(_compile, SOURCES))
+        binding.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     subprocess.run(cmd, check=True)
     if verbose:
         print("built", LIB)
+        print("built", BINDING)
     build_client(verbose)
     build_probe(verbose)
     return LIB

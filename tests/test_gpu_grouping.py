@@ -396,3 +396,39 @@ def test_pools_of_two_host_threads(gpu_device):
     for t in threads:
         t.join()
     assert not failed
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["cpu ids", "cpu reward", "long ids", "double reward", "strided", "no local reward", "extents", "no ids"])
+def test_refused_arguments(gpu_device, what):
+    """Arguments that a grouping call refuses, plain and mixed, and a call behind the refusal."""
+    ids = lambda: [torch.tensor([0, 0, 1, 1], dtype=torch.int32, device=gpu_device) for _ in range(3)]
+    a, r, extents = ids(), torch.tensor([1.0, 0.0, 1.0, 1.0], device=gpu_device), (2, 2, 2)
+    loc = torch.zeros_like(r)
+    good = [t.clone() for t in a]
+    if what == "cpu ids":
+        a[1] = a[1].cpu()
+    elif what == "cpu reward":
+        r = r.cpu()
+    elif what == "long ids":
+        a[2] = a[2].long()
+    elif what == "double reward":
+        r = r.double()
+    elif what == "strided":
+        a[0] = a[0].repeat_interleave(2)[::2]
+    elif what == "no local reward":
+        loc = None
+    elif what == "extents":
+        extents = (0, 2, 2)
+    else:
+        a[0] = None
+    with pytest.raises(api.AtGrpoError):
+        api.at_grpo_group_advantage_mixed(*a, r, loc, 1.0, *extents)
+    if what != "no local reward":
+        with pytest.raises(api.AtGrpoError):
+            api.at_grpo_group_advantage(*a, r, *extents)
+    out = api.at_grpo_group_advantage(*good, torch.tensor([1.0, 0.0, 1.0, 1.0], device=gpu_device), 2, 2, 2, want_stats=False)
+    assert list(out) == ["group_id", "n_groups", "seg_offsets", "perm", "adv", "group_mean", "group_std", "workspace"]
+    assert out["group_mean"] is None and out["group_std"] is None
+    assert out["group_id"].tolist() == [0, 0, 1, 1] and out["perm"].tolist() == [0, 1, 2, 3] and int(out["n_groups"]) == 2
+    assert out["adv"].dtype == torch.float32 and out["adv"].device == gpu_device
