@@ -459,7 +459,8 @@ __device__ __forceinline__ float reward_of(const GaArgs& a, const GaMix& mix, in
 // smaller and marks which smaller ones occur (one bit each): that is all it needs to know of the others to place its own
 // groups.  Its own members go through an LDS list.  Bound by latency: launches, the scan (from L2), a dozen workgroup
 // barriers.  Whole calls: 128 responses 43 -> 16 us (the outputs were cleared by fills of their own), 20480 mixed rewards
-// 71 -> 23 us (seven launches and the fills before).
+// 71 -> 23 us (seven launches and the fills before).  The kernel itself with the keys held from one pass to the next and one scan
+// for all four sums: 64 responses 7.4 -> 6.6 us, 20480 14.6 -> 13.0, 8100 groups of one 11.8 -> 10.2, 32000 shuffled 25.3 -> 24.7.
 // ------------------------------------------------------------------------------------------------
 constexpr int kRangeMaxResp = 65536, kRangeMaxKeys = 65528;
 constexpr int kRangeList = 4096;         // members listed in LDS; more go to global scratch
@@ -467,6 +468,7 @@ constexpr int kRangeDirect = 4096;       // responses up to which every workgrou
 constexpr int kRangeFew = 1024;          // responses up to which 256 threads do
 constexpr int kRangeRounds = 4;          // responses per thread whose ids are in flight together
 static_assert(kRangeFew <= kRangeRounds * 256 && kRangeDirect <= kRangeRounds * 1024, "the keys of all responses stay in registers");
+constexpr int kRangeKept = kRangeMaxResp / 8 / 1024;      // pieces of eight keys that a thread of 1024 holds from one pass to the next
 constexpr int kRangeOwn = 128;           // keys of a workgroup beyond which its list may be left to the whole grid
 constexpr int kRangeBlocks = 512;        // workgroups of such calls: 256 responses or 1024 keys each (more than kRangeOwn)
 static_assert(kRangeMaxKeys / kRangeOwn <= kRangeBlocks, "one word pair each");
@@ -500,6 +502,49 @@ __device__ __forceinline__ bool all_equal(const uint4& v) {
   return v.x == v.y && v.x == v.z && v.x == v.w && (v.x >> 16) == (v.x & 0xffff);
 }
 
+struct RangeSums {
+  int below, g_below, own_groups, own_members, g_own, f_own;
+};
+
+// Sums of `below` and `bits` over the workgroup, exclusive prefixes and sums of (c > 0) and c: one barrier, where four scans took eight.
+template <int NT>
+__device__ __forceinline__ RangeSums range_sums(int below, int bits, int c, int (&lds)[3][NT / 64]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int kShift = 17;                        // c adds up to kRangeMaxResp at most
+  static_assert(kRangeMaxResp < (1 << kShift) && NT <= (1 << (31 - kShift - 1)), "both prefixes fit a word");
+  const int v = (c > 0 ? 1 << kShift : 0) + c;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+    below += __shfl_xor(below, o, 64);
+    bits += __shfl_xor(bits, o, 64);
+  }
+  if (lane == 63) {
+    lds[0][wave] = incl;
+    lds[1][wave] = below;
+    lds[2][wave] = bits;
+  }
+  __syncthreads();
+  RangeSums s{0, 0, 0, 0, 0, 0};
+  int before = incl - v, total = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    const int t = lds[0][w];
+    before += w < wave ? t : 0;
+    total += t;
+    s.below += lds[1][w];
+    s.g_below += lds[2][w];
+  }
+  constexpr int kMask = (1 << kShift) - 1;
+  s.own_groups = total >> kShift;
+  s.own_members = total & kMask;
+  s.g_own = before >> kShift;
+  s.f_own = before & kMask;
+  return s;
+}
+
 // NT threads, each with at most one own key.  keys16: the keys (then a.reward holds the rewards), or null.
 // Where the responses lie in the key range is only seen here: a workgroup whose members do not fit its list finishes them out of
 // global scratch, or, with `left`, leaves them to k_ga_left and says which groups those are: left[2 b] groups from left[2 b + 1].
@@ -511,7 +556,7 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   __shared__ int count[NT], cursor[NT], first[NT], gid[NT];
   __shared__ int list_id[kRangeList];
   __shared__ float list_x[kRangeList];
-  __shared__ int lds16[16];
+  __shared__ int lds_sums[3][NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.x, lo = b * n_own, own = min(n_own, n_keys - lo);
   for (int k = tid; k < (lo + 31) / 32; k += NT) present[k] = 0;
@@ -531,9 +576,16 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
       atomicOr(&present[key >> 5], 1 << (key & 31));   // once per run of equal keys
     }
   };
+  uint4 kept[kRangeKept];          // with keys16: eight keys each
   if (keys16) {
-    for (int c = tid; c * 8 < a.n_resp; c += NT) {
-      const uint4 v = reinterpret_cast<const uint4*>(keys16)[c];
+    const int pieces = (a.n_resp + 7) / 8;
+#pragma unroll
+    for (int u = 0; u < kRangeKept; ++u)
+      if (u * NT < pieces) kept[u] = reinterpret_cast<const uint4*>(keys16)[min(u * NT + tid, pieces - 1)];
+#pragma unroll
+    for (int u = 0; u < kRangeKept; ++u) {
+      if (u * NT + tid >= pieces) break;
+      const uint4 v = kept[u];
       if (all_equal(v)) {
         look(v.x & 0xffff, true, 8);
         continue;
@@ -566,15 +618,12 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   __syncthreads();                 // every bit is set
   int bits = 0;
   for (int k = tid; k < (lo + 31) / 32; k += NT) bits += __popc(present[k]);
-  int all_below, g_below, own_groups, own_members;
-  block_exclusive_scan<NT>(below, lds16, &all_below);
-  block_exclusive_scan<NT>(bits, lds16, &g_below);
-  below = all_below;
-
-  // own keys: dense ids and offsets
+  // smaller keys: members and groups; own keys: dense ids and offsets.  One scan for the four: sums of at most 65536 and 65528 in one
+  // word pair, groups of at most 1024 over members of at most 65536 in the other
   const int c = tid < own ? count[tid] : 0;
-  const int g_own = block_exclusive_scan<NT>(c > 0 ? 1 : 0, lds16, &own_groups);
-  const int f_own = block_exclusive_scan<NT>(c, lds16, &own_members);
+  const RangeSums sums = range_sums<NT>(below, bits, c, lds_sums);
+  below = sums.below;
+  const int g_below = sums.g_below, own_groups = sums.own_groups, own_members = sums.own_members, g_own = sums.g_own, f_own = sums.f_own;
   first[tid] = f_own;
   cursor[tid] = f_own;
   gid[tid] = g_below + g_own;
@@ -601,8 +650,11 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
     }
   };
   if (keys16) {
-    for (int cc = tid; cc * 8 < a.n_resp; cc += NT) {
-      const uint4 v = reinterpret_cast<const uint4*>(keys16)[cc];
+#pragma unroll
+    for (int u = 0; u < kRangeKept; ++u) {
+      const int cc = u * NT + tid;
+      if (cc * 8 >= a.n_resp) break;
+      const uint4 v = kept[u];
       if (all_equal(v)) {
         enlist(cc * 8, v.x & 0xffff, 8);
         continue;
