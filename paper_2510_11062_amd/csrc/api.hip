@@ -251,6 +251,39 @@ int enqueue_logprob(const at_grpo_batch* b, const Plan& p, float* logp, float* l
   return enqueue_logprob_lists(b, p, p.g, p.S, logp, lse, entropy, s);
 }
 
+// the gradients, once the coefficients and the lists of rows that have one are there
+int enqueue_gradients(const at_grpo_batch* batch, const Plan& p, const float* lse, void* d_hidden, float* const* dW,
+                      int32_t accumulate_dW, hipStream_t s) {
+  const int64_t hidden_bytes = p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize;
+  const bool f32 = batch->dtype == AT_GRPO_F32;      // its first dZ launch clears d_hidden
+  if (!f32) ATG_TRY(launch_fill_bytes16(d_hidden, hidden_bytes, s));
+
+  for (int m = 0; m < batch->n_heads; ++m) {
+    ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, p.S.cnt + m, s));
+    for (int c = 0; c < p.n_chunks; ++c) {
+      const HeadChunk ch{p.S.idx + static_cast<size_t>(m) * p.L.n_tok, p.S.cnt + m, c * p.g.TC};
+      const int add = (accumulate_dW != 0 || c > 0) ? 1 : 0;
+      if (f32) {
+        ATG_TRY(launch_head_dz(p.g, ch, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, p.dZ, s, nullptr,
+                               m == 0 && c == 0 ? d_hidden : nullptr, hidden_bytes));
+        ATG_TRY(launch_head_grads(p.g, ch, p.dZ, batch->W[m], batch->hidden, d_hidden, dW[m], p.part, add, c == 0 ? 1 : 0, s));
+        continue;
+      }
+      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, nullptr, nullptr, nullptr, p.dZ));
+      HeadGeom gs = p.g;
+      gs.TC = p.sub;
+      for (int c1 = 0; c1 < p.g.TC; c1 += p.sub) {
+        const HeadChunk sub{ch.idx, ch.cnt, ch.c0 + c1};
+        char* dZ_sub = static_cast<char*>(p.dZ) + static_cast<size_t>(c1) * p.g.Vp * p.g.esize;
+        ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub, s));
+        ATG_TRY(launch_head_dh(gs, sub, dZ_sub, batch->W[m], p.Wt, d_hidden, p.part, s));
+      }
+      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.hG, dW[m], p.part, add, c == 0 ? 1 : 0, s));
+    }
+  }
+  return AT_GRPO_OK;
+}
+
 bool agg_ok(int agg) { return agg == AT_GRPO_AGG_TOKEN_MEAN || agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN; }
 bool eps_ok(float lo, float hi) { return lo >= 0.f && lo < 1.f && hi >= 0.f; }
 
@@ -388,34 +421,7 @@ extern "C" int at_grpo_policy_loss_bwd(const at_grpo_batch* batch, const float* 
     ATG_TRY(launch_coef(p.L, p.S, logp, old_logp, adv, eps_low, eps_high, agg, grad_loss, p.coef, s));
     ATG_TRY(launch_compact(p.L, p.S, true, s));
   }
-  const int64_t hidden_bytes = p.L.n_tok * static_cast<int64_t>(p.g.H) * p.g.esize;
-  const bool f32 = batch->dtype == AT_GRPO_F32;      // its first dZ launch clears d_hidden
-  if (!f32) ATG_TRY(launch_fill_bytes16(d_hidden, hidden_bytes, s));
-
-  for (int m = 0; m < batch->n_heads; ++m) {
-    ATG_TRY(launch_transpose_w(p.g, batch->W[m], p.Wt, p.S.cnt + m, s));
-    for (int c = 0; c < p.n_chunks; ++c) {
-      const HeadChunk ch{p.S.idx + static_cast<size_t>(m) * p.L.n_tok, p.S.cnt + m, c * p.g.TC};
-      const int add = (accumulate_dW != 0 || c > 0) ? 1 : 0;
-      if (f32) {
-        ATG_TRY(launch_head_dz(p.g, ch, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, p.dZ, s, nullptr,
-                               m == 0 && c == 0 ? d_hidden : nullptr, hidden_bytes));
-        ATG_TRY(launch_head_grads(p.g, ch, p.dZ, batch->W[m], batch->hidden, d_hidden, dW[m], p.part, add, c == 0 ? 1 : 0, s));
-        continue;
-      }
-      ATG_TRY(launch_gather_hidden(p.g, ch, batch->hidden, p.hG, s, nullptr, nullptr, nullptr, p.dZ));
-      HeadGeom gs = p.g;
-      gs.TC = p.sub;
-      for (int c1 = 0; c1 < p.g.TC; c1 += p.sub) {
-        const HeadChunk sub{ch.idx, ch.cnt, ch.c0 + c1};
-        char* dZ_sub = static_cast<char*>(p.dZ) + static_cast<size_t>(c1) * p.g.Vp * p.g.esize;
-        ATG_TRY(launch_head_dz(gs, sub, batch->hidden, batch->W[m], batch->token_id, lse, p.coef, dZ_sub, s));
-        ATG_TRY(launch_head_dh(gs, sub, dZ_sub, batch->W[m], p.Wt, d_hidden, p.part, s));
-      }
-      ATG_TRY(launch_head_dw(p.g, ch, p.dZ, p.hG, dW[m], p.part, add, c == 0 ? 1 : 0, s));
-    }
-  }
-  return AT_GRPO_OK;
+  return enqueue_gradients(batch, p, lse, d_hidden, dW, accumulate_dW, s);
 }
 
 extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const float* old_logp, const float* adv,
@@ -432,6 +438,18 @@ extern "C" int at_grpo_policy_loss_fwd_bwd(const at_grpo_batch* batch, const flo
     if (!dW[m]) return AT_GRPO_EINVAL;
   if (!agg_ok(agg) || !eps_ok(eps_low, eps_high)) return AT_GRPO_EINVAL;
   if (batch->dtype == AT_GRPO_F32) {
+    WsAlloc wf(workspace), wb(workspace);
+    Plan pf{}, pb{};
+    make_plan(batch, AT_GRPO_CALL_POLICY_LOSS_FWD, wf, &pf);
+    if (prep_takes_loss(pf.L)) {      // the loss comes beside the backward's preparation instead of in two launches in front of it
+      make_plan(batch, AT_GRPO_CALL_POLICY_LOSS_BWD, wb, &pb);
+      ATG_TRY(check_workspace(workspace, workspace_bytes, wf.bytes() > wb.bytes() ? wf.bytes() : wb.bytes()));
+      hipStream_t s = static_cast<hipStream_t>(hip_stream);
+      ATG_TRY(enqueue_logprob(batch, pf, logp, lse, nullptr, s));
+      ATG_TRY(launch_prep_backward_loss(pb.L, pb.S, logp, make_coef_args(pb.S, old_logp, adv, eps_low, eps_high, agg, grad_loss),
+                                        pb.coef, loss, clip_mask, n_valid, s));
+      return enqueue_gradients(batch, pb, lse, d_hidden, dW, accumulate_dW, s);
+    }
     ATG_TRY(at_grpo_policy_loss_fwd(batch, old_logp, adv, eps_low, eps_high, agg, loss, logp, lse, clip_mask,
                                     n_valid, workspace, workspace_bytes, hip_stream));
     return at_grpo_policy_loss_bwd(batch, old_logp, adv, logp, lse, eps_low, eps_high, agg, grad_loss, d_hidden,

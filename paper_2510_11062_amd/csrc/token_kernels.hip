@@ -195,14 +195,15 @@ struct Or {
 // also collects the errors, so no word has to be cleared beforehand (two launches of 1.4 us fewer for surrogate and monitors).
 constexpr int kNoHead = 0xff, kErrShift = 8;
 
-// head of a response, or -1 and an error bit
+// head of a response, or -1 and an error bit; its loads wait for nothing but each other
 __device__ __forceinline__ int head_or_error(const TokenLayout& L, int r, int* bad) {
   if (L.n_heads == 1 || L.resp_agent == nullptr || L.head_of_agent == nullptr) return 0;
   const int a = L.resp_agent[r];
-  const int h = (a < 0 || a >= L.n_agent) ? -1 : L.head_of_agent[a];
-  if (h >= 0 && h < L.n_heads) return h;
-  *bad |= AT_GRPO_DATA_AGENT_RANGE;
-  return -1;
+  const bool known = a >= 0 && a < L.n_agent;
+  const int h = L.head_of_agent[known ? a : 0];
+  const bool ok = known && h >= 0 && h < L.n_heads;
+  *bad |= ok ? 0 : AT_GRPO_DATA_AGENT_RANGE;
+  return ok ? h : -1;
 }
 
 template <int LPR, typename F>
@@ -260,59 +261,132 @@ __device__ __forceinline__ void each_row(const TokenLayout& L, const float* __re
   }
 }
 
-// Every row of the response is read once (logp, old_logp, mask, and token_id when given), its clip flags are written, and
+struct SurrogateArgs {
+  TokenLayout L;
+  const float *logp, *old_logp, *adv;
+  ClipConst cc;
+  int agg;
+  uint8_t* clip_mask;
+};
+
+// Every row of response r is read once (logp, old_logp, mask, and token_id when given), its clip flags are written, and
 // the response's sum of surrogate terms and its count of participating rows are reduced in a fixed order.  Needs no per-row
-// routing arrays: the advantage and the head are per-response scalars.
+// routing arrays: the advantage and the head are per-response scalars, requested together with its bounds (6228 responses 12.9 ->
+// 12.4 us, 768 8.4 -> 7.0, 24576 short ones 10.2 -> 8.5, the monitors as much).  `word`: head and errors.
 template <int LPR>
-__global__ __launch_bounds__(256) void k_surrogate_resp(TokenLayout L, const float* __restrict__ logp,
-                                                        const float* __restrict__ old_logp,
-                                                        const float* __restrict__ adv, ClipConst cc, int agg,
-                                                        uint8_t* __restrict__ clip_mask,
-                                                        float* __restrict__ resp_sum,
-                                                        int32_t* __restrict__ resp_cnt,
+__device__ __forceinline__ void surrogate_response(const SurrogateArgs& a, int r, int lane, float* lds_f, int* lds_i, float* total,
+                                                   int* rows, int* word) {
+  const TokenLayout& L = a.L;
+  const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
+  const float A = a.adv[r];
+  int bad = 0;
+  const int head = head_or_error(L, r, &bad);
+  *total = 0.f;
+  *rows = 0;
+  *word = kNoHead | AT_GRPO_DATA_SEQLENS << kErrShift;
+  if (lo < 0 || hi < lo || hi > L.n_tok) return;
+  float sum = 0.f;
+  int cnt = 0;
+  each_row<LPR>(L, a.logp, a.old_logp, lo, hi, head, lane, a.clip_mask, &bad, [&](float lp, float ol) {
+    int bits;
+    float ratio;
+    sum += surrogate_term(lp, ol, A, a.cc, &bits, &ratio);
+    ++cnt;
+    return bits;
+  });
+  // rows owned by no response (before the first / after the last range) carry no flags
+  if (a.clip_mask && r == 0)
+    for (int64_t t = lane; t < lo; t += LPR) a.clip_mask[t] = 0;
+  if (a.clip_mask && r == L.n_resp - 1)
+    for (int64_t t = hi + lane; t < L.n_tok; t += LPR) a.clip_mask[t] = 0;
+  sum = team_reduce<LPR>(sum, lds_f, Plus());
+  cnt = team_reduce<LPR>(cnt, lds_i, Plus());
+  bad = team_reduce<LPR>(bad, lds_i, Or());
+  *total = (a.agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN && cnt > 0) ? sum / static_cast<float>(cnt) : sum;
+  *rows = cnt;
+  *word = (head & kNoHead) | bad << kErrShift;
+}
+
+template <int LPR>
+__global__ __launch_bounds__(256) void k_surrogate_resp(SurrogateArgs a, float* __restrict__ resp_sum, int32_t* __restrict__ resp_cnt,
                                                         int32_t* __restrict__ resp_head) {
   __shared__ float lds_f[4];
   __shared__ int lds_i[4];
   const int lane = threadIdx.x & (LPR - 1);
   const int team = (blockIdx.x * blockDim.x + threadIdx.x) / LPR;
   const int n_teams = (gridDim.x * blockDim.x) / LPR;
-  for (int r = team; r < L.n_resp; r += n_teams) {
-    const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
-    if (lo < 0 || hi < lo || hi > L.n_tok) {
-      if (lane == 0) {
-        resp_sum[r] = 0.f;
-        resp_cnt[r] = 0;
-        resp_head[r] = kNoHead | AT_GRPO_DATA_SEQLENS << kErrShift;
-      }
-      continue;
-    }
-    int bad = 0;
-    const int head = head_or_error(L, r, &bad);
-    const float A = adv[r];
-    float sum = 0.f;
-    int cnt = 0;
-    each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, clip_mask, &bad, [&](float lp, float ol) {
-      int bits;
-      float ratio;
-      sum += surrogate_term(lp, ol, A, cc, &bits, &ratio);
-      ++cnt;
-      return bits;
-    });
-    // rows owned by no response (before the first / after the last range) carry no flags
-    if (clip_mask && r == 0)
-      for (int64_t t = lane; t < lo; t += LPR) clip_mask[t] = 0;
-    if (clip_mask && r == L.n_resp - 1)
-      for (int64_t t = hi + lane; t < L.n_tok; t += LPR) clip_mask[t] = 0;
-    sum = team_reduce<LPR>(sum, lds_f, Plus());
-    cnt = team_reduce<LPR>(cnt, lds_i, Plus());
-    bad = team_reduce<LPR>(bad, lds_i, Or());
+  for (int r = team; r < a.L.n_resp; r += n_teams) {
+    float total;
+    int rows, word;
+    surrogate_response<LPR>(a, r, lane, lds_f, lds_i, &total, &rows, &word);
     if (lane == 0) {
-      resp_sum[r] = (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN && cnt > 0) ? sum / static_cast<float>(cnt) : sum;
-      resp_cnt[r] = cnt;
-      resp_head[r] = (head & kNoHead) | bad << kErrShift;
+      resp_sum[r] = total;
+      resp_cnt[r] = rows;
+      resp_head[r] = word;
     }
   }
 }
+
+__device__ __forceinline__ float mean_loss(int agg, float total, int rows, int resps) {
+  const int denom = agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN ? resps : rows;
+  return denom > 0 ? -total / static_cast<float>(denom) : 0.f;
+}
+
+// Few responses of few rows: all of it by one workgroup, whose wavefront m then adds up head m.  err: null, or the word that gets
+// (first) or adds the data errors.
+constexpr int kOneThreads = 1024, kOneResp = 1024;
+
+struct LossOut {
+  float* loss;
+  int32_t *n_valid, *err;
+  int first;
+};
+
+template <int LPR>
+__device__ __forceinline__ void each_response(const SurrogateArgs& a, float* sums, int* rows, int* words) {
+  const int lane = threadIdx.x & (LPR - 1);
+  for (int r = threadIdx.x / LPR; r < a.L.n_resp; r += kOneThreads / LPR) {
+    float total;
+    int n, word;
+    surrogate_response<LPR>(a, r, lane, nullptr, nullptr, &total, &n, &word);
+    if (lane == 0) {
+      sums[r] = total;
+      rows[r] = n;
+      words[r] = word;
+    }
+  }
+}
+
+__device__ void surrogate_by_one(const SurrogateArgs& a, int lanes, const LossOut& o) {
+  __shared__ float sums[kOneResp];
+  __shared__ int rows[kOneResp], words[kOneResp];
+  static_assert(kOneThreads / 64 >= kMaxHeads, "a wavefront per head");
+  if (lanes == 64) each_response<64>(a, sums, rows, words);
+  else if (lanes == 32) each_response<32>(a, sums, rows, words);
+  else each_response<16>(a, sums, rows, words);
+  __syncthreads();
+  const int m = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (m >= a.L.n_heads) return;
+  float total = 0.f;
+  int n = 0, resps = 0, bad = 0;
+  for (int r = lane; r < a.L.n_resp; r += 64) {
+    const bool mine = (words[r] & kNoHead) == m;
+    bad |= words[r] >> kErrShift;
+    total += mine ? sums[r] : 0.f;
+    n += mine ? rows[r] : 0;
+    resps += mine && rows[r] > 0 ? 1 : 0;
+  }
+  total = wave_sum(total);
+  n = wave_sum_int(n);
+  resps = wave_sum_int(resps);
+  bad = team_reduce<64>(bad, static_cast<int*>(nullptr), Or());
+  if (lane != 0) return;
+  if (m == 0 && o.err) *o.err = o.first ? bad : *o.err | bad;      // kernels in front of this one may have raised bits
+  o.loss[m] = mean_loss(a.agg, total, n, resps);
+  if (o.n_valid) o.n_valid[m] = n;
+}
+
+__global__ __launch_bounds__(kOneThreads) void k_surrogate_one(SurrogateArgs a, int lanes, LossOut o) { surrogate_by_one(a, lanes, o); }
 
 // one 1024-thread block per head: fixed-order sums over the responses routed to it
 __global__ __launch_bounds__(1024) void k_loss_final(int n_resp, const float* __restrict__ resp_sum,
@@ -358,8 +432,7 @@ __global__ __launch_bounds__(1024) void k_loss_final(int n_resp, const float* __
       e |= ie[w];
     }
     if (m == 0) *err = first ? e : *err | e;      // kernels in front of this one may have raised bits
-    const int denom = (agg == AT_GRPO_AGG_SEQ_MEAN_TOKEN_MEAN) ? nr : c;
-    loss[m] = denom > 0 ? -tot / static_cast<float>(denom) : 0.f;
+    loss[m] = mean_loss(agg, tot, c, nr);
     if (n_valid) n_valid[m] = c;
   }
 }
@@ -387,14 +460,15 @@ __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* _
   const int n_teams = (gridDim.x * blockDim.x) / LPR;
   for (int r = team; r < L.n_resp; r += n_teams) {
     const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
-    int head = -1, bad = 0;
+    const float A = adv[r];
+    int bad = 0;
+    int head = head_or_error(L, r, &bad);
     int n = 0, low = 0, high = 0, zero = 0;
     float kl = 0.f, rs = 0.f;
     if (lo < 0 || hi < lo || hi > L.n_tok) {
+      head = -1;
       bad = AT_GRPO_DATA_SEQLENS;
     } else {
-      head = head_or_error(L, r, &bad);
-      const float A = adv[r];
       each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, nullptr, &bad, [&](float lp, float ol) {
         const float d = lp - ol;
         const bool is_low = d < cc.lo, is_high = d > cc.hi;
@@ -562,7 +636,7 @@ struct PrepArgs {
 };
 
 template <int MODE>
-__global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
+__device__ __forceinline__ void prep_small(const PrepArgs& a) {
   __shared__ __attribute__((aligned(16))) int8_t mark[kPsRows];
   __shared__ int part[2][kPsThreads / 64];
   __shared__ int rows_of_head[kMaxHeads], resps_of_head[kMaxHeads];
@@ -746,6 +820,18 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
   }
 }
 
+template <int MODE>
+__global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
+  prep_small<MODE>(a);
+}
+
+// Both read the log-probabilities and neither needs the other's results: the backward's preparation by one workgroup, the surrogate
+// and the loss by another (which raises no error bits: the first one meets the same data).
+__global__ __launch_bounds__(kPsThreads) void k_prep_backward_loss(PrepArgs a, SurrogateArgs sa, LossOut o) {
+  if (blockIdx.x == 0) prep_small<PREP_BACKWARD>(a);
+  else surrogate_by_one(sa, a.lanes, o);
+}
+
 unsigned grid_for(int64_t n, int per_block, int64_t cap = 1 << 20) {
   int64_t g = ceil_div(n, per_block);
   if (g < 1) g = 1;
@@ -763,6 +849,14 @@ int team_lanes_small(const TokenLayout& L) {
 // responses of 290 rows in the mean 10.1 -> 5.4 us; 1024 of 288 take 6.0 with a wavefront and 5.8 with a workgroup each, 6144 of 289
 // 13.0 and 19.0.
 constexpr int kWideTeams = 512;
+
+// One workgroup walks the responses 1024 / lanes at a time, 3 us each time.  Stage of one and of two launches, us on the stream with the
+// events around it: 50 responses of 20 rows 8.3 and 10.2, 100 10.0 and 11.5, 200 14.7 and 10.3; 40 of 87 9.8 and 10.4, 80 of 89 13.2 and
+// 11.2; 13 of 262 9.3 and 10.9, 27 of 256 12.1 and 10.5.
+bool surrogate_is_small(const TokenLayout& L) {
+  return L.n_tok <= 4096 && L.n_tok <= static_cast<int64_t>(L.n_resp) * 1024 &&
+         static_cast<int64_t>(L.n_resp) * team_lanes_small(L) <= 2 * kOneThreads;
+}
 
 // Lanes that share a response in the row kernels, by the mean number of rows and by how many responses there are.  The chip
 // holds 8192 of these wavefronts.  While the responses are few rounds of it, the call ends with its longest response, which may
@@ -837,11 +931,16 @@ int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* l
                      const float* adv, float eps_low, float eps_high, int agg, float* loss,
                      uint8_t* clip_mask, int32_t* n_valid, bool first, hipStream_t s) {
   ProfScope ps(PROF_SURROGATE, s);
-  const ClipConst cc = make_clip(eps_low, eps_high);
+  const SurrogateArgs a{L, logp, old_logp, adv, make_clip(eps_low, eps_high), agg, clip_mask};
+  if (surrogate_is_small(L)) {
+    hipLaunchKernelGGL(k_surrogate_one, dim3(1), dim3(kOneThreads), 0, s, a, team_lanes_small(L), LossOut{loss, n_valid, S.err, first ? 1 : 0});
+    ATG_LAUNCH_CHECK();
+    return AT_GRPO_OK;
+  }
   const int lanes = team_lanes(L);
   auto k = lanes == 256 ? k_surrogate_resp<256> : lanes == 64 ? k_surrogate_resp<64> : lanes == 32 ? k_surrogate_resp<32> : k_surrogate_resp<16>;
-  hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, L, logp, old_logp, adv, cc, agg,
-                     clip_mask, S.resp_sum, S.resp_len, S.resp_head);
+  hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, a, S.resp_sum, S.resp_len,
+                     S.resp_head);
   ATG_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_loss_final, dim3(L.n_heads), dim3(1024), 0, s, L.n_resp, S.resp_sum, S.resp_len,
                      S.resp_head, agg, loss, n_valid, S.err, first ? 1 : 0);
@@ -930,6 +1029,12 @@ bool prep_is_small(const TokenLayout& L) {
   return L.n_tok <= kPsRows && static_cast<int64_t>(L.n_resp) * team_lanes_small(L) <= 16 * kPsThreads;
 }
 
+// Beside the backward's preparation, which takes 1 us each time, the loss's workgroup is the longer one from some rounds on, and the two
+// launches saved are 8 us.
+bool prep_takes_loss(const TokenLayout& L) {
+  return prep_is_small(L) && L.n_tok <= 16384 && static_cast<int64_t>(L.n_resp) * team_lanes_small(L) <= 4 * kOneThreads;
+}
+
 static PrepArgs prep_args(const TokenLayout& L, const TokenScratch& S) {
   PrepArgs a{};
   a.L = L;
@@ -959,6 +1064,20 @@ int launch_prep_backward(const TokenLayout& L, const TokenScratch& S, const floa
   a.ca = ca;
   a.coef = coef;
   hipLaunchKernelGGL(k_prep_small<PREP_BACKWARD>, dim3(1), dim3(kPsThreads), 0, s, a);
+  ATG_LAUNCH_CHECK();
+  return AT_GRPO_OK;
+}
+
+int launch_prep_backward_loss(const TokenLayout& L, const TokenScratch& S, const float* logp, const CoefArgs& ca, float* coef,
+                              float* loss, uint8_t* clip_mask, int32_t* n_valid, hipStream_t s) {
+  static_assert(16 * kPsThreads / 16 <= kOneResp && kPsThreads == kOneThreads, "what prep_is_small lets through");
+  ProfScope ps(PROF_PREP, s);
+  PrepArgs a = prep_args(L, S);
+  a.logp = const_cast<float*>(logp);   // only read in this mode
+  a.ca = ca;
+  a.coef = coef;
+  const SurrogateArgs sa{L, logp, ca.old_logp, ca.adv, ca.cc, ca.agg, clip_mask};
+  hipLaunchKernelGGL(k_prep_backward_loss, dim3(2), dim3(kPsThreads), 0, s, a, sa, LossOut{loss, n_valid, nullptr, 0});
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

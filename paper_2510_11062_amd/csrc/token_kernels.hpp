@@ -152,6 +152,11 @@ int launch_prep_logprob(const TokenLayout& L, const TokenScratch& S, float* logp
 // resp_of_tok, resp_len, resp_cnt of S; coef; cnt and idx of the rows whose coefficient is not zero
 int launch_prep_backward(const TokenLayout& L, const TokenScratch& S, const float* logp, const CoefArgs& ca, float* coef,
                          hipStream_t s);
+// the same, and beside it what launch_surrogate computes, but for the error word (the preparation raises the same bits); for batches
+// that prep_takes_loss lets through
+bool prep_takes_loss(const TokenLayout& L);
+int launch_prep_backward_loss(const TokenLayout& L, const TokenScratch& S, const float* logp, const CoefArgs& ca, float* coef,
+                              float* loss, uint8_t* clip_mask, int32_t* n_valid, hipStream_t s);
 // resp_of_tok, resp_len, cnt, resp_cnt of S; cnt and idx of SB (advantage not zero) and SF (zero; a few of them stand behind
 // the others on SB's list instead); logp = lse = 0 on rows that take no part; gates = 0
 int launch_prep_step(const TokenLayout& L, const TokenScratch& S, const TokenScratch& SB, const TokenScratch& SF,

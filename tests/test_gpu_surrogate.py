@@ -118,3 +118,45 @@ def test_data_errors_per_team(gpu_device, n_resp, mean):
     check(16, token, cu, bad_agent, [2, k + 2, last - 1], [])
     check(28, bad_token, bad_cu, bad_agent, [k - 1, k, last, 2, k + 2, last - 1], at)
     check(0, token, cu, agent, [], [])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_resp,mean", [(1, 9), (128, 20), (129, 20), (60, 68), (61, 68), (31, 130), (32, 130), (4, 1024), (3, 1025)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_one_workgroup(gpu_device, n_resp, mean, shift):
+    """Both sides of where one workgroup computes the whole stage: two rounds of responses, 4096 rows, 1024 rows per response."""
+    test_rows_per_team(gpu_device, n_resp, mean, shift)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_resp,rows", [(5, 3), (256, 20), (257, 20), (128, 100), (129, 100), (64, 256), (64, 257)])
+@pytest.mark.parametrize("agg", ["token_mean", "seq_mean_token_mean"])
+def test_fp32_step_equals_two_calls(gpu_device, n_resp, rows, agg):
+    """Where the loss is computed beside the backward's preparation and where it is not (four rounds of responses, 16384 rows), with
+    tokens and an agent out of range: the same bits as the two calls but for the loss, whose terms are added in another order (sums
+    of up to 25700 fp32 terms of size about 1, 1e-6)."""
+    gen = torch.Generator(device=gpu_device).manual_seed(n_resp * rows)
+    n, H, V = n_resp * rows, 32, 200
+    rand = lambda *s: torch.randn(*s, generator=gen, device=gpu_device)
+    hidden, W = rand(n, H), [rand(V, H) * 0.1 for _ in range(2)]
+    token = torch.randint(0, V, (n,), generator=gen, device=gpu_device, dtype=torch.int32)
+    token[[1, n - 1]] = torch.tensor([V, -3], dtype=torch.int32, device=gpu_device)
+    mask = (torch.rand(n, generator=gen, device=gpu_device) < 0.8).to(torch.uint8)
+    mask[[1, n - 1]] = 1
+    agent = (torch.arange(n_resp, device=gpu_device) % 2).to(torch.int32)
+    agent[2] = 7
+    cu = torch.arange(n_resp + 1, device=gpu_device) * rows
+    batch = api.Batch(hidden, W, token, cu, mask, agent, torch.tensor([1, 0], dtype=torch.int32, device=gpu_device))
+    old, adv = -5.3 + 0.2 * rand(n), rand(n_resp)
+    adv[3] = 0
+    say(f"[surrogate] fp32 step of {n_resp} responses of {rows} rows, {agg}")
+    one = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, 0.2, 0.2, agg)
+    err = api.error_word(one["workspace"])
+    one = {k: [x.clone() for x in v] if k == "dW" else v.clone() for k, v in one.items() if k != "workspace"}
+    fwd = api.at_grpo_policy_loss_fwd(batch, old, adv, 0.2, 0.2, agg)
+    assert api.error_word(fwd["workspace"]) == err == 4 | 16      # tokens, agents
+    bwd = api.at_grpo_policy_loss_bwd(batch, old, adv, fwd["logp"], fwd["lse"], 0.2, 0.2, agg)
+    for k in ("logp", "lse", "clip_mask", "n_valid"):
+        assert torch.equal(one[k], fwd[k]), k
+    assert torch.equal(one["d_hidden"], bwd["d_hidden"]) and all(torch.equal(a, b) for a, b in zip(one["dW"], bwd["dW"]))
+    assert float((one["loss"] - fwd["loss"]).abs().max()) <= 1e-6
