@@ -307,24 +307,70 @@ __device__ __forceinline__ void surrogate_response(const SurrogateArgs& a, int r
   *word = (head & kNoHead) | bad << kErrShift;
 }
 
+// What a workgroup of the row kernels adds up per head, in LDS: each team its responses in ascending order, then the teams in turn.
+// The final sums read a word per workgroup and head: a word per response, read by one compute unit, took 16 us for 96000 responses and
+// 31 for the monitors' seven.
+template <int LPR, int NI, int NF>
+struct HeadSums {
+  static constexpr int kTeams = 256 / LPR;
+  int i[kTeams][kMaxHeads][NI];
+  float f[kTeams][kMaxHeads][NF];
+  int bad;
+  __device__ __forceinline__ void clear() {
+    for (int k = threadIdx.x; k < kTeams * kMaxHeads * NI; k += 256) (&i[0][0][0])[k] = 0;
+    for (int k = threadIdx.x; k < kTeams * kMaxHeads * NF; k += 256) (&f[0][0][0])[k] = 0.f;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+  }
+  // sums of head m over the teams
+  __device__ __forceinline__ void total(int m, int (&ti)[NI], float (&tf)[NF]) const {
+#pragma unroll
+    for (int k = 0; k < NI; ++k) ti[k] = i[0][m][k];
+#pragma unroll
+    for (int k = 0; k < NF; ++k) tf[k] = f[0][m][k];
+#pragma unroll
+    for (int t = 1; t < kTeams; ++t) {
+#pragma unroll
+      for (int k = 0; k < NI; ++k) ti[k] += i[t][m][k];
+#pragma unroll
+      for (int k = 0; k < NF; ++k) tf[k] += f[t][m][k];
+    }
+  }
+};
+
 template <int LPR>
-__global__ __launch_bounds__(256) void k_surrogate_resp(SurrogateArgs a, float* __restrict__ resp_sum, int32_t* __restrict__ resp_cnt,
-                                                        int32_t* __restrict__ resp_head) {
+__global__ __launch_bounds__(256) void k_surrogate_resp(SurrogateArgs a, RowParts p) {
   __shared__ float lds_f[4];
   __shared__ int lds_i[4];
-  const int lane = threadIdx.x & (LPR - 1);
+  __shared__ HeadSums<LPR, 2, 1> sums;
+  const int lane = threadIdx.x & (LPR - 1), mine = threadIdx.x / LPR;
   const int team = (blockIdx.x * blockDim.x + threadIdx.x) / LPR;
   const int n_teams = (gridDim.x * blockDim.x) / LPR;
+  sums.clear();
   for (int r = team; r < a.L.n_resp; r += n_teams) {
     float total;
     int rows, word;
     surrogate_response<LPR>(a, r, lane, lds_f, lds_i, &total, &rows, &word);
     if (lane == 0) {
-      resp_sum[r] = total;
-      resp_cnt[r] = rows;
-      resp_head[r] = word;
+      const int m = word & kNoHead;
+      if (m != kNoHead) {
+        sums.f[mine][m][0] += total;
+        sums.i[mine][m][0] += rows;
+        sums.i[mine][m][1] += rows > 0;
+      }
+      if (word >> kErrShift) atomicOr(&sums.bad, word >> kErrShift);
     }
   }
+  __syncthreads();
+  const int m = threadIdx.x;
+  if (m == 0) p.err[blockIdx.x] = sums.bad;
+  if (m >= a.L.n_heads) return;
+  int ti[2];
+  float tf[1];
+  sums.total(m, ti, tf);
+  const size_t at = static_cast<size_t>(m) * gridDim.x + blockIdx.x;
+  p.ints[at] = make_int4(ti[0], ti[1], 0, 0);
+  p.floats[at] = make_float2(tf[0], 0.f);
 }
 
 __device__ __forceinline__ float mean_loss(int agg, float total, int rows, int resps) {
@@ -388,76 +434,81 @@ __device__ void surrogate_by_one(const SurrogateArgs& a, int lanes, const LossOu
 
 __global__ __launch_bounds__(kOneThreads) void k_surrogate_one(SurrogateArgs a, int lanes, LossOut o) { surrogate_by_one(a, lanes, o); }
 
-// one 1024-thread block per head: fixed-order sums over the responses routed to it
-__global__ __launch_bounds__(1024) void k_loss_final(int n_resp, const float* __restrict__ resp_sum,
-                                                     const int32_t* __restrict__ resp_cnt,
-                                                     const int32_t* __restrict__ resp_head, int agg,
-                                                     float* __restrict__ loss, int32_t* __restrict__ n_valid,
-                                                     int32_t* __restrict__ err, int first) {
-  __shared__ float fs[16];
-  __shared__ int is[16], ir[16], ie[16];
-  const int m = blockIdx.x;
-  float acc = 0.f;
-  int cnt = 0, nresp = 0, bad = 0;
-#pragma unroll 8
-  for (int r = threadIdx.x; r < n_resp; r += 1024) {
-    const int hw = resp_head[r];
-    const bool mine = (hw & kNoHead) == m;
-    bad |= hw >> kErrShift;
-    const float sv = resp_sum[r];
-    const int cv = resp_cnt[r];
-    acc += mine ? sv : 0.f;
-    cnt += mine ? cv : 0;
-    nresp += (mine && cv > 0) ? 1 : 0;
-  }
-  acc = wave_sum(acc);
-  cnt = wave_sum_int(cnt);
-  nresp = wave_sum_int(nresp);
-  if (__builtin_amdgcn_ballot_w64(bad != 0) != 0ull) bad = team_reduce<64>(bad, ie, Or());
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    fs[wave] = acc;
-    is[wave] = cnt;
-    ir[wave] = nresp;
-    ie[wave] = bad;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float tot = 0.f;
-    int c = 0, nr = 0, e = 0;
-    for (int w = 0; w < 16; ++w) {
-      tot += fs[w];
-      c += is[w];
-      nr += ir[w];
-      e |= ie[w];
-    }
-    if (m == 0) *err = first ? e : *err | e;      // kernels in front of this one may have raised bits
-    loss[m] = mean_loss(agg, tot, c, nr);
-    if (n_valid) n_valid[m] = c;
-  }
-}
-
-// Diagnostics of the clipped-ratio update, LPR lanes per response: participating rows, rows below
-// / above the clip range, rows on the clipped branch, and the sums of ratio - 1 - d and of the ratio.
-struct DiagPartials {
-  int32_t* head;    // [n_resp]
-  int32_t* n;       // [n_resp] x 4: rows, low, high, zero-gradient (struct of arrays)
-  int32_t* low;
-  int32_t* high;
-  int32_t* zero;
-  float* kl;        // [n_resp]
-  float* ratio;     // [n_resp]
+// One 1024-thread block per head: fixed-order sums over the n workgroups of the row kernel.  Returns the head's totals and, to every
+// head, the data errors.
+struct FinalSums {
+  int i[4];
+  float f[2];
+  int bad;
 };
 
+__device__ __forceinline__ FinalSums final_sums(const RowParts& p, int n) {
+  __shared__ int is[4][16], ie[16];
+  __shared__ float fs[2][16];
+  const int4* ints = p.ints + static_cast<size_t>(blockIdx.x) * n;
+  const float2* floats = p.floats + static_cast<size_t>(blockIdx.x) * n;
+  FinalSums s{{0, 0, 0, 0}, {0.f, 0.f}, 0};
+#pragma unroll 4
+  for (int b = threadIdx.x; b < n; b += 1024) {
+    const int4 i = ints[b];
+    const float2 f = floats[b];
+    s.bad |= p.err[b];
+    s.i[0] += i.x;
+    s.i[1] += i.y;
+    s.i[2] += i.z;
+    s.i[3] += i.w;
+    s.f[0] += f.x;
+    s.f[1] += f.y;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    s.i[k] = wave_sum_int(s.i[k]);
+    if (lane == 0) is[k][wave] = s.i[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    s.f[k] = wave_sum(s.f[k]);
+    if (lane == 0) fs[k][wave] = s.f[k];
+  }
+  if (__builtin_amdgcn_ballot_w64(s.bad != 0) != 0ull) s.bad = team_reduce<64>(s.bad, ie, Or());
+  if (lane == 0) ie[wave] = s.bad;
+  __syncthreads();
+  s = FinalSums{{0, 0, 0, 0}, {0.f, 0.f}, 0};
+  if (threadIdx.x != 0) return s;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s.i[k] += is[k][w];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) s.f[k] += fs[k][w];
+    s.bad |= ie[w];
+  }
+  return s;
+}
+
+__global__ __launch_bounds__(1024) void k_loss_final(RowParts p, int n, int agg, LossOut o) {
+  const FinalSums s = final_sums(p, n);
+  if (threadIdx.x != 0) return;
+  const int m = blockIdx.x;
+  if (m == 0) *o.err = o.first ? s.bad : *o.err | s.bad;      // kernels in front of this one may have raised bits
+  o.loss[m] = mean_loss(agg, s.f[0], s.i[0], s.i[1]);
+  if (o.n_valid) o.n_valid[m] = s.i[0];
+}
+
+// Diagnostics of the clipped-ratio update, LPR lanes per response: participating rows, rows below / above the clip range, rows on
+// the clipped branch, and the sums of ratio - 1 - d and of the ratio.
 template <int LPR>
 __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* __restrict__ logp,
                                                    const float* __restrict__ old_logp,
-                                                   const float* __restrict__ adv, ClipConst cc, DiagPartials P) {
+                                                   const float* __restrict__ adv, ClipConst cc, RowParts p) {
   __shared__ float lds_f[4];
   __shared__ int lds_i[4];
-  const int lane = threadIdx.x & (LPR - 1);
+  __shared__ HeadSums<LPR, 4, 2> sums;
+  const int lane = threadIdx.x & (LPR - 1), mine = threadIdx.x / LPR;
   const int team = (blockIdx.x * blockDim.x + threadIdx.x) / LPR;
   const int n_teams = (gridDim.x * blockDim.x) / LPR;
+  sums.clear();
   for (int r = team; r < L.n_resp; r += n_teams) {
     const int64_t lo = L.cu_seqlens[r], hi = L.cu_seqlens[r + 1];
     const float A = adv[r];
@@ -489,68 +540,36 @@ __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* _
     kl = team_reduce<LPR>(kl, lds_f, Plus());
     rs = team_reduce<LPR>(rs, lds_f, Plus());
     if (lane == 0) {
-      P.head[r] = (head & kNoHead) | bad << kErrShift;
-      P.n[r] = n;
-      P.low[r] = low;
-      P.high[r] = high;
-      P.zero[r] = zero;
-      P.kl[r] = kl;
-      P.ratio[r] = rs;
+      if (head >= 0) {
+        const int add[4] = {n, low, high, zero};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sums.i[mine][head][k] += add[k];
+        sums.f[mine][head][0] += kl;
+        sums.f[mine][head][1] += rs;
+      }
+      if (bad) atomicOr(&sums.bad, bad);
     }
   }
+  __syncthreads();
+  const int m = threadIdx.x;
+  if (m == 0) p.err[blockIdx.x] = sums.bad;
+  if (m >= L.n_heads) return;
+  int ti[4];
+  float tf[2];
+  sums.total(m, ti, tf);
+  const size_t at = static_cast<size_t>(m) * gridDim.x + blockIdx.x;
+  p.ints[at] = make_int4(ti[0], ti[1], ti[2], ti[3]);
+  p.floats[at] = make_float2(tf[0], tf[1]);
 }
 
-// one 1024-thread block per head: fixed-order sums of the per-response partials
-__global__ __launch_bounds__(1024) void k_diag_final(int n_resp, DiagPartials P, int32_t* __restrict__ counts,
-                                                     float* __restrict__ stats, int32_t* __restrict__ err) {
-  __shared__ int is[4][16], ie[16];
-  __shared__ float fs[2][16];
+__global__ __launch_bounds__(1024) void k_diag_final(RowParts p, int n, int32_t* __restrict__ counts, float* __restrict__ stats,
+                                                     int32_t* __restrict__ err) {
+  const FinalSums s = final_sums(p, n);
+  if (threadIdx.x != 0) return;
   const int m = blockIdx.x;
-  int c[4] = {0, 0, 0, 0};
-  float f[2] = {0.f, 0.f};
-  int bad = 0;
-#pragma unroll 4
-  for (int r = threadIdx.x; r < n_resp; r += 1024) {   // loads that do not wait for the head: 7.1 us with a branch on it
-    const int hw = P.head[r];
-    const bool mine = (hw & kNoHead) == m;
-    bad |= hw >> kErrShift;
-    const int n = P.n[r], low = P.low[r], high = P.high[r], zero = P.zero[r];
-    const float kl = P.kl[r], ratio = P.ratio[r];
-    c[0] += mine ? n : 0;
-    c[1] += mine ? low : 0;
-    c[2] += mine ? high : 0;
-    c[3] += mine ? zero : 0;
-    f[0] += mine ? kl : 0.f;
-    f[1] += mine ? ratio : 0.f;
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    c[k] = wave_sum_int(c[k]);
-    if (lane == 0) is[k][wave] = c[k];
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    f[k] = wave_sum(f[k]);
-    if (lane == 0) fs[k][wave] = f[k];
-  }
-  if (__builtin_amdgcn_ballot_w64(bad != 0) != 0ull) bad = team_reduce<64>(bad, ie, Or());
-  if (lane == 0) ie[wave] = bad;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int e = 0;
-    for (int w = 0; w < 16; ++w) e |= ie[w];
-    if (m == 0) *err = e;
-    int tot[4] = {0, 0, 0, 0};
-    float ft[2] = {0.f, 0.f};
-    for (int w = 0; w < 16; ++w) {
-      for (int k = 0; k < 4; ++k) tot[k] += is[k][w];
-      for (int k = 0; k < 2; ++k) ft[k] += fs[k][w];
-    }
-    for (int k = 0; k < 4; ++k) counts[m * 4 + k] = tot[k];
-    stats[m * 2 + 0] = tot[0] > 0 ? ft[0] / static_cast<float>(tot[0]) : 0.f;
-    stats[m * 2 + 1] = tot[0] > 0 ? ft[1] / static_cast<float>(tot[0]) : 0.f;
-  }
+  if (m == 0) *err = s.bad;
+  for (int k = 0; k < 4; ++k) counts[m * 4 + k] = s.i[k];
+  for (int k = 0; k < 2; ++k) stats[m * 2 + k] = s.i[0] > 0 ? s.f[k] / static_cast<float>(s.i[0]) : 0.f;
 }
 
 __global__ __launch_bounds__(256) void k_coef(int64_t n_tok, int32_t* __restrict__ flag, CoefArgs ca,
@@ -872,6 +891,10 @@ int team_lanes(const TokenLayout& L) {
   return mean_rows >= 60 && L.n_resp <= 8192 ? 32 : 16;
 }
 
+// Workgroups of the row kernels, and parts for the final sums: 96000 responses, both passes and both sums with at most 16384 235 us, with
+// 4096 216, with 2048 242.
+int row_blocks(const TokenLayout& L) { return static_cast<int>(grid_for(L.n_resp, 256 / team_lanes(L), 4096)); }
+
 }  // namespace
 
 int launch_fill_i32(int32_t* p, int64_t n, int32_t value, hipStream_t s) {
@@ -937,21 +960,28 @@ int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* l
     ATG_LAUNCH_CHECK();
     return AT_GRPO_OK;
   }
-  const int lanes = team_lanes(L);
+  const int lanes = team_lanes(L), blocks = row_blocks(L);
   auto k = lanes == 256 ? k_surrogate_resp<256> : lanes == 64 ? k_surrogate_resp<64> : lanes == 32 ? k_surrogate_resp<32> : k_surrogate_resp<16>;
-  hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, a, S.resp_sum, S.resp_len,
-                     S.resp_head);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, a, S.parts);
   ATG_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_loss_final, dim3(L.n_heads), dim3(1024), 0, s, L.n_resp, S.resp_sum, S.resp_len,
-                     S.resp_head, agg, loss, n_valid, S.err, first ? 1 : 0);
+  hipLaunchKernelGGL(k_loss_final, dim3(L.n_heads), dim3(1024), 0, s, S.parts, blocks, agg, LossOut{loss, n_valid, S.err, first ? 1 : 0});
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }
 
-size_t diagnostics_workspace(int32_t n_resp) {
+RowParts take_row_parts(const TokenLayout& L, WsAlloc& ws) {
+  const size_t blocks = static_cast<size_t>(row_blocks(L));
+  RowParts p;
+  p.ints = ws.take<int4>(blocks * static_cast<size_t>(L.n_heads));
+  p.floats = ws.take<float2>(blocks * static_cast<size_t>(L.n_heads));
+  p.err = ws.take<int32_t>(blocks);
+  return p;
+}
+
+size_t diagnostics_workspace(const TokenLayout& L) {
   WsAlloc ws(nullptr);
   ws.take<int32_t>(64);
-  for (int k = 0; k < 7; ++k) ws.take<int32_t>(static_cast<size_t>(n_resp));
+  take_row_parts(L, ws);
   return ws.bytes();
 }
 
@@ -961,20 +991,13 @@ int launch_diagnostics(const TokenLayout& L, const float* logp, const float* old
   ProfScope ps(PROF_SURROGATE, s);
   WsAlloc ws(workspace);
   int32_t* err = ws.take<int32_t>(64);
-  DiagPartials P;
-  P.head = ws.take<int32_t>(static_cast<size_t>(L.n_resp));
-  P.n = ws.take<int32_t>(static_cast<size_t>(L.n_resp));
-  P.low = ws.take<int32_t>(static_cast<size_t>(L.n_resp));
-  P.high = ws.take<int32_t>(static_cast<size_t>(L.n_resp));
-  P.zero = ws.take<int32_t>(static_cast<size_t>(L.n_resp));
-  P.kl = reinterpret_cast<float*>(ws.take<int32_t>(static_cast<size_t>(L.n_resp)));
-  P.ratio = reinterpret_cast<float*>(ws.take<int32_t>(static_cast<size_t>(L.n_resp)));
+  const RowParts p = take_row_parts(L, ws);
   const ClipConst cc = make_clip(eps_low, eps_high);
-  const int lanes = team_lanes(L);
+  const int lanes = team_lanes(L), blocks = row_blocks(L);
   auto k = lanes == 256 ? k_diag_resp<256> : lanes == 64 ? k_diag_resp<64> : lanes == 32 ? k_diag_resp<32> : k_diag_resp<16>;
-  hipLaunchKernelGGL(k, dim3(grid_for(L.n_resp, 256 / lanes, 16384)), dim3(256), 0, s, L, logp, old_logp, adv, cc, P);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, s, L, logp, old_logp, adv, cc, p);
   ATG_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_diag_final, dim3(L.n_heads), dim3(1024), 0, s, L.n_resp, P, counts, stats, err);
+  hipLaunchKernelGGL(k_diag_final, dim3(L.n_heads), dim3(1024), 0, s, p, blocks, counts, stats, err);
   ATG_LAUNCH_CHECK();
   return AT_GRPO_OK;
 }

@@ -21,6 +21,14 @@ struct TokenLayout {
   const int32_t* head_of_agent;
 };
 
+// What the workgroups of the row kernels (surrogate, diagnostics) leave for the final sums: [n_heads][workgroups] counts and sums, and
+// the data errors that each met.
+struct RowParts {
+  int4* ints;
+  float2* floats;
+  int32_t* err;
+};
+
 struct TokenScratch {
   int32_t* err;          // [1] device error word
   int32_t* resp_of_tok;  // [n_tok]
@@ -31,8 +39,7 @@ struct TokenScratch {
   int32_t* idx;          // [n_heads * n_tok] compacted rows per head
   int32_t* resp_len;     // [n_resp] participating rows per response
   int32_t* resp_cnt;     // [kMaxHeads] responses with at least one participating row, per head
-  float* resp_sum;       // [n_resp] per-response sum (or mean) of surrogate terms
-  int32_t* resp_head;    // [n_resp] head of each response (kNoHead: takes no part) and, from bit kErrShift on, its data errors
+  RowParts parts;        // of the surrogate
   int64_t n_blk;         // ceil(n_tok / kTokPerBlock)
   int64_t n_blk256;      // ceil(n_tok / 256)
 };
@@ -116,7 +123,7 @@ int launch_compact(const TokenLayout& L, const TokenScratch& S, bool with_idx, h
 int launch_resp_len(const TokenLayout& L, const TokenScratch& S, hipStream_t s);
 
 // Per-token surrogate terms + clip mask + per-head loss (Eq. 2).  Self-contained: reads the layout
-// directly (16 to 256 lanes per response); overwrites resp_len with its own per-response counts.  first: the call's first
+// directly (16 to 256 lanes per response).  first: the call's first
 // kernel, which sets the error word; otherwise it adds to it.
 int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* logp,
                      const float* old_logp, const float* adv, float eps_low, float eps_high, int agg,
@@ -124,8 +131,9 @@ int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* l
 
 // Diagnostics of the clipped-ratio update: counts[n_heads][4] = (rows, below, above, zero-gradient),
 // stats[n_heads][2] = (mean of ratio - 1 - d, mean ratio).  Self-contained like launch_surrogate; its
-// scratch (an error word and seven per-response arrays) is taken from `workspace`.
-size_t diagnostics_workspace(int32_t n_resp);
+// scratch (an error word and the parts) is taken from `workspace`.
+RowParts take_row_parts(const TokenLayout& L, WsAlloc& ws);
+size_t diagnostics_workspace(const TokenLayout& L);
 int launch_diagnostics(const TokenLayout& L, const float* logp, const float* old_logp, const float* adv,
                        float eps_low, float eps_high, int32_t* counts, float* stats, void* workspace,
                        hipStream_t s);
