@@ -8,7 +8,8 @@
 // MFMA shape.  v_mfma_f32_16x16x32_bf16, not 32x32x16: both deliver the same peak, but these kernels are bound by
 // power, and per multiply-add the 16x16x32 form moves half as many accumulator words through the register file.
 // On 256 x 256 tiles 32x32x16 gave 1360 TFLOP/s at 1.59 GHz (k = 2048, the logits) and 1310 at 1.44-1.54 (k = 151936,
-// dHidden); 16x16x32 gives 1427-1473 at 1.74-1.82 and 1477-1523 at 1.68-1.74 (five runs on four boxes).
+// dHidden); 16x16x32 gave 1427-1473 at 1.74-1.82 and 1477-1523 at 1.68-1.74 (five runs on four boxes), and with the ring as it is
+// now 1550 at 1.84 and 1552 at 1.77 (1422 on dW's shape, 1339-1410 before).
 //
 // Data path: global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4, 16 bytes per lane) into a ring of five
 // 32 KiB slots (one operand panel each: all 160 KiB of a compute unit); LDS -> registers with ds_read_b128 (operands
@@ -51,7 +52,7 @@ constexpr int kRingFree = 2 * kRingSlot;          // the slot that a tile's firs
 //   Grid16<4, 2> / <2, 4>  8 wavefronts, two per SIMD (128 accumulator registers): one covers part of the other's
 //                          per-tile prologue and epilogue; used where the k loop is short (k = H)
 //   Grid16<2, 2>           4 wavefronts, one per SIMD (256 accumulator registers): a third fewer LDS reads per MFMA and
-//                          half as many wavefronts at each barrier; 7 % faster on the long k loop of dHidden
+//                          half as many wavefronts at each barrier; 2 % faster on the long k loop of dHidden
 // Tiles of fewer than 256 rows of an operand still take a whole ring slot per panel.
 template <int WA, int WB, int TA = kTile16, int TB = kTile16>
 struct Grid16 {

@@ -239,7 +239,8 @@ __device__ __forceinline__ int balanced_tokens(int n) {
 
 // All tiles of a launch, of G.  Those that do not fill a round of the grid are cut into halves or quarters of their tokens if there
 // are workgroups for all of them: 594 tiles (the full vocabulary, up to 256 tokens) are two rounds and a half instead of three
-// (197 tokens at H = 4096 372 -> 346 us with the call's other kernels, 400 at H = 2048, 4.6 rounds, 345 -> 328).
+// (197 tokens at H = 4096 372 -> 346 us with the call's other kernels, 400 at H = 2048, 4.6 rounds, 345 -> 328; with equal tiles and the
+// ring of gemm_bf16.hpp 331 and 268).
 template <typename G, bool PERMUTED, typename Off, typename Epilogue>
 __device__ __forceinline__ void logit_rounds(const LogitIn& in, int n_vtiles, char* smem, Epilogue epi) {
   constexpr bool kCut = sizeof(Off) == 4;       // (not for vocabularies beyond 8.3 million)
@@ -653,10 +654,10 @@ __global__ __launch_bounds__(kTpThreads) void k_transpose_w(const bf16_t* __rest
 
 // ------------------------------------------------------------------------------------------------
 // dHidden: A = columns of W (h), B = dZ / E rows (tokens), k = vocabulary.
-// For many rows W is transposed first and both operands are contiguous along k (1477-1523 TFLOP/s); for few rows the
-// contraction reads W as it stands, k-major (1404-1431 TFLOP/s on the same boxes), and the transposition is saved.  Per weight
-// the transposition takes 0.8 ps (H = 4096) to 1.1 ps (H = 2048) of the chip, the slower loop 0.07 to 0.085 fs per row:
-// the two meet between 9 000 and 16 000 rows of a head, and the line lies in the middle.
+// For many rows W is transposed first and both operands are contiguous along k (1552 TFLOP/s); for few rows the contraction reads
+// W as it stands, k-major (1486 on the same box), and the transposition is saved.  Per weight the transposition takes 0.8 ps (H =
+// 4096) to 1.1 ps (H = 2048) of the chip, the slower loop 0.06 to 0.08 fs per row: the two meet between 10 000 and 18 000 rows of a
+// head, and on either side of the line the wrong choice costs 1 % of this contraction at the most.
 // ------------------------------------------------------------------------------------------------
 constexpr int kUntransposedRows = 12288;
 
