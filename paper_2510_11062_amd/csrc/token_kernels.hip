@@ -978,11 +978,14 @@ RowParts take_row_parts(const TokenLayout& L, WsAlloc& ws) {
   return p;
 }
 
+// no less than the seven words per response that this scratch memory has always had room for
 size_t diagnostics_workspace(const TokenLayout& L) {
-  WsAlloc ws(nullptr);
+  WsAlloc ws(nullptr), words(nullptr);
   ws.take<int32_t>(64);
   take_row_parts(L, ws);
-  return ws.bytes();
+  words.take<int32_t>(64);
+  for (int k = 0; k < 7; ++k) words.take<int32_t>(static_cast<size_t>(L.n_resp));
+  return ws.bytes() > words.bytes() ? ws.bytes() : words.bytes();
 }
 
 int launch_diagnostics(const TokenLayout& L, const float* logp, const float* old_logp, const float* adv,
