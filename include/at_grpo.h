@@ -350,7 +350,8 @@ int at_grpo_head_update(int32_t dtype, int32_t H, int32_t V, int32_t n_heads, vo
 /*
  * Bytes of workspace a call needs.  `batch` may be NULL for AT_GRPO_CALL_GROUP_ADVANTAGE; the
  * id extents are ignored for the other calls.  Only sizes are read from `batch` (H, V, n_heads,
- * dtype, n_tok, n_resp); no pointer in it is dereferenced.  Returns 0 on invalid arguments.
+ * dtype, n_tok, n_resp); no pointer in it is dereferenced.  With the other sizes as they are, a batch of
+ * fewer responses never needs more.  Returns 0 on invalid arguments.
  */
 size_t at_grpo_workspace_bytes(int32_t which_call, const at_grpo_batch* batch, int32_t n_resp,
                                int32_t n_env, int32_t n_agent, int32_t n_turn);

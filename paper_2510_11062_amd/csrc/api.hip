@@ -142,7 +142,7 @@ void make_plan(const at_grpo_batch* b, int call, WsAlloc& ws, Plan* p) {
   S.blk_cnt = ws.take<int32_t>(static_cast<size_t>(M * S.n_blk));
   S.blk_off = ws.take<int32_t>(static_cast<size_t>(M * S.n_blk));
   S.resp_len = ws.take<int32_t>(static_cast<size_t>(b->n_resp));
-  S.parts = take_row_parts(p->L, ws);
+  S.parts = take_row_parts(b->n_resp, M, ws);
   const bool heads = call != AT_GRPO_CALL_SURROGATE;
   S.idx = heads ? ws.take<int32_t>(static_cast<size_t>(M) * static_cast<size_t>(n_tok)) : nullptr;
   if (!heads) return;
@@ -298,10 +298,7 @@ extern "C" size_t at_grpo_workspace_bytes(int32_t which_call, const at_grpo_batc
   if (which_call == AT_GRPO_CALL_HEAD_UPDATE) return head_update_workspace();
   if (which_call == AT_GRPO_CALL_DIAGNOSTICS) {
     if (check_layout(batch, false) != AT_GRPO_OK) return 0;
-    WsAlloc ws(nullptr);
-    Plan p{};
-    make_plan(batch, AT_GRPO_CALL_SURROGATE, ws, &p);     // layout only
-    return diagnostics_workspace(p.L);
+    return diagnostics_workspace(batch->n_resp);
   }
   if ((which_call < AT_GRPO_CALL_TOKEN_LOGPROB || which_call > AT_GRPO_CALL_SURROGATE) &&
       which_call != AT_GRPO_CALL_TOKEN_ENTROPY && which_call != AT_GRPO_CALL_POLICY_LOSS_FWD_BWD)
@@ -369,10 +366,10 @@ extern "C" int at_grpo_surrogate_diagnostics(const at_grpo_batch* batch, const f
   ATG_TRY(check_pointers(batch, false));
   if (!logp || !old_logp || !adv || !counts || !stats) return AT_GRPO_EINVAL;
   if (!eps_ok(eps_low, eps_high)) return AT_GRPO_EINVAL;
+  ATG_TRY(check_workspace(workspace, workspace_bytes, diagnostics_workspace(batch->n_resp)));
   WsAlloc ws(nullptr);
   Plan p{};
   make_plan(batch, AT_GRPO_CALL_SURROGATE, ws, &p);   // layout only; the scratch is laid out by the launcher
-  ATG_TRY(check_workspace(workspace, workspace_bytes, diagnostics_workspace(p.L)));
   return launch_diagnostics(p.L, logp, old_logp, adv, eps_low, eps_high, counts, stats, workspace,
                             static_cast<hipStream_t>(hip_stream));
 }

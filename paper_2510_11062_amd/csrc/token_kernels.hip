@@ -893,7 +893,8 @@ int team_lanes(const TokenLayout& L) {
 
 // Workgroups of the row kernels, and parts for the final sums: 96000 responses, both passes and both sums with at most 16384 235 us, with
 // 4096 216, with 2048 242.
-int row_blocks(const TokenLayout& L) { return static_cast<int>(grid_for(L.n_resp, 256 / team_lanes(L), 4096)); }
+constexpr int kRowBlocks = 4096;
+int row_blocks(const TokenLayout& L) { return static_cast<int>(grid_for(L.n_resp, 256 / team_lanes(L), kRowBlocks)); }
 
 }  // namespace
 
@@ -969,22 +970,25 @@ int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* l
   return AT_GRPO_OK;
 }
 
-RowParts take_row_parts(const TokenLayout& L, WsAlloc& ws) {
-  const size_t blocks = static_cast<size_t>(row_blocks(L));
+// Room for a workgroup per response, whatever row_blocks makes of the batch: it falls where responses get more or shorter, and scratch
+// memory that was asked for once, for the largest batch, has to serve the smaller ones.
+RowParts take_row_parts(int32_t n_resp, int n_heads, WsAlloc& ws) {
+  const size_t blocks = static_cast<size_t>(n_resp < kRowBlocks ? n_resp : kRowBlocks);
   RowParts p;
-  p.ints = ws.take<int4>(blocks * static_cast<size_t>(L.n_heads));
-  p.floats = ws.take<float2>(blocks * static_cast<size_t>(L.n_heads));
+  p.ints = ws.take<int4>(blocks * static_cast<size_t>(n_heads));
+  p.floats = ws.take<float2>(blocks * static_cast<size_t>(n_heads));
   p.err = ws.take<int32_t>(blocks);
   return p;
 }
 
-// no less than the seven words per response that this scratch memory has always had room for
-size_t diagnostics_workspace(const TokenLayout& L) {
+// By the number of responses alone, so for all heads that there may be; no less than the seven words per response that this scratch
+// memory has always had room for
+size_t diagnostics_workspace(int32_t n_resp) {
   WsAlloc ws(nullptr), words(nullptr);
   ws.take<int32_t>(64);
-  take_row_parts(L, ws);
+  take_row_parts(n_resp, kMaxHeads, ws);
   words.take<int32_t>(64);
-  for (int k = 0; k < 7; ++k) words.take<int32_t>(static_cast<size_t>(L.n_resp));
+  for (int k = 0; k < 7; ++k) words.take<int32_t>(static_cast<size_t>(n_resp));
   return ws.bytes() > words.bytes() ? ws.bytes() : words.bytes();
 }
 
@@ -994,7 +998,7 @@ int launch_diagnostics(const TokenLayout& L, const float* logp, const float* old
   ProfScope ps(PROF_SURROGATE, s);
   WsAlloc ws(workspace);
   int32_t* err = ws.take<int32_t>(64);
-  const RowParts p = take_row_parts(L, ws);
+  const RowParts p = take_row_parts(L.n_resp, L.n_heads, ws);
   const ClipConst cc = make_clip(eps_low, eps_high);
   const int lanes = team_lanes(L), blocks = row_blocks(L);
   auto k = lanes == 256 ? k_diag_resp<256> : lanes == 64 ? k_diag_resp<64> : lanes == 32 ? k_diag_resp<32> : k_diag_resp<16>;

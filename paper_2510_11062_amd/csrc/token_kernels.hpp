@@ -132,8 +132,8 @@ int launch_surrogate(const TokenLayout& L, const TokenScratch& S, const float* l
 // Diagnostics of the clipped-ratio update: counts[n_heads][4] = (rows, below, above, zero-gradient),
 // stats[n_heads][2] = (mean of ratio - 1 - d, mean ratio).  Self-contained like launch_surrogate; its
 // scratch (an error word and the parts) is taken from `workspace`.
-RowParts take_row_parts(const TokenLayout& L, WsAlloc& ws);
-size_t diagnostics_workspace(const TokenLayout& L);
+RowParts take_row_parts(int32_t n_resp, int n_heads, WsAlloc& ws);
+size_t diagnostics_workspace(int32_t n_resp);
 int launch_diagnostics(const TokenLayout& L, const float* logp, const float* old_logp, const float* adv,
                        float eps_low, float eps_high, int32_t* counts, float* stats, void* workspace,
                        hipStream_t s);
