@@ -6,9 +6,8 @@
 #include <Python.h>
 
 #include <ATen/ops/empty.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
-
-#include <exception>
 
 #include "at_grpo.h"
 
@@ -36,9 +35,9 @@ struct Outputs {
   ~Outputs() { Py_XDECREF(dict); }
   template <typename T>
   T* make(Key key, int64_t n, bool want = true) {
-    if (!dict) throw std::bad_alloc();
+    if (!dict) throw python_error();
     if (!want) {
-      if (PyDict_SetItem(dict, g_keys[key], Py_None) != 0) throw std::bad_alloc();
+      if (PyDict_SetItem(dict, g_keys[key], Py_None) != 0) throw python_error();
       return nullptr;
     }
     at::Tensor t = at::empty({n}, std::is_same<T, float>::value ? f32 : i32);
@@ -46,7 +45,7 @@ struct Outputs {
     PyObject* o = THPVariable_Wrap(std::move(t));
     const int failed = o ? PyDict_SetItem(dict, g_keys[key], o) : -1;
     Py_XDECREF(o);
-    if (failed != 0) throw std::bad_alloc();
+    if (failed != 0) throw python_error();
     return p;
   }
   PyObject* take() {
@@ -82,36 +81,33 @@ PyObject* group_advantage(PyObject*, PyObject* const* v, Py_ssize_t n_args) {
   void* stream = PyLong_AsVoidPtr(v[17]);
   if (PyErr_Occurred()) return nullptr;
 
+  HANDLE_TH_ERRORS      // an allocator's error keeps the Python type that torch.empty raises it with (torch.OutOfMemoryError)
   const int64_t R = reward->numel(), keys = n_env * n_agent * n_turn, groups = R < keys ? R : keys;
-  try {
-    Outputs out(*reward);
-    float* mix = mixed ? out.make<float>(REWARD, R) : nullptr;
-    int32_t* group_id = out.make<int32_t>(GROUP_ID, R);
-    int32_t* n_groups = out.make<int32_t>(N_GROUPS, 1);
-    int32_t* seg = out.make<int32_t>(SEG_OFFSETS, groups + 1);
-    int32_t* perm = out.make<int32_t>(PERM, R);
-    float* adv = out.make<float>(ADV, R);
-    float* mean = out.make<float>(MEAN, groups, want_stats);
-    float* std = out.make<float>(STD, groups, want_stats);
-    int32_t* best = mixed ? out.make<int32_t>(BEST, groups, want_best) : nullptr;
-    const int32_t *env = static_cast<const int32_t*>(ids[0]->data_ptr()), *agent = static_cast<const int32_t*>(ids[1]->data_ptr()),
-                  *turn = static_cast<const int32_t*>(ids[2]->data_ptr());
-    const float *r = static_cast<const float*>(reward->data_ptr()), *l = loc ? static_cast<const float*>(loc->data_ptr()) : nullptr;
-    const int32_t nR = static_cast<int32_t>(R), nE = static_cast<int32_t>(n_env), nA = static_cast<int32_t>(n_agent),
-                  nT = static_cast<int32_t>(n_turn), dd = static_cast<int32_t>(ddof), nm = static_cast<int32_t>(norm);
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = mixed ? reinterpret_cast<MixedFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, l, static_cast<float>(alpha),
-                                                   static_cast<float>(eps_std), dd, nm, mix, group_id, n_groups, seg, perm, adv, mean,
-                                                   std, best, ws, ws_bytes, stream)
-                   : reinterpret_cast<GroupFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, static_cast<float>(eps_std), dd, nm, group_id,
-                                                   n_groups, seg, perm, adv, mean, std, ws, ws_bytes, stream);
-    Py_END_ALLOW_THREADS
-    return status == AT_GRPO_OK ? out.take() : PyLong_FromLong(status);
-  } catch (const std::exception& e) {
-    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
-  }
+  Outputs out(*reward);
+  float* mix = mixed ? out.make<float>(REWARD, R) : nullptr;
+  int32_t* group_id = out.make<int32_t>(GROUP_ID, R);
+  int32_t* n_groups = out.make<int32_t>(N_GROUPS, 1);
+  int32_t* seg = out.make<int32_t>(SEG_OFFSETS, groups + 1);
+  int32_t* perm = out.make<int32_t>(PERM, R);
+  float* adv = out.make<float>(ADV, R);
+  float* mean = out.make<float>(MEAN, groups, want_stats);
+  float* std = out.make<float>(STD, groups, want_stats);
+  int32_t* best = mixed ? out.make<int32_t>(BEST, groups, want_best) : nullptr;
+  const int32_t *env = static_cast<const int32_t*>(ids[0]->data_ptr()), *agent = static_cast<const int32_t*>(ids[1]->data_ptr()),
+                *turn = static_cast<const int32_t*>(ids[2]->data_ptr());
+  const float *r = static_cast<const float*>(reward->data_ptr()), *l = loc ? static_cast<const float*>(loc->data_ptr()) : nullptr;
+  const int32_t nR = static_cast<int32_t>(R), nE = static_cast<int32_t>(n_env), nA = static_cast<int32_t>(n_agent),
+                nT = static_cast<int32_t>(n_turn), dd = static_cast<int32_t>(ddof), nm = static_cast<int32_t>(norm);
+  int status;
+  Py_BEGIN_ALLOW_THREADS
+  status = mixed ? reinterpret_cast<MixedFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, l, static_cast<float>(alpha),
+                                                 static_cast<float>(eps_std), dd, nm, mix, group_id, n_groups, seg, perm, adv, mean,
+                                                 std, best, ws, ws_bytes, stream)
+                 : reinterpret_cast<GroupFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, static_cast<float>(eps_std), dd, nm, group_id,
+                                                 n_groups, seg, perm, adv, mean, std, ws, ws_bytes, stream);
+  Py_END_ALLOW_THREADS
+  return status == AT_GRPO_OK ? out.take() : PyLong_FromLong(status);
+  END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef g_methods[] = {
