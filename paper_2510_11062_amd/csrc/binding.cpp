@@ -60,6 +60,9 @@ struct Outputs {
 // Returns the outputs, or the call's status, or None where an argument is no contiguous GPU tensor of its dtype (the caller says which).
 // With r_loc the function is at_grpo_group_advantage_mixed, else at_grpo_group_advantage.
 PyObject* group_advantage(PyObject*, PyObject* const* v, Py_ssize_t n_args) {
+  // From the first look at a tensor on: some cannot say whether they are contiguous, and what they throw must not leave C.  An
+  // allocator's error keeps the Python type that torch.empty raises it with (torch.OutOfMemoryError).
+  HANDLE_TH_ERRORS
   if (n_args != 18) {
     PyErr_SetString(PyExc_TypeError, "group_advantage takes 18 arguments");
     return nullptr;
@@ -81,7 +84,6 @@ PyObject* group_advantage(PyObject*, PyObject* const* v, Py_ssize_t n_args) {
   void* stream = PyLong_AsVoidPtr(v[17]);
   if (PyErr_Occurred()) return nullptr;
 
-  HANDLE_TH_ERRORS      // an allocator's error keeps the Python type that torch.empty raises it with (torch.OutOfMemoryError)
   const int64_t R = reward->numel(), keys = n_env * n_agent * n_turn, groups = R < keys ? R : keys;
   Outputs out(*reward);
   float* mix = mixed ? out.make<float>(REWARD, R) : nullptr;
