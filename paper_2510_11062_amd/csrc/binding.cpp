@@ -8,6 +8,7 @@
 #include <ATen/ops/empty.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include "at_grpo.h"
 
@@ -27,32 +28,11 @@ const at::Tensor* tensor(PyObject* o, at::ScalarType dtype) {
   return t.is_cuda() && t.scalar_type() == dtype && t.is_contiguous() ? &t : nullptr;
 }
 
-// The outputs of a call, as a dict in the making; a null pointer where there is none
-struct Outputs {
-  PyObject* dict = PyDict_New();
-  at::TensorOptions f32, i32;
-  explicit Outputs(const at::Tensor& like) : f32(like.options().dtype(at::kFloat)), i32(like.options().dtype(at::kInt)) {}
-  ~Outputs() { Py_XDECREF(dict); }
-  template <typename T>
-  T* make(Key key, int64_t n, bool want = true) {
-    if (!dict) throw python_error();
-    if (!want) {
-      if (PyDict_SetItem(dict, g_keys[key], Py_None) != 0) throw python_error();
-      return nullptr;
-    }
-    at::Tensor t = at::empty({n}, std::is_same<T, float>::value ? f32 : i32);
-    T* p = static_cast<T*>(t.data_ptr());
-    PyObject* o = THPVariable_Wrap(std::move(t));
-    const int failed = o ? PyDict_SetItem(dict, g_keys[key], o) : -1;
-    Py_XDECREF(o);
-    if (failed != 0) throw python_error();
-    return p;
-  }
-  PyObject* take() {
-    PyObject* d = dict;
-    dict = nullptr;
-    return d;
-  }
+// Other Python threads run while it lives, as they do during torch.empty: an allocation may have to wait for the driver, or for a thread
+// that holds the allocator's lock and waits for Python's.
+struct WithoutPythonLock {
+  PyThreadState* state = PyEval_SaveThread();
+  ~WithoutPythonLock() { PyEval_RestoreThread(state); }
 };
 
 // group_advantage(function's address, env_id, agent_id, turn_id, reward or r_team, r_loc or None, alpha, n_env, n_agent, n_turn,
@@ -85,30 +65,41 @@ PyObject* group_advantage(PyObject*, PyObject* const* v, Py_ssize_t n_args) {
   if (PyErr_Occurred()) return nullptr;
 
   const int64_t R = reward->numel(), keys = n_env * n_agent * n_turn, groups = R < keys ? R : keys;
-  Outputs out(*reward);
-  float* mix = mixed ? out.make<float>(REWARD, R) : nullptr;
-  int32_t* group_id = out.make<int32_t>(GROUP_ID, R);
-  int32_t* n_groups = out.make<int32_t>(N_GROUPS, 1);
-  int32_t* seg = out.make<int32_t>(SEG_OFFSETS, groups + 1);
-  int32_t* perm = out.make<int32_t>(PERM, R);
-  float* adv = out.make<float>(ADV, R);
-  float* mean = out.make<float>(MEAN, groups, want_stats);
-  float* std = out.make<float>(STD, groups, want_stats);
-  int32_t* best = mixed ? out.make<int32_t>(BEST, groups, want_best) : nullptr;
-  const int32_t *env = static_cast<const int32_t*>(ids[0]->data_ptr()), *agent = static_cast<const int32_t*>(ids[1]->data_ptr()),
-                *turn = static_cast<const int32_t*>(ids[2]->data_ptr());
-  const float *r = static_cast<const float*>(reward->data_ptr()), *l = loc ? static_cast<const float*>(loc->data_ptr()) : nullptr;
-  const int32_t nR = static_cast<int32_t>(R), nE = static_cast<int32_t>(n_env), nA = static_cast<int32_t>(n_agent),
-                nT = static_cast<int32_t>(n_turn), dd = static_cast<int32_t>(ddof), nm = static_cast<int32_t>(norm);
+  const at::TensorOptions f32 = reward->options(), i32 = f32.dtype(at::kInt);
+  at::Tensor out[KEYS];
   int status;
-  Py_BEGIN_ALLOW_THREADS
-  status = mixed ? reinterpret_cast<MixedFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, l, static_cast<float>(alpha),
-                                                 static_cast<float>(eps_std), dd, nm, mix, group_id, n_groups, seg, perm, adv, mean,
-                                                 std, best, ws, ws_bytes, stream)
-                 : reinterpret_cast<GroupFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, static_cast<float>(eps_std), dd, nm, group_id,
-                                                 n_groups, seg, perm, adv, mean, std, ws, ws_bytes, stream);
-  Py_END_ALLOW_THREADS
-  return status == AT_GRPO_OK ? out.take() : PyLong_FromLong(status);
+  {
+    const WithoutPythonLock others_run;
+    auto make_f = [&](Key key, int64_t n) { return static_cast<float*>((out[key] = at::empty({n}, f32)).data_ptr()); };
+    auto make_i = [&](Key key, int64_t n) { return static_cast<int32_t*>((out[key] = at::empty({n}, i32)).data_ptr()); };
+    float* mix = mixed ? make_f(REWARD, R) : nullptr;
+    int32_t* group_id = make_i(GROUP_ID, R);
+    int32_t* n_groups = make_i(N_GROUPS, 1);
+    int32_t* seg = make_i(SEG_OFFSETS, groups + 1);
+    int32_t* perm = make_i(PERM, R);
+    float* adv = make_f(ADV, R);
+    float* mean = want_stats ? make_f(MEAN, groups) : nullptr;
+    float* std = want_stats ? make_f(STD, groups) : nullptr;
+    int32_t* best = mixed && want_best ? make_i(BEST, groups) : nullptr;
+    const int32_t *env = static_cast<const int32_t*>(ids[0]->data_ptr()), *agent = static_cast<const int32_t*>(ids[1]->data_ptr()),
+                  *turn = static_cast<const int32_t*>(ids[2]->data_ptr());
+    const float *r = static_cast<const float*>(reward->data_ptr()), *l = loc ? static_cast<const float*>(loc->data_ptr()) : nullptr;
+    const int32_t nR = static_cast<int32_t>(R), nE = static_cast<int32_t>(n_env), nA = static_cast<int32_t>(n_agent),
+                  nT = static_cast<int32_t>(n_turn), dd = static_cast<int32_t>(ddof), nm = static_cast<int32_t>(norm);
+    status = mixed ? reinterpret_cast<MixedFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, l, static_cast<float>(alpha),
+                                                   static_cast<float>(eps_std), dd, nm, mix, group_id, n_groups, seg, perm, adv, mean,
+                                                   std, best, ws, ws_bytes, stream)
+                   : reinterpret_cast<GroupFn>(fn)(nR, nE, nA, nT, env, agent, turn, r, static_cast<float>(eps_std), dd, nm, group_id,
+                                                   n_groups, seg, perm, adv, mean, std, ws, ws_bytes, stream);
+  }
+  if (status != AT_GRPO_OK) return PyLong_FromLong(status);
+  THPObjectPtr dict(PyDict_New());
+  if (!dict) return nullptr;
+  for (int k = mixed ? REWARD : GROUP_ID; k < (mixed ? KEYS : BEST); ++k) {
+    THPObjectPtr o(THPVariable_Wrap(std::move(out[k])));      // None where there is no tensor
+    if (!o || PyDict_SetItem(dict.get(), g_keys[k], o.get()) != 0) return nullptr;
+  }
+  return dict.release();
   END_HANDLE_TH_ERRORS
 }
 
