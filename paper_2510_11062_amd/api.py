@@ -20,7 +20,7 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libat_grpo.so")
 _lib = None
-_binding = None             # csrc/binding.cpp, loaded with the library
+_binding = None             # csrc/binding.cpp, loaded by the first call that goes through it
 _group_fn = _mixed_fn = 0   # addresses of the library's grouping calls
 
 AGG = {"token_mean": 0, "seq_mean_token_mean": 1}
@@ -68,7 +68,7 @@ def library_path() -> str:
 
 def load_library():
     """Loads libat_grpo.so (built in-tree by paper_2510_11062_amd.build); raises if it is missing."""
-    global _lib, _binding, _group_fn, _mixed_fn
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -123,15 +123,24 @@ def load_library():
     lib.at_grpo_profile_classes.restype = i32
     lib.at_grpo_profile_read.argtypes = [i32, C.POINTER(C.c_char_p), C.POINTER(C.c_int64),
                                          C.POINTER(C.c_double)]
-    try:
-        from . import _binding as binding
-    except ImportError as e:
-        raise AtGrpoError(f"_binding.so is missing or does not load ({e}): run `python -m paper_2510_11062_amd.build`") from e
-    _group_fn = C.cast(lib.at_grpo_group_advantage, vp).value
-    _mixed_fn = C.cast(lib.at_grpo_group_advantage_mixed, vp).value
-    _binding = binding
     _lib = lib
     return lib
+
+
+def load_binding():
+    """Loads _binding.so (built in-tree with the library) for the two grouping calls that go through it; raises if it is missing or was
+    built for another torch.  Every other call does without."""
+    global _binding, _group_fn, _mixed_fn
+    if _binding is None:
+        lib = load_library()
+        try:
+            from . import _binding as binding
+        except ImportError as e:
+            raise AtGrpoError(f"_binding.so is missing or does not load ({e}): run `python -m paper_2510_11062_amd.build`") from e
+        _group_fn = C.cast(lib.at_grpo_group_advantage, C.c_void_p).value
+        _mixed_fn = C.cast(lib.at_grpo_group_advantage_mixed, C.c_void_p).value
+        _binding = binding
+    return _binding
 
 
 def _check(status: int, what: str):
@@ -256,8 +265,8 @@ def at_grpo_workspace_bytes(call: int, batch: Optional[Batch] = None, n_resp=0, 
 def at_grpo_group_advantage(env_id, agent_id, turn_id, reward, n_env: int, n_agent: int, n_turn: int,
                             eps_std: float = 1e-6, ddof: int = 0, norm: str = "std", want_stats: bool = True):
     """Returns dict(group_id, n_groups, seg_offsets, perm, adv, group_mean, group_std, workspace)."""
-    if _lib is None:
-        load_library()
+    if _binding is None:
+        load_binding()
     return _group_call("at_grpo_group_advantage", _group_fn, env_id, agent_id, turn_id, reward, None, 0.0, n_env, n_agent, n_turn,
                        eps_std, ddof, norm, want_stats, False)
 
@@ -369,8 +378,8 @@ def at_grpo_group_advantage_mixed(env_id, agent_id, turn_id, r_team, r_loc, alph
     """Eq. (3) mixing in front of at_grpo_group_advantage, plus the per-group arg max.
 
     Returns the dict of at_grpo_group_advantage extended by reward[R] and best[min(R, keys)]."""
-    if _lib is None:
-        load_library()
+    if _binding is None:
+        load_binding()
     if r_loc is None:
         raise AtGrpoError("at_grpo_group_advantage_mixed needs r_loc")
     return _group_call("at_grpo_group_advantage_mixed", _mixed_fn, env_id, agent_id, turn_id, r_team, r_loc, alpha, n_env, n_agent,

@@ -50,8 +50,10 @@ def build_binding() -> str:
     """The grouping call's host side as a CPython extension on torch's headers (csrc/binding.cpp).  It is handed the
     library's functions, so it is not linked with it."""
     import sysconfig
+    import torch
     from torch.utils import cpp_extension
     cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wno-attributes",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
            *[a for d in cpp_extension.include_paths() for a in ("-isystem", d)],
            "-isystem", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
            os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
