@@ -435,60 +435,63 @@ __device__ void surrogate_by_one(const SurrogateArgs& a, int lanes, const LossOu
 __global__ __launch_bounds__(kOneThreads) void k_surrogate_one(SurrogateArgs a, int lanes, LossOut o) { surrogate_by_one(a, lanes, o); }
 
 // One 1024-thread block per head: fixed-order sums over the n workgroups of the row kernel.  Returns the head's totals and, to every
-// head, the data errors.
+// head, the data errors.  The first NI counts and NF sums of a part: the reductions, one after the other, are most of the kernel where
+// workgroups are few (240 responses 3.1 us with four and two of them, 2.2 with the loss's two and one).
+template <int NI, int NF>
 struct FinalSums {
-  int i[4];
-  float f[2];
+  int i[NI];
+  float f[NF];
   int bad;
 };
 
-__device__ __forceinline__ FinalSums final_sums(const RowParts& p, int n) {
-  __shared__ int is[4][16], ie[16];
-  __shared__ float fs[2][16];
+template <int NI, int NF>
+__device__ __forceinline__ FinalSums<NI, NF> final_sums(const RowParts& p, int n) {
+  __shared__ int is[NI][16], ie[16];
+  __shared__ float fs[NF][16];
   const int4* ints = p.ints + static_cast<size_t>(blockIdx.x) * n;
   const float2* floats = p.floats + static_cast<size_t>(blockIdx.x) * n;
-  FinalSums s{{0, 0, 0, 0}, {0.f, 0.f}, 0};
+  FinalSums<NI, NF> s{};
 #pragma unroll 4
   for (int b = threadIdx.x; b < n; b += 1024) {
-    const int4 i = ints[b];
-    const float2 f = floats[b];
+    const int4 i4 = ints[b];
+    const float2 f2 = floats[b];
+    const int i[4] = {i4.x, i4.y, i4.z, i4.w};
+    const float f[2] = {f2.x, f2.y};
     s.bad |= p.err[b];
-    s.i[0] += i.x;
-    s.i[1] += i.y;
-    s.i[2] += i.z;
-    s.i[3] += i.w;
-    s.f[0] += f.x;
-    s.f[1] += f.y;
+#pragma unroll
+    for (int k = 0; k < NI; ++k) s.i[k] += i[k];
+#pragma unroll
+    for (int k = 0; k < NF; ++k) s.f[k] += f[k];
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < NI; ++k) {
     s.i[k] = wave_sum_int(s.i[k]);
     if (lane == 0) is[k][wave] = s.i[k];
   }
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < NF; ++k) {
     s.f[k] = wave_sum(s.f[k]);
     if (lane == 0) fs[k][wave] = s.f[k];
   }
   if (__builtin_amdgcn_ballot_w64(s.bad != 0) != 0ull) s.bad = team_reduce<64>(s.bad, ie, Or());
   if (lane == 0) ie[wave] = s.bad;
   __syncthreads();
-  s = FinalSums{{0, 0, 0, 0}, {0.f, 0.f}, 0};
+  s = FinalSums<NI, NF>{};
   if (threadIdx.x != 0) return s;
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s.i[k] += is[k][w];
+    for (int k = 0; k < NI; ++k) s.i[k] += is[k][w];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) s.f[k] += fs[k][w];
+    for (int k = 0; k < NF; ++k) s.f[k] += fs[k][w];
     s.bad |= ie[w];
   }
   return s;
 }
 
 __global__ __launch_bounds__(1024) void k_loss_final(RowParts p, int n, int agg, LossOut o) {
-  const FinalSums s = final_sums(p, n);
+  const FinalSums<2, 1> s = final_sums<2, 1>(p, n);
   if (threadIdx.x != 0) return;
   const int m = blockIdx.x;
   if (m == 0) *o.err = o.first ? s.bad : *o.err | s.bad;      // kernels in front of this one may have raised bits
@@ -564,7 +567,7 @@ __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* _
 
 __global__ __launch_bounds__(1024) void k_diag_final(RowParts p, int n, int32_t* __restrict__ counts, float* __restrict__ stats,
                                                      int32_t* __restrict__ err) {
-  const FinalSums s = final_sums(p, n);
+  const FinalSums<4, 2> s = final_sums<4, 2>(p, n);
   if (threadIdx.x != 0) return;
   const int m = blockIdx.x;
   if (m == 0) *err = s.bad;
