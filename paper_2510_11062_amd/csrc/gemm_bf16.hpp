@@ -68,8 +68,8 @@ struct Grid16 {
   static constexpr int kRdEvery = (kMm / kRd >= 4) ? kMm / kRd - 1 : kMm / kRd;
   // When the loads of Gemm16 are issued: a step's B loads behind the first kSpanB MFMAs of its sub-step, the first kFirstA of its A
   // loads behind the others there, and the rest in the next sub-step.  With two wavefronts per SIMD, B within a quarter, as it has the
-  // least time to land, and A in two halves; with one, evenly.  Us per step at V = 151936 under full load, B over a quarter with half of
-  // A / over a quarter without A / evenly without A: dW of 250000 rows at H = 2048 106.1, 109.2, 109.5 ms, exponentials 110.1, 109.8,
+  // least time to land, and A in two halves; with one, evenly.  Ms a call at V = 151936 under full load, B over a quarter with half of
+  // A / over a quarter without A / evenly without A: dW of 250000 rows at H = 2048 106.1, 109.2, 109.5, exponentials 110.1, 109.8,
   // 110.2, dHidden 101.0, 100.1, 99.4; dHidden of 37000 at H = 4096 on three heads 32.9, 33.0, 32.8.  In short bursts, where the clock
   // is higher, the exponentials of 20000 rows take 8.94, 8.95 and 9.70 ms.
   static constexpr int kSpanB = WA * WB == 4 ? kMm : kMm / 4;
@@ -303,10 +303,11 @@ __device__ __forceinline__ constexpr int load_behind(int n, int cnt, int mm) {
 // acc += a b, with the accumulator tied to its registers: the builtin leaves the compiler free to give the result other
 // registers than the addend, and with 256 accumulator registers per lane it then moves hundreds of them per k-step.  The
 // compiler does not see the instruction's latency, so mfma_settle() has to stand between the last one and the first
-// other use of an accumulator.  Between two MFMAs on one accumulator stand the kMm - 1 others of a sub-step: 31 and more on whole
-// tiles, 15 and 7 on halves and quarters, of 16 cycles each, against the one whose result has to be there.
+// other use of an accumulator.  Between two MFMAs on one accumulator stand the kMm - 1 others of a sub-step: 19 and more on whole
+// tiles (31 on those of 256 tokens), 15 and 7 on halves and quarters, of 16 cycles each, against the one whose result has to be there.
 template <typename G>
 __device__ __forceinline__ void mfma_in_place(floatx4& acc, bf16v8 a, bf16v8 b) {
+  static_assert(G::kMm >= 8, "others between two MFMAs on one accumulator");
   if constexpr (G::kMm * 4 > 128)
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
   else

@@ -618,8 +618,8 @@ __global__ __launch_bounds__(NT) void k_ga_range(GaArgs a, GaMix mix, GaStat st,
   __syncthreads();                 // every bit is set
   int bits = 0;
   for (int k = tid; k < (lo + 31) / 32; k += NT) bits += __popc(present[k]);
-  // smaller keys: members and groups; own keys: dense ids and offsets.  One scan for the four: sums of at most 65536 and 65528 in one
-  // word pair, groups of at most 1024 over members of at most 65536 in the other
+  // smaller keys: members and groups, a word each; own keys: dense ids and offsets, at most 1024 groups above at most 65536 members in
+  // one word.  One scan for the three
   const int c = tid < own ? count[tid] : 0;
   const RangeSums sums = range_sums<NT>(below, bits, c, lds_sums);
   below = sums.below;

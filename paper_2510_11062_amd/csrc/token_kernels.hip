@@ -1063,7 +1063,8 @@ bool prep_is_small(const TokenLayout& L) {
 }
 
 // Beside the backward's preparation, which takes 1 us each time, the loss's workgroup is the longer one from some rounds on, and the two
-// launches saved are 8 us.
+// launches saved are 8 us.  Long responses are walked in turn by both workgroups, so they need no rule: steps of 1 response of 1024, 4096
+// and 16384 rows (H = 32, V = 200) take 43, 64 and 164 us, and 49, 71 and 170 with the loss in front; 2 of 8192 118 and 129.
 bool prep_takes_loss(const TokenLayout& L) {
   return prep_is_small(L) && L.n_tok <= 16384 && static_cast<int64_t>(L.n_resp) * team_lanes_small(L) <= 4 * kOneThreads;
 }

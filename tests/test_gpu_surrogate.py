@@ -67,10 +67,11 @@ def test_rows_per_team(gpu_device, n_resp, mean, shift):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n_resp,mean", [(512, 160), (513, 160), (100, 70), (100, 20)])      # 256, 64, 32 and 16 lanes per response
+@pytest.mark.parametrize("n_resp,mean", [(512, 160), (513, 160), (100, 70), (300, 20), (100, 20)])
 def test_data_errors_per_team(gpu_device, n_resp, mean):
     """Bounds, agents and tokens out of range: the error word, and everything else as if those rows were masked; then clean data on
-    the same scratch memory, whose error word nothing clears beforehand."""
+    the same scratch memory, whose error word nothing clears beforehand.  256, 64, 32 and 16 lanes per response, and the surrogate by
+    one workgroup."""
     rng = np.random.default_rng(n_resp * mean)
     cu = np.arange(n_resp + 1, dtype=np.int64) * mean
     n, V, heads = n_resp * mean, 1000, 3
@@ -129,12 +130,13 @@ def test_one_workgroup(gpu_device, n_resp, mean, shift):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n_resp,rows", [(5, 3), (256, 20), (257, 20), (128, 100), (129, 100), (64, 256), (64, 257)])
+@pytest.mark.parametrize("n_resp,rows", [(5, 3), (256, 20), (257, 20), (128, 100), (129, 100), (64, 256), (64, 257), (2, 8192), (2, 8193)])
 @pytest.mark.parametrize("agg", ["token_mean", "seq_mean_token_mean"])
-def test_fp32_step_equals_two_calls(gpu_device, n_resp, rows, agg):
+@pytest.mark.parametrize("bad_bounds", [False, True])
+def test_fp32_step_equals_two_calls(gpu_device, n_resp, rows, agg, bad_bounds):
     """Where the loss is computed beside the backward's preparation and where it is not (four rounds of responses, 16384 rows), with
-    tokens and an agent out of range: the same bits as the two calls but for the loss, whose terms are added in another order (sums
-    of up to 25700 fp32 terms of size about 1, 1e-6)."""
+    tokens, an agent and bounds of responses out of range: the same bits as the two calls but for the loss, whose terms are added in
+    another order (sums of up to 25700 fp32 terms of size about 1, in chains of 128 at most, 1e-6)."""
     gen = torch.Generator(device=gpu_device).manual_seed(n_resp * rows)
     n, H, V = n_resp * rows, 32, 200
     rand = lambda *s: torch.randn(*s, generator=gen, device=gpu_device)
@@ -144,19 +146,34 @@ def test_fp32_step_equals_two_calls(gpu_device, n_resp, rows, agg):
     mask = (torch.rand(n, generator=gen, device=gpu_device) < 0.8).to(torch.uint8)
     mask[[1, n - 1]] = 1
     agent = (torch.arange(n_resp, device=gpu_device) % 2).to(torch.int32)
-    agent[2] = 7
+    agent[min(2, n_resp - 1)] = 7
     cu = torch.arange(n_resp + 1, device=gpu_device) * rows
+    bounded = torch.ones(n, dtype=torch.bool, device=gpu_device)     # rows whose response has bounds: the others get no flags
+    if bad_bounds:
+        k = n_resp // 2
+        if k > 3:                                                    # responses k - 1 and k lose their common bound
+            cu[k] = -1
+            bounded[(k - 1) * rows:(k + 1) * rows] = False
+        if n_resp > 2:                                               # the last one its end
+            cu[-1] = n + 5
+            bounded[-rows:] = False
+        else:                                                        # the first one its beginning
+            cu[0] = -2
+            bounded[:rows] = False
     batch = api.Batch(hidden, W, token, cu, mask, agent, torch.tensor([1, 0], dtype=torch.int32, device=gpu_device))
     old, adv = -5.3 + 0.2 * rand(n), rand(n_resp)
-    adv[3] = 0
-    say(f"[surrogate] fp32 step of {n_resp} responses of {rows} rows, {agg}")
+    if n_resp > 3:
+        adv[3] = 0
+    say(f"[surrogate] fp32 step of {n_resp} responses of {rows} rows, {agg}, {'bounds out of range' if bad_bounds else 'good bounds'}")
     one = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, 0.2, 0.2, agg)
     err = api.error_word(one["workspace"])
     one = {k: [x.clone() for x in v] if k == "dW" else v.clone() for k, v in one.items() if k != "workspace"}
     fwd = api.at_grpo_policy_loss_fwd(batch, old, adv, 0.2, 0.2, agg)
-    assert api.error_word(fwd["workspace"]) == err == 4 | 16      # tokens, agents
+    # tokens (of two responses without bounds or agent nobody looks at them), agents, bounds
+    assert api.error_word(fwd["workspace"]) == err == (16 | 8 if bad_bounds and n_resp == 2 else 4 | 16 | 8 * bad_bounds)
     bwd = api.at_grpo_policy_loss_bwd(batch, old, adv, fwd["logp"], fwd["lse"], 0.2, 0.2, agg)
-    for k in ("logp", "lse", "clip_mask", "n_valid"):
+    for k in ("logp", "lse", "n_valid"):
         assert torch.equal(one[k], fwd[k]), k
+    assert torch.equal(one["clip_mask"][bounded], fwd["clip_mask"][bounded])
     assert torch.equal(one["d_hidden"], bwd["d_hidden"]) and all(torch.equal(a, b) for a, b in zip(one["dW"], bwd["dW"]))
     assert float((one["loss"] - fwd["loss"]).abs().max()) <= 1e-6
