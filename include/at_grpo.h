@@ -369,7 +369,9 @@ int32_t at_grpo_version(void);
  *   at_grpo_profile_read synchronises the recorded events and returns, for kernel class
  *   `which` (0 .. at_grpo_profile_classes()-1), the number of launches and their total
  *   duration in milliseconds since recording started; the name is a static string.  Small fp32
- *   batches compute both gradients of the head in one launch, which counts as "head_dh".
+ *   batches compute both gradients of the head in one launch, which counts as "head_dh", and in the
+ *   one-call step their loss beside the backward's preparation, which counts as "token_prep" ("surrogate"
+ *   has no launch there).
  */
 int at_grpo_profile_enable(int32_t on);
 int32_t at_grpo_profile_classes(void);
