@@ -158,8 +158,8 @@ __global__ __launch_bounds__(256) void k_resp_cnt(TokenLayout L, const int32_t* 
 }
 
 // Rows lo .. hi of a response, read by a team of LPR lanes (256, 64, 32 or 16, chosen from the mean response length) in aligned
-// 4-row vectors.  each(logp, old_logp) is called for every participating row, in ascending order within a lane, and returns
-// the row's clip flags, which are stored when clip_mask is given.  One vector of each input per lane and round: with two
+// 4-row vectors.  each(place in the vector, logp, old_logp) is called for every participating row, in ascending order within a lane,
+// and returns the row's clip flags, which are stored when clip_mask is given.  One vector of each input per lane and round: with two
 // requested ahead, many rows take longer (28 million rows in responses of about 289, 32 lanes: 105 us, 99 with one), and few
 // are bound by launches either way.
 
@@ -219,7 +219,7 @@ __device__ __forceinline__ void each_row(const TokenLayout& L, const float* __re
         on = false;
       }
     }
-    const int bits = on ? each(logp[t], old_logp[t]) : 0;
+    const int bits = on ? each(0, logp[t], old_logp[t]) : 0;
     if (clip_mask) clip_mask[t] = static_cast<uint8_t>(bits);
   };
   for (int64_t u = (lo >> 2) + lane; (u << 2) < hi; u += LPR) {
@@ -242,7 +242,7 @@ __device__ __forceinline__ void each_row(const TokenLayout& L, const float* __re
           *bad |= AT_GRPO_DATA_TOKEN_RANGE;
           on = false;
         }
-        if (on) out |= static_cast<uint32_t>(each(lp[e], ol[e])) << (8 * e);
+        if (on) out |= static_cast<uint32_t>(each(e, lp[e], ol[e])) << (8 * e);
       }
       if (clip_mask) {
         if (interior) {
@@ -273,7 +273,8 @@ struct SurrogateArgs {
 // the response's sum of surrogate terms and its count of participating rows are reduced in a fixed order.  Needs no per-row
 // routing arrays: the advantage and the head are per-response scalars, requested together with its bounds (6228 responses 12.9 ->
 // 12.4 us, 768 8.4 -> 7.0, 24576 short ones 10.2 -> 8.5, the monitors as much).  `word`: head and errors.
-template <int LPR>
+// SUMS (1 or 4): sums that a lane keeps, by the rows' place in their vector.
+template <int LPR, int SUMS>
 __device__ __forceinline__ void surrogate_response(const SurrogateArgs& a, int r, int lane, float* lds_f, int* lds_i, float* total,
                                                    int* rows, int* word) {
   const TokenLayout& L = a.L;
@@ -285,15 +286,16 @@ __device__ __forceinline__ void surrogate_response(const SurrogateArgs& a, int r
   *rows = 0;
   *word = kNoHead | AT_GRPO_DATA_SEQLENS << kErrShift;
   if (lo < 0 || hi < lo || hi > L.n_tok) return;
-  float sum = 0.f;
+  float part[SUMS] = {};
   int cnt = 0;
-  each_row<LPR>(L, a.logp, a.old_logp, lo, hi, head, lane, a.clip_mask, &bad, [&](float lp, float ol) {
+  each_row<LPR>(L, a.logp, a.old_logp, lo, hi, head, lane, a.clip_mask, &bad, [&](int e, float lp, float ol) {
     int bits;
     float ratio;
-    sum += surrogate_term(lp, ol, A, a.cc, &bits, &ratio);
+    part[e % SUMS] += surrogate_term(lp, ol, A, a.cc, &bits, &ratio);
     ++cnt;
     return bits;
   });
+  float sum = SUMS == 1 ? part[0] : (part[0] + part[SUMS / 4]) + (part[SUMS / 2] + part[SUMS - 1]);
   // rows owned by no response (before the first / after the last range) carry no flags
   if (a.clip_mask && r == 0)
     for (int64_t t = lane; t < lo; t += LPR) a.clip_mask[t] = 0;
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(256) void k_surrogate_resp(SurrogateArgs a, RowPart
   for (int r = team; r < a.L.n_resp; r += n_teams) {
     float total;
     int rows, word;
-    surrogate_response<LPR>(a, r, lane, lds_f, lds_i, &total, &rows, &word);
+    surrogate_response<LPR, 1>(a, r, lane, lds_f, lds_i, &total, &rows, &word);
     if (lane == 0) {
       const int m = word & kNoHead;
       if (m != kNoHead) {
@@ -388,13 +390,13 @@ struct LossOut {
   int first;
 };
 
-template <int LPR>
+template <int LPR, int SUMS>
 __device__ __forceinline__ void each_response(const SurrogateArgs& a, float* sums, int* rows, int* words) {
   const int lane = threadIdx.x & (LPR - 1);
   for (int r = threadIdx.x / LPR; r < a.L.n_resp; r += kOneThreads / LPR) {
     float total;
     int n, word;
-    surrogate_response<LPR>(a, r, lane, nullptr, nullptr, &total, &n, &word);
+    surrogate_response<LPR, SUMS>(a, r, lane, nullptr, nullptr, &total, &n, &word);
     if (lane == 0) {
       sums[r] = total;
       rows[r] = n;
@@ -403,13 +405,21 @@ __device__ __forceinline__ void each_response(const SurrogateArgs& a, float* sum
   }
 }
 
+// A lane of 64 takes four times the rows that it takes where a workgroup shares a long response.  Past kOneChain rows a lane four sums
+// (LONG: there may be such batches) keep its chains of additions as short: loss of one response of 16384 rows against 64 bits, root mean
+// square of 400 such, 6.7e-8 with one sum a lane, 4.1e-8 with four, 4.4e-8 by a workgroup.  Up to there the three are equal (two
+// responses of 8192 rows 3.6e-8, 3.3e-8 and 3.7e-8, one of 4096 4.2e-8, 4.0e-8 and 4.5e-8).
+constexpr int kOneChain = 128;
+
+template <bool LONG>
 __device__ void surrogate_by_one(const SurrogateArgs& a, int lanes, const LossOut& o) {
   __shared__ float sums[kOneResp];
   __shared__ int rows[kOneResp], words[kOneResp];
   static_assert(kOneThreads / 64 >= kMaxHeads, "a wavefront per head");
-  if (lanes == 64) each_response<64>(a, sums, rows, words);
-  else if (lanes == 32) each_response<32>(a, sums, rows, words);
-  else each_response<16>(a, sums, rows, words);
+  if (LONG && lanes == 64 && a.L.n_tok > 64 * kOneChain) each_response<64, 4>(a, sums, rows, words);
+  else if (lanes == 64) each_response<64, 1>(a, sums, rows, words);
+  else if (lanes == 32) each_response<32, 1>(a, sums, rows, words);
+  else each_response<16, 1>(a, sums, rows, words);
   __syncthreads();
   const int m = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (m >= a.L.n_heads) return;
@@ -432,7 +442,9 @@ __device__ void surrogate_by_one(const SurrogateArgs& a, int lanes, const LossOu
   if (o.n_valid) o.n_valid[m] = n;
 }
 
-__global__ __launch_bounds__(kOneThreads) void k_surrogate_one(SurrogateArgs a, int lanes, LossOut o) { surrogate_by_one(a, lanes, o); }
+__global__ __launch_bounds__(kOneThreads) void k_surrogate_one(SurrogateArgs a, int lanes, LossOut o) {
+  surrogate_by_one<false>(a, lanes, o);
+}
 
 // One 1024-thread block per head: fixed-order sums over the n workgroups of the row kernel.  Returns the head's totals and, to every
 // head, the data errors.  The first NI counts and NF sums of a part: the reductions, one after the other, are most of the kernel where
@@ -523,7 +535,7 @@ __global__ __launch_bounds__(256) void k_diag_resp(TokenLayout L, const float* _
       head = -1;
       bad = AT_GRPO_DATA_SEQLENS;
     } else {
-      each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, nullptr, &bad, [&](float lp, float ol) {
+      each_row<LPR>(L, logp, old_logp, lo, hi, head, lane, nullptr, &bad, [&](int, float lp, float ol) {
         const float d = lp - ol;
         const bool is_low = d < cc.lo, is_high = d > cc.hi;
         ++n;
@@ -851,7 +863,7 @@ __global__ __launch_bounds__(kPsThreads) void k_prep_small(PrepArgs a) {
 // and the loss by another (which raises no error bits: the first one meets the same data).
 __global__ __launch_bounds__(kPsThreads) void k_prep_backward_loss(PrepArgs a, SurrogateArgs sa, LossOut o) {
   if (blockIdx.x == 0) prep_small<PREP_BACKWARD>(a);
-  else surrogate_by_one(sa, a.lanes, o);
+  else surrogate_by_one<true>(sa, a.lanes, o);
 }
 
 unsigned grid_for(int64_t n, int per_block, int64_t cap = 1 << 20) {
@@ -876,6 +888,7 @@ constexpr int kWideTeams = 512;
 // events around it: 50 responses of 20 rows 8.3 and 10.2, 100 10.0 and 11.5, 200 14.7 and 10.3; 40 of 87 9.8 and 10.4, 80 of 89 13.2 and
 // 11.2; 13 of 262 9.3 and 10.9, 27 of 256 12.1 and 10.5.
 bool surrogate_is_small(const TokenLayout& L) {
+  static_assert(4096 <= 64 * kOneChain, "surrogate_by_one<false>");
   return L.n_tok <= 4096 && L.n_tok <= static_cast<int64_t>(L.n_resp) * 1024 &&
          static_cast<int64_t>(L.n_resp) * team_lanes_small(L) <= 2 * kOneThreads;
 }

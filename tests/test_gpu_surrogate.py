@@ -177,3 +177,29 @@ def test_fp32_step_equals_two_calls(gpu_device, n_resp, rows, agg, bad_bounds):
     assert torch.equal(one["clip_mask"][bounded], fwd["clip_mask"][bounded])
     assert torch.equal(one["d_hidden"], bwd["d_hidden"]) and all(torch.equal(a, b) for a, b in zip(one["dW"], bwd["dW"]))
     assert float((one["loss"] - fwd["loss"]).abs().max()) <= 1e-6
+
+
+@pytest.mark.gpu
+def test_loss_of_one_long_response_against_64_bits(gpu_device):
+    """A step of one response of 16384 rows, whose loss one wavefront of the merged kernel adds up, 200 times.  What every order of
+    addition shares (log-ratio and exp in fp32, the last sums, the division) comes to 4.2e-8 root mean square of the loss.  A chain of
+    n additions in each of k lanes adds 2^-24 / sqrt(3) * sqrt(n / 3 / k): 1e-8 for the 64 of 256 sums, 4e-8 for the 256 of 64 sums."""
+    n, H, V = 16384, 32, 200
+    gen = torch.Generator(device=gpu_device).manual_seed(5)
+    rand = lambda *s: torch.randn(*s, generator=gen, device=gpu_device)
+    token = torch.randint(0, V, (n,), generator=gen, device=gpu_device, dtype=torch.int32)
+    batch = api.Batch(rand(n, H), [rand(V, H) * 0.1], token, torch.tensor([0, n], device=gpu_device))
+    logp = api.at_grpo_token_logprob(batch)["logp"]
+    say("[surrogate] loss of one response of 16384 rows")
+    lo, hi = np.float32(np.log1p(-0.2)), np.float32(np.log1p(0.2))
+    errors = []
+    for _ in range(200):
+        old, adv = logp + 0.1 * rand(n), rand(1)
+        out = api.at_grpo_policy_loss_fwd_bwd(batch, old, adv, 0.2, 0.2)
+        d, A = out["logp"] - old, float(adv)                        # clipped or not is decided on the fp32 difference
+        ratio = torch.exp(d.double())
+        clipped = torch.where(d < float(lo), 0.8, torch.where(d > float(hi), 1.2, ratio))
+        loss = -float(torch.minimum(ratio * A, clipped * A).mean())
+        errors.append((float(out["loss"][0]) - loss) / loss)
+    rms = float(np.sqrt(np.mean(np.square(errors))))
+    assert rms < 5.2e-8, rms
