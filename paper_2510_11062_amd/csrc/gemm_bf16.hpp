@@ -329,7 +329,7 @@ __device__ __forceinline__ void mfma_settle(floatx4 (&acc)[G::kIB][G::kJB]) {
 // 3 + kt % 2.  What step kt leaves free at its barrier is requested again from there on, B of step kt+2 first: it has up to a whole
 // step to land, A of step kt+3 up to two (the A panels are the weights, the B panels what more workgroups share).  With both
 // operands taking turns in the five slots (A of step kt+2 requested in front of that barrier, B behind it) steps of 20000 rows took
-// 27.8 ms at H = 2048 and 54.8 at H = 4096, now 26.1 and 51.8, and log-probabilities of 300 rows 235 -> 228 and 432 -> 411 us, of 8192
+// 27.8 ms at H = 2048 and 54.8 at H = 4096, now 26.1 and 51.8, and log-probabilities of 300 rows 235 -> 224 and 432 -> 405 us, of 8192
 // rows 3670 -> 3560.  Where the launches go on for long, power is the bound and the gain smaller: 250000 rows 329 -> 325 ms,
 // 37000 at H = 4096 on three heads 99.9 -> 98.4.  (Three slots for dW's B, the rows of dZ, instead: dW of 20000 rows 8.6 -> 9.0 ms.)
 // Per k-step:
